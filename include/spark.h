@@ -121,10 +121,11 @@ typedef struct spark_ctx spark_ctx;
  * What has to be kept follows from Sec. IV-B.3: the KV cache of all L layers for every position,
  * and the hidden states h^(e) of the early-exited positions until the next full-depth step; on
  * memory management itself the paper is silent.  For bf16 models whose widths are multiples of 8
- * the scratch size also has room for a second copy of the projection and head matrices, laid out
- * in the order the matrix units consume them, which the context writes when it is created and
- * which the projections of five and more rows read instead of the caller's tensors (as many bytes
- * again as those matrices).  cfg [host]; the two sizes are written to kv_pool_bytes /
+ * the scratch size also has room for a second copy of the projection and head matrices, as fp16
+ * scaled by powers of two and laid out in the order the matrix units consume them, which the
+ * context writes when it is created and which the projections of five and more rows read instead
+ * of the caller's tensors (as many bytes again as those matrices), and behind it for the buffers
+ * of prompt passes of 1024 rows.  A smaller area does without the latter, or without both.  cfg [host]; the two sizes are written to kv_pool_bytes /
  * scratch_bytes [host] (either may be NULL).
  * Returns SPARK_EINVAL for a configuration the library refuses. */
 int spark_workspace_bytes(const spark_config *cfg, size_t *kv_pool_bytes, size_t *scratch_bytes);
@@ -301,8 +302,11 @@ int spark_measure_read(spark_ctx *ctx, const void *buf, size_t bytes, int32_t re
  *   "attn_pieces" (64-token pieces per attention workgroup, 0 = by the size of the launch, at most
  *   8), "attn_mfma_min_rows", "gemv_big_kb", "mfma_tiled" (0: the MFMA projections stage the
  *   caller's weight rows through LDS instead of reading the context's copy in operand order),
- *   "mfma_small_max_k", "fuse_norm" (0: every RMSNorm of the batched path is its own launch),
- *   "prefill_rows" (prompt rows per pass, a multiple of 32, at most 256).
+ *   "mfma_small_max_k", "direct_max_rows" (rows up to which they do without LDS, at most 32),
+ *   "direct_whole_k" (the longest input width whose few tasks those never cut over workgroups),
+ *   "tiled_row_blocks" (blocks of 32 rows in a row tile of the others, 2..4), "fuse_norm" (0: every
+ *   RMSNorm of the batched path is its own launch), "prefill_rows" (prompt rows per pass, a
+ *   multiple of 32, at most 256; unset, passes of up to 1024 rows where the scratch area has room).
  * SPARK_EINVAL for an unknown name. */
 int spark_tune(spark_ctx *ctx, const char *name, int32_t value);
 

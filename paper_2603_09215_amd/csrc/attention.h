@@ -45,8 +45,8 @@ template <int HD, int G, int NT> constexpr int attn_lds_floats() {
 template <int HD, int NT, bool DS>
 __device__ __forceinline__ void attn_merge(const RowDesc &rd, int r, int hq0, int g_count, int nq,
                                            int n_splits, int slice_tokens, const float *__restrict__ part,
-                                           int *__restrict__ cnt, float *__restrict__ out,
-                                           const SplitOut &so, int *s_last) {
+                                           int *__restrict__ cnt, const RowOut &out,
+                                           const RowMax &row_max, int *s_last) {
   constexpr int PS = HD + 4;
   const int tid = threadIdx.x % NT;
   // Partials are written through to memory (device-scope stores) and counted with a device-scope
@@ -67,6 +67,7 @@ __device__ __forceinline__ void attn_merge(const RowDesc &rd, int r, int hq0, in
 
   // every thread merges four output elements of one head over all slices in one pass (running
   // maximum, rescaled sums), eight slices' loads in flight at a time
+  uint32_t big = 0u;
   for (int i = tid; i < g_count * (HD / 4); i += NT) {
     const int g = i / (HD / 4), c = (i - g * (HD / 4)) * 4;
     const float *p = part + (size_t)(r * nq + hq0 + g) * n_splits * PS;
@@ -94,12 +95,18 @@ __device__ __forceinline__ void attn_merge(const RowDesc &rd, int r, int hq0, in
       }
     }
     const float inv = 1.0f / L;
-    float *dst = out + (size_t)r * nq * HD + (hq0 + g) * HD + c;
+    float *dst = out.at(r, (hq0 + g) * HD + c);
     store2_maybe_ds<DS>(dst, make_float2(acc4.x * inv, acc4.y * inv));
     store2_maybe_ds<DS>(dst + 2, make_float2(acc4.z * inv, acc4.w * inv));
-    // for the MFMA output projection: the same values as three bf16 parts
-    if (so.xs)
-      split_store4(so, r, (hq0 + g) * HD + c, make_float4(acc4.x * inv, acc4.y * inv, acc4.z * inv, acc4.w * inv));
+    const uint32_t m01 = max(magnitude_bits(acc4.x * inv), magnitude_bits(acc4.y * inv));
+    const uint32_t m23 = max(magnitude_bits(acc4.z * inv), magnitude_bits(acc4.w * inv));
+    big = max(big, max(m01, m23));
+  }
+  // for the MFMA output projection: the largest magnitude of what each wave has written of the row
+  if (row_max.list) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) big = max(big, (uint32_t)__shfl_xor((int)big, o, 64));
+    if ((tid & 63) == 0) row_max.put(r, blockIdx.y * (NT / 64) + tid / 64, big);
   }
   if (DS) wait_memory_ops();   // the caller's next barrier arrival does not wait for these stores
 }
@@ -113,7 +120,7 @@ __device__ __forceinline__ void attn_task(const RowDesc &rd, int r, int hk, int 
                                           int split, const float *__restrict__ qbuf, const KVView &kv,
                                           int layer, int nq, int n_splits, float scale,
                                           float *__restrict__ part, int *__restrict__ cnt,
-                                          float *__restrict__ out, const SplitOut &so, float *lds) {
+                                          const RowOut &out, const RowMax &row_max, float *lds) {
   constexpr int VEC = Elem<KT>::VEC;
   constexpr int LPT = HD / VEC;                   // lanes per token
   constexpr int TPI = NT / LPT;                   // tokens per iteration of the workgroup
@@ -230,7 +237,7 @@ __device__ __forceinline__ void attn_task(const RowDesc &rd, int r, int hk, int 
     store_device_scope(part + ((size_t)(r * nq + hq0 + g) * n_splits + split) * PS + HD + w,
                        ml[g * 2 + w]);
   }
-  attn_merge<HD, NT, DS>(rd, r, hq0, g_count, nq, n_splits, ATTN_SLICE, part, cnt, out, so, s_last);
+  attn_merge<HD, NT, DS>(rd, r, hq0, g_count, nq, n_splits, ATTN_SLICE, part, cnt, out, row_max, s_last);
 }
 
 // stand-alone launch: one workgroup per (slice, group of G query heads, row).  A KV head's `group`
@@ -240,7 +247,7 @@ template <typename KT, int HD, int G>
 __global__ void __launch_bounds__(ATTN_THREADS)
 attn_rows_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbuf, KVView kv,
             int layer, int nq, int group, int n_splits, float scale, float *__restrict__ part,
-            int *__restrict__ arrivals, float *__restrict__ out, SplitOut so) {
+            int *__restrict__ arrivals, RowOut out, RowMax row_max) {
   __shared__ float lds[attn_lds_floats<HD, G, ATTN_THREADS>()];
   const int n_groups = (group + G - 1) / G;
   const int split = blockIdx.x, hk = blockIdx.y / n_groups, gi = blockIdx.y - hk * n_groups, r = blockIdx.z;
@@ -248,7 +255,7 @@ attn_rows_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbuf, KV
   if (split * ATTN_SLICE > rd.pos) return;        // slice beyond the row's context
   attn_task<KT, HD, G, ATTN_THREADS, false>(rd, r, hk, hk * group + gi * G, min(G, group - gi * G), split,
                                             qbuf, kv, layer, nq, n_splits, scale, part,
-                                            arrivals + r * gridDim.y + blockIdx.y, out, so, lds);
+                                            arrivals + r * gridDim.y + blockIdx.y, out, row_max, lds);
 }
 
 // ------------------------------------------------------------------ the same task on the MFMA units
@@ -311,7 +318,7 @@ template <int HD>
 __global__ void __launch_bounds__(ATTN_THREADS)
 attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbuf, KVView kv, int layer,
                  int nq, int kv_group, int heads_per_wg, int n_splits, int pieces, float scale,
-                 float *__restrict__ part, int *__restrict__ arrivals, float *__restrict__ out, SplitOut so) {
+                 float *__restrict__ part, int *__restrict__ arrivals, RowOut out, RowMax row_max) {
   static_assert(HD == 128, "four 32-wide steps per key row, four waves of 32 value columns");
   constexpr int PS = HD + 4;
   __shared__ __align__(16) bf16_t s_v[ATTN_SLICE * AM_VPITCH];
@@ -490,7 +497,7 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
     store_device_scope(part + ((size_t)(r * nq + hq0 + g) * n_splits + split) * PS + HD + (tid & 1), v);
   }
   attn_merge<HD, ATTN_THREADS, false>(rd, r, hq0, group, nq, n_splits, span, part,
-                                      arrivals + r * gridDim.y + blockIdx.y, out, so, &s_last);
+                                      arrivals + r * gridDim.y + blockIdx.y, out, row_max, &s_last);
 }
 
 }  // namespace spark

@@ -66,8 +66,8 @@ template <> struct Elem<bf16_t> {
   }
 };
 
-// x = hi + mid + lo exactly, each part a bf16 (3 x 8 mantissa bits cover the 24 of an fp32): the
-// form in which activations meet bf16 weights on the MFMA units without losing fp32 accuracy
+// x = hi + mid + lo exactly, each part a bf16 (3 x 8 mantissa bits cover the 24 of an fp32): how
+// activations meet the caller's bf16 weights on the MFMA units without losing fp32 accuracy
 __device__ __forceinline__ void split3_bf16(float x, bf16_t &hi, bf16_t &mid, bf16_t &lo) {
   hi = f32_to_bf16(x);
   const float rem = x - bf16_to_f32(hi);      // exact
@@ -75,60 +75,44 @@ __device__ __forceinline__ void split3_bf16(float x, bf16_t &hi, bf16_t &mid, bf
   lo = f32_to_bf16(rem - bf16_to_f32(mid));   // the exact remainder has at most 8 bits left
 }
 
-// Where the three parts of pass row r's activations go for the MFMA kernels: part p of element k at
-// xs[p * part_stride + r * row_stride + k]; rows are zero beyond the `width` real elements.
-struct SplitOut {
-  bf16_t *xs;            // nullptr: not wanted
-  size_t part_stride;
-  int row_stride, width;
+// The other split, for the copy of the weights that the library keeps as fp16: x * 2^n = hi + lo
+// with two fp16 parts (11 bits each, the remainder's sign is one more), where 2^n brings the
+// largest magnitude of the row just below 2^15.  What is left out is at most 2^-23 of an element,
+// or 2^-40 of the row's largest for elements far below it: the size of an fp32 rounding.
+// The power of two comes from the largest magnitude's exponent alone, as a biased exponent E
+// (2^(E - 127)), kept so that 2^(127 - E) is a normal number too.
+__device__ __forceinline__ int scale_exponent(int e) { return min(max(268 - e, 14), 240); }   // e: largest biased fp32 exponent
+__device__ __forceinline__ float scale_up(int E) { return __uint_as_float((uint32_t)E << 23); }
+__device__ __forceinline__ float scale_down(int E) { return __uint_as_float((uint32_t)(254 - E) << 23); }
+
+// What the launches of a pass hand each other about a row of its activations.
+// The sum of squares of its hidden state, fixed point, so that the order of the additions does not
+// matter: SSQ_WAYS words per row, so that few atomics meet at one address (56 workgroups on one
+// word took 5 us to drain); a reader adds them up.
+constexpr int SSQ_WAYS = 8;
+// The largest magnitude of the row that the next projection reads, as far as a power of two needs
+// it: a list of fp32 exponents, one byte from each part of the launches that produce the row, each
+// written with a plain store; a reader takes the largest.  (Gathered with atomics instead, the 592
+// finishing workgroups of an MLP of 18944 took 14 us for 32 rows and 31 us for 64: atomics on one
+// cache line drain one after the other.  With the list they take 7 and 11 us.)
+struct RowMax {
+  uint8_t *list;    // [row][stride]; nullptr: not wanted
+  int stride, n;    // bytes from row to row (a multiple of 16), bytes in use
+  __device__ __forceinline__ void put(int r, int i, uint32_t magnitude) const {
+    list[(size_t)r * stride + i] = (uint8_t)(magnitude >> 23);
+  }
 };
-
-// four consecutive elements k..k+3 (k a multiple of 4) of row r; the thread that writes the row's
-// last elements also clears its padding
-__device__ __forceinline__ void split_store4(const SplitOut &so, int r, int k, float4 v) {
-  const float f[4] = {v.x, v.y, v.z, v.w};
-  bf16_t h[4], m[4], l[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) split3_bf16(f[e], h[e], m[e], l[e]);
-  bf16_t *dst = so.xs + (size_t)r * so.row_stride + k;
-  *(uint2 *)dst = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
-  *(uint2 *)(dst + so.part_stride) = make_uint2(m[0] | ((uint32_t)m[1] << 16), m[2] | ((uint32_t)m[3] << 16));
-  *(uint2 *)(dst + 2 * so.part_stride) = make_uint2(l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16));
-  if (k + 4 >= so.width)
-    for (int z = so.width; z < so.row_stride; z += 4)
-#pragma unroll
-      for (int p = 0; p < 3; ++p)
-        *(uint2 *)(so.xs + p * so.part_stride + (size_t)r * so.row_stride + z) = make_uint2(0, 0);
-}
-
-// two consecutive elements k, k+1 (k even) of row r
-__device__ __forceinline__ void split_store2(const SplitOut &so, int r, int k, float v0, float v1) {
-  bf16_t h0, m0, l0, h1, m1, l1;
-  split3_bf16(v0, h0, m0, l0);
-  split3_bf16(v1, h1, m1, l1);
-  bf16_t *dst = so.xs + (size_t)r * so.row_stride + k;
-  *(uint32_t *)dst = h0 | ((uint32_t)h1 << 16);
-  *(uint32_t *)(dst + so.part_stride) = m0 | ((uint32_t)m1 << 16);
-  *(uint32_t *)(dst + 2 * so.part_stride) = l0 | ((uint32_t)l1 << 16);
-  if (k + 2 >= so.width)
-    for (int z = so.width; z < so.row_stride; z += 2)
-#pragma unroll
-      for (int p = 0; p < 3; ++p) *(uint32_t *)(so.xs + p * so.part_stride + (size_t)r * so.row_stride + z) = 0u;
-}
-
-// one element
-__device__ __forceinline__ void split_store1(const SplitOut &so, int r, int k, float v) {
-  bf16_t h, m, l;
-  split3_bf16(v, h, m, l);
-  bf16_t *dst = so.xs + (size_t)r * so.row_stride + k;
-  dst[0] = h;
-  dst[so.part_stride] = m;
-  dst[2 * so.part_stride] = l;
-  if (k + 1 >= so.width)
-    for (int z = so.width; z < so.row_stride; ++z)
-#pragma unroll
-      for (int p = 0; p < 3; ++p) so.xs[p * so.part_stride + (size_t)r * so.row_stride + z] = 0;
-}
+// Where the rows of a pass go that a projection will read: row-major, or for a pass of at most 32
+// rows in the order the projection's matrix operand wants them, [k / 4][32 rows][4].
+constexpr int OP_ROWS = 32;
+struct RowOut {
+  float *p;
+  int stride;       // elements from row to row; 0: operand order
+  __device__ __forceinline__ float *at(int r, int k) const {   // k..k|3 are neighbours in both
+    return p + (stride ? (size_t)r * stride + k : (size_t)(k >> 2) * (4 * OP_ROWS) + r * 4 + (k & 3));
+  }
+};
+__device__ __forceinline__ uint32_t magnitude_bits(float x) { return __float_as_uint(x) & 0x7fffffffu; }
 
 // Data handed from one workgroup to another inside a kernel goes through device-scope relaxed
 // atomic accesses: they are served at the level where all XCDs agree, so neither side has to

@@ -182,15 +182,12 @@ struct ProNorm {
 struct NoState {};
 
 // RMSNorm is linear in 1/rms: a projection of gamma (.) h can be scaled by 1/rms(h) afterwards.
-// The launch that produces h (a residual projection's finishing step) then also writes the split
-// gamma (.) h and adds the row's sum of squares, as a fixed-point integer so that the order of
-// the additions does not matter, into one word per row; the next projection's epilogue reads it.
+// The launch that produces h (a residual projection's finishing step) then also writes gamma (.) h
+// and adds the row's sum of squares, as a fixed-point integer so that the order of the additions
+// does not matter, to the row's words; the next projection's epilogue reads them.
 constexpr float SSQ_SCALE = 16777216.0f;   // 2^24: sums of squares up to 1e12 fit 64 bits
-// words per row: the workgroups of the finishing launch add to word (workgroup % SSQ_WAYS) of the
-// row, so that few atomics meet at one address (56 workgroups on one word took 5 us to drain)
-constexpr int SSQ_WAYS = 8;
 struct RowScale {
-  const unsigned long long *ssq;   // [pass row][SSQ_WAYS] fixed-point sums of squares, nullptr: rows are normalised already
+  const unsigned long long *ssq;   // [pass row][SSQ_WAYS], nullptr: rows are normalised already
   float inv_d, eps;
   __device__ __forceinline__ float of(int r) const {
     if (!ssq) return 1.0f;
@@ -225,25 +222,36 @@ template <typename WT, bool DS = false> struct EpiQKV {
     r0 = base + (size_t)(h * hd + i) * d;
     r1 = r0 + (size_t)half * d;
   }
-  __device__ void finish(int task, int r, const RowDesc &rd, float y0, float y1, State &) const {
-    int half = hd >> 1, head = task / half, i = task - head * half;
-    if (scale.ssq) { const float inv = scale.of(r); y0 *= inv; y1 *= inv; }
+  // what a pair needs besides its sums: the row's scale, the rotation and the cache entry's place
+  struct Old { float inv; float2 cs; size_t at; };
+  __device__ Old load_old(int task, int r, const RowDesc &rd) const {
+    const int half = hd >> 1, head = task / half, i = task - head * half;
+    Old o;
+    o.inv = scale.of(r);
+    o.cs = head < nq + nkv ? rope[(size_t)rd.pos * half + i] : make_float2(1.f, 0.f);
+    const int which = head < nq + nkv ? 0 : 1;
+    o.at = head < nq ? (size_t)r * nq * hd + head * hd + i
+                     : kv_elem_offset(kv, rd.seq, rd.pos, layer, which, head - nq - which * nkv) + i;
+    return o;
+  }
+  __device__ void finish_old(int task, int, const RowDesc &, float y0, float y1, const Old &o, State &) const {
+    const int half = hd >> 1, head = task / half;
+    if (scale.ssq) { y0 *= o.inv; y1 *= o.inv; }
     if (head < nq + nkv) {
-      float2 cs = rope[(size_t)rd.pos * half + i];
-      float a = y0 * cs.x - y1 * cs.y, b = y1 * cs.x + y0 * cs.y;
+      const float a = y0 * o.cs.x - y1 * o.cs.y, b = y1 * o.cs.x + y0 * o.cs.y;
       y0 = a; y1 = b;
     }
     if (head < nq) {
-      float *q = qbuf + (size_t)r * nq * hd + head * hd + i;
-      store_maybe_ds<DS>(q, y0);
-      store_maybe_ds<DS>(q + half, y1);
+      store_maybe_ds<DS>(qbuf + o.at, y0);
+      store_maybe_ds<DS>(qbuf + o.at + half, y1);
     } else {
-      int which = head < nq + nkv ? 0 : 1;
-      int h = head - nq - which * nkv;
-      WT *dst = (WT *)kv.pool + kv_elem_offset(kv, rd.seq, rd.pos, layer, which, h) + i;
+      WT *dst = (WT *)kv.pool + o.at;
       store_maybe_ds<DS>(dst, Elem<WT>::narrow(y0));
       store_maybe_ds<DS>(dst + half, Elem<WT>::narrow(y1));
     }
+  }
+  __device__ void finish(int task, int r, const RowDesc &rd, float y0, float y1, State &s) const {
+    finish_old(task, r, rd, y0, y1, load_old(task, r, rd), s);
   }
   __device__ void end(int, const RowDesc &, State &) const {}
 };
@@ -268,7 +276,7 @@ template <typename WT, bool DS = false> struct EpiResidual {
   }
   // the same in two halves, for a caller that fetches the old value long before the sum is ready
   typedef float2 Old;
-  __device__ float2 load_old(int task, const RowDesc &rd) const {
+  __device__ float2 load_old(int task, int, const RowDesc &rd) const {
     return load2_maybe_ds<DS>(hidden + (size_t)rd.x_slot * d + 2 * task);
   }
   __device__ void finish_old(int task, int r, const RowDesc &rd, float y0, float y1, float2 old, State &) const {
@@ -277,34 +285,27 @@ template <typename WT, bool DS = false> struct EpiResidual {
   __device__ void end(int, const RowDesc &, State &) const {}
 };
 // hidden[x_slot][i] += y as above, and what the next projection needs of the new hidden state
-// h: the three bf16 parts of gamma (.) h for pass row r, and h's sum of squares (see RowScale).
-// For the finishing launch of a k-split projection, whose threads of one row are 32 lanes apart.
+// h: gamma (.) h for pass row r, h's sum of squares (see RowScale) and the largest magnitude of
+// gamma (.) h.  For the finishing launch of a k-split projection, whose threads of one row are 32
+// lanes apart.
 template <typename WT> struct EpiResidualNorm {
-  struct State { float ssq; };
+  struct State { float ssq; uint32_t amax; };
   const WT *w;
   int n_in, n_out;
   float *hidden;
   int d;
   const float *gamma;          // gain of the norm that follows
-  SplitOut so;                 // where the split gamma (.) h goes
+  RowOut x;                    // gamma (.) h of the pass's rows
   unsigned long long *ssq;     // [pass row][SSQ_WAYS], zero before the launch
-  __device__ void init(State &s) const { s.ssq = 0.f; }
+  RowMax row_max;
+  __device__ void init(State &s) const { s.ssq = 0.f; s.amax = 0u; }
   __device__ void weight_rows(int task, const WT *&r0, const WT *&r1) const {
     r0 = w + (size_t)(2 * task) * n_in;
     r1 = r0 + n_in;
   }
-  __device__ void finish(int task, int r, const RowDesc &rd, float y0, float y1, State &s) const {
-    float *h = hidden + (size_t)rd.x_slot * d + 2 * task;
-    float2 v = *(const float2 *)h;
-    v.x += y0; v.y += y1;
-    *(float2 *)h = v;
-    s.ssq += v.x * v.x + v.y * v.y;
-    const float2 g = *(const float2 *)(gamma + 2 * task);
-    split_store2(so, r, 2 * task, v.x * g.x, v.y * g.y);
-  }
   // the old value and the gains, requested together long before the sums are ready
   typedef float4 Old;
-  __device__ float4 load_old(int task, const RowDesc &rd) const {
+  __device__ float4 load_old(int task, int, const RowDesc &rd) const {
     const float2 v = *(const float2 *)(hidden + (size_t)rd.x_slot * d + 2 * task);
     const float2 g = *(const float2 *)(gamma + 2 * task);
     return make_float4(v.x, v.y, g.x, g.y);
@@ -313,22 +314,30 @@ template <typename WT> struct EpiResidualNorm {
     const float2 v = make_float2(o.x + y0, o.y + y1);
     *(float2 *)(hidden + (size_t)rd.x_slot * d + 2 * task) = v;
     s.ssq += v.x * v.x + v.y * v.y;
-    split_store2(so, r, 2 * task, v.x * o.z, v.y * o.w);
+    const float2 n = make_float2(v.x * o.z, v.y * o.w);
+    *(float2 *)x.at(r, 2 * task) = n;
+    s.amax = max(s.amax, max(magnitude_bits(n.x), magnitude_bits(n.y)));
   }
-  // `sum`: the states of the threads that finished tasks of row r in this workgroup, added up
-  __device__ void add_row_sum(int r, float sum) const {
-    atomicAdd(ssq + r * SSQ_WAYS + (blockIdx.x % SSQ_WAYS), (unsigned long long)(sum * SSQ_SCALE + 0.5f));
+  __device__ void finish(int task, int r, const RowDesc &rd, float y0, float y1, State &s) const {
+    finish_old(task, r, rd, y0, y1, load_old(task, r, rd), s);
+  }
+  // `s`: the states of the threads that finished the 32 tasks of `block` in row r, combined
+  __device__ void put_row(int r, int block, const State &s) const {
+    atomicAdd(ssq + r * SSQ_WAYS + block % SSQ_WAYS, (unsigned long long)(s.ssq * SSQ_SCALE + 0.5f));
+    row_max.put(r, block, s.amax);
   }
   __device__ void end(int, const RowDesc &, State &) const {}
 };
-template <typename E> struct EpiHasRowSum { static constexpr bool value = false; };
-template <typename WT> struct EpiHasRowSum<EpiResidualNorm<WT>> { static constexpr bool value = true; };
+// epilogues that hand something about a whole row to a later launch, and what
+template <typename E> struct EpiRow { static constexpr bool sum = false, max = false; };
+template <typename WT> struct EpiRow<EpiResidualNorm<WT>> { static constexpr bool sum = true, max = true; };
 
 template <typename E> struct EpiHasLocalReduce { static constexpr bool value = false; };
 
 template <typename E> struct EpiReadsOld { static constexpr bool value = false; };
 template <typename WT, bool DS> struct EpiReadsOld<EpiResidual<WT, DS>> { static constexpr bool value = true; };
 template <typename WT> struct EpiReadsOld<EpiResidualNorm<WT>> { static constexpr bool value = true; };
+template <typename WT, bool DS> struct EpiReadsOld<EpiQKV<WT, DS>> { static constexpr bool value = true; };
 
 // act[r][i] = silu(Wg_i . n) * (Wu_i . n)
 template <typename WT, bool DS = false> struct EpiSwiGLU {
@@ -348,25 +357,41 @@ template <typename WT, bool DS = false> struct EpiSwiGLU {
   __device__ void end(int, const RowDesc &, State &) const {}
 };
 
-// the same, written as the three bf16 parts the down projection's MFMA kernel reads (no fp32 copy)
-template <typename WT> struct EpiSwiGLUSplit {
-  typedef NoState State;
+// the same for the MFMA path, which also wants the largest magnitude of a row's activations
+template <typename WT> struct EpiSwiGLUMax {
+  struct State { uint32_t amax; };
   const WT *wg, *wu;
   int d, F;
-  SplitOut so;
+  RowOut act;
+  RowMax row_max;
   RowScale scale = RowScale{nullptr, 0.f, 0.f};
-  __device__ void init(State &) const {}
+  __device__ void init(State &s) const { s.amax = 0u; }
   __device__ void weight_rows(int task, const WT *&r0, const WT *&r1) const {
     r0 = wg + (size_t)task * d;
     r1 = wu + (size_t)task * d;
   }
-  __device__ void finish(int task, int r, const RowDesc &, float y0, float y1, State &) const {
-    if (scale.ssq) { const float inv = scale.of(r); y0 *= inv; y1 *= inv; }
-    float s = y0 / (1.0f + expf(-y0));
-    split_store1(so, r, task, s * y1);
+  // value(row_scale(r), y0, y1) is what store_value puts into the row
+  __device__ float row_scale(int r) const { return scale.of(r); }
+  __device__ float value(float inv, float y0, float y1) const {
+    y0 *= inv; y1 *= inv;
+    return y0 / (1.0f + expf(-y0)) * y1;
   }
+  __device__ void store_value(int task, int r, float v) const { *act.at(r, task) = v; }
+  typedef float Old;   // the row's scale
+  __device__ float load_old(int, int r, const RowDesc &) const { return row_scale(r); }
+  __device__ void finish_old(int task, int r, const RowDesc &, float y0, float y1, float inv, State &s) const {
+    const float v = value(inv, y0, y1);
+    store_value(task, r, v);
+    s.amax = max(s.amax, magnitude_bits(v));
+  }
+  __device__ void finish(int task, int r, const RowDesc &rd, float y0, float y1, State &s) const {
+    finish_old(task, r, rd, y0, y1, row_scale(r), s);
+  }
+  __device__ void put_row(int r, int block, const State &s) const { row_max.put(r, block, s.amax); }
   __device__ void end(int, const RowDesc &, State &) const {}
 };
+template <typename WT> struct EpiReadsOld<EpiSwiGLUMax<WT>> { static constexpr bool value = true; };
+template <typename WT> struct EpiRow<EpiSwiGLUMax<WT>> { static constexpr bool sum = false, max = true; };
 
 // u[r][i] = h[i] + (A h)[i] + b[i]   (translator of the layer-specific head)
 template <typename WT> struct EpiLensAffine {
@@ -403,17 +428,23 @@ template <typename WT> struct EpiVocab {
     r0 = w + (size_t)(2 * task) * d;
     r1 = w + (size_t)i1 * d;
   }
-  __device__ void finish(int task, int r, const RowDesc &rd, float y0, float y1, State &s) const {
-    float *lg = logits + (size_t)rd.out_idx * V;
-    int i0 = 2 * task;
-    lg[i0] = y0;
+  __device__ void consider(int task, float y0, float y1, State &s) const {
+    const int i0 = 2 * task;
     unsigned long long k = argmax_key(y0, i0);
     if (k > s.best) s.best = k;
     if (i0 + 1 < V) {
-      lg[i0 + 1] = y1;
       k = argmax_key(y1, i0 + 1);
       if (k > s.best) s.best = k;
     }
+  }
+  __device__ void store_pair(int task, const RowDesc &rd, float y0, float y1) const {
+    float *lg = logits + (size_t)rd.out_idx * V + 2 * task;
+    lg[0] = y0;
+    if (2 * task + 1 < V) lg[1] = y1;
+  }
+  __device__ void finish(int task, int r, const RowDesc &rd, float y0, float y1, State &s) const {
+    store_pair(task, rd, y0, y1);
+    consider(task, y0, y1, s);
   }
   __device__ void end(int r, const RowDesc &rd, State &s) const {
     if (s.best) atomicMax(best + rd.out_idx, s.best);

@@ -1,20 +1,28 @@
-// Projections for 16..128 activation rows at once (prompt chunks, batched decoding) on the MFMA
+// Projections for 5 and more activation rows at once (prompt chunks, batched decoding) on the MFMA
 // units.  With that many rows a projection is a real dense contraction: every weight element is
-// used 32..128 times, so the vector kernel that serves a handful of rows would be ALU-bound.
+// used many times, so the vector kernel that serves a handful of rows would be ALU-bound.
 //
-// Weights are bf16.  Activations are fp32; each is split into three bf16 parts (x = hi + mid + lo
-// exactly, 3 x 8 mantissa bits) and all three go through the MFMA, which keeps the result at fp32
-// accuracy instead of rounding the activations to 8 bits of mantissa.  (Two parts leave 2^-17
-// relative error per element; re-rounded to bf16 in the KV cache that is enough to double the
-// deviation from the oracle, so the third part is kept.)
+// Weights are bf16, activations fp32, and the MFMA takes 16-bit operands: an activation goes through
+// it in parts that add up to the fp32 value, which keeps the result at fp32 accuracy instead of
+// rounding the activations to 8 bits of mantissa.  Activations lie in memory as fp32; the kernels
+// cut them into parts while they stage them in LDS.  Two kernels run the contraction:
 //
-// v_mfma_f32_32x32x16_bf16: A is 32 weight rows x 16 k, B is 16 k x 32 activation rows; lane l
+//   mfma_tiled_k (further down), the one a context with the memory for it runs, takes its weights
+//   from a copy in fp16 and in MFMA operand order, written when the context was created.  A bf16
+//   weight scaled by a power of two per block of 32 rows is an fp16 number (what lies 2^-40 below
+//   the block's largest weight is rounded there), so the activations are fp16 parts too, and fp16
+//   has 11 bits of mantissa: two parts hold what takes three of bf16.  A third of the MFMA work,
+//   and at the clock the chip holds under MFMA load a third of the time of a prompt's projections,
+//   is not done.
+//   mfma_rows_k, described next, takes the caller's row-major bf16 weights, for contexts without
+//   that copy: three bf16 parts (3 x 8 bits).
+//
+// (Two bf16 parts leave 2^-17 relative error per element; re-rounded to bf16 in the KV cache that
+// is enough to double the deviation from the oracle.)
+//
+// v_mfma_f32_32x32x16: A is 32 weight rows x 16 k, B is 16 k x 32 activation rows; lane l
 // supplies 8 consecutive k of row (l % 32), k-block (l / 32); of the 16 results in a lane,
 // register r belongs to weight row (r/4)*8 + (l/32)*4 + r%4 and activation row l % 32.
-//
-// Two kernels run the contraction: mfma_tiled_k (further down) takes its weights from a copy in
-// MFMA operand order that the context wrote when it was created, and is the one a context with
-// such a copy runs; mfma_rows_k, described next, takes them from the caller's row-major tensors.
 //
 // A workgroup of eight waves owns 256 "tasks" (the same pairs of weight rows the vector kernel
 // uses, so the epilogues are shared: rotary pairs, gate/up pairs, adjacent rows), 32 per wave, and
@@ -37,6 +45,8 @@
 namespace spark {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef _Float16 f16_t;
+typedef __attribute__((ext_vector_type(8))) _Float16 f16x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
 constexpr int MG_THREADS = 512;
@@ -46,11 +56,8 @@ constexpr int MG_ROWPAD = MG_KC + 8;   // bf16 per staged row (a 16-byte skew pe
 constexpr int MG_TASKS_PER_WAVE = 32;
 constexpr int MG_TASKS_PER_BLOCK = MG_WAVES * MG_TASKS_PER_WAVE;
 constexpr int MG_MAX_MTILES = 2;       // activation rows per workgroup: 32 or 64
-// bf16 parts of an activation that meet the weights: all three, so that every product is the
-// exact product of the fp32 activation and the bf16 weight, as in the vector kernel.  (Two parts,
-// 16 significant bits, would cut the MFMA and LDS work by a third at an error of 2^-17 per
-// product; tried: the 1e-5 perturbations change which cache entries round up or down to bf16,
-// and at the 40-layer shape that moved a logit by 0.022, past the 0.02 the parity tests allow.)
+// bf16 parts of an activation that meet bf16 weights: all three, so that every product is the
+// exact product of the fp32 activation and the bf16 weight, as in the vector kernel
 constexpr int MG_PARTS = 3;
 // weight chunks a wave has in registers, on their way from HBM
 constexpr int MG_W_DEPTH = 2;
@@ -62,17 +69,29 @@ constexpr size_t mg_lds_bytes(int mtiles, int waves = MG_WAVES) {
 
 // ------------------------------------------------------------------ activation preparation
 
-// xs[part][r][k] = the three bf16 parts of x_r[k], x_r = src row (plain) or
-// RMSNorm(hidden[x_slot_r]; gamma); rows are n_pad apart (n rounded up to the chunk of the
-// contraction) and zero beyond n; part p starts at xs + p * part_stride
+// x[r][k] = src row (plain) or RMSNorm(hidden[x_slot_r]; gamma), and the row's largest
+// magnitude: the input of a projection that no finishing launch
+// before it has prepared
 __global__ void __launch_bounds__(256)
 prep_rows_k(const RowDesc *__restrict__ rows, const float *__restrict__ src, int stride, int indirect,
-            const float *__restrict__ gamma, float eps, int n, int n_pad, bf16_t *__restrict__ xs,
-            size_t part_stride) {
+            const float *__restrict__ gamma, float eps, int n, RowOut x, RowMax row_max) {
   __shared__ float red[4];
+  __shared__ uint32_t big[4];
   const int r = blockIdx.x;
   const float *row = src + (size_t)(indirect ? rows[r].x_slot : r) * stride;
-  if (gamma && n <= 4096) {
+  uint32_t amax = 0u;
+  auto put = [&](int k, float4 f) {
+    *(float4 *)x.at(r, k) = f;
+    amax = max(amax, max(max(magnitude_bits(f.x), magnitude_bits(f.y)), max(magnitude_bits(f.z), magnitude_bits(f.w))));
+  };
+  auto finish = [&]() {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, o, 64));
+    if ((threadIdx.x & 63) == 0) big[threadIdx.x >> 6] = amax;
+    __syncthreads();
+    if (threadIdx.x == 0) row_max.put(r, 0, max(max(big[0], big[1]), max(big[2], big[3])));
+  };
+  if (n <= 4096) {
     // the row and the gains in registers: every load is issued before the first is used (one
     // memory round trip instead of one per loop trip of two passes)
     constexpr int NI = 4;
@@ -81,36 +100,27 @@ prep_rows_k(const RowDesc *__restrict__ rows, const float *__restrict__ src, int
     for (int i = 0; i < NI; ++i) {
       const int k = threadIdx.x * 4 + i * 1024;
       v[i] = *(const float4 *)(row + (k < n ? k : 0));
-      g[i] = *(const float4 *)(gamma + (k < n ? k : 0));
+      if (gamma) g[i] = *(const float4 *)(gamma + (k < n ? k : 0));
     }
-    float ss = 0.f;
+    float inv = 1.0f;
+    if (gamma) {
+      float ss = 0.f;
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
-      if (threadIdx.x * 4 + i * 1024 < n) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
-    ss = wave_sum(ss);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
-    __syncthreads();
-    const float inv = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)n + eps);
+      for (int i = 0; i < NI; ++i)
+        if (threadIdx.x * 4 + i * 1024 < n) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
+      ss = wave_sum(ss);
+      if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+      __syncthreads();
+      inv = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)n + eps);
+    }
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int k = threadIdx.x * 4 + i * 1024;
-      if (k < n) {
-        const float f[4] = {v[i].x * inv * g[i].x, v[i].y * inv * g[i].y, v[i].z * inv * g[i].z, v[i].w * inv * g[i].w};
-        bf16_t h[4], mid[4], l[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) split3_bf16(f[e], h[e], mid[e], l[e]);
-        bf16_t *dst = xs + (size_t)r * n_pad + k;
-        *(uint2 *)dst = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
-        *(uint2 *)(dst + part_stride) = make_uint2(mid[0] | ((uint32_t)mid[1] << 16), mid[2] | ((uint32_t)mid[3] << 16));
-        *(uint2 *)(dst + 2 * part_stride) = make_uint2(l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16));
-      }
+      if (k < n)
+        put(k, gamma ? make_float4(v[i].x * inv * g[i].x, v[i].y * inv * g[i].y, v[i].z * inv * g[i].z, v[i].w * inv * g[i].w)
+                     : v[i]);
     }
-    for (int k = n + threadIdx.x * 4; k < n_pad; k += 1024) {
-      bf16_t *dst = xs + (size_t)r * n_pad + k;
-      *(uint2 *)dst = make_uint2(0, 0);
-      *(uint2 *)(dst + part_stride) = make_uint2(0, 0);
-      *(uint2 *)(dst + 2 * part_stride) = make_uint2(0, 0);
-    }
+    finish();
     return;
   }
   float inv = 1.0f;
@@ -131,22 +141,66 @@ prep_rows_k(const RowDesc *__restrict__ rows, const float *__restrict__ src, int
       const float4 g = *(const float4 *)(gamma + k);
       v = make_float4(v.x * inv * g.x, v.y * inv * g.y, v.z * inv * g.z, v.w * inv * g.w);
     }
-    const float f[4] = {v.x, v.y, v.z, v.w};
-    bf16_t h[4], mid[4], l[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) split3_bf16(f[e], h[e], mid[e], l[e]);
-    bf16_t *dst = xs + (size_t)r * n_pad + k;
-    *(uint2 *)dst = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
-    *(uint2 *)(dst + part_stride) = make_uint2(mid[0] | ((uint32_t)mid[1] << 16), mid[2] | ((uint32_t)mid[3] << 16));
-    *(uint2 *)(dst + 2 * part_stride) = make_uint2(l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16));
+    put(k, v);
   }
-  for (int k = n + threadIdx.x * 4; k < n_pad; k += 1024) {
-    bf16_t *dst = xs + (size_t)r * n_pad + k;
-    *(uint2 *)dst = make_uint2(0, 0);
-    *(uint2 *)(dst + part_stride) = make_uint2(0, 0);
-    *(uint2 *)(dst + 2 * part_stride) = make_uint2(0, 0);
-  }
+  finish();
 }
+
+// The input of a projection: fp32 rows `stride` elements apart (0: in operand order, see RowOut) and
+// the lists of their magnitudes; and words that are to be zero for the launches after this one.
+struct ProjIn {
+  const float *x;
+  int stride;
+  RowMax row_max;
+  uint4 *zero;
+  int n_zero;   // 16-byte units
+};
+__device__ __forceinline__ void clear_words(const ProjIn &in) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < in.n_zero; i += gridDim.x * blockDim.x)
+    in.zero[i] = make_uint4(0, 0, 0, 0);
+}
+// Largest exponent in the list of row r, found by LANES (a power of two) neighbouring lanes of which
+// this is number `l`, in two halves: the first loads, issued before the weights' (memory answers in
+// order, and the weights come from further away), and the rest.
+template <int LANES> struct RowExponent {
+  static constexpr int U = 5, SPAN = 16 * LANES * U;   // bytes per trip: an MLP of 20480 in one
+  const uint8_t *p;
+  int n, l;
+  uint4 v[U];
+  __device__ __forceinline__ void load(int i0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + (u * LANES + l) * 16;
+      v[u] = *(const uint4 *)(p + (i < n ? i : 0));
+    }
+  }
+  __device__ __forceinline__ RowExponent(const RowMax &rm, int r, int l_) : p(rm.list + (size_t)r * rm.stride), n(rm.n), l(l_) { load(0); }
+  __device__ __forceinline__ int get() {
+    uint32_t even = 0u, odd = 0u;   // of the bytes 0, 2 and 1, 3 of every word
+    for (int i0 = 0;;) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + (u * LANES + l) * 16;
+        const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int left = n - (i + 4 * e);   // bytes past the end of the list are not anybody's
+          const uint32_t word = left >= 4 ? w[e] : left > 0 ? w[e] & ((1u << (8 * left)) - 1u) : 0u;
+          const uint32_t a = word & 0x00ff00ffu, b = (word >> 8) & 0x00ff00ffu;
+          even = max(even & 0xffffu, a & 0xffffu) | max(even & 0xff0000u, a & 0xff0000u);
+          odd = max(odd & 0xffffu, b & 0xffffu) | max(odd & 0xff0000u, b & 0xff0000u);
+        }
+      }
+      i0 += SPAN;
+      if (i0 >= n) break;
+      load(i0);
+    }
+    int big = (int)max(max(even & 0xffu, even >> 16), max(odd & 0xffu, odd >> 16));
+#pragma unroll
+    for (int o = LANES / 2; o > 0; o >>= 1) big = max(big, __shfl_xor(big, o, 64));
+    return big;
+  }
+};
 
 // ------------------------------------------------------------------ the contraction
 
@@ -167,11 +221,11 @@ prep_rows_k(const RowDesc *__restrict__ rows, const float *__restrict__ src, int
 // WAVES: 8, or 4 for matrices of few rows, whose launches then have twice as many workgroups
 template <int MTILES, typename Epi, bool SPLIT, int WAVES = MG_WAVES>
 __global__ void __launch_bounds__(64 * WAVES)
-mfma_rows_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, const bf16_t *__restrict__ xs,
-            size_t part_stride, int n_in, int n_tasks, int chunks_per_split,
-            float *__restrict__ part, int m_pad, int n_task_tiles, int n_splits, int n_row_tiles,
+mfma_rows_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, ProjIn in, int n_in, int n_tasks,
+            int chunks_per_split, float *__restrict__ part, int m_pad, int n_task_tiles, int n_splits, int n_row_tiles,
             int xcd_groups) {
   static_assert(MTILES <= MG_MAX_MTILES, "accumulators and LDS are sized for 64 rows");
+  clear_words(in);
   // Workgroup -> (task tile, k range, row tile).  Consecutive workgroup ids go to consecutive
   // XCDs, each with its own L2: the row tiles of one (task tile, k range) read the same weights,
   // so they get ids 8 apart (same XCD, launched together) and the weights cross HBM once for them.
@@ -214,13 +268,8 @@ mfma_rows_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, const bf16_t 
   const int row0 = bz * MROWS;
   const int task0 = bx * (WAVES * MG_TASKS_PER_WAVE) + wave * MG_TASKS_PER_WAVE;
   const int n_chunks = (n_in + MG_KC - 1) / MG_KC;   // the last one may be short: activations are zero-padded
-  const int x_stride = n_chunks * MG_KC;
   const int c_begin = by * chunks_per_split;
   const int c_end = min(n_chunks, c_begin + chunks_per_split);
-  // the rows' sums of squares that this projection's finishing launch will add up start at zero
-  if constexpr (EpiHasRowSum<Epi>::value)
-    if (blockIdx.x == 0)
-      for (int i = threadIdx.x; i < m_rows * SSQ_WAYS; i += 64 * WAVES) epi.ssq[i] = 0ull;
   if (c_begin >= c_end) return;
 
   // Load instruction i covers the wave's rows 8i..8i+7 (rows 0..31: first weight row of tasks
@@ -247,42 +296,53 @@ mfma_rows_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, const bf16_t 
     for (int r = 0; r < 16; ++r) acc0[c][r] = acc1[c][r] = 0.f;
 
   u32x4_t wr[WD][WI];   // (a native vector type: arrays of it are kept in registers)
-  // this thread's vectors of the three parts of a chunk's activations: xr[i][p]
-  int x_src[XV], x_dst[XV];
+  // this thread's vectors of eight activations of a chunk; they become three bf16 parts when they are
+  // written to LDS (zeros beyond the row's end)
+  const float *x_src[XV];
+  int x_dst[XV], x_k[XV];
 #pragma unroll
   for (int i = 0; i < XV; ++i) {
     const int pos = ((int)threadIdx.x + i * (64 * WAVES)) % XPOS;
-    const int m = pos / (MG_KC / 8), kv = (pos - m * (MG_KC / 8)) * 8;
-    x_src[i] = min(row0 + m, m_rows - 1) * x_stride + kv;    // rows past the end repeat the last one
-    x_dst[i] = m * MG_ROWPAD + kv;
+    const int m = pos / (MG_KC / 8);
+    x_k[i] = (pos - m * (MG_KC / 8)) * 8;
+    x_src[i] = in.x + (size_t)min(row0 + m, m_rows - 1) * in.stride;    // rows past the end repeat the last one
+    x_dst[i] = m * MG_ROWPAD + x_k[i];
   }
-  u32x4_t xr[XV][MG_PARTS];
+  float4 xr[XV][2];
+  auto load_x = [&](int chunk) {
+#pragma unroll
+    for (int i = 0; i < XV; ++i) {
+      const int k = min(chunk, c_end - 1) * MG_KC + x_k[i];
+      const float *src = x_src[i] + (k < n_in ? k : 0);
+      xr[i][0] = *(const float4 *)src;
+      xr[i][1] = *(const float4 *)(src + 4);
+    }
+  };
+  auto store_x = [&](int chunk, int buf) {
+#pragma unroll
+    for (int i = 0; i < XV; ++i) {
+      const bool real = min(chunk, c_end - 1) * MG_KC + x_k[i] < n_in;
+      const float f[8] = {xr[i][0].x, xr[i][0].y, xr[i][0].z, xr[i][0].w, xr[i][1].x, xr[i][1].y, xr[i][1].z, xr[i][1].w};
+      u32x4_t part[MG_PARTS];
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) {
+        bf16_t h0, m0, l0, h1, m1, l1;
+        split3_bf16(real ? f[e] : 0.f, h0, m0, l0);
+        split3_bf16(real ? f[e + 1] : 0.f, h1, m1, l1);
+        part[0][e >> 1] = h0 | ((uint32_t)h1 << 16);
+        part[1][e >> 1] = m0 | ((uint32_t)m1 << 16);
+        part[2][e >> 1] = l0 | ((uint32_t)l1 << 16);
+      }
+#pragma unroll
+      for (int p = 0; p < MG_PARTS; ++p) *(u32x4_t *)(s_x + (buf * MG_PARTS + p) * PART_ELEMS + x_dst[i]) = part[p];
+    }
+  };
 
-  {
-    const int k_ = c_begin * MG_KC;
-#pragma unroll
-    for (int i = 0; i < XV; ++i) {
-#pragma unroll
-      for (int p = 0; p < MG_PARTS; ++p) xr[i][p] = *(const u32x4_t *)(xs + p * part_stride + x_src[i] + k_);
-    }
-  }
+  load_x(c_begin);
   __builtin_amdgcn_sched_barrier(0);
-  {
-#pragma unroll
-    for (int i = 0; i < XV; ++i) {
-#pragma unroll
-      for (int p = 0; p < MG_PARTS; ++p) *(u32x4_t *)(s_x + p * PART_ELEMS + x_dst[i]) = xr[i][p];
-    }
-  }
+  store_x(c_begin, 0);
   __builtin_amdgcn_sched_barrier(0);
-  {
-    const int k_ = min(c_begin + 1, c_end - 1) * MG_KC;
-#pragma unroll
-    for (int i = 0; i < XV; ++i) {
-#pragma unroll
-      for (int p = 0; p < MG_PARTS; ++p) xr[i][p] = *(const u32x4_t *)(xs + p * part_stride + x_src[i] + k_);
-    }
-  }
+  load_x(c_begin + 1);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int j = 0; j < WD; ++j) {
@@ -304,23 +364,9 @@ mfma_rows_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, const bf16_t 
       for (int i = 0; i < WI; ++i) *(u32x4_t *)(s_w + 8 * i * MG_ROWPAD + w_dst) = wr[j][i];
       __builtin_amdgcn_sched_barrier(0);
       // activations of chunk + 1, requested one iteration ago, into the other buffer
-      {
-#pragma unroll
-        for (int i = 0; i < XV; ++i) {
-#pragma unroll
-          for (int p = 0; p < MG_PARTS; ++p)
-            *(u32x4_t *)(s_x + ((buf ^ 1) * MG_PARTS + p) * PART_ELEMS + x_dst[i]) = xr[i][p];
-        }
-      }
+      store_x(chunk + 1, buf ^ 1);
       __builtin_amdgcn_sched_barrier(0);
-      {
-        const int k_ = min(chunk + 2, c_end - 1) * MG_KC;
-#pragma unroll
-        for (int i = 0; i < XV; ++i) {
-#pragma unroll
-          for (int p = 0; p < MG_PARTS; ++p) xr[i][p] = *(const u32x4_t *)(xs + p * part_stride + x_src[i] + k_);
-        }
-      }
+      load_x(chunk + 2);
       __builtin_amdgcn_sched_barrier(0);
       {
         int k_ = min(chunk + WD, c_end - 1) * MG_KC + w_seg;
@@ -354,7 +400,7 @@ mfma_rows_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, const bf16_t 
   }
 
   // results: register r <-> task (r/4)*8 + (lane/32)*4 + r%4 of this wave, activation row lane%32
-  if constexpr (!SPLIT && std::is_same<typename Epi::State, NoState>::value) {
+  if constexpr (!SPLIT && !EpiHasLocalReduce<Epi>::value) {
     // The epilogue runs here, and what it writes runs along the tasks (consecutive elements of a
     // row of the hidden state, of q, of the cache, of the split activations), while a lane's
     // registers hold 16 tasks of ONE row: stored as they lie, every store instruction would put
@@ -363,7 +409,8 @@ mfma_rows_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, const bf16_t 
     // now; the wave's LDS operations execute in order, no barrier) and the epilogue is called with
     // the tasks across the lanes: 32 consecutive elements per half-wave.
     float *s_t = (float *)s_w;   // [2][32 tasks][33]
-    NoState st;
+    typename Epi::State st;      // (what it gathers about a row is for contexts with tiled weights)
+    epi.init(st);
     const int tl = lane & 31, rh = (lane >> 5) * 16;
 #pragma unroll
     for (int c = 0; c < MTILES; ++c) {
@@ -408,28 +455,67 @@ mfma_rows_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, const bf16_t 
 
 // ------------------------------------------------------------------ the contraction on tiled weights
 //
-// A context that owns enough memory keeps a second copy of every bf16 projection matrix in the
-// order the MFMA consumes it: for each block of 32 tasks, for each of its two weight rows per
-// task, for each 64-wide chunk of k, one 4 KiB tile [step 0..3][lane 0..63][8 elements], lane l of
-// step s holding row l % 32, elements 64 c + 16 s + 8 (l / 32) .. + 7.  A wave then loads a whole
-// A operand with one fully coalesced instruction (64 lanes x 16 bytes, consecutive) straight into
-// registers: the weights never touch LDS, which leaves LDS to the activations, and a wave can hold
-// four A tiles (64 tasks), so that every B operand it reads from LDS feeds four MFMAs instead of
-// two.  tile_weights_k writes the copy once, when the context is created, from the same
-// weight_rows() of the epilogue that the kernels use.
+// A context that owns enough memory keeps a second copy of every bf16 projection matrix as fp16 and
+// in the order the MFMA consumes it: for each block of 16 tasks (rows 0..15 of the operand: their
+// first weight rows, rows 16..31: their second) and for each 64-wide chunk of k, one 4 KiB tile
+// [step 0..3][lane 0..63][8 elements], lane l of step s holding row l % 32, elements
+// 64 c + 16 s + 8 (l / 32) .. + 7.  A wave then loads a whole A operand with one fully coalesced
+// instruction (64 lanes x 16 bytes, consecutive) straight into registers: the weights never touch
+// LDS, which leaves LDS to the activations, and a wave can hold several A tiles, so that every B
+// operand it reads feeds several MFMAs.  Both weight rows of a task end up in one lane: result
+// registers r and r + 8 (r < 8) are task (r/4)*8 + (l/32)*4 + r%4 of the block.
+// The 32 rows of a block share a power of two that brings their largest weight just below 2^15 (one
+// word per block holds that weight's magnitude).  Both are written once, when the context is
+// created, from the same weight_rows() of the epilogue that the kernels use.
 constexpr int TG_WAVES = 4;
 constexpr int TG_TILE = 32 * MG_KC;   // elements of one A tile of one chunk
+constexpr int TG_TASKS = 16;          // tasks of one A tile
+constexpr int TG_PARTS = 2;           // fp16 parts of an activation
 
 constexpr size_t tg_tiled_elems(int n_tasks, int n_in) {
-  return (size_t)((n_tasks + 31) / 32) * 2 * ((n_in + MG_KC - 1) / MG_KC) * TG_TILE;
+  return (size_t)((n_tasks + TG_TASKS - 1) / TG_TASKS) * ((n_in + MG_KC - 1) / MG_KC) * TG_TILE;
+}
+constexpr size_t tg_blocks(int n_tasks) { return (size_t)((n_tasks + TG_TASKS - 1) / TG_TASKS); }
+
+constexpr int TG_AMAX_CHUNKS = 8;   // chunks a workgroup of the first pass reads
+
+// largest finite magnitude of each block's weight rows, as an fp32 bit pattern; wmax zero before
+template <typename Epi>
+__global__ void __launch_bounds__(256)
+weights_amax_k(Epi epi, int n_tasks, int n_in, uint32_t *__restrict__ wmax) {
+  const int block = blockIdx.y, which = threadIdx.x >> 7;
+  const int task = block * TG_TASKS + ((threadIdx.x >> 3) & (TG_TASKS - 1));
+  const bf16_t *a, *b;
+  epi.weight_rows(task < n_tasks ? task : 0, a, b);
+  const bf16_t *row = which ? b : a;
+  u32x4_t v[TG_AMAX_CHUNKS];
+#pragma unroll
+  for (int c = 0; c < TG_AMAX_CHUNKS; ++c) {
+    const int k = (blockIdx.x * TG_AMAX_CHUNKS + c) * MG_KC + (threadIdx.x & 7) * 8;
+    v[c] = *(const u32x4_t *)(row + (k < n_in ? k : 0));
+  }
+  uint32_t m = 0u;
+#pragma unroll
+  for (int c = 0; c < TG_AMAX_CHUNKS; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t u = (h ? v[c][e] & 0xffff0000u : v[c][e] << 16) & 0x7fffffffu;
+        m = max(m, u < 0x7f800000u ? u : 0u);
+      }
+  if (task >= n_tasks) m = 0u;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
+  if ((threadIdx.x & 63) == 0 && m) atomicMax(wmax + block, m);
 }
 
 template <typename Epi>
 __global__ void __launch_bounds__(256)
-tile_weights_k(Epi epi, int n_tasks, int n_in, int n_chunks, bf16_t *__restrict__ dst) {
-  const int c = blockIdx.x, tbw = blockIdx.y, tb = tbw >> 1, which = tbw & 1;
+tile_weights_k(Epi epi, int n_tasks, int n_in, int n_chunks, const uint32_t *__restrict__ wmax, f16_t *__restrict__ dst) {
+  const int c = blockIdx.x, block = blockIdx.y;
   const int s = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int task = tb * 32 + (lane & 31);
+  const int task = block * TG_TASKS + (lane & (TG_TASKS - 1)), which = (lane >> 4) & 1;
   const int k = c * MG_KC + s * 16 + (lane >> 5) * 8;
   u32x4_t v = {0u, 0u, 0u, 0u};   // beyond the matrix: zeros
   if (task < n_tasks && k < n_in) {
@@ -437,86 +523,130 @@ tile_weights_k(Epi epi, int n_tasks, int n_in, int n_chunks, bf16_t *__restrict_
     epi.weight_rows(task, a, b);
     v = *(const u32x4_t *)((which ? b : a) + k);
   }
-  *(u32x4_t *)(dst + ((size_t)tbw * n_chunks + c) * TG_TILE + s * 512 + lane * 8) = v;
-}
-
-// dynamic LDS of mfma_tiled_k: two buffers of three parts of 32*MTILES padded activation rows, or
-// the four waves' pieces for turning the result tiles, whichever is larger
-constexpr size_t tg_lds_bytes(int mtiles) {
-  const size_t x = sizeof(bf16_t) * 2 * MG_PARTS * 32 * mtiles * MG_ROWPAD;
-  const size_t t = sizeof(float) * TG_WAVES * 2 * 32 * 33;
-  return x > t ? x : t;
-}
-
-// A workgroup of four waves takes 128 * TB tasks (wave w: TB blocks of 32 tasks, 2 * TB A tiles),
-// one k range and one tile of 32 * MTILES activation rows; grid and arguments as mfma_rows_k.
-// SPLIT, or an epilogue without a running state.
-//
-// The loop over the chunks is written group by group in the order it is to execute, and every
-// group ends with a scheduling barrier: a group is the 2 * TB MFMAs that share one B operand, the
-// LDS read of a B operand of the NEXT step, and at most a few of the chunk's other operations (a
-// weight load, an activation load, an LDS write of the staging), which issue while the MFMAs
-// execute.  Left to itself the compiler puts each LDS read next to its use and the loads at the
-// end of the chunk, and the MFMA pipe then idles half the time (measured on the gate/up projection
-// of a 192-row prompt pass: 174 us; in this order 133 us; the same loop without any memory
-// operation 110 us).
-template <int MTILES, int TB, typename Epi, bool SPLIT>
-__global__ void __launch_bounds__(64 * TG_WAVES)
-mfma_tiled_k(Epi epi, const bf16_t *__restrict__ tiled, const RowDesc *__restrict__ rows, int m_rows,
-             const bf16_t *__restrict__ xs, size_t part_stride, int n_in, int n_tasks, int chunks_per_split,
-             float *__restrict__ part, int m_pad, int n_task_tiles, int n_splits, int n_row_tiles,
-             int xcd_groups) {
-  static_assert(SPLIT || std::is_same<typename Epi::State, NoState>::value, "a running state needs the finishing launch");
-  static_assert(MTILES <= MG_MAX_MTILES && (TB == 1 || TB == 2), "accumulators are sized for 64 rows x 64 tasks");
-  int bx, by, bz;   // workgroup -> (task tile, k range, row tile), as in mfma_rows_k
-  if (!xcd_groups) {
-    const int tiles = n_task_tiles * n_splits;
-    bz = blockIdx.x / tiles;
-    const int tile = blockIdx.x - bz * tiles;
-    if (bz >= n_row_tiles) return;
-    by = tile / n_task_tiles;
-    bx = tile - by * n_task_tiles;
-  } else {
-    const int per_group = 8 * n_row_tiles;
-    const int group = blockIdx.x / per_group, r = blockIdx.x - group * per_group;
-    const int tile = group * 8 + (r & 7);
-    if (tile >= n_task_tiles * n_splits) return;
-    bz = r >> 3;
-    by = tile / n_task_tiles;
-    bx = tile - by * n_task_tiles;
+  const float up = scale_up(scale_exponent(wmax[block] >> 23));
+  f16x8_t o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    o[2 * e] = (f16_t)(__uint_as_float(v[e] << 16) * up);
+    o[2 * e + 1] = (f16_t)(__uint_as_float(v[e] & 0xffff0000u) * up);
   }
+  *(f16x8_t *)(dst + ((size_t)block * n_chunks + c) * TG_TILE + s * 512 + lane * 8) = o;
+}
+
+// How a launch covers a projection.  A tile is 128 * TB tasks x 32 * MTILES activation rows; the
+// first n_whole tiles are one workgroup each, over the whole k range, and end in the epilogue; the
+// n_cut tiles behind them are cut into n_split ranges of k, whose partial sums a finishing launch
+// adds up.  So whole rounds of the chip's CUs do without partial sums, and the tiles that would be
+// a nearly empty last round, or less than one, are spread over all CUs.
+struct TileCover {
+  int n_task_tiles, n_row_tiles;
+  int n_whole, n_cut, n_split, chunks_per_split;
+  int m_pitch;     // rows of a tile's partial sums (a pass of eight rows writes and reads a quarter of 32)
+  int max_words;   // bytes of a row's list of magnitudes that a wave of a whole tile writes: one, or one per block of 32 tasks
+  int xcd_groups;
+};
+// Tile -> (task tile, row tile).  Consecutive workgroup ids go to consecutive XCDs, each with its
+// own L2: the row tiles of one task tile read the same weights, so they get ids 8 apart (same XCD,
+// launched together) and the weights cross HBM once for them.  (xcd_groups: chosen by the launch;
+// measured to pay for few, long k ranges: gate/up of a prompt pass 191 -> 169 us, while down with
+// its many short ranges lost, 101 -> 116 us.)
+__device__ __forceinline__ void tile_place(const TileCover &tc, int t, int &bx, int &bz) {
+  if (!tc.xcd_groups) {
+    bz = t / tc.n_task_tiles;
+    bx = t - bz * tc.n_task_tiles;
+    return;
+  }
+  const int even = tc.n_task_tiles / 8 * 8;          // task tiles in whole groups of eight
+  const int per_group = 8 * tc.n_row_tiles, group = t / per_group;
+  if (group * 8 < even) {
+    const int r = t - group * per_group;
+    bx = group * 8 + (r & 7);
+    bz = r >> 3;
+  } else {
+    const int r = t - even * tc.n_row_tiles, rest = tc.n_task_tiles - even;
+    bz = r / rest;
+    bx = even + r - bz * rest;
+  }
+}
+
+// dynamic LDS of mfma_tiled_k: three buffers of two parts of 32*MTILES padded activation rows, or
+// the four waves' pieces for turning the result tiles, whichever is larger; the rows' scales and
+// arg-max keys
+constexpr int TG_BUFS = 3;
+constexpr size_t tg_lds_bytes(int mtiles) {
+  const size_t x = sizeof(f16_t) * TG_BUFS * TG_PARTS * 32 * mtiles * MG_ROWPAD;
+  const size_t t = sizeof(float) * TG_WAVES * 2 * 32 * 33;
+  return (x > t ? x : t) + (sizeof(float) + sizeof(unsigned long long)) * 32 * mtiles;
+}
+
+// A workgroup of four waves takes 128 * TB tasks (wave w: 2 * TB A tiles of 16 tasks),
+// one k range and one tile of 32 * MTILES activation rows.  WHOLE: the launch has tiles that end in
+// the epilogue here (others only write partial sums and the epilogue's code is left out).
+//
+// The loop over the chunks is written MFMA by MFMA in the order it is to execute, with a scheduling
+// barrier after each: the MFMAs of one B operand (2 * TB of them) form a group, and between them
+// issue the LDS read of the B operand PD groups ahead, a reload of weights whose last use has just
+// been issued, and pieces of the staging of the next chunk's activations (an fp32 load, two
+// elements cut into fp16 parts, an LDS write).  Left to itself the compiler puts each LDS read next
+// to its use and the loads at the end of the chunk, and the MFMA pipe then idles half the time.
+// Activations go through three LDS buffers, so that one barrier per chunk, placed before the first
+// read of the next chunk, is enough: a wave writes the buffer two chunks ahead of what the slowest
+// wave can still read.
+template <int MTILES, int TB, typename Epi, bool WHOLE>
+__global__ void __launch_bounds__(64 * TG_WAVES)
+mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restrict__ wmax,
+             const RowDesc *__restrict__ rows, int m_rows, ProjIn in, int n_in, int n_tasks, TileCover tc,
+             float *__restrict__ part) {
+  static_assert(MTILES * TB <= 6 && MTILES <= 4 && TB <= 2, "accumulators take at most 192 registers");
   constexpr int MROWS = 32 * MTILES;
   constexpr int NT = 64 * TG_WAVES;
-  constexpr int XPOS = MROWS * (MG_KC / 8);
-  constexpr int XV = XPOS / NT;
-  static_assert(XPOS % NT == 0, "every thread stages the same number of vectors");
+  constexpr int XV = MROWS * (MG_KC / 8) / NT;      // vectors of eight activations a thread stages per chunk
+  static_assert(XV == MTILES, "every thread stages the same number of vectors");
   constexpr int PART_ELEMS = MROWS * MG_ROWPAD;
   constexpr int STEPS = MG_KC / 16;
   constexpr int QT = 2 * TB;                        // A tiles per wave
-  constexpr int NB = MG_PARTS * MTILES;             // B operands (and groups of QT MFMAs) per step
-  constexpr int NX = XV * MG_PARTS;                 // activation vectors a thread stages per chunk
-  static_assert(NX == NB, "one staging operation per group");
+  constexpr int NB = TG_PARTS * MTILES;             // B operands (and groups of QT MFMAs) per step
+  constexpr int GROUPS = STEPS * NB;
+  constexpr int W = 4, PD = W - 1;                  // window of B operands in registers, and how far ahead they are read
+  static_assert(GROUPS % W == 0 && NB >= 2, "an operand keeps its place in the window from chunk to chunk");
+  constexpr int BAR = GROUPS - PD;                  // group before which the next chunk's activations must be visible
+  static_assert(BAR >= 2 * NB, "the staging of the next chunk ends two steps into this one");
   constexpr int PER = (QT + NB - 1) / NB;           // weight loads per group
-  constexpr int BUF_ELEMS = MG_PARTS * PART_ELEMS;
+  constexpr int BUF_ELEMS = TG_PARTS * PART_ELEMS;
+  constexpr int TASKS = 32 * TG_WAVES * TB;
+  constexpr size_t SCALE_AT = tg_lds_bytes(MTILES) - (sizeof(float) + sizeof(unsigned long long)) * MROWS;
   extern __shared__ uint4 tg_smem[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  bf16_t *s_x = (bf16_t *)tg_smem;                  // [2][3][MROWS * MG_ROWPAD]
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (known to be uniform: addresses of weights stay scalar)
+  f16_t *s_x = (f16_t *)tg_smem;                    // [3][2][MROWS * MG_ROWPAD]
+  float *s_down = (float *)((char *)tg_smem + SCALE_AT);   // per row: what undoes its scale
+  clear_words(in);
+
+  int t, split = 0, bx, bz;
+  const bool whole = WHOLE && (int)blockIdx.x < tc.n_whole;
+  if (whole) {
+    t = blockIdx.x;
+  } else {
+    const int i = blockIdx.x - tc.n_whole;
+    split = i / tc.n_cut;
+    t = tc.n_whole + i - split * tc.n_cut;
+  }
+  tile_place(tc, t, bx, bz);
   const int row0 = bz * MROWS;
   const int n_chunks = (n_in + MG_KC - 1) / MG_KC;
-  const int x_stride = n_chunks * MG_KC;
-  const int c_begin = by * chunks_per_split;
-  const int c_end = min(n_chunks, c_begin + chunks_per_split);
-  if constexpr (EpiHasRowSum<Epi>::value)
-    if (blockIdx.x == 0)
-      for (int i = threadIdx.x; i < m_rows * SSQ_WAYS; i += NT) epi.ssq[i] = 0ull;
-  if (c_begin >= c_end) return;
-  const int n_tb = (n_tasks + 31) / 32;
-  const int tb0 = (bx * TG_WAVES + wave) * TB;       // this wave's first block of 32 tasks
+  const int c_begin = whole ? 0 : split * tc.chunks_per_split;
+  const int c_end = whole ? n_chunks : min(n_chunks, c_begin + tc.chunks_per_split);
+  const int n_blocks = (n_tasks + TG_TASKS - 1) / TG_TASKS;
+  const int tb0 = (bx * TG_WAVES + wave) * TB;       // this wave's first 32 tasks
 
-  const bf16_t *abase[QT];   // A tile q: block tb0 + q / 2, weight row q % 2 of its tasks (blocks past the end: the last one)
+  const f16_t *abase[QT];   // A tile q: block 2 tb0 + q (past the end: the last one)
+  float wdown[QT];
 #pragma unroll
-  for (int q = 0; q < QT; ++q)
-    abase[q] = tiled + ((size_t)(min(tb0 + (q >> 1), n_tb - 1) * 2 + (q & 1)) * n_chunks) * TG_TILE + lane * 8;
+  for (int q = 0; q < QT; ++q) {
+    const int block = min(2 * tb0 + q, n_blocks - 1);
+    abase[q] = tiled + (size_t)block * n_chunks * TG_TILE + lane * 8;
+    wdown[q] = scale_down(scale_exponent(wmax[block] >> 23));
+  }
   const int a_off = (lane & 31) * MG_ROWPAD + (lane >> 5) * 8;
 
   f32x16_t acc[QT][MTILES];
@@ -527,52 +657,60 @@ mfma_tiled_k(Epi epi, const bf16_t *__restrict__ tiled, const RowDesc *__restric
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[q][c][r] = 0.f;
 
-  int x_src[XV], x_dst[XV];
-#pragma unroll
-  for (int i = 0; i < XV; ++i) {
-    const int pos = (int)threadIdx.x + i * NT;
-    const int m = pos / (MG_KC / 8), kv = (pos - m * (MG_KC / 8)) * 8;
-    x_src[i] = min(row0 + m, m_rows - 1) * x_stride + kv;    // rows past the end repeat the last one
-    x_dst[i] = m * MG_ROWPAD + kv;
-  }
-  u32x4_t xr[XV][MG_PARTS];
-  // chunks of weights in registers, slot = chunk % RING: three for 64-row tiles, whose one wave per
-  // SIMD has nothing else to cover a late load with (prompt pass 29.6 -> 28.6 ms, passes of 33..64
-  // rows in a batch of 32: 5.23 -> 5.17 ms per step); 32-row tiles keep two workgroups on a CU with
-  // a ring of two, and lose with three (4.44 -> 4.61 ms per step)
-  constexpr int RING = MTILES == 2 ? 3 : 2;
+  // chunks of weights in registers, slot = (chunk - c_begin) % RING
+  constexpr int RING = 2;
   u32x4_t wr[RING][QT][STEPS];
-  const u32x4_t zero4 = {0u, 0u, 0u, 0u};
-
   // all loads are unconditional (chunks past the range are clamped to its last one) so that the
   // compiler waits for exactly the loads a step needs; a chunk past the range is staged as zeros
-  auto load_x1 = [&](int n, int chunk) {
-    const int k_ = min(chunk, c_end - 1) * MG_KC;
-    xr[n / MG_PARTS][n % MG_PARTS] = *(const u32x4_t *)(xs + (n % MG_PARTS) * part_stride + x_src[n / MG_PARTS] + k_);
-  };
-  auto store_x1 = [&](int n, int buf, bool real) {
-    *(u32x4_t *)(s_x + buf * BUF_ELEMS + (n % MG_PARTS) * PART_ELEMS + x_dst[n / MG_PARTS]) =
-        real ? xr[n / MG_PARTS][n % MG_PARTS] : zero4;
-  };
-  // B operand i of step s of a buffer: parts from the smallest to the largest (the large terms
-  // are added last), row tiles inside
-  auto load_b1 = [&](int i, int buf, int s) -> u32x4_t {
-    const int p = MG_PARTS - 1 - i / MTILES, c = i % MTILES;
-    return *(const u32x4_t *)(s_x + buf * BUF_ELEMS + p * PART_ELEMS + c * 32 * MG_ROWPAD + s * 16 + a_off);
-  };
   auto load_a1 = [&](int slot, int q, int s, int chunk) {
     wr[slot][q][s] = __builtin_nontemporal_load(
         (const u32x4_t *)(abase[q] + (size_t)min(chunk, c_end - 1) * TG_TILE + s * 512));
   };
 
+  int x_src[XV], x_dst[XV];
+  float x_up[XV];
+  const int x_kv = ((int)threadIdx.x & 7) * 8;       // k of this thread's vectors inside a chunk
 #pragma unroll
-  for (int n = 0; n < NX; ++n) load_x1(n, c_begin);
-  __builtin_amdgcn_sched_barrier(0);
+  for (int n = 0; n < XV; ++n) {
+    const int m = ((int)threadIdx.x + n * NT) >> 3;
+    x_src[n] = min(row0 + m, m_rows - 1) * in.stride;                 // rows past the end repeat the last one
+    x_dst[n] = m * MG_ROWPAD + x_kv;
+  }
+  float4 xr[XV][2];
+  auto load_x1 = [&](int n, int half, int chunk) {
+    const int k = min(chunk, c_end - 1) * MG_KC + x_kv;
+    xr[n][half] = *(const float4 *)(in.x + x_src[n] + (k < n_in ? k : 0) + half * 4);
+  };
+  // elements 2 e and 2 e + 1 of vector n: two fp16 parts each, zeros where there is nothing to
+  // multiply; every second call writes four elements to the buffer at `at`
+  typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+  u32x2_t xh, xl;
+  auto cut_x2 = [&](int n, int e, int at, bool real) {
+    const float4 v = xr[n][e >> 1];
+    const float f0 = ((e & 1) ? v.z : v.x) * x_up[n], f1 = ((e & 1) ? v.w : v.y) * x_up[n];
+    const f16_t h0 = (f16_t)f0, h1 = (f16_t)f1;
+    const f16_t l0 = (f16_t)(f0 - (float)h0), l1 = (f16_t)(f1 - (float)h1);
+    const uint32_t h = (uint32_t)__builtin_bit_cast(uint16_t, h0) | ((uint32_t)__builtin_bit_cast(uint16_t, h1) << 16);
+    const uint32_t l = (uint32_t)__builtin_bit_cast(uint16_t, l0) | ((uint32_t)__builtin_bit_cast(uint16_t, l1) << 16);
+    xh[e & 1] = real ? h : 0u;
+    xl[e & 1] = real ? l : 0u;
+    if (e & 1) {
+      *(u32x2_t *)(s_x + at + x_dst[n] + 2 * (e - 1)) = xh;
+      *(u32x2_t *)(s_x + at + PART_ELEMS + x_dst[n] + 2 * (e - 1)) = xl;
+    }
+  };
+  // B operand i of step s of a buffer: the smaller part first (the large terms are added last), row tiles inside
+  auto load_b1 = [&](int i, int at, int s) -> u32x4_t {
+    const int p = TG_PARTS - 1 - i / MTILES, c = i % MTILES;
+    return *(const u32x4_t *)(s_x + at + p * PART_ELEMS + c * 32 * MG_ROWPAD + s * 16 + a_off);
+  };
+
+  // the first loads: the rows' magnitudes (of a row per eight lanes) and activations, then the weights
+  constexpr int LPR = MG_KC / 8;
+  const int xr0 = (int)threadIdx.x >> 3;
+  RowExponent<LPR> mag0(in.row_max, min(row0 + xr0, m_rows - 1), threadIdx.x & 7);
 #pragma unroll
-  for (int n = 0; n < NX; ++n) store_x1(n, 0, true);
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int n = 0; n < NX; ++n) load_x1(n, c_begin + 1);
+  for (int n = 0; n < XV; ++n) { load_x1(n, 0, c_begin); load_x1(n, 1, c_begin); }
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int j = 0; j < RING; ++j)
@@ -580,114 +718,219 @@ mfma_tiled_k(Epi epi, const bf16_t *__restrict__ tiled, const RowDesc *__restric
     for (int s = 0; s < STEPS; ++s)
 #pragma unroll
       for (int q = 0; q < QT; ++q) load_a1(j, q, s, c_begin + j);
-  __syncthreads();
-  u32x4_t bcur[NB], bnext[NB];
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int i = 0; i < NB; ++i) bcur[i] = zero4;
+  for (int n = 0; n < XV; ++n) {
+    const int m = xr0 + n * (NT / LPR);
+    const int E = scale_exponent(n == 0 ? mag0.get() : RowExponent<LPR>(in.row_max, min(row0 + m, m_rows - 1), threadIdx.x & 7).get());
+    x_up[n] = scale_up(E);
+    if (x_kv == 0) s_down[((int)threadIdx.x + n * NT) >> 3] = scale_down(E);
+  }
+#pragma unroll
+  for (int n = 0; n < XV; ++n) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) cut_x2(n, e, 0, c_begin * MG_KC + x_kv < n_in);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int n = 0; n < XV; ++n) { load_x1(n, 0, c_begin + 1); load_x1(n, 1, c_begin + 1); }
+  __syncthreads();
+  u32x4_t bw[W];
+#pragma unroll
+  for (int o = 0; o < PD; ++o) bw[o] = load_b1(o % NB, 0, o / NB);
 
-  // Region k (one barrier each) works on chunk i = c_begin + k, whose weights sit in ring slot
-  // k % RING and whose activations in LDS buffer k % 2:
-  //   step 3 of chunk i - 1 (its B operands were fetched before the last barrier; zeros in region 0),
-  //   steps 0..2 of chunk i, while the B operands of the step after each are fetched,
-  //   the staging of chunk i + 1 into the other buffer, the loads of the activations of chunk i + 2,
-  //   and the reloads of the weight registers whose step has just been finished with (chunks
-  //   i + RING - 1 and i + RING).
-  // Every read of a buffer lies in the region of its chunk, every write to it in the regions next
-  // to that one, so the one barrier per region separates them; the MFMAs run on across it.
-  // A number of chunks that is not a multiple of RING is filled up with regions on zeros.
-  const int n_regions = (c_end - c_begin + RING - 1) / RING * RING;
-  int buf = 0;   // LDS buffer of the region's chunk
-  for (int k0 = 0; k0 < n_regions; k0 += RING) {
+  int cur = 0, nxt = BUF_ELEMS, aft = 2 * BUF_ELEMS;   // LDS buffers of this chunk, the next, the one after
+  for (int base = c_begin; base < c_end; base += RING) {
 #pragma unroll
     for (int j = 0; j < RING; ++j) {
-      const int chunk = c_begin + k0 + j;
-      const int jp = (j + RING - 1) % RING;
+      const int chunk = base + j;
+      const bool next_real = chunk + 1 < c_end && (chunk + 1) * MG_KC + x_kv < n_in;
 #pragma unroll
-      for (int t = 0; t < STEPS; ++t) {
-        // t = 0: step 3 of the previous chunk; t = 1..3: steps 0..2 of this one
-        const int slot = t == 0 ? jp : j, s = t == 0 ? STEPS - 1 : t - 1;
+      for (int s = 0; s < STEPS; ++s) {
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-          const int c = i % MTILES;
+          const int o = s * NB + i;
+          if (o == BAR) __syncthreads();
 #pragma unroll
-          for (int q = 0; q < QT; ++q)
-            acc[q][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, wr[slot][q][s]),
-                                                                __builtin_bit_cast(bf16x8_t, bcur[i]), acc[q][c], 0, 0, 0);
-          bnext[i] = load_b1(i, buf, t);   // operands of step t of this chunk (t = 0 follows the last barrier)
-#pragma unroll
-          for (int e = 0; e < PER; ++e) {
-            const int q = i * PER + e;
-            if (q < QT) {
-              if (t == 0) load_a1(jp, q, STEPS - 2, chunk + RING - 1);        // step 2 of chunk i - 1 -> chunk i - 1 + RING
-              else if (t == 1) load_a1(jp, q, STEPS - 1, chunk + RING - 1);   // step 3 of chunk i - 1 likewise
-              else load_a1(j, q, t - 2, chunk + RING);                 // steps 0, 1 of chunk i -> chunk i + RING
+          for (int q = 0; q < QT; ++q) {
+            acc[q][i % MTILES] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, wr[j][q][s]),
+                                                                        __builtin_bit_cast(f16x8_t, bw[o % W]),
+                                                                        acc[q][i % MTILES], 0, 0, 0);
+            if (q == 0) {
+              const int n = o + PD;
+              bw[n % W] = n < GROUPS ? load_b1(n % NB, cur, n / NB) : load_b1((n - GROUPS) % NB, nxt, (n - GROUPS) / NB);
             }
-          }
-          if (t == 1) store_x1(i, buf ^ 1, chunk + 1 < c_end);
-          if (t == 2) load_x1(i, chunk + 2);
-          __builtin_amdgcn_sched_barrier(0);
-        }
+            if (q == 1 % QT) {
 #pragma unroll
-        for (int i = 0; i < NB; ++i) bcur[i] = bnext[i];
+              for (int e = 0; e < PER; ++e) {
+                const int qq = i * PER + e;
+                if (qq < QT) {
+                  if (s == 0) load_a1((j + RING - 1) % RING, qq, STEPS - 1, chunk - 1 + RING);   // last step of the chunk before
+                  else load_a1(j, qq, s - 1, chunk + RING);
+                }
+              }
+            }
+            if (q == QT - 1) {
+              // vector i / 2 of the next chunk: four pieces of two elements over the groups of steps 0 and 1
+              if (s < 2) cut_x2(i / 2, (i & 1) + 2 * s, nxt, next_real);
+              if (s == 2) load_x1(i / 2, i & 1, chunk + 2);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
       }
-      __syncthreads();
-      buf ^= 1;
+      const int old = cur;
+      cur = nxt;
+      nxt = aft;
+      aft = old;
     }
   }
-  // step 3 of the last chunk
-#pragma unroll
-  for (int i = 0; i < NB; ++i)
-#pragma unroll
-    for (int q = 0; q < QT; ++q)
-      acc[q][i % MTILES] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, wr[RING - 1][q][STEPS - 1]),
-                                                                   __builtin_bit_cast(bf16x8_t, bcur[i]), acc[q][i % MTILES], 0, 0, 0);
 
-  // register r of acc[2 jb + which][c] <-> weight row `which` of task (tb0 + jb) * 32 + (r/4)*8 + (lane/32)*4 + r%4,
-  // activation row lane % 32 of row tile c
-  if constexpr (SPLIT) {
+  // number r (0..15) of what a lane holds of 32 tasks jb and row tile c: task 32 (tb0 + jb) + task_of(r),
+  // activation row lane % 32, sums y_of(0 / 1, jb, c, r) of its two weight rows
+  auto task_of = [&](int r) { return (r >> 3) * TG_TASKS + ((r >> 2) & 1) * 8 + (lane >> 5) * 4 + (r & 3); };
+  auto y_of = [&](int which, int jb, int c, int r) { return acc[2 * jb + (r >> 3)][c][(r & 7) + 8 * which]; };
+#pragma unroll
+  for (int c = 0; c < MTILES; ++c) {
+    const float xd = s_down[c * 32 + (lane & 31)];
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+      const float f = xd * wdown[q];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[q][c][r] *= f;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (!whole) {
+    float *base = part + ((size_t)split * tc.n_cut + (t - tc.n_whole)) * TASKS * 2 * tc.m_pitch;
 #pragma unroll
     for (int jb = 0; jb < TB; ++jb)
 #pragma unroll
       for (int c = 0; c < MTILES; ++c) {
-        const int m = row0 + c * 32 + (lane & 31);
+        const int m = c * 32 + (lane & 31);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int task = (tb0 + jb) * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-          if (task < n_tasks && m < m_pad) {
-            float *p = part + (((size_t)by * n_tasks + task) * 2) * m_pad + m;
-            p[0] = acc[2 * jb][c][r];
-            p[m_pad] = acc[2 * jb + 1][c][r];
+          const int tl = (wave * TB + jb) * 32 + task_of(r);
+          if (m < tc.m_pitch) {
+            float *p = base + (size_t)tl * 2 * tc.m_pitch + m;
+            p[0] = y_of(0, jb, c, r);
+            p[tc.m_pitch] = y_of(1, jb, c, r);
           }
         }
       }
-  } else {
+    return;
+  }
+  if constexpr (WHOLE) {
     // the epilogue's stores run along the tasks: each 32 x 32 tile is turned in the wave's piece of
     // LDS (the buffers are free once every wave has left the loop)
     __syncthreads();
     float *s_t = (float *)tg_smem + wave * 2 * 32 * 33;
-    NoState st;
     const int tl = lane & 31, rh = (lane >> 5) * 16;
-#pragma unroll
-    for (int jb = 0; jb < TB; ++jb) {
+    if constexpr (EpiHasLocalReduce<Epi>::value) {
+      // a running state per activation row (the heads' arg-max): formed while a lane holds tasks of one
+      // row, combined over the workgroup in LDS, so that one atomic per row and workgroup reaches memory
+      unsigned long long *s_best = (unsigned long long *)((char *)tg_smem + SCALE_AT + sizeof(float) * MROWS);
+      if (threadIdx.x < MROWS) s_best[threadIdx.x] = 0ull;
+      __syncthreads();
 #pragma unroll
       for (int c = 0; c < MTILES; ++c) {
+        typename Epi::State st;
+        epi.init(st);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int t = (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-          s_t[t * 33 + (lane & 31)] = acc[2 * jb][c][r];
-          s_t[32 * 33 + t * 33 + (lane & 31)] = acc[2 * jb + 1][c][r];
+        for (int jb = 0; jb < TB; ++jb) {
+          const int t0 = (tb0 + jb) * 32;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int tt = task_of(r);
+            if (t0 + tt < n_tasks) epi.consider(t0 + tt, y_of(0, jb, c, r), y_of(1, jb, c, r), st);
+            s_t[tt * 33 + (lane & 31)] = y_of(0, jb, c, r);
+            s_t[32 * 33 + tt * 33 + (lane & 31)] = y_of(1, jb, c, r);
+          }
+          // (a few at a time: all sixteen in flight, times the tiles, is more than the registers hold)
+#pragma unroll 4
+          for (int i = 0; i < 16; ++i) {
+            const int m = row0 + c * 32 + rh + i;
+            if (t0 + tl < n_tasks && m < m_rows)
+              epi.store_pair(t0 + tl, rows[m], s_t[tl * 33 + rh + i], s_t[32 * 33 + tl * 33 + rh + i]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
-        const int task = (tb0 + jb) * 32 + tl;
+        epi.reduce_local(st, s_best + c * 32 + (lane & 31));
+      }
+      __syncthreads();
+      const int m = row0 + (int)threadIdx.x;
+      if (threadIdx.x < MROWS && m < m_rows && s_best[threadIdx.x]) epi.end_reduced(rows[m], s_best[threadIdx.x]);
+    } else if constexpr (EpiRow<Epi>::max) {
+      // one value per pair of weight rows: it is formed while a lane still holds 16 tasks of one row,
+      // so that the row's scale is one per lane and its largest magnitude stays in the lane
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int m = row0 + c * 32 + rh + i;
-          const float y0 = s_t[tl * 33 + rh + i], y1 = s_t[32 * 33 + tl * 33 + rh + i];
-          if (task < n_tasks && m < m_rows) epi.finish(task, m, rows[m], y0, y1, st);
+      for (int c = 0; c < MTILES; ++c) {
+        const int mine = row0 + c * 32 + (lane & 31);
+        const float inv = epi.row_scale(min(mine, m_rows - 1));
+        typename Epi::State st;
+        epi.init(st);
+#pragma unroll
+        for (int jb = 0; jb < TB; ++jb) {
+          const int t0 = (tb0 + jb) * 32;
+          if (tc.max_words > 1) epi.init(st);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int tt = task_of(r);
+            const float v = epi.value(inv, y_of(0, jb, c, r), y_of(1, jb, c, r));
+            if (t0 + tt < n_tasks) st.amax = max(st.amax, magnitude_bits(v));
+            s_t[tt * 33 + (lane & 31)] = v;
+            if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // (registers: sixteen exponentials at once are too many)
+          }
+#pragma unroll 4
+          for (int i = 0; i < 16; ++i) {
+            const int m = row0 + c * 32 + rh + i;
+            if (t0 + tl < n_tasks && m < m_rows) epi.store_value(t0 + tl, m, s_t[tl * 33 + rh + i]);
+          }
+          if (tc.max_words > 1 || jb == TB - 1) {
+            st.amax = max(st.amax, (uint32_t)__shfl_xor((int)st.amax, 32, 64));
+            const int word = tc.max_words > 1 ? tb0 + jb : bx * TG_WAVES + wave;
+            if (lane < 32 && mine < m_rows && (tc.max_words > 1 ? t0 : tb0 * 32) < n_tasks) epi.put_row(mine, word, st);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    } else {
+      typename Epi::State st;
+      epi.init(st);
+#pragma unroll
+      for (int jb = 0; jb < TB; ++jb) {
+#pragma unroll
+        for (int c = 0; c < MTILES; ++c) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int tt = task_of(r);
+            s_t[tt * 33 + (lane & 31)] = y_of(0, jb, c, r);
+            s_t[32 * 33 + tt * 33 + (lane & 31)] = y_of(1, jb, c, r);
+          }
+          const int task = (tb0 + jb) * 32 + tl;
+#pragma unroll 2
+          for (int i = 0; i < 16; ++i) {
+            const int m = row0 + c * 32 + rh + i;
+            const float y0 = s_t[tl * 33 + rh + i], y1 = s_t[32 * 33 + tl * 33 + rh + i];
+            if (task < n_tasks && m < m_rows) epi.finish(task, m, rows[m], y0, y1, st);
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
     }
   }
 }
+
+// ------------------------------------------------------------------ finishing
+
+// Where the partial sums of (task, row) lie, one range of k after the other `stride` floats apart.
+// Both kernels cut a projection into tiles for this purpose; mfma_rows_k into a single one.
+struct PartialSums {
+  const float *part;
+  int n_split, m_pitch, tasks_per_tile, rows_per_tile;
+  TileCover tc;
+  __device__ __forceinline__ size_t stride() const { return (size_t)tc.n_cut * tasks_per_tile * 2 * m_pitch; }
+};
 
 // The partial sums of one (task, row) over the k ranges, added in the order of the ranges.  All
 // loads are issued before the first is used: a loop that loads and adds pays a memory round trip
@@ -696,13 +939,11 @@ constexpr int MG_MAX_SPLIT = 32;
 // MAXS: the most ranges this instance adds (8 or MG_MAX_SPLIT): the loads live in 2 * MAXS
 // registers, and a finishing launch with hundreds of workgroups wants two of them on a CU
 template <int MAXS>
-__device__ __forceinline__ void sum_splits(const float *__restrict__ part, int n_split, int n_tasks, int task,
-                                           int m_pad, int m, float &y0, float &y1) {
-  const size_t stride = (size_t)n_tasks * 2 * m_pad;
-  const float *p = part + ((size_t)task * 2) * m_pad + m;
+__device__ __forceinline__ void sum_splits(const float *__restrict__ p, size_t stride, int n_split, int m_pitch,
+                                           float &y0, float &y1) {
   float a[MAXS], b[MAXS];
 #pragma unroll
-  for (int i = 0; i < MAXS; ++i) { const int s = i < n_split ? i : 0; a[i] = p[s * stride]; b[i] = p[s * stride + m_pad]; }
+  for (int i = 0; i < MAXS; ++i) { const int s = i < n_split ? i : 0; a[i] = p[s * stride]; b[i] = p[s * stride + m_pitch]; }
 #pragma unroll
   for (int i = 0; i < MAXS; ++i) if (i < n_split) { y0 += a[i]; y1 += b[i]; }
 }
@@ -760,51 +1001,237 @@ mfma_finish_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, int n_tasks
   if ((int)threadIdx.x < m_rows && s_best[threadIdx.x]) epi.end_reduced(rows[threadIdx.x], s_best[threadIdx.x]);
 }
 
-// The same for epilogues without a running state, with the stores in mind: a workgroup of 1024
-// threads takes 32 tasks x 32 activation rows, one pair per thread.  It sums the k ranges with the
-// rows fastest across threads (the order in which the partials lie), turns the tile in LDS, and
-// runs the epilogue with the tasks fastest, so that what the epilogue writes (consecutive
-// elements of a row of the hidden state, of q, of the cache, of the split activations) leaves a
-// wave as whole segments instead of single words 7 KB apart.  grid (tasks / 32, m_pad / 32).
+// What an epilogue needs besides the sums, requested before they are ready
+template <typename Epi> __device__ __forceinline__ auto load_old(const Epi &epi, int task, int m, const RowDesc &rd) {
+  if constexpr (EpiReadsOld<Epi>::value) return epi.load_old(task, m, rd);
+  else return 0;
+}
+// What an epilogue gathers about a row, combined over the LANES neighbouring lanes that have finished
+// tasks of it (shuffles: a fixed order) and handed on by the first of them as part `i`
+template <int LANES, typename Epi>
+__device__ __forceinline__ void hand_on_row(const Epi &epi, int m, bool row_live, typename Epi::State st, int i) {
+  if constexpr (EpiRow<Epi>::sum || EpiRow<Epi>::max) {
+#pragma unroll
+    for (int o = LANES / 2; o > 0; o >>= 1) {
+      if constexpr (EpiRow<Epi>::sum) st.ssq += __shfl_xor(st.ssq, o, 64);
+      if constexpr (EpiRow<Epi>::max) st.amax = max(st.amax, (uint32_t)__shfl_xor((int)st.amax, o, 64));
+    }
+    if ((threadIdx.x & (LANES - 1)) == 0 && row_live) epi.put_row(m, i, st);
+  }
+}
+template <typename Epi, typename Old>
+__device__ __forceinline__ void finish_pair(const Epi &epi, int task, int m, const RowDesc &rd, float y0, float y1, const Old &old,
+                                            typename Epi::State &st) {
+  if constexpr (EpiReadsOld<Epi>::value) epi.finish_old(task, m, rd, y0, y1, old, st);
+  else epi.finish(task, m, rd, y0, y1, st);
+}
+
+// The same for the other epilogues, with the stores in mind: a workgroup of 1024 threads takes 32
+// tasks x 32 activation rows, one pair per thread.  It sums the k ranges with the rows fastest
+// across threads (the order in which the partials lie), turns the tile in LDS, and runs the
+// epilogue with the tasks fastest, so that what the epilogue writes (consecutive elements of a row
+// of the hidden state, of q, of the cache, of the activations) leaves a wave as whole segments
+// instead of single words 7 KB apart.  grid (cut tiles * blocks of 32 tasks in a tile, blocks of 32
+// rows in a tile).
 template <typename Epi, int MAXS>
 __global__ void __launch_bounds__(1024)
-mfma_finish_tile_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, int n_tasks, int n_split,
-                   const float *__restrict__ part, int m_pad) {
+mfma_finish_tile_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, int n_tasks, PartialSums ps) {
   __shared__ float s_y[2][32][33];
-  const int task0 = blockIdx.x * 32, row0 = blockIdx.y * 32;
+  const int per_tile = (ps.tasks_per_tile + 31) / 32;
+  const int tile = blockIdx.x / per_tile, tb = blockIdx.x - tile * per_tile;   // cut tile, block of tasks in it
+  int bx, bz;
+  tile_place(ps.tc, ps.tc.n_whole + tile, bx, bz);
+  const int task0 = bx * ps.tasks_per_tile + tb * 32, row0 = bz * ps.rows_per_tile + blockIdx.y * 32;
+  if (task0 >= n_tasks || row0 >= m_rows) return;
   // what the epilogue will need besides the sums is requested first: the row's descriptor, and
   // through it the old value of a residual projection; both round trips run under the loads of
   // the partial sums
   const int tl = threadIdx.x & 31, ml = threadIdx.x >> 5, task = task0 + tl, m = row0 + ml;
   const bool live = task < n_tasks && m < m_rows;
   const RowDesc rd = rows[m < m_rows ? m : 0];
-  auto old = [&]() {
-    if constexpr (EpiReadsOld<Epi>::value) return epi.load_old(live ? task : 0, rd);
-    else return 0;
-  }();
+  const auto old = load_old(epi, live ? task : 0, m < m_rows ? m : 0, rd);
   {
-    const int ml_ = threadIdx.x & 31, tl_ = threadIdx.x >> 5, task_ = min(task0 + tl_, n_tasks - 1);
+    const int ml_ = blockIdx.y * 32 + (threadIdx.x & 31);                     // row and task inside the tile
+    const int tl_ = min(tb * 32 + (int)(threadIdx.x >> 5), ps.tasks_per_tile - 1);
     float y0 = 0.f, y1 = 0.f;
-    if (row0 + ml_ < m_pad) sum_splits<MAXS>(part, n_split, n_tasks, task_, m_pad, row0 + ml_, y0, y1);
-    s_y[0][tl_][ml_] = y0;
-    s_y[1][tl_][ml_] = y1;
+    if (ml_ < ps.m_pitch)
+      sum_splits<MAXS>(ps.part + ((size_t)tile * ps.tasks_per_tile + tl_) * 2 * ps.m_pitch + ml_, ps.stride(), ps.n_split,
+                       ps.m_pitch, y0, y1);
+    s_y[0][threadIdx.x >> 5][threadIdx.x & 31] = y0;
+    s_y[1][threadIdx.x >> 5][threadIdx.x & 31] = y1;
   }
   __syncthreads();
   typename Epi::State st;
   epi.init(st);
-  if (live) {
-    if constexpr (EpiReadsOld<Epi>::value) epi.finish_old(task, m, rd, s_y[0][tl][ml], s_y[1][tl][ml], old, st);
-    else epi.finish(task, m, rd, s_y[0][tl][ml], s_y[1][tl][ml], st);
-  }
-  if constexpr (EpiHasRowSum<Epi>::value) {
-    // the 32 threads of a row are half a wave: their states are added with shuffles (a fixed
-    // order), and one of them hands the sum on
-    float sum = st.ssq;
+  if (live) finish_pair(epi, task, m, rd, s_y[0][tl][ml], s_y[1][tl][ml], old, st);
+  hand_on_row<32>(epi, m, m < m_rows, st, task0 / 32);
+}
+
+// ------------------------------------------------------------------ at most 32 rows
+//
+// Batched decoding: the projection is a stream of weights again, only with more arithmetic per
+// weight.  A workgroup of eight waves takes NT A tiles (16 NT tasks) and one range of k, an eighth
+// of it for each wave; the waves' sums meet in LDS at the end.  Weights and activations go from
+// memory straight into registers, both in operand order, so the loop has no LDS traffic and no
+// barrier: every wave runs on its own behind its own loads, RING steps ahead (memory answers in
+// order: a shorter ring for the activations would empty the weights' longer one), and the
+// activations are cut into fp16 parts by the wave that multiplies them.
+//
+// One workgroup per CU, and NT so that all CUs have one of about the same size: a workgroup then
+// takes the whole range of k, and there are no partial sums and no finishing launch.  (Small
+// workgroups, several on a CU, were slower: 592 of them on 256 CUs leave some CUs a third more than
+// the average, and a CU's share of the memory system is what the stream runs at; and every
+// workgroup reads all activations, 271 MB for 592 of them at 32 rows, which cost what weights cost.)
+// Only a long k with few tasks (down) is cut: CUT writes partial sums.
+constexpr int TD_WAVES = 8;
+constexpr int td_ring(int nt) { return nt == 1 ? 8 : nt == 2 ? 6 : 4; }
+constexpr size_t td_lds_bytes(int nt) { return sizeof(float) * (TD_WAVES / 2) * nt * 32 * 33 + sizeof(int) * OP_ROWS; }
+
+template <int NT, typename Epi, bool CUT>
+__global__ void __launch_bounds__(64 * TD_WAVES, 2)
+mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restrict__ wmax,
+              const RowDesc *__restrict__ rows, int m_rows, ProjIn in, int n_in, int n_tasks, int n_groups,
+              int chunks_per_split, float *__restrict__ part, int m_pitch) {
+  constexpr int STEPS = MG_KC / 16, RING = td_ring(NT);
+  extern __shared__ uint4 td_smem[];
+  float *s_t = (float *)td_smem;                         // [4 waves][NT][32 operand rows][33]
+  int *s_exp = (int *)(s_t + (TD_WAVES / 2) * NT * 32 * 33);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  clear_words(in);
+  const int split = CUT ? blockIdx.x / n_groups : 0, group = blockIdx.x - split * n_groups;
+  const int n_chunks = (n_in + MG_KC - 1) / MG_KC, n_blocks = (n_tasks + TG_TASKS - 1) / TG_TASKS;
+  const int c_begin = CUT ? split * chunks_per_split : 0;
+  const int c_end = CUT ? min(n_chunks, c_begin + chunks_per_split) : n_chunks;
+
+  // this wave's steps [s_begin, s_end) of the range
+  const int per_wave = ((c_end - c_begin) * STEPS + TD_WAVES - 1) / TD_WAVES;
+  const int s_begin = min(c_begin * STEPS + wave * per_wave, c_end * STEPS), s_end = min(s_begin + per_wave, c_end * STEPS);
+  const int s_last = max(s_end - 1, 0);   // steps past the end read this one and are multiplied with zeros
+  const f16_t *a[NT];
 #pragma unroll
-    for (int o = 16; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-    if (tl == 0 && m < m_rows) epi.add_row_sum(m, sum);
+  for (int q = 0; q < NT; ++q) a[q] = tiled + (size_t)min(group * NT + q, n_blocks - 1) * n_chunks * TG_TILE + lane * 8;
+  u32x4_t wr[RING][NT];
+  float4 xr[RING][2];
+  auto load_w = [&](int u, int step) {
+    const size_t o = (size_t)min(step, s_last) * 512;
+#pragma unroll
+    for (int q = 0; q < NT; ++q) wr[u][q] = __builtin_nontemporal_load((const u32x4_t *)(a[q] + o));
+  };
+  // columns past the last row repeat it; beyond n_in the weights are zero and any activation will do
+  const int x_row = min(lane & 31, m_rows - 1) * 4;
+  const int x_off = (lane >> 5) * (2 * 4 * OP_ROWS) + x_row, x_most = (n_in / 4 - 2) * (4 * OP_ROWS) + x_row;
+  auto load_x = [&](int u, int step) {
+    const float *p = in.x + min(min(step, s_last) * (4 * 4 * OP_ROWS) + x_off, x_most);
+    xr[u][0] = *(const float4 *)p;
+    xr[u][1] = *(const float4 *)(p + 4 * OP_ROWS);
+  };
+  RowExponent<16> mag(in.row_max, min((int)threadIdx.x >> 4, m_rows - 1), threadIdx.x & 15);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < RING; ++u) { load_w(u, s_begin + u); load_x(u, s_begin + u); }
+  __builtin_amdgcn_sched_barrier(0);
+  {
+    const int e = mag.get();
+    if ((threadIdx.x & 15) == 0) s_exp[threadIdx.x >> 4] = scale_exponent(e);
+  }
+  __syncthreads();
+  const int E = s_exp[lane & 31];
+  const float x_up = scale_up(E);
+
+  f32x16_t acc[NT];
+#pragma unroll
+  for (int q = 0; q < NT; ++q)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[q][r] = 0.f;
+  for (int s0 = s_begin; s0 < s_end; s0 += RING) {
+#pragma unroll
+    for (int u = 0; u < RING; ++u) {
+      const int step = s0 + u;
+      const float up = step < s_end ? x_up : 0.f;
+      const float4 v0 = xr[u][0], v1 = xr[u][1];
+      const float f[8] = {v0.x * up, v0.y * up, v0.z * up, v0.w * up, v1.x * up, v1.y * up, v1.z * up, v1.w * up};
+      f16x8_t h, l;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        h[e] = (f16_t)f[e];
+        l[e] = (f16_t)(f[e] - (float)h[e]);
+      }
+#pragma unroll
+      for (int q = 0; q < NT; ++q)
+        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, wr[u][q]), l, acc[q], 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < NT; ++q)
+        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, wr[u][q]), h, acc[q], 0, 0, 0);
+      load_w(u, step + RING);
+      load_x(u, step + RING);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+
+  // the waves' sums: the upper four hand theirs to the lower four, those leave four to be added up
+  // by the thread that finishes a pair (always in the same order)
+  auto at = [&](int w, int q, int r) { return ((w * NT + q) * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * 33 + (lane & 31); };
+  if (wave >= TD_WAVES / 2) {
+#pragma unroll
+    for (int q = 0; q < NT; ++q)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s_t[at(wave - TD_WAVES / 2, q, r)] = acc[q][r];
+  }
+  __syncthreads();
+  if (wave < TD_WAVES / 2) {
+    const float down = scale_down(E);
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+      const float d = scale_down(scale_exponent(wmax[min(group * NT + q, n_blocks - 1)] >> 23)) * down;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s_t[at(wave, q, r)] = (acc[q][r] + s_t[at(wave, q, r)]) * d;
+    }
+  }
+  __syncthreads();
+  auto sum = [&](int q, int row, int m) {
+    float y = s_t[(q * 32 + row) * 33 + m];
+#pragma unroll
+    for (int w = 1; w < TD_WAVES / 2; ++w) y += s_t[((w * NT + q) * 32 + row) * 33 + m];
+    return y;
+  };
+  if constexpr (CUT) {
+    // rows fastest across the lanes, as the finishing launch reads them
+    float *base = part + (size_t)blockIdx.x * (TG_TASKS * NT) * 2 * m_pitch;
+    const int m = threadIdx.x & 31, t = threadIdx.x >> 5;   // 16 tasks
+    if (m < m_pitch) {
+#pragma unroll
+      for (int q = 0; q < NT; ++q) {
+        float *p = base + (size_t)(q * TG_TASKS + t) * 2 * m_pitch + m;
+        p[0] = sum(q, t, m);
+        p[m_pitch] = sum(q, TG_TASKS + t, m);
+      }
+    }
   } else {
-    if (live) epi.end(m, rd, st);
+    // tasks fastest: 16 lanes finish a row's tasks of one tile after the other
+    const int t = threadIdx.x & (TG_TASKS - 1), m = threadIdx.x >> 4;
+    const bool row_live = m < m_rows;
+    const RowDesc rd = rows[row_live ? m : m_rows - 1];
+    typename Epi::State st;
+    epi.init(st);
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+      const int task = (group * NT + q) * TG_TASKS + t;
+      const bool live = row_live && task < n_tasks;
+      const auto old = load_old(epi, live ? task : 0, row_live ? m : m_rows - 1, rd);
+      if (live) finish_pair(epi, task, m, rd, sum(q, t, m), sum(q, TG_TASKS + t, m), old, st);
+    }
+    if constexpr (EpiHasLocalReduce<Epi>::value) {
+      // the heads' arg-max: one atomic per row and workgroup
+#pragma unroll
+      for (int o = TG_TASKS / 2; o > 0; o >>= 1) {
+        const unsigned long long other =
+            ((unsigned long long)(uint32_t)__shfl_xor((int)(st.best >> 32), o, 64) << 32) | (uint32_t)__shfl_xor((int)st.best, o, 64);
+        if (other > st.best) st.best = other;
+      }
+      if (t == 0 && row_live) epi.end_reduced(rd, st.best);
+    } else {
+      hand_on_row<TG_TASKS>(epi, m, row_live, st, group);
+    }
   }
 }
 

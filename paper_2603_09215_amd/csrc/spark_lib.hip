@@ -27,20 +27,24 @@ using namespace spark;
 
 namespace {
 
-constexpr int PREFILL_CHUNK = 256;   // most prompt rows pushed through the layers together (buffers are sized for it)
+constexpr int PREFILL_CHUNK = 256;   // most prompt rows pushed through the layers together in the buffers that every context has
+constexpr int PROMPT_ROWS = 1024;    // and in those of a context with tiled weights
 constexpr size_t MFMA_PARTIAL_BYTES = 48u << 20;  // k-split partial sums of one projection
 constexpr int MAX_STEPS_PER_CALL = 256;
 // rows from which the MFMA projections run: up to four rows are one pass of the vector kernel
 // (measured at four rows: level at the GLM shape, 14-20 % faster for a batch of four at the Step
 // shape); five rows would be two such passes
 constexpr int MFMA_MIN_ROWS = 5;
+constexpr int TILED_WIDE_TASKS = 8192;   // projections from here on have tiles enough for 64 tasks a wave at any row count
 constexpr int MAX_SEQ_LEN = 16384;
 
 struct Layout {  // byte offsets into the scratch buffer
   size_t state, page_table, plan, lower, upper, ee, full, prefill_rows, prefill_tokens, seq_ids,
-      forced, step_flags, out_tokens, out_depth, best, arrivals, row_ssq, sample_hist, sample_arrive, sample_count, hidden, xsplit, xsplit2, mfma_part, sample_q, sample_cand, rand_words, qbuf, attn_out, part, act, lens_u,
+      forced, step_flags, out_tokens, out_depth, best, arrivals, row_ssq, max_x, max_attn, max_act, sample_hist, sample_arrive, sample_count, hidden, xnorm, mfma_part, sample_q, sample_cand, rand_words, qbuf, attn_out, part, act, lens_u,
       logits, rope, inv_freq, total,
-      tiled, total_tiled;   // the MFMA-ordered copy of the projection weights lies behind everything else (absent on the static area)
+      tiled, wmax, total_tiled,   // the MFMA-ordered copy of the projection weights and its scales lie behind everything else (absent on the static area)
+      prompt_hidden, prompt_q, prompt_attn, prompt_act, prompt_xnorm, prompt_ssq, prompt_max_x, prompt_max_attn, prompt_max_act,
+      total_prompt;        // and behind them the buffers of the largest prompt passes
 };
 
 struct Derived {
@@ -48,11 +52,21 @@ struct Derived {
   size_t page_elems, kv_pool_bytes;
 };
 
-// Where the MFMA-ordered copies of the projection matrices lie (element offsets from the start of
+// Where the MFMA-ordered copies of the projection matrices lie (from the start of
 // the tiled region; per layer for the four projections of a layer).
+struct TiledMatrix { size_t elems = 0, blocks = 0; };   // offsets of its tiles and of its blocks' scale words
 struct TiledMap {
-  std::vector<size_t> qkv, o, gateup, down;
-  size_t lens_a = 0, lens_head = 0, lm_head = 0, total = 0;
+  std::vector<TiledMatrix> qkv, o, gateup, down;
+  TiledMatrix lens_a, lens_head, lm_head;
+  size_t total = 0, blocks = 0;
+};
+
+// Where a pass through the layers keeps its rows
+struct PassBuffers {
+  float *hidden, *q, *attn, *act, *xnorm;
+  unsigned long long *ssq;           // two sets of SSQ_WAYS words per row
+  uint8_t *max_x, *max_attn, *max_act;
+  int rows;                          // rows that fit
 };
 
 struct Seq {
@@ -78,6 +92,7 @@ struct spark_ctx {
   char *scratch;
   void *kv_pool;
   int n_cu;
+  PassBuffers base, prompt, pb;   // of every pass; of large prompt passes (rows 0: none); of the pass being enqueued
   std::vector<Seq> seqs;
   std::vector<int> free_pages;
   int *h_in;   // pinned: seq_ids[max_batch] + forced[MAX_STEPS][max_batch]
@@ -86,8 +101,11 @@ struct spark_ctx {
   // kernel selection; the defaults are the measured choices, spark_tune moves them (tests, sweeps)
   bool mfma_ok = true;         // the shape allows the MFMA projections (16-byte vectors of 8 weights)
   bool use_mfma = true;        // "mfma" = 0 keeps every row count on the vector kernels
+  int tiled_row_blocks = 4;     // blocks of 32 rows in a tile of mfma_tiled_k, at most
+  int direct_max_rows = 32;     // rows up to which mfma_direct_k runs
+  int direct_whole_k = 8192;    // ... and the longest k that it never cuts
   int mfma_xcd_max_split = 4;  // row tiles share an XCD when k has at most this many ranges
-  int mfma_small_tiles = 32;   // launches with fewer 8-wave tiles use 4-wave workgroups
+  int mfma_small_tiles = 64;   // launches with fewer 8-wave tiles use 4-wave workgroups (mfma_rows_k), 32 tasks a wave (mfma_tiled_k)
   int mfma_min_rows = MFMA_MIN_ROWS;
   int attn_pieces = 0;         // 64-token pieces per attention workgroup (0: by the launch's size)
   int gemv_big_kb = 40;        // vector-kernel launches with more LDS per workgroup run eight waves per workgroup
@@ -99,7 +117,8 @@ struct spark_ctx {
   bool static_scratch = false; // the scratch area is the library's static device array (spark_init_static)
   int device = 0;
   float temperature = 0.f, top_p = 0.f;   // nucleus sampling, off while temperature <= 0
-  int prefill_chunk = 128;   // prompt rows per pass, see spark_init
+  int prefill_base = 128;    // prompt rows per pass in the base buffers, see spark_init
+  int prefill_chunk = 0;     // > 0: as set by "prefill_rows"
   int attn_splits_now = 0;   // context slices the rows of the passes being enqueued can reach (0: unknown, launch all)
   std::map<std::pair<const void *, size_t>, int> occ_cache;  // workgroups per CU of a (kernel, LDS bytes)
   // profiling of one kernel class
@@ -215,7 +234,12 @@ void tiled_map(const spark_config &c, const Derived &d, TiledMap &tm) {
   if (!shape_allows_mfma(c)) return;
   const int dm = c.d_model, qw = c.n_q_heads * c.head_dim, F = c.d_ffn;
   size_t o = 0;
-  auto take = [&](int n_tasks, int n_in) { size_t at = o; o += tg_tiled_elems(n_tasks, n_in); return at; };
+  auto take = [&](int n_tasks, int n_in) {
+    const TiledMatrix w{o, tm.blocks};
+    o += tg_tiled_elems(n_tasks, n_in);
+    tm.blocks += tg_blocks(n_tasks);
+    return w;
+  };
   for (int l = 0; l < c.n_layers; ++l) {
     tm.qkv.push_back(take((c.n_q_heads + 2 * c.n_kv_heads) * (c.head_dim / 2), dm));
     tm.o.push_back(take(dm / 2, qw));
@@ -228,6 +252,12 @@ void tiled_map(const spark_config &c, const Derived &d, TiledMap &tm) {
   tm.total = o;
 }
 
+// bytes per row of the lists of largest magnitudes, at most: one per block of 16 tasks of a residual
+// projection, per wave of the attention workgroups that merge a row, per block of 16 MLP activations
+int max_x_bytes(const spark_config &c) { return (int)align_up((c.d_model / 2 + TG_TASKS - 1) / TG_TASKS, 16); }
+int max_attn_bytes(const spark_config &c) { return (int)align_up(c.n_q_heads * (ATTN_THREADS / 64), 16); }
+int max_act_bytes(const spark_config &c) { return (int)align_up((c.d_ffn + TG_TASKS - 1) / TG_TASKS, 16); }
+
 void layout(const spark_config &c, const Derived &d, Layout &l) {
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
@@ -239,8 +269,8 @@ void layout(const spark_config &c, const Derived &d, Layout &l) {
   l.upper = take(sizeof(RowDesc) * (size_t)c.max_batch * d.rmax);
   l.ee = take(sizeof(RowDesc) * c.max_batch);
   l.full = take(sizeof(RowDesc) * c.max_batch);
-  l.prefill_rows = take(sizeof(RowDesc) * PREFILL_CHUNK);
-  l.prefill_tokens = take(sizeof(int) * PREFILL_CHUNK);
+  l.prefill_rows = take(sizeof(RowDesc) * PROMPT_ROWS);
+  l.prefill_tokens = take(sizeof(int) * PROMPT_ROWS);
   l.seq_ids = take(sizeof(int) * c.max_batch);
   l.forced = take(sizeof(int) * (size_t)MAX_STEPS_PER_CALL * c.max_batch);
   l.step_flags = take(sizeof(int) * c.max_batch);
@@ -248,7 +278,11 @@ void layout(const spark_config &c, const Derived &d, Layout &l) {
   l.out_depth = take(sizeof(int) * (size_t)MAX_STEPS_PER_CALL * c.max_batch);
   l.best = take(sizeof(unsigned long long) * c.max_batch);
   l.arrivals = take(sizeof(int) * (size_t)d.max_rows * c.n_q_heads);   // per (row, group of query heads)
-  l.row_ssq = take(sizeof(unsigned long long) * 2 * SSQ_WAYS * (size_t)d.max_rows);   // sums of squares handed from a finishing launch to the next projection
+  // what the launches of a pass hand each other about a row: sums of squares, lists of largest magnitudes
+  l.row_ssq = take(sizeof(unsigned long long) * 2 * SSQ_WAYS * (size_t)d.max_rows);
+  l.max_x = take((size_t)max_x_bytes(c) * d.max_rows);
+  l.max_attn = take((size_t)max_attn_bytes(c) * d.max_rows);
+  l.max_act = take((size_t)max_act_bytes(c) * d.max_rows);
   l.sample_hist = take(sizeof(unsigned long long) * (size_t)SAMPLE_BINS * c.max_batch);   // zero between launches
   l.sample_arrive = take(sizeof(unsigned) * c.max_batch);
   l.sample_count = take(sizeof(unsigned) * c.max_batch);
@@ -258,13 +292,8 @@ void layout(const spark_config &c, const Derived &d, Layout &l) {
   l.part = take(sizeof(float) * (size_t)d.max_rows * c.n_q_heads * d.n_splits * (c.head_dim + 4));
   l.act = take(sizeof(float) * (size_t)d.max_rows * c.d_ffn);
   l.lens_u = take(sizeof(float) * (size_t)c.max_batch * c.d_model);
-  {
-    const size_t widest = align_up(std::max((size_t)c.d_ffn, std::max((size_t)c.d_model, qw)), 64);
-    l.xsplit = take(sizeof(bf16_t) * 3 * (size_t)d.max_rows * widest);
-    // a second one for the MLP activations: the gate/up kernel writes them while it still reads its input
-    l.xsplit2 = take(c.dtype == SPARK_DTYPE_BF16 ? sizeof(bf16_t) * 3 * (size_t)d.max_rows * widest : 256);
-    l.mfma_part = take(c.dtype == SPARK_DTYPE_BF16 ? MFMA_PARTIAL_BYTES : 256);
-  }
+  l.xnorm = take(c.dtype == SPARK_DTYPE_BF16 ? sizeof(float) * (size_t)d.max_rows * c.d_model : 256);   // normalised rows, for the MFMA projections
+  l.mfma_part = take(c.dtype == SPARK_DTYPE_BF16 ? MFMA_PARTIAL_BYTES : 256);
   l.logits = take(sizeof(float) * (size_t)c.max_batch * d.V);
   l.sample_q = take(sizeof(unsigned) * (size_t)c.max_batch * d.V);   // integer masses of the sampler
   l.sample_cand = take(sizeof(unsigned long long) * (size_t)SAMPLE_CAP * c.max_batch);
@@ -277,7 +306,20 @@ void layout(const spark_config &c, const Derived &d, Layout &l) {
   TiledMap tm;
   tiled_map(c, d, tm);
   l.tiled = o;
-  l.total_tiled = o + align_up(sizeof(bf16_t) * tm.total, 256);
+  l.wmax = o + align_up(sizeof(f16_t) * tm.total, 256);
+  l.total_tiled = l.wmax + align_up(sizeof(uint32_t) * tm.blocks, 256);
+  o = l.total_tiled;
+  const size_t n = shape_allows_mfma(c) ? PROMPT_ROWS : 0;
+  l.prompt_hidden = take(sizeof(float) * n * c.d_model);
+  l.prompt_q = take(sizeof(float) * n * qw);
+  l.prompt_attn = take(sizeof(float) * n * qw);
+  l.prompt_act = take(sizeof(float) * n * c.d_ffn);
+  l.prompt_xnorm = take(sizeof(float) * n * c.d_model);
+  l.prompt_ssq = take(sizeof(unsigned long long) * 2 * SSQ_WAYS * n);
+  l.prompt_max_x = take(max_x_bytes(c) * n);
+  l.prompt_max_attn = take(max_attn_bytes(c) * n);
+  l.prompt_max_act = take(max_act_bytes(c) * n);
+  l.total_prompt = o;
 }
 
 template <typename T> T *at(spark_ctx *c, size_t off) { return (T *)(c->scratch + off); }
@@ -359,14 +401,6 @@ int launch_gemv(spark_ctx *c, const Pro &pro, const Epi &epi, const RowDesc *row
   return prof_end(c, kclass);
 }
 
-size_t xsplit_stride(spark_ctx *c);
-
-// a split-activation buffer seen as rows of `width` elements (padded to the MFMA chunk)
-SplitOut split_target(spark_ctx *c, int width, bool second = false) {
-  return SplitOut{at<bf16_t>(c, second ? c->lo.xsplit2 : c->lo.xsplit), xsplit_stride(c),
-                  (int)align_up(width, MG_KC), width};
-}
-
 KVView kv_view(spark_ctx *c) {
   KVView v;
   v.pool = c->kv_pool;
@@ -383,40 +417,39 @@ constexpr int ATTN_SPLIT_HEADS_MAX_ROWS = 4;
 
 // GT query heads per workgroup
 template <typename WT, int HD, int GT>
-void launch_attention_g(spark_ctx *c, const RowDesc *rows, int m, int layer, const SplitOut &so) {
+void launch_attention_g(spark_ctx *c, const RowDesc *rows, int m, int layer, const float *q, const RowOut &out, RowMax &row_max) {
   const spark_config &g = c->cfg;
   const Derived &d = c->dv;
   float *part = at<float>(c, c->lo.part);
   const int n_groups = (d.group + GT - 1) / GT;
   const int splits = c->attn_splits_now > 0 ? std::min(d.n_splits, c->attn_splits_now) : d.n_splits;
+  row_max.n = g.n_kv_heads * n_groups * (ATTN_THREADS / 64);
   attn_rows_k<WT, HD, GT><<<dim3(splits, g.n_kv_heads * n_groups, m), ATTN_THREADS, 0, c->stream>>>(
-      rows, at<float>(c, c->lo.qbuf), kv_view(c), layer, g.n_q_heads, d.group, d.n_splits,
-      1.0f / sqrtf((float)HD), part, at<int>(c, c->lo.arrivals), at<float>(c, c->lo.attn_out), so);
+      rows, q, kv_view(c), layer, g.n_q_heads, d.group, d.n_splits,
+      1.0f / sqrtf((float)HD), part, at<int>(c, c->lo.arrivals), out, row_max);
 }
 
 template <typename WT, int HD>
-void launch_attention_hd(spark_ctx *c, const RowDesc *rows, int m, int layer, const SplitOut &so) {
+void launch_attention_hd(spark_ctx *c, const RowDesc *rows, int m, int layer, const float *q, const RowOut &out, RowMax &row_max) {
   // a handful of rows: four query heads per workgroup, so that even two KV heads make enough
   // workgroups; many rows: all heads of a KV head together, K and V are read once
   const int group = c->dv.group;
   const int gt = (m <= ATTN_SPLIT_HEADS_MAX_ROWS && group > 2) ? 2 : group;
   switch (gt) {
-    case 1: launch_attention_g<WT, HD, 1>(c, rows, m, layer, so); break;
-    case 2: launch_attention_g<WT, HD, 2>(c, rows, m, layer, so); break;
-    case 3: launch_attention_g<WT, HD, 4>(c, rows, m, layer, so); break;
-    case 4: launch_attention_g<WT, HD, 4>(c, rows, m, layer, so); break;
-    case 5: case 6: case 7: launch_attention_g<WT, HD, 7>(c, rows, m, layer, so); break;
-    case 8: launch_attention_g<WT, HD, 8>(c, rows, m, layer, so); break;
-    default: launch_attention_g<WT, HD, 16>(c, rows, m, layer, so); break;
+    case 1: launch_attention_g<WT, HD, 1>(c, rows, m, layer, q, out, row_max); break;
+    case 2: launch_attention_g<WT, HD, 2>(c, rows, m, layer, q, out, row_max); break;
+    case 3: launch_attention_g<WT, HD, 4>(c, rows, m, layer, q, out, row_max); break;
+    case 4: launch_attention_g<WT, HD, 4>(c, rows, m, layer, q, out, row_max); break;
+    case 5: case 6: case 7: launch_attention_g<WT, HD, 7>(c, rows, m, layer, q, out, row_max); break;
+    case 8: launch_attention_g<WT, HD, 8>(c, rows, m, layer, q, out, row_max); break;
+    default: launch_attention_g<WT, HD, 16>(c, rows, m, layer, q, out, row_max); break;
   }
 }
 
-// split_out: also leave the output as the three bf16 parts the MFMA output projection reads
-template <typename WT> int launch_attention(spark_ctx *c, const RowDesc *rows, int m, int layer, bool split_out) {
-  int rc = prof_begin(c, SPARK_KC_ATTN);
-  if (rc) return rc;
-  const int qw = c->cfg.n_q_heads * c->cfg.head_dim;
-  const SplitOut so = split_out ? split_target(c, qw) : SplitOut{nullptr, 0, 0, 0};
+// row_max: where the rows' largest output magnitudes go, for the MFMA output projection (or no list);
+// its count is set to what the launch writes
+template <typename WT>
+int launch_attention_rows(spark_ctx *c, const RowDesc *rows, int m, int layer, const float *q, const RowOut &out, RowMax &row_max) {
   if (std::is_same<WT, bf16_t>::value && c->cfg.head_dim == 128 && c->dv.group <= 16 && c->use_mfma &&
       m >= c->attn_mfma_min_rows) {
     // the slice tasks on the MFMA units, all query heads of a KV head together; with many
@@ -429,33 +462,52 @@ template <typename WT> int launch_attention(spark_ctx *c, const RowDesc *rows, i
     // few workgroups (a handful of rows, two KV heads): eight query heads per workgroup
     const int heads_per_wg = (tasks < c->n_cu / 2 && c->dv.group > 8) ? 8 : c->dv.group;
     const int wg_per_kv = (c->dv.group + heads_per_wg - 1) / heads_per_wg;
+    row_max.n = c->cfg.n_kv_heads * wg_per_kv * (ATTN_THREADS / 64);
     attn_rows_mfma_k<128><<<dim3((splits + pieces - 1) / pieces, c->cfg.n_kv_heads * wg_per_kv, m), ATTN_THREADS, 0,
                             c->stream>>>(
-        rows, at<float>(c, c->lo.qbuf), kv_view(c), layer, c->cfg.n_q_heads, c->dv.group, heads_per_wg,
+        rows, q, kv_view(c), layer, c->cfg.n_q_heads, c->dv.group, heads_per_wg,
         c->dv.n_splits, pieces, 1.0f / sqrtf(128.0f), at<float>(c, c->lo.part), at<int>(c, c->lo.arrivals),
-        at<float>(c, c->lo.attn_out), so);
-  } else if (c->cfg.head_dim == 128) launch_attention_hd<WT, 128>(c, rows, m, layer, so);
-  else launch_attention_hd<WT, 64>(c, rows, m, layer, so);
+        out, row_max);
+  } else if (c->cfg.head_dim == 128) launch_attention_hd<WT, 128>(c, rows, m, layer, q, out, row_max);
+  else launch_attention_hd<WT, 64>(c, rows, m, layer, q, out, row_max);
   HIP_TRY(c, hipGetLastError());
+  return SPARK_OK;
+}
+
+template <typename WT> int launch_attention(spark_ctx *c, const RowDesc *rows, int m, int layer, const RowOut &out, RowMax &row_max) {
+  int rc = prof_begin(c, SPARK_KC_ATTN);
+  if (rc) return rc;
+  // (the slices' partial results fit for as many rows at a time as a pass in the base buffers has)
+  const size_t qw = (size_t)c->cfg.n_q_heads * c->cfg.head_dim;
+  for (int r0 = 0; r0 < m; r0 += c->base.rows) {
+    RowMax rm = row_max;
+    if (rm.list) rm.list += (size_t)r0 * rm.stride;
+    if ((rc = launch_attention_rows<WT>(c, rows + r0, std::min(c->base.rows, m - r0), layer, c->pb.q + r0 * qw,
+                                        RowOut{out.p + (size_t)r0 * out.stride, out.stride}, rm))) return rc;
+    row_max.n = rm.n;
+  }
   return prof_end(c, SPARK_KC_ATTN);
 }
 
 // ------------------------------------------------------------------ MFMA path (16..128+ rows, bf16)
 
 
-// the three bf16 parts of the split activations are stored one after the other
-size_t xsplit_stride(spark_ctx *c) {
-  const spark_config &g = c->cfg;
-  const size_t widest = align_up(std::max((size_t)g.d_ffn, std::max((size_t)g.d_model, (size_t)g.n_q_heads * g.head_dim)), 64);
-  return (size_t)c->dv.max_rows * widest;
-}
+// Which kernel takes a pass's projections, and with it how the rows that they read lie in memory: a
+// pass of at most 32 rows on tiled weights streams them (mfma_direct_k) and wants operand order.
+bool in_operand_order(spark_ctx *c, int m) { return c->has_tiled && c->use_tiled && m <= std::min(OP_ROWS, c->direct_max_rows); }
+RowOut rows_out(spark_ctx *c, float *p, int m, int width) { return RowOut{p, in_operand_order(c, m) ? 0 : width}; }
 
 int launch_prep(spark_ctx *c, const RowDesc *rows, int m, const float *src, int stride, int indirect,
                 const float *gamma, int n) {
-  prep_rows_k<<<m, 256, 0, c->stream>>>(rows, src, stride, indirect, gamma, c->cfg.rms_eps, n,
-                                        (int)align_up(n, MG_KC), at<bf16_t>(c, c->lo.xsplit), xsplit_stride(c));
+  prep_rows_k<<<m, 256, 0, c->stream>>>(rows, src, stride, indirect, gamma, c->cfg.rms_eps, n, rows_out(c, c->pb.xnorm, m, n),
+                                        RowMax{c->pb.max_x, max_x_bytes(c->cfg), 1});
   HIP_TRY(c, hipGetLastError());
   return SPARK_OK;
+}
+// normalised rows as a projection's input, their magnitudes in `n_max` parts
+ProjIn prepared(spark_ctx *c, int m, int n_max) {
+  const RowOut x = rows_out(c, c->pb.xnorm, m, c->cfg.d_model);
+  return ProjIn{x.p, x.stride, RowMax{c->pb.max_x, max_x_bytes(c->cfg), n_max}, nullptr, 0};
 }
 
 // tasks one thread of the finishing kernel takes: the vocabulary heads reduce their arg-max over 8
@@ -480,146 +532,267 @@ int mfma_occupancy(spark_ctx *c) {
   return found->second;
 }
 
-template <int MTILES, int TB, typename Epi, bool SPLIT>
-int tiled_occupancy(spark_ctx *c) {
-  auto kern = mfma_tiled_k<MTILES, TB, Epi, SPLIT>;
-  const size_t lds = tg_lds_bytes(MTILES);
-  const auto key = std::make_pair((const void *)kern, lds);
-  auto found = c->occ_cache.find(key);
-  if (found == c->occ_cache.end()) {
-    int o = 0;
-    HIP_TRY(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, kern, 64 * TG_WAVES, lds));
-    if (o < 1) return fail(c, SPARK_EHIP, "the tiled MFMA kernel for %d rows does not fit on a CU", 32 * MTILES);
-    found = c->occ_cache.emplace(key, o).first;
+// Ranges of k for `tiles` workgroups' worth of work on n_cu CUs: the count that keeps most of the
+// chip busy over whole rounds, with min_chunks chunks each at least (the pipeline needs a few to fill)
+int choose_split(int tiles, int slots, int n_chunks, int min_chunks, size_t bytes_per_split) {
+  const int most = (int)std::min<size_t>(std::max(1, n_chunks / min_chunks), std::max<size_t>(1, MFMA_PARTIAL_BYTES / bytes_per_split));
+  double best = 0.0;
+  int split = 1;
+  for (int s = 1; s <= std::min(most, MG_MAX_SPLIT); ++s) {
+    const int blocks = tiles * s, rounds = (blocks + slots - 1) / slots;
+    const double util = (double)blocks / ((double)rounds * slots);
+    if (util > best + 0.02) { best = util; split = s; }
   }
-  return found->second;
+  return split;
 }
 
-// tiled: the projection's weights in MFMA operand order (then the kernel that takes them from
-// there runs; its workgroups cover the same tiles of tasks), or nullptr
+template <typename Epi> int launch_finish(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_tasks, const PartialSums &ps) {
+  const dim3 grid(ps.tc.n_cut * ((ps.tasks_per_tile + 31) / 32), (ps.m_pitch + 31) / 32);
+  if (ps.n_split <= 8) mfma_finish_tile_k<Epi, 8><<<grid, 1024, 0, c->stream>>>(epi, rows, m, n_tasks, ps);
+  else mfma_finish_tile_k<Epi, MG_MAX_SPLIT><<<grid, 1024, 0, c->stream>>>(epi, rows, m, n_tasks, ps);
+  HIP_TRY(c, hipGetLastError());
+  return SPARK_OK;
+}
+
+// y = W x for m rows on the copy of the weights in MFMA operand order
+template <int MTILES, int TB, typename Epi>
+int launch_tiled(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,
+                 const TiledMatrix &w, int *max_words) {
+  // an epilogue that adds up a whole row runs in the finishing launch only (and with it the others of
+  // matrices that never have a CU's worth of tiles); one with a running arg-max in the projection only
+  constexpr bool ALWAYS_CUT = EpiRow<Epi>::sum || std::is_same<Epi, EpiResidual<bf16_t>>::value ||
+                              std::is_same<Epi, EpiLensAffine<bf16_t>>::value;
+  constexpr bool NEVER_CUT = EpiHasLocalReduce<Epi>::value;
+  constexpr int TASKS = 32 * TG_WAVES * TB, MROWS = 32 * MTILES;
+  const int n_chunks = (n_in + MG_KC - 1) / MG_KC;
+  TileCover tc;
+  tc.n_task_tiles = (n_tasks + TASKS - 1) / TASKS;
+  tc.n_row_tiles = (m + MROWS - 1) / MROWS;
+  tc.m_pitch = tc.n_row_tiles > 1 ? MROWS : (int)align_up(m, 8);
+  const int tiles = tc.n_task_tiles * tc.n_row_tiles;
+  const size_t tile_bytes = sizeof(float) * (size_t)TASKS * 2 * tc.m_pitch;
+  // (rounds are counted in CUs: one workgroup keeps a CU's share of the memory system or of the
+  // MFMA rate busy, two on a CU share it)
+  tc.n_whole = NEVER_CUT ? tiles : ALWAYS_CUT ? 0 : tiles / c->n_cu * c->n_cu;
+  tc.n_split = 1;
+  const int rest = tiles - tc.n_whole;
+  if (rest) {
+    const int min_chunks = tiles < 32 ? 4 : 8;   // few tiles: shorter k ranges are worth the pipeline fill they cost
+    tc.n_split = choose_split(rest, c->n_cu, n_chunks, min_chunks, tile_bytes * rest);
+    if (tc.n_split == 1 && !ALWAYS_CUT) tc.n_whole = tiles;
+  }
+  tc.n_cut = tiles - tc.n_whole;
+  tc.chunks_per_split = (n_chunks + tc.n_split - 1) / tc.n_split;
+  tc.n_split = (n_chunks + tc.chunks_per_split - 1) / tc.chunks_per_split;
+  tc.xcd_groups = tc.n_row_tiles > 1 && tc.n_split <= c->mfma_xcd_max_split;
+  tc.max_words = tc.n_cut ? 2 : 1;   // (a finishing workgroup writes one word per block of tasks: a wave then does too)
+  if (max_words) *max_words = tc.n_cut ? (n_tasks + 31) / 32 : (n_tasks + 32 * TB - 1) / (32 * TB);
+  const f16_t *tiled = at<f16_t>(c, c->lo.tiled) + w.elems;
+  const uint32_t *wmax = at<uint32_t>(c, c->lo.wmax) + w.blocks;
+  float *part = at<float>(c, c->lo.mfma_part);
+  const int grid = tc.n_whole + tc.n_cut * tc.n_split;
+  const size_t lds = tg_lds_bytes(MTILES);
+  auto launch = [&](auto kern) {
+    if (lds > 65536) {
+      const auto key = std::make_pair((const void *)kern, lds);
+      if (c->occ_cache.find(key) == c->occ_cache.end()) {
+        HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        c->occ_cache.emplace(key, 1);
+      }
+    }
+    kern<<<grid, 64 * TG_WAVES, lds, c->stream>>>(epi, tiled, wmax, rows, m, in, n_in, n_tasks, tc, part);
+    HIP_TRY(c, hipGetLastError());
+    return SPARK_OK;
+  };
+  int rc;
+  if constexpr (ALWAYS_CUT) rc = launch(mfma_tiled_k<MTILES, TB, Epi, false>);
+  else if constexpr (NEVER_CUT) rc = launch(mfma_tiled_k<MTILES, TB, Epi, true>);
+  else rc = tc.n_whole ? launch(mfma_tiled_k<MTILES, TB, Epi, true>) : launch(mfma_tiled_k<MTILES, TB, Epi, false>);
+  if (rc) return rc;
+  if constexpr (!NEVER_CUT) {
+    if (tc.n_cut) return launch_finish(c, epi, rows, m, n_tasks, PartialSums{part, tc.n_split, tc.m_pitch, TASKS, MROWS, tc});
+  }
+  return SPARK_OK;
+}
+
+template <int TB, typename Epi>
+int launch_tiled_rows(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,
+                      const TiledMatrix &w, int *max_words) {
+  // row tiles of equal height, as few as the accumulators allow: every further tile streams the weights again
+  const int blocks = (m + 31) / 32, most = std::min(c->tiled_row_blocks, TB == 1 ? 4 : 3);
+  const int z = (blocks + most - 1) / most, mt = (blocks + z - 1) / z;
+  switch (mt) {
+    case 1:   // (only where mfma_direct_k is switched off)
+    case 2: return launch_tiled<2, TB, Epi>(c, epi, rows, m, n_in, n_tasks, in, w, max_words);
+    case 3: return launch_tiled<3, TB, Epi>(c, epi, rows, m, n_in, n_tasks, in, w, max_words);
+    default:
+      if constexpr (TB == 1) return launch_tiled<4, TB, Epi>(c, epi, rows, m, n_in, n_tasks, in, w, max_words);
+      return fail(c, SPARK_EINVAL, "row tiles of %d blocks", mt);
+  }
+}
+
+// the same for at most 32 rows, in operand order
+template <int NT, bool CUT, typename Epi>
+int launch_direct_tiles(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,
+                        const TiledMatrix &w, int groups, int split, int cps) {
+  auto kern = mfma_direct_k<NT, Epi, CUT>;
+  const size_t lds = td_lds_bytes(NT);
+  if (lds > 65536) {
+    const auto key = std::make_pair((const void *)kern, lds);
+    if (c->occ_cache.find(key) == c->occ_cache.end()) {
+      HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+      c->occ_cache.emplace(key, 1);
+    }
+  }
+  kern<<<groups * split, 64 * TD_WAVES, lds, c->stream>>>(epi, at<f16_t>(c, c->lo.tiled) + w.elems, at<uint32_t>(c, c->lo.wmax) + w.blocks,
+                                                          rows, m, in, n_in, n_tasks, groups, cps, at<float>(c, c->lo.mfma_part),
+                                                          (int)align_up(m, 8));
+  HIP_TRY(c, hipGetLastError());
+  return SPARK_OK;
+}
+template <typename Epi>
+int launch_direct(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,
+                  const TiledMatrix &w, int *max_words) {
+  const int n_chunks = (n_in + MG_KC - 1) / MG_KC, blocks = (n_tasks + TG_TASKS - 1) / TG_TASKS, m_pitch = (int)align_up(m, 8);
+  // A long k with few tasks (down) would be streamed by few CUs, each reading all activations of a
+  // long row: its k is cut over the CUs.  (q/k/v and o, with a k of 3584 and 4096, are as fast on
+  // half of the CUs as cut over all of them, and need no second launch.)
+  constexpr int CUT_TILES = 2;
+  if constexpr (!EpiHasLocalReduce<Epi>::value && !EpiRow<Epi>::max || EpiRow<Epi>::sum) {
+    if (n_in > c->direct_whole_k && blocks < 4 * c->n_cu) {
+      const int groups = (blocks + CUT_TILES - 1) / CUT_TILES;
+      int split = std::max(1, std::min(std::min(c->n_cu / groups, n_chunks / 8), MG_MAX_SPLIT));
+      split = (int)std::min<size_t>(split, std::max<size_t>(1, MFMA_PARTIAL_BYTES / (sizeof(float) * (size_t)groups * CUT_TILES * TG_TASKS * 2 * m_pitch)));
+      const int cps = (n_chunks + split - 1) / split;
+      split = (n_chunks + cps - 1) / cps;
+      if (split > 1) {
+        if (max_words) *max_words = (n_tasks + 31) / 32;
+        if (int rc = launch_direct_tiles<CUT_TILES, true>(c, epi, rows, m, n_in, n_tasks, in, w, groups, split, cps)) return rc;
+        return launch_finish(c, epi, rows, m, n_tasks, PartialSums{at<float>(c, c->lo.mfma_part), split, m_pitch, CUT_TILES * TG_TASKS, OP_ROWS,
+                                                                   TileCover{groups, 1, 0, groups, split, cps, m_pitch, 1, 0}});
+      }
+    }
+  }
+  // tiles per workgroup: as few rounds of CUs as five tiles make, and the last one full
+  int nt = 1;
+  double best = 0.0;
+  for (int n = 1; n <= 5; ++n) {
+    const int groups = (blocks + n - 1) / n, rounds = (groups + c->n_cu - 1) / c->n_cu;
+    const double cost = (double)rounds * n;      // tiles the busiest CU takes
+    if (n == 1 || cost <= best) { best = cost; nt = n; }
+  }
+  const int groups = (blocks + nt - 1) / nt;
+  if (max_words) *max_words = groups;
+  switch (nt) {
+    case 1: return launch_direct_tiles<1, false>(c, epi, rows, m, n_in, n_tasks, in, w, groups, 1, n_chunks);
+    case 2: return launch_direct_tiles<2, false>(c, epi, rows, m, n_in, n_tasks, in, w, groups, 1, n_chunks);
+    case 3: return launch_direct_tiles<3, false>(c, epi, rows, m, n_in, n_tasks, in, w, groups, 1, n_chunks);
+    case 4: return launch_direct_tiles<4, false>(c, epi, rows, m, n_in, n_tasks, in, w, groups, 1, n_chunks);
+    default: return launch_direct_tiles<5, false>(c, epi, rows, m, n_in, n_tasks, in, w, groups, 1, n_chunks);
+  }
+}
+
+// y = W x for m rows on the caller's row-major weights
 template <int MTILES, typename Epi, int WAVES>
-int launch_mfma_shape(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks,
-                      bool may_split, bool second_input, const bf16_t *tiled) {
-  constexpr int TB = WAVES / 4;   // blocks of 32 tasks per wave of the four-wave tiled kernel
-  constexpr bool STATELESS = std::is_same<typename Epi::State, NoState>::value;
+int launch_mfma_shape(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in) {
+  constexpr bool LOCAL = EpiHasLocalReduce<Epi>::value;
   constexpr int TASKS_PER_BLOCK = WAVES * MG_TASKS_PER_WAVE;
   const int mrows = 32 * MTILES;
   const int z = (m + mrows - 1) / mrows;
   const int bx = (n_tasks + TASKS_PER_BLOCK - 1) / TASKS_PER_BLOCK;
   const int n_chunks = (n_in + MG_KC - 1) / MG_KC;
-  // rows of the partial sums: padded to eight only (a pass of eight rows then writes and reads a
-  // quarter of what 32 padded rows would)
+  // rows of the partial sums: padded to eight only
   const int m_pad = (int)align_up(m, 8);
   // resident workgroups on the chip: the k range is split until one round of them has work
-  int occ = tiled ? tiled_occupancy<MTILES, TB, Epi, true>(c) : mfma_occupancy<MTILES, Epi, true, WAVES>(c);
+  int occ = mfma_occupancy<MTILES, Epi, true, WAVES>(c);
   if (occ < 0) return occ;
-  // k splits: the count that keeps most of the chip busy over whole rounds of resident
-  // workgroups, with at least eight chunks each (the pipeline needs a few to fill)
-  int split = 1;
-  if (may_split) {
-    // (the tiled kernel: one workgroup already keeps a CU's share of the memory system busy, and
-    // two on a CU share that CU's throughput, so rounds are counted in CUs)
-    const int slots = (tiled ? 1 : occ) * c->n_cu, tiles = bx * z;
-    const size_t per_split = sizeof(float) * (size_t)n_tasks * 2 * m_pad;
-    // (few tiles: shorter k ranges are worth the pipeline fill they cost)
-    const int min_chunks = tiles < 32 ? 4 : 8;
-    const int max_split = (int)std::min<size_t>(std::max(1, n_chunks / min_chunks), std::max<size_t>(1, MFMA_PARTIAL_BYTES / per_split));
-    double best = 0.0;
-    for (int s = 1; s <= std::min(max_split, 32); ++s) {
-      const int blocks = tiles * s, rounds = (blocks + slots - 1) / slots;
-      const double util = (double)blocks / ((double)rounds * slots);
-      if (util > best + 0.02) { best = util; split = s; }
-    }
-  }
+  const int tiles = bx * z;
+  int split = choose_split(tiles, occ * c->n_cu, n_chunks, tiles < 32 ? 4 : 8, sizeof(float) * (size_t)n_tasks * 2 * m_pad);
   const int cps = (n_chunks + split - 1) / split;
   split = (n_chunks + cps - 1) / cps;
-  const bf16_t *xs = at<bf16_t>(c, second_input ? c->lo.xsplit2 : c->lo.xsplit);
-  const size_t xst = xsplit_stride(c);
   float *part = at<float>(c, c->lo.mfma_part);
   // one-dimensional grid: the kernel deals its ids so that the row tiles of a weight tile share an XCD
   const int xcd_groups = z > 1 && split <= c->mfma_xcd_max_split;
   const int tiles_padded = xcd_groups ? (bx * split + 7) / 8 * 8 : bx * split;
   dim3 grid(tiles_padded * z);
   const size_t lds = mg_lds_bytes(MTILES, WAVES);
-  // (an epilogue that sums over a row runs in the finishing launch only; so does, on tiled
-  // weights, one with a running state: the tiled kernel hands every lane 64 tasks of one row,
-  // the finishing launch reduces the states of a row before they reach memory)
-  if (split > 1 || EpiHasRowSum<Epi>::value || (tiled && !STATELESS)) {
-    if (tiled)
-      mfma_tiled_k<MTILES, TB, Epi, true><<<grid, 64 * TG_WAVES, tg_lds_bytes(MTILES), c->stream>>>(
-          epi, tiled, rows, m, xs, xst, n_in, n_tasks, cps, part, m_pad, bx, split, z, xcd_groups);
-    else
-      mfma_rows_k<MTILES, Epi, true, WAVES><<<grid, 64 * WAVES, lds, c->stream>>>(
-          epi, rows, m, xs, xst, n_in, n_tasks, cps, part, m_pad, bx, split, z, xcd_groups);
-    if constexpr (std::is_same<typename Epi::State, NoState>::value || EpiHasRowSum<Epi>::value) {
-      // epilogues without a running state: stores coalesced over tasks
-      const dim3 fgrid((n_tasks + 31) / 32, (m_pad + 31) / 32);
-      if (split <= 8) mfma_finish_tile_k<Epi, 8><<<fgrid, 1024, 0, c->stream>>>(epi, rows, m, n_tasks, split, part, m_pad);
-      else mfma_finish_tile_k<Epi, MG_MAX_SPLIT><<<fgrid, 1024, 0, c->stream>>>(epi, rows, m, n_tasks, split, part, m_pad);
+  // (an epilogue that sums over a row runs in the finishing launch only)
+  if (split > 1 || EpiRow<Epi>::sum) {
+    mfma_rows_k<MTILES, Epi, true, WAVES><<<grid, 64 * WAVES, lds, c->stream>>>(
+        epi, rows, m, in, n_in, n_tasks, cps, part, m_pad, bx, split, z, xcd_groups);
+    HIP_TRY(c, hipGetLastError());
+    if constexpr (!LOCAL) {
+      return launch_finish(c, epi, rows, m, n_tasks,
+                           PartialSums{part, split, m_pad, n_tasks, m_pad, TileCover{1, 1, 0, 1, split, cps, m_pad, 1, 0}});
     } else {
       const int tpt = finish_tasks_per_thread(epi);
       const int total = ((n_tasks + tpt - 1) / tpt) * m_pad;
       mfma_finish_k<Epi><<<(total + 255) / 256, 256, 0, c->stream>>>(epi, rows, m, n_tasks, split, part, m_pad, tpt);
     }
-  } else if constexpr (!EpiHasRowSum<Epi>::value) {
-    bool done = false;
-    if constexpr (STATELESS) {
-      if (tiled) {
-        mfma_tiled_k<MTILES, TB, Epi, false><<<grid, 64 * TG_WAVES, tg_lds_bytes(MTILES), c->stream>>>(
-            epi, tiled, rows, m, xs, xst, n_in, n_tasks, cps, part, m_pad, bx, split, z, xcd_groups);
-        done = true;
-      }
-    }
-    if (!done) {
-      occ = mfma_occupancy<MTILES, Epi, false, WAVES>(c);
-      if (occ < 0) return occ;
-      mfma_rows_k<MTILES, Epi, false, WAVES><<<grid, 64 * WAVES, lds, c->stream>>>(
-          epi, rows, m, xs, xst, n_in, n_tasks, cps, part, m_pad, bx, split, z, xcd_groups);
-    }
+  } else if constexpr (!EpiRow<Epi>::sum) {
+    occ = mfma_occupancy<MTILES, Epi, false, WAVES>(c);
+    if (occ < 0) return occ;
+    mfma_rows_k<MTILES, Epi, false, WAVES><<<grid, 64 * WAVES, lds, c->stream>>>(
+        epi, rows, m, in, n_in, n_tasks, cps, part, m_pad, bx, split, z, xcd_groups);
   }
   HIP_TRY(c, hipGetLastError());
   return SPARK_OK;
 }
 
 template <int MTILES, typename Epi>
-int launch_mfma_tiles(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks,
-                      bool may_split, const bf16_t *tiled, bool second_input = false) {
+int launch_mfma_tiles(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in) {
   if (n_in % 8) return fail(c, SPARK_EINVAL, "MFMA path needs an input width that is a multiple of 8, not %d", n_in);
   // matrices of few rows and a short k (q/k/v, o, the lens translator): four waves per workgroup,
   // so that the launch has enough workgroups without cutting k into ranges too short to stream
   // (measured at 32 rows: q/k/v 23.5 -> 20.8 us, o 20.2 -> 16.0 us; down, with its long k, and
   // gate/up, with its many tiles, are better off with eight)
   const int tiles8 = ((n_tasks + MG_TASKS_PER_BLOCK - 1) / MG_TASKS_PER_BLOCK) * ((m + 32 * MTILES - 1) / (32 * MTILES));
-  if (tiles8 < c->mfma_small_tiles && n_in <= c->mfma_small_max_k)
-    return launch_mfma_shape<MTILES, Epi, 4>(c, epi, rows, m, n_in, n_tasks, may_split, second_input, tiled);
-  return launch_mfma_shape<MTILES, Epi, 8>(c, epi, rows, m, n_in, n_tasks, may_split, second_input, tiled);
+  const bool few = tiles8 < c->mfma_small_tiles && n_in <= c->mfma_small_max_k;
+  if (few) return launch_mfma_shape<MTILES, Epi, 4>(c, epi, rows, m, n_in, n_tasks, in);
+  return launch_mfma_shape<MTILES, Epi, 8>(c, epi, rows, m, n_in, n_tasks, in);
 }
 
-// y = W x for m rows whose hi/lo split sits in the xhi/xlo buffers
+// y = W x for m rows of `in`; w: the copy of the weights in MFMA operand order, or nullptr; max_words:
+// how many words of each row's list of magnitudes the launch writes, for an epilogue that does
 template <typename Epi>
-int launch_mfma(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks,
-                bool may_split, int kclass, const bf16_t *tiled, bool second_input = false) {
+int launch_mfma(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,
+                int kclass, const TiledMatrix *w, int *max_words = nullptr) {
   int rc = prof_begin(c, kclass);
   if (rc) return rc;
-  if (m <= 32) rc = launch_mfma_tiles<1>(c, epi, rows, m, n_in, n_tasks, may_split, tiled, second_input);
-  else rc = launch_mfma_tiles<2>(c, epi, rows, m, n_in, n_tasks, may_split, tiled, second_input);   // tiles of 64 rows
+  if (w && in_operand_order(c, m)) {
+    rc = launch_direct(c, epi, rows, m, n_in, n_tasks, in, *w, max_words);
+  } else if (w) {
+    // 32 tasks per wave for matrices of few rows (q/k/v, o, down, the lens translator), so that the
+    // launch has enough workgroups without cutting k into ranges too short to stream, and for the
+    // heads, whose tiles are never cut; 64 for the others
+    const int tiles8 = ((n_tasks + MG_TASKS_PER_BLOCK - 1) / MG_TASKS_PER_BLOCK) * ((m + 63) / 64);
+    if constexpr (EpiHasLocalReduce<Epi>::value) {
+      rc = launch_tiled_rows<1>(c, epi, rows, m, n_in, n_tasks, in, *w, max_words);
+    } else {
+      if (n_tasks < TILED_WIDE_TASKS && tiles8 < c->mfma_small_tiles) rc = launch_tiled_rows<1>(c, epi, rows, m, n_in, n_tasks, in, *w, max_words);
+      else rc = launch_tiled_rows<2>(c, epi, rows, m, n_in, n_tasks, in, *w, max_words);
+    }
+  } else {
+    // (mfma_rows_k keeps a running state for one tile of 32 rows at most)
+    if (m <= 32 || EpiHasLocalReduce<Epi>::value) rc = launch_mfma_tiles<1>(c, epi, rows, m, n_in, n_tasks, in);
+    else rc = launch_mfma_tiles<2>(c, epi, rows, m, n_in, n_tasks, in);   // tiles of 64 rows
+  }
   if (rc) return rc;
   return prof_end(c, kclass);
 }
 
-template <typename WT> int launch_attention(spark_ctx *c, const RowDesc *rows, int m, int layer, bool split_out);
 
 // The copy of one projection's weights in MFMA operand order, or nullptr when the context has none
 // (or is told not to use it).
-const bf16_t *tiled_at(spark_ctx *c, size_t elem_off) {
-  return c->has_tiled && c->use_tiled ? at<bf16_t>(c, c->lo.tiled) + elem_off : nullptr;
-}
+const TiledMatrix *tiled_at(spark_ctx *c, const TiledMatrix &w) { return c->has_tiled && c->use_tiled ? &w : nullptr; }
 
 template <typename Epi>
-int tile_one(spark_ctx *c, const Epi &epi, int n_tasks, int n_in, size_t elem_off) {
-  const int n_chunks = (n_in + MG_KC - 1) / MG_KC, n_tb = (n_tasks + 31) / 32;
-  tile_weights_k<<<dim3(n_chunks, n_tb * 2), 256, 0, c->stream>>>(epi, n_tasks, n_in, n_chunks,
-                                                               at<bf16_t>(c, c->lo.tiled) + elem_off);
+int tile_one(spark_ctx *c, const Epi &epi, int n_tasks, int n_in, const TiledMatrix &w) {
+  const int n_chunks = (n_in + MG_KC - 1) / MG_KC, blocks = (int)tg_blocks(n_tasks);
+  uint32_t *wmax = at<uint32_t>(c, c->lo.wmax) + w.blocks;
+  weights_amax_k<<<dim3((n_chunks + TG_AMAX_CHUNKS - 1) / TG_AMAX_CHUNKS, blocks), 256, 0, c->stream>>>(epi, n_tasks, n_in, wmax);
+  tile_weights_k<<<dim3(n_chunks, blocks), 256, 0, c->stream>>>(epi, n_tasks, n_in, n_chunks, wmax,
+                                                               at<f16_t>(c, c->lo.tiled) + w.elems);
   HIP_TRY(c, hipGetLastError());
   return SPARK_OK;
 }
@@ -632,6 +805,7 @@ int build_tiled(spark_ctx *c) {
   const int d = g.d_model, hd = g.head_dim, nq = g.n_q_heads, nkv = g.n_kv_heads, F = g.d_ffn, V = c->dv.V;
   const size_t qw = (size_t)nq * hd, kvw = (size_t)nkv * hd;
   int rc;
+  HIP_TRY(c, hipMemsetAsync(at<uint32_t>(c, c->lo.wmax), 0, sizeof(uint32_t) * c->tm.blocks, c->stream));
   for (int l = 0; l < g.n_layers; ++l) {
     EpiQKV<WT> eq;
     eq.wq = (const WT *)c->w.wq + (size_t)l * qw * d;
@@ -642,8 +816,8 @@ int build_tiled(spark_ctx *c) {
     if ((rc = tile_one(c, eq, (nq + 2 * nkv) * (hd / 2), d, c->tm.qkv[l]))) return rc;
     EpiResidual<WT> eo{(const WT *)c->w.wo + (size_t)l * d * qw, (int)qw, d, nullptr, d};
     if ((rc = tile_one(c, eo, d / 2, (int)qw, c->tm.o[l]))) return rc;
-    EpiSwiGLUSplit<WT> eg{(const WT *)c->w.wg + (size_t)l * F * d, (const WT *)c->w.wu + (size_t)l * F * d, d, F,
-                          SplitOut{nullptr, 0, 0, 0}};
+    EpiSwiGLUMax<WT> eg{(const WT *)c->w.wg + (size_t)l * F * d, (const WT *)c->w.wu + (size_t)l * F * d, d, F,
+                        RowOut{nullptr, 0}, RowMax{nullptr, 0, 0}};
     if ((rc = tile_one(c, eg, F, d, c->tm.gateup[l]))) return rc;
     EpiResidual<WT> ed{(const WT *)c->w.wd + (size_t)l * d * F, F, d, nullptr, d};
     if ((rc = tile_one(c, ed, d / 2, F, c->tm.down[l]))) return rc;
@@ -658,18 +832,26 @@ int build_tiled(spark_ctx *c) {
   return SPARK_OK;
 }
 
-// layers [l0, l1) on m >= 16 rows, bf16 weights
+// layers [l0, l1) on m rows, bf16 weights
 int run_layers_mfma(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
   typedef bf16_t WT;
   const spark_config &g = c->cfg;
   const int d = g.d_model, hd = g.head_dim, nq = g.n_q_heads, nkv = g.n_kv_heads, F = g.d_ffn;
   const size_t qw = (size_t)nq * hd, kvw = (size_t)nkv * hd;
-  float *hidden = at<float>(c, c->lo.hidden);
-  // RMSNorm is linear in 1/rms: the finishing launch of a residual projection writes the split
-  // gamma (.) h for the projection that follows and adds up h's sum of squares per row; that
-  // projection's epilogue scales by 1/rms.  Only the first norm of a run is a launch of its own.
-  unsigned long long *ssq_attn = at<unsigned long long>(c, c->lo.row_ssq);
-  unsigned long long *ssq_mlp = ssq_attn + (size_t)SSQ_WAYS * c->dv.max_rows;
+  float *hidden = c->pb.hidden;
+  const RowOut xnorm = rows_out(c, c->pb.xnorm, m, d), attn_out = rows_out(c, c->pb.attn, m, (int)qw),
+               act = rows_out(c, c->pb.act, m, F);
+  // RMSNorm is linear in 1/rms: the finishing launch of a residual projection writes gamma (.) h
+  // for the projection that follows and adds up h's sum of squares per row; that projection's
+  // epilogue scales by 1/rms.  Only the first norm of a run is a launch of its own.
+  // The sums start at zero: those of the MLP's norm are cleared by q/k/v (read last by gate/up of
+  // the layer before, added to next by o), those of the layer's input by gate/up (read last by
+  // q/k/v, added to next by down).
+  unsigned long long *ssq_in = c->pb.ssq, *ssq_mlp = ssq_in + (size_t)SSQ_WAYS * c->pb.rows;
+  const int ssq_units = m * SSQ_WAYS * (int)sizeof(unsigned long long) / 16;
+  RowMax max_x{c->pb.max_x, max_x_bytes(g), 1};   // (the count: what the launch that wrote the lists last has written)
+  RowMax max_attn{c->pb.max_attn, max_attn_bytes(g), 0};
+  RowMax max_act{c->pb.max_act, max_act_bytes(g), 0};
   const bool fuse = c->fuse_norm;
   int rc;
   for (int l = l0; l < l1; ++l) {
@@ -680,36 +862,45 @@ int run_layers_mfma(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
     eq.wk = (const WT *)c->w.wk + (size_t)l * kvw * d;
     eq.wv = (const WT *)c->w.wv + (size_t)l * kvw * d;
     eq.d = d; eq.nq = nq; eq.nkv = nkv; eq.hd = hd; eq.layer = l;
-    eq.qbuf = at<float>(c, c->lo.qbuf);
+    eq.qbuf = c->pb.q;
     eq.rope = at<float2>(c, c->lo.rope);
     eq.kv = kv_view(c);
-    if (qkv_scaled) eq.scale = RowScale{ssq_attn, 1.0f / (float)d, g.rms_eps};
-    if ((rc = launch_mfma(c, eq, rows, m, d, (nq + 2 * nkv) * (hd / 2), true, SPARK_KC_QKV, tiled_at(c, c->tm.qkv[l])))) return rc;
+    if (qkv_scaled) eq.scale = RowScale{ssq_in, 1.0f / (float)d, g.rms_eps};
+    ProjIn in = prepared(c, m, qkv_scaled ? max_x.n : 1);
+    in.zero = (uint4 *)ssq_mlp;
+    in.n_zero = ssq_units;
+    if ((rc = launch_mfma(c, eq, rows, m, d, (nq + 2 * nkv) * (hd / 2), in, SPARK_KC_QKV, tiled_at(c, c->tm.qkv[l])))) return rc;
 
-    // attention leaves its output split for the MFMA kernel; so does the SwiGLU epilogue below
-    if ((rc = launch_attention<WT>(c, rows, m, l, true))) return rc;
+    if ((rc = launch_attention<WT>(c, rows, m, l, attn_out, max_attn))) return rc;
 
-    EpiSwiGLUSplit<WT> eg{(const WT *)c->w.wg + (size_t)l * F * d, (const WT *)c->w.wu + (size_t)l * F * d,
-                          d, F, split_target(c, F, true)};
+    const ProjIn in_o{attn_out.p, attn_out.stride, max_attn, nullptr, 0};
+    EpiSwiGLUMax<WT> eg{(const WT *)c->w.wg + (size_t)l * F * d, (const WT *)c->w.wu + (size_t)l * F * d,
+                        d, F, act, max_act};
     if (fuse) {
       EpiResidualNorm<WT> eo{(const WT *)c->w.wo + (size_t)l * d * qw, (int)qw, d, hidden, d,
-                             c->w.mlp_norm + (size_t)l * d, split_target(c, d), ssq_mlp};
-      if ((rc = launch_mfma(c, eo, rows, m, (int)qw, d / 2, true, SPARK_KC_OPROJ, tiled_at(c, c->tm.o[l])))) return rc;
+                             c->w.mlp_norm + (size_t)l * d, xnorm, ssq_mlp, max_x};
+      if ((rc = launch_mfma(c, eo, rows, m, (int)qw, d / 2, in_o, SPARK_KC_OPROJ, tiled_at(c, c->tm.o[l]), &max_x.n))) return rc;
       eg.scale = RowScale{ssq_mlp, 1.0f / (float)d, g.rms_eps};
+      in = prepared(c, m, max_x.n);
+      in.zero = (uint4 *)ssq_in;
+      in.n_zero = ssq_units;
     } else {
       EpiResidual<WT> eo{(const WT *)c->w.wo + (size_t)l * d * qw, (int)qw, d, hidden, d};
-      if ((rc = launch_mfma(c, eo, rows, m, (int)qw, d / 2, true, SPARK_KC_OPROJ, tiled_at(c, c->tm.o[l])))) return rc;
+      if ((rc = launch_mfma(c, eo, rows, m, (int)qw, d / 2, in_o, SPARK_KC_OPROJ, tiled_at(c, c->tm.o[l])))) return rc;
       if ((rc = launch_prep(c, rows, m, hidden, d, 1, c->w.mlp_norm + (size_t)l * d, d))) return rc;
+      in = prepared(c, m, 1);
     }
-    if ((rc = launch_mfma(c, eg, rows, m, d, F, true, SPARK_KC_GATEUP, tiled_at(c, c->tm.gateup[l])))) return rc;
+    max_act.n = 0;
+    if ((rc = launch_mfma(c, eg, rows, m, d, F, in, SPARK_KC_GATEUP, tiled_at(c, c->tm.gateup[l]), &max_act.n))) return rc;
 
+    const ProjIn in_d{act.p, act.stride, max_act, nullptr, 0};
     if (fuse && l + 1 < l1) {
       EpiResidualNorm<WT> ed{(const WT *)c->w.wd + (size_t)l * d * F, F, d, hidden, d,
-                             c->w.attn_norm + (size_t)(l + 1) * d, split_target(c, d), ssq_attn};
-      if ((rc = launch_mfma(c, ed, rows, m, F, d / 2, true, SPARK_KC_DOWN, tiled_at(c, c->tm.down[l]), true))) return rc;
+                             c->w.attn_norm + (size_t)(l + 1) * d, xnorm, ssq_in, max_x};
+      if ((rc = launch_mfma(c, ed, rows, m, F, d / 2, in_d, SPARK_KC_DOWN, tiled_at(c, c->tm.down[l]), &max_x.n))) return rc;
     } else {
       EpiResidual<WT> ed{(const WT *)c->w.wd + (size_t)l * d * F, F, d, hidden, d};
-      if ((rc = launch_mfma(c, ed, rows, m, F, d / 2, true, SPARK_KC_DOWN, tiled_at(c, c->tm.down[l]), true))) return rc;
+      if ((rc = launch_mfma(c, ed, rows, m, F, d / 2, in_d, SPARK_KC_DOWN, tiled_at(c, c->tm.down[l])))) return rc;
     }
   }
   return SPARK_OK;
@@ -721,11 +912,19 @@ int run_layers(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
   const spark_config &g = c->cfg;
   if (l0 >= l1 || m <= 0) return SPARK_OK;
   // many rows: the projections are dense contractions for the MFMA units
-  if (std::is_same<WT, bf16_t>::value && m >= c->mfma_min_rows && c->use_mfma)
-    return run_layers_mfma(c, l0, l1, rows, m);
+  if (std::is_same<WT, bf16_t>::value && m >= c->mfma_min_rows && c->use_mfma) {
+    // a residual projection's partial sums of all rows have to fit their buffer: more rows go through
+    // the layers in pieces, in order, so that a piece finds the K and V of the rows before it
+    const int most = (int)(MFMA_PARTIAL_BYTES / (sizeof(float) * align_up(g.d_model, 512))) / 64 * 64;
+    for (int r0 = 0; r0 < m; r0 += most) {
+      const int rc = run_layers_mfma(c, l0, l1, rows + r0, std::min(most, m - r0));
+      if (rc) return rc;
+    }
+    return SPARK_OK;
+  }
   const int d = g.d_model, hd = g.head_dim, nq = g.n_q_heads, nkv = g.n_kv_heads, F = g.d_ffn;
   const size_t qw = (size_t)nq * hd, kvw = (size_t)nkv * hd;
-  float *hidden = at<float>(c, c->lo.hidden);
+  float *hidden = c->pb.hidden;
   int rc;
   for (int l = l0; l < l1; ++l) {
     ProNorm n1{hidden, c->w.attn_norm + (size_t)l * d, g.rms_eps, d, 1};
@@ -734,23 +933,24 @@ int run_layers(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
     eq.wk = (const WT *)c->w.wk + (size_t)l * kvw * d;
     eq.wv = (const WT *)c->w.wv + (size_t)l * kvw * d;
     eq.d = d; eq.nq = nq; eq.nkv = nkv; eq.hd = hd; eq.layer = l;
-    eq.qbuf = at<float>(c, c->lo.qbuf);
+    eq.qbuf = c->pb.q;
     eq.rope = at<float2>(c, c->lo.rope);
     eq.kv = kv_view(c);
     if ((rc = launch_gemv<WT>(c, n1, eq, rows, m, d, (nq + 2 * nkv) * (hd / 2), SPARK_KC_QKV))) return rc;
 
-    if ((rc = launch_attention<WT>(c, rows, m, l, false))) return rc;
+    RowMax no_list{nullptr, 0, 0};
+    if ((rc = launch_attention<WT>(c, rows, m, l, RowOut{c->pb.attn, (int)qw}, no_list))) return rc;
 
-    ProPlain pa{at<float>(c, c->lo.attn_out), (int)qw, 0};
+    ProPlain pa{c->pb.attn, (int)qw, 0};
     EpiResidual<WT> eo{(const WT *)c->w.wo + (size_t)l * d * qw, (int)qw, d, hidden, d};
     if ((rc = launch_gemv<WT>(c, pa, eo, rows, m, (int)qw, d / 2, SPARK_KC_OPROJ))) return rc;
 
     ProNorm n2{hidden, c->w.mlp_norm + (size_t)l * d, g.rms_eps, d, 1};
     EpiSwiGLU<WT> eg{(const WT *)c->w.wg + (size_t)l * F * d, (const WT *)c->w.wu + (size_t)l * F * d,
-                     d, F, at<float>(c, c->lo.act)};
+                     d, F, c->pb.act};
     if ((rc = launch_gemv<WT>(c, n2, eg, rows, m, d, F, SPARK_KC_GATEUP))) return rc;
 
-    ProPlain pd{at<float>(c, c->lo.act), F, 0};
+    ProPlain pd{c->pb.act, F, 0};
     EpiResidual<WT> ed{(const WT *)c->w.wd + (size_t)l * d * F, F, d, hidden, d};
     if ((rc = launch_gemv<WT>(c, pd, ed, rows, m, F, d / 2, SPARK_KC_DOWN))) return rc;
   }
@@ -760,19 +960,16 @@ int run_layers(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
 template <typename WT> int run_lens_head(spark_ctx *c, const RowDesc *rows, int m) {
   const spark_config &g = c->cfg;
   const int d = g.d_model, V = c->dv.V;
-  float *hidden = at<float>(c, c->lo.hidden), *u = at<float>(c, c->lo.lens_u);
+  float *hidden = c->pb.hidden, *u = at<float>(c, c->lo.lens_u);
   int rc;
   if (std::is_same<WT, bf16_t>::value && m >= c->mfma_min_rows && c->use_mfma) {
     if ((rc = launch_prep(c, rows, m, hidden, d, 1, nullptr, d))) return rc;
     EpiLensAffine<bf16_t> ea{(const bf16_t *)c->w.lens_a, c->w.lens_b, hidden, u, d};
-    if ((rc = launch_mfma(c, ea, rows, m, d, d / 2, true, SPARK_KC_LENS, tiled_at(c, c->tm.lens_a)))) return rc;
+    if ((rc = launch_mfma(c, ea, rows, m, d, d / 2, prepared(c, m, 1), SPARK_KC_LENS, tiled_at(c, c->tm.lens_a)))) return rc;
     if ((rc = launch_prep(c, rows, m, u, d, 0, c->w.lens_norm, d))) return rc;
     EpiVocab<bf16_t> ev{(const bf16_t *)c->w.lens_head, d, V, at<float>(c, c->lo.logits),
                         at<unsigned long long>(c, c->lo.best)};
-    rc = prof_begin(c, SPARK_KC_LENS);
-    if (rc) return rc;
-    if ((rc = launch_mfma_tiles<1>(c, ev, rows, m, d, (V + 1) / 2, true, tiled_at(c, c->tm.lens_head)))) return rc;
-    return prof_end(c, SPARK_KC_LENS);
+    return launch_mfma(c, ev, rows, m, d, (V + 1) / 2, prepared(c, m, 1), SPARK_KC_LENS, tiled_at(c, c->tm.lens_head));
   }
   ProPlain ph{hidden, d, 1};
   EpiLensAffine<WT> ea{(const WT *)c->w.lens_a, c->w.lens_b, hidden, u, d};
@@ -789,15 +986,12 @@ template <typename WT> int run_final_head(spark_ctx *c, const RowDesc *rows, int
   const int d = g.d_model, V = c->dv.V;
   if (std::is_same<WT, bf16_t>::value && m >= c->mfma_min_rows && c->use_mfma) {
     int rc;
-    if ((rc = launch_prep(c, rows, m, at<float>(c, c->lo.hidden), d, 1, c->w.final_norm, d))) return rc;
+    if ((rc = launch_prep(c, rows, m, c->pb.hidden, d, 1, c->w.final_norm, d))) return rc;
     EpiVocab<bf16_t> ev{(const bf16_t *)c->w.lm_head, d, V, at<float>(c, c->lo.logits),
                         at<unsigned long long>(c, c->lo.best)};
-    rc = prof_begin(c, SPARK_KC_HEAD);
-    if (rc) return rc;
-    if ((rc = launch_mfma_tiles<1>(c, ev, rows, m, d, (V + 1) / 2, true, tiled_at(c, c->tm.lm_head)))) return rc;
-    return prof_end(c, SPARK_KC_HEAD);
+    return launch_mfma(c, ev, rows, m, d, (V + 1) / 2, prepared(c, m, 1), SPARK_KC_HEAD, tiled_at(c, c->tm.lm_head));
   }
-  ProNorm pn{at<float>(c, c->lo.hidden), c->w.final_norm, g.rms_eps, d, 1};
+  ProNorm pn{c->pb.hidden, c->w.final_norm, g.rms_eps, d, 1};
   EpiVocab<WT> ev{(const WT *)c->w.lm_head, d, V, at<float>(c, c->lo.logits),
                   at<unsigned long long>(c, c->lo.best)};
   return launch_gemv<WT>(c, pn, ev, rows, m, d, (V + 1) / 2, SPARK_KC_HEAD);
@@ -848,7 +1042,7 @@ int enqueue_step(spark_ctx *c, int n, int n_upper, int n_ee, int n_full, const i
   sched_dispatch_k<<<1, SCHED_THREADS, 0, c->stream>>>(c->sp, n, seq_ids, state, lower, upper, ee,
                                                       full, plan, flags, out_depth_dev, best);
   embed_rows_k<WT><<<n, 256, 0, c->stream>>>(lower, state, nullptr, (const WT *)c->w.embed,
-                                             g.d_model, at<float>(c, c->lo.hidden));
+                                             g.d_model, c->pb.hidden);
   HIP_TRY(c, hipGetLastError());
   if ((rc = run_layers<WT>(c, 0, g.exit_layer, lower, n))) return rc;
   if (n_ee && (rc = run_lens_head<WT>(c, ee, n_ee))) return rc;
@@ -1011,24 +1205,37 @@ int decode_chunk(spark_ctx *c, int steps, int n, const int32_t *seq_ids, const i
 
 template <typename WT> int prefill_rows(spark_ctx *c, int id, const int32_t *prompt, int n_rows) {
   const spark_config &g = c->cfg;
-  const int base_slot = g.max_batch * c->dv.rmax;
-  std::vector<RowDesc> rows(PREFILL_CHUNK);
+  // A large pass has its own buffers; one in the base buffers takes the slots behind the sequences'.
+  // Passes are of equal size, in whole tiles of rows, unless their size has been set.
+  const bool large = c->prompt.rows > 0 && c->prefill_chunk == 0 && c->use_tiled && c->use_mfma && n_rows > c->prefill_base;
+  int chunk = c->prefill_chunk > 0 ? c->prefill_chunk : c->prefill_base;
+  if (large) {
+    const int passes = (n_rows + PROMPT_ROWS - 1) / PROMPT_ROWS;
+    chunk = std::min(PROMPT_ROWS, (int)align_up((n_rows + passes - 1) / passes, 128));
+  }
+  const int base_slot = large ? 0 : g.max_batch * c->dv.rmax;
+  std::vector<RowDesc> rows(chunk);
   RowDesc *rows_dev = at<RowDesc>(c, c->lo.prefill_rows);
   int *tok_dev = at<int>(c, c->lo.prefill_tokens);
-  int rc;
-  for (int p0 = 0; p0 < n_rows; p0 += c->prefill_chunk) {
-    const int m = std::min(c->prefill_chunk, n_rows - p0);
+  int rc = SPARK_OK;
+  if (large) c->pb = c->prompt;
+  for (int p0 = 0; p0 < n_rows && rc == SPARK_OK; p0 += chunk) {
+    const int m = std::min(chunk, n_rows - p0);
     for (int r = 0; r < m; ++r) rows[r] = RowDesc{base_slot + r, id, p0 + r, -1};
-    HIP_TRY(c, hipMemcpyAsync(rows_dev, rows.data(), sizeof(RowDesc) * m, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(tok_dev, prompt + p0, sizeof(int) * m, hipMemcpyHostToDevice, c->stream));
-    embed_rows_k<WT><<<m, 256, 0, c->stream>>>(rows_dev, nullptr, tok_dev, (const WT *)c->w.embed,
-                                               g.d_model, at<float>(c, c->lo.hidden));
-    HIP_TRY(c, hipGetLastError());
-    c->attn_splits_now = (p0 + m - 1) / ATTN_SLICE + 1;
-    if ((rc = run_layers<WT>(c, 0, g.n_layers, rows_dev, m))) return rc;
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    auto pass = [&]() {
+      HIP_TRY(c, hipMemcpyAsync(rows_dev, rows.data(), sizeof(RowDesc) * m, hipMemcpyHostToDevice, c->stream));
+      HIP_TRY(c, hipMemcpyAsync(tok_dev, prompt + p0, sizeof(int) * m, hipMemcpyHostToDevice, c->stream));
+      embed_rows_k<WT><<<m, 256, 0, c->stream>>>(rows_dev, nullptr, tok_dev, (const WT *)c->w.embed, g.d_model, c->pb.hidden);
+      HIP_TRY(c, hipGetLastError());
+      c->attn_splits_now = (p0 + m - 1) / ATTN_SLICE + 1;
+      if (int e = run_layers<WT>(c, 0, g.n_layers, rows_dev, m)) return e;
+      HIP_TRY(c, hipStreamSynchronize(c->stream));
+      return SPARK_OK;
+    };
+    rc = pass();
   }
-  return SPARK_OK;
+  c->pb = c->base;
+  return rc;
 }
 
 }  // namespace
@@ -1043,7 +1250,7 @@ int spark_workspace_bytes(const spark_config *cfg, size_t *kv_pool_bytes, size_t
   derive(*cfg, d);
   layout(*cfg, d, l);
   if (kv_pool_bytes) *kv_pool_bytes = d.kv_pool_bytes;
-  if (scratch_bytes) *scratch_bytes = l.total_tiled;
+  if (scratch_bytes) *scratch_bytes = l.total_prompt;
   return SPARK_OK;
 }
 
@@ -1104,12 +1311,21 @@ int init_context(const spark_config *cfg, const spark_weights *weights, void *kv
   // static area never does)
   tiled_map(*cfg, c->dv, c->tm);
   c->has_tiled = !static_scratch && c->tm.total > 0 && scratch_bytes >= c->lo.total_tiled;
+  const Layout &lo = c->lo;
+  c->base = PassBuffers{at<float>(c, lo.hidden), at<float>(c, lo.qbuf), at<float>(c, lo.attn_out), at<float>(c, lo.act),
+                        at<float>(c, lo.xnorm), at<unsigned long long>(c, lo.row_ssq), at<uint8_t>(c, lo.max_x),
+                        at<uint8_t>(c, lo.max_attn), at<uint8_t>(c, lo.max_act), c->dv.max_rows};
+  c->prompt = PassBuffers{at<float>(c, lo.prompt_hidden), at<float>(c, lo.prompt_q), at<float>(c, lo.prompt_attn),
+                          at<float>(c, lo.prompt_act), at<float>(c, lo.prompt_xnorm), at<unsigned long long>(c, lo.prompt_ssq),
+                          at<uint8_t>(c, lo.prompt_max_x), at<uint8_t>(c, lo.prompt_max_attn), at<uint8_t>(c, lo.prompt_max_act),
+                          c->has_tiled && scratch_bytes >= lo.total_prompt ? PROMPT_ROWS : 0};
+  c->pb = c->base;
   // Prompt rows per pass: on the MFMA path the widest projection (gate/up) is cut into tiles of 256
   // weight-row pairs x 64 prompt rows; the row count is chosen so that one round of tiles about
   // fills the chip, which needs no k split and no second kernel for that projection.
   if (c->use_mfma && cfg->dtype == SPARK_DTYPE_BF16) {
     const int x_tiles = (cfg->d_ffn + MG_TASKS_PER_BLOCK - 1) / MG_TASKS_PER_BLOCK;
-    c->prefill_chunk = std::max(128, std::min(PREFILL_CHUNK, 64 * (c->n_cu / std::max(1, x_tiles))));
+    c->prefill_base = std::max(128, std::min(PREFILL_CHUNK, 64 * (c->n_cu / std::max(1, x_tiles))));
   }
   size_t in_ints = (size_t)cfg->max_batch * (1 + MAX_STEPS_PER_CALL);
   size_t out_ints = (size_t)cfg->max_batch * 2 * MAX_STEPS_PER_CALL + PL_WORDS;
@@ -1219,6 +1435,9 @@ int spark_tune(spark_ctx *c, const char *name, int32_t value) {
   else if (k == "prefill_rows") c->prefill_chunk = std::max(32, std::min(PREFILL_CHUNK, (int)value / 32 * 32));
   else if (k == "mfma_small_max_k") c->mfma_small_max_k = std::max(8, (int)value);
   else if (k == "mfma_tiled") c->use_tiled = value != 0;
+  else if (k == "tiled_row_blocks") c->tiled_row_blocks = std::max(2, std::min(4, (int)value));
+  else if (k == "direct_max_rows") c->direct_max_rows = value;
+  else if (k == "direct_whole_k") c->direct_whole_k = value;
   else if (k == "fuse_norm") c->fuse_norm = value != 0;
   else return fail(c, SPARK_EINVAL, "unknown tuning name '%s'", name);
   return SPARK_OK;

@@ -1,0 +1,64 @@
+"""The MFMA projections at the edges of their row tiles, large prompt passes, and activations and
+weights whose magnitudes lie far apart (the projections cut activations into two fp16 parts of a
+row-wise scaled value and keep weights as fp16 scaled by blocks), against the CPU oracle."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from parity_util import TOL, compare_run, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sb():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_09215_amd import binding
+    return binding
+
+
+# input widths that are no multiple of a 64-wide chunk, task counts that end inside a tile
+SHAPE = wl.TINY.shape.replace(name="bf16-edges", dtype=wl.DTYPE_BF16, n_layers=3, d_model=264, n_q_heads=7,
+                              n_kv_heads=1, head_dim=128, d_ffn=1024 + 40, vocab_text=900, vocab_speech=301)
+
+
+@pytest.mark.parametrize("B", [5, 16, 31, 32, 33, 64, 65, 96, 97, 128, 129])
+def test_rows_at_the_edges_of_the_tiles(sb, B):
+    """B sequences on the same schedule: B rows in every pass of the lower layers and of the heads
+    (32 is the last count without LDS, 64, 96 and 128 fill a tile of two, three and four blocks of
+    rows, 129 starts a second tile), up to 4 B in the flushes"""
+    say(f"case {B} rows")
+    weights = wl.make_weights(SHAPE, seed=11, gain_std=0.1)
+    prompts = [wl.make_prompt(SHAPE, 1 + i % 3, seed=60 + i) for i in range(B)]
+    sp = sb.Spark(SHAPE, wl.TINY.schedule, weights, max_batch=B, max_seq_len=64, kv_page_tokens=16)
+    compare_run(sp, SHAPE, wl.TINY.schedule, weights, prompts, [0] * B, 7, label=f"{B} rows")
+    sp.close()
+
+
+@pytest.mark.parametrize("B", [6, 40])
+def test_magnitudes_far_apart(sb, B):
+    """Gains of 2^-30 and 2^30 with weights that undo them, and MLP activations spread over a factor
+    of 1024 within a row, undone by the columns of the down projection: powers of two, so that the
+    model is the same one.  What the two fp16 parts leave out is 2^-23 of an element or 2^-40 of its
+    row's largest, 2^-30 of the smallest elements here, so the tolerance is that of any bf16 model."""
+    say(f"case magnitudes, {B} rows")
+    weights = wl.make_weights(SHAPE, seed=13, gain_std=0.1)
+
+    def times(bits, power):   # exact: no weight comes near the ends of the exponent range
+        return wl.f32_to_bf16_bits(wl.bf16_bits_to_f32(bits) * np.exp2(power).astype(np.float32))
+
+    for gain, power, users in (("attn_norm", -30, ("wq", "wk", "wv")), ("mlp_norm", 30, ("wg", "wu")),
+                               ("final_norm", -20, ("lm_head",))):
+        weights[gain] = (weights[gain] * np.float32(2.0 ** power)).astype(np.float32)
+        for u in users:
+            weights[u] = times(weights[u], np.float32(-power))
+    spread = np.random.Generator(np.random.Philox(5)).integers(-5, 6, size=SHAPE.d_ffn).astype(np.float32)
+    weights["wu"] = times(weights["wu"], spread[None, :, None])
+    weights["wd"] = times(weights["wd"], -spread[None, None, :])
+    prompts = [wl.make_prompt(SHAPE, 3 + 7 * (i % 9), seed=80 + i) for i in range(B)]
+    sp = sb.Spark(SHAPE, wl.TINY.schedule, weights, max_batch=B, max_seq_len=128, kv_page_tokens=16)
+    res = compare_run(sp, SHAPE, wl.TINY.schedule, weights, prompts, [0] * B, 7, label=f"magnitudes, {B} rows")
+    assert res["worst"] <= TOL[wl.DTYPE_BF16]
+    sp.close()
