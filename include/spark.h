@@ -300,7 +300,8 @@ int spark_measure_read(spark_ctx *ctx, const void *buf, size_t bytes, int32_t re
  *   "mfma" (0: every row count stays on the vector kernels), "mfma_min_rows" (rows from which the
  *   projections run on the MFMA units), "mfma_small_tiles", "mfma_xcd_max_split",
  *   "attn_pieces" (64-token pieces per attention workgroup, 0 = by the size of the launch, at most
- *   8), "attn_mfma_min_rows", "gemv_big_kb", "mfma_tiled" (0: the MFMA projections stage the
+ *   8), "attn_mfma_min_rows", "attn_prompt_min_rows" (rows from which a prompt pass shares K and V
+ *   between its rows), "gemv_big_kb", "mfma_tiled" (0: the MFMA projections stage the
  *   caller's weight rows through LDS instead of reading the context's copy in operand order),
  *   "mfma_small_max_k", "direct_max_rows" (rows up to which they do without LDS, at most 32),
  *   "direct_whole_k" (the longest input width whose few tasks those never cut over workgroups),

@@ -500,4 +500,248 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
                                       arrivals + r * gridDim.y + blockIdx.y, out, row_max, &s_last);
 }
 
+// ------------------------------------------------------------------ prompt passes
+//
+// The rows of a prompt pass are consecutive positions of one sequence, so they share their K and V:
+// a workgroup takes one KV head and as many rows as make 128 (row, query head) pairs (8 rows of 16
+// heads, 18 of 7), and reads every K and V row of the context once for all of them.  With one
+// workgroup per row, as above, a prompt of 8192 tokens reads its cache from L2 for every row again
+// (8 MB per row and layer at two KV heads), which is what bounded it.
+//
+// Eight waves: wave w takes the pairs 32 (w % 4) .. + 31, and of the context's 64-token tiles the
+// even ones (w < 4) or the odd ones; the two halves are combined at the end.  Two waves share a
+// SIMD, so that one's softmax runs under the other's MFMAs.  v_mfma_f32_32x32x16_bf16 twice:
+//   scores  S^T[token][pair] = K . Q^T   A: token l % 32, eight elements at 16 s + 8 (l / 32);
+//           B: the pair's scaled query, three bf16 parts that add up to the fp32 value, in
+//           registers for the whole context.
+//   values  O^T[hd][pair] = V^T . P^T    a lane holds 16 of a block's 32 scores of its own pair (tokens
+//           8 i + 4 (l / 32) + 0..3), and since a sum over tokens may take them in any order, those
+//           are its B operand as they are: the probabilities (two bf16 parts, rounded to nearest)
+//           never leave the lane.  A: V^T, staged transposed in LDS, in the same order of tokens.
+// Maximum and sum of a pair live in its two lanes.  K and V of the next tile are on their way in
+// registers while a tile is computed; two LDS buffers per half, one barrier per tile.
+constexpr int AP_PAIRS = 128;                       // (row, query head) pairs of a workgroup
+constexpr int AP_THREADS = 512;
+// rows in LDS, padded so that the 16 lanes of an access meet different banks (and, unlike turned
+// columns, so that every address of a tile is one register and a constant)
+constexpr int AP_KPITCH = 128 + 8, AP_VPITCH = ATTN_SLICE + 4;
+constexpr int AP_K_ELEMS = ATTN_SLICE * AP_KPITCH, AP_V_ELEMS = 128 * AP_VPITCH, AP_BUF_ELEMS = AP_K_ELEMS + AP_V_ELEMS;
+constexpr size_t AP_LDS_BYTES = sizeof(bf16_t) * 2 * 2 * AP_BUF_ELEMS;   // halves, buffers
+typedef __attribute__((ext_vector_type(16))) float attn_f32x16_t;
+
+typedef __attribute__((ext_vector_type(2))) __bf16 attn_bf16x2_t;
+typedef __attribute__((ext_vector_type(2))) float attn_f32x2_t;
+__device__ __forceinline__ unsigned pack_bf16_rn(float a, float b) {   // (one instruction)
+  const attn_f32x2_t f = {a, b};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(f, attn_bf16x2_t));
+}
+
+template <int HD>
+__global__ void __launch_bounds__(AP_THREADS, 2)
+attn_prompt_k(const RowDesc *__restrict__ rows, int m_rows, const float *__restrict__ qbuf, KVView kv, int layer, int nq,
+              int group, int rows_per_wg, int n_row_tiles, float scale, RowOut out, RowMax row_max) {
+  static_assert(HD == 128, "tiles and swizzles are for 128 elements");
+  extern __shared__ uint4 ap_smem[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int half = wave >> 2, hl = lane >> 5, col = lane & 31;
+  const int hk = blockIdx.x % kv.n_kv_heads;
+  // the longest contexts first
+  const int tile_row = n_row_tiles - 1 - blockIdx.x / kv.n_kv_heads;
+  const int row0 = tile_row * rows_per_wg, n_rows = min(rows_per_wg, m_rows - row0);
+  const int seq = rows[row0].seq, pos0 = rows[row0].pos;          // the pass's rows are consecutive positions
+  const int n_tiles = (pos0 + n_rows - 1) / ATTN_SLICE + 1, trips = (n_tiles + 1) / 2;
+  const bf16_t *pool = (const bf16_t *)kv.pool;
+  bf16_t *s_k = (bf16_t *)ap_smem + half * 2 * AP_BUF_ELEMS, *s_v = s_k + AP_K_ELEMS;   // + AP_BUF_ELEMS: the other buffer
+
+  // this lane's pair; pairs past the last row repeat a valid one and are not stored
+  const int pair = (wave & 3) * 32 + col;
+  const bool live = pair / group < n_rows;
+  const int row = live ? pair / group : 0, head = hk * group + (live ? pair % group : 0);
+  const int pos = pos0 + row;
+
+  // staging: this thread's share of a tile (of its half): four 16-byte pieces of K (one column of the
+  // tokens kt + 16 i), four of V (one column of the tokens 4 kt .. + 3)
+  const int st = threadIdx.x & 255, kt = st >> 4, kc = st & 15;
+  const bool one_page = (kv.page_tokens & (ATTN_SLICE - 1)) == 0;
+  attn_u32x4_t kv_r[4];   // of K or of V: K of the next tile goes to LDS before its V is asked for
+  auto load_kv = [&](int t, int which) {
+    const int t0 = min(t, n_tiles - 1) * ATTN_SLICE, last = pos0 + n_rows - 1;   // tokens past the last row: that one, masked
+    const size_t tile = one_page ? kv_elem_offset(kv, seq, t0, layer, which, hk) : 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int tok = min(t0 + (which ? 4 * kt + i : kt + 16 * i), last);
+      const size_t at = one_page ? tile + (size_t)(tok - t0) * HD : kv_elem_offset(kv, seq, tok, layer, which, hk);
+      kv_r[i] = *(const attn_u32x4_t *)(pool + at + kc * 8);
+    }
+  };
+  auto store_k = [&](int buf) {
+    bf16_t *d = s_k + buf * AP_BUF_ELEMS + kt * AP_KPITCH + kc * 8;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *(attn_u32x4_t *)(d + 16 * i * AP_KPITCH) = kv_r[i];
+  };
+  auto store_v = [&](int buf) {
+    bf16_t *d = s_v + buf * AP_BUF_ELEMS + 8 * kc * AP_VPITCH + 4 * kt;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {   // element 8 kc + e of four tokens
+      const unsigned sel = (e & 1) ? 0x07060302u : 0x05040100u;
+      const attn_u32x2_t w = {__builtin_amdgcn_perm(kv_r[1][e >> 1], kv_r[0][e >> 1], sel),
+                              __builtin_amdgcn_perm(kv_r[3][e >> 1], kv_r[2][e >> 1], sel)};
+      *(attn_u32x2_t *)(d + e * AP_VPITCH) = w;
+    }
+  };
+  load_kv(half, 0);
+  store_k(0);
+  load_kv(half, 1);
+  store_v(0);
+  __builtin_amdgcn_sched_barrier(0);
+
+  // the scaled query, three bf16 parts (truncation, exact remainders)
+  attn_bf16x8_t qp[3][HD / 16];
+  {
+    const float *q = qbuf + ((size_t)(row0 + row) * nq + head) * HD + 8 * hl;
+#pragma unroll
+    for (int s = 0; s < HD / 16; ++s) {
+      const float4 a = *(const float4 *)(q + 16 * s), b = *(const float4 *)(q + 16 * s + 4);
+      const float f[8] = {a.x * scale, a.y * scale, a.z * scale, a.w * scale, b.x * scale, b.y * scale, b.z * scale, b.w * scale};
+      unsigned hi[8], mi[8], lo[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        hi[e] = __float_as_uint(f[e]) & 0xffff0000u;
+        const float r1 = f[e] - __uint_as_float(hi[e]);
+        mi[e] = __float_as_uint(r1) & 0xffff0000u;
+        lo[e] = __float_as_uint(r1 - __uint_as_float(mi[e]));
+      }
+      attn_u32x4_t ph, pm, pl;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        ph[e] = (hi[2 * e] >> 16) | hi[2 * e + 1];
+        pm[e] = (mi[2 * e] >> 16) | mi[2 * e + 1];
+        pl[e] = (lo[2 * e] >> 16) | (lo[2 * e + 1] & 0xffff0000u);
+      }
+      qp[0][s] = __builtin_bit_cast(attn_bf16x8_t, ph);
+      qp[1][s] = __builtin_bit_cast(attn_bf16x8_t, pm);
+      qp[2][s] = __builtin_bit_cast(attn_bf16x8_t, pl);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  __syncthreads();
+
+  float run_max = -INFINITY, run_sum = 0.f;   // the sum: over this lane's tokens
+  attn_f32x16_t o[HD / 32];
+#pragma unroll
+  for (int b = 0; b < HD / 32; ++b)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
+
+  for (int it = 0; it < trips; ++it) {
+    const int t = 2 * it + half, buf = it & 1;
+    const bool more = it + 1 < trips;
+    const bf16_t *bk = s_k + buf * AP_BUF_ELEMS + col * AP_KPITCH + 8 * hl, *bv = s_v + buf * AP_BUF_ELEMS + col * AP_VPITCH + 4 * hl;
+    if (more) load_kv(t + 2, 0);
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb) {              // 32 tokens at a time
+      if (t < n_tiles) {
+        attn_f32x16_t sc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sc[r] = 0.f;
+#pragma unroll
+        for (int s = 0; s < HD / 16; ++s) {
+          const attn_bf16x8_t ka = __builtin_bit_cast(attn_bf16x8_t, *(const attn_u32x4_t *)(bk + 32 * tb * AP_KPITCH + 16 * s));
+#pragma unroll
+          for (int p = 2; p >= 0; --p) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qp[p][s], sc, 0, 0, 0);
+        }
+        const int t0 = t * ATTN_SLICE + 32 * tb;
+        if (t0 + 31 > pos0) {                     // the tokens reach past the first row
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (t0 + (r >> 2) * 8 + 4 * hl + (r & 3) > pos) sc[r] = -INFINITY;
+        }
+        float mx = sc[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sc[r]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float new_max = fmaxf(run_max, mx);
+        // (a pair of the odd half may have no token yet: nothing to add, and nothing to rescale)
+        const float base = new_max == -INFINITY ? 0.f : new_max;
+        const float alpha = expf(run_max - base);
+        run_max = new_max;
+        float sum = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          sc[r] = expf(sc[r] - base);
+          sum += sc[r];
+        }
+        run_sum = run_sum * alpha + sum;
+        if (__any(alpha != 1.f)) {
+#pragma unroll
+          for (int b = 0; b < HD / 32; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[b][r] *= alpha;
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {             // 16 tokens of them
+          attn_u32x4_t ph, pl;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float p0 = sc[8 * j + 2 * e], p1 = sc[8 * j + 2 * e + 1];
+            ph[e] = pack_bf16_rn(p0, p1);
+            pl[e] = pack_bf16_rn(p0 - __uint_as_float(ph[e] << 16), p1 - __uint_as_float(ph[e] & 0xffff0000u));
+          }
+#pragma unroll
+          for (int b = 0; b < HD / 32; ++b) {
+            const bf16_t *v = bv + 32 * b * AP_VPITCH + 32 * tb + 16 * j;
+            const attn_u32x2_t v0 = *(const attn_u32x2_t *)v, v1 = *(const attn_u32x2_t *)(v + 8);
+            const attn_u32x4_t va = {v0.x, v0.y, v1.x, v1.y};
+            const attn_bf16x8_t a = __builtin_bit_cast(attn_bf16x8_t, va);
+            o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(attn_bf16x8_t, pl), o[b], 0, 0, 0);
+            o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(attn_bf16x8_t, ph), o[b], 0, 0, 0);
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (more) {
+        if (tb == 0) { store_k(buf ^ 1); load_kv(t + 2, 1); }
+        else store_v(buf ^ 1);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
+  }
+
+  // the odd half hands its share to the even one
+  run_sum += __shfl_xor(run_sum, 32, 64);
+  float *s_o = (float *)ap_smem;                  // [4 waves][64 registers + maximum, sum][64 lanes]
+  float *mine = s_o + (wave & 3) * 66 * 64 + lane;
+  if (half == 1) {
+#pragma unroll
+    for (int b = 0; b < HD / 32; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mine[(b * 16 + r) * 64] = o[b][r];
+    mine[64 * 64] = run_max;
+    mine[65 * 64] = run_sum;
+  }
+  __syncthreads();
+  if (half == 1) return;
+  const float other_max = mine[64 * 64], M = fmaxf(run_max, other_max);   // (token 0 is everybody's: finite)
+  const float f0 = expf(run_max - M), f1 = expf(other_max - M);
+  const float inv = 1.0f / (run_sum * f0 + mine[65 * 64] * f1);
+  uint32_t big = 0u;
+#pragma unroll
+  for (int b = 0; b < HD / 32; ++b)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float y[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        y[e] = (o[b][4 * i + e] * f0 + mine[(b * 16 + 4 * i + e) * 64] * f1) * inv;
+        big = max(big, magnitude_bits(y[e]));
+      }
+      if (live) *(float4 *)out.at(row0 + row, head * HD + 32 * b + 8 * i + 4 * hl) = make_float4(y[0], y[1], y[2], y[3]);
+    }
+  if (row_max.list) {
+    big = max(big, (uint32_t)__shfl_xor((int)big, 32, 64));
+    if (live && hl == 0) row_max.put(row0 + row, head, big);
+  }
+}
+
 }  // namespace spark

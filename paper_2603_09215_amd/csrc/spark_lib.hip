@@ -119,6 +119,8 @@ struct spark_ctx {
   float temperature = 0.f, top_p = 0.f;   // nucleus sampling, off while temperature <= 0
   int prefill_base = 128;    // prompt rows per pass in the base buffers, see spark_init
   int prefill_chunk = 0;     // > 0: as set by "prefill_rows"
+  bool prompt_pass = false;  // the pass being enqueued: consecutive positions of one sequence
+  int attn_prompt_min_rows = 64;   // rows from which such a pass shares K and V between its rows
   int attn_splits_now = 0;   // context slices the rows of the passes being enqueued can reach (0: unknown, launch all)
   std::map<std::pair<const void *, size_t>, int> occ_cache;  // workgroups per CU of a (kernel, LDS bytes)
   // profiling of one kernel class
@@ -477,6 +479,23 @@ int launch_attention_rows(spark_ctx *c, const RowDesc *rows, int m, int layer, c
 template <typename WT> int launch_attention(spark_ctx *c, const RowDesc *rows, int m, int layer, const RowOut &out, RowMax &row_max) {
   int rc = prof_begin(c, SPARK_KC_ATTN);
   if (rc) return rc;
+  // the rows of a prompt pass share their sequence's K and V
+  if constexpr (std::is_same<WT, bf16_t>::value) {
+    if (c->prompt_pass && m >= c->attn_prompt_min_rows && c->cfg.head_dim == 128 && c->dv.group <= 16 && c->use_mfma) {
+      auto kern = attn_prompt_k<128>;
+      const auto key = std::make_pair((const void *)kern, AP_LDS_BYTES);
+      if (c->occ_cache.find(key) == c->occ_cache.end()) {
+        HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)AP_LDS_BYTES));
+        c->occ_cache.emplace(key, 1);
+      }
+      const int per = AP_PAIRS / c->dv.group, tiles = (m + per - 1) / per;
+      kern<<<tiles * c->cfg.n_kv_heads, AP_THREADS, AP_LDS_BYTES, c->stream>>>(rows, m, c->pb.q, kv_view(c), layer, c->cfg.n_q_heads, c->dv.group,
+                                                                              per, tiles, 1.0f / sqrtf(128.0f), out, row_max);
+      HIP_TRY(c, hipGetLastError());
+      row_max.n = c->cfg.n_q_heads;
+      return prof_end(c, SPARK_KC_ATTN);
+    }
+  }
   // (the slices' partial results fit for as many rows at a time as a pass in the base buffers has)
   const size_t qw = (size_t)c->cfg.n_q_heads * c->cfg.head_dim;
   for (int r0 = 0; r0 < m; r0 += c->base.rows) {
@@ -1219,6 +1238,7 @@ template <typename WT> int prefill_rows(spark_ctx *c, int id, const int32_t *pro
   int *tok_dev = at<int>(c, c->lo.prefill_tokens);
   int rc = SPARK_OK;
   if (large) c->pb = c->prompt;
+  c->prompt_pass = true;
   for (int p0 = 0; p0 < n_rows && rc == SPARK_OK; p0 += chunk) {
     const int m = std::min(chunk, n_rows - p0);
     for (int r = 0; r < m; ++r) rows[r] = RowDesc{base_slot + r, id, p0 + r, -1};
@@ -1235,6 +1255,7 @@ template <typename WT> int prefill_rows(spark_ctx *c, int id, const int32_t *pro
     rc = pass();
   }
   c->pb = c->base;
+  c->prompt_pass = false;
   return rc;
 }
 
@@ -1436,6 +1457,7 @@ int spark_tune(spark_ctx *c, const char *name, int32_t value) {
   else if (k == "mfma_small_max_k") c->mfma_small_max_k = std::max(8, (int)value);
   else if (k == "mfma_tiled") c->use_tiled = value != 0;
   else if (k == "tiled_row_blocks") c->tiled_row_blocks = std::max(2, std::min(4, (int)value));
+  else if (k == "attn_prompt_min_rows") c->attn_prompt_min_rows = std::max(1, (int)value);
   else if (k == "direct_max_rows") c->direct_max_rows = value;
   else if (k == "direct_whole_k") c->direct_whole_k = value;
   else if (k == "fuse_norm") c->fuse_norm = value != 0;

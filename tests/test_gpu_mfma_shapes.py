@@ -37,6 +37,21 @@ def test_rows_at_the_edges_of_the_tiles(sb, B):
     sp.close()
 
 
+@pytest.mark.parametrize("n,page,group", [(34, 64, 7), (65, 16, 7), (66, 64, 2), (130, 16, 16), (386, 64, 7), (1025, 64, 16),
+                                          (1102, 16, 7)])
+def test_prompt_lengths(sb, n, page, group):
+    """prompts of one pass and of two (1024 rows is the largest pass), ragged last tiles of rows and of
+    tokens, pages smaller than an attention tile, 16, 7 and 2 query heads per KV head: cache entries of
+    every position and the steps behind the prompt"""
+    say(f"case prompt of {n}, pages of {page}, {group} heads")
+    shape = SHAPE.replace(n_q_heads=2 * group, n_kv_heads=2)
+    weights = wl.make_weights(shape, seed=12, gain_std=0.1)
+    sp = sb.Spark(shape, wl.TINY.schedule, weights, max_batch=1, max_seq_len=n + 64, kv_page_tokens=page)
+    compare_run(sp, shape, wl.TINY.schedule, weights, [wl.make_prompt(shape, n, seed=61)], [0], 3, check_kv_every=2,
+                label=f"prompt {n}", kv_all_positions=n < 400)
+    sp.close()
+
+
 @pytest.mark.parametrize("B", [6, 40])
 def test_magnitudes_far_apart(sb, B):
     """Gains of 2^-30 and 2^30 with weights that undo them, and MLP activations spread over a factor
