@@ -36,6 +36,15 @@ template <int HD, int G, int NT> constexpr int attn_lds_floats() {
   return G * ATTN_SLICE + G * 2 + (NT / 64) * G * HD + 4;
 }
 
+// for the MFMA output projection: the largest magnitude of what each wave has written of row r
+template <int NT> __device__ __forceinline__ void put_wave_max(const RowMax &row_max, int r, uint32_t big) {
+  if (!row_max.list) return;
+  const int tid = threadIdx.x % NT;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) big = max(big, (uint32_t)__shfl_xor((int)big, o, 64));
+  if ((tid & 63) == 0) row_max.put(r, blockIdx.y * (NT / 64) + tid / 64, big);
+}
+
 // partial layout: part[((r*nq + hq)*n_splits + split)*(HD+4)] = {o[HD], m, l, pad, pad}
 //
 // Second half of a task, executed by all NT threads that produced the partial of one slice for
@@ -102,12 +111,7 @@ __device__ __forceinline__ void attn_merge(const RowDesc &rd, int r, int hq0, in
     const uint32_t m23 = max(magnitude_bits(acc4.z * inv), magnitude_bits(acc4.w * inv));
     big = max(big, max(m01, m23));
   }
-  // for the MFMA output projection: the largest magnitude of what each wave has written of the row
-  if (row_max.list) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) big = max(big, (uint32_t)__shfl_xor((int)big, o, 64));
-    if ((tid & 63) == 0) row_max.put(r, blockIdx.y * (NT / 64) + tid / 64, big);
-  }
+  put_wave_max<NT>(row_max, r, big);
   if (DS) wait_memory_ops();   // the caller's next barrier arrival does not wait for these stores
 }
 
@@ -225,6 +229,23 @@ __device__ __forceinline__ void attn_task(const RowDesc &rd, int r, int hk, int 
       if (lane < LPT) ored[(wave * G + g) * HD + dc * VEC + e] = a;
     }
   task_sync<NT>();
+  if (rd.pos < ATTN_SLICE) {
+    // the whole context is this slice: nothing to hand over and nobody to wait for (a small fp32
+    // model's contexts of 16 to 80 tokens: 7.3 -> 6.2 us a layer on average, 4.7 without the hand-over)
+    uint32_t big = 0u;
+    for (int i = tid; i < g_count * HD; i += NT) {
+      const int g = i / HD, c = i - g * HD;
+      float o = 0.f;
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) o += ored[(w * G + g) * HD + c];
+      const float inv = 1.0f / ml[g * 2 + 1], y = o * inv;
+      store_maybe_ds<DS>(out.at(r, (hq0 + g) * HD + c), y);
+      big = max(big, magnitude_bits(y));
+    }
+    put_wave_max<NT>(row_max, r, big);
+    if (DS) wait_memory_ops();
+    return;
+  }
   for (int i = tid; i < g_count * HD; i += NT) {
     const int g = i / HD, c = i - g * HD;
     float o = 0.f;
@@ -481,6 +502,24 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
 
   // the slice's partial: weighted values, maximum, sum over the waves
   if (quad == 0) { s_sum[wave * 16 + col] = run_sum; s_max[col] = run_max; }
+  if (rd.pos < span) {   // the whole context is this slice: nothing to hand over and nobody to wait for
+    __syncthreads();
+    uint32_t big = 0u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int g = 4 * quad + i;
+      const float inv = 1.0f / (s_sum[g] + s_sum[16 + g] + s_sum[32 + g] + s_sum[48 + g]);
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        if (g < group) {
+          const float y = oacc[t][i] * inv;
+          *out.at(r, (hq0 + g) * HD + 32 * wave + 16 * t + col) = y;
+          big = max(big, magnitude_bits(y));
+        }
+    }
+    put_wave_max<ATTN_THREADS>(row_max, r, big);
+    return;
+  }
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll

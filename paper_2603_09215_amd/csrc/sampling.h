@@ -270,30 +270,35 @@ sample_pick_k(const float *__restrict__ logits, int V, double top_p, const u64 *
   }
   __syncthreads();
   const int n_local = s_n;
-  if (threadIdx.x == 0 && n_local > 0)
-    s_slot = (int)__hip_atomic_fetch_add(cand_count + row, (unsigned)n_local, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT);
-  __syncthreads();
-  if (n_local > 0) {
-    const int slot = s_slot;
-    for (int j = threadIdx.x; j < n_local && j < SAMPLE_CAP; j += SAMPLE_THREADS)
-      if (slot + j < SAMPLE_CAP)
-        __hip_atomic_store(row_cand + slot + j, s_keys[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  wait_memory_ops();                     // candidates written before the count
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const unsigned prev = __hip_atomic_fetch_add(arrive + row, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = prev == gridDim.x - 1;
-    if (s_last) {
-      __hip_atomic_store(arrive + row, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      s_n = (int)__hip_atomic_load(cand_count + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(cand_count + row, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  // (a row of one workgroup, i.e. a vocabulary of at most SAMPLE_CHUNK, has nobody to wait for and its
+  // candidates in LDS already: 17.4 -> 15.3 us at 1536 logits)
+  const bool alone = gridDim.x == 1;
+  if (!alone) {
+    if (threadIdx.x == 0 && n_local > 0)
+      s_slot = (int)__hip_atomic_fetch_add(cand_count + row, (unsigned)n_local, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (n_local > 0) {
+      const int slot = s_slot;
+      for (int j = threadIdx.x; j < n_local && j < SAMPLE_CAP; j += SAMPLE_THREADS)
+        if (slot + j < SAMPLE_CAP)
+          __hip_atomic_store(row_cand + slot + j, s_keys[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    wait_memory_ops();                     // candidates written before the count
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const unsigned prev = __hip_atomic_fetch_add(arrive + row, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s_last = prev == gridDim.x - 1;
+      if (s_last) {
+        __hip_atomic_store(arrive + row, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_n = (int)__hip_atomic_load(cand_count + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(cand_count + row, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      }
+    }
+    __syncthreads();
+    if (!s_last) return;
   }
-  __syncthreads();
-  if (!s_last) return;
 
   // ---- the last workgroup of the row (every workgroup has read the class masses by now)
   for (int b = threadIdx.x; b < SAMPLE_BINS; b += SAMPLE_THREADS) row_mass[b] = 0;
@@ -303,7 +308,8 @@ sample_pick_k(const float *__restrict__ logits, int V, double top_p, const u64 *
     int np = 64;
     while (np < n) np <<= 1;
     for (int i = threadIdx.x; i < np; i += SAMPLE_THREADS)
-      s_keys[i] = i < n ? __hip_atomic_load(row_cand + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+      if (i >= n) s_keys[i] = 0ull;
+      else if (!alone) s_keys[i] = __hip_atomic_load(row_cand + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // bitonic sort, largest key first
     for (int k = 2; k <= np; k <<= 1)
       for (int j = k >> 1; j > 0; j >>= 1) {
