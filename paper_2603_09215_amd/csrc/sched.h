@@ -62,27 +62,66 @@ __host__ __device__ inline void schedule_decide(const SchedParams &sp, int g, in
 
 constexpr int SCHED_THREADS = 256;  // >= max_batch
 
+// Everything between two steps is a handful of integers per sequence and one row of the embedding:
+// one launch does what three would (a launch costs its 4.6 us whatever it does).
+//   emit      of the step before (has_prev): tokens from the arg-max keys, state advance
+//   dispatch  of the step that follows: row lists, depths, keys cleared
+//   embed     the new rows, when EMBED (a workgroup of 1024 threads, few sequences); otherwise
+//             embed_rows_k follows
+struct StepIO {
+  int n;
+  const int *seq_ids;
+  int *state, *plan, *flags;
+  unsigned long long *best;
+};
+__device__ __forceinline__ void emit_one(const StepIO &io, int i, const int *__restrict__ forced, int *__restrict__ out_tokens) {
+  const int seq = io.seq_ids[i];
+  int *st = io.state + seq * ST_WORDS;
+  const unsigned long long key = io.best[i];
+  if ((uint32_t)(key >> 32) == 0xffffffffu || key == 0ull) atomicOr(io.plan + PL_ERR, ERR_NAN);
+  const int tok = (int)(0xffffffffu - (uint32_t)(key & 0xffffffffull));
+  const int full = io.flags[i] & 1, is_text = (io.flags[i] >> 1) & 1;
+  out_tokens[i] = tok;
+  const int f = forced ? forced[i] : -1;
+  st[ST_LEN] += 1;
+  st[ST_G] += 1;
+  if (!is_text) st[ST_JSTREAM] += 1;
+  st[ST_NPENDING] = full ? 0 : st[ST_NPENDING] + 1;
+  st[ST_NEXT] = f >= 0 ? f : tok;
+  st[ST_LASTFULL] = full;
+}
+
 __global__ void __launch_bounds__(SCHED_THREADS)
-sched_dispatch_k(SchedParams sp, int n, const int *__restrict__ seq_ids, const int *__restrict__ state,
-                 RowDesc *lower, RowDesc *upper, RowDesc *ee, RowDesc *full_rows, int *plan,
-                 int *step_flags, int *out_depth, unsigned long long *best) {
+emit_k(StepIO io, const int *__restrict__ forced, int *__restrict__ out_tokens) {
+  if ((int)threadIdx.x < io.n) emit_one(io, threadIdx.x, forced, out_tokens);
+}
+
+constexpr int EMBED_SEQS = 8;   // sequences whose rows the one workgroup embeds itself
+template <typename WT, bool EMBED>
+__global__ void __launch_bounds__(EMBED ? 1024 : SCHED_THREADS)
+next_step_k(SchedParams sp, StepIO io, int has_prev, const int *__restrict__ forced, int *__restrict__ out_tokens,
+            RowDesc *lower, RowDesc *upper, RowDesc *ee, RowDesc *full_rows, int *out_depth,
+            const WT *__restrict__ embed, int d, float *__restrict__ hidden) {
   __shared__ int s_m[SCHED_THREADS], s_full[SCHED_THREADS];
   __shared__ int s_uoff[SCHED_THREADS], s_hidx[SCHED_THREADS];
-  const int i = threadIdx.x;
+  __shared__ int s_tok[EMBED_SEQS], s_slot[EMBED_SEQS];
+  const int i = threadIdx.x, n = io.n;
   int seq = 0, len = 0, npend = 0, is_text = 0, full = 0;
   if (i < n) {
-    seq = seq_ids[i];
-    const int *st = state + seq * ST_WORDS;
+    if (has_prev) emit_one(io, i, forced, out_tokens);   // (this thread's own sequence: what it writes it reads below)
+    seq = io.seq_ids[i];
+    const int *st = io.state + seq * ST_WORDS;
     len = st[ST_LEN];
     npend = st[ST_NPENDING];
     schedule_decide(sp, st[ST_G], st[ST_OFFSET], st[ST_JSTREAM], st[ST_TEXTBUDGET], st[ST_PHASE], is_text, full);
     lower[i] = RowDesc{seq * sp.rmax + npend, seq, len, i};
     out_depth[i] = full ? sp.n_layers : sp.exit_layer;
-    step_flags[i] = full | (is_text << 1);
-    best[i] = 0ull;
+    io.flags[i] = full | (is_text << 1);
+    io.best[i] = 0ull;
     s_m[i] = full ? npend + 1 : 0;
     s_full[i] = full;
-    if (!st[ST_ACTIVE]) atomicOr(plan + PL_ERR, ERR_INACTIVE);
+    if (EMBED) { s_tok[i] = st[ST_NEXT]; s_slot[i] = seq * sp.rmax + npend; }
+    if (!st[ST_ACTIVE]) atomicOr(io.plan + PL_ERR, ERR_INACTIVE);
   }
   __syncthreads();
   if (i == 0) {
@@ -92,10 +131,10 @@ sched_dispatch_k(SchedParams sp, int n, const int *__restrict__ seq_ids, const i
       u += s_m[b];
       s_hidx[b] = s_full[b] ? nf++ : ne++;
     }
-    plan[PL_NLOWER] = n;
-    plan[PL_NUPPER] = u;
-    plan[PL_NEE] = ne;
-    plan[PL_NFULL] = nf;
+    io.plan[PL_NLOWER] = n;
+    io.plan[PL_NUPPER] = u;
+    io.plan[PL_NEE] = ne;
+    io.plan[PL_NFULL] = nf;
   }
   __syncthreads();
   if (i < n) {
@@ -107,6 +146,19 @@ sched_dispatch_k(SchedParams sp, int n, const int *__restrict__ seq_ids, const i
       full_rows[s_hidx[i]] = cur;
     } else {
       ee[s_hidx[i]] = cur;
+    }
+  }
+  if constexpr (EMBED) {
+    constexpr int VEC = Elem<WT>::VEC;
+    for (int b = 0; b < n; ++b) {
+      const WT *e = embed + (size_t)s_tok[b] * d;
+      float *h = hidden + (size_t)s_slot[b] * d;
+      for (int k = i * VEC; k < d; k += 1024 * VEC) {   // (d is a multiple of 8)
+        float f[VEC];
+        Elem<WT>::unpack(*(const uint4 *)(e + k), f);
+#pragma unroll
+        for (int j = 0; j < VEC; j += 4) *(float4 *)(h + k + j) = make_float4(f[j], f[j + 1], f[j + 2], f[j + 3]);
+      }
     }
   }
 }
@@ -144,28 +196,6 @@ embed_rows_k(const RowDesc *__restrict__ rows, const int *__restrict__ state,
     return;
   }
   for (int k = threadIdx.x; k < d; k += 256) h[k] = Elem<WT>::widen(e[k]);
-}
-
-__global__ void __launch_bounds__(SCHED_THREADS)
-emit_k(int n, const int *__restrict__ seq_ids, const int *__restrict__ forced,
-       const int *__restrict__ step_flags, const unsigned long long *__restrict__ best, int *state,
-       int *plan, int *out_tokens) {
-  const int i = threadIdx.x;
-  if (i >= n) return;
-  const int seq = seq_ids[i];
-  int *st = state + seq * ST_WORDS;
-  const unsigned long long key = best[i];
-  if ((uint32_t)(key >> 32) == 0xffffffffu || key == 0ull) atomicOr(plan + PL_ERR, ERR_NAN);
-  const int tok = (int)(0xffffffffu - (uint32_t)(key & 0xffffffffull));
-  const int full = step_flags[i] & 1, is_text = (step_flags[i] >> 1) & 1;
-  out_tokens[i] = tok;
-  const int f = forced ? forced[i] : -1;
-  st[ST_LEN] += 1;
-  st[ST_G] += 1;
-  if (!is_text) st[ST_JSTREAM] += 1;
-  st[ST_NPENDING] = full ? 0 : st[ST_NPENDING] + 1;
-  st[ST_NEXT] = f >= 0 ? f : tok;
-  st[ST_LASTFULL] = full;
 }
 
 // rope[pos][i] = (cos, sin)(pos * inv_freq[i]), angle formed in fp32, evaluated in fp64

@@ -1049,20 +1049,32 @@ int ensure_pages(spark_ctx *c, int id, int upto) {
   return SPARK_OK;
 }
 
+StepIO step_io(spark_ctx *c, int n) {
+  return StepIO{n, at<int>(c, c->lo.seq_ids), at<int>(c, c->lo.state), at<int>(c, c->lo.plan), at<int>(c, c->lo.step_flags),
+                at<unsigned long long>(c, c->lo.best)};
+}
+
+// One step.  The tokens of the step before it in the same call (prev_tokens: not the first) are
+// emitted by the launch that dispatches this one; prev_forced: the ids forced upon it.
 template <typename WT>
-int enqueue_step(spark_ctx *c, int n, int n_upper, int n_ee, int n_full, const int *forced_dev,
-                 const unsigned long long *rand_dev, int *out_tok_dev, int *out_depth_dev) {
+int enqueue_step(spark_ctx *c, int n, int n_upper, int n_ee, int n_full, const int *prev_forced, int *prev_tokens,
+                 const unsigned long long *rand_dev, int *out_depth_dev) {
   const spark_config &g = c->cfg;
   RowDesc *lower = at<RowDesc>(c, c->lo.lower), *upper = at<RowDesc>(c, c->lo.upper);
   RowDesc *ee = at<RowDesc>(c, c->lo.ee), *full = at<RowDesc>(c, c->lo.full);
-  int *state = at<int>(c, c->lo.state), *plan = at<int>(c, c->lo.plan);
-  int *seq_ids = at<int>(c, c->lo.seq_ids), *flags = at<int>(c, c->lo.step_flags);
   unsigned long long *best = at<unsigned long long>(c, c->lo.best);
   int rc;
-  sched_dispatch_k<<<1, SCHED_THREADS, 0, c->stream>>>(c->sp, n, seq_ids, state, lower, upper, ee,
-                                                      full, plan, flags, out_depth_dev, best);
-  embed_rows_k<WT><<<n, 256, 0, c->stream>>>(lower, state, nullptr, (const WT *)c->w.embed,
-                                             g.d_model, c->pb.hidden);
+  const StepIO io = step_io(c, n);
+  // one workgroup embeds up to eight rows as fast as a second launch would start (as launches of a small model's
+  // step the three took 1.7 + 2.1 + 3.9 us and the gaps between them, this one 3.9)
+  if (n <= EMBED_SEQS) {
+    next_step_k<WT, true><<<1, 1024, 0, c->stream>>>(c->sp, io, prev_tokens != nullptr, prev_forced, prev_tokens, lower, upper, ee, full,
+                                                     out_depth_dev, (const WT *)c->w.embed, g.d_model, c->pb.hidden);
+  } else {
+    next_step_k<WT, false><<<1, SCHED_THREADS, 0, c->stream>>>(c->sp, io, prev_tokens != nullptr, prev_forced, prev_tokens, lower, upper, ee,
+                                                               full, out_depth_dev, (const WT *)c->w.embed, g.d_model, c->pb.hidden);
+    embed_rows_k<WT><<<n, 256, 0, c->stream>>>(lower, io.state, nullptr, (const WT *)c->w.embed, g.d_model, c->pb.hidden);
+  }
   HIP_TRY(c, hipGetLastError());
   if ((rc = run_layers<WT>(c, 0, g.exit_layer, lower, n))) return rc;
   if (n_ee && (rc = run_lens_head<WT>(c, ee, n_ee))) return rc;
@@ -1084,9 +1096,6 @@ int enqueue_step(spark_ctx *c, int n, int n_upper, int n_ee, int n_full, const i
         at<unsigned>(c, c->lo.sample_arrive), best);
     if ((rc = prof_end(c, SPARK_KC_SAMPLE))) return rc;
   }
-  emit_k<<<1, SCHED_THREADS, 0, c->stream>>>(n, seq_ids, forced_dev, flags, best, state, plan,
-                                            out_tok_dev);
-  HIP_TRY(c, hipGetLastError());
   return SPARK_OK;
 }
 
@@ -1168,15 +1177,18 @@ int decode_chunk(spark_ctx *c, int steps, int n, const int32_t *seq_ids, const i
       if (!is_text) mir[i].j += 1;
       mir[i].len += 1;
     }
-    const int *f = forced ? at<int>(c, c->lo.forced) + (size_t)st * n : nullptr;
-    int *ot = at<int>(c, c->lo.out_tokens) + (size_t)st * n;
+    const int *pf = forced && st ? at<int>(c, c->lo.forced) + (size_t)(st - 1) * n : nullptr;
+    int *pt = st ? at<int>(c, c->lo.out_tokens) + (size_t)(st - 1) * n : nullptr;
     int *od = at<int>(c, c->lo.out_depth) + (size_t)st * n;
     const unsigned long long *rw =
         rand_words ? at<unsigned long long>(c, c->lo.rand_words) + (size_t)st * n : nullptr;
-    rc = g.dtype == SPARK_DTYPE_BF16 ? enqueue_step<bf16_t>(c, n, n_upper, n_ee, n_full, f, rw, ot, od)
-                                     : enqueue_step<float>(c, n, n_upper, n_ee, n_full, f, rw, ot, od);
+    rc = g.dtype == SPARK_DTYPE_BF16 ? enqueue_step<bf16_t>(c, n, n_upper, n_ee, n_full, pf, pt, rw, od)
+                                     : enqueue_step<float>(c, n, n_upper, n_ee, n_full, pf, pt, rw, od);
     if (rc) return rc;
   }
+  emit_k<<<1, SCHED_THREADS, 0, c->stream>>>(step_io(c, n), forced ? at<int>(c, c->lo.forced) + (size_t)(steps - 1) * n : nullptr,
+                                            at<int>(c, c->lo.out_tokens) + (size_t)(steps - 1) * n);
+  HIP_TRY(c, hipGetLastError());
 
   // results
   const size_t cnt = (size_t)steps * n;
