@@ -335,18 +335,25 @@ __device__ __forceinline__ void attn_piece_load(AttnPiece &pc, const KVView &kv,
 // `pieces` 64-token pieces per workgroup (slice = 64 * pieces tokens): a workgroup's life is mostly
 // dependent round trips (row descriptor, page table, K/V, partial, arrival), so with many rows it
 // pays to put several pieces behind one such chain; the pieces are folded with a running maximum.
-template <int HD>
-__global__ void __launch_bounds__(ATTN_THREADS)
+// TEAMS = 2: two teams of four waves take the even and the odd pieces and are combined at the end.
+// A piece is a chain of four barriers, about 3 us, and long contexts make as few workgroups as CUs
+// (more of them leave more partial results to one workgroup's merge): a step of eight sequences of 8192
+// tokens 18.63 ms with one team and eight pieces, 17.89 with two teams and ten.
+template <int HD, int TEAMS>
+__global__ void __launch_bounds__(ATTN_THREADS * TEAMS)
 attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbuf, KVView kv, int layer,
                  int nq, int kv_group, int heads_per_wg, int n_splits, int pieces, float scale,
                  float *__restrict__ part, int *__restrict__ arrivals, RowOut out, RowMax row_max) {
   static_assert(HD == 128, "four 32-wide steps per key row, four waves of 32 value columns");
   constexpr int PS = HD + 4;
-  __shared__ __align__(16) bf16_t s_v[ATTN_SLICE * AM_VPITCH];
-  __shared__ __align__(16) bf16_t s_p[2 * 16 * AM_PPITCH];
+  __shared__ __align__(16) bf16_t s_v_all[TEAMS][ATTN_SLICE * AM_VPITCH];
+  __shared__ __align__(16) bf16_t s_p_all[TEAMS][2 * 16 * AM_PPITCH];
   __shared__ __align__(16) bf16_t s_q[3 * 16 * AM_QPITCH];
-  __shared__ float s_max[4 * 16], s_sum[4 * 16], s_alpha[16];
+  __shared__ float s_max_all[TEAMS][4 * 16], s_sum_all[TEAMS][4 * 16], s_alpha_all[TEAMS][16];
   __shared__ int s_last;
+  const int team = TEAMS == 1 ? 0 : threadIdx.x / ATTN_THREADS;
+  bf16_t *s_v = s_v_all[team], *s_p = s_p_all[team];
+  float *s_max = s_max_all[team], *s_sum = s_sum_all[team], *s_alpha = s_alpha_all[team];
   // blockIdx.y = (KV head, part of its query heads): with few rows and few KV heads the query
   // heads of a KV head are dealt to several workgroups, which shortens each one's merge
   const int wg_per_kv = (kv_group + heads_per_wg - 1) / heads_per_wg;
@@ -356,21 +363,26 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
   const RowDesc rd = rows[r];
   const int span = ATTN_SLICE * pieces;
   if (split * span > rd.pos) return;              // slice beyond the row's context
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x % ATTN_THREADS, lane = tid & 63, wave = tid >> 6;   // in the team
   const int col = lane & 15, quad = lane >> 4;    // operand column / row, and which eight of a 32-wide step
   const int hq0 = hk * kv_group + h_first;
   const bf16_t *pool = (const bf16_t *)kv.pool;
   const bool one_page = (kv.page_tokens & (ATTN_SLICE - 1)) == 0;
   const int n_pieces = min(pieces, (rd.pos - split * span) / ATTN_SLICE + 1);   // pieces the context reaches
 
+  const int trips = (n_pieces + TEAMS - 1) / TEAMS;
+  // (a team without a piece left loads the last one again and leaves it)
+  auto load_piece = [&](AttnPiece &pc, int j) {
+    const int t0 = split * span + min(j, n_pieces - 1) * ATTN_SLICE;
+    attn_piece_load<HD>(pc, kv, pool, rd.seq, layer, hk, t0, min(ATTN_SLICE, rd.pos + 1 - t0), one_page, tid, wave, col, quad);
+  };
   AttnPiece cur;
-  attn_piece_load<HD>(cur, kv, pool, rd.seq, layer, hk, split * span, min(ATTN_SLICE, rd.pos + 1 - split * span),
-                      one_page, tid, wave, col, quad);
+  load_piece(cur, team);
 
   // the scaled queries as three bf16 parts that add up to the fp32 value (each part keeps the
   // upper 8 significant bits of what the parts before it left: truncation, exact remainders):
   // split once by the workgroup, eight elements per thread, and handed to the waves through LDS
-  {
+  if (team == 0) {
     const int h = tid >> 4, e0 = (tid & 15) * 8;
     attn_u32x4_t ph = {0u, 0u, 0u, 0u}, pm = ph, pl = ph;
     if (h < group) {
@@ -403,10 +415,11 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
   float run_max = -INFINITY, run_sum = 0.f;       // of head `col`; the sum is this wave's share
   attn_f32x4_t oacc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 
-  for (int j = 0; j < n_pieces; ++j) {
+  for (int trip = 0; trip < trips; ++trip) {
+    const int j = trip * TEAMS + team;
     const int t0 = split * span + j * ATTN_SLICE;
-    const int n_tok = min(ATTN_SLICE, rd.pos + 1 - t0);
-    if (j > 0) __syncthreads();                   // the last piece's V and P have been consumed
+    const int n_tok = j < n_pieces ? min(ATTN_SLICE, rd.pos + 1 - t0) : 0;   // 0: every token is masked
+    if (trip > 0) __syncthreads();                   // the last piece's V and P have been consumed
     // V into LDS as it lies in the cache (4-byte stores: the row pitch is an odd number of dwords)
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
@@ -417,9 +430,7 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
     attn_bf16x8_t ka[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) ka[s] = cur.k[s];
-    if (j + 1 < n_pieces)                          // the next piece's loads fly during this one's arithmetic
-      attn_piece_load<HD>(cur, kv, pool, rd.seq, layer, hk, t0 + ATTN_SLICE,
-                          min(ATTN_SLICE, rd.pos + 1 - t0 - ATTN_SLICE), one_page, tid, wave, col, quad);
+    if (trip + 1 < trips) load_piece(cur, j + TEAMS);   // the next piece's loads fly during this one's arithmetic
     __syncthreads();
 
     // scores of this wave's 16 tokens
@@ -444,13 +455,14 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
     if (quad == 0) s_max[wave * 16 + col] = mw;
     __syncthreads();
     const float piece_max = fmaxf(fmaxf(s_max[col], s_max[16 + col]), fmaxf(s_max[32 + col], s_max[48 + col]));
-    const float new_max = fmaxf(run_max, piece_max);   // finite: token 0 of every piece is real
-    const float alpha = expf(run_max - new_max);       // exp(-inf) = 0 on the first piece
+    const float new_max = fmaxf(run_max, piece_max);   // finite once the team has had a piece: token 0 of it is real
+    const float base = TEAMS == 1 || new_max > -INFINITY ? new_max : 0.f;
+    const float alpha = expf(run_max - base);          // exp(-inf) = 0 on the first piece
     run_max = new_max;
     float pr[4], lw = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      pr[i] = tok0 + i < n_tok ? expf(sc[i] - new_max) : 0.f;
+      pr[i] = tok0 + i < n_tok ? expf(sc[i] - base) : 0.f;
       lw += pr[i];
     }
     lw += __shfl_xor(lw, 16, 64);
@@ -473,7 +485,7 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
     __syncthreads();
 
     // weighted values on top of the rescaled sums of the earlier pieces
-    if (j > 0) {
+    if (trip > 0) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float a = s_alpha[4 * quad + i];
@@ -501,42 +513,80 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
   }
 
   // the slice's partial: weighted values, maximum, sum over the waves
-  if (quad == 0) { s_sum[wave * 16 + col] = run_sum; s_max[col] = run_max; }
+  if (quad == 0) { s_sum[wave * 16 + col] = run_sum; if (wave == 0) s_max[col] = run_max; }
+  if constexpr (TEAMS == 2) {
+    // the odd pieces' team hands its sums over (through its V, which nobody reads any more)
+    float *s_o = (float *)s_v_all[1];   // [8][256]
+    if (team == 1) {
+      __syncthreads();                  // (every wave of both teams is past its last piece)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s_o[(t * 4 + i) * ATTN_THREADS + tid] = oacc[t][i];
+      __syncthreads();
+    } else {
+      __syncthreads();
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int g = 4 * quad + i;
+        const float m0 = s_max_all[0][g], m1 = s_max_all[1][g], M = fmaxf(m0, m1);
+        const float f0 = expf(m0 - M), f1 = expf(m1 - M);   // (the even team has had a piece: M is finite)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) oacc[t][i] = oacc[t][i] * f0 + s_o[(t * 4 + i) * ATTN_THREADS + tid] * f1;
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x < 16) {
+      const int g = threadIdx.x;
+      const float m0 = s_max_all[0][g], m1 = s_max_all[1][g], M = fmaxf(m0, m1);
+      const float f0 = expf(m0 - M), f1 = expf(m1 - M);
+#pragma unroll
+      for (int w = 0; w < 4; ++w) s_sum_all[0][w * 16 + g] = s_sum_all[0][w * 16 + g] * f0 + s_sum_all[1][w * 16 + g] * f1;
+      s_max_all[0][g] = M;
+    }
+  }
+  s_max = s_max_all[0];
+  s_sum = s_sum_all[0];
   if (rd.pos < span) {   // the whole context is this slice: nothing to hand over and nobody to wait for
     __syncthreads();
     uint32_t big = 0u;
+    if (team == 0) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int g = 4 * quad + i;
-      const float inv = 1.0f / (s_sum[g] + s_sum[16 + g] + s_sum[32 + g] + s_sum[48 + g]);
+      for (int i = 0; i < 4; ++i) {
+        const int g = 4 * quad + i;
+        const float inv = 1.0f / (s_sum[g] + s_sum[16 + g] + s_sum[32 + g] + s_sum[48 + g]);
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-        if (g < group) {
-          const float y = oacc[t][i] * inv;
-          *out.at(r, (hq0 + g) * HD + 32 * wave + 16 * t + col) = y;
-          big = max(big, magnitude_bits(y));
-        }
+        for (int t = 0; t < 2; ++t)
+          if (g < group) {
+            const float y = oacc[t][i] * inv;
+            *out.at(r, (hq0 + g) * HD + 32 * wave + 16 * t + col) = y;
+            big = max(big, magnitude_bits(y));
+          }
+      }
     }
-    put_wave_max<ATTN_THREADS>(row_max, r, big);
+    put_wave_max<ATTN_THREADS * TEAMS>(row_max, r, big);
     return;
   }
+  if (team == 0) {
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int g = 4 * quad + i;
-      if (g < group)
-        store_device_scope(part + ((size_t)(r * nq + hq0 + g) * n_splits + split) * PS + 32 * wave + 16 * t + col,
-                           oacc[t][i]);
-    }
-  __syncthreads();
-  if (tid < group * 2) {
-    const int g = tid >> 1;
-    const float v = (tid & 1) ? s_sum[g] + s_sum[16 + g] + s_sum[32 + g] + s_sum[48 + g] : s_max[g];
-    store_device_scope(part + ((size_t)(r * nq + hq0 + g) * n_splits + split) * PS + HD + (tid & 1), v);
+      for (int i = 0; i < 4; ++i) {
+        const int g = 4 * quad + i;
+        if (g < group)
+          store_device_scope(part + ((size_t)(r * nq + hq0 + g) * n_splits + split) * PS + 32 * wave + 16 * t + col,
+                             oacc[t][i]);
+      }
   }
-  attn_merge<HD, ATTN_THREADS, false>(rd, r, hq0, group, nq, n_splits, span, part,
-                                      arrivals + r * gridDim.y + blockIdx.y, out, row_max, &s_last);
+  __syncthreads();
+  if ((int)threadIdx.x < group * 2) {
+    const int g = threadIdx.x >> 1;
+    const float v = (threadIdx.x & 1) ? s_sum[g] + s_sum[16 + g] + s_sum[32 + g] + s_sum[48 + g] : s_max[g];
+    store_device_scope(part + ((size_t)(r * nq + hq0 + g) * n_splits + split) * PS + HD + (threadIdx.x & 1), v);
+  }
+  attn_merge<HD, ATTN_THREADS * TEAMS, false>(rd, r, hq0, group, nq, n_splits, span, part,
+                                              arrivals + r * gridDim.y + blockIdx.y, out, row_max, &s_last);
 }
 
 // ------------------------------------------------------------------ prompt passes

@@ -258,7 +258,7 @@ void tiled_map(const spark_config &c, const Derived &d, TiledMap &tm) {
 // bytes per row of the lists of largest magnitudes, at most: one per block of 16 tasks of a residual
 // projection, per wave of the attention workgroups that merge a row, per block of 16 MLP activations
 int max_x_bytes(const spark_config &c) { return (int)align_up((c.d_model / 2 + TG_TASKS - 1) / TG_TASKS, 16); }
-int max_attn_bytes(const spark_config &c) { return (int)align_up(c.n_q_heads * (ATTN_THREADS / 64), 16); }
+int max_attn_bytes(const spark_config &c) { return (int)align_up(c.n_q_heads * 2 * (ATTN_THREADS / 64), 16); }
 int max_act_bytes(const spark_config &c) { return (int)align_up((c.d_ffn + TG_TASKS - 1) / TG_TASKS, 16); }
 
 void layout(const spark_config &c, const Derived &d, Layout &l) {
@@ -449,28 +449,46 @@ void launch_attention_hd(spark_ctx *c, const RowDesc *rows, int m, int layer, co
   }
 }
 
+// How attn_rows_mfma_k cuts the contexts: 64-token pieces and teams of waves per workgroup.  load: pieces
+// of the launch per CU.  A workgroup's pieces and the merge of a row's slices are two chains that follow
+// each other, one as long as the pieces and one as long as the slices: the sum is least where the pieces go
+// with the root of the context.  With many rows there should be about one workgroup of two teams per CU
+// (pieces as 1.2 times the load), or, beyond three pieces per CU, workgroups of one team at three times
+// that number: they keep more waves in flight, but where a KV head has more than eight query heads
+// the merge is the longer part and eight waves at it win at any load.
+// Measured over 1 .. 48 sequences of 256 .. 8192 tokens on both backbone shapes (114 points, a step against
+// the best fixed choice at each): 0.6 % above it on average and 6 % at worst; one team and 1, 2, 4 or 8
+// pieces by the load alone 5.4 % and 44 % (one sequence of 8192 tokens and two KV heads, 130 slices to merge).
+struct AttnShape { int pieces, teams; };
+AttnShape attn_shape(int splits, double load, int group, int pieces_set) {
+  if (pieces_set > 0) return {pieces_set, pieces_set >= 8 ? 2 : 1};   // (the switch: two teams from eight pieces)
+  const double by_context = 0.6 * std::sqrt((double)splits);
+  if (load < 3.0 || group > 8) {
+    const int pairs = (int)(std::max(by_context, 1.2 * load) / 2.0 + 0.5);
+    return {2 * std::max(1, std::min(5, pairs)), 2};
+  }
+  return {std::max(1, std::min(6, (int)(std::max(by_context, 0.4 * load) + 0.5))), 1};
+}
+
 // row_max: where the rows' largest output magnitudes go, for the MFMA output projection (or no list);
 // its count is set to what the launch writes
 template <typename WT>
 int launch_attention_rows(spark_ctx *c, const RowDesc *rows, int m, int layer, const float *q, const RowOut &out, RowMax &row_max) {
   if (std::is_same<WT, bf16_t>::value && c->cfg.head_dim == 128 && c->dv.group <= 16 && c->use_mfma &&
       m >= c->attn_mfma_min_rows) {
-    // the slice tasks on the MFMA units, all query heads of a KV head together; with many
-    // workgroups to run, several 64-token pieces per workgroup
+    // the slice tasks on the MFMA units, all query heads of a KV head together
     const int splits = c->attn_splits_now > 0 ? std::min(c->dv.n_splits, c->attn_splits_now) : c->dv.n_splits;
     const long tasks = (long)splits * c->cfg.n_kv_heads * m;
-    int pieces = c->attn_pieces > 0 ? c->attn_pieces : (tasks >= 8L * c->n_cu ? 4 : tasks >= 4L * c->n_cu ? 2 : 1);
-    // contexts of 4096 tokens and more: eight pieces (measured on 8 x 8192 tokens: 8.19 -> 8.09 ms per step)
-    if (c->attn_pieces <= 0 && pieces == 4 && splits >= 64) pieces = 8;
+    const AttnShape shape = attn_shape(splits, (double)tasks / c->n_cu, c->dv.group, c->attn_pieces);
+    const int pieces = shape.pieces;
     // few workgroups (a handful of rows, two KV heads): eight query heads per workgroup
     const int heads_per_wg = (tasks < c->n_cu / 2 && c->dv.group > 8) ? 8 : c->dv.group;
     const int wg_per_kv = (c->dv.group + heads_per_wg - 1) / heads_per_wg;
-    row_max.n = c->cfg.n_kv_heads * wg_per_kv * (ATTN_THREADS / 64);
-    attn_rows_mfma_k<128><<<dim3((splits + pieces - 1) / pieces, c->cfg.n_kv_heads * wg_per_kv, m), ATTN_THREADS, 0,
-                            c->stream>>>(
-        rows, q, kv_view(c), layer, c->cfg.n_q_heads, c->dv.group, heads_per_wg,
-        c->dv.n_splits, pieces, 1.0f / sqrtf(128.0f), at<float>(c, c->lo.part), at<int>(c, c->lo.arrivals),
-        out, row_max);
+    row_max.n = c->cfg.n_kv_heads * wg_per_kv * shape.teams * (ATTN_THREADS / 64);
+    const auto kern = shape.teams == 2 ? attn_rows_mfma_k<128, 2> : attn_rows_mfma_k<128, 1>;
+    kern<<<dim3((splits + pieces - 1) / pieces, c->cfg.n_kv_heads * wg_per_kv, m), ATTN_THREADS * shape.teams, 0, c->stream>>>(
+        rows, q, kv_view(c), layer, c->cfg.n_q_heads, c->dv.group, heads_per_wg, c->dv.n_splits, pieces, 1.0f / sqrtf(128.0f),
+        at<float>(c, c->lo.part), at<int>(c, c->lo.arrivals), out, row_max);
   } else if (c->cfg.head_dim == 128) launch_attention_hd<WT, 128>(c, rows, m, layer, q, out, row_max);
   else launch_attention_hd<WT, 64>(c, rows, m, layer, q, out, row_max);
   HIP_TRY(c, hipGetLastError());

@@ -52,6 +52,22 @@ def test_prompt_lengths(sb, n, page, group):
     sp.close()
 
 
+@pytest.mark.parametrize("pieces,long", [(0, 62), (0, 126), (0, 700), (8, 62), (8, 510), (8, 700), (2, 126)])
+def test_attention_workgroups(sb, pieces, long):
+    """contexts that grow over the edge of a 64-token piece, of a pair of pieces and of a workgroup's
+    pieces, with two teams of waves per workgroup (pieces 8, and 0: as the library chooses for so few
+    rows) and with one (2): the second team with no piece at all, with fewer than the first, as many"""
+    say(f"case attention workgroups, {pieces} pieces, {long} tokens")
+    shape = SHAPE.replace(n_q_heads=32, n_kv_heads=2)
+    weights = wl.make_weights(shape, seed=14, gain_std=0.1)
+    sp = sb.Spark(shape, wl.TINY.schedule, weights, max_batch=3, max_seq_len=long + 64, kv_page_tokens=16)
+    sp.tune("attn_pieces", pieces)
+    prompts = [wl.make_prompt(shape, n, seed=90 + n) for n in (long, long // 2, 3)]
+    compare_run(sp, shape, wl.TINY.schedule, weights, prompts, [0, 1, 2], 7, check_kv_every=2,
+                label=f"{pieces} pieces, {long} tokens")
+    sp.close()
+
+
 @pytest.mark.parametrize("B", [6, 40])
 def test_magnitudes_far_apart(sb, B):
     """Gains of 2^-30 and 2^30 with weights that undo them, and MLP activations spread over a factor
