@@ -1,0 +1,112 @@
+// How a launch covers a projection with workgroups, and what its partial sums need: plain integer
+// arithmetic, so that a host program can check it over all shapes without a GPU.
+#pragma once
+#include <stddef.h>
+
+namespace spark {
+
+constexpr int MG_KC = 64;              // k per chunk: one 128-byte line of a weight row, 4 MFMA steps
+constexpr int MG_MAX_SPLIT = 32;       // ranges of k whose sums a finishing launch adds up, at most
+constexpr int TG_WAVES = 4;
+constexpr int TG_TASKS = 16;           // tasks of one A tile
+constexpr int OP_ROWS = 32;            // rows of a pass whose activations lie in operand order, at most
+constexpr int TD_CUT_TILES = 2;        // A tiles of a workgroup of mfma_direct_k whose k is cut
+constexpr size_t MFMA_PARTIAL_BYTES = 48u << 20;  // k-split partial sums of one projection
+
+constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// A tile is 128 * TB tasks x 32 * MTILES activation rows; the
+// first n_whole tiles are one workgroup each, over the whole k range, and end in the epilogue; the
+// n_cut tiles behind them are cut into n_split ranges of k, whose partial sums a finishing launch
+// adds up.  So whole rounds of the chip's CUs do without partial sums, and the tiles that would be
+// a nearly empty last round, or less than one, are spread over all CUs.
+struct TileCover {
+  int n_task_tiles, n_row_tiles;
+  int n_whole, n_cut, n_split, chunks_per_split;
+  int m_pitch;     // rows of a tile's partial sums (a pass of eight rows writes and reads a quarter of 32)
+  int max_words;   // bytes of a row's list of magnitudes that a wave of a whole tile writes: one, or one per block of 32 tasks
+  int xcd_groups;
+};
+
+// bytes of one range's sums of `tiles` tiles, both weight rows of every task
+constexpr size_t range_bytes(int tiles, int tasks_per_tile, int m_pitch) {
+  return sizeof(float) * (size_t)tiles * tasks_per_tile * 2 * m_pitch;
+}
+
+// Ranges of k for `tiles` workgroups' worth of work on n_cu CUs: the count that keeps most of the
+// chip busy over whole rounds, with min_chunks chunks each at least (the pipeline needs a few to fill)
+inline int choose_split(int tiles, int slots, int n_chunks, int min_chunks, size_t bytes_per_split) {
+  int most = n_chunks / min_chunks;
+  const size_t fit = MFMA_PARTIAL_BYTES / bytes_per_split;
+  if ((size_t)most > fit) most = (int)fit;
+  double best = 0.0;
+  int split = 1;
+  for (int s = 1; s <= most && s <= MG_MAX_SPLIT; ++s) {
+    const int blocks = tiles * s, rounds = ceil_div(blocks, slots);
+    const double util = (double)blocks / ((double)rounds * slots);
+    if (util > best + 0.02) { best = util; split = s; }
+  }
+  return split;
+}
+
+// Blocks of 32 rows in a row tile of m rows: row tiles of equal height, as few as `most_blocks`
+// allows, every further tile streams the weights again.  (One block: only where mfma_direct_k is
+// switched off; it runs as a tile of two.)
+inline int tiled_row_blocks_for(int m, int most_blocks) {
+  const int blocks = ceil_div(m, 32), z = ceil_div(blocks, most_blocks), mt = ceil_div(blocks, z);
+  return mt < 2 ? 2 : mt;
+}
+
+// mfma_tiled_k.  always_cut: the epilogue runs in the finishing launch only; never_cut: in the
+// projection only.
+inline TileCover cover_tiled(int m, int n_in, int n_tasks, int mtiles, int tb, bool always_cut, bool never_cut, int n_cu,
+                             int xcd_max_split) {
+  const int tasks = 32 * TG_WAVES * tb, mrows = 32 * mtiles, n_chunks = ceil_div(n_in, MG_KC);
+  TileCover tc;
+  tc.n_task_tiles = ceil_div(n_tasks, tasks);
+  tc.n_row_tiles = ceil_div(m, mrows);
+  tc.m_pitch = tc.n_row_tiles > 1 ? mrows : ceil_div(m, 8) * 8;
+  const int tiles = tc.n_task_tiles * tc.n_row_tiles;
+  // (rounds are counted in CUs: one workgroup keeps a CU's share of the memory system or of the
+  // MFMA rate busy, two on a CU share it)
+  tc.n_whole = never_cut ? tiles : always_cut ? 0 : tiles / n_cu * n_cu;
+  tc.n_split = 1;
+  const int rest = tiles - tc.n_whole;
+  if (rest) {
+    const int min_chunks = tiles < 32 ? 4 : 8;   // few tiles: shorter k ranges are worth the pipeline fill they cost
+    tc.n_split = choose_split(rest, n_cu, n_chunks, min_chunks, range_bytes(rest, tasks, tc.m_pitch));
+    if (tc.n_split == 1 && !always_cut) tc.n_whole = tiles;
+  }
+  tc.n_cut = tiles - tc.n_whole;
+  tc.chunks_per_split = ceil_div(n_chunks, tc.n_split);
+  tc.n_split = ceil_div(n_chunks, tc.chunks_per_split);
+  tc.xcd_groups = tc.n_row_tiles > 1 && tc.n_split <= xcd_max_split;
+  tc.max_words = tc.n_cut ? 2 : 1;   // (a finishing workgroup writes one word per block of tasks: a wave then does too)
+  return tc;
+}
+constexpr size_t tiled_partial_bytes(const TileCover &tc, int tb) {
+  return tc.n_cut ? tc.n_split * range_bytes(tc.n_cut, 32 * TG_WAVES * tb, tc.m_pitch) : 0;
+}
+
+// mfma_direct_k with its k cut: ranges (1: it is not cut) and chunks in each
+inline int direct_split(int m, int n_in, int n_tasks, int n_cu, int &chunks_per_split) {
+  const int n_chunks = ceil_div(n_in, MG_KC), groups = ceil_div(ceil_div(n_tasks, TG_TASKS), TD_CUT_TILES);
+  const size_t fit = MFMA_PARTIAL_BYTES / range_bytes(groups, TD_CUT_TILES * TG_TASKS, ceil_div(m, 8) * 8);
+  int split = n_cu / groups;
+  if (split > n_chunks / 8) split = n_chunks / 8;
+  if (split > MG_MAX_SPLIT) split = MG_MAX_SPLIT;
+  if ((size_t)split > fit) split = (int)fit;
+  if (split < 1) split = 1;
+  chunks_per_split = ceil_div(n_chunks, split);
+  return ceil_div(n_chunks, chunks_per_split);
+}
+
+// Rows that go through the layers together at most: the partial sums of a residual projection
+// (d_model outputs), one range of k at least, have to fit their buffer.  They are written for whole
+// tiles: of 256 tasks (512 outputs), and of 64, 96 or 128 rows, which a multiple of 384 rows holds a
+// whole number of, however the rows up to it are dealt to tiles.
+inline int pass_rows_limit(int d_model) {
+  return (int)(MFMA_PARTIAL_BYTES / (sizeof(float) * (size_t)ceil_div(d_model, 512) * 512)) / 384 * 384;
+}
+
+}  // namespace spark

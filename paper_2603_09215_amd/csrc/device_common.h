@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "cover.h"
+
 namespace spark {
 
 typedef uint16_t bf16_t;  // bf16 bit pattern
@@ -104,7 +106,6 @@ struct RowMax {
 };
 // Where the rows of a pass go that a projection will read: row-major, or for a pass of at most 32
 // rows in the order the projection's matrix operand wants them, [k / 4][32 rows][4].
-constexpr int OP_ROWS = 32;
 struct RowOut {
   float *p;
   int stride;       // elements from row to row; 0: operand order

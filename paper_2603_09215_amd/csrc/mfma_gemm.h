@@ -39,6 +39,7 @@
 // segment), read back as (lane % 32 = row, lane / 32 = segment of the MFMA step).
 #pragma once
 #include <type_traits>
+#include "cover.h"
 #include "device_common.h"
 #include "gemv.h"
 
@@ -51,7 +52,6 @@ typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
 constexpr int MG_THREADS = 512;
 constexpr int MG_WAVES = 8;
-constexpr int MG_KC = 64;              // k per chunk: one 128-byte line of a weight row, 4 MFMA steps
 constexpr int MG_ROWPAD = MG_KC + 8;   // bf16 per staged row (a 16-byte skew per row keeps the operand reads conflict-free)
 constexpr int MG_TASKS_PER_WAVE = 32;
 constexpr int MG_TASKS_PER_BLOCK = MG_WAVES * MG_TASKS_PER_WAVE;
@@ -467,9 +467,7 @@ mfma_rows_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, ProjIn in, in
 // The 32 rows of a block share a power of two that brings their largest weight just below 2^15 (one
 // word per block holds that weight's magnitude).  Both are written once, when the context is
 // created, from the same weight_rows() of the epilogue that the kernels use.
-constexpr int TG_WAVES = 4;
 constexpr int TG_TILE = 32 * MG_KC;   // elements of one A tile of one chunk
-constexpr int TG_TASKS = 16;          // tasks of one A tile
 constexpr int TG_PARTS = 2;           // fp16 parts of an activation
 
 constexpr size_t tg_tiled_elems(int n_tasks, int n_in) {
@@ -533,18 +531,6 @@ tile_weights_k(Epi epi, int n_tasks, int n_in, int n_chunks, const uint32_t *__r
   *(f16x8_t *)(dst + ((size_t)block * n_chunks + c) * TG_TILE + s * 512 + lane * 8) = o;
 }
 
-// How a launch covers a projection.  A tile is 128 * TB tasks x 32 * MTILES activation rows; the
-// first n_whole tiles are one workgroup each, over the whole k range, and end in the epilogue; the
-// n_cut tiles behind them are cut into n_split ranges of k, whose partial sums a finishing launch
-// adds up.  So whole rounds of the chip's CUs do without partial sums, and the tiles that would be
-// a nearly empty last round, or less than one, are spread over all CUs.
-struct TileCover {
-  int n_task_tiles, n_row_tiles;
-  int n_whole, n_cut, n_split, chunks_per_split;
-  int m_pitch;     // rows of a tile's partial sums (a pass of eight rows writes and reads a quarter of 32)
-  int max_words;   // bytes of a row's list of magnitudes that a wave of a whole tile writes: one, or one per block of 32 tasks
-  int xcd_groups;
-};
 // Tile -> (task tile, row tile).  Consecutive workgroup ids go to consecutive XCDs, each with its
 // own L2: the row tiles of one task tile read the same weights, so they get ids 8 apart (same XCD,
 // launched together) and the weights cross HBM once for them.  (xcd_groups: chosen by the launch;
@@ -935,7 +921,6 @@ struct PartialSums {
 // The partial sums of one (task, row) over the k ranges, added in the order of the ranges.  All
 // loads are issued before the first is used: a loop that loads and adds pays a memory round trip
 // per trip, and a projection with few tiles has up to MG_MAX_SPLIT ranges.
-constexpr int MG_MAX_SPLIT = 32;
 // MAXS: the most ranges this instance adds (8 or MG_MAX_SPLIT): the loads live in 2 * MAXS
 // registers, and a finishing launch with hundreds of workgroups wants two of them on a CU
 template <int MAXS>

@@ -29,7 +29,6 @@ namespace {
 
 constexpr int PREFILL_CHUNK = 256;   // most prompt rows pushed through the layers together in the buffers that every context has
 constexpr int PROMPT_ROWS = 1024;    // and in those of a context with tiled weights
-constexpr size_t MFMA_PARTIAL_BYTES = 48u << 20;  // k-split partial sums of one projection
 constexpr int MAX_STEPS_PER_CALL = 256;
 // rows from which the MFMA projections run: up to four rows are one pass of the vector kernel
 // (measured at four rows: level at the GLM shape, 14-20 % faster for a batch of four at the Step
@@ -570,18 +569,10 @@ int mfma_occupancy(spark_ctx *c) {
   return found->second;
 }
 
-// Ranges of k for `tiles` workgroups' worth of work on n_cu CUs: the count that keeps most of the
-// chip busy over whole rounds, with min_chunks chunks each at least (the pipeline needs a few to fill)
-int choose_split(int tiles, int slots, int n_chunks, int min_chunks, size_t bytes_per_split) {
-  const int most = (int)std::min<size_t>(std::max(1, n_chunks / min_chunks), std::max<size_t>(1, MFMA_PARTIAL_BYTES / bytes_per_split));
-  double best = 0.0;
-  int split = 1;
-  for (int s = 1; s <= std::min(most, MG_MAX_SPLIT); ++s) {
-    const int blocks = tiles * s, rounds = (blocks + slots - 1) / slots;
-    const double util = (double)blocks / ((double)rounds * slots);
-    if (util > best + 0.02) { best = util; split = s; }
-  }
-  return split;
+// (a cover is chosen so that its partial sums fit; one that did not would write into what lies behind them)
+int partials_fit(spark_ctx *c, size_t bytes) {
+  if (bytes <= MFMA_PARTIAL_BYTES) return SPARK_OK;
+  return fail(c, SPARK_EINVAL, "partial sums of %zu bytes do not fit their buffer", bytes);
 }
 
 template <typename Epi> int launch_finish(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_tasks, const PartialSums &ps) {
@@ -602,28 +593,8 @@ int launch_tiled(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n
                               std::is_same<Epi, EpiLensAffine<bf16_t>>::value;
   constexpr bool NEVER_CUT = EpiHasLocalReduce<Epi>::value;
   constexpr int TASKS = 32 * TG_WAVES * TB, MROWS = 32 * MTILES;
-  const int n_chunks = (n_in + MG_KC - 1) / MG_KC;
-  TileCover tc;
-  tc.n_task_tiles = (n_tasks + TASKS - 1) / TASKS;
-  tc.n_row_tiles = (m + MROWS - 1) / MROWS;
-  tc.m_pitch = tc.n_row_tiles > 1 ? MROWS : (int)align_up(m, 8);
-  const int tiles = tc.n_task_tiles * tc.n_row_tiles;
-  const size_t tile_bytes = sizeof(float) * (size_t)TASKS * 2 * tc.m_pitch;
-  // (rounds are counted in CUs: one workgroup keeps a CU's share of the memory system or of the
-  // MFMA rate busy, two on a CU share it)
-  tc.n_whole = NEVER_CUT ? tiles : ALWAYS_CUT ? 0 : tiles / c->n_cu * c->n_cu;
-  tc.n_split = 1;
-  const int rest = tiles - tc.n_whole;
-  if (rest) {
-    const int min_chunks = tiles < 32 ? 4 : 8;   // few tiles: shorter k ranges are worth the pipeline fill they cost
-    tc.n_split = choose_split(rest, c->n_cu, n_chunks, min_chunks, tile_bytes * rest);
-    if (tc.n_split == 1 && !ALWAYS_CUT) tc.n_whole = tiles;
-  }
-  tc.n_cut = tiles - tc.n_whole;
-  tc.chunks_per_split = (n_chunks + tc.n_split - 1) / tc.n_split;
-  tc.n_split = (n_chunks + tc.chunks_per_split - 1) / tc.chunks_per_split;
-  tc.xcd_groups = tc.n_row_tiles > 1 && tc.n_split <= c->mfma_xcd_max_split;
-  tc.max_words = tc.n_cut ? 2 : 1;   // (a finishing workgroup writes one word per block of tasks: a wave then does too)
+  const TileCover tc = cover_tiled(m, n_in, n_tasks, MTILES, TB, ALWAYS_CUT, NEVER_CUT, c->n_cu, c->mfma_xcd_max_split);
+  if (int rc = partials_fit(c, tiled_partial_bytes(tc, TB))) return rc;
   if (max_words) *max_words = tc.n_cut ? (n_tasks + 31) / 32 : (n_tasks + 32 * TB - 1) / (32 * TB);
   const f16_t *tiled = at<f16_t>(c, c->lo.tiled) + w.elems;
   const uint32_t *wmax = at<uint32_t>(c, c->lo.wmax) + w.blocks;
@@ -656,11 +627,8 @@ int launch_tiled(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n
 template <int TB, typename Epi>
 int launch_tiled_rows(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,
                       const TiledMatrix &w, int *max_words) {
-  // row tiles of equal height, as few as the accumulators allow: every further tile streams the weights again
-  const int blocks = (m + 31) / 32, most = std::min(c->tiled_row_blocks, TB == 1 ? 4 : 3);
-  const int z = (blocks + most - 1) / most, mt = (blocks + z - 1) / z;
+  const int mt = tiled_row_blocks_for(m, std::min(c->tiled_row_blocks, TB == 1 ? 4 : 3));   // (what the accumulators allow)
   switch (mt) {
-    case 1:   // (only where mfma_direct_k is switched off)
     case 2: return launch_tiled<2, TB, Epi>(c, epi, rows, m, n_in, n_tasks, in, w, max_words);
     case 3: return launch_tiled<3, TB, Epi>(c, epi, rows, m, n_in, n_tasks, in, w, max_words);
     default:
@@ -695,18 +663,15 @@ int launch_direct(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int 
   // A long k with few tasks (down) would be streamed by few CUs, each reading all activations of a
   // long row: its k is cut over the CUs.  (q/k/v and o, with a k of 3584 and 4096, are as fast on
   // half of the CUs as cut over all of them, and need no second launch.)
-  constexpr int CUT_TILES = 2;
   if constexpr (!EpiHasLocalReduce<Epi>::value && !EpiRow<Epi>::max || EpiRow<Epi>::sum) {
     if (n_in > c->direct_whole_k && blocks < 4 * c->n_cu) {
-      const int groups = (blocks + CUT_TILES - 1) / CUT_TILES;
-      int split = std::max(1, std::min(std::min(c->n_cu / groups, n_chunks / 8), MG_MAX_SPLIT));
-      split = (int)std::min<size_t>(split, std::max<size_t>(1, MFMA_PARTIAL_BYTES / (sizeof(float) * (size_t)groups * CUT_TILES * TG_TASKS * 2 * m_pitch)));
-      const int cps = (n_chunks + split - 1) / split;
-      split = (n_chunks + cps - 1) / cps;
+      int cps;
+      const int groups = ceil_div(blocks, TD_CUT_TILES), split = direct_split(m, n_in, n_tasks, c->n_cu, cps);
       if (split > 1) {
+        if (int rc = partials_fit(c, split * range_bytes(groups, TD_CUT_TILES * TG_TASKS, m_pitch))) return rc;
         if (max_words) *max_words = (n_tasks + 31) / 32;
-        if (int rc = launch_direct_tiles<CUT_TILES, true>(c, epi, rows, m, n_in, n_tasks, in, w, groups, split, cps)) return rc;
-        return launch_finish(c, epi, rows, m, n_tasks, PartialSums{at<float>(c, c->lo.mfma_part), split, m_pitch, CUT_TILES * TG_TASKS, OP_ROWS,
+        if (int rc = launch_direct_tiles<TD_CUT_TILES, true>(c, epi, rows, m, n_in, n_tasks, in, w, groups, split, cps)) return rc;
+        return launch_finish(c, epi, rows, m, n_tasks, PartialSums{at<float>(c, c->lo.mfma_part), split, m_pitch, TD_CUT_TILES * TG_TASKS, OP_ROWS,
                                                                    TileCover{groups, 1, 0, groups, split, cps, m_pitch, 1, 0}});
       }
     }
@@ -745,7 +710,7 @@ int launch_mfma_shape(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, 
   int occ = mfma_occupancy<MTILES, Epi, true, WAVES>(c);
   if (occ < 0) return occ;
   const int tiles = bx * z;
-  int split = choose_split(tiles, occ * c->n_cu, n_chunks, tiles < 32 ? 4 : 8, sizeof(float) * (size_t)n_tasks * 2 * m_pad);
+  int split = choose_split(tiles, occ * c->n_cu, n_chunks, tiles < 32 ? 4 : 8, range_bytes(1, n_tasks, m_pad));
   const int cps = (n_chunks + split - 1) / split;
   split = (n_chunks + cps - 1) / cps;
   float *part = at<float>(c, c->lo.mfma_part);
@@ -756,6 +721,7 @@ int launch_mfma_shape(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, 
   const size_t lds = mg_lds_bytes(MTILES, WAVES);
   // (an epilogue that sums over a row runs in the finishing launch only)
   if (split > 1 || EpiRow<Epi>::sum) {
+    if (int rc = partials_fit(c, split * range_bytes(1, n_tasks, m_pad))) return rc;
     mfma_rows_k<MTILES, Epi, true, WAVES><<<grid, 64 * WAVES, lds, c->stream>>>(
         epi, rows, m, in, n_in, n_tasks, cps, part, m_pad, bx, split, z, xcd_groups);
     HIP_TRY(c, hipGetLastError());
@@ -951,9 +917,8 @@ int run_layers(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
   if (l0 >= l1 || m <= 0) return SPARK_OK;
   // many rows: the projections are dense contractions for the MFMA units
   if (std::is_same<WT, bf16_t>::value && m >= c->mfma_min_rows && c->use_mfma) {
-    // a residual projection's partial sums of all rows have to fit their buffer: more rows go through
-    // the layers in pieces, in order, so that a piece finds the K and V of the rows before it
-    const int most = (int)(MFMA_PARTIAL_BYTES / (sizeof(float) * align_up(g.d_model, 512))) / 64 * 64;
+    // (more rows go through the layers in pieces, in order, so that a piece finds the K and V of the rows before it)
+    const int most = pass_rows_limit(g.d_model);
     for (int r0 = 0; r0 < m; r0 += most) {
       const int rc = run_layers_mfma(c, l0, l1, rows + r0, std::min(most, m - r0));
       if (rc) return rc;

@@ -1,0 +1,84 @@
+"""The covers that the MFMA projections are launched with (csrc/cover.h, plain integer arithmetic),
+checked on the host over every model width, row count and tile shape that the library accepts: the
+partial sums of every launch fit their buffer, which other buffers lie directly behind, and the
+tiles of a cover are all there, once."""
+import pathlib
+import subprocess
+
+CSRC = pathlib.Path(__file__).resolve().parent.parent / "paper_2603_09215_amd" / "csrc"
+
+DRIVER = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "cover.h"
+using namespace spark;
+static long checked = 0, cut = 0, mixed = 0;
+static void bad(const char *what, int m, int n_in, int n_tasks, int mt, int tb, size_t bytes) {
+  printf("%s: %d rows, k = %d, %d tasks, tiles of %d rows x %d tasks: %zu bytes\n", what, m, n_in, n_tasks, 32 * mt, 128 * tb, bytes);
+  exit(1);
+}
+static void projection(int m, int n_in, int n_tasks, bool always, bool never, int n_cu) {
+  for (int tb = 1; tb <= 2; ++tb)
+    for (int most = 2; most <= (tb == 1 ? 4 : 3); ++most) {
+      const int mt = tiled_row_blocks_for(m, most);
+      if (mt < 2 || mt > most) bad("row blocks", m, n_in, n_tasks, mt, tb, 0);
+      const TileCover tc = cover_tiled(m, n_in, n_tasks, mt, tb, always, never, n_cu, 4);
+      const size_t bytes = tiled_partial_bytes(tc, tb);
+      if (bytes > MFMA_PARTIAL_BYTES) bad("partial sums", m, n_in, n_tasks, mt, tb, bytes);
+      const int chunks = ceil_div(n_in, MG_KC);
+      if (tc.n_whole + tc.n_cut != tc.n_task_tiles * tc.n_row_tiles || tc.n_task_tiles * 128 * tb < n_tasks ||
+          tc.n_row_tiles * 32 * mt < m || (always && tc.n_whole) || (never && tc.n_cut) || tc.n_split > MG_MAX_SPLIT ||
+          (tc.n_split - 1) * tc.chunks_per_split >= chunks || tc.n_split * tc.chunks_per_split < chunks ||
+          (tc.n_row_tiles == 1 && tc.m_pitch < m))
+        bad("cover", m, n_in, n_tasks, mt, tb, bytes);
+      ++checked;
+      cut += tc.n_cut > 0;
+      mixed += tc.n_cut > 0 && tc.n_whole > 0;
+    }
+  if (m <= OP_ROWS) {
+    int cps;
+    const int split = direct_split(m, n_in, n_tasks, n_cu, cps), groups = ceil_div(ceil_div(n_tasks, TG_TASKS), TD_CUT_TILES);
+    const size_t bytes = split * range_bytes(groups, TD_CUT_TILES * TG_TASKS, ceil_div(m, 8) * 8);
+    if (split > 1 && bytes > MFMA_PARTIAL_BYTES) bad("direct", m, n_in, n_tasks, 1, 1, bytes);
+    if (split < 1 || split > MG_MAX_SPLIT || split * cps < ceil_div(n_in, MG_KC)) bad("direct ranges", m, n_in, n_tasks, 1, 1, bytes);
+  }
+  // the kernel on the caller's weights: one tile, all rows; its residual projections are always cut
+  const size_t rows_bytes = range_bytes(1, n_tasks, ceil_div(m, 8) * 8);
+  const int split = choose_split(8, n_cu, ceil_div(n_in, MG_KC), 4, rows_bytes);
+  if ((split > 1 || always) && split * rows_bytes > MFMA_PARTIAL_BYTES) bad("rows", m, n_in, n_tasks, 0, 0, split * rows_bytes);
+}
+int main() {
+  const int cus[] = {256, 64};
+  for (int d = 8; d <= 4096; d += 8) {
+    const int limit = pass_rows_limit(d), top = limit < 8192 ? limit : 8192;   // max_batch 256 x 32 slots
+    if (limit < 384) bad("limit", limit, 0, d, 0, 0, 0);
+    for (int n_cu : cus)
+      for (int b = 1; b <= ceil_div(top, 32); ++b) {
+        const int m = 32 * b < top ? 32 * b : top;
+        if (d > 512 && d % 512 > 24 && m + 400 < top && b % 7) continue;   // (thinned away from the edges)
+        projection(m, 1024, d / 2, true, false, n_cu);        // residual projections, the lens translator
+        projection(m, 18944, d / 2, true, false, n_cu);
+        if (m > 31) projection(m - 31, 4096, d / 2, true, false, n_cu);
+      }
+  }
+  const int widths[] = {40, 1064, 2304, 8192, 13696, 18944, 40000};   // q/k/v, gate/up and vocabularies in tasks
+  for (int tasks : widths)
+    for (int m = 1; m <= 8192; m += m < 300 ? 1 : 31)
+      for (int n_cu : cus) {
+        projection(m, 3584, tasks, false, false, n_cu);
+        if (m <= 256) projection(m, 4096, tasks, false, true, n_cu);
+      }
+  printf("%ld covers, %ld cut, %ld with whole and cut tiles\n", checked, cut, mixed);
+  return 0;
+}
+"""
+
+
+def test_partial_sums_of_every_cover_fit_their_buffer(tmp_path):
+    src, exe = tmp_path / "covers.cpp", tmp_path / "covers"
+    src.write_text(DRIVER)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", f"-I{CSRC}", "-o", str(exe), str(src)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, out.stdout
+    n, n_cut, n_mixed = (int(w) for w in out.stdout.split() if w.isdigit())
+    assert n > 500_000 and n_cut > 100_000 and n_mixed > 1000, out.stdout
