@@ -432,11 +432,11 @@ void launch_attention_g(spark_ctx *c, const RowDesc *rows, int m, int layer, con
 }
 
 template <typename WT, int HD>
-void launch_attention_hd(spark_ctx *c, const RowDesc *rows, int m, int layer, const float *q, const RowOut &out, RowMax &row_max) {
-  // a handful of rows: four query heads per workgroup, so that even two KV heads make enough
+void launch_attention_hd(spark_ctx *c, const RowDesc *rows, int m, int m_pass, int layer, const float *q, const RowOut &out, RowMax &row_max) {
+  // a handful of rows: two query heads per workgroup, so that even two KV heads make enough
   // workgroups; many rows: all heads of a KV head together, K and V are read once
   const int group = c->dv.group;
-  const int gt = (m <= ATTN_SPLIT_HEADS_MAX_ROWS && group > 2) ? 2 : group;
+  const int gt = (m_pass <= ATTN_SPLIT_HEADS_MAX_ROWS && group > 2) ? 2 : group;
   switch (gt) {
     case 1: launch_attention_g<WT, HD, 1>(c, rows, m, layer, q, out, row_max); break;
     case 2: launch_attention_g<WT, HD, 2>(c, rows, m, layer, q, out, row_max); break;
@@ -470,14 +470,15 @@ AttnShape attn_shape(int splits, double load, int group, int pieces_set) {
 }
 
 // row_max: where the rows' largest output magnitudes go, for the MFMA output projection (or no list);
-// its count is set to what the launch writes
+// its count is set to what the launch writes.  m_pass: rows of the whole pass, which m may be a part of;
+// the workgroups' shape, and with it the length of a row's list, is the same for all parts.
 template <typename WT>
-int launch_attention_rows(spark_ctx *c, const RowDesc *rows, int m, int layer, const float *q, const RowOut &out, RowMax &row_max) {
+int launch_attention_rows(spark_ctx *c, const RowDesc *rows, int m, int m_pass, int layer, const float *q, const RowOut &out, RowMax &row_max) {
   if (std::is_same<WT, bf16_t>::value && c->cfg.head_dim == 128 && c->dv.group <= 16 && c->use_mfma &&
-      m >= c->attn_mfma_min_rows) {
+      m_pass >= c->attn_mfma_min_rows) {
     // the slice tasks on the MFMA units, all query heads of a KV head together
     const int splits = c->attn_splits_now > 0 ? std::min(c->dv.n_splits, c->attn_splits_now) : c->dv.n_splits;
-    const long tasks = (long)splits * c->cfg.n_kv_heads * m;
+    const long tasks = (long)splits * c->cfg.n_kv_heads * m_pass;
     const AttnShape shape = attn_shape(splits, (double)tasks / c->n_cu, c->dv.group, c->attn_pieces);
     const int pieces = shape.pieces;
     // few workgroups (a handful of rows, two KV heads): eight query heads per workgroup
@@ -488,8 +489,8 @@ int launch_attention_rows(spark_ctx *c, const RowDesc *rows, int m, int layer, c
     kern<<<dim3((splits + pieces - 1) / pieces, c->cfg.n_kv_heads * wg_per_kv, m), ATTN_THREADS * shape.teams, 0, c->stream>>>(
         rows, q, kv_view(c), layer, c->cfg.n_q_heads, c->dv.group, heads_per_wg, c->dv.n_splits, pieces, 1.0f / sqrtf(128.0f),
         at<float>(c, c->lo.part), at<int>(c, c->lo.arrivals), out, row_max);
-  } else if (c->cfg.head_dim == 128) launch_attention_hd<WT, 128>(c, rows, m, layer, q, out, row_max);
-  else launch_attention_hd<WT, 64>(c, rows, m, layer, q, out, row_max);
+  } else if (c->cfg.head_dim == 128) launch_attention_hd<WT, 128>(c, rows, m, m_pass, layer, q, out, row_max);
+  else launch_attention_hd<WT, 64>(c, rows, m, m_pass, layer, q, out, row_max);
   HIP_TRY(c, hipGetLastError());
   return SPARK_OK;
 }
@@ -519,7 +520,7 @@ template <typename WT> int launch_attention(spark_ctx *c, const RowDesc *rows, i
   for (int r0 = 0; r0 < m; r0 += c->base.rows) {
     RowMax rm = row_max;
     if (rm.list) rm.list += (size_t)r0 * rm.stride;
-    if ((rc = launch_attention_rows<WT>(c, rows + r0, std::min(c->base.rows, m - r0), layer, c->pb.q + r0 * qw,
+    if ((rc = launch_attention_rows<WT>(c, rows + r0, std::min(c->base.rows, m - r0), m, layer, c->pb.q + r0 * qw,
                                         RowOut{out.p + (size_t)r0 * out.stride, out.stride}, rm))) return rc;
     row_max.n = rm.n;
   }

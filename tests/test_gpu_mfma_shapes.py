@@ -52,6 +52,40 @@ def test_prompt_lengths(sb, n, page, group):
     sp.close()
 
 
+@pytest.fixture
+def filled_scratch():
+    """torch.empty filled with 0xff bytes: what the scratch area holds that nobody has written"""
+    import torch
+    before = torch.are_deterministic_algorithms_enabled(), torch.utils.deterministic.fill_uninitialized_memory
+    torch.use_deterministic_algorithms(True)
+    torch.utils.deterministic.fill_uninitialized_memory = True
+    assert int(torch.empty(64, dtype=torch.uint8, device="cuda:0").min()) == 255
+    yield
+    torch.use_deterministic_algorithms(before[0])
+    torch.utils.deterministic.fill_uninitialized_memory = before[1]
+
+
+@pytest.mark.parametrize("n,shape_kw,tune", [
+    # more rows than the slices' partial results hold at a time, one to five in the second turn
+    (258, dict(n_q_heads=16, head_dim=64), {}), (260, dict(n_q_heads=14, n_kv_heads=2, head_dim=64), {}),
+    (261, dict(n_q_heads=16, head_dim=64), {}), (262, dict(n_q_heads=16, head_dim=64), {}),
+    (259, dict(n_q_heads=16), dict(attn_prompt_min_rows=2000)),
+    (560, dict(n_q_heads=16), dict(attn_prompt_min_rows=2000)),
+])
+def test_prompt_attention_in_turns(sb, filled_scratch, n, shape_kw, tune):
+    """passes whose rows do not share K and V and are attended in turns: every row's list of
+    magnitudes, as long as the output projection reads it, has been written"""
+    say(f"case prompt of {n} in turns, {shape_kw} {tune}")
+    shape = SHAPE.replace(**shape_kw)
+    weights = wl.make_weights(shape, seed=12, gain_std=0.1)
+    sp = sb.Spark(shape, wl.TINY.schedule, weights, max_batch=1, max_seq_len=n + 64, kv_page_tokens=64)
+    for name, value in tune.items():
+        sp.tune(name, value)
+    compare_run(sp, shape, wl.TINY.schedule, weights, [wl.make_prompt(shape, n, seed=61)], [0], 3, check_kv_every=2,
+                label=f"prompt {n} in turns", kv_all_positions=True)
+    sp.close()
+
+
 @pytest.mark.parametrize("pieces,long", [(0, 62), (0, 126), (0, 700), (8, 62), (8, 510), (8, 700), (2, 126)])
 def test_attention_workgroups(sb, pieces, long):
     """contexts that grow over the edge of a 64-token piece, of a pair of pieces and of a workgroup's
