@@ -1122,7 +1122,7 @@ int decode_chunk(spark_ctx *c, int steps, int n, const int32_t *seq_ids, const i
   // inputs
   int *h_ids = c->h_in, *h_forced = c->h_in + g.max_batch;
   memcpy(h_ids, seq_ids, sizeof(int) * n);
-  std::copy(seq_ids, seq_ids + n, c->last_ids.begin());   // what the device array holds, for spark_get_logits
+  c->last_ids.assign(seq_ids, seq_ids + n);   // (for spark_get_logits)
   HIP_TRY(c, hipMemcpyAsync(at<int>(c, c->lo.seq_ids), h_ids, sizeof(int) * n, hipMemcpyHostToDevice,
                             c->stream));
   if (forced) {
@@ -1314,7 +1314,7 @@ int init_context(const spark_config *cfg, const spark_weights *weights, void *kv
   c->static_scratch = static_scratch;
   c->sp = sched_params(cfg);
   c->seqs.resize(cfg->max_batch);
-  c->last_ids.assign(cfg->max_batch, 0);
+  c->last_ids.reserve(cfg->max_batch);
   for (int p = c->dv.n_pages_total - 1; p >= 0; --p) c->free_pages.push_back(p);
   c->h_in = c->h_out = nullptr;
   auto bail = [&](int code) { spark_destroy(c); return code; };
@@ -1555,7 +1555,7 @@ int spark_get_logits(spark_ctx *c, int32_t seq_id, float *out_logits, int32_t *h
   if (!s->g) return fail(c, SPARK_ESTATE, "sequence %d has not been stepped", seq_id);
   // logits rows are indexed by the position of the sequence in the last batch
   int row = -1;
-  for (int i = 0; i < c->cfg.max_batch; ++i)
+  for (int i = 0; i < (int)c->last_ids.size(); ++i)
     if (c->last_ids[i] == seq_id) { row = i; break; }
   if (row < 0) return fail(c, SPARK_ESTATE, "sequence %d was not in the last step", seq_id);
   HIP_TRY(c, hipMemcpy(out_logits, at<float>(c, c->lo.logits) + (size_t)row * c->dv.V,

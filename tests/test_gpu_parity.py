@@ -218,6 +218,32 @@ def test_edge_cases_and_errors(sb, tiny_weights):
     sp.close()
 
 
+def test_logits_are_those_of_the_latest_step(sb, tiny_weights):
+    """spark_get_logits of a sequence that the latest step did not contain is refused, whatever
+    older calls have left in the rows behind the step's"""
+    w = wl.TINY
+    say("case logits of the latest step")
+    sp = sb.Spark(w.shape, w.schedule, tiny_weights, max_batch=4, max_seq_len=64, kv_page_tokens=16)
+    ids = [sp.seq_open(0) for _ in range(4)]
+    for i in ids:
+        sp.prefill(i, wl.make_prompt(w.shape, 5 + i, seed=30 + i))
+
+    def readable():
+        out = []
+        for i in ids:
+            try:
+                logits, _ = sp.get_logits(i)
+                out.append((i, int(np.argmax(logits))))
+            except sb.SparkError as e:
+                assert e.code == -4
+        return out
+
+    for batch in ([0], [1], [3, 0, 2], [2], [1, 2], [0, 1, 2, 3], [3, 1]):
+        tok, _ = sp.step(batch)
+        assert readable() == sorted(zip(batch, tok.tolist())), batch
+    sp.close()
+
+
 def test_reopened_slot_reproduces_a_fresh_run(sb, tiny_weights):
     w = wl.TINY
     say("case reuse")
