@@ -469,6 +469,7 @@ mfma_rows_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, ProjIn in, in
 // created, from the same weight_rows() of the epilogue that the kernels use.
 constexpr int TG_TILE = 32 * MG_KC;   // elements of one A tile of one chunk
 constexpr int TG_PARTS = 2;           // fp16 parts of an activation
+constexpr int TG_FOLD_CHUNKS = 10;    // chunks that go into one set of sums
 
 constexpr size_t tg_tiled_elems(int n_tasks, int n_in) {
   return (size_t)((n_tasks + TG_TASKS - 1) / TG_TASKS) * ((n_in + MG_KC - 1) / MG_KC) * TG_TILE;
@@ -578,6 +579,14 @@ constexpr size_t tg_lds_bytes(int mtiles) {
 // Activations go through three LDS buffers, so that one barrier per chunk, placed before the first
 // read of the next chunk, is enough: a wave writes the buffer two chunks ahead of what the slowest
 // wave can still read.
+//
+// Every MFMA rounds the running sum to 32 bits, and what K / 8 of them leave grows with the root of
+// their number: 5.4e-7 of the result for the 448 of a k of 3584.  So the sums of TG_FOLD_CHUNKS chunks
+// are added to a second set of registers and begin at zero again (error of the heads' logits against 64
+// bits, k of 3584: 2.4e-7, and 2.5e-7 to 3.2e-7 as three bf16 parts with k cut into ranges; steps of 48
+// and 96 sequences take under 1 % longer for it).  64 tasks a wave have no registers for that; they
+// serve gate/up, whose k is d_model (MLP of 18944, 33 to 256 rows: 5.3e-7 to 8.6e-7; three bf16 parts 6.7e-7
+// to 1.16e-6).
 template <int MTILES, int TB, typename Epi, bool WHOLE>
 __global__ void __launch_bounds__(64 * TG_WAVES)
 mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restrict__ wmax,
@@ -600,6 +609,9 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restric
   constexpr int PER = (QT + NB - 1) / NB;           // weight loads per group
   constexpr int BUF_ELEMS = TG_PARTS * PART_ELEMS;
   constexpr int TASKS = 32 * TG_WAVES * TB;
+  constexpr bool FOLD = TB == 1;
+  constexpr int SEGMENT = FOLD ? TG_FOLD_CHUNKS : 1 << 20;   // chunks that are added up before they are folded
+  static_assert(SEGMENT % 2 == 0, "whole turns of the ring of chunks");
   constexpr size_t SCALE_AT = tg_lds_bytes(MTILES) - (sizeof(float) + sizeof(unsigned long long)) * MROWS;
   extern __shared__ uint4 tg_smem[];
   const int lane = threadIdx.x & 63;
@@ -642,6 +654,12 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restric
     for (int c = 0; c < MTILES; ++c)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[q][c][r] = 0.f;
+  f32x16_t folded[FOLD ? QT : 1][FOLD ? MTILES : 1];
+  if constexpr (FOLD)
+#pragma unroll
+    for (int q = 0; q < QT; ++q)
+#pragma unroll
+      for (int c = 0; c < MTILES; ++c) folded[q][c] = acc[q][c];
 
   // chunks of weights in registers, slot = (chunk - c_begin) % RING
   constexpr int RING = 2;
@@ -653,15 +671,15 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restric
         (const u32x4_t *)(abase[q] + (size_t)min(chunk, c_end - 1) * TG_TILE + s * 512));
   };
 
-  int x_src[XV], x_dst[XV];
+  int x_src[XV];
   float x_up[XV];
   const int x_kv = ((int)threadIdx.x & 7) * 8;       // k of this thread's vectors inside a chunk
 #pragma unroll
   for (int n = 0; n < XV; ++n) {
     const int m = ((int)threadIdx.x + n * NT) >> 3;
     x_src[n] = min(row0 + m, m_rows - 1) * in.stride;                 // rows past the end repeat the last one
-    x_dst[n] = m * MG_ROWPAD + x_kv;
   }
+  const int x_dst = ((int)threadIdx.x >> 3) * MG_ROWPAD + x_kv;         // + 32 rows from vector to vector
   float4 xr[XV][2];
   auto load_x1 = [&](int n, int half, int chunk) {
     const int k = min(chunk, c_end - 1) * MG_KC + x_kv;
@@ -681,8 +699,8 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restric
     xh[e & 1] = real ? h : 0u;
     xl[e & 1] = real ? l : 0u;
     if (e & 1) {
-      *(u32x2_t *)(s_x + at + x_dst[n] + 2 * (e - 1)) = xh;
-      *(u32x2_t *)(s_x + at + PART_ELEMS + x_dst[n] + 2 * (e - 1)) = xl;
+      *(u32x2_t *)(s_x + at + x_dst + n * 32 * MG_ROWPAD + 2 * (e - 1)) = xh;
+      *(u32x2_t *)(s_x + at + PART_ELEMS + x_dst + n * 32 * MG_ROWPAD + 2 * (e - 1)) = xl;
     }
   };
   // B operand i of step s of a buffer: the smaller part first (the large terms are added last), row tiles inside
@@ -726,49 +744,65 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restric
   for (int o = 0; o < PD; ++o) bw[o] = load_b1(o % NB, 0, o / NB);
 
   int cur = 0, nxt = BUF_ELEMS, aft = 2 * BUF_ELEMS;   // LDS buffers of this chunk, the next, the one after
-  for (int base = c_begin; base < c_end; base += RING) {
+  for (int seg = c_begin; seg < c_end; seg += SEGMENT) {
+    const int seg_end = min(c_end, seg + SEGMENT);
+    for (int base = seg; base < seg_end; base += RING) {
 #pragma unroll
-    for (int j = 0; j < RING; ++j) {
-      const int chunk = base + j;
-      const bool next_real = chunk + 1 < c_end && (chunk + 1) * MG_KC + x_kv < n_in;
+      for (int j = 0; j < RING; ++j) {
+        const int chunk = base + j;
+        const bool next_real = chunk + 1 < c_end && (chunk + 1) * MG_KC + x_kv < n_in;
 #pragma unroll
-      for (int s = 0; s < STEPS; ++s) {
+        for (int s = 0; s < STEPS; ++s) {
 #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-          const int o = s * NB + i;
-          if (o == BAR) __syncthreads();
+          for (int i = 0; i < NB; ++i) {
+            const int o = s * NB + i;
+            if (o == BAR) __syncthreads();
 #pragma unroll
-          for (int q = 0; q < QT; ++q) {
-            acc[q][i % MTILES] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, wr[j][q][s]),
-                                                                        __builtin_bit_cast(f16x8_t, bw[o % W]),
-                                                                        acc[q][i % MTILES], 0, 0, 0);
-            if (q == 0) {
-              const int n = o + PD;
-              bw[n % W] = n < GROUPS ? load_b1(n % NB, cur, n / NB) : load_b1((n - GROUPS) % NB, nxt, (n - GROUPS) / NB);
-            }
-            if (q == 1 % QT) {
+            for (int q = 0; q < QT; ++q) {
+              acc[q][i % MTILES] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, wr[j][q][s]),
+                                                                          __builtin_bit_cast(f16x8_t, bw[o % W]),
+                                                                          acc[q][i % MTILES], 0, 0, 0);
+              if (q == 0) {
+                const int n = o + PD;
+                bw[n % W] = n < GROUPS ? load_b1(n % NB, cur, n / NB) : load_b1((n - GROUPS) % NB, nxt, (n - GROUPS) / NB);
+              }
+              if (q == 1 % QT) {
 #pragma unroll
-              for (int e = 0; e < PER; ++e) {
-                const int qq = i * PER + e;
-                if (qq < QT) {
-                  if (s == 0) load_a1((j + RING - 1) % RING, qq, STEPS - 1, chunk - 1 + RING);   // last step of the chunk before
-                  else load_a1(j, qq, s - 1, chunk + RING);
+                for (int e = 0; e < PER; ++e) {
+                  const int qq = i * PER + e;
+                  if (qq < QT) {
+                    if (s == 0) load_a1((j + RING - 1) % RING, qq, STEPS - 1, chunk - 1 + RING);   // last step of the chunk before
+                    else load_a1(j, qq, s - 1, chunk + RING);
+                  }
                 }
               }
+              if (q == QT - 1) {
+                // vector i / 2 of the next chunk: four pieces of two elements over the groups of steps 0 and 1
+                if (s < 2) cut_x2(i / 2, (i & 1) + 2 * s, nxt, next_real);
+                if (s == 2) load_x1(i / 2, i & 1, chunk + 2);
+              }
+              __builtin_amdgcn_sched_barrier(0);
             }
-            if (q == QT - 1) {
-              // vector i / 2 of the next chunk: four pieces of two elements over the groups of steps 0 and 1
-              if (s < 2) cut_x2(i / 2, (i & 1) + 2 * s, nxt, next_real);
-              if (s == 2) load_x1(i / 2, i & 1, chunk + 2);
-            }
-            __builtin_amdgcn_sched_barrier(0);
           }
         }
+        const int old = cur;
+        cur = nxt;
+        nxt = aft;
+        aft = old;
       }
-      const int old = cur;
-      cur = nxt;
-      nxt = aft;
-      aft = old;
+    }
+    if constexpr (FOLD) {
+#pragma unroll
+      for (int q = 0; q < QT; ++q)
+#pragma unroll
+        for (int c = 0; c < MTILES; ++c) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            folded[q][c][r] += acc[q][c][r];
+            acc[q][c][r] = 0.f;
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
     }
   }
 
@@ -783,7 +817,10 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restric
     for (int q = 0; q < QT; ++q) {
       const float f = xd * wdown[q];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[q][c][r] *= f;
+      for (int r = 0; r < 16; ++r) {
+        if constexpr (FOLD) acc[q][c][r] = folded[q][c][r];
+        acc[q][c][r] *= f;
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
   }

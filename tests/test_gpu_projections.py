@@ -1,0 +1,124 @@
+"""Single projections of the MFMA path against 64 bits, with nothing behind them that would round:
+models whose other matrices are zero, so that the logits are one product (the heads) or one MLP, of
+fp32 activations with all their bits.  A run through many layers of a bf16 cache cannot tell parts of
+activations that add up to 16 bits from parts that add up to 23: the cache rounds to 8.
+
+Bounds (largest relative error of a row, 2-norm, without the factor that the norm's own rounding
+gives the whole row).  One rounding to 32 bits leaves 0.22 * 2^-23 of the value on average (root mean
+square): 2.6e-8.  Activations: two roundings in the norm, up to 2^-23 of an element (2^-24 on average)
+by the two fp16 parts: 8e-8.  A sum of n MFMAs: each rounds a running sum that is half of the result's
+size on average (square), sqrt(n / 2) * 2.6e-8, with n = k / 8; in segments of 80 whose sums are added,
+sqrt(40) * 2.6e-8 whatever the segments' number: 1.7e-7.  The heads: 1.9e-7 in all; bound 3e-7.
+Gate/up, without segments at k = 3584: 3.9e-7, times sqrt(2) for the product of the two; down 1.7e-7;
+5.8e-7 in all; bound 9e-7.  (Parts that add up to 16 bits, 2^-17, leave 4e-6; one unbroken sum of the heads 5.4e-7.)"""
+import numpy as np
+import pytest
+
+import workloads as wl
+from parity_util import say
+
+pytestmark = pytest.mark.gpu
+
+D, FFN, VOCAB = 3584, 8264, 2305   # 8192 and more MLP activations: 64 tasks a wave; a down projection with its k cut
+
+
+@pytest.fixture(scope="module")
+def sb():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_09215_amd import binding
+    return binding
+
+
+def model(shape, mlp):
+    import torch
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(21)
+
+    def normal(*size, std=0.02):
+        return (torch.randn(size, generator=gen, device="cuda:0") * std).bfloat16()
+
+    W = {}
+    for name, size in wl.tensor_shapes(shape).items():
+        if name in wl.GAIN_TENSORS:
+            W[name] = 1.0 + 0.1 * torch.randn(size, generator=gen, device="cuda:0")
+        elif name in wl.FP32_TENSORS:
+            W[name] = torch.zeros(size, device="cuda:0")
+        elif name in ("wo", "wd", "lens_a"):
+            W[name] = torch.zeros(size, device="cuda:0").bfloat16()
+        else:
+            W[name] = normal(*size, std=0.05 if mlp and name == "embed" else 1.0 if name == "embed" else 0.02)
+    if mlp:   # the second layer and the head leave the first layer's result as it is
+        W["wd"][0] = normal(*W["wd"][0].shape)
+        W["lm_head"] = torch.eye(D, device="cuda:0").bfloat16()
+        W["final_norm"] = torch.ones(D, device="cuda:0")
+    W["lens_head"] = W["lm_head"]
+    return W
+
+
+def norm64(x, gain, eps):
+    import torch
+    x = x.double()
+    return x / torch.sqrt((x * x).mean(-1, keepdim=True) + eps) * gain.double()
+
+
+def row_errors(got, want):
+    import torch
+    got = torch.as_tensor(np.stack(got)).to(want.device).double()
+    factor = (got * want).sum(-1, keepdim=True) / (want * want).sum(-1, keepdim=True)
+    assert float((factor - 1).abs().max()) < 1e-6
+    return ((got - factor * want).norm(dim=-1) / want.norm(dim=-1)).cpu().numpy()
+
+
+def first_step(spark, tokens, full=None):
+    """one step of sequences that hold one token each; full: those that run full depth at once"""
+    ids = [spark.seq_open(0) for _ in tokens]
+    for i, t in zip(ids, tokens):
+        spark.prefill(i, [int(t)])
+    for b in full if full is not None else []:
+        spark.seq_set_phase(ids[b], 0)
+    _, depth = spark.step(ids)
+    return ids, depth
+
+
+@pytest.mark.parametrize("rows", [5, 32, 33, 64, 96, 128, 129])
+def test_head_against_64_bits(sb, rows):
+    import torch
+    say(f"case head alone, {rows} rows")
+    shape = wl.TINY.shape.replace(name="head", dtype=wl.DTYPE_BF16, n_layers=1, d_model=D, n_q_heads=2, n_kv_heads=1,
+                                  head_dim=128, d_ffn=64, vocab_text=VOCAB, vocab_speech=0)
+    sched = wl.TINY.schedule.replace(exit_layer=1, period_k=1, phase=0, n_text=1, n_speech=0)
+    W = model(shape, False)
+    sp = sb.Spark(shape, sched, W, max_batch=rows, max_seq_len=16, kv_page_tokens=16)
+    tokens = np.random.default_rng(rows).integers(0, VOCAB, rows)
+    ids, _ = first_step(sp, tokens)
+    x = norm64(W["embed"][torch.as_tensor(tokens, device="cuda:0")], W["final_norm"], shape.rms_eps)
+    err = row_errors([sp.get_logits(i)[0] for i in ids], x @ W["lm_head"].double().T)
+    say(f"  head, {rows} rows: mean {err.mean():.3g}, largest {err.max():.3g}")
+    assert err.max() <= 3e-7
+    sp.close()
+
+
+@pytest.mark.parametrize("rows", [6, 32, 40, 96, 150])
+def test_mlp_against_64_bits(sb, rows):
+    import torch
+    say(f"case MLP alone, {rows} rows")
+    shape = wl.TINY.shape.replace(name="mlp", dtype=wl.DTYPE_BF16, n_layers=2, d_model=D, n_q_heads=2, n_kv_heads=1,
+                                  head_dim=128, d_ffn=FFN, vocab_text=0, vocab_speech=D)
+    sched = wl.TINY.schedule.replace(exit_layer=1, period_k=2, phase=1, n_text=0, n_speech=1, scope=wl.SCOPE_STREAM)
+    W = model(shape, True)
+    sp = sb.Spark(shape, sched, W, max_batch=rows, max_seq_len=16, kv_page_tokens=16)
+    tokens = np.random.default_rng(rows).integers(0, D, rows)
+    # four rows run full depth: their head is the vector kernel, in fp32, and shows the hidden state
+    seen = sorted({0, rows // 3, 2 * rows // 3, rows - 1})
+    ids, depth = first_step(sp, tokens, seen)
+    assert list(np.flatnonzero(depth == 2)) == seen
+    h = W["embed"][torch.as_tensor(tokens[seen], device="cuda:0")].double()
+    n = norm64(h, W["mlp_norm"][0], shape.rms_eps)
+    act = torch.nn.functional.silu(n @ W["wg"][0].double().T) * (n @ W["wu"][0].double().T)
+    want = norm64(h + act @ W["wd"][0].double().T, W["final_norm"], shape.rms_eps)
+    err = row_errors([sp.get_logits(ids[b])[0] for b in seen], want)
+    say(f"  MLP, {rows} rows: mean {err.mean():.3g}, largest {err.max():.3g}")
+    assert err.max() <= 9e-7
+    sp.close()

@@ -20,7 +20,7 @@ static void bad(const char *what, int m, int n_in, int n_tasks, int mt, int tb, 
 static void projection(int m, int n_in, int n_tasks, bool always, bool never, int n_cu) {
   for (int tb = 1; tb <= 2; ++tb)
     for (int most = 2; most <= (tb == 1 ? 4 : 3); ++most) {
-      const int mt = tiled_row_blocks_for(m, most);
+      const int mt = tb == 1 && !never ? narrow_row_blocks(m, n_in, n_tasks, most, always, n_cu) : tiled_row_blocks_for(m, most);
       if (mt < 2 || mt > most) bad("row blocks", m, n_in, n_tasks, mt, tb, 0);
       const TileCover tc = cover_tiled(m, n_in, n_tasks, mt, tb, always, never, n_cu, 4);
       const size_t bytes = tiled_partial_bytes(tc, tb);
