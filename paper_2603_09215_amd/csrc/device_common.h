@@ -79,11 +79,12 @@ __device__ __forceinline__ void split3_bf16(float x, bf16_t &hi, bf16_t &mid, bf
 
 // The other split, for the copy of the weights that the library keeps as fp16: x * 2^n = hi + lo
 // with two fp16 parts (11 bits each, the remainder's sign is one more), where 2^n brings the
-// largest magnitude of the row just below 2^15.  What is left out is at most 2^-23 of an element,
-// or 2^-40 of the row's largest for elements far below it: the size of an fp32 rounding.
+// largest magnitude of the row just below 2^15.  What is left out is at most 2^-23 of an element
+// (2^-24 on average, the size of an fp32 rounding), or 2^-39 of the row's largest for elements
+// more than 2^-16 below it, where fp16 ends.
 // The power of two comes from the largest magnitude's exponent alone, as a biased exponent E
 // (2^(E - 127)), kept so that 2^(127 - E) is a normal number too.
-__device__ __forceinline__ int scale_exponent(int e) { return min(max(268 - e, 14), 240); }   // e: largest biased fp32 exponent
+__device__ __forceinline__ int scale_exponent(int e) { return min(max(268 - e, 14), 253); }   // e: largest biased fp32 exponent
 __device__ __forceinline__ float scale_up(int E) { return __uint_as_float((uint32_t)E << 23); }
 __device__ __forceinline__ float scale_down(int E) { return __uint_as_float((uint32_t)(254 - E) << 23); }
 

@@ -9,11 +9,11 @@
 //
 //   mfma_tiled_k (further down), the one a context with the memory for it runs, takes its weights
 //   from a copy in fp16 and in MFMA operand order, written when the context was created.  A bf16
-//   weight scaled by a power of two per block of 32 rows is an fp16 number (what lies 2^-40 below
-//   the block's largest weight is rounded there), so the activations are fp16 parts too, and fp16
-//   has 11 bits of mantissa: two parts hold what takes three of bf16.  A third of the MFMA work,
-//   and at the clock the chip holds under MFMA load a third of the time of a prompt's projections,
-//   is not done.
+//   weight scaled by a power of two per row is an fp16 number (exact down to 2^-31 of the row's
+//   largest weight), so the activations are fp16 parts too, and fp16
+//   has 11 bits of mantissa: two parts hold 23 of the 24 bits that three of bf16 hold.  A third of the
+//   MFMA work, and at the clock the chip holds under MFMA load a third of the time of a prompt's
+//   projections, is not done.
 //   mfma_rows_k, described next, takes the caller's row-major bf16 weights, for contexts without
 //   that copy: three bf16 parts (3 x 8 bits).
 //
@@ -464,9 +464,10 @@ mfma_rows_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, ProjIn in, in
 // LDS, which leaves LDS to the activations, and a wave can hold several A tiles, so that every B
 // operand it reads feeds several MFMAs.  Both weight rows of a task end up in one lane: result
 // registers r and r + 8 (r < 8) are task (r/4)*8 + (l/32)*4 + r%4 of the block.
-// The 32 rows of a block share a power of two that brings their largest weight just below 2^15 (one
-// word per block holds that weight's magnitude).  Both are written once, when the context is
-// created, from the same weight_rows() of the epilogue that the kernels use.
+// Every row has a power of two that brings its largest weight just below 2^15 (`wdown`, 32 words a
+// block, undoes it).  A bf16 weight has 8 significant bits and fp16 a least unit of 2^-24, so a weight
+// is exact down to 2^-31 of its row's largest and off by at most 2^-39 of that below.  Both are written
+// once, when the context is created, from the same weight_rows() of the epilogue that the kernels use.
 constexpr int TG_TILE = 32 * MG_KC;   // elements of one A tile of one chunk
 constexpr int TG_PARTS = 2;           // fp16 parts of an activation
 constexpr int TG_FOLD_CHUNKS = 10;    // chunks that go into one set of sums
@@ -476,60 +477,56 @@ constexpr size_t tg_tiled_elems(int n_tasks, int n_in) {
 }
 constexpr size_t tg_blocks(int n_tasks) { return (size_t)((n_tasks + TG_TASKS - 1) / TG_TASKS); }
 
-constexpr int TG_AMAX_CHUNKS = 8;   // chunks a workgroup of the first pass reads
-
-// largest finite magnitude of each block's weight rows, as an fp32 bit pattern; wmax zero before
+// Writes the tiles of eight operand rows of a block and what undoes their scales.  A wave takes the
+// eight rows eight elements at a time, so that it reads 128 bytes of a row and writes 128 bytes of a tile
+// in one piece.  (Infinities and NaN have no part in a row's largest magnitude.)
+constexpr int TW_THREADS = 1024, TW_ROWS = 8;
 template <typename Epi>
-__global__ void __launch_bounds__(256)
-weights_amax_k(Epi epi, int n_tasks, int n_in, uint32_t *__restrict__ wmax) {
-  const int block = blockIdx.y, which = threadIdx.x >> 7;
-  const int task = block * TG_TASKS + ((threadIdx.x >> 3) & (TG_TASKS - 1));
+__global__ void __launch_bounds__(TW_THREADS)
+tile_weights_k(Epi epi, int n_tasks, int n_in, int n_chunks, float *__restrict__ wdown, f16_t *__restrict__ dst) {
+  constexpr int STRIDE = TW_THREADS / TW_ROWS;   // vectors of eight elements from trip to trip
+  __shared__ uint32_t s_max[TW_THREADS / 64][TW_ROWS];
+  const int block = blockIdx.x / (32 / TW_ROWS), r = threadIdx.x % TW_ROWS;
+  const int op_row = blockIdx.x % (32 / TW_ROWS) * TW_ROWS + r, task = block * TG_TASKS + op_row % TG_TASKS;
   const bf16_t *a, *b;
   epi.weight_rows(task < n_tasks ? task : 0, a, b);
-  const bf16_t *row = which ? b : a;
-  u32x4_t v[TG_AMAX_CHUNKS];
-#pragma unroll
-  for (int c = 0; c < TG_AMAX_CHUNKS; ++c) {
-    const int k = (blockIdx.x * TG_AMAX_CHUNKS + c) * MG_KC + (threadIdx.x & 7) * 8;
-    v[c] = *(const u32x4_t *)(row + (k < n_in ? k : 0));
-  }
+  const bf16_t *row = op_row < TG_TASKS ? a : b;
+  const int vec0 = threadIdx.x / TW_ROWS, n_vecs = n_chunks * (MG_KC / 8);
+  auto load = [&](int vec) {   // beyond the matrix: zeros
+    const bool real = task < n_tasks && vec * 8 < n_in;
+    const u32x4_t v = *(const u32x4_t *)(row + (real ? vec * 8 : 0)), zero = {0u, 0u, 0u, 0u};
+    return real ? v : zero;
+  };
   uint32_t m = 0u;
-#pragma unroll
-  for (int c = 0; c < TG_AMAX_CHUNKS; ++c)
+  auto consider = [&](const u32x4_t &v) {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const uint32_t u = (h ? v[c][e] & 0xffff0000u : v[c][e] << 16) & 0x7fffffffu;
+        const uint32_t u = (h ? v[e] & 0xffff0000u : v[e] << 16) & 0x7fffffffu;
         m = max(m, u < 0x7f800000u ? u : 0u);
       }
-  if (task >= n_tasks) m = 0u;
+  };
+  for (int vec = vec0; vec < n_vecs; vec += STRIDE) consider(load(vec));
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
-  if ((threadIdx.x & 63) == 0 && m) atomicMax(wmax + block, m);
-}
-
-template <typename Epi>
-__global__ void __launch_bounds__(256)
-tile_weights_k(Epi epi, int n_tasks, int n_in, int n_chunks, const uint32_t *__restrict__ wmax, f16_t *__restrict__ dst) {
-  const int c = blockIdx.x, block = blockIdx.y;
-  const int s = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int task = block * TG_TASKS + (lane & (TG_TASKS - 1)), which = (lane >> 4) & 1;
-  const int k = c * MG_KC + s * 16 + (lane >> 5) * 8;
-  u32x4_t v = {0u, 0u, 0u, 0u};   // beyond the matrix: zeros
-  if (task < n_tasks && k < n_in) {
-    const bf16_t *a, *b;
-    epi.weight_rows(task, a, b);
-    v = *(const u32x4_t *)((which ? b : a) + k);
-  }
-  const float up = scale_up(scale_exponent(wmax[block] >> 23));
-  f16x8_t o;
+  for (int o = 32; o >= TW_ROWS; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
+  if ((threadIdx.x & 63) < TW_ROWS) s_max[threadIdx.x >> 6][r] = m;
+  __syncthreads();
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    o[2 * e] = (f16_t)(__uint_as_float(v[e] << 16) * up);
-    o[2 * e + 1] = (f16_t)(__uint_as_float(v[e] & 0xffff0000u) * up);
-  }
-  *(f16x8_t *)(dst + ((size_t)block * n_chunks + c) * TG_TILE + s * 512 + lane * 8) = o;
+  for (int w = 0; w < TW_THREADS / 64; ++w) m = max(m, s_max[w][r]);
+  const int E = scale_exponent(m >> 23);
+  const float up = scale_up(E);
+  if (vec0 == 0) wdown[block * 32 + op_row] = scale_down(E);
+  auto store = [&](int vec, const u32x4_t &v) {
+    f16x8_t o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o[2 * e] = (f16_t)(__uint_as_float(v[e] << 16) * up);
+      o[2 * e + 1] = (f16_t)(__uint_as_float(v[e] & 0xffff0000u) * up);
+    }
+    *(f16x8_t *)(dst + ((size_t)block * n_chunks + vec / 8) * TG_TILE + vec % 8 / 2 * 512 + (op_row + vec % 2 * 32) * 8) = o;
+  };
+  for (int vec = vec0; vec < n_vecs; vec += STRIDE) store(vec, load(vec));
 }
 
 // Tile -> (task tile, row tile).  Consecutive workgroup ids go to consecutive XCDs, each with its
@@ -557,13 +554,16 @@ __device__ __forceinline__ void tile_place(const TileCover &tc, int t, int &bx, 
 }
 
 // dynamic LDS of mfma_tiled_k: three buffers of two parts of 32*MTILES padded activation rows, or
-// the four waves' pieces for turning the result tiles, whichever is larger; the rows' scales and
-// arg-max keys
+// the four waves' pieces for turning the result tiles, whichever is larger; the activation rows' scales and
+// arg-max keys, the weight rows' scales
 constexpr int TG_BUFS = 3;
-constexpr size_t tg_lds_bytes(int mtiles) {
+constexpr size_t tg_scales_at(int mtiles) {
   const size_t x = sizeof(f16_t) * TG_BUFS * TG_PARTS * 32 * mtiles * MG_ROWPAD;
   const size_t t = sizeof(float) * TG_WAVES * 2 * 32 * 33;
-  return (x > t ? x : t) + (sizeof(float) + sizeof(unsigned long long)) * 32 * mtiles;
+  return x > t ? x : t;
+}
+constexpr size_t tg_lds_bytes(int mtiles, int tb) {
+  return tg_scales_at(mtiles) + (sizeof(float) + sizeof(unsigned long long)) * 32 * mtiles + sizeof(float) * 64 * TG_WAVES * tb;
 }
 
 // A workgroup of four waves takes 128 * TB tasks (wave w: 2 * TB A tiles of 16 tasks),
@@ -589,7 +589,7 @@ constexpr size_t tg_lds_bytes(int mtiles) {
 // to 1.16e-6).
 template <int MTILES, int TB, typename Epi, bool WHOLE>
 __global__ void __launch_bounds__(64 * TG_WAVES)
-mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restrict__ wmax,
+mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__ wdown,
              const RowDesc *__restrict__ rows, int m_rows, ProjIn in, int n_in, int n_tasks, TileCover tc,
              float *__restrict__ part) {
   static_assert(MTILES * TB <= 6 && MTILES <= 4 && TB <= 2, "accumulators take at most 192 registers");
@@ -612,12 +612,13 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restric
   constexpr bool FOLD = TB == 1;
   constexpr int SEGMENT = FOLD ? TG_FOLD_CHUNKS : 1 << 20;   // chunks that are added up before they are folded
   static_assert(SEGMENT % 2 == 0, "whole turns of the ring of chunks");
-  constexpr size_t SCALE_AT = tg_lds_bytes(MTILES) - (sizeof(float) + sizeof(unsigned long long)) * MROWS;
+  constexpr size_t SCALE_AT = tg_scales_at(MTILES);
   extern __shared__ uint4 tg_smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (known to be uniform: addresses of weights stay scalar)
   f16_t *s_x = (f16_t *)tg_smem;                    // [3][2][MROWS * MG_ROWPAD]
-  float *s_down = (float *)((char *)tg_smem + SCALE_AT);   // per row: what undoes its scale
+  float *s_down = (float *)((char *)tg_smem + SCALE_AT);   // per activation row: what undoes its scale
+  float *s_wdown = (float *)((char *)tg_smem + SCALE_AT + (sizeof(float) + sizeof(unsigned long long)) * MROWS);   // and per weight row
   clear_words(in);
 
   int t, split = 0, bx, bz;
@@ -638,12 +639,10 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restric
   const int tb0 = (bx * TG_WAVES + wave) * TB;       // this wave's first 32 tasks
 
   const f16_t *abase[QT];   // A tile q: block 2 tb0 + q (past the end: the last one)
-  float wdown[QT];
 #pragma unroll
   for (int q = 0; q < QT; ++q) {
     const int block = min(2 * tb0 + q, n_blocks - 1);
     abase[q] = tiled + (size_t)block * n_chunks * TG_TILE + lane * 8;
-    wdown[q] = scale_down(scale_exponent(wmax[block] >> 23));
   }
   const int a_off = (lane & 31) * MG_ROWPAD + (lane >> 5) * 8;
 
@@ -713,6 +712,12 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restric
   constexpr int LPR = MG_KC / 8;
   const int xr0 = (int)threadIdx.x >> 3;
   RowExponent<LPR> mag0(in.row_max, min(row0 + xr0, m_rows - 1), threadIdx.x & 7);
+  float wd[TB];             // of weight row threadIdx.x + NT u of the workgroup's 64 TG_WAVES TB
+#pragma unroll
+  for (int u = 0; u < TB; ++u) {
+    const int r = (int)threadIdx.x + NT * u;
+    wd[u] = wdown[min(bx * (2 * TG_WAVES * TB) + r / 32, n_blocks - 1) * 32 + r % 32];
+  }
 #pragma unroll
   for (int n = 0; n < XV; ++n) { load_x1(n, 0, c_begin); load_x1(n, 1, c_begin); }
   __builtin_amdgcn_sched_barrier(0);
@@ -730,6 +735,8 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restric
     x_up[n] = scale_up(E);
     if (x_kv == 0) s_down[((int)threadIdx.x + n * NT) >> 3] = scale_down(E);
   }
+#pragma unroll
+  for (int u = 0; u < TB; ++u) s_wdown[(int)threadIdx.x + NT * u] = wd[u];
 #pragma unroll
   for (int n = 0; n < XV; ++n) {
 #pragma unroll
@@ -810,19 +817,23 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restric
   // activation row lane % 32, sums y_of(0 / 1, jb, c, r) of its two weight rows
   auto task_of = [&](int r) { return (r >> 3) * TG_TASKS + ((r >> 2) & 1) * 8 + (lane >> 5) * 4 + (r & 3); };
   auto y_of = [&](int which, int jb, int c, int r) { return acc[2 * jb + (r >> 3)][c][(r & 7) + 8 * which]; };
+  // (one factor after the other: their product may lie outside the range of an fp32 where the result does not)
 #pragma unroll
-  for (int c = 0; c < MTILES; ++c) {
-    const float xd = s_down[c * 32 + (lane & 31)];
+  for (int q = 0; q < QT; ++q) {
+    const float4 *w4 = (const float4 *)(s_wdown + (wave * QT + q) * 32 + 4 * (lane >> 5));   // operand rows 8 j + 4 (lane / 32) + 0..3
+    float w[16];
 #pragma unroll
-    for (int q = 0; q < QT; ++q) {
-      const float f = xd * wdown[q];
+    for (int j = 0; j < 4; ++j) *(float4 *)(w + 4 * j) = w4[2 * j];
+#pragma unroll
+    for (int c = 0; c < MTILES; ++c) {
+      const float xd = s_down[c * 32 + (lane & 31)];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         if constexpr (FOLD) acc[q][c][r] = folded[q][c][r];
-        acc[q][c][r] *= f;
+        acc[q][c][r] = acc[q][c][r] * xd * w[r];
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_sched_barrier(0);
   }
   if (!whole) {
     float *base = part + ((size_t)split * tc.n_cut + (t - tc.n_whole)) * TASKS * 2 * tc.m_pitch;
@@ -1107,17 +1118,18 @@ mfma_finish_tile_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, int n_
 // Only a long k with few tasks (down) is cut: CUT writes partial sums.
 constexpr int TD_WAVES = 8;
 constexpr int td_ring(int nt) { return nt == 1 ? 8 : nt == 2 ? 6 : 4; }
-constexpr size_t td_lds_bytes(int nt) { return sizeof(float) * (TD_WAVES / 2) * nt * 32 * 33 + sizeof(int) * OP_ROWS; }
+constexpr size_t td_lds_bytes(int nt) { return sizeof(float) * ((TD_WAVES / 2) * nt * 32 * 33 + OP_ROWS + nt * 32); }
 
 template <int NT, typename Epi, bool CUT>
 __global__ void __launch_bounds__(64 * TD_WAVES, 2)
-mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restrict__ wmax,
+mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__ wdown,
               const RowDesc *__restrict__ rows, int m_rows, ProjIn in, int n_in, int n_tasks, int n_groups,
               int chunks_per_split, float *__restrict__ part, int m_pitch) {
   constexpr int STEPS = MG_KC / 16, RING = td_ring(NT);
   extern __shared__ uint4 td_smem[];
   float *s_t = (float *)td_smem;                         // [4 waves][NT][32 operand rows][33]
   int *s_exp = (int *)(s_t + (TD_WAVES / 2) * NT * 32 * 33);
+  float *s_wdown = (float *)(s_exp + OP_ROWS);           // [NT][32 operand rows]
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   clear_words(in);
   const int split = CUT ? blockIdx.x / n_groups : 0, group = blockIdx.x - split * n_groups;
@@ -1148,6 +1160,9 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restri
     xr[u][1] = *(const float4 *)(p + 4 * OP_ROWS);
   };
   RowExponent<16> mag(in.row_max, min((int)threadIdx.x >> 4, m_rows - 1), threadIdx.x & 15);
+  static_assert(NT * 32 <= 64 * TD_WAVES, "a thread fetches one weight row's scale at most");
+  const int wd_row = min((int)threadIdx.x, NT * 32 - 1);
+  const float wd = wdown[min(group * NT + wd_row / 32, n_blocks - 1) * 32 + wd_row % 32];
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int u = 0; u < RING; ++u) { load_w(u, s_begin + u); load_x(u, s_begin + u); }
@@ -1155,6 +1170,7 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restri
   {
     const int e = mag.get();
     if ((threadIdx.x & 15) == 0) s_exp[threadIdx.x >> 4] = scale_exponent(e);
+    if (threadIdx.x < NT * 32) s_wdown[threadIdx.x] = wd;
   }
   __syncthreads();
   const int E = s_exp[lane & 31];
@@ -1204,9 +1220,12 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const uint32_t *__restri
     const float down = scale_down(E);
 #pragma unroll
     for (int q = 0; q < NT; ++q) {
-      const float d = scale_down(scale_exponent(wmax[min(group * NT + q, n_blocks - 1)] >> 23)) * down;
+      const float4 *w4 = (const float4 *)(s_wdown + q * 32 + 4 * (lane >> 5));
+      float w[16];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s_t[at(wave, q, r)] = (acc[q][r] + s_t[at(wave, q, r)]) * d;
+      for (int j = 0; j < 4; ++j) *(float4 *)(w + 4 * j) = w4[2 * j];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s_t[at(wave, q, r)] = (acc[q][r] + s_t[at(wave, q, r)]) * down * w[r];
     }
   }
   __syncthreads();

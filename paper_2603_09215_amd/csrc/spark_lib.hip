@@ -41,7 +41,7 @@ struct Layout {  // byte offsets into the scratch buffer
   size_t state, page_table, plan, lower, upper, ee, full, prefill_rows, prefill_tokens, seq_ids,
       forced, step_flags, out_tokens, out_depth, best, arrivals, row_ssq, max_x, max_attn, max_act, sample_hist, sample_arrive, sample_count, hidden, xnorm, mfma_part, sample_q, sample_cand, rand_words, qbuf, attn_out, part, act, lens_u,
       logits, rope, inv_freq, total,
-      tiled, wmax, total_tiled,   // the MFMA-ordered copy of the projection weights and its scales lie behind everything else (absent on the static area)
+      tiled, wdown, total_tiled,   // the MFMA-ordered copy of the projection weights and its scales lie behind everything else (absent on the static area)
       prompt_hidden, prompt_q, prompt_attn, prompt_act, prompt_xnorm, prompt_ssq, prompt_max_x, prompt_max_attn, prompt_max_act,
       total_prompt;        // and behind them the buffers of the largest prompt passes
 };
@@ -53,7 +53,7 @@ struct Derived {
 
 // Where the MFMA-ordered copies of the projection matrices lie (from the start of
 // the tiled region; per layer for the four projections of a layer).
-struct TiledMatrix { size_t elems = 0, blocks = 0; };   // offsets of its tiles and of its blocks' scale words
+struct TiledMatrix { size_t elems = 0, blocks = 0; };   // offsets of its tiles (elements) and of its scales (blocks of 32)
 struct TiledMap {
   std::vector<TiledMatrix> qkv, o, gateup, down;
   TiledMatrix lens_a, lens_head, lm_head;
@@ -308,8 +308,8 @@ void layout(const spark_config &c, const Derived &d, Layout &l) {
   TiledMap tm;
   tiled_map(c, d, tm);
   l.tiled = o;
-  l.wmax = o + align_up(sizeof(f16_t) * tm.total, 256);
-  l.total_tiled = l.wmax + align_up(sizeof(uint32_t) * tm.blocks, 256);
+  l.wdown = o + align_up(sizeof(f16_t) * tm.total, 256);
+  l.total_tiled = l.wdown + align_up(sizeof(float) * 32 * tm.blocks, 256);
   o = l.total_tiled;
   const size_t n = shape_allows_mfma(c) ? PROMPT_ROWS : 0;
   l.prompt_hidden = take(sizeof(float) * n * c.d_model);
@@ -601,10 +601,10 @@ int launch_tiled(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n
   if (int rc = partials_fit(c, tiled_partial_bytes(tc, TB))) return rc;
   if (max_words) *max_words = tc.n_cut ? (n_tasks + 31) / 32 : (n_tasks + 32 * TB - 1) / (32 * TB);
   const f16_t *tiled = at<f16_t>(c, c->lo.tiled) + w.elems;
-  const uint32_t *wmax = at<uint32_t>(c, c->lo.wmax) + w.blocks;
+  const float *wdown = at<float>(c, c->lo.wdown) + w.blocks * 32;
   float *part = at<float>(c, c->lo.mfma_part);
   const int grid = tc.n_whole + tc.n_cut * tc.n_split;
-  const size_t lds = tg_lds_bytes(MTILES);
+  const size_t lds = tg_lds_bytes(MTILES, TB);
   auto launch = [&](auto kern) {
     if (lds > 65536) {
       const auto key = std::make_pair((const void *)kern, lds);
@@ -613,7 +613,7 @@ int launch_tiled(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n
         c->occ_cache.emplace(key, 1);
       }
     }
-    kern<<<grid, 64 * TG_WAVES, lds, c->stream>>>(epi, tiled, wmax, rows, m, in, n_in, n_tasks, tc, part);
+    kern<<<grid, 64 * TG_WAVES, lds, c->stream>>>(epi, tiled, wdown, rows, m, in, n_in, n_tasks, tc, part);
     HIP_TRY(c, hipGetLastError());
     return SPARK_OK;
   };
@@ -656,7 +656,7 @@ int launch_direct_tiles(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m
       c->occ_cache.emplace(key, 1);
     }
   }
-  kern<<<groups * split, 64 * TD_WAVES, lds, c->stream>>>(epi, at<f16_t>(c, c->lo.tiled) + w.elems, at<uint32_t>(c, c->lo.wmax) + w.blocks,
+  kern<<<groups * split, 64 * TD_WAVES, lds, c->stream>>>(epi, at<f16_t>(c, c->lo.tiled) + w.elems, at<float>(c, c->lo.wdown) + w.blocks * 32,
                                                           rows, m, in, n_in, n_tasks, groups, cps, at<float>(c, c->lo.mfma_part),
                                                           (int)align_up(m, 8));
   HIP_TRY(c, hipGetLastError());
@@ -799,10 +799,8 @@ const TiledMatrix *tiled_at(spark_ctx *c, const TiledMatrix &w) { return c->has_
 template <typename Epi>
 int tile_one(spark_ctx *c, const Epi &epi, int n_tasks, int n_in, const TiledMatrix &w) {
   const int n_chunks = (n_in + MG_KC - 1) / MG_KC, blocks = (int)tg_blocks(n_tasks);
-  uint32_t *wmax = at<uint32_t>(c, c->lo.wmax) + w.blocks;
-  weights_amax_k<<<dim3((n_chunks + TG_AMAX_CHUNKS - 1) / TG_AMAX_CHUNKS, blocks), 256, 0, c->stream>>>(epi, n_tasks, n_in, wmax);
-  tile_weights_k<<<dim3(n_chunks, blocks), 256, 0, c->stream>>>(epi, n_tasks, n_in, n_chunks, wmax,
-                                                               at<f16_t>(c, c->lo.tiled) + w.elems);
+  tile_weights_k<<<blocks * (32 / TW_ROWS), TW_THREADS, 0, c->stream>>>(epi, n_tasks, n_in, n_chunks, at<float>(c, c->lo.wdown) + w.blocks * 32,
+                                                                       at<f16_t>(c, c->lo.tiled) + w.elems);
   HIP_TRY(c, hipGetLastError());
   return SPARK_OK;
 }
@@ -815,7 +813,6 @@ int build_tiled(spark_ctx *c) {
   const int d = g.d_model, hd = g.head_dim, nq = g.n_q_heads, nkv = g.n_kv_heads, F = g.d_ffn, V = c->dv.V;
   const size_t qw = (size_t)nq * hd, kvw = (size_t)nkv * hd;
   int rc;
-  HIP_TRY(c, hipMemsetAsync(at<uint32_t>(c, c->lo.wmax), 0, sizeof(uint32_t) * c->tm.blocks, c->stream));
   for (int l = 0; l < g.n_layers; ++l) {
     EpiQKV<WT> eq;
     eq.wq = (const WT *)c->w.wq + (size_t)l * qw * d;

@@ -82,32 +82,40 @@ def first_step(spark, tokens, full=None):
     return ids, depth
 
 
-@pytest.mark.parametrize("rows", [5, 32, 33, 64, 96, 128, 129])
-def test_head_against_64_bits(sb, rows):
+@pytest.mark.parametrize("rows,spread", [(5, 0), (32, 0), (33, 0), (64, 0), (96, 0), (128, 0), (129, 0), (7, 60), (70, 60)])
+def test_head_against_64_bits(sb, rows, spread):
+    """spread: the vocabulary's rows times powers of two between 2^-spread and 2^spread (their logits
+    are compared without them): neighbouring rows share tiles, and nothing else"""
     import torch
-    say(f"case head alone, {rows} rows")
+    say(f"case head alone, {rows} rows, spread {spread}")
     shape = wl.TINY.shape.replace(name="head", dtype=wl.DTYPE_BF16, n_layers=1, d_model=D, n_q_heads=2, n_kv_heads=1,
                                   head_dim=128, d_ffn=64, vocab_text=VOCAB, vocab_speech=0)
     sched = wl.TINY.schedule.replace(exit_layer=1, period_k=1, phase=0, n_text=1, n_speech=0)
     W = model(shape, False)
+    power = torch.as_tensor(np.random.default_rng(3).integers(-spread, spread + 1, VOCAB), device="cuda:0")
+    W["lm_head"] = torch.ldexp(W["lm_head"].float(), power[:, None]).bfloat16()
     sp = sb.Spark(shape, sched, W, max_batch=rows, max_seq_len=16, kv_page_tokens=16)
     tokens = np.random.default_rng(rows).integers(0, VOCAB, rows)
     ids, _ = first_step(sp, tokens)
     x = norm64(W["embed"][torch.as_tensor(tokens, device="cuda:0")], W["final_norm"], shape.rms_eps)
-    err = row_errors([sp.get_logits(i)[0] for i in ids], x @ W["lm_head"].double().T)
+    unit = torch.ldexp(torch.ones(VOCAB, device="cuda:0", dtype=torch.float64), -power)
+    err = row_errors([sp.get_logits(i)[0] * unit.cpu().numpy() for i in ids], x @ W["lm_head"].double().T * unit)
     say(f"  head, {rows} rows: mean {err.mean():.3g}, largest {err.max():.3g}")
     assert err.max() <= 3e-7
     sp.close()
 
 
-@pytest.mark.parametrize("rows", [6, 32, 40, 96, 150])
-def test_mlp_against_64_bits(sb, rows):
+@pytest.mark.parametrize("rows,power", [(6, 0), (32, 0), (40, 0), (96, 0), (150, 0), (6, 50), (40, 50), (40, -50)])
+def test_mlp_against_64_bits(sb, rows, power):
+    """power: the up projection times 2^-power, which the down projection undoes; gate and up share
+    tiles"""
     import torch
-    say(f"case MLP alone, {rows} rows")
+    say(f"case MLP alone, {rows} rows, power {power}")
     shape = wl.TINY.shape.replace(name="mlp", dtype=wl.DTYPE_BF16, n_layers=2, d_model=D, n_q_heads=2, n_kv_heads=1,
                                   head_dim=128, d_ffn=FFN, vocab_text=0, vocab_speech=D)
     sched = wl.TINY.schedule.replace(exit_layer=1, period_k=2, phase=1, n_text=0, n_speech=1, scope=wl.SCOPE_STREAM)
     W = model(shape, True)
+    W["wu"], W["wd"] = W["wu"] * 2.0 ** -power, W["wd"] * 2.0 ** power
     sp = sb.Spark(shape, sched, W, max_batch=rows, max_seq_len=16, kv_page_tokens=16)
     tokens = np.random.default_rng(rows).integers(0, D, rows)
     # four rows run full depth: their head is the vector kernel, in fp32, and shows the hidden state
