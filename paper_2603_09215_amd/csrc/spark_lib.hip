@@ -799,8 +799,9 @@ const TiledMatrix *tiled_at(spark_ctx *c, const TiledMatrix &w) { return c->has_
 template <typename Epi>
 int tile_one(spark_ctx *c, const Epi &epi, int n_tasks, int n_in, const TiledMatrix &w) {
   const int n_chunks = (n_in + MG_KC - 1) / MG_KC, blocks = (int)tg_blocks(n_tasks);
-  tile_weights_k<<<blocks * (32 / TW_ROWS), TW_THREADS, 0, c->stream>>>(epi, n_tasks, n_in, n_chunks, at<float>(c, c->lo.wdown) + w.blocks * 32,
-                                                                       at<f16_t>(c, c->lo.tiled) + w.elems);
+  const auto kern = n_in <= 4 * 1024 ? tile_weights_k<Epi, 4> : n_in <= TW_HELD * 1024 ? tile_weights_k<Epi, TW_HELD> : tile_weights_k<Epi, 0>;
+  kern<<<blocks * (32 / TW_ROWS), TW_THREADS, 0, c->stream>>>(epi, n_tasks, n_in, n_chunks, at<float>(c, c->lo.wdown) + w.blocks * 32,
+                                                             at<f16_t>(c, c->lo.tiled) + w.elems);
   HIP_TRY(c, hipGetLastError());
   return SPARK_OK;
 }

@@ -105,14 +105,15 @@ def test_head_against_64_bits(sb, rows, spread):
     sp.close()
 
 
-@pytest.mark.parametrize("rows,power", [(6, 0), (32, 0), (40, 0), (96, 0), (150, 0), (6, 50), (40, 50), (40, -50)])
-def test_mlp_against_64_bits(sb, rows, power):
+@pytest.mark.parametrize("rows,power,ffn", [(6, 0, FFN), (32, 0, FFN), (40, 0, FFN), (96, 0, FFN), (150, 0, FFN), (6, 50, FFN),
+                                           (40, 50, FFN), (40, -50, FFN), (6, 0, 20488), (40, 0, 20480)])
+def test_mlp_against_64_bits(sb, rows, power, ffn):
     """power: the up projection times 2^-power, which the down projection undoes; gate and up share
-    tiles"""
+    tiles.  20480 is the longest input whose copy is written from registers."""
     import torch
     say(f"case MLP alone, {rows} rows, power {power}")
     shape = wl.TINY.shape.replace(name="mlp", dtype=wl.DTYPE_BF16, n_layers=2, d_model=D, n_q_heads=2, n_kv_heads=1,
-                                  head_dim=128, d_ffn=FFN, vocab_text=0, vocab_speech=D)
+                                  head_dim=128, d_ffn=ffn, vocab_text=0, vocab_speech=D)
     sched = wl.TINY.schedule.replace(exit_layer=1, period_k=2, phase=1, n_text=0, n_speech=1, scope=wl.SCOPE_STREAM)
     W = model(shape, True)
     W["wu"], W["wd"] = W["wu"] * 2.0 ** -power, W["wd"] * 2.0 ** power
