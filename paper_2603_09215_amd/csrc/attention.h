@@ -11,6 +11,8 @@
 // reads 64/LPT whole rows per instruction; all K and V loads of the slice are issued before any
 // use.
 #pragma once
+#include <limits.h>
+
 #include "device_common.h"
 
 namespace spark {
@@ -631,6 +633,7 @@ attn_prompt_k(const RowDesc *__restrict__ rows, int m_rows, const float *__restr
               int group, int rows_per_wg, int n_row_tiles, float scale, RowOut out, RowMax row_max) {
   static_assert(HD == 128, "tiles and swizzles are for 128 elements");
   extern __shared__ uint4 ap_smem[];
+  __shared__ int s_bad;   // the first token whose values were left out for not being finite
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int half = wave >> 2, hl = lane >> 5, col = lane & 31;
   const int hk = blockIdx.x % kv.n_kv_heads;
@@ -668,7 +671,25 @@ attn_prompt_k(const RowDesc *__restrict__ rows, int m_rows, const float *__restr
 #pragma unroll
     for (int i = 0; i < 4; ++i) *(attn_u32x4_t *)(d + 16 * i * AP_KPITCH) = kv_r[i];
   };
-  auto store_v = [&](int buf) {
+  // The values of a token meet the zero probabilities of the rows before it, and zero times infinity is
+  // NaN: in tiles that reach past the first row, a token that not all rows attend goes in as zeros if it
+  // is not finite, and what the rows from it on get is set to NaN at the end (which is what their next
+  // projection would make of one such element).
+  auto store_v = [&](int t, int buf) {
+    const int t0 = min(t, n_tiles - 1) * ATTN_SLICE, last = pos0 + n_rows - 1;
+    if (t0 + ATTN_SLICE - 1 > pos0) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int tok = min(t0 + 4 * kt + i, last);
+        bool bad = false;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bad |= (kv_r[i][e] & 0x7f80u) == 0x7f80u || (kv_r[i][e] & 0x7f800000u) == 0x7f800000u;
+        if (bad && tok > pos0) {
+          kv_r[i] = attn_u32x4_t{0u, 0u, 0u, 0u};
+          atomicMin(&s_bad, tok);
+        }
+      }
+    }
     bf16_t *d = s_v + buf * AP_BUF_ELEMS + 8 * kc * AP_VPITCH + 4 * kt;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {   // element 8 kc + e of four tokens
@@ -679,9 +700,11 @@ attn_prompt_k(const RowDesc *__restrict__ rows, int m_rows, const float *__restr
     }
   };
   load_kv(half, 0);
+  if (threadIdx.x == 0) s_bad = INT_MAX;
+  __syncthreads();
   store_k(0);
   load_kv(half, 1);
-  store_v(0);
+  store_v(half, 0);
   __builtin_amdgcn_sched_barrier(0);
 
   // the scaled query, three bf16 parts (truncation, exact remainders)
@@ -790,7 +813,7 @@ attn_prompt_k(const RowDesc *__restrict__ rows, int m_rows, const float *__restr
       __builtin_amdgcn_sched_barrier(0);
       if (more) {
         if (tb == 0) { store_k(buf ^ 1); load_kv(t + 2, 1); }
-        else store_v(buf ^ 1);
+        else store_v(t + 2, buf ^ 1);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -813,7 +836,7 @@ attn_prompt_k(const RowDesc *__restrict__ rows, int m_rows, const float *__restr
   if (half == 1) return;
   const float other_max = mine[64 * 64], M = fmaxf(run_max, other_max);   // (token 0 is everybody's: finite)
   const float f0 = expf(run_max - M), f1 = expf(other_max - M);
-  const float inv = 1.0f / (run_sum * f0 + mine[65 * 64] * f1);
+  const float inv = pos >= s_bad ? NAN : 1.0f / (run_sum * f0 + mine[65 * 64] * f1);
   uint32_t big = 0u;
 #pragma unroll
   for (int b = 0; b < HD / 32; ++b)

@@ -52,6 +52,33 @@ def test_prompt_lengths(sb, n, page, group):
     sp.close()
 
 
+@pytest.mark.parametrize("n,at,page", [(130, 70, 64), (130, 127, 16), (200, 3, 64), (1030, 1020, 64)])
+def test_a_nan_stays_behind_its_position(sb, n, at, page):
+    """a prompt with a token whose embedding is NaN: cache entries of the positions before it are
+    those of the same prompt without it, bit by bit, and from it on none is finite in the upper layers"""
+    say(f"case NaN at {at} of {n}")
+    shape = SHAPE.replace(n_q_heads=14, n_kv_heads=2)
+    weights = wl.make_weights(shape, seed=12, gain_std=0.1)
+    bad = shape.vocab - 1
+    weights["embed"][bad] = wl.f32_to_bf16_bits(np.full(shape.d_model, np.nan, dtype=np.float32))
+    prompt = wl.make_prompt(shape, n, seed=61) % bad
+    marked = prompt.copy()
+    marked[at] = bad
+    sp = sb.Spark(shape, wl.TINY.schedule, weights, max_batch=2, max_seq_len=n + 64, kv_page_tokens=page)
+    a, b = sp.seq_open(0), sp.seq_open(0)
+    sp.prefill(a, prompt)
+    sp.prefill(b, marked)
+    top = shape.n_layers - 1
+    for pos in range(n - 1):
+        if pos < at:
+            for layer in (1, top):
+                for want, got in zip(sp.get_kv(a, layer, pos), sp.get_kv(b, layer, pos)):
+                    assert np.array_equal(want, got), (layer, pos)
+        else:
+            assert all(np.all(np.isnan(x)) for x in sp.get_kv(b, top, pos)), pos
+    sp.close()
+
+
 @pytest.fixture
 def filled_scratch():
     """torch.empty filled with 0xff bytes: what the scratch area holds that nobody has written"""
