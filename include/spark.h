@@ -298,16 +298,19 @@ int spark_measure_read(spark_ctx *ctx, const void *buf, size_t bytes, int32_t re
 /* Kernel-selection switches of one context, for tests and sweeps; the defaults are the measured
  * choices and nothing in the results depends on them beyond rounding order.  name [host]:
  *   "mfma" (0: every row count stays on the vector kernels), "mfma_min_rows" (rows from which the
- *   projections run on the MFMA units), "mfma_small_tiles", "mfma_xcd_max_split",
- *   "attn_pieces" (64-token pieces per attention workgroup, 0 = by the size of the launch, at most
- *   8), "attn_mfma_min_rows", "attn_prompt_min_rows" (rows from which a prompt pass shares K and V
+ *   projections run on the MFMA units), "mfma_xcd_max_split",
+ *   "attn_pieces" (64-token pieces per attention workgroup, from eight on with two teams of waves, at
+ *   most 10; 0: pieces and teams by the size of the launch), "attn_mfma_min_rows",
+ *   "attn_prompt_min_rows" (rows from which a prompt pass shares K and V
  *   between its rows), "gemv_big_kb", "mfma_tiled" (0: the MFMA projections stage the
  *   caller's weight rows through LDS instead of reading the context's copy in operand order),
- *   "mfma_small_max_k", "direct_max_rows" (rows up to which they do without LDS, at most 32),
+ *   "mfma_small_tiles" and "mfma_small_max_k" (which of those launches run four waves a workgroup),
+ *   "direct_max_rows" (rows up to which those on the copy do without LDS, at most 32),
  *   "direct_whole_k" (the longest input width whose few tasks those never cut over workgroups),
- *   "tiled_row_blocks" (blocks of 32 rows in a row tile of the others, 2..4), "fuse_norm" (0: every
- *   RMSNorm of the batched path is its own launch), "prefill_rows" (prompt rows per pass, a
- *   multiple of 32, at most 256; unset, passes of up to 1024 rows where the scratch area has room).
+ *   "tiled_row_blocks" (blocks of 32 rows in a row tile of the others, 2..4, at most), "fuse_norm" (0:
+ *   every RMSNorm of the batched path is its own launch), "prefill_rows" (prompt rows per pass, a
+ *   multiple of 32, at most 1024, or 256 where the scratch area has no room for more; 0: by the
+ *   length of the prompt, as in a new context).
  * SPARK_EINVAL for an unknown name. */
 int spark_tune(spark_ctx *ctx, const char *name, int32_t value);
 

@@ -118,7 +118,7 @@ struct spark_ctx {
   int device = 0;
   float temperature = 0.f, top_p = 0.f;   // nucleus sampling, off while temperature <= 0
   int prefill_base = 128;    // prompt rows per pass in the base buffers, see spark_init
-  int prefill_chunk = 0;     // > 0: as set by "prefill_rows"
+  int prefill_chunk = 0;     // > 0: prompt rows per pass, as set by "prefill_rows"
   bool prompt_pass = false;  // the pass being enqueued: consecutive positions of one sequence
   int attn_prompt_min_rows = 64;   // rows from which such a pass shares K and V between its rows
   int attn_splits_now = 0;   // context slices the rows of the passes being enqueued can reach (0: unknown, launch all)
@@ -1227,9 +1227,10 @@ template <typename WT> int prefill_rows(spark_ctx *c, int id, const int32_t *pro
   const spark_config &g = c->cfg;
   // A large pass has its own buffers; one in the base buffers takes the slots behind the sequences'.
   // Passes are of equal size, in whole tiles of rows, unless their size has been set.
-  const bool large = c->prompt.rows > 0 && c->prefill_chunk == 0 && c->use_tiled && c->use_mfma && n_rows > c->prefill_base;
-  int chunk = c->prefill_chunk > 0 ? c->prefill_chunk : c->prefill_base;
-  if (large) {
+  const bool large = c->prompt.rows > 0 && c->use_tiled && c->use_mfma &&
+                     (c->prefill_chunk > 0 ? c->prefill_chunk > PREFILL_CHUNK : n_rows > c->prefill_base);
+  int chunk = c->prefill_chunk > 0 ? std::min(c->prefill_chunk, large ? PROMPT_ROWS : PREFILL_CHUNK) : c->prefill_base;
+  if (large && c->prefill_chunk == 0) {
     const int passes = (n_rows + PROMPT_ROWS - 1) / PROMPT_ROWS;
     chunk = std::min(PROMPT_ROWS, (int)align_up((n_rows + passes - 1) / passes, 128));
   }
@@ -1452,10 +1453,10 @@ int spark_tune(spark_ctx *c, const char *name, int32_t value) {
   else if (k == "mfma_min_rows") c->mfma_min_rows = std::max(1, (int)value);
   else if (k == "mfma_small_tiles") c->mfma_small_tiles = value;
   else if (k == "mfma_xcd_max_split") c->mfma_xcd_max_split = value;
-  else if (k == "attn_pieces") c->attn_pieces = std::max(0, std::min(8, (int)value));
+  else if (k == "attn_pieces") c->attn_pieces = std::max(0, std::min(10, (int)value));
   else if (k == "attn_mfma_min_rows") c->attn_mfma_min_rows = std::max(1, (int)value);
   else if (k == "gemv_big_kb") c->gemv_big_kb = std::max(1, (int)value);
-  else if (k == "prefill_rows") c->prefill_chunk = std::max(32, std::min(PREFILL_CHUNK, (int)value / 32 * 32));
+  else if (k == "prefill_rows") c->prefill_chunk = value == 0 ? 0 : std::max(32, std::min(PROMPT_ROWS, (int)value / 32 * 32));
   else if (k == "mfma_small_max_k") c->mfma_small_max_k = std::max(8, (int)value);
   else if (k == "mfma_tiled") c->use_tiled = value != 0;
   else if (k == "tiled_row_blocks") c->tiled_row_blocks = std::max(2, std::min(4, (int)value));

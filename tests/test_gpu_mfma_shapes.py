@@ -52,6 +52,31 @@ def test_prompt_lengths(sb, n, page, group):
     sp.close()
 
 
+def test_prompt_rows_can_be_set_and_unset(sb):
+    """"prefill_rows": passes of a set size, up to that of the large buffers, and back to the size that
+    a new context chooses"""
+    say("case prompt rows set and unset")
+    weights = wl.make_weights(SHAPE, seed=12, gain_std=0.1)
+    prompt = wl.make_prompt(SHAPE, 600, seed=61)
+
+    def entries(*values):
+        sp = sb.Spark(SHAPE, wl.TINY.schedule, weights, max_batch=1, max_seq_len=640, kv_page_tokens=64)
+        for v in values:
+            sp.tune("prefill_rows", v)
+        sid = sp.seq_open(0)
+        sp.prefill(sid, prompt)
+        out = np.stack([np.concatenate(sp.get_kv(sid, SHAPE.n_layers - 1, p)) for p in range(599)])
+        sp.close()
+        return out
+
+    default = entries()
+    assert np.array_equal(default, entries(128, 0))       # unset: the same passes, bit by bit
+    assert not np.array_equal(default, entries(32))       # other passes: other k ranges, other roundings
+    assert np.array_equal(default, entries(640))          # one pass of 599 rows either way
+    for rows in (32, 256, 320, 1024, 5000):
+        assert np.max(np.abs(default - entries(rows))) <= TOL[wl.DTYPE_BF16] + 2.0 ** -7 * np.abs(default).max()
+
+
 @pytest.mark.parametrize("n,at,page", [(130, 70, 64), (130, 127, 16), (200, 3, 64), (1030, 1020, 64)])
 def test_a_nan_stays_behind_its_position(sb, n, at, page):
     """a prompt with a token whose embedding is NaN: cache entries of the positions before it are
