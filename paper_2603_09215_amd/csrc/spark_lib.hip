@@ -105,7 +105,7 @@ struct spark_ctx {
   int direct_max_rows = 32;     // rows up to which mfma_direct_k runs
   int direct_whole_k = 8192;    // ... and the longest k that it never cuts
   int mfma_xcd_max_split = 4;  // row tiles share an XCD when k has at most this many ranges
-  int mfma_small_tiles = 64;   // launches of mfma_rows_k with fewer 8-wave tiles use 4-wave workgroups
+  int mfma_small_tiles = 32;   // launches of mfma_rows_k with fewer 8-wave tiles use 4-wave workgroups
   int mfma_min_rows = MFMA_MIN_ROWS;
   int attn_pieces = 0;         // 64-token pieces per attention workgroup (0: by the launch's size)
   int gemv_big_kb = 40;        // vector-kernel launches with more LDS per workgroup run eight waves per workgroup
