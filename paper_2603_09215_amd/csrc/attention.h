@@ -106,9 +106,7 @@ __device__ __forceinline__ void attn_merge(const RowDesc &rd, int r, int hq0, in
       }
     }
     const float inv = 1.0f / L;
-    float *dst = out.at(r, (hq0 + g) * HD + c);
-    store2_maybe_ds<DS>(dst, make_float2(acc4.x * inv, acc4.y * inv));
-    store2_maybe_ds<DS>(dst + 2, make_float2(acc4.z * inv, acc4.w * inv));
+    out.put(r, (hq0 + g) * HD + c, make_float4(acc4.x * inv, acc4.y * inv, acc4.z * inv, acc4.w * inv));
     const uint32_t m01 = max(magnitude_bits(acc4.x * inv), magnitude_bits(acc4.y * inv));
     const uint32_t m23 = max(magnitude_bits(acc4.z * inv), magnitude_bits(acc4.w * inv));
     big = max(big, max(m01, m23));
@@ -241,7 +239,7 @@ __device__ __forceinline__ void attn_task(const RowDesc &rd, int r, int hk, int 
 #pragma unroll
       for (int w = 0; w < WAVES; ++w) o += ored[(w * G + g) * HD + c];
       const float inv = 1.0f / ml[g * 2 + 1], y = o * inv;
-      store_maybe_ds<DS>(out.at(r, (hq0 + g) * HD + c), y);
+      out.put(r, (hq0 + g) * HD + c, y);
       big = max(big, magnitude_bits(y));
     }
     put_wave_max<NT>(row_max, r, big);
@@ -553,7 +551,7 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
   if (rd.pos < span) {   // the whole context is this slice: nothing to hand over and nobody to wait for
     __syncthreads();
     uint32_t big = 0u;
-    if (team == 0) {
+    auto finish = [&](auto store) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int g = 4 * quad + i;
@@ -562,10 +560,14 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
         for (int t = 0; t < 2; ++t)
           if (g < group) {
             const float y = oacc[t][i] * inv;
-            *out.at(r, (hq0 + g) * HD + 32 * wave + 16 * t + col) = y;
+            store((hq0 + g) * HD + 32 * wave + 16 * t + col, y);
             big = max(big, magnitude_bits(y));
           }
       }
+    };
+    if (team == 0) {
+      if (out.part_units) finish([&](int k, float y) { out.put_parts(r, k, y); });
+      else finish([&](int k, float y) { *out.at(r, k) = y; });
     }
     put_wave_max<ATTN_THREADS * TEAMS>(row_max, r, big);
     return;
@@ -848,7 +850,7 @@ attn_prompt_k(const RowDesc *__restrict__ rows, int m_rows, const float *__restr
         y[e] = (o[b][4 * i + e] * f0 + mine[(b * 16 + 4 * i + e) * 64] * f1) * inv;
         big = max(big, magnitude_bits(y[e]));
       }
-      if (live) *(float4 *)out.at(row0 + row, head * HD + 32 * b + 8 * i + 4 * hl) = make_float4(y[0], y[1], y[2], y[3]);
+      if (live) out.put(row0 + row, head * HD + 32 * b + 8 * i + 4 * hl, make_float4(y[0], y[1], y[2], y[3]));
     }
   if (row_max.list) {
     big = max(big, (uint32_t)__shfl_xor((int)big, 32, 64));

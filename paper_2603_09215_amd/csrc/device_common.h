@@ -105,13 +105,62 @@ struct RowMax {
     list[(size_t)r * stride + i] = (uint8_t)(magnitude >> 23);
   }
 };
-// Where the rows of a pass go that a projection will read: row-major, or for a pass of at most 32
-// rows in the order the projection's matrix operand wants them, [k / 4][32 rows][4].
+// Where the rows of a pass go that a projection will read.  For the kernels on the fp16 copy of the
+// weights: fp32, row-major, or for a pass of at most 32 rows in the order the projection's matrix operand
+// wants them, [k / 4][32 rows][4].  For the kernel on the caller's bf16 weights: three bf16 parts, written
+// by whoever produces a row, once (with every workgroup of a projection cutting them itself, steps and
+// prompts of such contexts took 12 to 45 % longer).
 struct RowOut {
   float *p;
-  int stride;       // elements from row to row; 0: operand order
+  int stride;       // fp32: elements from row to row, 0: operand order; parts: elements of a row
+  int part_units;   // 0: fp32; otherwise p points to bf16 parts, this many 64 elements apart, rows padded to 64
   __device__ __forceinline__ float *at(int r, int k) const {   // k..k|3 are neighbours in both
     return p + (stride ? (size_t)r * stride + k : (size_t)(k >> 2) * (4 * OP_ROWS) + r * 4 + (k & 3));
+  }
+  __host__ __device__ __forceinline__ int pitch() const { return (stride + 63) & ~63; }
+  __device__ __forceinline__ size_t part_stride() const { return (size_t)part_units * 64; }
+  __device__ __forceinline__ bf16_t *part_at(int r, int k) const { return (bf16_t *)p + (size_t)r * pitch() + k; }
+  // the thread that writes a row's last elements also clears what follows them
+  __device__ __forceinline__ void clear_rest(int r, int k_end) const {
+    if (k_end < stride) return;
+    for (int z = stride; z < pitch(); z += 2)
+#pragma unroll
+      for (int i = 0; i < 3; ++i) *(uint32_t *)(part_at(r, z) + i * part_stride()) = 0u;
+  }
+  __device__ __forceinline__ void put_parts(int r, int k, float v) const {
+    bf16_t *d = part_at(r, k);
+    bf16_t h, m, l;
+    split3_bf16(v, h, m, l);
+    d[0] = h;
+    d[part_stride()] = m;
+    d[2 * part_stride()] = l;
+    clear_rest(r, k + 1);
+  }
+  __device__ __forceinline__ void put_parts(int r, int k, float v0, float v1) const {   // k even
+    bf16_t *d = part_at(r, k);
+    bf16_t h0, m0, l0, h1, m1, l1;
+    split3_bf16(v0, h0, m0, l0);
+    split3_bf16(v1, h1, m1, l1);
+    *(uint32_t *)d = h0 | ((uint32_t)h1 << 16);
+    *(uint32_t *)(d + part_stride()) = m0 | ((uint32_t)m1 << 16);
+    *(uint32_t *)(d + 2 * part_stride()) = l0 | ((uint32_t)l1 << 16);
+    clear_rest(r, k + 2);
+  }
+  __device__ __forceinline__ void put(int r, int k, float v) const {
+    if (part_units) put_parts(r, k, v);
+    else *at(r, k) = v;
+  }
+  __device__ __forceinline__ void put(int r, int k, float4 v) const {                   // k a multiple of four
+    if (!part_units) { *(float4 *)at(r, k) = v; return; }
+    const float f[4] = {v.x, v.y, v.z, v.w};
+    bf16_t h[4], m[4], l[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) split3_bf16(f[e], h[e], m[e], l[e]);
+    bf16_t *d = part_at(r, k);
+    *(uint2 *)d = make_uint2(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16));
+    *(uint2 *)(d + part_stride()) = make_uint2(m[0] | ((uint32_t)m[1] << 16), m[2] | ((uint32_t)m[3] << 16));
+    *(uint2 *)(d + 2 * part_stride()) = make_uint2(l[0] | ((uint32_t)l[1] << 16), l[2] | ((uint32_t)l[3] << 16));
+    clear_rest(r, k + 4);
   }
 };
 __device__ __forceinline__ uint32_t magnitude_bits(float x) { return __float_as_uint(x) & 0x7fffffffu; }

@@ -288,7 +288,8 @@ template <typename WT, bool DS = false> struct EpiResidual {
 // h: gamma (.) h for pass row r, h's sum of squares (see RowScale) and the largest magnitude of
 // gamma (.) h.  For the finishing launch of a k-split projection, whose threads of one row are 32
 // lanes apart.
-template <typename WT> struct EpiResidualNorm {
+// SPLIT: as three bf16 parts, and without the magnitude.
+template <typename WT, bool SPLIT = false> struct EpiResidualNorm {
   struct State { float ssq; uint32_t amax; };
   const WT *w;
   int n_in, n_out;
@@ -315,7 +316,8 @@ template <typename WT> struct EpiResidualNorm {
     *(float2 *)(hidden + (size_t)rd.x_slot * d + 2 * task) = v;
     s.ssq += v.x * v.x + v.y * v.y;
     const float2 n = make_float2(v.x * o.z, v.y * o.w);
-    *(float2 *)x.at(r, 2 * task) = n;
+    if constexpr (SPLIT) x.put_parts(r, 2 * task, n.x, n.y);
+    else *(float2 *)x.at(r, 2 * task) = n;
     s.amax = max(s.amax, max(magnitude_bits(n.x), magnitude_bits(n.y)));
   }
   __device__ void finish(int task, int r, const RowDesc &rd, float y0, float y1, State &s) const {
@@ -324,19 +326,23 @@ template <typename WT> struct EpiResidualNorm {
   // `s`: the states of the threads that finished the 32 tasks of `block` in row r, combined
   __device__ void put_row(int r, int block, const State &s) const {
     atomicAdd(ssq + r * SSQ_WAYS + block % SSQ_WAYS, (unsigned long long)(s.ssq * SSQ_SCALE + 0.5f));
-    row_max.put(r, block, s.amax);
+    if constexpr (!SPLIT) row_max.put(r, block, s.amax);
   }
   __device__ void end(int, const RowDesc &, State &) const {}
 };
 // epilogues that hand something about a whole row to a later launch, and what
 template <typename E> struct EpiRow { static constexpr bool sum = false, max = false; };
-template <typename WT> struct EpiRow<EpiResidualNorm<WT>> { static constexpr bool sum = true, max = true; };
+template <typename WT, bool SPLIT> struct EpiRow<EpiResidualNorm<WT, SPLIT>> { static constexpr bool sum = true, max = !SPLIT; };
+// epilogues whose rows the next projection reads, and thereby the kernels they run in: those on the copy of
+// the weights (OutParts 0), the one on the caller's (1), or either (-1)
+template <typename E> struct EpiOutParts { static constexpr int value = -1; };
+template <typename WT, bool SPLIT> struct EpiOutParts<EpiResidualNorm<WT, SPLIT>> { static constexpr int value = SPLIT; };
 
 template <typename E> struct EpiHasLocalReduce { static constexpr bool value = false; };
 
 template <typename E> struct EpiReadsOld { static constexpr bool value = false; };
 template <typename WT, bool DS> struct EpiReadsOld<EpiResidual<WT, DS>> { static constexpr bool value = true; };
-template <typename WT> struct EpiReadsOld<EpiResidualNorm<WT>> { static constexpr bool value = true; };
+template <typename WT, bool SPLIT> struct EpiReadsOld<EpiResidualNorm<WT, SPLIT>> { static constexpr bool value = true; };
 template <typename WT, bool DS> struct EpiReadsOld<EpiQKV<WT, DS>> { static constexpr bool value = true; };
 
 // act[r][i] = silu(Wg_i . n) * (Wu_i . n)
@@ -357,8 +363,9 @@ template <typename WT, bool DS = false> struct EpiSwiGLU {
   __device__ void end(int, const RowDesc &, State &) const {}
 };
 
-// the same for the MFMA path, which also wants the largest magnitude of a row's activations
-template <typename WT> struct EpiSwiGLUMax {
+// the same for the MFMA path, which also wants the largest magnitude of a row's activations, or (SPLIT)
+// three bf16 parts of them
+template <typename WT, bool SPLIT = false> struct EpiSwiGLUMax {
   struct State { uint32_t amax; };
   const WT *wg, *wu;
   int d, F;
@@ -376,7 +383,10 @@ template <typename WT> struct EpiSwiGLUMax {
     y0 *= inv; y1 *= inv;
     return y0 / (1.0f + expf(-y0)) * y1;
   }
-  __device__ void store_value(int task, int r, float v) const { *act.at(r, task) = v; }
+  __device__ void store_value(int task, int r, float v) const {
+    if constexpr (SPLIT) act.put_parts(r, task, v);
+    else *act.at(r, task) = v;
+  }
   typedef float Old;   // the row's scale
   __device__ float load_old(int, int r, const RowDesc &) const { return row_scale(r); }
   __device__ void finish_old(int task, int r, const RowDesc &, float y0, float y1, float inv, State &s) const {
@@ -390,8 +400,9 @@ template <typename WT> struct EpiSwiGLUMax {
   __device__ void put_row(int r, int block, const State &s) const { row_max.put(r, block, s.amax); }
   __device__ void end(int, const RowDesc &, State &) const {}
 };
-template <typename WT> struct EpiReadsOld<EpiSwiGLUMax<WT>> { static constexpr bool value = true; };
-template <typename WT> struct EpiRow<EpiSwiGLUMax<WT>> { static constexpr bool sum = false, max = true; };
+template <typename WT, bool SPLIT> struct EpiReadsOld<EpiSwiGLUMax<WT, SPLIT>> { static constexpr bool value = true; };
+template <typename WT, bool SPLIT> struct EpiRow<EpiSwiGLUMax<WT, SPLIT>> { static constexpr bool sum = false, max = !SPLIT; };
+template <typename WT, bool SPLIT> struct EpiOutParts<EpiSwiGLUMax<WT, SPLIT>> { static constexpr int value = SPLIT; };
 
 // u[r][i] = h[i] + (A h)[i] + b[i]   (translator of the layer-specific head)
 template <typename WT> struct EpiLensAffine {

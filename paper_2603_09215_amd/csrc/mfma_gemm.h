@@ -4,18 +4,17 @@
 //
 // Weights are bf16, activations fp32, and the MFMA takes 16-bit operands: an activation goes through
 // it in parts that add up to the fp32 value, which keeps the result at fp32 accuracy instead of
-// rounding the activations to 8 bits of mantissa.  Activations lie in memory as fp32; the kernels
-// cut them into parts while they stage them in LDS.  Two kernels run the contraction:
+// rounding the activations to 8 bits of mantissa.  Three kernels run the contraction:
 //
-//   mfma_tiled_k (further down), the one a context with the memory for it runs, takes its weights
-//   from a copy in fp16 and in MFMA operand order, written when the context was created.  A bf16
+//   mfma_tiled_k and, for at most 32 rows, mfma_direct_k (further down), which a context with the
+//   memory for it runs, take their weights from a copy in fp16 and in MFMA operand order, written when the context was created.  A bf16
 //   weight scaled by a power of two per row is an fp16 number (exact down to 2^-31 of the row's
 //   largest weight), so the activations are fp16 parts too, and fp16
 //   has 11 bits of mantissa: two parts hold 23 of the 24 bits that three of bf16 hold.  A third of the
 //   MFMA work, and at the clock the chip holds under MFMA load a third of the time of a prompt's
 //   projections, is not done.
 //   mfma_rows_k, described next, takes the caller's row-major bf16 weights, for contexts without
-//   that copy: three bf16 parts (3 x 8 bits).
+//   that copy: three bf16 parts (3 x 8 bits), which the producers of the rows write.
 //
 // (Two bf16 parts leave 2^-17 relative error per element; re-rounded to bf16 in the KV cache that
 // is enough to double the deviation from the oracle.)
@@ -81,7 +80,7 @@ prep_rows_k(const RowDesc *__restrict__ rows, const float *__restrict__ src, int
   const float *row = src + (size_t)(indirect ? rows[r].x_slot : r) * stride;
   uint32_t amax = 0u;
   auto put = [&](int k, float4 f) {
-    *(float4 *)x.at(r, k) = f;
+    x.put(r, k, f);
     amax = max(amax, max(max(magnitude_bits(f.x), magnitude_bits(f.y)), max(magnitude_bits(f.z), magnitude_bits(f.w))));
   };
   auto finish = [&]() {
@@ -89,7 +88,7 @@ prep_rows_k(const RowDesc *__restrict__ rows, const float *__restrict__ src, int
     for (int o = 32; o > 0; o >>= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, o, 64));
     if ((threadIdx.x & 63) == 0) big[threadIdx.x >> 6] = amax;
     __syncthreads();
-    if (threadIdx.x == 0) row_max.put(r, 0, max(max(big[0], big[1]), max(big[2], big[3])));
+    if (threadIdx.x == 0 && row_max.list) row_max.put(r, 0, max(max(big[0], big[1]), max(big[2], big[3])));
   };
   if (n <= 4096) {
     // the row and the gains in registers: every load is issued before the first is used (one
@@ -150,7 +149,7 @@ prep_rows_k(const RowDesc *__restrict__ rows, const float *__restrict__ src, int
 // the lists of their magnitudes; and words that are to be zero for the launches after this one.
 struct ProjIn {
   const float *x;
-  int stride;
+  int stride, part_units;   // (as in RowOut; parts for the kernel on the caller's weights)
   RowMax row_max;
   uint4 *zero;
   int n_zero;   // 16-byte units
@@ -296,51 +295,36 @@ mfma_rows_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, ProjIn in, in
     for (int r = 0; r < 16; ++r) acc0[c][r] = acc1[c][r] = 0.f;
 
   u32x4_t wr[WD][WI];   // (a native vector type: arrays of it are kept in registers)
-  // this thread's vectors of eight activations of a chunk; they become three bf16 parts when they are
-  // written to LDS (zeros beyond the row's end)
-  const float *x_src[XV];
-  int x_dst[XV], x_k[XV];
+  // this thread's vectors of the three parts of a chunk's activations (beyond the row's end: zeros)
+  const bf16_t *parts = (const bf16_t *)in.x;
+  const size_t part_stride = (size_t)in.part_units * 64;
+  const int x_pitch = n_chunks * MG_KC;
+  int x_src[XV], x_dst[XV];
 #pragma unroll
   for (int i = 0; i < XV; ++i) {
     const int pos = ((int)threadIdx.x + i * (64 * WAVES)) % XPOS;
-    const int m = pos / (MG_KC / 8);
-    x_k[i] = (pos - m * (MG_KC / 8)) * 8;
-    x_src[i] = in.x + (size_t)min(row0 + m, m_rows - 1) * in.stride;    // rows past the end repeat the last one
-    x_dst[i] = m * MG_ROWPAD + x_k[i];
+    const int m = pos / (MG_KC / 8), x_k = (pos - m * (MG_KC / 8)) * 8;
+    x_src[i] = min(row0 + m, m_rows - 1) * x_pitch + x_k;    // rows past the end repeat the last one
+    x_dst[i] = m * MG_ROWPAD + x_k;
   }
-  float4 xr[XV][2];
+  u32x4_t xr[XV][MG_PARTS];
   auto load_x = [&](int chunk) {
+    const int k = min(chunk, c_end - 1) * MG_KC;
 #pragma unroll
-    for (int i = 0; i < XV; ++i) {
-      const int k = min(chunk, c_end - 1) * MG_KC + x_k[i];
-      const float *src = x_src[i] + (k < n_in ? k : 0);
-      xr[i][0] = *(const float4 *)src;
-      xr[i][1] = *(const float4 *)(src + 4);
-    }
+    for (int i = 0; i < XV; ++i)
+#pragma unroll
+      for (int p = 0; p < MG_PARTS; ++p) xr[i][p] = *(const u32x4_t *)(parts + p * part_stride + k + x_src[i]);
   };
-  auto store_x = [&](int chunk, int buf) {
+  auto store_x = [&](int buf) {
 #pragma unroll
-    for (int i = 0; i < XV; ++i) {
-      const bool real = min(chunk, c_end - 1) * MG_KC + x_k[i] < n_in;
-      const float f[8] = {xr[i][0].x, xr[i][0].y, xr[i][0].z, xr[i][0].w, xr[i][1].x, xr[i][1].y, xr[i][1].z, xr[i][1].w};
-      u32x4_t part[MG_PARTS];
+    for (int i = 0; i < XV; ++i)
 #pragma unroll
-      for (int e = 0; e < 8; e += 2) {
-        bf16_t h0, m0, l0, h1, m1, l1;
-        split3_bf16(real ? f[e] : 0.f, h0, m0, l0);
-        split3_bf16(real ? f[e + 1] : 0.f, h1, m1, l1);
-        part[0][e >> 1] = h0 | ((uint32_t)h1 << 16);
-        part[1][e >> 1] = m0 | ((uint32_t)m1 << 16);
-        part[2][e >> 1] = l0 | ((uint32_t)l1 << 16);
-      }
-#pragma unroll
-      for (int p = 0; p < MG_PARTS; ++p) *(u32x4_t *)(s_x + (buf * MG_PARTS + p) * PART_ELEMS + x_dst[i]) = part[p];
-    }
+      for (int p = 0; p < MG_PARTS; ++p) *(u32x4_t *)(s_x + (buf * MG_PARTS + p) * PART_ELEMS + x_dst[i]) = xr[i][p];
   };
 
   load_x(c_begin);
   __builtin_amdgcn_sched_barrier(0);
-  store_x(c_begin, 0);
+  store_x(0);
   __builtin_amdgcn_sched_barrier(0);
   load_x(c_begin + 1);
   __builtin_amdgcn_sched_barrier(0);
@@ -364,7 +348,7 @@ mfma_rows_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, ProjIn in, in
       for (int i = 0; i < WI; ++i) *(u32x4_t *)(s_w + 8 * i * MG_ROWPAD + w_dst) = wr[j][i];
       __builtin_amdgcn_sched_barrier(0);
       // activations of chunk + 1, requested one iteration ago, into the other buffer
-      store_x(chunk + 1, buf ^ 1);
+      store_x(buf ^ 1);
       __builtin_amdgcn_sched_barrier(0);
       load_x(chunk + 2);
       __builtin_amdgcn_sched_barrier(0);
@@ -734,7 +718,7 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__
 #pragma unroll
   for (int u = 0; u < TB; ++u) {
     const int r = (int)threadIdx.x + NT * u;
-    wd[u] = wdown[min(bx * (2 * TG_WAVES * TB) + r / 32, n_blocks - 1) * 32 + r % 32];
+    wd[u] = wdown[(size_t)min(bx * (2 * TG_WAVES * TB) + r / 32, n_blocks - 1) * 32 + r % 32];
   }
 #pragma unroll
   for (int n = 0; n < XV; ++n) { load_x1(n, 0, c_begin); load_x1(n, 1, c_begin); }
@@ -1052,10 +1036,16 @@ mfma_finish_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, int n_tasks
   if ((int)threadIdx.x < m_rows && s_best[threadIdx.x]) epi.end_reduced(rows[threadIdx.x], s_best[threadIdx.x]);
 }
 
-// What an epilogue needs besides the sums, requested before they are ready
-template <typename Epi> __device__ __forceinline__ auto load_old(const Epi &epi, int task, int m, const RowDesc &rd) {
-  if constexpr (EpiReadsOld<Epi>::value) return epi.load_old(task, m, rd);
-  else return 0;
+// What an epilogue needs besides the sums, requested before they are ready, if `wanted` (a finishing launch
+// for eight rows has four times as many threads as pairs: q/k/v 6.2 us with the others' requests, 5.3 without)
+template <typename Epi> __device__ __forceinline__ auto load_old(const Epi &epi, int task, int m, const RowDesc &rd, bool wanted) {
+  if constexpr (EpiReadsOld<Epi>::value) {
+    typename Epi::Old o{};
+    if (wanted) o = epi.load_old(task, m, rd);
+    return o;
+  } else {
+    return 0;
+  }
 }
 // What an epilogue gathers about a row, combined over the LANES neighbouring lanes that have finished
 // tasks of it (shuffles: a fixed order) and handed on by the first of them as part `i`
@@ -1100,7 +1090,7 @@ mfma_finish_tile_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, int n_
   const int tl = threadIdx.x & 31, ml = threadIdx.x >> 5, task = task0 + tl, m = row0 + ml;
   const bool live = task < n_tasks && m < m_rows;
   const RowDesc rd = rows[m < m_rows ? m : 0];
-  const auto old = load_old(epi, live ? task : 0, m < m_rows ? m : 0, rd);
+  const auto old = load_old(epi, task, m, rd, live);
   {
     const int ml_ = blockIdx.y * 32 + (threadIdx.x & 31);                     // row and task inside the tile
     const int tl_ = min(tb * 32 + (int)(threadIdx.x >> 5), ps.tasks_per_tile - 1);
@@ -1178,17 +1168,17 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
     xr[u][1] = *(const float4 *)(p + 4 * OP_ROWS);
   };
   RowExponent<16> mag(in.row_max, min((int)threadIdx.x >> 4, m_rows - 1), threadIdx.x & 15);
-  static_assert(NT * 32 <= 64 * TD_WAVES, "a thread fetches one weight row's scale at most");
-  const int wd_row = min((int)threadIdx.x, NT * 32 - 1);
-  const float wd = wdown[min(group * NT + wd_row / 32, n_blocks - 1) * 32 + wd_row % 32];
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int u = 0; u < RING; ++u) { load_w(u, s_begin + u); load_x(u, s_begin + u); }
   __builtin_amdgcn_sched_barrier(0);
+  static_assert(NT * 32 <= 64 * TD_WAVES, "a thread fetches one weight row's scale at most");
+  const int wd_row = min((int)threadIdx.x, NT * 32 - 1);   // (needed last, and from far away)
+  const float wd = wdown[(size_t)min(group * NT + wd_row / 32, n_blocks - 1) * 32 + wd_row % 32];
+  __builtin_amdgcn_sched_barrier(0);
   {
     const int e = mag.get();
     if ((threadIdx.x & 15) == 0) s_exp[threadIdx.x >> 4] = scale_exponent(e);
-    if (threadIdx.x < NT * 32) s_wdown[threadIdx.x] = wd;
   }
   __syncthreads();
   const int E = s_exp[lane & 31];
@@ -1224,6 +1214,7 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
     }
   }
 
+  if (threadIdx.x < NT * 32) s_wdown[threadIdx.x] = wd;
   // the waves' sums: the upper four hand theirs to the lower four, those leave four to be added up
   // by the thread that finishes a pair (always in the same order)
   auto at = [&](int w, int q, int r) { return ((w * NT + q) * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * 33 + (lane & 31); };
@@ -1276,7 +1267,7 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
     for (int q = 0; q < NT; ++q) {
       const int task = (group * NT + q) * TG_TASKS + t;
       const bool live = row_live && task < n_tasks;
-      const auto old = load_old(epi, live ? task : 0, row_live ? m : m_rows - 1, rd);
+      const auto old = load_old(epi, live ? task : 0, row_live ? m : m_rows - 1, rd, true);
       if (live) finish_pair(epi, task, m, rd, sum(q, t, m), sum(q, TG_TASKS + t, m), old, st);
     }
     if constexpr (EpiHasLocalReduce<Epi>::value) {

@@ -39,10 +39,10 @@ constexpr int MAX_SEQ_LEN = 16384;
 
 struct Layout {  // byte offsets into the scratch buffer
   size_t state, page_table, plan, lower, upper, ee, full, prefill_rows, prefill_tokens, seq_ids,
-      forced, step_flags, out_tokens, out_depth, best, arrivals, row_ssq, max_x, max_attn, max_act, sample_hist, sample_arrive, sample_count, hidden, xnorm, mfma_part, sample_q, sample_cand, rand_words, qbuf, attn_out, part, act, lens_u,
+      forced, step_flags, out_tokens, out_depth, best, arrivals, row_ssq, max_x, max_attn, max_act, sample_hist, sample_arrive, sample_count, hidden, xnorm, part_elems, act_part_elems, mfma_part, sample_q, sample_cand, rand_words, qbuf, attn_out, part, act, lens_u,
       logits, rope, inv_freq, total,
       tiled, wdown, total_tiled,   // the MFMA-ordered copy of the projection weights and its scales lie behind everything else (absent on the static area)
-      prompt_hidden, prompt_q, prompt_attn, prompt_act, prompt_xnorm, prompt_ssq, prompt_max_x, prompt_max_attn, prompt_max_act,
+      prompt_rows, prompt_tokens, prompt_hidden, prompt_q, prompt_attn, prompt_act, prompt_xnorm, prompt_ssq, prompt_max_x, prompt_max_attn, prompt_max_act,
       total_prompt;        // and behind them the buffers of the largest prompt passes
 };
 
@@ -65,6 +65,8 @@ struct PassBuffers {
   float *hidden, *q, *attn, *act, *xnorm;
   unsigned long long *ssq;           // two sets of SSQ_WAYS words per row
   uint8_t *max_x, *max_attn, *max_act;
+  RowDesc *descs;                    // of a prompt pass
+  int *tokens;
   int rows;                          // rows that fit
 };
 
@@ -271,8 +273,8 @@ void layout(const spark_config &c, const Derived &d, Layout &l) {
   l.upper = take(sizeof(RowDesc) * (size_t)c.max_batch * d.rmax);
   l.ee = take(sizeof(RowDesc) * c.max_batch);
   l.full = take(sizeof(RowDesc) * c.max_batch);
-  l.prefill_rows = take(sizeof(RowDesc) * PROMPT_ROWS);
-  l.prefill_tokens = take(sizeof(int) * PROMPT_ROWS);
+  l.prefill_rows = take(sizeof(RowDesc) * PREFILL_CHUNK);
+  l.prefill_tokens = take(sizeof(int) * PREFILL_CHUNK);
   l.seq_ids = take(sizeof(int) * c.max_batch);
   l.forced = take(sizeof(int) * (size_t)MAX_STEPS_PER_CALL * c.max_batch);
   l.step_flags = take(sizeof(int) * c.max_batch);
@@ -282,9 +284,9 @@ void layout(const spark_config &c, const Derived &d, Layout &l) {
   l.arrivals = take(sizeof(int) * (size_t)d.max_rows * c.n_q_heads);   // per (row, group of query heads)
   // what the launches of a pass hand each other about a row: sums of squares, lists of largest magnitudes
   l.row_ssq = take(sizeof(unsigned long long) * 2 * SSQ_WAYS * (size_t)d.max_rows);
-  l.max_x = take((size_t)max_x_bytes(c) * d.max_rows);
-  l.max_attn = take((size_t)max_attn_bytes(c) * d.max_rows);
-  l.max_act = take((size_t)max_act_bytes(c) * d.max_rows);
+  l.max_x = take(shape_allows_mfma(c) ? (size_t)max_x_bytes(c) * d.max_rows : 0);
+  l.max_attn = take(shape_allows_mfma(c) ? (size_t)max_attn_bytes(c) * d.max_rows : 0);
+  l.max_act = take(shape_allows_mfma(c) ? (size_t)max_act_bytes(c) * d.max_rows : 0);
   l.sample_hist = take(sizeof(unsigned long long) * (size_t)SAMPLE_BINS * c.max_batch);   // zero between launches
   l.sample_arrive = take(sizeof(unsigned) * c.max_batch);
   l.sample_count = take(sizeof(unsigned) * c.max_batch);
@@ -292,9 +294,15 @@ void layout(const spark_config &c, const Derived &d, Layout &l) {
   l.qbuf = take(sizeof(float) * d.max_rows * qw);
   l.attn_out = take(sizeof(float) * d.max_rows * qw);
   l.part = take(sizeof(float) * (size_t)d.max_rows * c.n_q_heads * d.n_splits * (c.head_dim + 4));
-  l.act = take(sizeof(float) * (size_t)d.max_rows * c.d_ffn);
   l.lens_u = take(sizeof(float) * (size_t)c.max_batch * c.d_model);
-  l.xnorm = take(c.dtype == SPARK_DTYPE_BF16 ? sizeof(float) * (size_t)d.max_rows * c.d_model : 256);   // normalised rows, for the MFMA projections
+  // rows that the MFMA projections read, as three bf16 parts: normalised rows and attention output in the
+  // one buffer, MLP activations in the other.  A pass on the copy of the weights has normalised rows in
+  // fp32 in the one, and it and the vector kernels MLP activations in the other.
+  const bool bf16 = c.dtype == SPARK_DTYPE_BF16;
+  l.part_elems = bf16 ? (size_t)d.max_rows * align_up(std::max((size_t)c.d_model, qw), 64) : 0;
+  l.act_part_elems = bf16 ? (size_t)d.max_rows * align_up(c.d_ffn, 64) : 0;
+  l.xnorm = take(sizeof(bf16_t) * 3 * l.part_elems);
+  l.act = take(bf16 ? sizeof(bf16_t) * 3 * l.act_part_elems : sizeof(float) * (size_t)d.max_rows * c.d_ffn);
   l.mfma_part = take(c.dtype == SPARK_DTYPE_BF16 ? MFMA_PARTIAL_BYTES : 256);
   l.logits = take(sizeof(float) * (size_t)c.max_batch * d.V);
   l.sample_q = take(sizeof(unsigned) * (size_t)c.max_batch * d.V);   // integer masses of the sampler
@@ -312,6 +320,8 @@ void layout(const spark_config &c, const Derived &d, Layout &l) {
   l.total_tiled = l.wdown + align_up(sizeof(float) * 32 * tm.blocks, 256);
   o = l.total_tiled;
   const size_t n = shape_allows_mfma(c) ? PROMPT_ROWS : 0;
+  l.prompt_rows = take(sizeof(RowDesc) * n);
+  l.prompt_tokens = take(sizeof(int) * n);
   l.prompt_hidden = take(sizeof(float) * n * c.d_model);
   l.prompt_q = take(sizeof(float) * n * qw);
   l.prompt_attn = take(sizeof(float) * n * qw);
@@ -495,6 +505,10 @@ int launch_attention_rows(spark_ctx *c, const RowDesc *rows, int m, int m_pass, 
   return SPARK_OK;
 }
 
+RowOut from_row(const RowOut &o, int r0) {
+  return RowOut{o.part_units ? (float *)((bf16_t *)o.p + (size_t)r0 * o.pitch()) : o.p + (size_t)r0 * o.stride, o.stride, o.part_units};
+}
+
 template <typename WT> int launch_attention(spark_ctx *c, const RowDesc *rows, int m, int layer, const RowOut &out, RowMax &row_max) {
   int rc = prof_begin(c, SPARK_KC_ATTN);
   if (rc) return rc;
@@ -521,7 +535,7 @@ template <typename WT> int launch_attention(spark_ctx *c, const RowDesc *rows, i
     RowMax rm = row_max;
     if (rm.list) rm.list += (size_t)r0 * rm.stride;
     if ((rc = launch_attention_rows<WT>(c, rows + r0, std::min(c->base.rows, m - r0), m, layer, c->pb.q + r0 * qw,
-                                        RowOut{out.p + (size_t)r0 * out.stride, out.stride}, rm))) return rc;
+                                        from_row(out, r0), rm))) return rc;
     row_max.n = rm.n;
   }
   return prof_end(c, SPARK_KC_ATTN);
@@ -530,22 +544,28 @@ template <typename WT> int launch_attention(spark_ctx *c, const RowDesc *rows, i
 // ------------------------------------------------------------------ MFMA path (16..128+ rows, bf16)
 
 
-// Which kernel takes a pass's projections, and with it how the rows that they read lie in memory: a
-// pass of at most 32 rows on tiled weights streams them (mfma_direct_k) and wants operand order.
-bool in_operand_order(spark_ctx *c, int m) { return c->has_tiled && c->use_tiled && m <= std::min(OP_ROWS, c->direct_max_rows); }
-RowOut rows_out(spark_ctx *c, float *p, int m, int width) { return RowOut{p, in_operand_order(c, m) ? 0 : width}; }
+// Which kernel takes a pass's projections, and with it how the rows that they read lie in memory: on the
+// copy of the weights fp32 rows, where a pass of at most 32 of them streams it (mfma_direct_k) and wants
+// operand order; on the caller's weights bf16 parts, part_elems apart.
+bool on_copy(spark_ctx *c) { return c->has_tiled && c->use_tiled; }
+bool in_operand_order(spark_ctx *c, int m) { return on_copy(c) && m <= std::min(OP_ROWS, c->direct_max_rows); }
+RowOut rows_out(spark_ctx *c, float *p, size_t part_elems, int m, int width) {
+  if (!on_copy(c)) return RowOut{p, width, (int)(part_elems / 64)};
+  return RowOut{p, in_operand_order(c, m) ? 0 : width, 0};
+}
+RowMax row_max_list(spark_ctx *c, uint8_t *list, int bytes, int n) { return on_copy(c) ? RowMax{list, bytes, n} : RowMax{nullptr, 0, 0}; }
+ProjIn proj_in(const RowOut &x, const RowMax &row_max) { return ProjIn{x.p, x.stride, x.part_units, row_max, nullptr, 0}; }
 
 int launch_prep(spark_ctx *c, const RowDesc *rows, int m, const float *src, int stride, int indirect,
                 const float *gamma, int n) {
-  prep_rows_k<<<m, 256, 0, c->stream>>>(rows, src, stride, indirect, gamma, c->cfg.rms_eps, n, rows_out(c, c->pb.xnorm, m, n),
-                                        RowMax{c->pb.max_x, max_x_bytes(c->cfg), 1});
+  prep_rows_k<<<m, 256, 0, c->stream>>>(rows, src, stride, indirect, gamma, c->cfg.rms_eps, n,
+                                        rows_out(c, c->pb.xnorm, c->lo.part_elems, m, n), row_max_list(c, c->pb.max_x, max_x_bytes(c->cfg), 1));
   HIP_TRY(c, hipGetLastError());
   return SPARK_OK;
 }
 // normalised rows as a projection's input, their magnitudes in `n_max` parts
 ProjIn prepared(spark_ctx *c, int m, int n_max) {
-  const RowOut x = rows_out(c, c->pb.xnorm, m, c->cfg.d_model);
-  return ProjIn{x.p, x.stride, RowMax{c->pb.max_x, max_x_bytes(c->cfg), n_max}, nullptr, 0};
+  return proj_in(rows_out(c, c->pb.xnorm, c->lo.part_elems, m, c->cfg.d_model), row_max_list(c, c->pb.max_x, max_x_bytes(c->cfg), n_max));
 }
 
 // tasks one thread of the finishing kernel takes: the vocabulary heads reduce their arg-max over 8
@@ -762,6 +782,12 @@ int launch_mfma_tiles(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, 
   return launch_mfma_shape<MTILES, Epi, 8>(c, epi, rows, m, n_in, n_tasks, in);
 }
 
+template <typename Epi>
+int launch_wide(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in, const TiledMatrix &w, int *max_words) {
+  if constexpr (std::is_same<Epi, EpiSwiGLUMax<bf16_t>>::value) return launch_tiled_rows<2>(c, epi, rows, m, n_in, n_tasks, in, w, max_words);
+  else return SPARK_EINVAL;
+}
+
 // y = W x for m rows of `in`; w: the copy of the weights in MFMA operand order, or nullptr; max_words:
 // how many words of each row's list of magnitudes the launch writes, for an epilogue that does
 template <typename Epi>
@@ -769,23 +795,21 @@ int launch_mfma(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_
                 int kclass, const TiledMatrix *w, int *max_words = nullptr) {
   int rc = prof_begin(c, kclass);
   if (rc) return rc;
-  if (w && in_operand_order(c, m)) {
-    rc = launch_direct(c, epi, rows, m, n_in, n_tasks, in, *w, max_words);
-  } else if (w) {
+  if constexpr (EpiOutParts<Epi>::value != 1) {
     // 64 tasks per wave for gate/up, 32 for matrices of few rows (q/k/v, o, down, the lens translator), so
     // that the launch has enough workgroups without cutting k into ranges too short to stream, and for the
-    // heads, whose tiles are never cut.  (64 for q/k/v, o and down of large prompt passes too: prompts of
-    // 512, 1024, 2300 and 8192 tokens 0 to 2 % faster on one backbone, 6 % slower to 7 % faster on the other.)
-    if constexpr (std::is_same<Epi, EpiSwiGLUMax<bf16_t>>::value) {
-      if (n_tasks >= TILED_WIDE_TASKS) rc = launch_tiled_rows<2>(c, epi, rows, m, n_in, n_tasks, in, *w, max_words);
-      else rc = launch_tiled_rows<1>(c, epi, rows, m, n_in, n_tasks, in, *w, max_words);
-    } else {
-      rc = launch_tiled_rows<1>(c, epi, rows, m, n_in, n_tasks, in, *w, max_words);
-    }
-  } else {
+    // heads, whose tiles are never cut.  (64 for q/k/v, o and down of passes of 700 to 1024 rows, without
+    // folded sums: the layers of one backbone 3 to 4 % shorter, of the other 1 to 6 % longer.)
+    if (w && in_operand_order(c, m)) rc = launch_direct(c, epi, rows, m, n_in, n_tasks, in, *w, max_words);
+    else if (w && std::is_same<Epi, EpiSwiGLUMax<bf16_t>>::value && n_tasks >= TILED_WIDE_TASKS) rc = launch_wide(c, epi, rows, m, n_in, n_tasks, in, *w, max_words);
+    else if (w) rc = launch_tiled_rows<1>(c, epi, rows, m, n_in, n_tasks, in, *w, max_words);
+  }
+  if constexpr (EpiOutParts<Epi>::value != 0) {
     // (mfma_rows_k keeps a running state for one tile of 32 rows at most)
-    if (m <= 32 || EpiHasLocalReduce<Epi>::value) rc = launch_mfma_tiles<1>(c, epi, rows, m, n_in, n_tasks, in);
-    else rc = launch_mfma_tiles<2>(c, epi, rows, m, n_in, n_tasks, in);   // tiles of 64 rows
+    if (!w) {
+      if (m <= 32 || EpiHasLocalReduce<Epi>::value) rc = launch_mfma_tiles<1>(c, epi, rows, m, n_in, n_tasks, in);
+      else rc = launch_mfma_tiles<2>(c, epi, rows, m, n_in, n_tasks, in);   // tiles of 64 rows
+    }
   }
   if (rc) return rc;
   return prof_end(c, kclass);
@@ -794,7 +818,7 @@ int launch_mfma(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_
 
 // The copy of one projection's weights in MFMA operand order, or nullptr when the context has none
 // (or is told not to use it).
-const TiledMatrix *tiled_at(spark_ctx *c, const TiledMatrix &w) { return c->has_tiled && c->use_tiled ? &w : nullptr; }
+const TiledMatrix *tiled_at(spark_ctx *c, const TiledMatrix &w) { return on_copy(c) ? &w : nullptr; }
 
 template <typename Epi>
 int tile_one(spark_ctx *c, const Epi &epi, int n_tasks, int n_in, const TiledMatrix &w) {
@@ -825,7 +849,7 @@ int build_tiled(spark_ctx *c) {
     EpiResidual<WT> eo{(const WT *)c->w.wo + (size_t)l * d * qw, (int)qw, d, nullptr, d};
     if ((rc = tile_one(c, eo, d / 2, (int)qw, c->tm.o[l]))) return rc;
     EpiSwiGLUMax<WT> eg{(const WT *)c->w.wg + (size_t)l * F * d, (const WT *)c->w.wu + (size_t)l * F * d, d, F,
-                        RowOut{nullptr, 0}, RowMax{nullptr, 0, 0}};
+                        RowOut{nullptr, 0, 0}, RowMax{nullptr, 0, 0}};
     if ((rc = tile_one(c, eg, F, d, c->tm.gateup[l]))) return rc;
     EpiResidual<WT> ed{(const WT *)c->w.wd + (size_t)l * d * F, F, d, nullptr, d};
     if ((rc = tile_one(c, ed, d / 2, F, c->tm.down[l]))) return rc;
@@ -840,15 +864,18 @@ int build_tiled(spark_ctx *c) {
   return SPARK_OK;
 }
 
-// layers [l0, l1) on m rows, bf16 weights
+// layers [l0, l1) on m rows, bf16 weights.  SPLIT: on the caller's weights, the rows handed on as bf16 parts
+template <bool SPLIT>
 int run_layers_mfma(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
   typedef bf16_t WT;
   const spark_config &g = c->cfg;
   const int d = g.d_model, hd = g.head_dim, nq = g.n_q_heads, nkv = g.n_kv_heads, F = g.d_ffn;
   const size_t qw = (size_t)nq * hd, kvw = (size_t)nkv * hd;
   float *hidden = c->pb.hidden;
-  const RowOut xnorm = rows_out(c, c->pb.xnorm, m, d), attn_out = rows_out(c, c->pb.attn, m, (int)qw),
-               act = rows_out(c, c->pb.act, m, F);
+  // (as parts, the attention output takes the place of the rows that q/k/v have read)
+  const RowOut xnorm = rows_out(c, c->pb.xnorm, c->lo.part_elems, m, d),
+               attn_out = rows_out(c, on_copy(c) ? c->pb.attn : c->pb.xnorm, c->lo.part_elems, m, (int)qw),
+               act = rows_out(c, c->pb.act, c->lo.act_part_elems, m, F);
   // RMSNorm is linear in 1/rms: the finishing launch of a residual projection writes gamma (.) h
   // for the projection that follows and adds up h's sum of squares per row; that projection's
   // epilogue scales by 1/rms.  Only the first norm of a run is a launch of its own.
@@ -857,9 +884,9 @@ int run_layers_mfma(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
   // q/k/v, added to next by down).
   unsigned long long *ssq_in = c->pb.ssq, *ssq_mlp = ssq_in + (size_t)SSQ_WAYS * c->pb.rows;
   const int ssq_units = m * SSQ_WAYS * (int)sizeof(unsigned long long) / 16;
-  RowMax max_x{c->pb.max_x, max_x_bytes(g), 1};   // (the count: what the launch that wrote the lists last has written)
-  RowMax max_attn{c->pb.max_attn, max_attn_bytes(g), 0};
-  RowMax max_act{c->pb.max_act, max_act_bytes(g), 0};
+  // (the counts: what the launch that wrote the lists last has written)
+  RowMax max_x = row_max_list(c, c->pb.max_x, max_x_bytes(g), 1), max_attn = row_max_list(c, c->pb.max_attn, max_attn_bytes(g), 0),
+         max_act = row_max_list(c, c->pb.max_act, max_act_bytes(g), 0);
   const bool fuse = c->fuse_norm;
   int rc;
   for (int l = l0; l < l1; ++l) {
@@ -881,11 +908,11 @@ int run_layers_mfma(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
 
     if ((rc = launch_attention<WT>(c, rows, m, l, attn_out, max_attn))) return rc;
 
-    const ProjIn in_o{attn_out.p, attn_out.stride, max_attn, nullptr, 0};
-    EpiSwiGLUMax<WT> eg{(const WT *)c->w.wg + (size_t)l * F * d, (const WT *)c->w.wu + (size_t)l * F * d,
+    const ProjIn in_o = proj_in(attn_out, max_attn);
+    EpiSwiGLUMax<WT, SPLIT> eg{(const WT *)c->w.wg + (size_t)l * F * d, (const WT *)c->w.wu + (size_t)l * F * d,
                         d, F, act, max_act};
     if (fuse) {
-      EpiResidualNorm<WT> eo{(const WT *)c->w.wo + (size_t)l * d * qw, (int)qw, d, hidden, d,
+      EpiResidualNorm<WT, SPLIT> eo{(const WT *)c->w.wo + (size_t)l * d * qw, (int)qw, d, hidden, d,
                              c->w.mlp_norm + (size_t)l * d, xnorm, ssq_mlp, max_x};
       if ((rc = launch_mfma(c, eo, rows, m, (int)qw, d / 2, in_o, SPARK_KC_OPROJ, tiled_at(c, c->tm.o[l]), &max_x.n))) return rc;
       eg.scale = RowScale{ssq_mlp, 1.0f / (float)d, g.rms_eps};
@@ -901,9 +928,9 @@ int run_layers_mfma(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
     max_act.n = 0;
     if ((rc = launch_mfma(c, eg, rows, m, d, F, in, SPARK_KC_GATEUP, tiled_at(c, c->tm.gateup[l]), &max_act.n))) return rc;
 
-    const ProjIn in_d{act.p, act.stride, max_act, nullptr, 0};
+    const ProjIn in_d = proj_in(act, max_act);
     if (fuse && l + 1 < l1) {
-      EpiResidualNorm<WT> ed{(const WT *)c->w.wd + (size_t)l * d * F, F, d, hidden, d,
+      EpiResidualNorm<WT, SPLIT> ed{(const WT *)c->w.wd + (size_t)l * d * F, F, d, hidden, d,
                              c->w.attn_norm + (size_t)(l + 1) * d, xnorm, ssq_in, max_x};
       if ((rc = launch_mfma(c, ed, rows, m, F, d / 2, in_d, SPARK_KC_DOWN, tiled_at(c, c->tm.down[l]), &max_x.n))) return rc;
     } else {
@@ -924,7 +951,8 @@ int run_layers(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
     // (more rows go through the layers in pieces, in order, so that a piece finds the K and V of the rows before it)
     const int most = pass_rows_limit(g.d_model);
     for (int r0 = 0; r0 < m; r0 += most) {
-      const int rc = run_layers_mfma(c, l0, l1, rows + r0, std::min(most, m - r0));
+      const int rc = on_copy(c) ? run_layers_mfma<false>(c, l0, l1, rows + r0, std::min(most, m - r0))
+                                : run_layers_mfma<true>(c, l0, l1, rows + r0, std::min(most, m - r0));
       if (rc) return rc;
     }
     return SPARK_OK;
@@ -946,7 +974,7 @@ int run_layers(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
     if ((rc = launch_gemv<WT>(c, n1, eq, rows, m, d, (nq + 2 * nkv) * (hd / 2), SPARK_KC_QKV))) return rc;
 
     RowMax no_list{nullptr, 0, 0};
-    if ((rc = launch_attention<WT>(c, rows, m, l, RowOut{c->pb.attn, (int)qw}, no_list))) return rc;
+    if ((rc = launch_attention<WT>(c, rows, m, l, RowOut{c->pb.attn, (int)qw, 0}, no_list))) return rc;
 
     ProPlain pa{c->pb.attn, (int)qw, 0};
     EpiResidual<WT> eo{(const WT *)c->w.wo + (size_t)l * d * qw, (int)qw, d, hidden, d};
@@ -1236,10 +1264,10 @@ template <typename WT> int prefill_rows(spark_ctx *c, int id, const int32_t *pro
   }
   const int base_slot = large ? 0 : g.max_batch * c->dv.rmax;
   std::vector<RowDesc> rows(chunk);
-  RowDesc *rows_dev = at<RowDesc>(c, c->lo.prefill_rows);
-  int *tok_dev = at<int>(c, c->lo.prefill_tokens);
   int rc = SPARK_OK;
   if (large) c->pb = c->prompt;
+  RowDesc *rows_dev = c->pb.descs;
+  int *tok_dev = c->pb.tokens;
   c->prompt_pass = true;
   for (int p0 = 0; p0 < n_rows && rc == SPARK_OK; p0 += chunk) {
     const int m = std::min(chunk, n_rows - p0);
@@ -1338,10 +1366,12 @@ int init_context(const spark_config *cfg, const spark_weights *weights, void *kv
   const Layout &lo = c->lo;
   c->base = PassBuffers{at<float>(c, lo.hidden), at<float>(c, lo.qbuf), at<float>(c, lo.attn_out), at<float>(c, lo.act),
                         at<float>(c, lo.xnorm), at<unsigned long long>(c, lo.row_ssq), at<uint8_t>(c, lo.max_x),
-                        at<uint8_t>(c, lo.max_attn), at<uint8_t>(c, lo.max_act), c->dv.max_rows};
+                        at<uint8_t>(c, lo.max_attn), at<uint8_t>(c, lo.max_act),
+                        at<RowDesc>(c, lo.prefill_rows), at<int>(c, lo.prefill_tokens), c->dv.max_rows};
   c->prompt = PassBuffers{at<float>(c, lo.prompt_hidden), at<float>(c, lo.prompt_q), at<float>(c, lo.prompt_attn),
                           at<float>(c, lo.prompt_act), at<float>(c, lo.prompt_xnorm), at<unsigned long long>(c, lo.prompt_ssq),
                           at<uint8_t>(c, lo.prompt_max_x), at<uint8_t>(c, lo.prompt_max_attn), at<uint8_t>(c, lo.prompt_max_act),
+                          at<RowDesc>(c, lo.prompt_rows), at<int>(c, lo.prompt_tokens),
                           c->has_tiled && scratch_bytes >= lo.total_prompt ? PROMPT_ROWS : 0};
   c->pb = c->base;
   // Prompt rows per pass: on the MFMA path the widest projection (gate/up) is cut into tiles of 256
@@ -1773,7 +1803,7 @@ int spark_measure_read(spark_ctx *c, const void *buf, size_t bytes, int32_t reps
   if (bytes < 16 || bytes % 16 || ((uintptr_t)buf & 15)) return fail(c, SPARK_EINVAL, "buffer must be 16-byte aligned and sized");
   // the wave sums go where the attention partials live between steps (at least 69 KB)
   const int blocks = c->n_cu * 8, words = blocks * (READ_THREADS / 64);
-  const size_t part_bytes = c->lo.act - c->lo.part;
+  const size_t part_bytes = c->lo.lens_u - c->lo.part;
   if (sizeof(unsigned) * words > part_bytes) return fail(c, SPARK_ENOMEM, "scratch too small for the read kernel's sums");
   unsigned *sink = at<unsigned>(c, c->lo.part);
   const read_u32x4 *p = (const read_u32x4 *)buf;
