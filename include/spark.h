@@ -302,7 +302,7 @@ int spark_measure_read(spark_ctx *ctx, const void *buf, size_t bytes, int32_t re
  *   "attn_pieces" (64-token pieces per attention workgroup, from eight on with two teams of waves, at
  *   most 10; 0: pieces and teams by the size of the launch), "attn_mfma_min_rows",
  *   "attn_prompt_min_rows" (rows from which a prompt pass shares K and V
- *   between its rows), "gemv_big_kb", "mfma_tiled" (0: the MFMA projections stage the
+ *   between its rows; 0: by the sizes of pass and context), "gemv_big_kb", "mfma_tiled" (0: the MFMA projections stage the
  *   caller's weight rows through LDS instead of reading the context's copy in operand order),
  *   "mfma_small_tiles" and "mfma_small_max_k" (which of those launches run four waves a workgroup),
  *   "direct_max_rows" (rows up to which those on the copy do without LDS, at most 32),

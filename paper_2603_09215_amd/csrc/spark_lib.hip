@@ -122,7 +122,7 @@ struct spark_ctx {
   int prefill_base = 128;    // prompt rows per pass in the base buffers, see spark_init
   int prefill_chunk = 0;     // > 0: prompt rows per pass, as set by "prefill_rows"
   bool prompt_pass = false;  // the pass being enqueued: consecutive positions of one sequence
-  int attn_prompt_min_rows = 64;   // rows from which such a pass shares K and V between its rows
+  int attn_prompt_min_rows = 0;   // rows from which such a pass shares K and V between its rows (0: by the pass's size)
   int attn_splits_now = 0;   // context slices the rows of the passes being enqueued can reach (0: unknown, launch all)
   std::map<std::pair<const void *, size_t>, int> occ_cache;  // workgroups per CU of a (kernel, LDS bytes)
   // profiling of one kernel class
@@ -509,12 +509,25 @@ RowOut from_row(const RowOut &o, int r0) {
   return RowOut{o.part_units ? (float *)((bf16_t *)o.p + (size_t)r0 * o.pitch()) : o.p + (size_t)r0 * o.stride, o.stride, o.part_units};
 }
 
+// Whether the rows of a prompt pass share K and V (attn_prompt_k) or are attended one by one.  Shared, a
+// pass is a chain of 6 us per 128 tokens of context however few its rows are, after a start of some
+// 10 us; one by one, 4.1 ns per row, KV head and 64 tokens (16 query heads per KV head: 5.8 ns), and
+// contexts that one workgroup takes whole cost least of all.  So there have to be rows enough, and context.
+// Measured, us per layer, passes behind each other, shared against one by one: 4 KV heads of 7 query heads,
+// 192 rows up to 192 / 576 / 1536 tokens 20 : 10, 36 : 47, 70 : 78, 128 rows up to 1024 tokens 50 : 42; 2 of 16,
+// 256 rows up to 512 / 768 / 2048 tokens 31 : 20, 42 : 51, 88 : 93, 512 rows up to 512 tokens 32 : 32.
+bool rows_share_kv(spark_ctx *c, int m) {
+  if (c->attn_prompt_min_rows > 0) return m >= c->attn_prompt_min_rows;
+  const int pairs = m * c->cfg.n_kv_heads, tokens = c->attn_splits_now * ATTN_SLICE;
+  return m >= 64 && (c->dv.group > 8 ? pairs >= 576 && tokens >= 512 : pairs >= 704 && tokens >= 320);
+}
+
 template <typename WT> int launch_attention(spark_ctx *c, const RowDesc *rows, int m, int layer, const RowOut &out, RowMax &row_max) {
   int rc = prof_begin(c, SPARK_KC_ATTN);
   if (rc) return rc;
   // the rows of a prompt pass share their sequence's K and V
   if constexpr (std::is_same<WT, bf16_t>::value) {
-    if (c->prompt_pass && m >= c->attn_prompt_min_rows && c->cfg.head_dim == 128 && c->dv.group <= 16 && c->use_mfma) {
+    if (c->prompt_pass && rows_share_kv(c, m) && c->cfg.head_dim == 128 && c->dv.group <= 16 && c->use_mfma) {
       auto kern = attn_prompt_k<128>;
       const auto key = std::make_pair((const void *)kern, AP_LDS_BYTES);
       if (c->occ_cache.find(key) == c->occ_cache.end()) {
@@ -1490,7 +1503,7 @@ int spark_tune(spark_ctx *c, const char *name, int32_t value) {
   else if (k == "mfma_small_max_k") c->mfma_small_max_k = std::max(8, (int)value);
   else if (k == "mfma_tiled") c->use_tiled = value != 0;
   else if (k == "tiled_row_blocks") c->tiled_row_blocks = std::max(2, std::min(4, (int)value));
-  else if (k == "attn_prompt_min_rows") c->attn_prompt_min_rows = std::max(1, (int)value);
+  else if (k == "attn_prompt_min_rows") c->attn_prompt_min_rows = std::max(0, (int)value);
   else if (k == "direct_max_rows") c->direct_max_rows = value;
   else if (k == "direct_whole_k") c->direct_whole_k = value;
   else if (k == "fuse_norm") c->fuse_norm = value != 0;

@@ -37,16 +37,20 @@ def test_rows_at_the_edges_of_the_tiles(sb, B):
     sp.close()
 
 
-@pytest.mark.parametrize("n,page,group", [(34, 64, 7), (65, 16, 7), (66, 64, 2), (130, 16, 16), (386, 64, 7), (1025, 64, 16),
-                                          (1102, 16, 7)])
-def test_prompt_lengths(sb, n, page, group):
-    """prompts of one pass and of two (1024 rows is the largest pass), ragged last tiles of rows and of
+@pytest.mark.parametrize("n,page,group,shared", [(34, 64, 7, 1), (65, 16, 7, 1), (66, 64, 2, 1), (130, 16, 16, 1), (386, 64, 7, 1),
+                                                 (1025, 64, 16, 1), (1102, 16, 7, 1), (130, 16, 7, 0), (600, 64, 16, 0),
+                                                 (1102, 16, 2, 0)])
+def test_prompt_lengths(sb, n, page, group, shared):
+    """shared: the rows of passes of 64 and more share K and V, otherwise as the library chooses.
+    Prompts of one pass and of two (1024 rows is the largest pass), ragged last tiles of rows and of
     tokens, pages smaller than an attention tile, 16, 7 and 2 query heads per KV head: cache entries of
     every position and the steps behind the prompt"""
-    say(f"case prompt of {n}, pages of {page}, {group} heads")
+    say(f"case prompt of {n}, pages of {page}, {group} heads, shared {shared}")
     shape = SHAPE.replace(n_q_heads=2 * group, n_kv_heads=2)
     weights = wl.make_weights(shape, seed=12, gain_std=0.1)
     sp = sb.Spark(shape, wl.TINY.schedule, weights, max_batch=1, max_seq_len=n + 64, kv_page_tokens=page)
+    if shared:
+        sp.tune("attn_prompt_min_rows", 64)
     compare_run(sp, shape, wl.TINY.schedule, weights, [wl.make_prompt(shape, n, seed=61)], [0], 3, check_kv_every=2,
                 label=f"prompt {n}", kv_all_positions=n < 400)
     sp.close()
@@ -90,6 +94,7 @@ def test_a_nan_stays_behind_its_position(sb, n, at, page):
     marked = prompt.copy()
     marked[at] = bad
     sp = sb.Spark(shape, wl.TINY.schedule, weights, max_batch=2, max_seq_len=n + 64, kv_page_tokens=page)
+    sp.tune("attn_prompt_min_rows", 64)
     a, b = sp.seq_open(0), sp.seq_open(0)
     sp.prefill(a, prompt)
     sp.prefill(b, marked)
