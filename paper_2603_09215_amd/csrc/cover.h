@@ -84,6 +84,7 @@ inline TileCover cover_tiled(int m, int n_in, int n_tasks, int mtiles, int tb, b
   tc.max_words = tc.n_cut ? 2 : 1;   // (a finishing workgroup writes one word per block of tasks: a wave then does too)
   return tc;
 }
+
 constexpr size_t tiled_partial_bytes(const TileCover &tc, int tb) {
   return tc.n_cut ? tc.n_split * range_bytes(tc.n_cut, 32 * TG_WAVES * tb, tc.m_pitch) : 0;
 }
@@ -91,19 +92,20 @@ constexpr size_t tiled_partial_bytes(const TileCover &tc, int tb) {
 // Blocks of 32 rows in a row tile of a projection with 32 tasks a wave and more rows than one tile
 // takes: such a launch is one to three rounds of CUs, and what the last of them leaves idle differs
 // more between the heights than the heights themselves do.  The time of a cover is taken as that of
-// the CU with the most chunks, a chunk of a tile as its blocks of rows and one for its weights.
+// the CU with the most chunks, 0.4 us for each of a chunk's blocks of rows and as much for its weights, and
+// that of its partial sums, at 5 TB/s there and back; a lower tile has to save a twentieth.
 // (down, 768 rows of d 4096, k 13696: tiles of 128 rows make two ranges on 192 CUs, of 96 rows two
-// on all 256; a prompt of 2300 tokens in three such passes 25.4 ms with the former, 23.4 now.)
+// on all 256; a prompt of 2300 tokens in three such passes 25.4 ms with the former, 23.8 with the latter.)
 inline int narrow_row_blocks(int m, int n_in, int n_tasks, int most_blocks, bool always_cut, int n_cu) {
   if (ceil_div(m, 32) <= most_blocks) return tiled_row_blocks_for(m, most_blocks);
   int best = most_blocks;
-  long least = 0;
+  double least = 0.0;
   for (int mt = most_blocks; mt >= 2; --mt) {
     const TileCover tc = cover_tiled(m, n_in, n_tasks, mt, 1, always_cut, false, n_cu, 0);
     const long chunks = (long)ceil_div(tc.n_whole, n_cu) * ceil_div(n_in, MG_KC) +
                         (tc.n_cut ? (long)ceil_div(tc.n_cut * tc.n_split, n_cu) * tc.chunks_per_split : 0);
-    const long cost = chunks * (mt + 1);
-    if (mt == most_blocks || cost < least) { least = cost; best = mt; }
+    const double cost = (double)chunks * (mt + 1) * 0.4 + (double)tiled_partial_bytes(tc, 1) * 2.0 / 5e6;
+    if (mt == most_blocks || cost < 0.95 * least) { least = cost; best = mt; }
   }
   return best;
 }
