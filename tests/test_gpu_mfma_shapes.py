@@ -56,6 +56,41 @@ def test_prompt_lengths(sb, n, page, group, shared):
     sp.close()
 
 
+# inputs long enough that k is cut
+LONG_K = SHAPE.replace(name="bf16-long-k", d_model=1032, n_q_heads=8, n_kv_heads=2, d_ffn=1304)
+
+
+@pytest.mark.parametrize("B,tune", [(6, {}), (6, dict(direct_whole_k=64)), (19, dict(direct_whole_k=64)), (6, dict(direct_max_rows=0)),
+                                    (30, dict(direct_max_rows=16)), (36, {}), (36, dict(tiled_row_blocks=2)),
+                                    (36, dict(fuse_norm=0)), (6, dict(fuse_norm=0)), (12, dict(mfma_tiled=0)),
+                                    (36, dict(mfma_tiled=0)), (36, dict(mfma_tiled=0, fuse_norm=0))])
+def test_projection_kernels_by_their_switches(sb, B, tune):
+    """the kernels that the switches lead to, k cut and whole, on the same rows: without LDS and with it
+    for at most 32 rows, row tiles of two blocks, norms as launches, the caller's weights"""
+    say(f"case {B} rows, {tune}")
+    weights = wl.make_weights(LONG_K, seed=15, gain_std=0.1)
+    prompts = [wl.make_prompt(LONG_K, 1 + i % 3, seed=60 + i) for i in range(B)]
+    sp = sb.Spark(LONG_K, wl.TINY.schedule, weights, max_batch=B, max_seq_len=64, kv_page_tokens=16)
+    for name, value in tune.items():
+        sp.tune(name, value)
+    compare_run(sp, LONG_K, wl.TINY.schedule, weights, prompts, [0] * B, 6, label=f"{B} rows {tune}")
+    sp.close()
+
+
+def test_prompt_without_the_large_buffers(sb, monkeypatch):
+    """a scratch area one byte short of the buffers of 1024-row passes: the copy of the weights and
+    passes in the buffers that every context has"""
+    say("case prompt without the large buffers")
+    lib = sb.load_library()
+    init = lib.spark_init
+    weights = wl.make_weights(SHAPE, seed=12, gain_std=0.1)
+    monkeypatch.setattr(lib, "spark_init", lambda c, w, kv, kvb, sc, scb, st, out: init(c, w, kv, kvb, sc, scb - 1, st, out))
+    sp = sb.Spark(SHAPE, wl.TINY.schedule, weights, max_batch=1, max_seq_len=660, kv_page_tokens=64)
+    compare_run(sp, SHAPE, wl.TINY.schedule, weights, [wl.make_prompt(SHAPE, 600, seed=61)], [0], 3, check_kv_every=2,
+                label="prompt without the large buffers", kv_all_positions=True)
+    sp.close()
+
+
 def test_prompt_rows_can_be_set_and_unset(sb):
     """"prefill_rows": passes of a set size, up to that of the large buffers, and back to the size that
     a new context chooses"""

@@ -310,9 +310,9 @@ def test_batched_decode_on_the_mfma_path(sb, tiled):
 
 @pytest.mark.parametrize("rows,small_max_k", [(32, 32768), (96, 32768), (96, 8), (160, 8)])
 def test_prompt_pass_row_counts_and_tile_shapes(sb, rows, small_max_k):
-    """a 150-token prompt in passes of 32, 96 or 160 rows (one 32-row tile; a 64-row and a 32-row
-    tile; ragged last tiles), with the 128-task tiles that matrices of few tiles get by default and
-    with 256-task tiles forced for every projection (64 tasks, four A tiles, per wave); the decoding
+    """a 150-token prompt in passes of 32, 96 or 160 rows (one block of rows; three and five of them;
+    ragged last tiles) on the copy of the weights, and (small_max_k 8) on the caller's weights with
+    eight-wave workgroups, whose tiles are of 256 tasks, forced for every projection; the decoding
     steps behind the prompt and cache entries across it are compared with the oracle"""
     shape = wl.TINY.shape.replace(name="bf16-prompt", dtype=wl.DTYPE_BF16, n_layers=4, d_model=512,
                                   n_q_heads=4, n_kv_heads=2, head_dim=128, d_ffn=1024 + 40,
@@ -323,6 +323,7 @@ def test_prompt_pass_row_counts_and_tile_shapes(sb, rows, small_max_k):
     sp = sb.Spark(shape, sched, weights, max_batch=1, max_seq_len=256, kv_page_tokens=64)
     sp.tune("prefill_rows", rows)
     sp.tune("mfma_small_max_k", small_max_k)
+    sp.tune("mfma_tiled", small_max_k > 8)
     compare_run(sp, shape, sched, weights, [wl.make_prompt(shape, 150, seed=61)], [2], 8, check_kv_every=1,
                 label=f"prompt150 rows={rows} small_k={small_max_k}", kv_all_positions=True)
     sp.close()
@@ -408,11 +409,11 @@ def test_long_contexts(sb, name, shape_kw, page, long_prompt):
     sp.close()
 
 
-@pytest.mark.parametrize("pieces", [3, 8])
+@pytest.mark.parametrize("pieces", [3, 8, 10])
 def test_attention_pieces_per_workgroup(sb, pieces):
     """the MFMA attention kernel with a fixed number of 64-token pieces per workgroup (the library
-    picks 1, 2, 4 or 8 by the size of the launch; eight is what contexts of 4096 tokens and more
-    get): a 2300-token context is 36 slices, so workgroups with all their pieces, with some, and
+    picks one to six for workgroups of one team of waves, and an even number up to ten for two teams, by
+    the size of the launch; set by the switch, eight and more run two): a 2300-token context is 36 slices, so workgroups with all their pieces, with some, and
     the ragged last one all occur; prompt passes and decode steps"""
     shape = wl.TINY.shape.replace(name="bf16-hd128-pieces", dtype=wl.DTYPE_BF16, n_layers=3, d_model=512,
                                   n_q_heads=4, n_kv_heads=2, head_dim=128, d_ffn=1024)

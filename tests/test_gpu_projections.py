@@ -131,3 +131,38 @@ def test_mlp_against_64_bits(sb, rows, power, ffn):
     say(f"  MLP, {rows} rows: mean {err.mean():.3g}, largest {err.max():.3g}")
     assert err.max() <= 9e-7
     sp.close()
+
+
+@pytest.mark.parametrize("rows", [1023, 700])
+def test_prompt_mlp_with_whole_and_cut_tiles(sb, rows):
+    """gate/up of a large prompt pass: more tiles of 256 tasks x 96 rows than CUs, so that some end in the
+    projection and the others in the finishing launch (33 x 11 tiles, 256 whole; 33 x 8, 256 whole), both
+    of which write the rows' lists of magnitudes for the down projection.  Seen in the second layer's
+    value entries, which are rounded to bf16: within 2^-8 of themselves and 1e-4 of a row's typical one."""
+    import torch
+    say(f"case MLP of a prompt of {rows}")
+    d, ffn, V = 1032, 8264, 900
+    shape = wl.TINY.shape.replace(name="prompt-mlp", dtype=wl.DTYPE_BF16, n_layers=2, d_model=d, n_q_heads=2, n_kv_heads=1,
+                                  head_dim=128, d_ffn=ffn, vocab_text=V, vocab_speech=0)
+    sched = wl.TINY.schedule.replace(exit_layer=1, period_k=1, phase=0, n_text=1, n_speech=0)
+    W = model(shape, False)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(5)
+    W["wd"][0] = (torch.randn(d, ffn, generator=gen, device="cuda:0") * 0.05).bfloat16()
+    spread = torch.randint(-8, 9, (ffn,), generator=gen, device="cuda:0")
+    W["wu"][0] = torch.ldexp(W["wu"][0].float(), spread[:, None]).bfloat16()   # activations far apart: the lists matter
+    W["wd"][0] = torch.ldexp(W["wd"][0].float(), -spread[None, :]).bfloat16()
+    sp = sb.Spark(shape, sched, W, max_batch=1, max_seq_len=rows + 64, kv_page_tokens=64)
+    prompt = wl.make_prompt(shape, rows + 1, seed=7)
+    sid = sp.seq_open(0)
+    sp.prefill(sid, prompt)
+    h = W["embed"][torch.as_tensor(prompt[:rows], device="cuda:0").long()].double()
+    n = norm64(h, W["mlp_norm"][0], shape.rms_eps)
+    act = torch.nn.functional.silu(n @ W["wg"][0].double().T) * (n @ W["wu"][0].double().T)
+    v = norm64(h + act @ W["wd"][0].double().T, W["attn_norm"][1], shape.rms_eps) @ W["wv"][1].double().T
+    want = v.cpu().numpy()
+    typical = np.sqrt((want ** 2).mean(axis=1))
+    for pos in range(0, rows, 3):
+        _, got = sp.get_kv(sid, 1, pos)
+        assert np.all(np.abs(got - want[pos]) <= 2.0 ** -8 * np.abs(want[pos]) + 1e-4 * typical[pos]), pos
+    sp.close()
