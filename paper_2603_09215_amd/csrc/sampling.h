@@ -244,6 +244,7 @@ sample_pick_k(const float *__restrict__ logits, int V, double top_p, const u64 *
   __syncthreads();
   u64 total = 0;
   for (int w = 0; w < SAMPLE_WAVES; ++w) total += s_wave[w];
+  if (total == 0) return;   // (an infinite logit leaves no masses to draw from: the arg-max stands)
   u64 target = (u64)ceil(top_p * (double)total);
   target = target < 1 ? 1 : (target > total ? total : target);
   const u64 word = omega[row];

@@ -162,3 +162,28 @@ def test_chunked_free_running_sampled_decode(sb):
         os_.close()
     om.close()
     sp.close()
+
+
+def test_an_infinite_logit_is_the_token(sb):
+    """a logit beyond the range of an fp32 leaves no masses to draw from (the others are zero times it,
+    its own is not a number): the arg-max is emitted and the next step runs on it"""
+    w = wl.TINY
+    say("case infinite logits")
+    weights = wl.make_weights(w.shape, seed=0, gain_std=0.1)
+    for head in ("lm_head", "lens_head"):
+        weights[head] = weights[head].copy()
+        for j in range(64):                       # one element each: its sign decides which of two is +inf
+            for sign in (0, 1):
+                weights[head][100 + 2 * j + sign] = 0.0
+                weights[head][100 + 2 * j + sign, j] = (1 - 2 * sign) * np.float32(3.4e38)
+    sp = sb.Spark(w.shape, w.schedule, weights, max_batch=2, max_seq_len=64, kv_page_tokens=16)
+    sp.set_sampling(0.7, 0.9)
+    ids = [sp.seq_open(0), sp.seq_open(1)]
+    for i in ids:
+        sp.prefill(i, wl.make_prompt(w.shape, 7 + i, seed=3 + i))
+    for step in range(6):
+        tok, _ = sp.decode_sampled(1, ids, np.array([1, 2 ** 63], dtype=np.uint64))
+        for b, i in enumerate(ids):
+            logits, _ = sp.get_logits(i)
+            assert logits.max() == np.inf and tok[0, b] == int(np.argmax(logits)), (step, b)
+    sp.close()
