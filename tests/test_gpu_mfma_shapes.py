@@ -77,6 +77,35 @@ def test_projection_kernels_by_their_switches(sb, B, tune):
     sp.close()
 
 
+def test_flush_of_more_rows_than_a_pass_takes(sb):
+    """256 sequences with fifteen pending positions each complete them on the same step: 4096 rows, which
+    go through the upper layers in two pieces (3072 at this width); the sequences' logits are those that
+    a few of them have alone"""
+    import torch
+    say("case flush of 4096 rows")
+    shape = SHAPE.replace(n_layers=2, d_model=4096, n_q_heads=2, n_kv_heads=1, d_ffn=72, vocab_text=0, vocab_speech=300)
+    sched = wl.TINY.schedule.replace(exit_layer=1, period_k=16, phase=15, n_text=0, n_speech=1, scope=wl.SCOPE_STREAM)
+    weights = wl.make_weights(shape, seed=16, gain_std=0.1)
+    rng = np.random.default_rng(9)
+    first, forced = rng.integers(0, 300, 256), rng.integers(0, 300, (16, 256))
+
+    def run(which):
+        sp = sb.Spark(shape, sched, weights, max_batch=len(which), max_seq_len=32, kv_page_tokens=16)
+        ids = [sp.seq_open(0) for _ in which]
+        for i, b in zip(ids, which):
+            sp.prefill(i, [int(first[b])])
+        _, depth = sp.decode(16, ids, forced[:, which])
+        assert np.all(depth[:15] == 1) and np.all(depth[15] == 2)
+        out = np.stack([sp.get_logits(i)[0] for i in ids])
+        assert sp.get_stats(ids[0])["flush_hist"] == {16: 1}
+        sp.close()
+        return out
+
+    some = [0, 1, 100, 191, 192, 193, 254, 255]   # 191 and 192: the rows around the cut
+    assert np.max(np.abs(run(list(range(256)))[some] - run(some))) <= TOL[wl.DTYPE_BF16]
+    torch.cuda.empty_cache()
+
+
 def test_prompt_without_the_large_buffers(sb, monkeypatch):
     """a scratch area one byte short of the buffers of 1024-row passes: the copy of the weights and
     passes in the buffers that every context has"""
