@@ -286,8 +286,8 @@ template <typename WT, bool DS = false> struct EpiResidual {
 };
 // hidden[x_slot][i] += y as above, and what the next projection needs of the new hidden state
 // h: gamma (.) h for pass row r, h's sum of squares (see RowScale) and the largest magnitude of
-// gamma (.) h.  For the finishing launch of a k-split projection, whose threads of one row are 32
-// lanes apart.
+// gamma (.) h.  For launches that see a whole group of a row's tasks at once: the finishing launch of a
+// k-split projection (32 tasks, on 32 lanes) and mfma_direct_k (a workgroup's, 16 lanes).
 // SPLIT: as three bf16 parts, and without the magnitude.
 template <typename WT, bool SPLIT = false> struct EpiResidualNorm {
   struct State { float ssq; uint32_t amax; };
@@ -323,7 +323,7 @@ template <typename WT, bool SPLIT = false> struct EpiResidualNorm {
   __device__ void finish(int task, int r, const RowDesc &rd, float y0, float y1, State &s) const {
     finish_old(task, r, rd, y0, y1, load_old(task, r, rd), s);
   }
-  // `s`: the states of the threads that finished the 32 tasks of `block` in row r, combined
+  // `s`: the states of the threads that finished the tasks of group `block` in row r, combined
   __device__ void put_row(int r, int block, const State &s) const {
     atomicAdd(ssq + r * SSQ_WAYS + block % SSQ_WAYS, (unsigned long long)(s.ssq * SSQ_SCALE + 0.5f));
     if constexpr (!SPLIT) row_max.put(r, block, s.amax);

@@ -34,7 +34,7 @@ constexpr int MAX_STEPS_PER_CALL = 256;
 // (measured at four rows: level at the GLM shape, 14-20 % faster for a batch of four at the Step
 // shape); five rows would be two such passes
 constexpr int MFMA_MIN_ROWS = 5;
-constexpr int TILED_WIDE_TASKS = 8192;   // projections from here on have tiles enough for 64 tasks a wave at any row count
+constexpr int TILED_WIDE_TASKS = 8192;   // gate/up from here on has tiles enough for 64 tasks a wave at any row count (32 tiles)
 constexpr int MAX_SEQ_LEN = 16384;
 
 struct Layout {  // byte offsets into the scratch buffer
@@ -554,7 +554,7 @@ template <typename WT> int launch_attention(spark_ctx *c, const RowDesc *rows, i
   return prof_end(c, SPARK_KC_ATTN);
 }
 
-// ------------------------------------------------------------------ MFMA path (16..128+ rows, bf16)
+// ------------------------------------------------------------------ MFMA path (five and more rows, bf16)
 
 
 // Which kernel takes a pass's projections, and with it how the rows that they read lie in memory: on the

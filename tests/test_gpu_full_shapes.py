@@ -43,8 +43,8 @@ def sampled_draws_match(sp, w, prompt, offset, n_steps=12, temperature=0.7, top_
 @pytest.mark.parametrize("name,n_steps,offset,n_prompt", [
     ("step_audio_2_mini", 36, 0, 32),    # 3 * (1 + 2) * 4 steps: flushes of 1, 2 and 3 rows
     ("glm_4_voice", 24, 10, 32),         # enters the cycle 3 text slots before a 26-slot speech chunk
-    # a prompt longer than one pass of the prompt path (192 rows at this shape: three tiles of 64
-    # rows on the MFMA units, then a ragged pass), and a context of several attention slices
+    # a prompt whose pass is of several row tiles on the MFMA units (199 rows, a ragged last tile), and a
+    # context of several attention slices
     ("step_audio_2_mini", 8, 1, 200),
 ])
 def test_full_shape_short_run(name, n_steps, offset, n_prompt):
