@@ -53,7 +53,7 @@ template <int NT> __device__ __forceinline__ void put_wave_max(const RowMax &row
 // query heads hq0 .. hq0 + g_count - 1 of row r: count the slice as done; the workgroup that
 // arrives last for this (row, group of heads) merges the slices,
 // out = sum_s exp(m_s - M) o_s / sum_s exp(m_s - M) l_s.
-template <int HD, int NT, bool DS>
+template <int HD, int NT, bool PARTS>
 __device__ __forceinline__ void attn_merge(const RowDesc &rd, int r, int hq0, int g_count, int nq,
                                            int n_splits, int slice_tokens, const float *__restrict__ part,
                                            int *__restrict__ cnt, const RowOut &out,
@@ -106,20 +106,18 @@ __device__ __forceinline__ void attn_merge(const RowDesc &rd, int r, int hq0, in
       }
     }
     const float inv = 1.0f / L;
-    out.put(r, (hq0 + g) * HD + c, make_float4(acc4.x * inv, acc4.y * inv, acc4.z * inv, acc4.w * inv));
+    out.put<PARTS>(r, (hq0 + g) * HD + c, make_float4(acc4.x * inv, acc4.y * inv, acc4.z * inv, acc4.w * inv));
     const uint32_t m01 = max(magnitude_bits(acc4.x * inv), magnitude_bits(acc4.y * inv));
     const uint32_t m23 = max(magnitude_bits(acc4.z * inv), magnitude_bits(acc4.w * inv));
     big = max(big, max(m01, m23));
   }
   put_wave_max<NT>(row_max, r, big);
-  if (DS) wait_memory_ops();   // the caller's next barrier arrival does not wait for these stores
 }
 
 // One task, executed by all NT threads of a workgroup: query heads hq0 .. hq0 + g_count - 1
 // (g_count <= G, all sharing KV head hk) of row r over one slice; `cnt` counts the slices of this
-// (row, group of heads) that are done.  DS: the queries were written, and the output will be
-// read, by other workgroups of the same kernel (device-scope accesses).
-template <typename KT, int HD, int G, int NT, bool DS>
+// (row, group of heads) that are done.
+template <typename KT, int HD, int G, int NT, bool PARTS>
 __device__ __forceinline__ void attn_task(const RowDesc &rd, int r, int hk, int hq0, int g_count,
                                           int split, const float *__restrict__ qbuf, const KVView &kv,
                                           int layer, int nq, int n_splits, float scale,
@@ -165,7 +163,7 @@ __device__ __forceinline__ void attn_task(const RowDesc &rd, int r, int hk, int 
     const float *qp = qbuf + (size_t)r * nq * HD + (hq0 + min(g, g_count - 1)) * HD + dc * VEC;
 #pragma unroll
     for (int e = 0; e < VEC; e += 2) {
-      float2 v = load2_maybe_ds<DS>(qp + e);
+      float2 v = *(const float2 *)(qp + e);
       q[g][e] = v.x * scale; q[g][e + 1] = v.y * scale;
     }
   }
@@ -239,11 +237,10 @@ __device__ __forceinline__ void attn_task(const RowDesc &rd, int r, int hk, int 
 #pragma unroll
       for (int w = 0; w < WAVES; ++w) o += ored[(w * G + g) * HD + c];
       const float inv = 1.0f / ml[g * 2 + 1], y = o * inv;
-      out.put(r, (hq0 + g) * HD + c, y);
+      out.put<PARTS>(r, (hq0 + g) * HD + c, y);
       big = max(big, magnitude_bits(y));
     }
     put_wave_max<NT>(row_max, r, big);
-    if (DS) wait_memory_ops();
     return;
   }
   for (int i = tid; i < g_count * HD; i += NT) {
@@ -258,13 +255,13 @@ __device__ __forceinline__ void attn_task(const RowDesc &rd, int r, int hk, int 
     store_device_scope(part + ((size_t)(r * nq + hq0 + g) * n_splits + split) * PS + HD + w,
                        ml[g * 2 + w]);
   }
-  attn_merge<HD, NT, DS>(rd, r, hq0, g_count, nq, n_splits, ATTN_SLICE, part, cnt, out, row_max, s_last);
+  attn_merge<HD, NT, PARTS>(rd, r, hq0, g_count, nq, n_splits, ATTN_SLICE, part, cnt, out, row_max, s_last);
 }
 
 // stand-alone launch: one workgroup per (slice, group of G query heads, row).  A KV head's `group`
 // query heads are dealt to ceil(group / G) workgroups: with few rows and few KV heads that is what
 // gives the chip enough workgroups, at the price of reading the slice's K and V once per group.
-template <typename KT, int HD, int G>
+template <typename KT, int HD, int G, bool PARTS>
 __global__ void __launch_bounds__(ATTN_THREADS)
 attn_rows_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbuf, KVView kv,
             int layer, int nq, int group, int n_splits, float scale, float *__restrict__ part,
@@ -274,7 +271,7 @@ attn_rows_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbuf, KV
   const int split = blockIdx.x, hk = blockIdx.y / n_groups, gi = blockIdx.y - hk * n_groups, r = blockIdx.z;
   const RowDesc rd = rows[r];
   if (split * ATTN_SLICE > rd.pos) return;        // slice beyond the row's context
-  attn_task<KT, HD, G, ATTN_THREADS, false>(rd, r, hk, hk * group + gi * G, min(G, group - gi * G), split,
+  attn_task<KT, HD, G, ATTN_THREADS, PARTS>(rd, r, hk, hk * group + gi * G, min(G, group - gi * G), split,
                                             qbuf, kv, layer, nq, n_splits, scale, part,
                                             arrivals + r * gridDim.y + blockIdx.y, out, row_max, lds);
 }
@@ -339,7 +336,7 @@ __device__ __forceinline__ void attn_piece_load(AttnPiece &pc, const KVView &kv,
 // A piece is a chain of four barriers, about 3 us, and long contexts make as few workgroups as CUs
 // (more of them leave more partial results to one workgroup's merge): a step of eight sequences of 8192
 // tokens 18.63 ms with one team and eight pieces, 17.89 with two teams and ten.
-template <int HD, int TEAMS>
+template <int HD, int TEAMS, bool PARTS>
 __global__ void __launch_bounds__(ATTN_THREADS * TEAMS)
 attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbuf, KVView kv, int layer,
                  int nq, int kv_group, int heads_per_wg, int n_splits, int pieces, float scale,
@@ -551,7 +548,7 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
   if (rd.pos < span) {   // the whole context is this slice: nothing to hand over and nobody to wait for
     __syncthreads();
     uint32_t big = 0u;
-    auto finish = [&](auto store) {
+    if (team == 0) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int g = 4 * quad + i;
@@ -560,14 +557,10 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
         for (int t = 0; t < 2; ++t)
           if (g < group) {
             const float y = oacc[t][i] * inv;
-            store((hq0 + g) * HD + 32 * wave + 16 * t + col, y);
+            out.put<PARTS>(r, (hq0 + g) * HD + 32 * wave + 16 * t + col, y);
             big = max(big, magnitude_bits(y));
           }
       }
-    };
-    if (team == 0) {
-      if (out.part_units) finish([&](int k, float y) { out.put_parts(r, k, y); });
-      else finish([&](int k, float y) { *out.at(r, k) = y; });
     }
     put_wave_max<ATTN_THREADS * TEAMS>(row_max, r, big);
     return;
@@ -589,7 +582,7 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
     const float v = (threadIdx.x & 1) ? s_sum[g] + s_sum[16 + g] + s_sum[32 + g] + s_sum[48 + g] : s_max[g];
     store_device_scope(part + ((size_t)(r * nq + hq0 + g) * n_splits + split) * PS + HD + (threadIdx.x & 1), v);
   }
-  attn_merge<HD, ATTN_THREADS * TEAMS, false>(rd, r, hq0, group, nq, n_splits, span, part,
+  attn_merge<HD, ATTN_THREADS * TEAMS, PARTS>(rd, r, hq0, group, nq, n_splits, span, part,
                                               arrivals + r * gridDim.y + blockIdx.y, out, row_max, &s_last);
 }
 
@@ -629,7 +622,7 @@ __device__ __forceinline__ unsigned pack_bf16_rn(float a, float b) {   // (one i
   return __builtin_bit_cast(unsigned, __builtin_convertvector(f, attn_bf16x2_t));
 }
 
-template <int HD>
+template <int HD, bool PARTS>
 __global__ void __launch_bounds__(AP_THREADS, 2)
 attn_prompt_k(const RowDesc *__restrict__ rows, int m_rows, const float *__restrict__ qbuf, KVView kv, int layer, int nq,
               int group, int rows_per_wg, int n_row_tiles, float scale, RowOut out, RowMax row_max) {
@@ -850,7 +843,7 @@ attn_prompt_k(const RowDesc *__restrict__ rows, int m_rows, const float *__restr
         y[e] = (o[b][4 * i + e] * f0 + mine[(b * 16 + 4 * i + e) * 64] * f1) * inv;
         big = max(big, magnitude_bits(y[e]));
       }
-      if (live) out.put(row0 + row, head * HD + 32 * b + 8 * i + 4 * hl, make_float4(y[0], y[1], y[2], y[3]));
+      if (live) out.put<PARTS>(row0 + row, head * HD + 32 * b + 8 * i + 4 * hl, make_float4(y[0], y[1], y[2], y[3]));
     }
   if (row_max.list) {
     big = max(big, (uint32_t)__shfl_xor((int)big, 32, 64));

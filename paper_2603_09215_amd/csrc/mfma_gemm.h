@@ -80,7 +80,8 @@ prep_rows_k(const RowDesc *__restrict__ rows, const float *__restrict__ src, int
   const float *row = src + (size_t)(indirect ? rows[r].x_slot : r) * stride;
   uint32_t amax = 0u;
   auto put = [&](int k, float4 f) {
-    x.put(r, k, f);
+    if (x.part_units) x.put<true>(r, k, f);
+    else x.put<false>(r, k, f);
     amax = max(amax, max(max(magnitude_bits(f.x), magnitude_bits(f.y)), max(magnitude_bits(f.z), magnitude_bits(f.w))));
   };
   auto finish = [&]() {

@@ -436,7 +436,10 @@ void launch_attention_g(spark_ctx *c, const RowDesc *rows, int m, int layer, con
   const int n_groups = (d.group + GT - 1) / GT;
   const int splits = c->attn_splits_now > 0 ? std::min(d.n_splits, c->attn_splits_now) : d.n_splits;
   row_max.n = g.n_kv_heads * n_groups * (ATTN_THREADS / 64);
-  attn_rows_k<WT, HD, GT><<<dim3(splits, g.n_kv_heads * n_groups, m), ATTN_THREADS, 0, c->stream>>>(
+  auto kern = attn_rows_k<WT, HD, GT, false>;
+  if constexpr (std::is_same<WT, bf16_t>::value)
+    if (out.part_units) kern = attn_rows_k<WT, HD, GT, true>;
+  kern<<<dim3(splits, g.n_kv_heads * n_groups, m), ATTN_THREADS, 0, c->stream>>>(
       rows, q, kv_view(c), layer, g.n_q_heads, d.group, d.n_splits,
       1.0f / sqrtf((float)HD), part, at<int>(c, c->lo.arrivals), out, row_max);
 }
@@ -495,7 +498,8 @@ int launch_attention_rows(spark_ctx *c, const RowDesc *rows, int m, int m_pass, 
     const int heads_per_wg = (tasks < c->n_cu / 2 && c->dv.group > 8) ? 8 : c->dv.group;
     const int wg_per_kv = (c->dv.group + heads_per_wg - 1) / heads_per_wg;
     row_max.n = c->cfg.n_kv_heads * wg_per_kv * shape.teams * (ATTN_THREADS / 64);
-    const auto kern = shape.teams == 2 ? attn_rows_mfma_k<128, 2> : attn_rows_mfma_k<128, 1>;
+    const auto kern = out.part_units ? (shape.teams == 2 ? attn_rows_mfma_k<128, 2, true> : attn_rows_mfma_k<128, 1, true>)
+                                     : (shape.teams == 2 ? attn_rows_mfma_k<128, 2, false> : attn_rows_mfma_k<128, 1, false>);
     kern<<<dim3((splits + pieces - 1) / pieces, c->cfg.n_kv_heads * wg_per_kv, m), ATTN_THREADS * shape.teams, 0, c->stream>>>(
         rows, q, kv_view(c), layer, c->cfg.n_q_heads, c->dv.group, heads_per_wg, c->dv.n_splits, pieces, 1.0f / sqrtf(128.0f),
         at<float>(c, c->lo.part), at<int>(c, c->lo.arrivals), out, row_max);
@@ -528,7 +532,7 @@ template <typename WT> int launch_attention(spark_ctx *c, const RowDesc *rows, i
   // the rows of a prompt pass share their sequence's K and V
   if constexpr (std::is_same<WT, bf16_t>::value) {
     if (c->prompt_pass && rows_share_kv(c, m) && c->cfg.head_dim == 128 && c->dv.group <= 16 && c->use_mfma) {
-      auto kern = attn_prompt_k<128>;
+      auto kern = out.part_units ? attn_prompt_k<128, true> : attn_prompt_k<128, false>;
       const auto key = std::make_pair((const void *)kern, AP_LDS_BYTES);
       if (c->occ_cache.find(key) == c->occ_cache.end()) {
         HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)AP_LDS_BYTES));
