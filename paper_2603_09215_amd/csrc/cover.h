@@ -110,6 +110,21 @@ inline int narrow_row_blocks(int m, int n_in, int n_tasks, int most_blocks, bool
   return best;
 }
 
+// mfma_direct_k with its k whole: tiles of a workgroup.  One for at most 8 rows, whose activations cost
+// a workgroup little (the weights' time of gate/up at 8 rows, d 3584 and 4096: 46.7 and 43.0 us with one tile, 49.1
+// and 44.1 as below; at 16 rows 52.4 and 47.0 against 49.0 and 43.7); not for the heads, whose workgroups
+// each send an atomic per row (39624 outputs, 8 rows: 56 us with one tile, 50 with three).  Otherwise as few
+// rounds of CUs as five tiles make, and the last one full.
+inline int direct_tiles(int m, int blocks, int n_cu, bool heads) {
+  if (m <= 8 && !heads) return 1;
+  int nt = 1, best = 0;
+  for (int n = 1; n <= 5; ++n) {
+    const int cost = ceil_div(ceil_div(blocks, n), n_cu) * n;   // tiles the busiest CU takes
+    if (n == 1 || cost <= best) { best = cost; nt = n; }
+  }
+  return nt;
+}
+
 // mfma_direct_k with its k cut: ranges (1: it is not cut) and chunks in each
 inline int direct_split(int m, int n_in, int n_tasks, int n_cu, int &chunks_per_split) {
   const int n_chunks = ceil_div(n_in, MG_KC), groups = ceil_div(ceil_div(n_tasks, TG_TASKS), TD_CUT_TILES);

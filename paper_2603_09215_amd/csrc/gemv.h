@@ -187,13 +187,14 @@ struct NoState {};
 // does not matter, to the row's words; the next projection's epilogue reads them.
 constexpr float SSQ_SCALE = 16777216.0f;   // 2^24: sums of squares up to 1e12 fit 64 bits
 struct RowScale {
-  const unsigned long long *ssq;   // [pass row][SSQ_WAYS], nullptr: rows are normalised already
+  const unsigned long long *ssq;   // [SSQ_WAYS][pitch], nullptr: rows are normalised already
+  int pitch;
   float inv_d, eps;
   __device__ __forceinline__ float of(int r) const {
     if (!ssq) return 1.0f;
     unsigned long long w[SSQ_WAYS], tot = 0ull;
 #pragma unroll
-    for (int i = 0; i < SSQ_WAYS; ++i) w[i] = ssq[r * SSQ_WAYS + i];
+    for (int i = 0; i < SSQ_WAYS; ++i) w[i] = ssq[i * pitch + r];
 #pragma unroll
     for (int i = 0; i < SSQ_WAYS; ++i) tot += w[i];
     return 1.0f / sqrtf((float)((double)tot * (1.0 / (double)SSQ_SCALE)) * inv_d + eps);
@@ -210,7 +211,7 @@ template <typename WT, bool DS = false> struct EpiQKV {
   float *qbuf;             // [pass row][nq*hd], rotated queries
   const float2 *rope;      // [pos][hd/2] (cos, sin)
   KVView kv;
-  RowScale scale = RowScale{nullptr, 0.f, 0.f};
+  RowScale scale = RowScale{nullptr, 0, 0.f, 0.f};
   __device__ void init(State &) const {}
   __device__ void weight_rows(int task, const WT *&r0, const WT *&r1) const {
     int half = hd >> 1, head = task / half, i = task - head * half;
@@ -297,7 +298,8 @@ template <typename WT, bool SPLIT = false> struct EpiResidualNorm {
   int d;
   const float *gamma;          // gain of the norm that follows
   RowOut x;                    // gamma (.) h of the pass's rows
-  unsigned long long *ssq;     // [pass row][SSQ_WAYS], zero before the launch
+  unsigned long long *ssq;     // [SSQ_WAYS][ssq_pitch], zero before the launch
+  int ssq_pitch;
   RowMax row_max;
   __device__ void init(State &s) const { s.ssq = 0.f; s.amax = 0u; }
   __device__ void weight_rows(int task, const WT *&r0, const WT *&r1) const {
@@ -325,7 +327,7 @@ template <typename WT, bool SPLIT = false> struct EpiResidualNorm {
   }
   // `s`: the states of the threads that finished the tasks of group `block` in row r, combined
   __device__ void put_row(int r, int block, const State &s) const {
-    atomicAdd(ssq + r * SSQ_WAYS + block % SSQ_WAYS, (unsigned long long)(s.ssq * SSQ_SCALE + 0.5f));
+    atomicAdd(ssq + block % SSQ_WAYS * ssq_pitch + r, (unsigned long long)(s.ssq * SSQ_SCALE + 0.5f));
     if constexpr (!SPLIT) row_max.put(r, block, s.amax);
   }
   __device__ void end(int, const RowDesc &, State &) const {}
@@ -371,7 +373,7 @@ template <typename WT, bool SPLIT = false> struct EpiSwiGLUMax {
   int d, F;
   RowOut act;
   RowMax row_max;
-  RowScale scale = RowScale{nullptr, 0.f, 0.f};
+  RowScale scale = RowScale{nullptr, 0, 0.f, 0.f};
   __device__ void init(State &s) const { s.amax = 0u; }
   __device__ void weight_rows(int task, const WT *&r0, const WT *&r1) const {
     r0 = wg + (size_t)task * d;

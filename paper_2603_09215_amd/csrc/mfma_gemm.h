@@ -1112,34 +1112,57 @@ mfma_finish_tile_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, int n_
 // ------------------------------------------------------------------ at most 32 rows
 //
 // Batched decoding: the projection is a stream of weights again, only with more arithmetic per
-// weight.  A workgroup of eight waves takes NT A tiles (16 NT tasks) and one range of k, an eighth
+// weight.  A workgroup of four waves takes NT A tiles (16 NT tasks) and one range of k, a quarter
 // of it for each wave; the waves' sums meet in LDS at the end.  Weights and activations go from
 // memory straight into registers, both in operand order, so the loop has no LDS traffic and no
 // barrier: every wave runs on its own behind its own loads, RING steps ahead (memory answers in
 // order: a shorter ring for the activations would empty the weights' longer one), and the
 // activations are cut into fp16 parts by the wave that multiplies them.
 //
-// One workgroup per CU, and NT so that all CUs have one of about the same size: a workgroup then
-// takes the whole range of k, and there are no partial sums and no finishing launch.  (Small
-// workgroups, several on a CU, were slower: 592 of them on 256 CUs leave some CUs a third more than
-// the average, and a CU's share of the memory system is what the stream runs at; and every
-// workgroup reads all activations, 271 MB for 592 of them at 32 rows, which cost what weights cost.)
+// v_mfma_f32_16x16x32_f16, COLS = 16 or 32 activation rows as one or two B operands: with 32-wide
+// operands a pass of 16 rows would fetch and cut as many activations as one of 32.  What bounds the short
+// launches is what a CU has to fetch, activations (from L2, 4 COLS bytes per k) as much as weights:
+// q/k/v of 8 rows, k 3584, 33 MB: 11.0 us with the activations' loads left out, 16.2 with 32 columns, 11.9
+// with 16.
+// More in flight is not better: the same launch takes 12.5, 11.9, 12.3, 19 us with rings of 3, 4, 6 and 14 steps,
+// and 13 to 16 with eight or sixteen waves; gate/up of 271 MB 46.7 us with four waves and one tile,
+// 53 with eight and five (237 workgroups that all start, and all finish, together).
+// So: few loads in flight per wave, four waves, and for at most 8 rows one tile a workgroup, several
+// workgroups on a CU, whose starts and ends run under the others' streaming.  From 9 rows on fetching all
+// activations in every workgroup costs more than that gains (gate/up of 16 rows 52.4 us with one tile, 49.0 with
+// five): then NT makes one round of CUs, or as few as can be, of about equal size.  Either way a workgroup
+// takes all of k, and there are no partial sums and no finishing launch.
 // Only a long k with few tasks (down) is cut: CUT writes partial sums.
-constexpr int TD_WAVES = 8;
-constexpr int td_ring(int nt) { return nt == 1 ? 8 : nt == 2 ? 6 : 4; }
-constexpr size_t td_lds_bytes(int nt) { return sizeof(float) * ((TD_WAVES / 2) * nt * 32 * 33 + OP_ROWS + nt * 32); }
+//
+// Loads are buffer loads: the lane's place is one register for all of them, step and tile are scalars, and
+// what lies past the end of a matrix or of the activations comes back as zeros.
+constexpr int TD_WAVES = 4;
+constexpr int td_ring(int nt) { return nt == 1 ? 4 : 2; }
+constexpr int TD_PITCH = 36;   // floats of LDS per (tile, activation row): 32 weight rows and a skew of one 16-byte word
+constexpr size_t td_lds_bytes(int nt, int cols) { return sizeof(float) * (TD_WAVES * nt * cols * TD_PITCH + nt * 32 + OP_ROWS); }
 
-template <int NT, typename Epi, bool CUT>
-__global__ void __launch_bounds__(64 * TD_WAVES, 2)
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __amdgpu_buffer_rsrc_t buffer_t;
+__device__ __forceinline__ buffer_t buffer_of(const void *p, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)(uint32_t)(bytes < 0xfffffff0ull ? bytes : 0xfffffff0ull), 0x00027000);
+}
+template <bool ONCE> __device__ __forceinline__ u32x4_t load_buffer16(buffer_t b, int lane_at, int at) {   // ONCE: non-temporal
+  return __builtin_amdgcn_raw_buffer_load_b128(b, lane_at, at, ONCE ? 2 : 0);
+}
+
+template <int NT, int COLS, typename Epi, bool CUT>
+__global__ void __launch_bounds__(64 * TD_WAVES, 1)
 mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__ wdown,
               const RowDesc *__restrict__ rows, int m_rows, ProjIn in, int n_in, int n_tasks, int n_groups,
               int chunks_per_split, float *__restrict__ part, int m_pitch) {
-  constexpr int STEPS = MG_KC / 16, RING = td_ring(NT);
+  static_assert(COLS == 16 || COLS == OP_ROWS, "one or two operands of 16 activation rows");
+  constexpr int CG = COLS / 16, KS = 32, STEPS = MG_KC / KS, RING = td_ring(NT), THREADS = 64 * TD_WAVES;
   extern __shared__ uint4 td_smem[];
-  float *s_t = (float *)td_smem;                         // [4 waves][NT][32 operand rows][33]
-  int *s_exp = (int *)(s_t + (TD_WAVES / 2) * NT * 32 * 33);
-  float *s_wdown = (float *)(s_exp + OP_ROWS);           // [NT][32 operand rows]
+  float *s_t = (float *)td_smem;                             // [waves][NT][COLS][TD_PITCH]
+  float *s_wdown = s_t + TD_WAVES * NT * COLS * TD_PITCH;    // [NT][32 operand rows]
+  int *s_exp = (int *)(s_wdown + NT * 32);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 15, kq = lane >> 4;   // operand row / column, and which eight of the step's 32 k
   clear_words(in);
   const int split = CUT ? blockIdx.x / n_groups : 0, group = blockIdx.x - split * n_groups;
   const int n_chunks = (n_in + MG_KC - 1) / MG_KC, n_blocks = (n_tasks + TG_TASKS - 1) / TG_TASKS;
@@ -1150,138 +1173,155 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
   const int per_wave = ((c_end - c_begin) * STEPS + TD_WAVES - 1) / TD_WAVES;
   const int s_begin = min(c_begin * STEPS + wave * per_wave, c_end * STEPS), s_end = min(s_begin + per_wave, c_end * STEPS);
   const int s_last = max(s_end - 1, 0);   // steps past the end read this one and are multiplied with zeros
-  const f16_t *a[NT];
-#pragma unroll
-  for (int q = 0; q < NT; ++q) a[q] = tiled + (size_t)min(group * NT + q, n_blocks - 1) * n_chunks * TG_TILE + lane * 8;
-  u32x4_t wr[RING][NT];
-  float4 xr[RING][2];
+  const size_t tile_bytes = sizeof(f16_t) * TG_TILE, first = (size_t)group * NT * n_chunks;
+  const buffer_t w_buf = buffer_of(tiled + first * TG_TILE, ((size_t)n_blocks * n_chunks - first) * tile_bytes);
+  const buffer_t x_buf = buffer_of(in.x, sizeof(float) * OP_ROWS * (size_t)n_in);
+  // of a tile's chunk: operand rows 16 h + col, elements 32 step + 8 kq .. + 7
+  const int w_at = (int)sizeof(f16_t) * ((kq >> 1) * 512 + (col + 32 * (kq & 1)) * 8);
+  u32x4_t wr[RING][NT][2], xr[RING][CG][2];
   auto load_w = [&](int u, int step) {
-    const size_t o = (size_t)min(step, s_last) * 512;
+    const int at = min(step, s_last) * (32 * KS * (int)sizeof(f16_t));
 #pragma unroll
-    for (int q = 0; q < NT; ++q) wr[u][q] = __builtin_nontemporal_load((const u32x4_t *)(a[q] + o));
+    for (int q = 0; q < NT; ++q)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) wr[u][q][h] = load_buffer16<true>(w_buf, w_at + h * 256, at + q * n_chunks * (int)tile_bytes);
   };
-  // columns past the last row repeat it; beyond n_in the weights are zero and any activation will do
-  const int x_row = min(lane & 31, m_rows - 1) * 4;
-  const int x_off = (lane >> 5) * (2 * 4 * OP_ROWS) + x_row, x_most = (n_in / 4 - 2) * (4 * OP_ROWS) + x_row;
+  int x_at[CG];   // (columns past the last row repeat it)
+#pragma unroll
+  for (int g = 0; g < CG; ++g) x_at[g] = (2 * kq * OP_ROWS + min(16 * g + col, m_rows - 1)) * 16;
   auto load_x = [&](int u, int step) {
-    const float *p = in.x + min(min(step, s_last) * (4 * 4 * OP_ROWS) + x_off, x_most);
-    xr[u][0] = *(const float4 *)p;
-    xr[u][1] = *(const float4 *)(p + 4 * OP_ROWS);
+    const int at = min(step, s_last) * (KS * OP_ROWS * (int)sizeof(float));
+#pragma unroll
+    for (int g = 0; g < CG; ++g)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) xr[u][g][i] = load_buffer16<false>(x_buf, x_at[g] + i * OP_ROWS * 16, at);
   };
-  RowExponent<16> mag(in.row_max, min((int)threadIdx.x >> 4, m_rows - 1), threadIdx.x & 15);
+  // (finishing, a thread has task t of every tile and the rows m0 + 16 g)
+  const int t = threadIdx.x & (TG_TASKS - 1), m0 = threadIdx.x >> 4;
+  RowDesc rd[CG];
+#pragma unroll
+  for (int g = 0; g < CG; ++g) rd[g] = rows[min(m0 + 16 * g, m_rows - 1)];
+  constexpr int LPR = THREADS / COLS;
+  RowExponent<LPR> mag(in.row_max, min((int)threadIdx.x / LPR, m_rows - 1), threadIdx.x & (LPR - 1));
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int u = 0; u < RING; ++u) { load_w(u, s_begin + u); load_x(u, s_begin + u); }
   __builtin_amdgcn_sched_barrier(0);
-  static_assert(NT * 32 <= 64 * TD_WAVES, "a thread fetches one weight row's scale at most");
+  static_assert(NT * 32 <= THREADS, "a thread fetches one weight row's scale at most");
   const int wd_row = min((int)threadIdx.x, NT * 32 - 1);   // (needed last, and from far away)
   const float wd = wdown[(size_t)min(group * NT + wd_row / 32, n_blocks - 1) * 32 + wd_row % 32];
   __builtin_amdgcn_sched_barrier(0);
   {
     const int e = mag.get();
-    if ((threadIdx.x & 15) == 0) s_exp[threadIdx.x >> 4] = scale_exponent(e);
+    if ((threadIdx.x & (LPR - 1)) == 0) s_exp[threadIdx.x / LPR] = scale_exponent(e);
   }
   __syncthreads();
-  const int E = s_exp[lane & 31];
-  const float x_up = scale_up(E);
+  float x_up[CG];
+#pragma unroll
+  for (int g = 0; g < CG; ++g) x_up[g] = scale_up(s_exp[16 * g + col]);
 
-  f32x16_t acc[NT];
+  f32x4_t acc[NT][CG][2];
 #pragma unroll
   for (int q = 0; q < NT; ++q)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[q][r] = 0.f;
+    for (int g = 0; g < CG; ++g)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) acc[q][g][h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   for (int s0 = s_begin; s0 < s_end; s0 += RING) {
 #pragma unroll
     for (int u = 0; u < RING; ++u) {
       const int step = s0 + u;
-      const float up = step < s_end ? x_up : 0.f;
-      const float4 v0 = xr[u][0], v1 = xr[u][1];
-      const float f[8] = {v0.x * up, v0.y * up, v0.z * up, v0.w * up, v1.x * up, v1.y * up, v1.z * up, v1.w * up};
-      f16x8_t h, l;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        h[e] = (f16_t)f[e];
-        l[e] = (f16_t)(f[e] - (float)h[e]);
+      for (int g = 0; g < CG; ++g) {
+        const float up = step < s_end ? x_up[g] : 0.f;
+        f16x8_t hi, lo;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float f = __uint_as_float(xr[u][g][e >> 2][e & 3]);
+          hi[e] = (f16_t)(f * up);
+          lo[e] = (f16_t)__builtin_fmaf(f, up, -(float)hi[e]);   // (up is a power of two: the product is exact)
+        }
+#pragma unroll
+        for (int q = 0; q < NT; ++q)
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            acc[q][g][h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, wr[u][q][h]), lo, acc[q][g][h], 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < NT; ++q)
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            acc[q][g][h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, wr[u][q][h]), hi, acc[q][g][h], 0, 0, 0);
       }
-#pragma unroll
-      for (int q = 0; q < NT; ++q)
-        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, wr[u][q]), l, acc[q], 0, 0, 0);
-#pragma unroll
-      for (int q = 0; q < NT; ++q)
-        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, wr[u][q]), h, acc[q], 0, 0, 0);
       load_w(u, step + RING);
       load_x(u, step + RING);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
 
+  // the waves' sums, [activation row][weight row]: a lane has four neighbouring weight rows of one activation row
   if (threadIdx.x < NT * 32) s_wdown[threadIdx.x] = wd;
-  // the waves' sums: the upper four hand theirs to the lower four, those leave four to be added up
-  // by the thread that finishes a pair (always in the same order)
-  auto at = [&](int w, int q, int r) { return ((w * NT + q) * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * 33 + (lane & 31); };
-  if (wave >= TD_WAVES / 2) {
 #pragma unroll
-    for (int q = 0; q < NT; ++q)
+  for (int q = 0; q < NT; ++q)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s_t[at(wave - TD_WAVES / 2, q, r)] = acc[q][r];
-  }
+    for (int g = 0; g < CG; ++g)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        *(f32x4_t *)(s_t + ((wave * NT + q) * COLS + 16 * g + col) * TD_PITCH + 16 * h + 4 * kq) = acc[q][g][h];
   __syncthreads();
-  if (wave < TD_WAVES / 2) {
-    const float down = scale_down(E);
+  // the sum of an operand row, always in the order of the waves, without its scales
+  // (one factor after the other: their product may lie outside the range of an fp32 where the result does not)
+  auto sum = [&](int q, int row, int m, float x_down) {
+    float y = s_t[(q * COLS + m) * TD_PITCH + row];
 #pragma unroll
-    for (int q = 0; q < NT; ++q) {
-      const float4 *w4 = (const float4 *)(s_wdown + q * 32 + 4 * (lane >> 5));
-      float w[16];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) *(float4 *)(w + 4 * j) = w4[2 * j];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s_t[at(wave, q, r)] = (acc[q][r] + s_t[at(wave, q, r)]) * down * w[r];
-    }
-  }
-  __syncthreads();
-  auto sum = [&](int q, int row, int m) {
-    float y = s_t[(q * 32 + row) * 33 + m];
-#pragma unroll
-    for (int w = 1; w < TD_WAVES / 2; ++w) y += s_t[((w * NT + q) * 32 + row) * 33 + m];
-    return y;
+    for (int w = 1; w < TD_WAVES; ++w) y += s_t[((w * NT + q) * COLS + m) * TD_PITCH + row];
+    return y * x_down * s_wdown[q * 32 + row];
   };
   if constexpr (CUT) {
     // rows fastest across the lanes, as the finishing launch reads them
     float *base = part + (size_t)blockIdx.x * (TG_TASKS * NT) * 2 * m_pitch;
-    const int m = threadIdx.x & 31, t = threadIdx.x >> 5;   // 16 tasks
+    const int m = threadIdx.x % COLS;
+    const float x_down = scale_down(s_exp[m]);
     if (m < m_pitch) {
 #pragma unroll
-      for (int q = 0; q < NT; ++q) {
-        float *p = base + (size_t)(q * TG_TASKS + t) * 2 * m_pitch + m;
-        p[0] = sum(q, t, m);
-        p[m_pitch] = sum(q, TG_TASKS + t, m);
+      for (int i = threadIdx.x / COLS; i < NT * TG_TASKS; i += THREADS / COLS) {
+        const int q = i / TG_TASKS, r = i % TG_TASKS;
+        float *p = base + (size_t)i * 2 * m_pitch + m;
+        p[0] = sum(q, r, m, x_down);
+        p[m_pitch] = sum(q, TG_TASKS + r, m, x_down);
       }
     }
   } else {
     // tasks fastest: 16 lanes finish a row's tasks of one tile after the other
-    const int t = threadIdx.x & (TG_TASKS - 1), m = threadIdx.x >> 4;
-    const bool row_live = m < m_rows;
-    const RowDesc rd = rows[row_live ? m : m_rows - 1];
-    typename Epi::State st;
-    epi.init(st);
 #pragma unroll
-    for (int q = 0; q < NT; ++q) {
-      const int task = (group * NT + q) * TG_TASKS + t;
-      const bool live = row_live && task < n_tasks;
-      const auto old = load_old(epi, live ? task : 0, row_live ? m : m_rows - 1, rd, true);
-      if (live) finish_pair(epi, task, m, rd, sum(q, t, m), sum(q, TG_TASKS + t, m), old, st);
-    }
-    if constexpr (EpiHasLocalReduce<Epi>::value) {
-      // the heads' arg-max: one atomic per row and workgroup
+    for (int g = 0; g < CG; ++g) {
+      const int m = m0 + 16 * g;
+      const bool row_live = m < m_rows;
+      const float x_down = scale_down(s_exp[m]);
+      typename Epi::State st;
+      epi.init(st);
+      decltype(load_old(epi, 0, 0, rd[0], true)) old[NT];   // (requested together: the stores between them would hold them back)
 #pragma unroll
-      for (int o = TG_TASKS / 2; o > 0; o >>= 1) {
-        const unsigned long long other =
-            ((unsigned long long)(uint32_t)__shfl_xor((int)(st.best >> 32), o, 64) << 32) | (uint32_t)__shfl_xor((int)st.best, o, 64);
-        if (other > st.best) st.best = other;
+      for (int q = 0; q < NT; ++q) {
+        const int task = (group * NT + q) * TG_TASKS + t;
+        old[q] = load_old(epi, row_live && task < n_tasks ? task : 0, min(m, m_rows - 1), rd[g], true);
       }
-      if (t == 0 && row_live) epi.end_reduced(rd, st.best);
-    } else {
-      hand_on_row<TG_TASKS>(epi, m, row_live, st, group);
+#pragma unroll
+      for (int q = 0; q < NT; ++q) {
+        const int task = (group * NT + q) * TG_TASKS + t;
+        if (row_live && task < n_tasks) finish_pair(epi, task, m, rd[g], sum(q, t, m, x_down), sum(q, TG_TASKS + t, m, x_down), old[q], st);
+      }
+      if constexpr (EpiHasLocalReduce<Epi>::value) {
+        // the heads' arg-max: one atomic per row and workgroup
+#pragma unroll
+        for (int o = TG_TASKS / 2; o > 0; o >>= 1) {
+          const unsigned long long other =
+              ((unsigned long long)(uint32_t)__shfl_xor((int)(st.best >> 32), o, 64) << 32) | (uint32_t)__shfl_xor((int)st.best, o, 64);
+          if (other > st.best) st.best = other;
+        }
+        if (t == 0 && row_live) epi.end_reduced(rd[g], st.best);
+      } else {
+        hand_on_row<TG_TASKS>(epi, m, row_live, st, group);
+      }
     }
   }
 }

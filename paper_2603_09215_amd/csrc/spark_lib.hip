@@ -681,11 +681,11 @@ int launch_tiled_rows(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, 
 }
 
 // the same for at most 32 rows, in operand order
-template <int NT, bool CUT, typename Epi>
-int launch_direct_tiles(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,
-                        const TiledMatrix &w, int groups, int split, int cps) {
-  auto kern = mfma_direct_k<NT, Epi, CUT>;
-  const size_t lds = td_lds_bytes(NT);
+template <int NT, int COLS, bool CUT, typename Epi>
+int launch_direct_cols(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,
+                       const TiledMatrix &w, int groups, int split, int cps) {
+  auto kern = mfma_direct_k<NT, COLS, Epi, CUT>;
+  const size_t lds = td_lds_bytes(NT, COLS);
   if (lds > 65536) {
     const auto key = std::make_pair((const void *)kern, lds);
     if (c->occ_cache.find(key) == c->occ_cache.end()) {
@@ -698,6 +698,12 @@ int launch_direct_tiles(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m
                                                           (int)align_up(m, 8));
   HIP_TRY(c, hipGetLastError());
   return SPARK_OK;
+}
+template <int NT, bool CUT, typename Epi>
+int launch_direct_tiles(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,
+                        const TiledMatrix &w, int groups, int split, int cps) {
+  return m <= 16 ? launch_direct_cols<NT, 16, CUT>(c, epi, rows, m, n_in, n_tasks, in, w, groups, split, cps)
+                 : launch_direct_cols<NT, OP_ROWS, CUT>(c, epi, rows, m, n_in, n_tasks, in, w, groups, split, cps);
 }
 template <typename Epi>
 int launch_direct(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,
@@ -719,14 +725,7 @@ int launch_direct(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int 
       }
     }
   }
-  // tiles per workgroup: as few rounds of CUs as five tiles make, and the last one full
-  int nt = 1;
-  double best = 0.0;
-  for (int n = 1; n <= 5; ++n) {
-    const int groups = (blocks + n - 1) / n, rounds = (groups + c->n_cu - 1) / c->n_cu;
-    const double cost = (double)rounds * n;      // tiles the busiest CU takes
-    if (n == 1 || cost <= best) { best = cost; nt = n; }
-  }
+  const int nt = direct_tiles(m, blocks, c->n_cu, EpiHasLocalReduce<Epi>::value);
   const int groups = (blocks + nt - 1) / nt;
   if (max_words) *max_words = groups;
   switch (nt) {
@@ -900,7 +899,7 @@ int run_layers_mfma(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
   // the layer before, added to next by o), those of the layer's input by gate/up (read last by
   // q/k/v, added to next by down).
   unsigned long long *ssq_in = c->pb.ssq, *ssq_mlp = ssq_in + (size_t)SSQ_WAYS * c->pb.rows;
-  const int ssq_units = m * SSQ_WAYS * (int)sizeof(unsigned long long) / 16;
+  const int ssq_pitch = std::min((int)align_up(m, 16), c->pb.rows), ssq_units = ssq_pitch * SSQ_WAYS * (int)sizeof(unsigned long long) / 16;
   // (the counts: what the launch that wrote the lists last has written)
   RowMax max_x = row_max_list(c, c->pb.max_x, max_x_bytes(g), 1), max_attn = row_max_list(c, c->pb.max_attn, max_attn_bytes(g), 0),
          max_act = row_max_list(c, c->pb.max_act, max_act_bytes(g), 0);
@@ -917,7 +916,7 @@ int run_layers_mfma(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
     eq.qbuf = c->pb.q;
     eq.rope = at<float2>(c, c->lo.rope);
     eq.kv = kv_view(c);
-    if (qkv_scaled) eq.scale = RowScale{ssq_in, 1.0f / (float)d, g.rms_eps};
+    if (qkv_scaled) eq.scale = RowScale{ssq_in, ssq_pitch, 1.0f / (float)d, g.rms_eps};
     ProjIn in = prepared(c, m, qkv_scaled ? max_x.n : 1);
     in.zero = (uint4 *)ssq_mlp;
     in.n_zero = ssq_units;
@@ -930,9 +929,9 @@ int run_layers_mfma(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
                         d, F, act, max_act};
     if (fuse) {
       EpiResidualNorm<WT, SPLIT> eo{(const WT *)c->w.wo + (size_t)l * d * qw, (int)qw, d, hidden, d,
-                             c->w.mlp_norm + (size_t)l * d, xnorm, ssq_mlp, max_x};
+                             c->w.mlp_norm + (size_t)l * d, xnorm, ssq_mlp, ssq_pitch, max_x};
       if ((rc = launch_mfma(c, eo, rows, m, (int)qw, d / 2, in_o, SPARK_KC_OPROJ, tiled_at(c, c->tm.o[l]), &max_x.n))) return rc;
-      eg.scale = RowScale{ssq_mlp, 1.0f / (float)d, g.rms_eps};
+      eg.scale = RowScale{ssq_mlp, ssq_pitch, 1.0f / (float)d, g.rms_eps};
       in = prepared(c, m, max_x.n);
       in.zero = (uint4 *)ssq_in;
       in.n_zero = ssq_units;
@@ -948,7 +947,7 @@ int run_layers_mfma(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
     const ProjIn in_d = proj_in(act, max_act);
     if (fuse && l + 1 < l1) {
       EpiResidualNorm<WT, SPLIT> ed{(const WT *)c->w.wd + (size_t)l * d * F, F, d, hidden, d,
-                             c->w.attn_norm + (size_t)(l + 1) * d, xnorm, ssq_in, max_x};
+                             c->w.attn_norm + (size_t)(l + 1) * d, xnorm, ssq_in, ssq_pitch, max_x};
       if ((rc = launch_mfma(c, ed, rows, m, F, d / 2, in_d, SPARK_KC_DOWN, tiled_at(c, c->tm.down[l]), &max_x.n))) return rc;
     } else {
       EpiResidual<WT> ed{(const WT *)c->w.wd + (size_t)l * d * F, F, d, hidden, d};
