@@ -1138,6 +1138,12 @@ mfma_finish_tile_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, int n_
 // what lies past the end of a matrix or of the activations comes back as zeros.
 constexpr int TD_WAVES = 4;
 constexpr int td_ring(int nt) { return nt == 1 ? 4 : 2; }
+// Every MFMA rounds its running sums to 32 bits, and a quarter of k in one chain leaves 2.8e-7 of the heads'
+// logits (k 3584, against 64 bits): the sums of a few steps are added to a second set and begin at zero again,
+// and where there are registers for it the activations' lower parts have sums of their own.  1.3e-7 without
+// the latter, 1.2e-7 with them (vector kernel: 1.1e-7); MLP blocks 2.6e-7 and 2.3e-7 (vector kernels 2.5e-7).
+constexpr bool td_fine(int nt, int cols) { return nt * cols <= 32; }   // (what the registers of four waves a SIMD allow)
+constexpr int td_fold_steps(int nt, int cols) { return td_fine(nt, cols) ? 2 : 4; }   // steps of 32 k whose products go into one set of sums
 constexpr int TD_PITCH = 36;   // floats of LDS per (tile, activation row): 32 weight rows and a skew of one 16-byte word
 constexpr size_t td_lds_bytes(int nt, int cols) { return sizeof(float) * (TD_WAVES * nt * cols * TD_PITCH + nt * 32 + OP_ROWS); }
 
@@ -1220,17 +1226,27 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
 #pragma unroll
   for (int g = 0; g < CG; ++g) x_up[g] = scale_up(s_exp[16 * g + col]);
 
-  f32x4_t acc[NT][CG][2];
+  const f32x4_t none = {0.f, 0.f, 0.f, 0.f};
+  constexpr bool FINE = td_fine(NT, COLS);
+  constexpr int FOLD = td_fold_steps(NT, COLS), TURN = RING > FOLD ? RING : FOLD;
+  static_assert(TURN % RING == 0 && TURN % FOLD == 0, "whole turns of the ring, whole sets of sums");
+  f32x4_t acc[NT][CG][2], folded[NT][CG][2], small[FINE ? NT : 1][CG][2];   // small: of the lower parts, if kept apart
 #pragma unroll
   for (int q = 0; q < NT; ++q)
 #pragma unroll
     for (int g = 0; g < CG; ++g)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) acc[q][g][h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  for (int s0 = s_begin; s0 < s_end; s0 += RING) {
+      for (int h = 0; h < 2; ++h) {
+        folded[q][g][h] = none;
+        if constexpr (FINE) small[q][g][h] = none;
+      }
+  auto mm = [](const u32x4_t &w, const f16x8_t &x, const f32x4_t &c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, w), x, c, 0, 0, 0);
+  };
+  for (int s0 = s_begin; s0 < s_end; s0 += TURN) {
 #pragma unroll
-    for (int u = 0; u < RING; ++u) {
-      const int step = s0 + u;
+    for (int i = 0; i < TURN; ++i) {
+      const int step = s0 + i, u = i % RING;
 #pragma unroll
       for (int g = 0; g < CG; ++g) {
         const float up = step < s_end ? x_up[g] : 0.f;
@@ -1244,18 +1260,35 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
 #pragma unroll
         for (int q = 0; q < NT; ++q)
 #pragma unroll
-          for (int h = 0; h < 2; ++h)
-            acc[q][g][h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, wr[u][q][h]), lo, acc[q][g][h], 0, 0, 0);
+          for (int h = 0; h < 2; ++h) {
+            if constexpr (FINE) small[q][g][h] = mm(wr[u][q][h], lo, small[q][g][h]);
+            else acc[q][g][h] = mm(wr[u][q][h], lo, i % FOLD == 0 ? none : acc[q][g][h]);
+          }
 #pragma unroll
         for (int q = 0; q < NT; ++q)
 #pragma unroll
-          for (int h = 0; h < 2; ++h)
-            acc[q][g][h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, wr[u][q][h]), hi, acc[q][g][h], 0, 0, 0);
+          for (int h = 0; h < 2; ++h) acc[q][g][h] = mm(wr[u][q][h], hi, FINE && i % FOLD == 0 ? none : acc[q][g][h]);
       }
       load_w(u, step + RING);
       load_x(u, step + RING);
+      if (i % FOLD == FOLD - 1) {
+#pragma unroll
+        for (int q = 0; q < NT; ++q)
+#pragma unroll
+          for (int g = 0; g < CG; ++g)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) folded[q][g][h] += acc[q][g][h];
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
+  }
+  if constexpr (FINE) {
+#pragma unroll
+    for (int q = 0; q < NT; ++q)
+#pragma unroll
+      for (int g = 0; g < CG; ++g)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) folded[q][g][h] += small[q][g][h];
   }
 
   // the waves' sums, [activation row][weight row]: a lane has four neighbouring weight rows of one activation row
@@ -1266,7 +1299,7 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
     for (int g = 0; g < CG; ++g)
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        *(f32x4_t *)(s_t + ((wave * NT + q) * COLS + 16 * g + col) * TD_PITCH + 16 * h + 4 * kq) = acc[q][g][h];
+        *(f32x4_t *)(s_t + ((wave * NT + q) * COLS + 16 * g + col) * TD_PITCH + 16 * h + 4 * kq) = folded[q][g][h];
   __syncthreads();
   // the sum of an operand row, always in the order of the waves, without its scales
   // (one factor after the other: their product may lie outside the range of an fp32 where the result does not)
