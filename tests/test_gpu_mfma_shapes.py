@@ -77,6 +77,19 @@ def test_projection_kernels_by_their_switches(sb, B, tune):
     sp.close()
 
 
+@pytest.mark.parametrize("B", [3, 4, 8, 9, 16, 17, 31, 32])
+def test_rows_at_the_edges_of_the_direct_kernels(sb, B):
+    """one operand of 16 activation rows or two, one tile a workgroup (up to 8 rows) or a round of CUs;
+    inputs of 1032 and 1304, no multiples of a chunk; three and four rows: layers on the MFMA kernels,
+    heads on the vector kernel"""
+    say(f"case direct kernels, {B} rows")
+    weights = wl.make_weights(LONG_K, seed=18, gain_std=0.1)
+    prompts = [wl.make_prompt(LONG_K, 1 + i % 3, seed=80 + i) for i in range(B)]
+    sp = sb.Spark(LONG_K, wl.TINY.schedule, weights, max_batch=B, max_seq_len=64, kv_page_tokens=16)
+    compare_run(sp, LONG_K, wl.TINY.schedule, weights, prompts, [0] * B, 6, label=f"{B} rows")
+    sp.close()
+
+
 def test_flush_of_more_rows_than_a_pass_takes(sb):
     """256 sequences with fifteen pending positions each complete them on the same step: 4096 rows, which
     go through the upper layers in two pieces (3072 at this width); the sequences' logits are those that
