@@ -89,6 +89,97 @@ constexpr size_t tiled_partial_bytes(const TileCover &tc, int tb) {
   return tc.n_cut ? tc.n_split * range_bytes(tc.n_cut, 32 * TG_WAVES * tb, tc.m_pitch) : 0;
 }
 
+// Whole tiles of three and of two blocks of 32 rows, so that the CUs get about as many blocks each: the first
+// task tiles are covered by part[0].n_row_tiles high and part[2].n_row_tiles low ones, the others by part[1] and
+// part[3].  (74 task tiles of 16 blocks of rows, 4.6 blocks for each of 256 CUs: tiles of three alone are two rounds,
+// six blocks; 236 of three and 238 of two are one of each, five.)
+struct MixedCover {
+  TileCover part[4];
+  float cost;   // microseconds, see mixed_tile_cost
+  int tiles() const {
+    int n = 0;
+    for (const TileCover &p : part) n += p.n_task_tiles * p.n_row_tiles;
+    return n;
+  }
+};
+
+// Microseconds of a whole tile of 256 tasks with `blocks` blocks of rows: 2.45 and 1.75 per chunk with three and
+// two, all CUs busy, and its start and epilogue
+inline float wide_tile_cost(int blocks, int n_chunks) { return n_chunks * (0.35f + 0.7f * blocks) + 4.f + 3.f * blocks; }
+
+// Time until n_cu CUs have taken n_high jobs of one length and then n_low of a shorter one, each as it becomes free
+inline float two_lengths_makespan(int n_high, float high, int n_low, float low, int n_cu) {
+  struct Group { float t; int n; } g[64];
+  int groups = 1;
+  g[0] = Group{0.f, n_cu};
+  float end = 0.f;
+  while (n_high + n_low > 0) {
+    int k = 0;
+    for (int i = 1; i < groups; ++i)
+      if (g[i].t < g[k].t) k = i;
+    const bool is_high = n_high > 0;
+    int &left = is_high ? n_high : n_low;
+    const int n = left < g[k].n ? left : g[k].n;
+    const float t = g[k].t + (is_high ? high : low);
+    left -= n;
+    if (t > end) end = t;
+    g[k].n -= n;
+    if (g[k].n == 0) g[k] = g[--groups];
+    int same = -1;
+    for (int i = 0; i < groups; ++i)
+      if (g[i].t == t) same = i;
+    if (same >= 0) g[same].n += n;
+    else if (groups < 64) g[groups++] = Group{t, n};
+    else return 1e30f;
+  }
+  return end;
+}
+
+inline TileCover whole_part(int n_task_tiles, int n_row_tiles) {
+  TileCover tc;
+  tc.n_task_tiles = n_task_tiles;
+  tc.n_row_tiles = n_row_tiles;
+  tc.n_whole = n_task_tiles * n_row_tiles;
+  tc.n_cut = 0;
+  tc.n_split = 1;
+  tc.chunks_per_split = tc.m_pitch = 0;
+  tc.max_words = 1;
+  tc.xcd_groups = n_row_tiles > 1;
+  return tc;
+}
+
+// The best such cover of m rows by tiles of 256 tasks: x task tiles with a high and b low tiles, the others with
+// two high ones less and three low ones more (as many blocks)
+inline MixedCover cover_mixed(int m, int n_in, int n_tasks, int n_cu) {
+  const int T = ceil_div(n_tasks, 64 * TG_WAVES), blocks = ceil_div(m, 32), n_chunks = ceil_div(n_in, MG_KC);
+  const float high = wide_tile_cost(3, n_chunks), low = wide_tile_cost(2, n_chunks);
+  float best = 1e30f;
+  int best_a = 0, best_b = 0, best_x = T;
+  for (int total = blocks; total <= blocks + 1; ++total)
+    for (int a = 0; 3 * a <= total; ++a) {
+      if ((total - 3 * a) % 2) continue;
+      const int b = (total - 3 * a) / 2;
+      for (int x = a >= 2 ? 1 : T; x <= T; ++x) {
+        const int n_high = x * a + (T - x) * (a - 2), n_low = x * b + (T - x) * (b + 3);
+        const float t = two_lengths_makespan(n_high, high, n_low, low, n_cu);
+        if (t < best) { best = t; best_a = a; best_b = b; best_x = x; }
+      }
+    }
+  const int rest = T - best_x;
+  MixedCover mc{{whole_part(best_x, best_a), whole_part(rest, rest ? best_a - 2 : 0), whole_part(best_x, best_b), whole_part(rest, rest ? best_b + 3 : 0)}, best};
+  return mc;
+}
+
+// The same estimate for tiles of equal height, the last round cut over k and summed by a finishing launch
+inline float tiled_cost(const TileCover &tc, int n_in, int mtiles, int n_cu) {
+  const int n_chunks = ceil_div(n_in, MG_KC);
+  float t = ceil_div(tc.n_whole, n_cu) * wide_tile_cost(mtiles, n_chunks);
+  if (tc.n_cut)
+    t += ceil_div(tc.n_cut * tc.n_split, n_cu) * wide_tile_cost(mtiles, tc.chunks_per_split) + 5.f +
+         2.f * (float)(tc.n_split * range_bytes(tc.n_cut, 64 * TG_WAVES, tc.m_pitch)) / 5e6f;
+  return t;
+}
+
 // Blocks of 32 rows in a row tile of a projection with 32 tasks a wave and more rows than one tile
 // takes: such a launch is one to three rounds of CUs, and what the last of them leaves idle differs
 // more between the heights than the heights themselves do.  The time of a cover is taken as that of

@@ -201,6 +201,14 @@ struct RowScale {
   }
 };
 
+// What a tile's epilogue needs of an activation row, found once per workgroup
+struct RowFacts {
+  unsigned long long at;   // of the row's cache entries of the layer: element of its first key head
+  int pos;
+  float inv;               // 1 / rms
+};
+template <typename E> struct EpiFacts { static constexpr bool value = false; };   // epilogues that take them
+
 // q, k, v projection + rotary embedding + KV-cache write.  Task t -> head t / (hd/2), pair index
 // i = t % (hd/2): weight rows (head*hd + i) and (head*hd + i + hd/2), the two elements that the
 // rotary embedding mixes.  Heads [0,nq) are queries, [nq,nq+nkv) keys, the rest values.
@@ -255,7 +263,45 @@ template <typename WT, bool DS = false> struct EpiQKV {
     finish_old(task, r, rd, y0, y1, load_old(task, r, rd), s);
   }
   __device__ void end(int, const RowDesc &, State &) const {}
+  // the same for four neighbouring tasks (a multiple of four: all of one head) and a row whose facts are known
+  __device__ RowFacts row_facts(int r, const RowDesc &rd) const {
+    return RowFacts{kv_elem_offset(kv, rd.seq, rd.pos, layer, 0, 0), rd.pos, scale.of(r)};
+  }
+  struct Turn { float4 a, b; };   // cosine and sine of four tasks
+  __device__ Turn load_turn(int task, const RowFacts &f) const {
+    const int half = hd >> 1, head = task / half, i = task - head * half;
+    Turn t{make_float4(1.f, 0.f, 1.f, 0.f), make_float4(1.f, 0.f, 1.f, 0.f)};
+    if (head < nq + nkv) {
+      const float4 *p = (const float4 *)(rope + (size_t)f.pos * half + i);
+      t.a = p[0];
+      t.b = p[1];
+    }
+    return t;
+  }
+  __device__ void finish4(int task, int r, const RowFacts &f, const float4 &y0, const float4 &y1, const Turn &t) const {
+    const int half = hd >> 1, head = task / half, i = task - head * half;
+    float a[4] = {y0.x, y0.y, y0.z, y0.w}, b[4] = {y1.x, y1.y, y1.z, y1.w};
+    const float cs[8] = {t.a.x, t.a.y, t.a.z, t.a.w, t.b.x, t.b.y, t.b.z, t.b.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (scale.ssq) { a[e] *= f.inv; b[e] *= f.inv; }
+      if (head < nq + nkv) {
+        const float u = a[e] * cs[2 * e] - b[e] * cs[2 * e + 1], v = b[e] * cs[2 * e] + a[e] * cs[2 * e + 1];
+        a[e] = u; b[e] = v;
+      }
+    }
+    if (head < nq) {
+      float *q = qbuf + ((size_t)r * nq + head) * hd + i;
+      *(float4 *)q = make_float4(a[0], a[1], a[2], a[3]);
+      *(float4 *)(q + half) = make_float4(b[0], b[1], b[2], b[3]);
+    } else {   // key heads, then value heads, page_tokens apart
+      bf16_t *dst = (bf16_t *)kv.pool + f.at + (size_t)(head - nq) * kv.page_tokens * hd + i;
+      *(uint2 *)dst = make_uint2(f32_to_bf16(a[0]) | ((uint32_t)f32_to_bf16(a[1]) << 16), f32_to_bf16(a[2]) | ((uint32_t)f32_to_bf16(a[3]) << 16));
+      *(uint2 *)(dst + half) = make_uint2(f32_to_bf16(b[0]) | ((uint32_t)f32_to_bf16(b[1]) << 16), f32_to_bf16(b[2]) | ((uint32_t)f32_to_bf16(b[3]) << 16));
+    }
+  }
 };
+template <> struct EpiFacts<EpiQKV<bf16_t>> { static constexpr bool value = true; };
 
 // hidden[x_slot][i] += y  (attention output projection, MLP down projection)
 template <typename WT, bool DS = false> struct EpiResidual {
@@ -381,6 +427,9 @@ template <typename WT, bool SPLIT = false> struct EpiSwiGLUMax {
   }
   // value(row_scale(r), y0, y1) is what store_value puts into the row
   __device__ float row_scale(int r) const { return scale.of(r); }
+  __device__ RowFacts row_facts(int r, const RowDesc &) const { return RowFacts{0ull, 0, scale.of(r)}; }
+  // of four neighbouring tasks, for a row that lies in memory as a row
+  __device__ void store_values(int task, int r, const float4 &v) const { *(float4 *)(act.p + (size_t)r * act.stride + task) = v; }
   __device__ float value(float inv, float y0, float y1) const {
     y0 *= inv; y1 *= inv;
     return y0 / (1.0f + expf(-y0)) * y1;
@@ -402,6 +451,7 @@ template <typename WT, bool SPLIT = false> struct EpiSwiGLUMax {
   __device__ void put_row(int r, int block, const State &s) const { row_max.put(r, block, s.amax); }
   __device__ void end(int, const RowDesc &, State &) const {}
 };
+template <typename WT> struct EpiFacts<EpiSwiGLUMax<WT, false>> { static constexpr bool value = true; };
 template <typename WT, bool SPLIT> struct EpiReadsOld<EpiSwiGLUMax<WT, SPLIT>> { static constexpr bool value = true; };
 template <typename WT, bool SPLIT> struct EpiRow<EpiSwiGLUMax<WT, SPLIT>> { static constexpr bool sum = false, max = !SPLIT; };
 template <typename WT, bool SPLIT> struct EpiOutParts<EpiSwiGLUMax<WT, SPLIT>> { static constexpr int value = SPLIT; };

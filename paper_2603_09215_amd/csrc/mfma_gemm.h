@@ -558,16 +558,18 @@ __device__ __forceinline__ void tile_place(const TileCover &tc, int t, int &bx, 
 
 // dynamic LDS of mfma_tiled_k: three buffers of two parts of 32*MTILES padded activation rows, or
 // the four waves' pieces for turning the result tiles, whichever is larger; the activation rows' scales and
-// arg-max keys, the weight rows' scales
+// arg-max keys, the weight rows' scales, what the epilogue needs of the rows
 constexpr int TG_BUFS = 3;
+constexpr int TG_TPITCH = 36;   // floats of a row of a turned tile: 32 tasks and a skew of one 16-byte word
 constexpr size_t tg_scales_at(int mtiles) {
   const size_t x = sizeof(f16_t) * TG_BUFS * TG_PARTS * 32 * mtiles * MG_ROWPAD;
-  const size_t t = sizeof(float) * TG_WAVES * 2 * 32 * 33;
+  const size_t t = sizeof(float) * TG_WAVES * 2 * 32 * TG_TPITCH;
   return x > t ? x : t;
 }
-constexpr size_t tg_lds_bytes(int mtiles, int tb) {
+constexpr size_t tg_rows_at(int mtiles, int tb) {
   return tg_scales_at(mtiles) + (sizeof(float) + sizeof(unsigned long long)) * 32 * mtiles + sizeof(float) * 64 * TG_WAVES * tb;
 }
+constexpr size_t tg_lds_bytes(int mtiles, int tb) { return tg_rows_at(mtiles, tb) + sizeof(RowFacts) * 32 * mtiles; }
 
 // A workgroup of four waves takes 128 * TB tasks (wave w: 2 * TB A tiles of 16 tasks),
 // one k range and one tile of 32 * MTILES activation rows.  WHOLE: the launch has tiles that end in
@@ -590,11 +592,16 @@ constexpr size_t tg_lds_bytes(int mtiles, int tb) {
 // and 96 sequences take under 1 % longer for it).  64 tasks a wave have no registers for that; they
 // serve gate/up, whose k is d_model (MLP of 18944, 33 to 256 rows: 5.3e-7 to 8.6e-7; three bf16 parts 6.7e-7
 // to 1.16e-6).
+//
+// A tile that ends here turns its results in LDS, eight rows of four tasks a lane and store, and finds what the
+// epilogue needs of a row (its scale, its cache entries' place) once per workgroup, at the start: with single
+// words and a chain of loads per row the epilogue took 10 to 15 us of a round of 185 (q/k/v of 1023 rows, d 4096:
+// 134 -> 116 us).
 template <int MTILES, int TB, typename Epi, bool WHOLE>
-__global__ void __launch_bounds__(64 * TG_WAVES)
-mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__ wdown,
-             const RowDesc *__restrict__ rows, int m_rows, ProjIn in, int n_in, int n_tasks, TileCover tc,
-             float *__restrict__ part) {
+__device__ __forceinline__ void
+tiled_tile(const Epi &epi, const f16_t *__restrict__ tiled, const float *__restrict__ wdown, const RowDesc *__restrict__ rows, int m_rows,
+           const ProjIn &in, int n_in, int n_tasks, const TileCover &tc, float *__restrict__ part, uint4 *tg_smem,
+           int bx, int row0, bool whole, int split, int cut_tile) {
   static_assert(MTILES * TB <= 6 && MTILES <= 4 && TB <= 2, "accumulators take at most 192 registers");
   constexpr int MROWS = 32 * MTILES;
   constexpr int NT = 64 * TG_WAVES;
@@ -616,25 +623,13 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__
   constexpr int SEGMENT = FOLD ? TG_FOLD_CHUNKS : 1 << 20;   // chunks that are added up before they are folded
   static_assert(SEGMENT % 2 == 0, "whole turns of the ring of chunks");
   constexpr size_t SCALE_AT = tg_scales_at(MTILES);
-  extern __shared__ uint4 tg_smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (known to be uniform: addresses of weights stay scalar)
   f16_t *s_x = (f16_t *)tg_smem;                    // [3][2][MROWS * MG_ROWPAD]
   float *s_down = (float *)((char *)tg_smem + SCALE_AT);   // per activation row: what undoes its scale
   float *s_wdown = (float *)((char *)tg_smem + SCALE_AT + (sizeof(float) + sizeof(unsigned long long)) * MROWS);   // and per weight row
-  clear_words(in);
+  RowFacts *s_rows = (RowFacts *)((char *)tg_smem + tg_rows_at(MTILES, TB));   // what the epilogue needs of the rows
 
-  int t, split = 0, bx, bz;
-  const bool whole = WHOLE && (int)blockIdx.x < tc.n_whole;
-  if (whole) {
-    t = blockIdx.x;
-  } else {
-    const int i = blockIdx.x - tc.n_whole;
-    split = i / tc.n_cut;
-    t = tc.n_whole + i - split * tc.n_cut;
-  }
-  tile_place(tc, t, bx, bz);
-  const int row0 = bz * MROWS;
   const int n_chunks = (n_in + MG_KC - 1) / MG_KC;
   const int c_begin = whole ? 0 : split * tc.chunks_per_split;
   const int c_end = whole ? n_chunks : min(n_chunks, c_begin + tc.chunks_per_split);
@@ -715,6 +710,11 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__
   constexpr int LPR = MG_KC / 8;
   const int xr0 = (int)threadIdx.x >> 3;
   RowExponent<LPR> mag0(in.row_max, min(row0 + xr0, m_rows - 1), threadIdx.x & 7);
+  RowFacts facts;
+  if constexpr (WHOLE && EpiFacts<Epi>::value) {
+    const int r = min(row0 + min((int)threadIdx.x, MROWS - 1), m_rows - 1);
+    if (whole) facts = epi.row_facts(r, rows[r]);
+  }
   float wd[TB];             // of weight row threadIdx.x + NT u of the workgroup's 64 TG_WAVES TB
 #pragma unroll
   for (int u = 0; u < TB; ++u) {
@@ -740,6 +740,9 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__
   }
 #pragma unroll
   for (int u = 0; u < TB; ++u) s_wdown[(int)threadIdx.x + NT * u] = wd[u];
+  if constexpr (WHOLE && EpiFacts<Epi>::value) {
+    if (whole && (int)threadIdx.x < MROWS) s_rows[threadIdx.x] = facts;
+  }
 #pragma unroll
   for (int n = 0; n < XV; ++n) {
 #pragma unroll
@@ -839,7 +842,7 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__
     }
   }
   if (!whole) {
-    float *base = part + ((size_t)split * tc.n_cut + (t - tc.n_whole)) * TASKS * 2 * tc.m_pitch;
+    float *base = part + ((size_t)split * tc.n_cut + cut_tile) * TASKS * 2 * tc.m_pitch;
 #pragma unroll
     for (int jb = 0; jb < TB; ++jb)
 #pragma unroll
@@ -861,7 +864,7 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__
     // the epilogue's stores run along the tasks: each 32 x 32 tile is turned in the wave's piece of
     // LDS (the buffers are free once every wave has left the loop)
     __syncthreads();
-    float *s_t = (float *)tg_smem + wave * 2 * 32 * 33;
+    float *s_t = (float *)tg_smem + wave * 2 * 32 * TG_TPITCH;
     const int tl = lane & 31, rh = (lane >> 5) * 16;
     if constexpr (EpiHasLocalReduce<Epi>::value) {
       // a running state per activation row (the heads' arg-max): formed while a lane holds tasks of one
@@ -903,7 +906,7 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__
 #pragma unroll
       for (int c = 0; c < MTILES; ++c) {
         const int mine = row0 + c * 32 + (lane & 31);
-        const float inv = epi.row_scale(min(mine, m_rows - 1));
+        const float inv = s_rows[c * 32 + (lane & 31)].inv;
         typename Epi::State st;
         epi.init(st);
 #pragma unroll
@@ -911,22 +914,57 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__
           const int t0 = (tb0 + jb) * 32;
           if (tc.max_words > 1) epi.init(st);
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int tt = task_of(r);
-            const float v = epi.value(inv, y_of(0, jb, c, r), y_of(1, jb, c, r));
-            if (t0 + tt < n_tasks) st.amax = max(st.amax, magnitude_bits(v));
-            s_t[tt * 33 + (lane & 31)] = v;
-            if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // (registers: sixteen exponentials at once are too many)
+          for (int j = 0; j < 4; ++j) {
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int r = 4 * j + e;
+              v[e] = epi.value(inv, y_of(0, jb, c, r), y_of(1, jb, c, r));
+              if (t0 + task_of(r) < n_tasks) st.amax = max(st.amax, magnitude_bits(v[e]));
+            }
+            *(float4 *)(s_t + (lane & 31) * TG_TPITCH + task_of(4 * j)) = make_float4(v[0], v[1], v[2], v[3]);
+            __builtin_amdgcn_sched_barrier(0);   // (registers: sixteen exponentials at once are too many)
           }
-#pragma unroll 4
-          for (int i = 0; i < 16; ++i) {
-            const int m = row0 + c * 32 + rh + i;
-            if (t0 + tl < n_tasks && m < m_rows) epi.store_value(t0 + tl, m, s_t[tl * 33 + rh + i]);
+          // eight rows a store, four tasks a lane
+          float4 out[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) out[i] = *(const float4 *)(s_t + ((lane >> 3) + 8 * i) * TG_TPITCH + (lane & 7) * 4);
+          const int task = t0 + (lane & 7) * 4;   // (the number of tasks is a multiple of four)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int m = row0 + c * 32 + (lane >> 3) + 8 * i;
+            if (task < n_tasks && m < m_rows) epi.store_values(task, m, out[i]);
           }
           if (tc.max_words > 1 || jb == TB - 1) {
             st.amax = max(st.amax, (uint32_t)__shfl_xor((int)st.amax, 32, 64));
             const int word = tc.max_words > 1 ? tb0 + jb : bx * TG_WAVES + wave;
             if (lane < 32 && mine < m_rows && (tc.max_words > 1 ? t0 : tb0 * 32) < n_tasks) epi.put_row(mine, word, st);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    } else if constexpr (EpiFacts<Epi>::value) {
+      // pairs, four tasks of a row a lane: 32 tasks lie in one head, and what depends on the row is in LDS
+#pragma unroll
+      for (int jb = 0; jb < TB; ++jb) {
+        const int task = (tb0 + jb) * 32 + (lane & 7) * 4;
+#pragma unroll
+        for (int c = 0; c < MTILES; ++c) {
+#pragma unroll
+          for (int w = 0; w < 2; ++w)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              *(float4 *)(s_t + (32 * w + (lane & 31)) * TG_TPITCH + task_of(4 * j)) =
+                  make_float4(y_of(w, jb, c, 4 * j), y_of(w, jb, c, 4 * j + 1), y_of(w, jb, c, 4 * j + 2), y_of(w, jb, c, 4 * j + 3));
+          typename Epi::Turn turn[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) turn[i] = epi.load_turn(task, s_rows[c * 32 + (lane >> 3) + 8 * i]);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int rl = (lane >> 3) + 8 * i, m = row0 + c * 32 + rl;
+            const float *p = s_t + rl * TG_TPITCH + (lane & 7) * 4;
+            if (task < n_tasks && m < m_rows)
+              epi.finish4(task, m, s_rows[c * 32 + rl], *(const float4 *)p, *(const float4 *)(p + 32 * TG_TPITCH), turn[i]);
           }
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -956,6 +994,55 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__
       }
     }
   }
+}
+
+template <int MTILES, int TB, typename Epi, bool WHOLE>
+__global__ void __launch_bounds__(64 * TG_WAVES)
+mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__ wdown,
+             const RowDesc *__restrict__ rows, int m_rows, ProjIn in, int n_in, int n_tasks, TileCover tc,
+             float *__restrict__ part) {
+  extern __shared__ uint4 tg_smem[];
+  clear_words(in);
+  int t, split = 0, bx, bz;
+  const bool whole = WHOLE && (int)blockIdx.x < tc.n_whole;
+  if (whole) {
+    t = blockIdx.x;
+  } else {
+    const int i = blockIdx.x - tc.n_whole;
+    split = i / tc.n_cut;
+    t = tc.n_whole + i - split * tc.n_cut;
+  }
+  tile_place(tc, t, bx, bz);
+  tiled_tile<MTILES, TB, Epi, WHOLE>(epi, tiled, wdown, rows, m_rows, in, n_in, n_tasks, tc, part, tg_smem, bx, bz * 32 * MTILES, whole, split,
+                                     t - tc.n_whole);
+}
+
+// Whole tiles of three and of two blocks of rows in one launch (see MixedCover): the higher ones first.
+// (gate/up of 18944 tasks, 511 rows: 308 -> 285 us; of 13696, 1023 rows: 450 and a finishing launch of 20 -> 451, which is
+// what the chip's power allows: 1.02 PFLOP/s executed.)
+template <int TB, typename Epi>
+__global__ void __launch_bounds__(64 * TG_WAVES)
+mfma_tiled_mixed_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__ wdown,
+                   const RowDesc *__restrict__ rows, int m_rows, ProjIn in, int n_in, int n_tasks, MixedCover mc) {
+  extern __shared__ uint4 tg_smem[];
+  clear_words(in);
+  int t = blockIdx.x, k = 0;
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    if (k == i && t >= mc.part[i].n_task_tiles * mc.part[i].n_row_tiles) {
+      t -= mc.part[i].n_task_tiles * mc.part[i].n_row_tiles;
+      k = i + 1;
+    }
+  TileCover tc = mc.part[0];
+#pragma unroll
+  for (int i = 1; i < 4; ++i)
+    if (k == i) tc = mc.part[i];
+  int bx, bz;
+  tile_place(tc, t, bx, bz);
+  if (k & 1) bx += mc.part[0].n_task_tiles;   // (0, 1: the higher tiles of the first and of the other task tiles; 2, 3: the lower ones)
+  if (k < 2) tiled_tile<3, TB, Epi, true>(epi, tiled, wdown, rows, m_rows, in, n_in, n_tasks, tc, nullptr, tg_smem, bx, bz * 96, true, 0, 0);
+  else tiled_tile<2, TB, Epi, true>(epi, tiled, wdown, rows, m_rows, in, n_in, n_tasks, tc, nullptr, tg_smem, bx,
+                                    (k == 2 ? mc.part[0].n_row_tiles : mc.part[1].n_row_tiles) * 96 + bz * 64, true, 0, 0);
 }
 
 // ------------------------------------------------------------------ finishing

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -125,6 +126,7 @@ struct spark_ctx {
   bool prompt_pass = false;  // the pass being enqueued: consecutive positions of one sequence
   int attn_prompt_min_rows = 0;   // rows from which such a pass shares K and V between its rows (0: by the pass's size)
   int attn_splits_now = 0;   // context slices the rows of the passes being enqueued can reach (0: unknown, launch all)
+  std::map<std::array<int, 3>, MixedCover> mixed_covers;   // (blocks of rows, input, tasks) of large passes
   std::map<std::pair<const void *, size_t>, int> occ_cache;  // workgroups per CU of a (kernel, LDS bytes)
   // profiling of one kernel class
   int prof_class = -1;
@@ -680,6 +682,44 @@ int launch_tiled_rows(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, 
   }
 }
 
+// the same on whole tiles of two heights
+template <int TB, typename Epi>
+int launch_mixed(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,
+                 const TiledMatrix &w, const MixedCover &mc, int *max_words) {
+  auto kern = mfma_tiled_mixed_k<TB, Epi>;
+  const size_t lds = tg_lds_bytes(3, TB);
+  if (lds > 65536) {
+    const auto key = std::make_pair((const void *)kern, lds);
+    if (c->occ_cache.find(key) == c->occ_cache.end()) {
+      HIP_TRY(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+      c->occ_cache.emplace(key, 1);
+    }
+  }
+  if (max_words) *max_words = (n_tasks + 32 * TB - 1) / (32 * TB);
+  kern<<<mc.tiles(), 64 * TG_WAVES, lds, c->stream>>>(epi, at<f16_t>(c, c->lo.tiled) + w.elems, at<float>(c, c->lo.wdown) + w.blocks * 32, rows, m, in,
+                                                     n_in, n_tasks, mc);
+  HIP_TRY(c, hipGetLastError());
+  return SPARK_OK;
+}
+// The cover by tiles of two heights if it is the better one, or nullptr.  (Found once for a shape: some tens of microseconds.)
+int mixed_cover(spark_ctx *c, int m, int n_in, int n_tasks, const MixedCover **out) {
+  *out = nullptr;
+  const int blocks = ceil_div(m, 32), most = std::min(c->tiled_row_blocks, 3);
+  if (most < 3 || blocks < 3) return SPARK_OK;
+  const std::array<int, 3> key{blocks, n_in, n_tasks};
+  auto found = c->mixed_covers.find(key);
+  if (found == c->mixed_covers.end()) {
+    if (c->mixed_covers.size() >= 64) c->mixed_covers.clear();
+    MixedCover mc = cover_mixed(32 * blocks, n_in, n_tasks, c->n_cu);
+    const int mt = tiled_row_blocks_for(32 * blocks, most);
+    const TileCover tc = cover_tiled(32 * blocks, n_in, n_tasks, mt, 2, false, false, c->n_cu, c->mfma_xcd_max_split);
+    if (mc.cost >= tiled_cost(tc, n_in, mt, c->n_cu)) mc.cost = 0.f;   // (no gain)
+    found = c->mixed_covers.emplace(key, mc).first;
+  }
+  if (found->second.cost > 0.f) *out = &found->second;
+  return SPARK_OK;
+}
+
 // the same for at most 32 rows, in operand order
 template <int NT, int COLS, bool CUT, typename Epi>
 int launch_direct_cols(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,
@@ -800,7 +840,12 @@ int launch_mfma_tiles(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, 
 
 template <typename Epi>
 int launch_wide(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in, const TiledMatrix &w, int *max_words) {
-  if constexpr (std::is_same<Epi, EpiSwiGLUMax<bf16_t>>::value) return launch_tiled_rows<2>(c, epi, rows, m, n_in, n_tasks, in, w, max_words);
+  if constexpr (std::is_same<Epi, EpiSwiGLUMax<bf16_t>>::value) {
+    const MixedCover *mc;
+    if (int rc = mixed_cover(c, m, n_in, n_tasks, &mc)) return rc;
+    if (mc) return launch_mixed<2>(c, epi, rows, m, n_in, n_tasks, in, w, *mc, max_words);
+    return launch_tiled_rows<2>(c, epi, rows, m, n_in, n_tasks, in, w, max_words);
+  }
   else return SPARK_EINVAL;
 }
 

@@ -74,6 +74,51 @@ int main() {
 """
 
 
+MIXED = r"""
+#include <cstdio>
+#include <vector>
+#include "cover.h"
+using namespace spark;
+int main() {
+  long covers = 0, two = 0;
+  const int widths[] = {8192, 8264, 13696, 18944, 40000};
+  for (int tasks : widths)
+    for (int n_cu : {256, 64})
+      for (int m = 65; m <= 3072; m += m < 400 ? 1 : 37) {
+        const MixedCover mc = cover_mixed(m, 3584, tasks, n_cu);
+        const int T = ceil_div(tasks, 256), blocks = ceil_div(m, 32);
+        std::vector<int> hit(T * (blocks + 8), 0);
+        for (int k = 0; k < 4; ++k)     // as the kernel places them
+          for (int bx = 0; bx < mc.part[k].n_task_tiles; ++bx)
+            for (int bz = 0; bz < mc.part[k].n_row_tiles; ++bz) {
+              const int first = k < 2 ? 3 * bz : 3 * mc.part[k - 2].n_row_tiles + 2 * bz, x = bx + (k & 1 ? mc.part[0].n_task_tiles : 0);
+              for (int b = first; b < first + (k < 2 ? 3 : 2); ++b) {
+                if (x >= T || b >= blocks + 2) { printf("out of range: %d tasks, %d rows\n", tasks, m); return 1; }
+                ++hit[x * (blocks + 8) + b];
+              }
+            }
+        for (int x = 0; x < T; ++x)
+          for (int b = 0; b < blocks; ++b)
+            if (hit[x * (blocks + 8) + b] != 1) { printf("not once: %d tasks, %d rows\n", tasks, m); return 1; }
+        ++covers;
+        two += mc.part[1].n_task_tiles > 0;
+      }
+  printf("%ld covers, %ld with two kinds of task tile\n", covers, two);
+  return 0;
+}
+"""
+
+
+def test_covers_by_tiles_of_two_heights_take_every_block_once(tmp_path):
+    src, exe = tmp_path / "mixed.cpp", tmp_path / "mixed"
+    src.write_text(MIXED)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", f"-I{CSRC}", "-o", str(exe), str(src)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, out.stdout
+    n, n_two = (int(w) for w in out.stdout.split() if w.isdigit())
+    assert n > 3000 and n_two > 300, out.stdout
+
+
 def test_partial_sums_of_every_cover_fit_their_buffer(tmp_path):
     src, exe = tmp_path / "covers.cpp", tmp_path / "covers"
     src.write_text(DRIVER)
