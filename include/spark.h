@@ -305,7 +305,7 @@ int spark_measure_read(spark_ctx *ctx, const void *buf, size_t bytes, int32_t re
  *   between its rows; 0: by the sizes of pass and context), "gemv_big_kb", "mfma_tiled" (0: the MFMA projections stage the
  *   caller's weight rows through LDS instead of reading the context's copy in operand order),
  *   "mfma_small_tiles" and "mfma_small_max_k" (which of those launches run four waves a workgroup),
- *   "direct_max_rows" (rows up to which those on the copy do without LDS, at most 32),
+ *   "direct_max_rows" (rows up to which those on the copy do without LDS, at most 48),
  *   "direct_whole_k" (the longest input width whose few tasks those never cut over workgroups),
  *   "tiled_row_blocks" (blocks of 32 rows in a row tile of the others, 2..4, at most), "fuse_norm" (0:
  *   every RMSNorm of the batched path is its own launch), "prefill_rows" (prompt rows per pass, a

@@ -9,7 +9,7 @@ constexpr int MG_KC = 64;              // k per chunk: one 128-byte line of a we
 constexpr int MG_MAX_SPLIT = 32;       // ranges of k whose sums a finishing launch adds up, at most
 constexpr int TG_WAVES = 4;
 constexpr int TG_TASKS = 16;           // tasks of one A tile
-constexpr int OP_ROWS = 32;            // rows of a pass whose activations lie in operand order, at most
+constexpr int OP_ROWS = 48;            // rows of a pass whose activations lie in operand order, at most
 constexpr int TD_CUT_TILES = 2;        // A tiles of a workgroup of mfma_direct_k whose k is cut
 constexpr size_t MFMA_PARTIAL_BYTES = 48u << 20;  // k-split partial sums of one projection
 
@@ -183,8 +183,9 @@ inline float tiled_cost(const TileCover &tc, int n_in, int mtiles, int n_cu) {
 // Blocks of 32 rows in a row tile of a projection with 32 tasks a wave and more rows than one tile
 // takes: such a launch is one to three rounds of CUs, and what the last of them leaves idle differs
 // more between the heights than the heights themselves do.  The time of a cover is taken as that of
-// the CU with the most chunks, 0.4 us for each of a chunk's blocks of rows and as much for its weights, and
-// that of its partial sums, at 5 TB/s there and back; a lower tile has to save a twentieth.
+// the CU with the most chunks, 0.4 us for each of a chunk's blocks of rows and as much for its weights, its
+// starts and epilogues, and
+// that of its partial sums, at 5 TB/s there and back, and the launch that adds them up; a lower tile has to save a twentieth.
 // (down, 768 rows of d 4096, k 13696: tiles of 128 rows make two ranges on 192 CUs, of 96 rows two
 // on all 256; a prompt of 2300 tokens in three such passes 25.4 ms with the former, 23.8 with the latter.)
 inline int narrow_row_blocks(int m, int n_in, int n_tasks, int most_blocks, bool always_cut, int n_cu) {
@@ -193,9 +194,14 @@ inline int narrow_row_blocks(int m, int n_in, int n_tasks, int most_blocks, bool
   double least = 0.0;
   for (int mt = most_blocks; mt >= 2; --mt) {
     const TileCover tc = cover_tiled(m, n_in, n_tasks, mt, 1, always_cut, false, n_cu, 0);
-    const long chunks = (long)ceil_div(tc.n_whole, n_cu) * ceil_div(n_in, MG_KC) +
-                        (tc.n_cut ? (long)ceil_div(tc.n_cut * tc.n_split, n_cu) * tc.chunks_per_split : 0);
-    const double cost = (double)chunks * (mt + 1) * 0.4 + (double)tiled_partial_bytes(tc, 1) * 2.0 / 5e6;
+    // (a chunk of a launch that leaves CUs idle is faster: the others share the chip's power and caches)
+    auto round_cost = [&](int workgroups, int chunks) {
+      const int rounds = ceil_div(workgroups, n_cu);
+      return rounds * (chunks * (mt + 1) * 0.4 * (0.6 + 0.4 * workgroups / ((double)rounds * n_cu)) + 4.0 + 3.0 * mt);
+    };
+    double cost = (double)tiled_partial_bytes(tc, 1) * 2.0 / 5e6;
+    if (tc.n_whole) cost += round_cost(tc.n_whole, ceil_div(n_in, MG_KC));
+    if (tc.n_cut) cost += round_cost(tc.n_cut * tc.n_split, tc.chunks_per_split) + 5.0;
     if (mt == most_blocks || cost < 0.95 * least) { least = cost; best = mt; }
   }
   return best;

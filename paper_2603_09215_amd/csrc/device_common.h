@@ -106,16 +106,16 @@ struct RowMax {
   }
 };
 // Where the rows of a pass go that a projection will read.  For the kernels on the fp16 copy of the
-// weights: fp32, row-major, or for a pass of at most 32 rows in the order the projection's matrix operand
-// wants them, [k / 4][32 rows][4].  For the kernel on the caller's bf16 weights: three bf16 parts, written
+// weights: fp32, row-major, or for a pass of few rows (OP_ROWS) in the order the projection's matrix operand
+// wants them, [k / 4][rows, in groups of 16][4].  For the kernel on the caller's bf16 weights: three bf16 parts, written
 // by whoever produces a row, once (with every workgroup of a projection cutting them itself, steps and
 // prompts of such contexts took 12 to 45 % longer).
 struct RowOut {
   float *p;
-  int stride;       // fp32: elements from row to row, 0: operand order; parts: elements of a row
+  int stride;       // fp32: elements from row to row, or minus the rows of the operand order; parts: elements of a row
   int part_units;   // 0: fp32; otherwise p points to bf16 parts, this many 64 elements apart, rows padded to 64
   __device__ __forceinline__ float *at(int r, int k) const {   // k..k|3 are neighbours in both
-    return p + (stride ? (size_t)r * stride + k : (size_t)(k >> 2) * (4 * OP_ROWS) + r * 4 + (k & 3));
+    return p + (stride > 0 ? (size_t)r * stride + k : (size_t)(k >> 2) * (-4 * stride) + r * 4 + (k & 3));
   }
   __host__ __device__ __forceinline__ int pitch() const { return (stride + 63) & ~63; }
   __device__ __forceinline__ size_t part_stride() const { return (size_t)part_units * 64; }

@@ -6,7 +6,7 @@
 // it in parts that add up to the fp32 value, which keeps the result at fp32 accuracy instead of
 // rounding the activations to 8 bits of mantissa.  Three kernels run the contraction:
 //
-//   mfma_tiled_k and, for at most 32 rows, mfma_direct_k (further down), which a context with the
+//   mfma_tiled_k and, for at most 48 rows, mfma_direct_k (further down), which a context with the
 //   memory for it runs, take their weights from a copy in fp16 and in MFMA operand order, written when the context was created.  A bf16
 //   weight scaled by a power of two per row is an fp16 number (exact down to 2^-31 of the row's
 //   largest weight), so the activations are fp16 parts too, and fp16
@@ -146,7 +146,7 @@ prep_rows_k(const RowDesc *__restrict__ rows, const float *__restrict__ src, int
   finish();
 }
 
-// The input of a projection: fp32 rows `stride` elements apart (0: in operand order, see RowOut) and
+// The input of a projection: fp32 rows `stride` elements apart (or in operand order, see RowOut) and
 // the lists of their magnitudes; and words that are to be zero for the launches after this one.
 struct ProjIn {
   const float *x;
@@ -1196,7 +1196,7 @@ mfma_finish_tile_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, int n_
   hand_on_row<32>(epi, m, m < m_rows, st, task0 / 32);
 }
 
-// ------------------------------------------------------------------ at most 32 rows
+// ------------------------------------------------------------------ at most 48 rows
 //
 // Batched decoding: the projection is a stream of weights again, only with more arithmetic per
 // weight.  A workgroup of four waves takes NT A tiles (16 NT tasks) and one range of k, a quarter
@@ -1206,7 +1206,7 @@ mfma_finish_tile_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, int n_
 // order: a shorter ring for the activations would empty the weights' longer one), and the
 // activations are cut into fp16 parts by the wave that multiplies them.
 //
-// v_mfma_f32_16x16x32_f16, COLS = 16 or 32 activation rows as one or two B operands: with 32-wide
+// v_mfma_f32_16x16x32_f16, COLS = 16, 32 or 48 activation rows as one to three B operands: with 32-wide
 // operands a pass of 16 rows would fetch and cut as many activations as one of 32.  What bounds the short
 // launches is what a CU has to fetch, activations (from L2, 4 COLS bytes per k) as much as weights:
 // q/k/v of 8 rows, k 3584, 33 MB: 11.0 us with the activations' loads left out, 16.2 with 32 columns, 11.9
@@ -1221,6 +1221,8 @@ mfma_finish_tile_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, int n_
 // takes all of k, and there are no partial sums and no finishing launch.
 // Only a long k with few tasks (down) is cut: CUT writes partial sums.
 //
+// (48 rows: gate/up of 271 MB 58 us, where mfma_tiled_k and its finishing launch take 58 and 12; a quarter of the heads 61
+// against 87; down 37 and 5 against 40 and 8; q/k/v and o level.  With 64 the sums of five tiles spill.)
 // Loads are buffer loads: the lane's place is one register for all of them, step and tile are scalars, and
 // what lies past the end of a matrix or of the activations comes back as zeros.
 constexpr int TD_WAVES = 4;
@@ -1230,9 +1232,10 @@ constexpr int td_ring(int nt) { return nt == 1 ? 4 : 2; }
 // and where there are registers for it the activations' lower parts have sums of their own.  1.3e-7 without
 // the latter, 1.2e-7 with them (vector kernel: 1.1e-7); MLP blocks 2.6e-7 and 2.3e-7 (vector kernels 2.5e-7).
 constexpr bool td_fine(int nt, int cols) { return nt * cols <= 32; }   // (what the registers of four waves a SIMD allow)
-constexpr int td_fold_steps(int nt, int cols) { return td_fine(nt, cols) ? 2 : 4; }   // steps of 32 k whose products go into one set of sums
+constexpr int td_fold_steps(int nt, int cols) { return td_fine(nt, cols) || nt * cols > 160 ? 2 : 4; }   // steps of 32 k whose products go into one set of sums (240: four spill)
 constexpr int TD_PITCH = 36;   // floats of LDS per (tile, activation row): 32 weight rows and a skew of one 16-byte word
-constexpr size_t td_lds_bytes(int nt, int cols) { return sizeof(float) * (TD_WAVES * nt * cols * TD_PITCH + nt * 32 + OP_ROWS); }
+constexpr int td_pieces(int nt, int cols) { return nt * cols <= 240 ? TD_WAVES : TD_WAVES / 2; }   // waves' sums that LDS holds at once
+constexpr size_t td_lds_bytes(int nt, int cols) { return sizeof(float) * (td_pieces(nt, cols) * nt * cols * TD_PITCH + nt * 32 + OP_ROWS); }
 
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __amdgpu_buffer_rsrc_t buffer_t;
@@ -1248,11 +1251,11 @@ __global__ void __launch_bounds__(64 * TD_WAVES, 1)
 mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__ wdown,
               const RowDesc *__restrict__ rows, int m_rows, ProjIn in, int n_in, int n_tasks, int n_groups,
               int chunks_per_split, float *__restrict__ part, int m_pitch) {
-  static_assert(COLS == 16 || COLS == OP_ROWS, "one or two operands of 16 activation rows");
-  constexpr int CG = COLS / 16, KS = 32, STEPS = MG_KC / KS, RING = td_ring(NT), THREADS = 64 * TD_WAVES;
+  static_assert(COLS % 16 == 0 && COLS <= OP_ROWS, "operands of 16 activation rows");
+  constexpr int CG = COLS / 16, KS = 32, STEPS = MG_KC / KS, RING = td_ring(NT), THREADS = 64 * TD_WAVES, PIECES = td_pieces(NT, COLS);
   extern __shared__ uint4 td_smem[];
   float *s_t = (float *)td_smem;                             // [waves][NT][COLS][TD_PITCH]
-  float *s_wdown = s_t + TD_WAVES * NT * COLS * TD_PITCH;    // [NT][32 operand rows]
+  float *s_wdown = s_t + PIECES * NT * COLS * TD_PITCH;      // [NT][32 operand rows]
   int *s_exp = (int *)(s_wdown + NT * 32);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, kq = lane >> 4;   // operand row / column, and which eight of the step's 32 k
@@ -1268,7 +1271,8 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
   const int s_last = max(s_end - 1, 0);   // steps past the end read this one and are multiplied with zeros
   const size_t tile_bytes = sizeof(f16_t) * TG_TILE, first = (size_t)group * NT * n_chunks;
   const buffer_t w_buf = buffer_of(tiled + first * TG_TILE, ((size_t)n_blocks * n_chunks - first) * tile_bytes);
-  const buffer_t x_buf = buffer_of(in.x, sizeof(float) * OP_ROWS * (size_t)n_in);
+  const int op_rows = -in.stride;
+  const buffer_t x_buf = buffer_of(in.x, sizeof(float) * op_rows * (size_t)n_in);
   // of a tile's chunk: operand rows 16 h + col, elements 32 step + 8 kq .. + 7
   const int w_at = (int)sizeof(f16_t) * ((kq >> 1) * 512 + (col + 32 * (kq & 1)) * 8);
   u32x4_t wr[RING][NT][2], xr[RING][CG][2];
@@ -1281,20 +1285,21 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
   };
   int x_at[CG];   // (columns past the last row repeat it)
 #pragma unroll
-  for (int g = 0; g < CG; ++g) x_at[g] = (2 * kq * OP_ROWS + min(16 * g + col, m_rows - 1)) * 16;
+  for (int g = 0; g < CG; ++g) x_at[g] = (2 * kq * op_rows + min(16 * g + col, m_rows - 1)) * 16;
   auto load_x = [&](int u, int step) {
-    const int at = min(step, s_last) * (KS * OP_ROWS * (int)sizeof(float));
+    const int at = min(step, s_last) * (KS * (int)sizeof(float)) * op_rows;
 #pragma unroll
     for (int g = 0; g < CG; ++g)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) xr[u][g][i] = load_buffer16<false>(x_buf, x_at[g] + i * OP_ROWS * 16, at);
+      for (int i = 0; i < 2; ++i) xr[u][g][i] = load_buffer16<false>(x_buf, x_at[g], at + i * 16 * op_rows);
   };
   // (finishing, a thread has task t of every tile and the rows m0 + 16 g)
   const int t = threadIdx.x & (TG_TASKS - 1), m0 = threadIdx.x >> 4;
-  RowDesc rd[CG];
+  constexpr int EARLY = CG <= 2 ? CG : 0;   // descriptors requested now (registers)
+  RowDesc early[EARLY > 0 ? EARLY : 1];
 #pragma unroll
-  for (int g = 0; g < CG; ++g) rd[g] = rows[min(m0 + 16 * g, m_rows - 1)];
-  constexpr int LPR = THREADS / COLS;
+  for (int g = 0; g < EARLY; ++g) early[g] = rows[min(m0 + 16 * g, m_rows - 1)];
+  constexpr int LPR = COLS == 16 ? 16 : COLS == 32 ? 8 : 4;   // neighbouring lanes that find a row's largest exponent
   RowExponent<LPR> mag(in.row_max, min((int)threadIdx.x / LPR, m_rows - 1), threadIdx.x & (LPR - 1));
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -1306,7 +1311,7 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
   __builtin_amdgcn_sched_barrier(0);
   {
     const int e = mag.get();
-    if ((threadIdx.x & (LPR - 1)) == 0) s_exp[threadIdx.x / LPR] = scale_exponent(e);
+    if ((threadIdx.x & (LPR - 1)) == 0) s_exp[threadIdx.x / LPR] = scale_exponent(e);   // (rows past COLS repeat the last)
   }
   __syncthreads();
   float x_up[CG];
@@ -1380,20 +1385,36 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
 
   // the waves' sums, [activation row][weight row]: a lane has four neighbouring weight rows of one activation row
   if (threadIdx.x < NT * 32) s_wdown[threadIdx.x] = wd;
+  auto piece = [&](int w, int q, int g, int h) { return (f32x4_t *)(s_t + ((w * NT + q) * COLS + 16 * g + col) * TD_PITCH + 16 * h + 4 * kq); };
+  if constexpr (PIECES < TD_WAVES) {   // the upper waves hand theirs to the lower ones
+    if (wave >= PIECES) {
 #pragma unroll
-  for (int q = 0; q < NT; ++q)
+      for (int q = 0; q < NT; ++q)
 #pragma unroll
-    for (int g = 0; g < CG; ++g)
+        for (int g = 0; g < CG; ++g)
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
-        *(f32x4_t *)(s_t + ((wave * NT + q) * COLS + 16 * g + col) * TD_PITCH + 16 * h + 4 * kq) = folded[q][g][h];
+          for (int h = 0; h < 2; ++h) *piece(wave - PIECES, q, g, h) = folded[q][g][h];
+    }
+    __syncthreads();
+  }
+  if (wave < PIECES) {
+#pragma unroll
+    for (int q = 0; q < NT; ++q)
+#pragma unroll
+      for (int g = 0; g < CG; ++g)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          f32x4_t *p = piece(wave, q, g, h);
+          *p = PIECES < TD_WAVES ? folded[q][g][h] + *p : folded[q][g][h];
+        }
+  }
   __syncthreads();
   // the sum of an operand row, always in the order of the waves, without its scales
   // (one factor after the other: their product may lie outside the range of an fp32 where the result does not)
   auto sum = [&](int q, int row, int m, float x_down) {
     float y = s_t[(q * COLS + m) * TD_PITCH + row];
 #pragma unroll
-    for (int w = 1; w < TD_WAVES; ++w) y += s_t[((w * NT + q) * COLS + m) * TD_PITCH + row];
+    for (int w = 1; w < PIECES; ++w) y += s_t[((w * NT + q) * COLS + m) * TD_PITCH + row];
     return y * x_down * s_wdown[q * 32 + row];
   };
   if constexpr (CUT) {
@@ -1416,19 +1437,20 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
     for (int g = 0; g < CG; ++g) {
       const int m = m0 + 16 * g;
       const bool row_live = m < m_rows;
+      const RowDesc rd = EARLY > 0 ? early[EARLY > 0 ? g : 0] : rows[min(m, m_rows - 1)];
       const float x_down = scale_down(s_exp[m]);
       typename Epi::State st;
       epi.init(st);
-      decltype(load_old(epi, 0, 0, rd[0], true)) old[NT];   // (requested together: the stores between them would hold them back)
+      decltype(load_old(epi, 0, 0, rd, true)) old[NT];   // (requested together: the stores between them would hold them back)
 #pragma unroll
       for (int q = 0; q < NT; ++q) {
         const int task = (group * NT + q) * TG_TASKS + t;
-        old[q] = load_old(epi, row_live && task < n_tasks ? task : 0, min(m, m_rows - 1), rd[g], true);
+        old[q] = load_old(epi, row_live && task < n_tasks ? task : 0, min(m, m_rows - 1), rd, true);
       }
 #pragma unroll
       for (int q = 0; q < NT; ++q) {
         const int task = (group * NT + q) * TG_TASKS + t;
-        if (row_live && task < n_tasks) finish_pair(epi, task, m, rd[g], sum(q, t, m, x_down), sum(q, TG_TASKS + t, m, x_down), old[q], st);
+        if (row_live && task < n_tasks) finish_pair(epi, task, m, rd, sum(q, t, m, x_down), sum(q, TG_TASKS + t, m, x_down), old[q], st);
       }
       if constexpr (EpiHasLocalReduce<Epi>::value) {
         // the heads' arg-max: one atomic per row and workgroup
@@ -1438,7 +1460,7 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
               ((unsigned long long)(uint32_t)__shfl_xor((int)(st.best >> 32), o, 64) << 32) | (uint32_t)__shfl_xor((int)st.best, o, 64);
           if (other > st.best) st.best = other;
         }
-        if (t == 0 && row_live) epi.end_reduced(rd[g], st.best);
+        if (t == 0 && row_live) epi.end_reduced(rd, st.best);
       } else {
         hand_on_row<TG_TASKS>(epi, m, row_live, st, group);
       }

@@ -106,7 +106,7 @@ struct spark_ctx {
   bool mfma_ok = true;         // the shape allows the MFMA projections (16-byte vectors of 8 weights)
   bool use_mfma = true;        // "mfma" = 0 keeps every row count on the vector kernels
   int tiled_row_blocks = 4;     // blocks of 32 rows in a tile of mfma_tiled_k, at most
-  int direct_max_rows = 32;     // rows up to which mfma_direct_k runs
+  int direct_max_rows = OP_ROWS;   // rows up to which mfma_direct_k runs
   int direct_whole_k = 8192;    // ... and the longest k that it never cuts
   int mfma_xcd_max_split = 4;  // row tiles share an XCD when k has at most this many ranges
   int mfma_small_tiles = 32;   // launches of mfma_rows_k with fewer 8-wave tiles use 4-wave workgroups
@@ -564,13 +564,13 @@ template <typename WT> int launch_attention(spark_ctx *c, const RowDesc *rows, i
 // ------------------------------------------------------------------ MFMA path (three or five and more rows, bf16)
 
 // Which kernel takes a pass's projections, and with it how the rows that they read lie in memory: on the
-// copy of the weights fp32 rows, where a pass of at most 32 of them streams it (mfma_direct_k) and wants
+// copy of the weights fp32 rows, where a pass of few of them streams it (mfma_direct_k) and wants
 // operand order; on the caller's weights bf16 parts, part_elems apart.
 bool on_copy(spark_ctx *c) { return c->has_tiled && c->use_tiled; }
 bool in_operand_order(spark_ctx *c, int m) { return on_copy(c) && m <= std::min(OP_ROWS, c->direct_max_rows); }
 RowOut rows_out(spark_ctx *c, float *p, size_t part_elems, int m, int width) {
   if (!on_copy(c)) return RowOut{p, width, (int)(part_elems / 64)};
-  return RowOut{p, in_operand_order(c, m) ? 0 : width, 0};
+  return RowOut{p, in_operand_order(c, m) ? -(m <= 32 ? 32 : OP_ROWS) : width, 0};
 }
 RowMax row_max_list(spark_ctx *c, uint8_t *list, int bytes, int n) { return on_copy(c) ? RowMax{list, bytes, n} : RowMax{nullptr, 0, 0}; }
 ProjIn proj_in(const RowOut &x, const RowMax &row_max) { return ProjIn{x.p, x.stride, x.part_units, row_max, nullptr, 0}; }
@@ -720,7 +720,7 @@ int mixed_cover(spark_ctx *c, int m, int n_in, int n_tasks, const MixedCover **o
   return SPARK_OK;
 }
 
-// the same for at most 32 rows, in operand order
+// the same for few rows, in operand order
 template <int NT, int COLS, bool CUT, typename Epi>
 int launch_direct_cols(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,
                        const TiledMatrix &w, int groups, int split, int cps) {
@@ -742,8 +742,9 @@ int launch_direct_cols(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m,
 template <int NT, bool CUT, typename Epi>
 int launch_direct_tiles(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,
                         const TiledMatrix &w, int groups, int split, int cps) {
-  return m <= 16 ? launch_direct_cols<NT, 16, CUT>(c, epi, rows, m, n_in, n_tasks, in, w, groups, split, cps)
-                 : launch_direct_cols<NT, OP_ROWS, CUT>(c, epi, rows, m, n_in, n_tasks, in, w, groups, split, cps);
+  if (m <= 16) return launch_direct_cols<NT, 16, CUT>(c, epi, rows, m, n_in, n_tasks, in, w, groups, split, cps);
+  if (m <= 32) return launch_direct_cols<NT, 32, CUT>(c, epi, rows, m, n_in, n_tasks, in, w, groups, split, cps);
+  return launch_direct_cols<NT, 48, CUT>(c, epi, rows, m, n_in, n_tasks, in, w, groups, split, cps);
 }
 template <typename Epi>
 int launch_direct(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,

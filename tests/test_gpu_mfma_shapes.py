@@ -77,9 +77,9 @@ def test_projection_kernels_by_their_switches(sb, B, tune):
     sp.close()
 
 
-@pytest.mark.parametrize("B", [3, 4, 8, 9, 16, 17, 31, 32])
+@pytest.mark.parametrize("B", [3, 4, 8, 9, 16, 17, 32, 33, 47, 48])
 def test_rows_at_the_edges_of_the_direct_kernels(sb, B):
-    """one operand of 16 activation rows or two, one tile a workgroup (up to 8 rows) or a round of CUs;
+    """one operand of 16 activation rows to three, one tile a workgroup (up to 8 rows) or a round of CUs;
     inputs of 1032 and 1304, no multiples of a chunk; three and four rows: layers on the MFMA kernels,
     heads on the vector kernel"""
     say(f"case direct kernels, {B} rows")
