@@ -10,7 +10,8 @@
 // Both questions have the form "the element at which the running mass of the order first reaches
 // t", and the vocabulary is never sorted to answer them.
 //
-// Two launches, SAMPLE_CHUNK logits of one row per workgroup in both:
+// Two launches, SAMPLE_CHUNK logits of one row per workgroup in both (a vocabulary that fits one workgroup: the second
+// alone, which then forms the masses itself and hands nothing through memory):
 //   sample_mass_k  masses; every mass falls into one of 2048 classes (position of its leading one
 //                  and the six bits below it, so a class spans 1/64 of its value); the row's mass
 //                  per class is summed in memory.
@@ -72,6 +73,13 @@ __device__ __forceinline__ void hist_add(u64 *s_hist, bool valid, unsigned bucke
   } else if (valid) {
     atomicAdd(&s_hist[bucket], (u64)v);
   }
+}
+
+// mass of a logit: in double, as the definition states it (the masses are integers that have to come out the
+// same wherever they are computed; 2^32 steps are finer than a float's exp resolves)
+__device__ __forceinline__ unsigned mass_of(float logit, float mx, double temperature) {
+  const double scaled = floor(exp(((double)logit - (double)mx) / temperature) * 4294967296.0 + 0.5);
+  return scaled >= 4294967295.0 ? 4294967295u : (unsigned)scaled;
 }
 
 // Walks the buckets from the highest down: the bucket at which the running mass first reaches
@@ -171,11 +179,7 @@ sample_mass_k(const float *__restrict__ logits, int V, double temperature, unsig
     const int i = c0 + j * SAMPLE_THREADS + threadIdx.x;
     unsigned v = 0;
     if (i < V) {
-      // (in double, as the definition states it: the masses are integers that have to come out the
-      // same wherever they are computed; 2^32 steps are finer than a float's exp resolves)
-      const double w = exp(((double)lg[i] - (double)mx) / temperature);
-      const double scaled = floor(w * 4294967296.0 + 0.5);
-      v = scaled >= 4294967295.0 ? 4294967295u : (unsigned)scaled;
+      v = mass_of(lg[i], mx, temperature);
       q[i] = v;
     }
     hist_add(s_first, v != 0, v ? mass_class(v) : 0u, v);
@@ -213,54 +217,129 @@ __device__ __forceinline__ void class_walk(const u64 *s_keys, const u64 *s_run, 
   __syncthreads();
 }
 
+// Running masses of the 2048 classes from the highest down, found once and asked for several targets.
+// Thread t holds the classes at places 2t and 2t + 1 of that walk.
+struct ClassRun {
+  u64 h0, h1, before;
+  int b0;
+  __device__ __forceinline__ u64 init(const u64 *s_first, u64 *s_wave) {   // returns the total
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    b0 = SAMPLE_BINS - 1 - 2 * (int)threadIdx.x;
+    h0 = s_first[b0];
+    h1 = s_first[b0 - 1];
+    u64 incl = h0 + h1;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const u64 up = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += up;
+    }
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    before = incl - (h0 + h1);
+    u64 total = 0;
+    for (int w = 0; w < SAMPLE_WAVES; ++w) {
+      const u64 m = s_wave[w];
+      if (w < wave) before += m;
+      total += m;
+    }
+    return total;
+  }
+  // the thread whose class the running mass reaches `t` in (1 <= t <= total) writes class, mass above it, its mass
+  __device__ __forceinline__ void find(u64 t, u64 *s_out) const {
+    if (before < t && t <= before + h0) { s_out[0] = (u64)b0; s_out[1] = before; s_out[2] = h0; }
+    else if (before + h0 < t && t <= before + h0 + h1) { s_out[0] = (u64)(b0 - 1); s_out[1] = before + h0; s_out[2] = h1; }
+  }
+};
+
+// The same answer as class_walk for at most 64 candidates, sorted one per lane; run: the running mass through this lane's
+__device__ __forceinline__ u64 wave_walk(u64 key, u64 run, unsigned cls, u64 t, u64 &through_out) {
+  const unsigned qi = (unsigned)(key >> 32);
+  const bool mine = qi != 0 && mass_class(qi) == cls;
+  const int first = __ffsll((long long)__ballot(mine)) - 1;
+  const u64 front = __shfl(run - qi, first, 64);
+  const u64 through = run - front;
+  const int at = __ffsll((long long)__ballot(mine && through >= t)) - 1;
+  through_out = __shfl(through, at, 64);
+  return __shfl(key, at, 64);
+}
+
 // grid (workgroups per row, rows); omega [row]; cand [row][SAMPLE_CAP]; class_mass as
 // sample_mass_k left it, zero on exit; cand_count [row] and arrive [row] zero on entry and exit;
 // best [row]: the head's arg-max key on entry, the key of the drawn token on return.
+// ALONE: one workgroup has the whole row (a vocabulary of at most SAMPLE_CHUNK) and forms its masses itself; qbuf,
+// class_mass and the others are not touched.  (1536 logits: 3.1 and 15.1 us as two launches with some 60 barriers in
+// the second, 8.0 as one with the classes' running sums found once and up to 64 candidates sorted by one wave.)
+template <bool ALONE>
 __global__ void __launch_bounds__(SAMPLE_THREADS)
-sample_pick_k(const float *__restrict__ logits, int V, double top_p, const u64 *__restrict__ omega,
+sample_pick_k(const float *__restrict__ logits, int V, double temperature, double top_p, const u64 *__restrict__ omega,
               const unsigned *__restrict__ qbuf, u64 *__restrict__ class_mass, u64 *__restrict__ cand,
               unsigned *__restrict__ cand_count, unsigned *__restrict__ arrive, u64 *__restrict__ best) {
-  __shared__ u64 s_first[SAMPLE_BINS], s_keys[SAMPLE_CAP], s_run[SAMPLE_CAP], s_wave[SAMPLE_WAVES], s_pick[3];
+  __shared__ u64 s_first[SAMPLE_BINS], s_keys[SAMPLE_CAP], s_run[SAMPLE_CAP], s_wave[SAMPLE_WAVES], s_pick[3], s_found[3][3];
   __shared__ int s_cnt[SAMPLE_WAVES], s_n, s_slot, s_last;
+  constexpr int PER = SAMPLE_CHUNK / SAMPLE_THREADS;
+  static_assert(sizeof(unsigned) * SAMPLE_CHUNK <= sizeof(s_run), "a row of masses takes the place of the running sums");
   const int row = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const float *lg = logits + (size_t)row * V;
-  const unsigned *q = qbuf + (size_t)row * V;
+  const unsigned *q = ALONE ? (const unsigned *)s_run : qbuf + (size_t)row * V;
   u64 *row_mass = class_mass + (size_t)row * SAMPLE_BINS;
   u64 *row_cand = cand + (size_t)row * SAMPLE_CAP;
+  const int c0 = blockIdx.x * SAMPLE_CHUNK;
+  const u64 word = omega[row];
   float mx;
   if (!row_max(best[row], mx)) return;
 
   // ---- every workgroup: total, target, the classes that can matter
-  u64 mine = 0;
-  for (int b = threadIdx.x; b < SAMPLE_BINS; b += SAMPLE_THREADS) {
-    const u64 h = row_mass[b];
-    s_first[b] = h;
-    mine += h;
+  unsigned mass[PER];
+  if constexpr (ALONE) {
+    float l[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int i = j * SAMPLE_THREADS + threadIdx.x;
+      l[j] = lg[i < V ? i : 0];
+    }
+    for (int b = threadIdx.x; b < SAMPLE_BINS; b += SAMPLE_THREADS) s_first[b] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int i = j * SAMPLE_THREADS + threadIdx.x;
+      mass[j] = 0u;
+      if (j * SAMPLE_THREADS < V) {   // (whole waves vote)
+        if (i < V) mass[j] = mass_of(l[j], mx, temperature);
+        hist_add(s_first, mass[j] != 0, mass[j] ? mass_class(mass[j]) : 0u, mass[j]);
+      }
+      ((unsigned *)s_run)[i] = mass[j];
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int i = c0 + j * SAMPLE_THREADS + threadIdx.x;
+      mass[j] = i < V ? q[i] : 0u;
+    }
+    for (int b = threadIdx.x; b < SAMPLE_BINS; b += SAMPLE_THREADS) s_first[b] = row_mass[b];
   }
   if (threadIdx.x == 0) s_n = 0;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
-  if (lane == 0) s_wave[wave] = mine;
   __syncthreads();
-  u64 total = 0;
-  for (int w = 0; w < SAMPLE_WAVES; ++w) total += s_wave[w];
+  ClassRun classes;
+  const u64 total = classes.init(s_first, s_wave);
   if (total == 0) return;   // (an infinite logit leaves no masses to draw from: the arg-max stands)
   u64 target = (u64)ceil(top_p * (double)total);
   target = target < 1 ? 1 : (target > total ? total : target);
-  const u64 word = omega[row];
-  u64 above_cut, unused;
-  const unsigned c_cut = pick_digit(s_first, SAMPLE_BINS, target, s_wave, s_pick, above_cut);
+  classes.find(target, s_found[0]);
+  __syncthreads();
+  const unsigned c_cut = (unsigned)s_found[0][0];
+  const u64 above_cut = s_found[0][1];
   // target <= M <= mass through class c_cut, and x = floor(word * M / 2^64) grows with M
-  const u64 x_lo = __umul64hi(word, target), x_hi = __umul64hi(word, above_cut + s_first[c_cut]);
-  const unsigned c_hi = pick_digit(s_first, SAMPLE_BINS, x_lo + 1, s_wave, s_pick, unused);
-  const unsigned c_lo = pick_digit(s_first, SAMPLE_BINS, x_hi + 1, s_wave, s_pick, unused);
+  const u64 x_lo = __umul64hi(word, target), x_hi = __umul64hi(word, above_cut + s_found[0][2]);
+  classes.find(x_lo + 1, s_found[1]);
+  classes.find(x_hi + 1, s_found[2]);
+  __syncthreads();
+  const unsigned c_hi = (unsigned)s_found[1][0], c_lo = (unsigned)s_found[2][0];
 
   // ---- this workgroup's candidates, then into the row's list
-  const int c0 = blockIdx.x * SAMPLE_CHUNK;
 #pragma unroll
-  for (int j = 0; j < SAMPLE_CHUNK / SAMPLE_THREADS; ++j) {
+  for (int j = 0; j < PER; ++j) {
     const int i = c0 + j * SAMPLE_THREADS + threadIdx.x;
-    const unsigned v = i < V ? q[i] : 0u;
+    const unsigned v = mass[j];
     if (v != 0) {
       const unsigned cls = mass_class(v);
       if (cls == c_cut || (cls >= c_lo && cls <= c_hi)) {
@@ -270,11 +349,8 @@ sample_pick_k(const float *__restrict__ logits, int V, double top_p, const u64 *
     }
   }
   __syncthreads();
-  const int n_local = s_n;
-  // (a row of one workgroup, i.e. a vocabulary of at most SAMPLE_CHUNK, has nobody to wait for and its
-  // candidates in LDS already: 17.4 -> 15.3 us at 1536 logits)
-  const bool alone = gridDim.x == 1;
-  if (!alone) {
+  if constexpr (!ALONE) {
+    const int n_local = s_n;
     if (threadIdx.x == 0 && n_local > 0)
       s_slot = (int)__hip_atomic_fetch_add(cand_count + row, (unsigned)n_local, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
@@ -299,18 +375,55 @@ sample_pick_k(const float *__restrict__ logits, int V, double top_p, const u64 *
     }
     __syncthreads();
     if (!s_last) return;
+    // the last workgroup of the row (every workgroup has read the class masses by now)
+    for (int b = threadIdx.x; b < SAMPLE_BINS; b += SAMPLE_THREADS) row_mass[b] = 0;
   }
-
-  // ---- the last workgroup of the row (every workgroup has read the class masses by now)
-  for (int b = threadIdx.x; b < SAMPLE_BINS; b += SAMPLE_THREADS) row_mass[b] = 0;
   const int n = s_n;
+  if (n <= 64) {
+    // one wave sorts the candidates, largest key first, one per lane; the others wait to be asked for a class
+    u64 key = 0, run = 0;
+    if (wave == 0) {
+      if (lane < n) key = ALONE ? s_keys[lane] : __hip_atomic_load(row_cand + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int k = 2; k <= 64; k <<= 1)
+#pragma unroll
+        for (int j = k >> 1; j > 0; j >>= 1) {
+          const u64 other = __shfl_xor(key, j, 64);
+          const bool larger_here = ((lane & j) == 0) == ((lane & k) == 0);
+          key = larger_here == (key > other) ? key : other;
+        }
+      run = key >> 32;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const u64 up = __shfl_up(run, o, 64);
+        if (lane >= o) run += up;
+      }
+      // the nucleus ends inside class c_cut; the draw ends inside the class that holds x + 1
+      u64 through;
+      wave_walk(key, run, c_cut, target - above_cut, through);
+      if (lane == 0) s_pick[0] = __umul64hi(word, above_cut + through);
+    }
+    __syncthreads();
+    const u64 x = s_pick[0];
+    classes.find(x + 1, s_found[0]);
+    __syncthreads();
+    if (wave == 0) {
+      u64 through;
+      const u64 k = wave_walk(key, run, (unsigned)s_found[0][0], x + 1 - s_found[0][1], through);
+      if (lane == 0) {
+        const int tok = (int)(0xffffffffu - (unsigned)(k & 0xffffffffull));
+        best[row] = argmax_key(lg[tok], tok);
+      }
+    }
+    return;
+  }
   if (n <= SAMPLE_CAP) {
     // candidates into LDS, padded with zero keys (they sort last) to a power of two
     int np = 64;
     while (np < n) np <<= 1;
     for (int i = threadIdx.x; i < np; i += SAMPLE_THREADS)
       if (i >= n) s_keys[i] = 0ull;
-      else if (!alone) s_keys[i] = __hip_atomic_load(row_cand + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else if (!ALONE) s_keys[i] = __hip_atomic_load(row_cand + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // bitonic sort, largest key first
     for (int k = 2; k <= np; k <<= 1)
       for (int j = k >> 1; j > 0; j >>= 1) {
@@ -341,13 +454,12 @@ sample_pick_k(const float *__restrict__ logits, int V, double top_p, const u64 *
       if (i0 < np) s_run[i0] = before + q0;
       if (i0 + 1 < np) s_run[i0 + 1] = before + q0 + q1;
     }
-    // the nucleus ends inside class c_cut; the draw ends inside the class that holds x + 1
     class_walk(s_keys, s_run, np, c_cut, target - above_cut, s_pick);
     const u64 nucleus_mass = above_cut + s_pick[1];
     const u64 x = __umul64hi(word, nucleus_mass);
-    u64 above_tok;
-    const unsigned c_tok = pick_digit(s_first, SAMPLE_BINS, x + 1, s_wave, s_pick, above_tok);
-    class_walk(s_keys, s_run, np, c_tok, x + 1 - above_tok, s_pick);
+    classes.find(x + 1, s_found[0]);
+    __syncthreads();
+    class_walk(s_keys, s_run, np, (unsigned)s_found[0][0], x + 1 - s_found[0][1], s_pick);
     if (threadIdx.x == 0) {
       const int tok = (int)(0xffffffffu - (unsigned)(s_pick[0] & 0xffffffffull));
       best[row] = argmax_key(lg[tok], tok);

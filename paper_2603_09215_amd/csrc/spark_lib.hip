@@ -1165,12 +1165,16 @@ int enqueue_step(spark_ctx *c, int n, int n_upper, int n_ee, int n_full, const i
     float *logits = at<float>(c, c->lo.logits);
     unsigned *masses = at<unsigned>(c, c->lo.sample_q);
     unsigned long long *class_mass = at<unsigned long long>(c, c->lo.sample_hist);
-    sample_mass_k<<<grid, SAMPLE_THREADS, 0, c->stream>>>(logits, c->dv.V, (double)c->temperature, masses,
-                                                          class_mass, best);
-    sample_pick_k<<<grid, SAMPLE_THREADS, 0, c->stream>>>(
-        logits, c->dv.V, (double)c->top_p, rand_dev, masses, class_mass,
-        at<unsigned long long>(c, c->lo.sample_cand), at<unsigned>(c, c->lo.sample_count),
-        at<unsigned>(c, c->lo.sample_arrive), best);
+    u64 *cand = at<u64>(c, c->lo.sample_cand);
+    unsigned *count = at<unsigned>(c, c->lo.sample_count), *arrive = at<unsigned>(c, c->lo.sample_arrive);
+    if (grid.x == 1) {
+      sample_pick_k<true><<<grid, SAMPLE_THREADS, 0, c->stream>>>(logits, c->dv.V, (double)c->temperature, (double)c->top_p, rand_dev, masses,
+                                                                 class_mass, cand, count, arrive, best);
+    } else {
+      sample_mass_k<<<grid, SAMPLE_THREADS, 0, c->stream>>>(logits, c->dv.V, (double)c->temperature, masses, class_mass, best);
+      sample_pick_k<false><<<grid, SAMPLE_THREADS, 0, c->stream>>>(logits, c->dv.V, (double)c->temperature, (double)c->top_p, rand_dev, masses,
+                                                                  class_mass, cand, count, arrive, best);
+    }
     if ((rc = prof_end(c, SPARK_KC_SAMPLE))) return rc;
   }
   return SPARK_OK;

@@ -112,6 +112,22 @@ def test_equal_logits_over_a_larger_vocabulary(sb):
     sp.close()
 
 
+@pytest.mark.parametrize("vocab", [(20, 12), (40, 24), (41, 24), (1000, 536), (2048, 1), (3000, 1096)])
+def test_equal_logits_in_one_workgroup(sb, vocab):
+    """a vocabulary that one workgroup has whole, all masses equal, so that all of it are candidates: up to 64
+    sorted by one wave, up to 2048 in LDS, more by the radix descent over masses that lie in LDS"""
+    import dataclasses
+    say(f"case sampling with all of {sum(vocab)} logits equal")
+    shape = dataclasses.replace(wl.TINY.shape, vocab_text=vocab[0], vocab_speech=vocab[1])
+    weights = wl.make_weights(shape, seed=4, gain_std=0.1)
+    weights["lm_head"][:] = 0
+    weights["lens_head"][:] = 0
+    sp = sb.Spark(shape, wl.TINY.schedule, weights, max_batch=2, max_seq_len=64, kv_page_tokens=16)
+    moved, sizes = run_sampled(sp, shape, wl.TINY.schedule, 2, 12, 0.7, 0.9, 14, f"equal {sum(vocab)}")
+    assert min(sizes) == max(sizes) == int(np.ceil(f32(0.9) * sum(vocab)))
+    sp.close()
+
+
 def test_chunked_free_running_sampled_decode(sb):
     """several steps per call, no teacher forcing: the drawn token is the next input.  The oracle
     replays the GPU's tokens; its own logits (1e-4 away) must draw the same token unless the draw
