@@ -308,22 +308,22 @@ struct AttnPiece {
   attn_bf16x8_t k[4];
 };
 
-template <int HD>
+template <int HD, bool ONE_PAGE>
 __device__ __forceinline__ void attn_piece_load(AttnPiece &pc, const KVView &kv, const bf16_t *pool, int seq,
-                                                int layer, int hk, int t0, int n_tok, bool one_page,
+                                                int layer, int hk, int t0, int n_tok,
                                                 int tid, int wave, int col, int quad) {
   // tokens beyond the context read token t0 instead (it exists) and are masked later.  With pages
   // of a multiple of 64 tokens the piece lies inside one page: one address for the workgroup.
-  const size_t piece_k = one_page ? kv_elem_offset(kv, seq, t0, layer, 0, hk) : 0;
-  const size_t piece_v = one_page ? kv_elem_offset(kv, seq, t0, layer, 1, hk) : 0;
+  const size_t piece_k = ONE_PAGE ? kv_elem_offset(kv, seq, t0, layer, 0, hk) : 0;
+  const size_t piece_v = ONE_PAGE ? piece_k + (size_t)kv.n_kv_heads * kv.page_tokens * HD : 0;
 #pragma unroll
   for (int it = 0; it < 4; ++it) {
     const int t = it * 16 + (tid >> 4), tt = t < n_tok ? t : 0;
-    const size_t o = one_page ? piece_v + (size_t)tt * HD : kv_elem_offset(kv, seq, t0 + tt, layer, 1, hk);
+    const size_t o = ONE_PAGE ? piece_v + (size_t)tt * HD : kv_elem_offset(kv, seq, t0 + tt, layer, 1, hk);
     pc.v[it] = *(const attn_u32x4_t *)(pool + o + (tid & 15) * 8);
   }
   const int t = 16 * wave + col, tt = t < n_tok ? t : 0;
-  const size_t o = one_page ? piece_k + (size_t)tt * HD : kv_elem_offset(kv, seq, t0 + tt, layer, 0, hk);
+  const size_t o = ONE_PAGE ? piece_k + (size_t)tt * HD : kv_elem_offset(kv, seq, t0 + tt, layer, 0, hk);
   const bf16_t *kp = pool + o + quad * 8;
 #pragma unroll
   for (int s = 0; s < 4; ++s) pc.k[s] = __builtin_bit_cast(attn_bf16x8_t, *(const attn_u32x4_t *)(kp + 32 * s));
@@ -333,10 +333,13 @@ __device__ __forceinline__ void attn_piece_load(AttnPiece &pc, const KVView &kv,
 // dependent round trips (row descriptor, page table, K/V, partial, arrival), so with many rows it
 // pays to put several pieces behind one such chain; the pieces are folded with a running maximum.
 // TEAMS = 2: two teams of four waves take the even and the odd pieces and are combined at the end.
+// ONE_PAGE: pages hold a multiple of 64 tokens.  Known when the kernel is compiled: with both ways of finding
+// an address in the loop a piece had 400 vector instructions, forty of them 32-bit products (batch of 32, contexts of 256 to
+// 2048: 27.1 -> 23.4 us a launch, of 8 15.0 -> 13.7, one row of 512 tokens 8.5 -> 8.3).
 // A piece is a chain of four barriers, about 3 us, and long contexts make as few workgroups as CUs
 // (more of them leave more partial results to one workgroup's merge): a step of eight sequences of 8192
 // tokens 18.63 ms with one team and eight pieces, 17.89 with two teams and ten.
-template <int HD, int TEAMS, bool PARTS>
+template <int HD, int TEAMS, bool PARTS, bool ONE_PAGE>
 __global__ void __launch_bounds__(ATTN_THREADS * TEAMS)
 attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbuf, KVView kv, int layer,
                  int nq, int kv_group, int heads_per_wg, int n_splits, int pieces, float scale,
@@ -364,14 +367,13 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
   const int col = lane & 15, quad = lane >> 4;    // operand column / row, and which eight of a 32-wide step
   const int hq0 = hk * kv_group + h_first;
   const bf16_t *pool = (const bf16_t *)kv.pool;
-  const bool one_page = (kv.page_tokens & (ATTN_SLICE - 1)) == 0;
   const int n_pieces = min(pieces, (rd.pos - split * span) / ATTN_SLICE + 1);   // pieces the context reaches
 
   const int trips = (n_pieces + TEAMS - 1) / TEAMS;
   // (a team without a piece left loads the last one again and leaves it)
   auto load_piece = [&](AttnPiece &pc, int j) {
     const int t0 = split * span + min(j, n_pieces - 1) * ATTN_SLICE;
-    attn_piece_load<HD>(pc, kv, pool, rd.seq, layer, hk, t0, min(ATTN_SLICE, rd.pos + 1 - t0), one_page, tid, wave, col, quad);
+    attn_piece_load<HD, ONE_PAGE>(pc, kv, pool, rd.seq, layer, hk, t0, min(ATTN_SLICE, rd.pos + 1 - t0), tid, wave, col, quad);
   };
   AttnPiece cur;
   load_piece(cur, team);

@@ -501,8 +501,13 @@ int launch_attention_rows(spark_ctx *c, const RowDesc *rows, int m, int m_pass, 
     const int heads_per_wg = (tasks < c->n_cu / 2 && c->dv.group > 8) ? 8 : c->dv.group;
     const int wg_per_kv = (c->dv.group + heads_per_wg - 1) / heads_per_wg;
     row_max.n = c->cfg.n_kv_heads * wg_per_kv * shape.teams * (ATTN_THREADS / 64);
-    const auto kern = out.part_units ? (shape.teams == 2 ? attn_rows_mfma_k<128, 2, true> : attn_rows_mfma_k<128, 1, true>)
-                                     : (shape.teams == 2 ? attn_rows_mfma_k<128, 2, false> : attn_rows_mfma_k<128, 1, false>);
+    const bool one_page = c->cfg.kv_page_tokens % ATTN_SLICE == 0;
+    auto pick = [&](auto two_teams, auto parts) {
+      return one_page ? attn_rows_mfma_k<128, two_teams ? 2 : 1, parts, true> : attn_rows_mfma_k<128, two_teams ? 2 : 1, parts, false>;
+    };
+    const std::true_type yes{};
+    const std::false_type no{};
+    const auto kern = out.part_units ? (shape.teams == 2 ? pick(yes, yes) : pick(no, yes)) : (shape.teams == 2 ? pick(yes, no) : pick(no, no));
     kern<<<dim3((splits + pieces - 1) / pieces, c->cfg.n_kv_heads * wg_per_kv, m), ATTN_THREADS * shape.teams, 0, c->stream>>>(
         rows, q, kv_view(c), layer, c->cfg.n_q_heads, c->dv.group, heads_per_wg, c->dv.n_splits, pieces, 1.0f / sqrtf(128.0f),
         at<float>(c, c->lo.part), at<int>(c, c->lo.arrivals), out, row_max);
