@@ -222,7 +222,8 @@ inline int direct_tiles(int m, int blocks, int n_cu, bool heads) {
   return nt;
 }
 
-// mfma_direct_k with its k cut: ranges (1: it is not cut) and chunks in each
+// A long k with few tasks (down) would be streamed by few CUs, each reading all activations of a long row: it is cut
+// over the CUs.  Ranges (1: it is not cut) and chunks in each
 inline int direct_split(int m, int n_in, int n_tasks, int n_cu, int &chunks_per_split) {
   const int n_chunks = ceil_div(n_in, MG_KC), groups = ceil_div(ceil_div(n_tasks, TG_TASKS), TD_CUT_TILES);
   const size_t fit = MFMA_PARTIAL_BYTES / range_bytes(groups, TD_CUT_TILES * TG_TASKS, ceil_div(m, 8) * 8);
@@ -233,6 +234,32 @@ inline int direct_split(int m, int n_in, int n_tasks, int n_cu, int &chunks_per_
   if (split < 1) split = 1;
   chunks_per_split = ceil_div(n_chunks, split);
   return ceil_div(n_chunks, chunks_per_split);
+}
+
+// mfma_direct_k with its k cut: tiles of a workgroup, workgroups per range, ranges (1: it is not cut) and chunks in each
+struct DirectCut { int tiles, groups, split, chunks_per_split; };
+// bytes of the ranges' sums: both weight rows of every task, for whole operands of 16 rows
+constexpr size_t direct_partial_bytes(int m, const DirectCut &c) {
+  return sizeof(float) * (size_t)c.split * c.groups * c.tiles * 2 * TG_TASKS * (ceil_div(m, 16) * 16);
+}
+// whole_k: the longest k that counts as short.  Of those, what leaves half of the CUs idle (o) is cut in two from 9 rows
+// on: 16 rows 12.60 -> 12.51 ms a step, 32 rows 16.05 -> 15.87, 48 rows 17.09 -> 16.85; 3 and 8 rows are level.  What fills
+// more than half would need a second round of CUs (q/k/v, 288 halves on 256 CUs: a step 1 % slower).
+inline DirectCut direct_cut(int m, int n_in, int n_tasks, int n_cu, int whole_k) {
+  const int n_chunks = ceil_div(n_in, MG_KC), blocks = ceil_div(n_tasks, TG_TASKS);
+  DirectCut c{1, blocks, 1, n_chunks};
+  if (n_in > whole_k && blocks < 4 * n_cu) {
+    c.tiles = TD_CUT_TILES;
+    c.groups = ceil_div(blocks, TD_CUT_TILES);
+    c.split = direct_split(m, n_in, n_tasks, n_cu, c.chunks_per_split);
+  } else if (n_in <= whole_k && m > 8 && 2 * blocks <= n_cu && n_chunks >= 16) {
+    c.split = 2;
+  }
+  while (c.split > 1 && direct_partial_bytes(m, c) > MFMA_PARTIAL_BYTES) --c.split;
+  if (c.split < 1) c.split = 1;
+  c.chunks_per_split = ceil_div(n_chunks, c.split);
+  c.split = ceil_div(n_chunks, c.chunks_per_split);
+  return c;
 }
 
 // Rows that go through the layers together at most: the partial sums of a residual projection

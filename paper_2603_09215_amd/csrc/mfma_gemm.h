@@ -1218,8 +1218,11 @@ mfma_finish_tile_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, int n_
 // workgroups on a CU, whose starts and ends run under the others' streaming.  From 9 rows on fetching all
 // activations in every workgroup costs more than that gains (gate/up of 16 rows 52.4 us with one tile, 49.0 with
 // five): then NT makes one round of CUs, or as few as can be, of about equal size.  Either way a workgroup
-// takes all of k, and there are no partial sums and no finishing launch.
-// Only a long k with few tasks (down) is cut: CUT writes partial sums.
+// takes all of k, and there are no partial sums.
+// Where that leaves CUs idle k is cut (CUT): a long one with few tasks (down) into as many ranges as fill the chip, and
+// that of o in two from 9 rows on.  The last workgroup to arrive adds the ranges up; a launch that did so took 5 us (down
+// of 136 MB: 8 rows 24.5 and 4.9 us in two launches, 27.6 in one; 48 rows 40.5 and 5.2, 45.6, but the next
+// launch no longer waits for a small one to start and drain).
 //
 // (48 rows: gate/up of 271 MB 58 us, where mfma_tiled_k and its finishing launch take 58 and 12; a quarter of the heads 61
 // against 87; down 37 and 5 against 40 and 8; q/k/v and o level.  With 64 the sums of five tiles spill.)
@@ -1250,7 +1253,7 @@ template <int NT, int COLS, typename Epi, bool CUT>
 __global__ void __launch_bounds__(64 * TD_WAVES, 1)
 mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__ wdown,
               const RowDesc *__restrict__ rows, int m_rows, ProjIn in, int n_in, int n_tasks, int n_groups,
-              int chunks_per_split, float *__restrict__ part, int m_pitch) {
+              int chunks_per_split, float *__restrict__ part, int *__restrict__ arrivals) {
   static_assert(COLS % 16 == 0 && COLS <= OP_ROWS, "operands of 16 activation rows");
   constexpr int CG = COLS / 16, KS = 32, STEPS = MG_KC / KS, RING = td_ring(NT), THREADS = 64 * TD_WAVES, PIECES = td_pieces(NT, COLS);
   extern __shared__ uint4 td_smem[];
@@ -1417,53 +1420,106 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
     for (int w = 1; w < PIECES; ++w) y += s_t[((w * NT + q) * COLS + m) * TD_PITCH + row];
     return y * x_down * s_wdown[q * 32 + row];
   };
-  if constexpr (CUT) {
-    // rows fastest across the lanes, as the finishing launch reads them
-    float *base = part + (size_t)blockIdx.x * (TG_TASKS * NT) * 2 * m_pitch;
-    const int m = threadIdx.x % COLS;
-    const float x_down = scale_down(s_exp[m]);
-    if (m < m_pitch) {
+  // 16 lanes finish a row's tasks of one tile after the other
+  auto task_of = [&](int q) { return (group * NT + q) * TG_TASKS + t; };
+  typedef decltype(load_old(epi, 0, 0, RowDesc{}, true)) Old;
+  // (requested together: the stores between them would hold them back)
+  auto load_olds = [&](int m, const RowDesc &rd, Old *old) {
 #pragma unroll
-      for (int i = threadIdx.x / COLS; i < NT * TG_TASKS; i += THREADS / COLS) {
-        const int q = i / TG_TASKS, r = i % TG_TASKS;
-        float *p = base + (size_t)i * 2 * m_pitch + m;
-        p[0] = sum(q, r, m, x_down);
-        p[m_pitch] = sum(q, TG_TASKS + r, m, x_down);
+    for (int q = 0; q < NT; ++q) old[q] = load_old(epi, m < m_rows && task_of(q) < n_tasks ? task_of(q) : 0, min(m, m_rows - 1), rd, true);
+  };
+  auto hand_on = [&](int m, const RowDesc &rd, const typename Epi::State &st) {
+    const bool row_live = m < m_rows;
+    if constexpr (EpiHasLocalReduce<Epi>::value) {
+      // the heads' arg-max: one atomic per row and workgroup
+      unsigned long long best = st.best;
+#pragma unroll
+      for (int o = TG_TASKS / 2; o > 0; o >>= 1) {
+        const unsigned long long other =
+            ((unsigned long long)(uint32_t)__shfl_xor((int)(best >> 32), o, 64) << 32) | (uint32_t)__shfl_xor((int)best, o, 64);
+        if (other > best) best = other;
       }
+      if (t == 0 && row_live) epi.end_reduced(rd, best);
+    } else {
+      hand_on_row<TG_TASKS>(epi, m, row_live, st, group);
     }
-  } else {
-    // tasks fastest: 16 lanes finish a row's tasks of one tile after the other
+  };
+  if constexpr (CUT) {
+    // This range's sums go to memory, written through; the workgroup that arrives last adds up the ranges, in
+    // their order, and runs the epilogue.
+    const int n_split = gridDim.x / n_groups;
+    auto place = [&](int s, int q, int m) { return part + (((size_t)(s * n_groups + group) * COLS + m) * NT + q) * 32 + t; };
+    RowDesc rd[CG];
+    Old old[CG][NT];
 #pragma unroll
     for (int g = 0; g < CG; ++g) {
       const int m = m0 + 16 * g;
-      const bool row_live = m < m_rows;
+      const float x_down = scale_down(s_exp[m]);
+#pragma unroll
+      for (int q = 0; q < NT; ++q)
+        if (m < m_rows) {
+          store_device_scope(place(split, q, m), sum(q, t, m, x_down));
+          store_device_scope(place(split, q, m) + TG_TASKS, sum(q, TG_TASKS + t, m, x_down));
+        }
+      rd[g] = EARLY > 0 ? early[EARLY > 0 ? g : 0] : rows[min(m, m_rows - 1)];
+      load_olds(m, rd[g], old[g]);
+    }
+    wait_memory_ops();
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const int last = __hip_atomic_fetch_add(arrivals + group, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_split - 1;
+      if (last) {
+        __hip_atomic_store(arrivals + group, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      }
+      s_exp[0] = last;
+    }
+    __syncthreads();
+    if (!s_exp[0]) return;
+#pragma unroll
+    for (int g = 0; g < CG; ++g) {
+      const int m = m0 + 16 * g, m_read = min(m, m_rows - 1);
+      typename Epi::State st;
+      epi.init(st);
+      float y0[NT], y1[NT];
+#pragma unroll
+      for (int q = 0; q < NT; ++q) y0[q] = y1[q] = 0.f;
+      for (int s0 = 0; s0 < n_split; s0 += 4) {   // four ranges' loads at a time
+        float a[4][NT], b[4][NT];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int q = 0; q < NT; ++q) {
+            const float *p = place(min(s0 + i, n_split - 1), q, m_read);
+            a[i][q] = p[0];
+            b[i][q] = p[TG_TASKS];
+          }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int q = 0; q < NT; ++q)
+            if (s0 + i < n_split) { y0[q] += a[i][q]; y1[q] += b[i][q]; }
+      }
+#pragma unroll
+      for (int q = 0; q < NT; ++q)
+        if (m < m_rows && task_of(q) < n_tasks) finish_pair(epi, task_of(q), m, rd[g], y0[q], y1[q], old[g][q], st);
+      hand_on(m, rd[g], st);
+    }
+  } else {
+#pragma unroll
+    for (int g = 0; g < CG; ++g) {
+      const int m = m0 + 16 * g;
       const RowDesc rd = EARLY > 0 ? early[EARLY > 0 ? g : 0] : rows[min(m, m_rows - 1)];
       const float x_down = scale_down(s_exp[m]);
       typename Epi::State st;
       epi.init(st);
-      decltype(load_old(epi, 0, 0, rd, true)) old[NT];   // (requested together: the stores between them would hold them back)
+      Old old[NT];
+      load_olds(m, rd, old);
 #pragma unroll
-      for (int q = 0; q < NT; ++q) {
-        const int task = (group * NT + q) * TG_TASKS + t;
-        old[q] = load_old(epi, row_live && task < n_tasks ? task : 0, min(m, m_rows - 1), rd, true);
-      }
-#pragma unroll
-      for (int q = 0; q < NT; ++q) {
-        const int task = (group * NT + q) * TG_TASKS + t;
-        if (row_live && task < n_tasks) finish_pair(epi, task, m, rd, sum(q, t, m, x_down), sum(q, TG_TASKS + t, m, x_down), old[q], st);
-      }
-      if constexpr (EpiHasLocalReduce<Epi>::value) {
-        // the heads' arg-max: one atomic per row and workgroup
-#pragma unroll
-        for (int o = TG_TASKS / 2; o > 0; o >>= 1) {
-          const unsigned long long other =
-              ((unsigned long long)(uint32_t)__shfl_xor((int)(st.best >> 32), o, 64) << 32) | (uint32_t)__shfl_xor((int)st.best, o, 64);
-          if (other > st.best) st.best = other;
-        }
-        if (t == 0 && row_live) epi.end_reduced(rd, st.best);
-      } else {
-        hand_on_row<TG_TASKS>(epi, m, row_live, st, group);
-      }
+      for (int q = 0; q < NT; ++q)
+        if (m < m_rows && task_of(q) < n_tasks)
+          finish_pair(epi, task_of(q), m, rd, sum(q, t, m, x_down), sum(q, TG_TASKS + t, m, x_down), old[q], st);
+      hand_on(m, rd, st);
     }
   }
 }

@@ -107,7 +107,7 @@ struct spark_ctx {
   bool use_mfma = true;        // "mfma" = 0 keeps every row count on the vector kernels
   int tiled_row_blocks = 4;     // blocks of 32 rows in a tile of mfma_tiled_k, at most
   int direct_max_rows = OP_ROWS;   // rows up to which mfma_direct_k runs
-  int direct_whole_k = 8192;    // ... and the longest k that it never cuts
+  int direct_whole_k = 8192;    // ... and the longest k that it cuts in two at most
   int mfma_xcd_max_split = 4;  // row tiles share an XCD when k has at most this many ranges
   int mfma_small_tiles = 32;   // launches of mfma_rows_k with fewer 8-wave tiles use 4-wave workgroups
   int mfma_min_rows = MFMA_MIN_ROWS, mfma_min_rows_copy = MFMA_MIN_ROWS_COPY;   // ("mfma_min_rows" sets both)
@@ -740,7 +740,7 @@ int launch_direct_cols(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m,
   }
   kern<<<groups * split, 64 * TD_WAVES, lds, c->stream>>>(epi, at<f16_t>(c, c->lo.tiled) + w.elems, at<float>(c, c->lo.wdown) + w.blocks * 32,
                                                           rows, m, in, n_in, n_tasks, groups, cps, at<float>(c, c->lo.mfma_part),
-                                                          (int)align_up(m, 8));
+                                                          at<int>(c, c->lo.arrivals));   // (zero between launches, attention's too)
   HIP_TRY(c, hipGetLastError());
   return SPARK_OK;
 }
@@ -754,21 +754,14 @@ int launch_direct_tiles(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m
 template <typename Epi>
 int launch_direct(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n_in, int n_tasks, const ProjIn &in,
                   const TiledMatrix &w, int *max_words) {
-  const int n_chunks = (n_in + MG_KC - 1) / MG_KC, blocks = (n_tasks + TG_TASKS - 1) / TG_TASKS, m_pitch = (int)align_up(m, 8);
-  // A long k with few tasks (down) would be streamed by few CUs, each reading all activations of a
-  // long row: its k is cut over the CUs.  (q/k/v and o, with a k of 3584 and 4096, are as fast on
-  // half of the CUs as cut over all of them, and need no second launch.)
+  const int n_chunks = (n_in + MG_KC - 1) / MG_KC, blocks = (n_tasks + TG_TASKS - 1) / TG_TASKS;
   if constexpr (!EpiHasLocalReduce<Epi>::value && !EpiRow<Epi>::max || EpiRow<Epi>::sum) {
-    if (n_in > c->direct_whole_k && blocks < 4 * c->n_cu) {
-      int cps;
-      const int groups = ceil_div(blocks, TD_CUT_TILES), split = direct_split(m, n_in, n_tasks, c->n_cu, cps);
-      if (split > 1) {
-        if (int rc = partials_fit(c, split * range_bytes(groups, TD_CUT_TILES * TG_TASKS, m_pitch))) return rc;
-        if (max_words) *max_words = (n_tasks + 31) / 32;
-        if (int rc = launch_direct_tiles<TD_CUT_TILES, true>(c, epi, rows, m, n_in, n_tasks, in, w, groups, split, cps)) return rc;
-        return launch_finish(c, epi, rows, m, n_tasks, PartialSums{at<float>(c, c->lo.mfma_part), split, m_pitch, TD_CUT_TILES * TG_TASKS, OP_ROWS,
-                                                                   TileCover{groups, 1, 0, groups, split, cps, m_pitch, 1, 0}});
-      }
+    const DirectCut cut = direct_cut(m, n_in, n_tasks, c->n_cu, c->direct_whole_k);
+    if (cut.split > 1 && (size_t)cut.groups <= (size_t)c->dv.max_rows * c->cfg.n_q_heads) {   // (one arrival word per group)
+      if (int rc = partials_fit(c, direct_partial_bytes(m, cut))) return rc;
+      if (max_words) *max_words = cut.groups;
+      return cut.tiles == 1 ? launch_direct_tiles<1, true>(c, epi, rows, m, n_in, n_tasks, in, w, cut.groups, cut.split, cut.chunks_per_split)
+                            : launch_direct_tiles<TD_CUT_TILES, true>(c, epi, rows, m, n_in, n_tasks, in, w, cut.groups, cut.split, cut.chunks_per_split);
     }
   }
   const int nt = direct_tiles(m, blocks, c->n_cu, EpiHasLocalReduce<Epi>::value);

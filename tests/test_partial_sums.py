@@ -119,6 +119,44 @@ def test_covers_by_tiles_of_two_heights_take_every_block_once(tmp_path):
     assert n > 3000 and n_two > 300, out.stdout
 
 
+CUTS = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "cover.h"
+using namespace spark;
+int main() {
+  long cuts = 0, cut = 0;
+  for (int n_cu : {256, 304, 64, 8})
+    for (int n_in : {64, 128, 896, 1024, 3584, 4096, 8192, 8256, 13696, 18944})
+      for (int tasks = 8; tasks <= 20000; tasks += tasks < 5000 ? 8 : 168)
+        for (int m = 1; m <= 48; m += m < 9 ? 1 : 13)
+          for (int whole_k : {0, 8192}) {
+            const DirectCut c = direct_cut(m, n_in, tasks, n_cu, whole_k);
+            const int chunks = ceil_div(n_in, MG_KC);
+            const bool bad = c.split < 1 || c.split > MG_MAX_SPLIT || c.split * c.chunks_per_split < chunks ||      // all of k,
+                             (c.split - 1) * c.chunks_per_split >= chunks ||                                        // no empty range,
+                             c.groups * c.tiles * TG_TASKS < tasks || (c.groups - 1) * c.tiles * TG_TASKS >= tasks ||   // all tasks,
+                             (c.split > 1 && (direct_partial_bytes(m, c) > MFMA_PARTIAL_BYTES || c.groups > 2 * n_cu));
+            if (bad) { printf("%d rows, %d x %d on %d CUs: %d groups of %d, %d ranges of %d\n", m, n_in, tasks, n_cu, c.groups, c.tiles, c.split, c.chunks_per_split); return 1; }
+            ++cuts;
+            cut += c.split > 1;
+          }
+  printf("%ld checked, %ld cut\n", cuts, cut);
+  return 0;
+}
+"""
+
+
+def test_cuts_of_a_few_rows_take_every_range_and_task_once(tmp_path):
+    src, exe = tmp_path / "cuts.cpp", tmp_path / "cuts"
+    src.write_text(CUTS)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", f"-I{CSRC}", "-o", str(exe), str(src)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, out.stdout
+    n, n_cut = (int(w) for w in out.stdout.split() if w.isdigit())
+    assert n > 100_000 and n_cut > 10_000, out.stdout
+
+
 def test_partial_sums_of_every_cover_fit_their_buffer(tmp_path):
     src, exe = tmp_path / "covers.cpp", tmp_path / "covers"
     src.write_text(DRIVER)
