@@ -280,53 +280,58 @@ attn_rows_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbuf, KV
 //
 // bf16 cache, head_dim 128, up to 16 query heads per KV head, one workgroup (4 waves) per
 // (slice, KV head or half of its query heads, row); a slice is one or several 64-token pieces,
-// taken one after the other.  Per piece, v_mfma_f32_16x16x32_bf16 twice:
-//   scores   S^T[token][head] = K[token][:] . Q[head][:]   wave w takes tokens 16w .. 16w+15; the K
+// taken one after the other.  Of a piece wave w takes tokens 16w .. 16w+15, from the scores to the weighted values, with
+// a maximum and sums of its own, so that the waves wait for each other at the slice's end only:
+//   scores   S^T[token][head] = K[token][:] . Q[head][:]   v_mfma_f32_16x16x32_bf16: the K
 //            rows go from memory straight into the A operand (lane l: token l%16, eight
 //            consecutive elements at 8*(l/16) of each 32-wide step), the scaled queries, split into
 //            three bf16 parts that add up to the fp32 value (once per workgroup, handed to the
 //            waves through LDS), are the B operand;
-//   values   O[head][hd] = P[head][token] . V[token][hd]   wave w takes hd 32w .. 32w+31 over all
-//            64 tokens; P (two bf16 parts) crosses the waves through LDS in A-operand order, V is
-//            staged in LDS as it lies in the cache (token-major) and gathered column-wise, the
-//            only transposition the operation needs.
+//   values   O^T[hd][head] = V[token][hd] . P[token][head]   v_mfma_f32_16x16x16_bf16: the probabilities (two
+//            bf16 parts) are the B operand in the registers where the scores have left them, V is
+//            staged in the wave's piece of LDS as it lies in the cache (token-major) and read with the transposing
+//            LDS load, four tokens of one hd a lane.
+// (The waves used to share a piece's maximum, P and V: three barriers a piece.  A launch of 8 rows of 8192 tokens, 2 KV heads,
+// 26.5 -> 24.0 us, of 48 rows of 256 to 2048 tokens, 4 KV heads, 41.2 -> 39.5, of 32 28.2 -> 27.5; 8 rows 14.8 and one row 8.8, level.
+// What bounds it is the K and V that few bytes in flight per workgroup fetch: the old one without its arithmetic took nine
+// tenths of its time, 113 MB in 31 us.)
 // The partial it leaves and the merge are those of the vector task.
 typedef __attribute__((ext_vector_type(8))) __bf16 attn_bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float attn_f32x4_t;
 typedef unsigned int attn_u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int attn_u32x2_t __attribute__((ext_vector_type(2)));
+typedef short attn_s16x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int AM_VPITCH = 130;   // bf16 elements per V row in LDS: 65 dwords, so the four token groups of a gather hit different banks
-constexpr int AM_PPITCH = 72;    // tokens per P row in LDS (16-byte aligned rows)
+constexpr int AM_VPITCH = 132;   // bf16 elements per V row in LDS: 4 * 66 dwords lie between the four token groups of a gather, eight banks apart
+constexpr int AM_OPITCH = 132;   // floats per head of a wave's sums in LDS
 constexpr int AM_QPITCH = 136;   // elements per Q row in LDS (16-byte aligned rows, 4 dwords of skew)
 
-__device__ __forceinline__ unsigned pack_bf16(bf16_t lo, bf16_t hi) { return (unsigned)lo | ((unsigned)hi << 16); }
-
-// loads of one 64-token piece: V as the workgroup stages it, K as this wave's A operand
 struct AttnPiece {
   attn_u32x4_t v[4];
   attn_bf16x8_t k[4];
 };
 
+// loads of a wave's 16 tokens of a 64-token piece that begins with token t0 and reaches n_tok: V as the wave stages it, K as
+// its A operand
 template <int HD, bool ONE_PAGE>
 __device__ __forceinline__ void attn_piece_load(AttnPiece &pc, const KVView &kv, const bf16_t *pool, int seq,
-                                                int layer, int hk, int t0, int n_tok,
-                                                int tid, int wave, int col, int quad) {
+                                                int layer, int hk, int t0, int n_tok, int lane, int wave) {
   // tokens beyond the context read token t0 instead (it exists) and are masked later.  With pages
   // of a multiple of 64 tokens the piece lies inside one page: one address for the workgroup.
+  const int col = lane & 15, quad = lane >> 4;
   const size_t piece_k = ONE_PAGE ? kv_elem_offset(kv, seq, t0, layer, 0, hk) : 0;
   const size_t piece_v = ONE_PAGE ? piece_k + (size_t)kv.n_kv_heads * kv.page_tokens * HD : 0;
-#pragma unroll
-  for (int it = 0; it < 4; ++it) {
-    const int t = it * 16 + (tid >> 4), tt = t < n_tok ? t : 0;
-    const size_t o = ONE_PAGE ? piece_v + (size_t)tt * HD : kv_elem_offset(kv, seq, t0 + tt, layer, 1, hk);
-    pc.v[it] = *(const attn_u32x4_t *)(pool + o + (tid & 15) * 8);
-  }
   const int t = 16 * wave + col, tt = t < n_tok ? t : 0;
   const size_t o = ONE_PAGE ? piece_k + (size_t)tt * HD : kv_elem_offset(kv, seq, t0 + tt, layer, 0, hk);
   const bf16_t *kp = pool + o + quad * 8;
 #pragma unroll
   for (int s = 0; s < 4; ++s) pc.k[s] = __builtin_bit_cast(attn_bf16x8_t, *(const attn_u32x4_t *)(kp + 32 * s));
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {
+    const int t = 16 * wave + 4 * it + quad, tt = t < n_tok ? t : 0;
+    const size_t o = ONE_PAGE ? piece_v + (size_t)tt * HD : kv_elem_offset(kv, seq, t0 + tt, layer, 1, hk);
+    pc.v[it] = *(const attn_u32x4_t *)(pool + o + col * 8);
+  }
 }
 
 // `pieces` 64-token pieces per workgroup (slice = 64 * pieces tokens): a workgroup's life is mostly
@@ -336,7 +341,7 @@ __device__ __forceinline__ void attn_piece_load(AttnPiece &pc, const KVView &kv,
 // ONE_PAGE: pages hold a multiple of 64 tokens.  Known when the kernel is compiled: with both ways of finding
 // an address in the loop a piece had 400 vector instructions, forty of them 32-bit products (batch of 32, contexts of 256 to
 // 2048: 27.1 -> 23.4 us a launch, of 8 15.0 -> 13.7, one row of 512 tokens 8.5 -> 8.3).
-// A piece is a chain of four barriers, about 3 us, and long contexts make as few workgroups as CUs
+// A piece is a chain of about 3 us, and long contexts make as few workgroups as CUs
 // (more of them leave more partial results to one workgroup's merge): a step of eight sequences of 8192
 // tokens 18.63 ms with one team and eight pieces, 17.89 with two teams and ten.
 template <int HD, int TEAMS, bool PARTS, bool ONE_PAGE>
@@ -346,14 +351,14 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
                  float *__restrict__ part, int *__restrict__ arrivals, RowOut out, RowMax row_max) {
   static_assert(HD == 128, "four 32-wide steps per key row, four waves of 32 value columns");
   constexpr int PS = HD + 4;
-  __shared__ __align__(16) bf16_t s_v_all[TEAMS][ATTN_SLICE * AM_VPITCH];
-  __shared__ __align__(16) bf16_t s_p_all[TEAMS][2 * 16 * AM_PPITCH];
-  __shared__ __align__(16) bf16_t s_q[3 * 16 * AM_QPITCH];
-  __shared__ float s_max_all[TEAMS][4 * 16], s_sum_all[TEAMS][4 * 16], s_alpha_all[TEAMS][16];
+  constexpr int WAVES = ATTN_THREADS / 64 * TEAMS, VS = 16 * AM_VPITCH, V_BYTES = WAVES * VS * 2;
+  constexpr int USED = V_BYTES + 3 * 16 * AM_QPITCH * 2, O_BYTES = 4 * 16 * AM_OPITCH * 4;
+  // the waves' V and the queries; in the end, when nobody reads those any more, the sums of four waves
+  __shared__ __align__(16) char s_mem[USED > O_BYTES ? USED : O_BYTES];
+  __shared__ float s_max[WAVES * 16], s_sum[WAVES * 16];
   __shared__ int s_last;
+  bf16_t *s_q = (bf16_t *)(s_mem + V_BYTES);
   const int team = TEAMS == 1 ? 0 : threadIdx.x / ATTN_THREADS;
-  bf16_t *s_v = s_v_all[team], *s_p = s_p_all[team];
-  float *s_max = s_max_all[team], *s_sum = s_sum_all[team], *s_alpha = s_alpha_all[team];
   // blockIdx.y = (KV head, part of its query heads): with few rows and few KV heads the query
   // heads of a KV head are dealt to several workgroups, which shortens each one's merge
   const int wg_per_kv = (kv_group + heads_per_wg - 1) / heads_per_wg;
@@ -365,6 +370,7 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
   if (split * span > rd.pos) return;              // slice beyond the row's context
   const int tid = threadIdx.x % ATTN_THREADS, lane = tid & 63, wave = tid >> 6;   // in the team
   const int col = lane & 15, quad = lane >> 4;    // operand column / row, and which eight of a 32-wide step
+  bf16_t *s_v = (bf16_t *)s_mem + (threadIdx.x >> 6) * VS;   // this wave's 16 tokens
   const int hq0 = hk * kv_group + h_first;
   const bf16_t *pool = (const bf16_t *)kv.pool;
   const int n_pieces = min(pieces, (rd.pos - split * span) / ATTN_SLICE + 1);   // pieces the context reaches
@@ -373,7 +379,7 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
   // (a team without a piece left loads the last one again and leaves it)
   auto load_piece = [&](AttnPiece &pc, int j) {
     const int t0 = split * span + min(j, n_pieces - 1) * ATTN_SLICE;
-    attn_piece_load<HD, ONE_PAGE>(pc, kv, pool, rd.seq, layer, hk, t0, min(ATTN_SLICE, rd.pos + 1 - t0), tid, wave, col, quad);
+    attn_piece_load<HD, ONE_PAGE>(pc, kv, pool, rd.seq, layer, hk, t0, min(ATTN_SLICE, rd.pos + 1 - t0), lane, wave);
   };
   AttnPiece cur;
   load_piece(cur, team);
@@ -409,28 +415,30 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
     *(attn_u32x4_t *)(s_q + (2 * 16 + h) * AM_QPITCH + e0) = pl;
   }
 
-  // running state.  Score layout: lane = (head col, tokens 4*quad + i of the wave's 16);
-  // output layout: lane = (hd 32*wave + 16*t + col, heads 4*quad + i).
-  float run_max = -INFINITY, run_sum = 0.f;       // of head `col`; the sum is this wave's share
-  attn_f32x4_t oacc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  __syncthreads();
+
+  // this wave's running state, of head `col`.  Score layout: lane = (head col, tokens 4*quad + i of the wave's 16);
+  // output layout: lane = (head col, hd 16*t + 4*quad + i).
+  float run_max = -INFINITY, run_sum = 0.f;
+  attn_f32x4_t oacc[HD / 16];
+#pragma unroll
+  for (int t = 0; t < HD / 16; ++t) oacc[t] = attn_f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   for (int trip = 0; trip < trips; ++trip) {
     const int j = trip * TEAMS + team;
     const int t0 = split * span + j * ATTN_SLICE;
     const int n_tok = j < n_pieces ? min(ATTN_SLICE, rd.pos + 1 - t0) : 0;   // 0: every token is masked
-    if (trip > 0) __syncthreads();                   // the last piece's V and P have been consumed
-    // V into LDS as it lies in the cache (4-byte stores: the row pitch is an odd number of dwords)
+    // V into LDS as it lies in the cache
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
-      unsigned *dst = (unsigned *)(s_v + (it * 16 + (tid >> 4)) * AM_VPITCH + (tid & 15) * 8);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) dst[e] = cur.v[it][e];
+      attn_u32x2_t *dst = (attn_u32x2_t *)(s_v + (4 * it + quad) * AM_VPITCH + col * 8);
+      dst[0] = attn_u32x2_t{cur.v[it][0], cur.v[it][1]};
+      dst[1] = attn_u32x2_t{cur.v[it][2], cur.v[it][3]};
     }
     attn_bf16x8_t ka[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) ka[s] = cur.k[s];
     if (trip + 1 < trips) load_piece(cur, j + TEAMS);   // the next piece's loads fly during this one's arithmetic
-    __syncthreads();
 
     // scores of this wave's 16 tokens
     attn_f32x4_t sc = {0.f, 0.f, 0.f, 0.f};
@@ -451,13 +459,8 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
     }
     mw = fmaxf(mw, __shfl_xor(mw, 16, 64));
     mw = fmaxf(mw, __shfl_xor(mw, 32, 64));
-    if (quad == 0) s_max[wave * 16 + col] = mw;
-    __syncthreads();
-    const float piece_max = fmaxf(fmaxf(s_max[col], s_max[16 + col]), fmaxf(s_max[32 + col], s_max[48 + col]));
-    const float new_max = fmaxf(run_max, piece_max);   // finite once the team has had a piece: token 0 of it is real
-    const float base = TEAMS == 1 || new_max > -INFINITY ? new_max : 0.f;
+    const float new_max = fmaxf(run_max, mw), base = new_max > -INFINITY ? new_max : 0.f;   // (-inf: the wave has had no token)
     const float alpha = expf(run_max - base);          // exp(-inf) = 0 on the first piece
-    run_max = new_max;
     float pr[4], lw = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -467,122 +470,104 @@ attn_rows_mfma_k(const RowDesc *__restrict__ rows, const float *__restrict__ qbu
     lw += __shfl_xor(lw, 16, 64);
     lw += __shfl_xor(lw, 32, 64);
     run_sum = run_sum * alpha + lw;
-    if (wave == 0 && quad == 0) s_alpha[col] = alpha;
-    {
-      // probabilities as two bf16 parts (16 significant bits)
-      unsigned h[4], l[4];
+    // probabilities as two bf16 parts (16 significant bits)
+    unsigned h[4], l[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        h[i] = __float_as_uint(pr[i]) & 0xffff0000u;
-        l[i] = __float_as_uint(pr[i] - __uint_as_float(h[i])) & 0xffff0000u;
-      }
-      attn_u32x2_t ph = {(h[0] >> 16) | h[1], (h[2] >> 16) | h[3]};
-      attn_u32x2_t pl = {(l[0] >> 16) | l[1], (l[2] >> 16) | l[3]};
-      *(attn_u32x2_t *)(s_p + col * AM_PPITCH + tok0) = ph;
-      *(attn_u32x2_t *)(s_p + 16 * AM_PPITCH + col * AM_PPITCH + tok0) = pl;
+    for (int i = 0; i < 4; ++i) {
+      h[i] = __float_as_uint(pr[i]) & 0xffff0000u;
+      l[i] = __float_as_uint(pr[i] - __uint_as_float(h[i])) & 0xffff0000u;
     }
-    __syncthreads();
+    const attn_s16x4_t ph = __builtin_bit_cast(attn_s16x4_t, attn_u32x2_t{(h[0] >> 16) | h[1], (h[2] >> 16) | h[3]});
+    const attn_s16x4_t pl = __builtin_bit_cast(attn_s16x4_t, attn_u32x2_t{(l[0] >> 16) | l[1], (l[2] >> 16) | l[3]});
 
     // weighted values on top of the rescaled sums of the earlier pieces
-    if (trip > 0) {
+    if (__any(new_max > run_max)) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float a = s_alpha[4 * quad + i];
-        oacc[0][i] *= a;
-        oacc[1][i] *= a;
-      }
+      for (int t = 0; t < HD / 16; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) oacc[t][i] *= alpha;
     }
+    run_max = new_max;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (other lanes of the wave have stored what this one reads)
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const attn_bf16x8_t pa0 = __builtin_bit_cast(
-          attn_bf16x8_t, *(const attn_u32x4_t *)(s_p + col * AM_PPITCH + 32 * ks + 8 * quad));
-      const attn_bf16x8_t pa1 = __builtin_bit_cast(
-          attn_bf16x8_t, *(const attn_u32x4_t *)(s_p + 16 * AM_PPITCH + col * AM_PPITCH + 32 * ks + 8 * quad));
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const bf16_t *vcol = s_v + (32 * ks + 8 * quad) * AM_VPITCH + 32 * wave + 16 * t + col;
-        attn_u32x4_t vb;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) vb[e] = pack_bf16(vcol[(2 * e) * AM_VPITCH], vcol[(2 * e + 1) * AM_VPITCH]);
-        const attn_bf16x8_t b = __builtin_bit_cast(attn_bf16x8_t, vb);
-        oacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa0, b, oacc[t], 0, 0, 0);
-        oacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa1, b, oacc[t], 0, 0, 0);
-      }
+    for (int t = 0; t < HD / 16; ++t) {
+      // 16 lanes read 16 elements of four tokens, four of one token a lane, and get one element of all four each
+      const attn_s16x4_t va = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+          (__attribute__((address_space(3))) attn_s16x4_t *)(s_v + (4 * quad + (col >> 2)) * AM_VPITCH + 4 * (col & 3) + 16 * t));
+      oacc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(va, ph, oacc[t], 0, 0, 0);
+      oacc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(va, pl, oacc[t], 0, 0, 0);
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
 
-  // the slice's partial: weighted values, maximum, sum over the waves
-  if (quad == 0) { s_sum[wave * 16 + col] = run_sum; if (wave == 0) s_max[col] = run_max; }
-  if constexpr (TEAMS == 2) {
-    // the odd pieces' team hands its sums over (through its V, which nobody reads any more)
-    float *s_o = (float *)s_v_all[1];   // [8][256]
-    if (team == 1) {
-      __syncthreads();                  // (every wave of both teams is past its last piece)
+  // the slice's partial: the waves' weighted values brought to one maximum and added up
+  const int w_all = threadIdx.x >> 6;
+  if (quad == 0) { s_max[w_all * 16 + col] = run_max; s_sum[w_all * 16 + col] = run_sum; }
+  __syncthreads();                        // (and every wave is past its last piece)
+  auto slice_max = [&](int g) {           // (the first token's wave has had it: finite)
+    float m = s_max[g];
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+    for (int w = 1; w < WAVES; ++w) m = fmaxf(m, s_max[w * 16 + g]);
+    return m;
+  };
+  auto slice_sum = [&](int g) {
+    const float m = slice_max(g);
+    float y = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s_o[(t * 4 + i) * ATTN_THREADS + tid] = oacc[t][i];
-      __syncthreads();
-    } else {
-      __syncthreads();
-      __syncthreads();
+    for (int w = 0; w < WAVES; ++w) y += s_sum[w * 16 + g] * expf(s_max[w * 16 + g] - m);
+    return y;
+  };
+  float *s_o = (float *)s_mem + (w_all & 3) * 16 * AM_OPITCH + col * AM_OPITCH + 4 * quad;
+  {
+    const float f = expf(run_max - slice_max(col));
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int g = 4 * quad + i;
-        const float m0 = s_max_all[0][g], m1 = s_max_all[1][g], M = fmaxf(m0, m1);
-        const float f0 = expf(m0 - M), f1 = expf(m1 - M);   // (the even team has had a piece: M is finite)
+    for (int t = 0; t < HD / 16; ++t)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) oacc[t][i] = oacc[t][i] * f0 + s_o[(t * 4 + i) * ATTN_THREADS + tid] * f1;
-      }
-    }
-    __syncthreads();
-    if (threadIdx.x < 16) {
-      const int g = threadIdx.x;
-      const float m0 = s_max_all[0][g], m1 = s_max_all[1][g], M = fmaxf(m0, m1);
-      const float f0 = expf(m0 - M), f1 = expf(m1 - M);
-#pragma unroll
-      for (int w = 0; w < 4; ++w) s_sum_all[0][w * 16 + g] = s_sum_all[0][w * 16 + g] * f0 + s_sum_all[1][w * 16 + g] * f1;
-      s_max_all[0][g] = M;
-    }
+      for (int i = 0; i < 4; ++i) oacc[t][i] *= f;
   }
-  s_max = s_max_all[0];
-  s_sum = s_sum_all[0];
-  if (rd.pos < span) {   // the whole context is this slice: nothing to hand over and nobody to wait for
+  if constexpr (TEAMS == 2) {
+    // the odd pieces' team first
+    if (team == 1) {
+#pragma unroll
+      for (int t = 0; t < HD / 16; ++t) *(attn_f32x4_t *)(s_o + 16 * t) = oacc[t];
+    }
     __syncthreads();
-    uint32_t big = 0u;
     if (team == 0) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int g = 4 * quad + i;
-        const float inv = 1.0f / (s_sum[g] + s_sum[16 + g] + s_sum[32 + g] + s_sum[48 + g]);
+      for (int t = 0; t < HD / 16; ++t) {
+        const attn_f32x4_t other = *(const attn_f32x4_t *)(s_o + 16 * t);
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
-          if (g < group) {
-            const float y = oacc[t][i] * inv;
-            out.put<PARTS>(r, (hq0 + g) * HD + 32 * wave + 16 * t + col, y);
-            big = max(big, magnitude_bits(y));
-          }
+        for (int i = 0; i < 4; ++i) oacc[t][i] += other[i];
       }
+    }
+  }
+  if (team == 0) {   // (a lane writes where it has read)
+#pragma unroll
+    for (int t = 0; t < HD / 16; ++t) *(attn_f32x4_t *)(s_o + 16 * t) = oacc[t];
+  }
+  __syncthreads();
+  auto value = [&](int i) {   // element i of the group's heads, the waves in their order
+    const float *p = (const float *)s_mem + (i / HD) * AM_OPITCH + i % HD;
+    return p[0] + p[16 * AM_OPITCH] + p[2 * 16 * AM_OPITCH] + p[3 * 16 * AM_OPITCH];
+  };
+  if (rd.pos < span) {   // the whole context is this slice: nothing to hand over and nobody to wait for
+    uint32_t big = 0u;
+    for (int i = threadIdx.x; i < group * HD; i += 64 * WAVES) {
+      const float y = value(i) * (1.0f / slice_sum(i / HD));
+      out.put<PARTS>(r, hq0 * HD + i, y);
+      big = max(big, magnitude_bits(y));
     }
     put_wave_max<ATTN_THREADS * TEAMS>(row_max, r, big);
     return;
   }
-  if (team == 0) {
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int g = 4 * quad + i;
-        if (g < group)
-          store_device_scope(part + ((size_t)(r * nq + hq0 + g) * n_splits + split) * PS + 32 * wave + 16 * t + col,
-                             oacc[t][i]);
-      }
-  }
-  __syncthreads();
+  for (int i = threadIdx.x; i < group * HD; i += 64 * WAVES)
+    store_device_scope(part + ((size_t)(r * nq + hq0 + i / HD) * n_splits + split) * PS + i % HD, value(i));
   if ((int)threadIdx.x < group * 2) {
     const int g = threadIdx.x >> 1;
-    const float v = (threadIdx.x & 1) ? s_sum[g] + s_sum[16 + g] + s_sum[32 + g] + s_sum[48 + g] : s_max[g];
-    store_device_scope(part + ((size_t)(r * nq + hq0 + g) * n_splits + split) * PS + HD + (threadIdx.x & 1), v);
+    store_device_scope(part + ((size_t)(r * nq + hq0 + g) * n_splits + split) * PS + HD + (threadIdx.x & 1),
+                       (threadIdx.x & 1) ? slice_sum(g) : slice_max(g));
   }
   attn_merge<HD, ATTN_THREADS * TEAMS, PARTS>(rd, r, hq0, group, nq, n_splits, span, part,
                                               arrivals + r * gridDim.y + blockIdx.y, out, row_max, &s_last);

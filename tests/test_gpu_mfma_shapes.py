@@ -236,6 +236,19 @@ def test_attention_workgroups(sb, pieces, long):
     sp.close()
 
 
+@pytest.mark.parametrize("pieces,page", [(0, 64), (1, 64), (2, 64), (2, 16)])
+def test_attention_waves_without_tokens(sb, pieces, page):
+    """contexts that grow over the edges of a wave's 16 tokens: pieces of which one to four waves have tokens,
+    in one slice and in the last of several"""
+    say(f"case attention waves, {pieces} pieces, pages of {page}")
+    weights = wl.make_weights(SHAPE, seed=14, gain_std=0.1)
+    sp = sb.Spark(SHAPE, wl.TINY.schedule, weights, max_batch=4, max_seq_len=256, kv_page_tokens=page)
+    sp.tune("attn_pieces", pieces)
+    prompts = [wl.make_prompt(SHAPE, n, seed=90 + n) for n in (12, 29, 45, 140)]
+    compare_run(sp, SHAPE, wl.TINY.schedule, weights, prompts, [0, 1, 2, 0], 8, check_kv_every=4, label=f"{pieces} pieces, pages of {page}")
+    sp.close()
+
+
 @pytest.mark.parametrize("B", [6, 40])
 def test_magnitudes_far_apart(sb, B):
     """Gains of 2^-30 and 2^30 with weights that undo them, and MLP activations spread over a factor
