@@ -10,6 +10,7 @@ constexpr int MG_MAX_SPLIT = 32;       // ranges of k whose sums a finishing lau
 constexpr int TG_WAVES = 4;
 constexpr int TG_TASKS = 16;           // tasks of one A tile
 constexpr int OP_ROWS = 48;            // rows of a pass whose activations lie in operand order, at most
+constexpr int TD_WAVES = 4;            // of a workgroup of mfma_direct_k
 constexpr int TD_CUT_TILES = 2;        // A tiles of a workgroup of mfma_direct_k whose k is cut
 constexpr size_t MFMA_PARTIAL_BYTES = 48u << 20;  // k-split partial sums of one projection
 
@@ -206,6 +207,15 @@ inline int narrow_row_blocks(int m, int n_in, int n_tasks, int most_blocks, bool
   }
   return best;
 }
+
+// Dynamic LDS of mfma_direct_k with nt tiles and operands of cols activation rows: the waves' sums, the weight
+// rows' scales, and the activation rows' exponents, which all threads find together, td_lanes_per_row of them a
+// row: 16, 32 or 64 rows, of which the last operand has 48.
+constexpr int TD_PITCH = 36;   // floats per (tile, activation row): 32 weight rows and a skew of one 16-byte word
+constexpr int td_pieces(int nt, int cols) { return nt * cols <= 240 ? TD_WAVES : TD_WAVES / 2; }   // waves' sums that LDS holds at once
+constexpr int td_lanes_per_row(int cols) { return cols == 16 ? 16 : cols == 32 ? 8 : 4; }
+constexpr size_t td_exp_at(int nt, int cols) { return sizeof(float) * (td_pieces(nt, cols) * nt * cols * TD_PITCH + nt * 32); }
+constexpr size_t td_lds_bytes(int nt, int cols) { return td_exp_at(nt, cols) + sizeof(int) * (64 * TD_WAVES / td_lanes_per_row(cols)); }
 
 // mfma_direct_k with its k whole: tiles of a workgroup.  One for at most 8 rows, whose activations cost
 // a workgroup little (the weights' time of gate/up at 8 rows, d 3584 and 4096: 46.7 and 43.0 us with one tile, 49.1

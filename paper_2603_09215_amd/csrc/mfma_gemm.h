@@ -1228,7 +1228,6 @@ mfma_finish_tile_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, int n_
 // against 87; down 37 and 5 against 40 and 8; q/k/v and o level.  With 64 the sums of five tiles spill.)
 // Loads are buffer loads: the lane's place is one register for all of them, step and tile are scalars, and
 // what lies past the end of a matrix or of the activations comes back as zeros.
-constexpr int TD_WAVES = 4;
 constexpr int td_ring(int nt) { return nt == 1 ? 4 : 2; }
 // Every MFMA rounds its running sums to 32 bits, and a quarter of k in one chain leaves 2.8e-7 of the heads'
 // logits (k 3584, against 64 bits): the sums of a few steps are added to a second set and begin at zero again,
@@ -1236,9 +1235,6 @@ constexpr int td_ring(int nt) { return nt == 1 ? 4 : 2; }
 // the latter, 1.2e-7 with them (vector kernel: 1.1e-7); MLP blocks 2.6e-7 and 2.3e-7 (vector kernels 2.5e-7).
 constexpr bool td_fine(int nt, int cols) { return nt * cols <= 32; }   // (what the registers of four waves a SIMD allow)
 constexpr int td_fold_steps(int nt, int cols) { return td_fine(nt, cols) || nt * cols > 160 ? 2 : 4; }   // steps of 32 k whose products go into one set of sums (240: four spill)
-constexpr int TD_PITCH = 36;   // floats of LDS per (tile, activation row): 32 weight rows and a skew of one 16-byte word
-constexpr int td_pieces(int nt, int cols) { return nt * cols <= 240 ? TD_WAVES : TD_WAVES / 2; }   // waves' sums that LDS holds at once
-constexpr size_t td_lds_bytes(int nt, int cols) { return sizeof(float) * (td_pieces(nt, cols) * nt * cols * TD_PITCH + nt * 32 + OP_ROWS); }
 
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __amdgpu_buffer_rsrc_t buffer_t;
@@ -1259,7 +1255,7 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
   extern __shared__ uint4 td_smem[];
   float *s_t = (float *)td_smem;                             // [waves][NT][COLS][TD_PITCH]
   float *s_wdown = s_t + PIECES * NT * COLS * TD_PITCH;      // [NT][32 operand rows]
-  int *s_exp = (int *)(s_wdown + NT * 32);
+  int *s_exp = (int *)((char *)td_smem + td_exp_at(NT, COLS));   // [THREADS / LPR], the first COLS are needed
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, kq = lane >> 4;   // operand row / column, and which eight of the step's 32 k
   clear_words(in);
@@ -1302,7 +1298,9 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
   RowDesc early[EARLY > 0 ? EARLY : 1];
 #pragma unroll
   for (int g = 0; g < EARLY; ++g) early[g] = rows[min(m0 + 16 * g, m_rows - 1)];
-  constexpr int LPR = COLS == 16 ? 16 : COLS == 32 ? 8 : 4;   // neighbouring lanes that find a row's largest exponent
+  constexpr int LPR = td_lanes_per_row(COLS);   // neighbouring lanes that find a row's largest exponent
+  static_assert(THREADS % LPR == 0 && THREADS / LPR >= COLS && td_exp_at(NT, COLS) + sizeof(int) * (THREADS / LPR) <= td_lds_bytes(NT, COLS),
+                "every row's exponent, also those of rows that nobody asks for, has its place in LDS");
   RowExponent<LPR> mag(in.row_max, min((int)threadIdx.x / LPR, m_rows - 1), threadIdx.x & (LPR - 1));
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -1314,7 +1312,7 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
   __builtin_amdgcn_sched_barrier(0);
   {
     const int e = mag.get();
-    if ((threadIdx.x & (LPR - 1)) == 0) s_exp[threadIdx.x / LPR] = scale_exponent(e);   // (rows past COLS repeat the last)
+    if ((threadIdx.x & (LPR - 1)) == 0) s_exp[threadIdx.x / LPR] = scale_exponent(e);   // (rows past the last repeat it)
   }
   __syncthreads();
   float x_up[CG];

@@ -157,6 +157,37 @@ def test_cuts_of_a_few_rows_take_every_range_and_task_once(tmp_path):
     assert n > 100_000 and n_cut > 10_000, out.stdout
 
 
+DIRECT_LDS = r"""
+#include <cstdio>
+#include "cover.h"
+using namespace spark;
+int main() {
+  int layouts = 0;
+  for (int cols = 16; cols <= OP_ROWS; cols += 16)
+    for (int nt = 1; nt <= 5; ++nt) {
+      // every thread's group of lanes stores the exponent of one row
+      const size_t lds = td_lds_bytes(nt, cols), last = td_exp_at(nt, cols) + sizeof(int) * ((64 * TD_WAVES - 1) / td_lanes_per_row(cols));
+      if (last + sizeof(int) > lds || 64 * TD_WAVES / td_lanes_per_row(cols) < cols || lds > 160 * 1024) {
+        printf("%d tiles, %d rows: the last exponent ends at byte %zu of %zu\n", nt, cols, last + sizeof(int), lds);
+        return 1;
+      }
+      ++layouts;
+    }
+  printf("%d layouts\n", layouts);
+  return 0;
+}
+"""
+
+
+def test_exponents_of_all_rows_lie_inside_the_lds_of_a_launch(tmp_path):
+    src, exe = tmp_path / "lds.cpp", tmp_path / "lds"
+    src.write_text(DIRECT_LDS)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", f"-I{CSRC}", "-o", str(exe), str(src)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, out.stdout
+    assert out.stdout.split() == ["15", "layouts"], out.stdout
+
+
 def test_partial_sums_of_every_cover_fit_their_buffer(tmp_path):
     src, exe = tmp_path / "covers.cpp", tmp_path / "covers"
     src.write_text(DRIVER)
