@@ -208,6 +208,17 @@ inline int narrow_row_blocks(int m, int n_in, int n_tasks, int most_blocks, bool
   return best;
 }
 
+// Where mfma_direct_k reads the activations of a step of 32 k, in operand order ([n_in / 4][op_rows][4] floats): lane group kq
+// (0..3) has the eight k from 32 step + 8 kq on, two words of 16 bytes that lie 16 op_rows bytes apart.  n_in is a multiple
+// of 8, the last step may end behind it, and the last chunk may have a step that begins behind it: there the last
+// eight are read, finite numbers of the row's own range for weights that are zeros.
+constexpr int direct_x_step(int step, int n_in) { return step < (n_in - 8) / 32 ? step : (n_in - 8) / 32; }   // the step that is read
+constexpr int direct_x_quad(int kq, int read_step, int n_in) {   // of that step the quad of k
+  return 2 * kq < n_in / 4 - 2 - 8 * read_step ? 2 * kq : n_in / 4 - 2 - 8 * read_step;
+}
+// And the tile of weights behind the workgroup's first that its tile q is read from: past the last one, the last
+constexpr int direct_w_tile(int q, int first, int n_blocks) { return q < n_blocks - 1 - first ? q : n_blocks - 1 - first; }
+
 // Dynamic LDS of mfma_direct_k with nt tiles and operands of cols activation rows: the waves' sums, the weight
 // rows' scales, and the activation rows' exponents, which all threads find together, td_lanes_per_row of them a
 // row: 16, 32 or 64 rows, of which the last operand has 48.

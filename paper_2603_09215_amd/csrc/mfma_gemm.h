@@ -1226,8 +1226,9 @@ mfma_finish_tile_k(Epi epi, const RowDesc *__restrict__ rows, int m_rows, int n_
 //
 // (48 rows: gate/up of 271 MB 58 us, where mfma_tiled_k and its finishing launch take 58 and 12; a quarter of the heads 61
 // against 87; down 37 and 5 against 40 and 8; q/k/v and o level.  With 64 the sums of five tiles spill.)
-// Loads are buffer loads: the lane's place is one register for all of them, step and tile are scalars, and
-// what lies past the end of a matrix or of the activations comes back as zeros.
+// Loads are buffer loads: the lane's place is one register for all of them, step and tile are scalars.  No load
+// leaves the matrix or the activations (direct_x_step, direct_x_quad, direct_w_tile): whether a scalar offset takes part in
+// the check of a buffer's end is not something to rely on.
 constexpr int td_ring(int nt) { return nt == 1 ? 4 : 2; }
 // Every MFMA rounds its running sums to 32 bits, and a quarter of k in one chain leaves 2.8e-7 of the heads'
 // logits (k 3584, against 64 bits): the sums of a few steps are added to a second set and begin at zero again,
@@ -1280,17 +1281,19 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
 #pragma unroll
     for (int q = 0; q < NT; ++q)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) wr[u][q][h] = load_buffer16<true>(w_buf, w_at + h * 256, at + q * n_chunks * (int)tile_bytes);
+      for (int h = 0; h < 2; ++h)
+        wr[u][q][h] = load_buffer16<true>(w_buf, w_at + h * 256, at + direct_w_tile(q, group * NT, n_blocks) * n_chunks * (int)tile_bytes);
   };
-  int x_at[CG];   // (columns past the last row repeat it)
+  int x_row[CG];   // (columns past the last row repeat it)
 #pragma unroll
-  for (int g = 0; g < CG; ++g) x_at[g] = (2 * kq * op_rows + min(16 * g + col, m_rows - 1)) * 16;
+  for (int g = 0; g < CG; ++g) x_row[g] = min(16 * g + col, m_rows - 1) * 16;
   auto load_x = [&](int u, int step) {
-    const int at = min(step, s_last) * (KS * (int)sizeof(float)) * op_rows;
+    const int s = direct_x_step(min(step, s_last), n_in), at = s * (KS * (int)sizeof(float)) * op_rows;
+    const int quad = direct_x_quad(kq, s, n_in) * 16 * op_rows;
 #pragma unroll
     for (int g = 0; g < CG; ++g)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) xr[u][g][i] = load_buffer16<false>(x_buf, x_at[g], at + i * 16 * op_rows);
+      for (int i = 0; i < 2; ++i) xr[u][g][i] = load_buffer16<false>(x_buf, quad + x_row[g], at + i * 16 * op_rows);
   };
   // (finishing, a thread has task t of every tile and the rows m0 + 16 g)
   const int t = threadIdx.x & (TG_TASKS - 1), m0 = threadIdx.x >> 4;

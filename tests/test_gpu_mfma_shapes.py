@@ -78,9 +78,10 @@ def test_projection_kernels_by_their_switches(sb, B, tune):
 
 
 @pytest.mark.parametrize("B", [3, 4, 8, 9, 16, 17, 32, 33, 47, 48])
-def test_rows_at_the_edges_of_the_direct_kernels(sb, B):
+def test_rows_at_the_edges_of_the_direct_kernels(sb, filled_scratch, B):
     """one operand of 16 activation rows to three, one tile a workgroup (up to 8 rows) or a round of CUs;
-    inputs of 1024, 1032 and 1304, two of them no multiples of a chunk, cut in two from 9 rows on; three and four rows: layers on the MFMA kernels,
+    inputs of 1024, 1032 and 1304, two of them no multiples of a chunk (what lies behind their last row of
+    k is NaN), cut in two from 9 rows on; three and four rows: layers on the MFMA kernels,
     heads on the vector kernel"""
     say(f"case direct kernels, {B} rows")
     weights = wl.make_weights(LONG_K, seed=18, gain_std=0.1)

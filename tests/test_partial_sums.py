@@ -188,6 +188,55 @@ def test_exponents_of_all_rows_lie_inside_the_lds_of_a_launch(tmp_path):
     assert out.stdout.split() == ["15", "layouts"], out.stdout
 
 
+DIRECT_READS = r"""
+#include <cstdio>
+#include <cstddef>
+#include <initializer_list>
+#include "cover.h"
+using namespace spark;
+int main() {
+  long reads = 0, tiles = 0;
+  for (int n_in = 8; n_in <= 2200; n_in += 8)
+    for (int op_rows : {32, 48})
+      for (int m : {1, 5, 32, op_rows}) {
+        const size_t bytes = sizeof(float) * (size_t)op_rows * n_in;
+        const int steps = 2 * ceil_div(n_in, MG_KC);
+        for (int step = 0; step < steps; ++step)
+          for (int kq = 0; kq < 4; ++kq) {
+            const int s = direct_x_step(step, n_in), quad = direct_x_quad(kq, s, n_in), k = 32 * step + 8 * kq;
+            // as the kernel forms it: a part of the lane, of which no step makes a negative one, and a scalar one
+            const long lane = (long)quad * 16 * op_rows + (m - 1) * 16, at = (long)s * 128 * op_rows;
+            for (int i = 0; i < 2; ++i, ++reads) {
+              const long byte = at + i * 16 * op_rows + lane;
+              if (quad < 0 || s < 0 || byte < 0 || (size_t)byte + 16 > bytes) { printf("k %d of %d, %d rows: byte %ld of %zu\n", k, n_in, m, byte, bytes); return 1; }
+              if (k < n_in && byte != ((long)(k / 4 + i) * op_rows + m - 1) * 16) { printf("k %d of %d, %d rows: byte %ld\n", k, n_in, m, byte); return 1; }
+              if ((byte / 16) % op_rows != m - 1) { printf("k %d of %d: another row than %d\n", k, n_in, m - 1); return 1; }
+            }
+          }
+      }
+  for (int n_blocks = 1; n_blocks <= 1200; ++n_blocks)
+    for (int nt = 1; nt <= 5; ++nt)
+      for (int group = 0; group < ceil_div(n_blocks, nt); ++group)
+        for (int q = 0; q < nt; ++q, ++tiles) {
+          const int tile = group * nt + direct_w_tile(q, group * nt, n_blocks), want = group * nt + q < n_blocks ? group * nt + q : n_blocks - 1;
+          if (tile != want) { printf("tile %d of group %d of %d, %d blocks: %d\n", q, group, nt, n_blocks, tile); return 1; }
+        }
+  printf("%ld reads, %ld tiles\n", reads, tiles);
+  return 0;
+}
+"""
+
+
+def test_direct_reads_stay_inside_activations_and_weights(tmp_path):
+    src, exe = tmp_path / "reads.cpp", tmp_path / "reads"
+    src.write_text(DIRECT_READS)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", f"-I{CSRC}", "-o", str(exe), str(src)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, out.stdout
+    n, n_tiles = (int(w) for w in out.stdout.split() if w.isdigit())
+    assert n > 500_000 and n_tiles > 1_000_000, out.stdout
+
+
 def test_partial_sums_of_every_cover_fit_their_buffer(tmp_path):
     src, exe = tmp_path / "covers.cpp", tmp_path / "covers"
     src.write_text(DRIVER)
