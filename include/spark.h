@@ -123,7 +123,7 @@ typedef struct spark_ctx spark_ctx;
  * memory management itself the paper is silent.  For bf16 models whose widths are multiples of 8
  * the scratch size also has room for a second copy of the projection and head matrices, as fp16
  * scaled by powers of two and laid out in the order the matrix units consume them, which the
- * context writes when it is created and which the projections of three and more rows read instead
+ * context writes when it is created and which the projections of five and more rows read instead
  * of the caller's tensors (as many bytes again as those matrices), and behind it for the buffers
  * of prompt passes of 1024 rows.  A smaller area does without the latter, or without both.  cfg [host]; the two sizes are written to kv_pool_bytes /
  * scratch_bytes [host] (either may be NULL).

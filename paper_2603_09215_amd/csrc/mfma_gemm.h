@@ -1,4 +1,4 @@
-// Projections for 3 and more activation rows at once (prompt chunks, batched decoding) on the MFMA
+// Projections for 5 and more activation rows at once (prompt chunks, batched decoding) on the MFMA
 // units.  With that many rows a projection is a real dense contraction: every weight element is
 // used many times, so the vector kernel that serves a handful of rows would be ALU-bound.
 //

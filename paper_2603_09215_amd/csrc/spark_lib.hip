@@ -31,11 +31,11 @@ namespace {
 constexpr int PREFILL_CHUNK = 256;   // most prompt rows pushed through the layers together in the buffers that every context has
 constexpr int PROMPT_ROWS = 1024;    // and in those of a context with tiled weights
 constexpr int MAX_STEPS_PER_CALL = 256;
-// Rows from which the MFMA projections run: five where they stage the caller's weights, and for the heads (up
-// to four rows are one pass of the vector kernel, five would be two); three for the layers of a context with the
-// copy of the weights (twelve steps of a quarter of the layers, five against three: three sequences 11.47 against
-// 10.68 ms, four 12.5 against 11.0, three of 8192 tokens on the other backbone 16.1 against 14.8; two rows: level).
-constexpr int MFMA_MIN_ROWS = 5, MFMA_MIN_ROWS_COPY = 3;
+// Rows from which the MFMA projections run: five rows would be two passes of the vector kernel.  Three and four are one, in
+// 32 bits, with the caller's weights and with norms that have no upper end.  On the copy they would be faster (a batch of
+// three 11.6 against 10.7 ms for twelve steps of a quarter of the layers, of four 12.5 against 11.0), but a value that lies
+// 2^-39 below its row's largest is lost there, and a row whose sum of squares passes 1e12 (gemv.h, SSQ_SCALE) is wrong.
+constexpr int MFMA_MIN_ROWS = 5;
 constexpr int TILED_WIDE_TASKS = 8192;   // gate/up from here on has tiles enough for 64 tasks a wave at any row count (32 tiles)
 constexpr int MAX_SEQ_LEN = 16384;
 
@@ -110,7 +110,7 @@ struct spark_ctx {
   int direct_whole_k = 8192;    // ... and the longest k that it cuts in two at most
   int mfma_xcd_max_split = 4;  // row tiles share an XCD when k has at most this many ranges
   int mfma_small_tiles = 32;   // launches of mfma_rows_k with fewer 8-wave tiles use 4-wave workgroups
-  int mfma_min_rows = MFMA_MIN_ROWS, mfma_min_rows_copy = MFMA_MIN_ROWS_COPY;   // ("mfma_min_rows" sets both)
+  int mfma_min_rows = MFMA_MIN_ROWS;
   int attn_pieces = 0;         // 64-token pieces per attention workgroup (0: by the launch's size)
   int gemv_big_kb = 40;        // vector-kernel launches with more LDS per workgroup run eight waves per workgroup
   int attn_mfma_min_rows = 1;  // passes with at least this many rows run attention on the MFMA units (where the shape allows)
@@ -566,7 +566,8 @@ template <typename WT> int launch_attention(spark_ctx *c, const RowDesc *rows, i
   return prof_end(c, SPARK_KC_ATTN);
 }
 
-// ------------------------------------------------------------------ MFMA path (three or five and more rows, bf16)
+// ------------------------------------------------------------------ MFMA path (five and more rows, bf16)
+
 
 // Which kernel takes a pass's projections, and with it how the rows that they read lie in memory: on the
 // copy of the weights fp32 rows, where a pass of few of them streams it (mfma_direct_k) and wants
@@ -1007,7 +1008,7 @@ int run_layers(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
   const spark_config &g = c->cfg;
   if (l0 >= l1 || m <= 0) return SPARK_OK;
   // many rows: the projections are dense contractions for the MFMA units
-  if (std::is_same<WT, bf16_t>::value && m >= (on_copy(c) ? c->mfma_min_rows_copy : c->mfma_min_rows) && c->use_mfma) {
+  if (std::is_same<WT, bf16_t>::value && m >= c->mfma_min_rows && c->use_mfma) {
     // (more rows go through the layers in pieces, in order, so that a piece finds the K and V of the rows before it)
     const int most = pass_rows_limit(g.d_model);
     for (int r0 = 0; r0 < m; r0 += most) {
@@ -1544,7 +1545,7 @@ int spark_tune(spark_ctx *c, const char *name, int32_t value) {
   if (!c || !name) return SPARK_EINVAL;
   const std::string k(name);
   if (k == "mfma") c->use_mfma = value != 0 && c->mfma_ok;
-  else if (k == "mfma_min_rows") c->mfma_min_rows = c->mfma_min_rows_copy = std::max(1, (int)value);
+  else if (k == "mfma_min_rows") c->mfma_min_rows = std::max(1, (int)value);
   else if (k == "mfma_small_tiles") c->mfma_small_tiles = value;
   else if (k == "mfma_xcd_max_split") c->mfma_xcd_max_split = value;
   else if (k == "attn_pieces") c->attn_pieces = std::max(0, std::min(10, (int)value));

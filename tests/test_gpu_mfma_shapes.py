@@ -81,8 +81,7 @@ def test_projection_kernels_by_their_switches(sb, B, tune):
 def test_rows_at_the_edges_of_the_direct_kernels(sb, filled_scratch, B):
     """one operand of 16 activation rows to three, one tile a workgroup (up to 8 rows) or a round of CUs;
     inputs of 1024, 1032 and 1304, two of them no multiples of a chunk (what lies behind their last row of
-    k is NaN), cut in two from 9 rows on; three and four rows: layers on the MFMA kernels,
-    heads on the vector kernel"""
+    k is NaN), cut in two from 9 rows on; three and four rows: on the vector kernels, flushes on these"""
     say(f"case direct kernels, {B} rows")
     weights = wl.make_weights(LONG_K, seed=18, gain_std=0.1)
     prompts = [wl.make_prompt(LONG_K, 1 + i % 3, seed=80 + i) for i in range(B)]
@@ -274,4 +273,20 @@ def test_magnitudes_far_apart(sb, B):
     sp = sb.Spark(SHAPE, wl.TINY.schedule, weights, max_batch=B, max_seq_len=128, kv_page_tokens=16)
     res = compare_run(sp, SHAPE, wl.TINY.schedule, weights, prompts, [0] * B, 7, label=f"magnitudes, {B} rows")
     assert res["worst"] <= TOL[wl.DTYPE_BF16]
+    sp.close()
+
+
+@pytest.mark.parametrize("B,flushes", [(1, True), (2, False), (3, False), (4, False)])
+def test_large_hidden_states_of_a_few_rows(sb, B, flushes):
+    """hidden states 2^26 times as large as usual (a row's sum of squares around 1e15): up to four rows, also
+    those of one sequence's flush, are normalised with sums in floating point, which have no upper end near there.
+    The norms take the factor out again, so the tolerance is that of any bf16 model."""
+    say(f"case large hidden states, {B} sequences")
+    weights = wl.make_weights(SHAPE, seed=19, gain_std=0.1)
+    for name in ("embed", "wo", "wd"):   # exact: powers of two
+        weights[name] = wl.f32_to_bf16_bits(wl.bf16_bits_to_f32(weights[name]) * np.float32(2.0 ** 26))
+    sched = wl.TINY.schedule if flushes else wl.TINY.schedule.replace(period_k=1, phase=0)
+    prompts = [wl.make_prompt(SHAPE, 1 + i, seed=70 + i) for i in range(B)]
+    sp = sb.Spark(SHAPE, sched, weights, max_batch=B, max_seq_len=64, kv_page_tokens=16)
+    compare_run(sp, SHAPE, sched, weights, prompts, [0] * B, 7, label=f"large hidden states, {B} sequences")
     sp.close()

@@ -133,6 +133,35 @@ def test_mlp_against_64_bits(sb, rows, power, ffn):
     sp.close()
 
 
+@pytest.mark.parametrize("rows", [1, 2, 3, 4])
+def test_mlp_of_a_few_rows_keeps_32_bits(sb, rows):
+    """MLP activations between 2^-25 and 2^25 of their usual size within a row, undone by the columns of the down
+    projection: up to four rows are multiplied in 32 bits with the caller's weights, so the sums are those of
+    the plain model, bit for bit but for their order, and the bound is the plain model's.  (Two fp16 parts of
+    a value scaled with its row would leave out all that lies 2^-39 below the row's largest.)"""
+    import torch
+    say(f"case MLP alone, activations far apart, {rows} rows")
+    shape = wl.TINY.shape.replace(name="mlp", dtype=wl.DTYPE_BF16, n_layers=2, d_model=D, n_q_heads=2, n_kv_heads=1,
+                                  head_dim=128, d_ffn=FFN, vocab_text=0, vocab_speech=D)
+    sched = wl.TINY.schedule.replace(exit_layer=1, period_k=2, phase=1, n_text=0, n_speech=1, scope=wl.SCOPE_STREAM)
+    W = model(shape, True)
+    power = torch.as_tensor(np.random.default_rng(4).integers(-25, 26, FFN), device="cuda:0")
+    W["wu"][0] = torch.ldexp(W["wu"][0].float(), power[:, None]).bfloat16()
+    W["wd"][0] = torch.ldexp(W["wd"][0].float(), -power[None, :]).bfloat16()
+    sp = sb.Spark(shape, sched, W, max_batch=rows, max_seq_len=16, kv_page_tokens=16)
+    tokens = np.random.default_rng(rows).integers(0, D, rows)
+    ids, depth = first_step(sp, tokens, range(rows))
+    assert np.all(depth == 2)
+    h = W["embed"][torch.as_tensor(tokens, device="cuda:0")].double()
+    n = norm64(h, W["mlp_norm"][0], shape.rms_eps)
+    act = torch.nn.functional.silu(n @ W["wg"][0].double().T) * (n @ W["wu"][0].double().T)
+    want = norm64(h + act @ W["wd"][0].double().T, W["final_norm"], shape.rms_eps)
+    err = row_errors([sp.get_logits(i)[0] for i in ids], want)
+    say(f"  MLP, far apart, {rows} rows: mean {err.mean():.3g}, largest {err.max():.3g}")
+    assert err.max() <= 9e-7
+    sp.close()
+
+
 @pytest.mark.parametrize("rows", [1023, 700])
 def test_prompt_mlp_with_whole_and_cut_tiles(sb, rows):
     """gate/up of a large prompt pass: more tiles of 256 tasks x 96 rows than CUs, so that some end in the
