@@ -96,7 +96,7 @@ constexpr size_t tiled_partial_bytes(const TileCover &tc, int tb) {
 // six blocks; 236 of three and 238 of two are one of each, five.)
 struct MixedCover {
   TileCover part[4];
-  float cost;   // microseconds, see mixed_tile_cost
+  float cost;   // microseconds, see wide_tile_cost; 0: no such cover
   int tiles() const {
     int n = 0;
     for (const TileCover &p : part) n += p.n_task_tiles * p.n_row_tiles;
@@ -171,14 +171,19 @@ inline MixedCover cover_mixed(int m, int n_in, int n_tasks, int n_cu) {
   return mc;
 }
 
-// The same estimate for tiles of equal height, the last round cut over k and summed by a finishing launch
-inline float tiled_cost(const TileCover &tc, int n_in, int mtiles, int n_cu) {
-  const int n_chunks = ceil_div(n_in, MG_KC);
-  float t = ceil_div(tc.n_whole, n_cu) * wide_tile_cost(mtiles, n_chunks);
-  if (tc.n_cut)
-    t += ceil_div(tc.n_cut * tc.n_split, n_cu) * wide_tile_cost(mtiles, tc.chunks_per_split) + 5.f +
-         2.f * (float)(tc.n_split * range_bytes(tc.n_cut, 64 * TG_WAVES, tc.m_pitch)) / 5e6f;
-  return t;
+// That cover where it is the better one: against tiles of equal height, `most_blocks` at most, by the same estimate.  Only against whole ones: a tile
+// whose k is cut has shorter chains of running sums, each of which an MFMA rounds to 32 bits, than a whole tile of this
+// kernel has (64 tasks a wave leave no registers to fold them), so where the last round of equal tiles would be cut it stays.
+// (There the mixed cover was up to 4 % faster, gate/up of 1023 rows, d 4096, 13696 tasks 470 -> 451 us, and a seventh of the results
+// had chains three times as long.)
+inline MixedCover choose_mixed(int m, int n_in, int n_tasks, int most_blocks, int n_cu) {
+  MixedCover none{};
+  if (most_blocks < 3 || ceil_div(m, 32) < 3) return none;
+  const int mt = tiled_row_blocks_for(m, 3);
+  const TileCover tc = cover_tiled(m, n_in, n_tasks, mt, 2, false, false, n_cu, 0);
+  if (tc.n_cut) return none;
+  const MixedCover mc = cover_mixed(m, n_in, n_tasks, n_cu);
+  return mc.cost < ceil_div(tc.n_whole, n_cu) * wide_tile_cost(mt, ceil_div(n_in, MG_KC)) ? mc : none;
 }
 
 // Blocks of 32 rows in a row tile of a projection with 32 tasks a wave and more rows than one tile

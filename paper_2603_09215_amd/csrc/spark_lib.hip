@@ -710,17 +710,13 @@ int launch_mixed(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n
 // The cover by tiles of two heights if it is the better one, or nullptr.  (Found once for a shape: some tens of microseconds.)
 int mixed_cover(spark_ctx *c, int m, int n_in, int n_tasks, const MixedCover **out) {
   *out = nullptr;
-  const int blocks = ceil_div(m, 32), most = std::min(c->tiled_row_blocks, 3);
-  if (most < 3 || blocks < 3) return SPARK_OK;
+  if (c->tiled_row_blocks < 3) return SPARK_OK;
+  const int blocks = ceil_div(m, 32);
   const std::array<int, 3> key{blocks, n_in, n_tasks};
   auto found = c->mixed_covers.find(key);
   if (found == c->mixed_covers.end()) {
     if (c->mixed_covers.size() >= 64) c->mixed_covers.clear();
-    MixedCover mc = cover_mixed(32 * blocks, n_in, n_tasks, c->n_cu);
-    const int mt = tiled_row_blocks_for(32 * blocks, most);
-    const TileCover tc = cover_tiled(32 * blocks, n_in, n_tasks, mt, 2, false, false, c->n_cu, c->mfma_xcd_max_split);
-    if (mc.cost >= tiled_cost(tc, n_in, mt, c->n_cu)) mc.cost = 0.f;   // (no gain)
-    found = c->mixed_covers.emplace(key, mc).first;
+    found = c->mixed_covers.emplace(key, choose_mixed(32 * blocks, n_in, n_tasks, 3, c->n_cu)).first;
   }
   if (found->second.cost > 0.f) *out = &found->second;
   return SPARK_OK;

@@ -162,15 +162,17 @@ def test_mlp_of_a_few_rows_keeps_32_bits(sb, rows):
     sp.close()
 
 
-@pytest.mark.parametrize("rows", [1023, 700])
-def test_prompt_mlp_with_whole_and_cut_tiles(sb, rows):
+@pytest.mark.parametrize("rows,ffn", [(1023, 8264), (700, 8264), (340, 8264), (990, 10248)])
+def test_prompt_mlp_with_whole_and_cut_tiles(sb, rows, ffn):
     """gate/up of a large prompt pass: more tiles of 256 tasks x 96 rows than CUs, so that some end in the
     projection and the others in the finishing launch (33 x 11 tiles, 256 whole; 33 x 8, 256 whole), both
-    of which write the rows' lists of magnitudes for the down projection.  Seen in the second layer's
+    of which write the rows' lists of magnitudes for the down projection; and whole tiles of two heights in one
+    launch (198 of 64 rows; 247 of 96 and 265 of 64 rows).  (tests/test_partial_sums.py checks that these are the
+    covers.)  Seen in the second layer's
     value entries, which are rounded to bf16: within 2^-8 of themselves and 1e-4 of a row's typical one."""
     import torch
-    say(f"case MLP of a prompt of {rows}")
-    d, ffn, V = 1032, 8264, 900
+    say(f"case MLP of a prompt of {rows}, {ffn} activations")
+    d, V = 1032, 900
     shape = wl.TINY.shape.replace(name="prompt-mlp", dtype=wl.DTYPE_BF16, n_layers=2, d_model=d, n_q_heads=2, n_kv_heads=1,
                                   head_dim=128, d_ffn=ffn, vocab_text=V, vocab_speech=0)
     sched = wl.TINY.schedule.replace(exit_layer=1, period_k=1, phase=0, n_text=1, n_speech=0)

@@ -80,7 +80,7 @@ MIXED = r"""
 #include "cover.h"
 using namespace spark;
 int main() {
-  long covers = 0, two = 0;
+  long covers = 0, two = 0, chosen = 0, stays = 0;
   const int widths[] = {8192, 8264, 13696, 18944, 40000};
   for (int tasks : widths)
     for (int n_cu : {256, 64})
@@ -102,8 +102,27 @@ int main() {
             if (hit[x * (blocks + 8) + b] != 1) { printf("not once: %d tasks, %d rows\n", tasks, m); return 1; }
         ++covers;
         two += mc.part[1].n_task_tiles > 0;
+        // taken only where no result has a longer chain of running sums for it: no tile of equal height is cut
+        const TileCover tc = cover_tiled(m, 3584, tasks, tiled_row_blocks_for(m, 3), 2, false, false, n_cu, 4);
+        if (choose_mixed(m, 3584, tasks, 3, n_cu).cost > 0.f) {
+          if (tc.n_cut) { printf("in place of cut tiles: %d tasks, %d rows\n", tasks, m); return 1; }
+          ++chosen;
+        }
+        stays += tc.n_cut > 0;
       }
-  printf("%ld covers, %ld with two kinds of task tile\n", covers, two);
+  // what the GPU tests of a prompt's MLP are about: whole and cut tiles, lower tiles alone, both heights
+  const struct { int rows, d, tasks, whole, cut, high, low; } cases[] = {
+      {1023, 1032, 8264, 256, 107, 0, 0}, {700, 1032, 8264, 256, 8, 0, 0}, {340, 1032, 8264, 132, 0, 0, 198}, {990, 1032, 10248, 451, 0, 247, 265}};
+  for (const auto &c : cases) {
+    const TileCover tc = cover_tiled(c.rows, c.d, c.tasks, tiled_row_blocks_for(c.rows, 3), 2, false, false, 256, 4);
+    const MixedCover mc = choose_mixed(c.rows, c.d, c.tasks, 3, 256);
+    const int high = mc.cost > 0.f ? mc.part[0].n_whole + mc.part[1].n_whole : 0, low = mc.cost > 0.f ? mc.part[2].n_whole + mc.part[3].n_whole : 0;
+    if (tc.n_whole != c.whole || tc.n_cut != c.cut || high != c.high || low != c.low) {
+      printf("%d rows: %d whole, %d cut, %d high, %d low\n", c.rows, tc.n_whole, tc.n_cut, high, low);
+      return 1;
+    }
+  }
+  printf("%ld covers, %ld with two kinds of task tile, %ld taken, %ld stay cut\n", covers, two, chosen, stays);
   return 0;
 }
 """
@@ -115,8 +134,8 @@ def test_covers_by_tiles_of_two_heights_take_every_block_once(tmp_path):
     subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", f"-I{CSRC}", "-o", str(exe), str(src)], check=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0, out.stdout
-    n, n_two = (int(w) for w in out.stdout.split() if w.isdigit())
-    assert n > 3000 and n_two > 300, out.stdout
+    n, n_two, n_taken, n_cut = (int(w) for w in out.stdout.split() if w.isdigit())
+    assert n > 3000 and n_two > 300 and n_taken > 500 and n_cut > 500, out.stdout
 
 
 CUTS = r"""
