@@ -189,25 +189,24 @@ inline MixedCover choose_mixed(int m, int n_in, int n_tasks, int most_blocks, in
 // Blocks of 32 rows in a row tile of a projection with 32 tasks a wave and more rows than one tile
 // takes: such a launch is one to three rounds of CUs, and what the last of them leaves idle differs
 // more between the heights than the heights themselves do.  The time of a cover is taken as that of
-// the CU with the most chunks, 0.4 us for each of a chunk's blocks of rows and as much for its weights, its
-// starts and epilogues, and
-// that of its partial sums, at 5 TB/s there and back, and the launch that adds them up; a lower tile has to save a twentieth.
+// the CU with the most chunks, 0.4 us for each of a chunk's blocks of rows and as much for its weights, and
+// that of its partial sums, at 5 TB/s there and back; a lower tile has to save a twentieth.
 // (down, 768 rows of d 4096, k 13696: tiles of 128 rows make two ranges on 192 CUs, of 96 rows two
 // on all 256; a prompt of 2300 tokens in three such passes 25.4 ms with the former, 23.8 with the latter.)
+// With the starts and epilogues of tiles and the speed of idle CUs in the estimate a third of the sizes of q/k/v and o get
+// other heights, with k whole or in two where this one cuts it in four to seven, and prompts were up to 1.2 % faster (4096
+// wide, a quarter of the layers, 1024 tokens 10941 -> 10841 us, 8192 92071 -> 90473; 3584 wide, 701 tokens 6820 -> 6711).  But the
+// sums of whole k have longer chains, and logits behind such prompts were further from 64 bits: 2 % in the mean
+// of 312 (batches of 32 and of 48, standard error 1 %).
 inline int narrow_row_blocks(int m, int n_in, int n_tasks, int most_blocks, bool always_cut, int n_cu) {
   if (ceil_div(m, 32) <= most_blocks) return tiled_row_blocks_for(m, most_blocks);
   int best = most_blocks;
   double least = 0.0;
   for (int mt = most_blocks; mt >= 2; --mt) {
     const TileCover tc = cover_tiled(m, n_in, n_tasks, mt, 1, always_cut, false, n_cu, 0);
-    // (a chunk of a launch that leaves CUs idle is faster: the others share the chip's power and caches)
-    auto round_cost = [&](int workgroups, int chunks) {
-      const int rounds = ceil_div(workgroups, n_cu);
-      return rounds * (chunks * (mt + 1) * 0.4 * (0.6 + 0.4 * workgroups / ((double)rounds * n_cu)) + 4.0 + 3.0 * mt);
-    };
-    double cost = (double)tiled_partial_bytes(tc, 1) * 2.0 / 5e6;
-    if (tc.n_whole) cost += round_cost(tc.n_whole, ceil_div(n_in, MG_KC));
-    if (tc.n_cut) cost += round_cost(tc.n_cut * tc.n_split, tc.chunks_per_split) + 5.0;
+    const long chunks = (long)ceil_div(tc.n_whole, n_cu) * ceil_div(n_in, MG_KC) +
+                        (tc.n_cut ? (long)ceil_div(tc.n_cut * tc.n_split, n_cu) * tc.chunks_per_split : 0);
+    const double cost = (double)chunks * (mt + 1) * 0.4 + (double)tiled_partial_bytes(tc, 1) * 2.0 / 5e6;
     if (mt == most_blocks || cost < 0.95 * least) { least = cost; best = mt; }
   }
   return best;

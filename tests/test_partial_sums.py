@@ -256,6 +256,40 @@ def test_direct_reads_stay_inside_activations_and_weights(tmp_path):
     assert n > 500_000 and n_tiles > 1_000_000, out.stdout
 
 
+HEIGHTS = r"""
+#include <cstdio>
+#include "cover.h"
+using namespace spark;
+int main() {
+  const struct { int n_in, n_tasks; bool always_cut; } shapes[] = {
+      {3584, 2304, false}, {3584, 1792, true}, {18944, 1792, true}, {4096, 2304, false}, {4096, 2048, true}, {13696, 2048, true}};
+  for (const auto &s : shapes) {
+    for (int b = 2; b <= 32; ++b) printf("%d", narrow_row_blocks(32 * b, s.n_in, s.n_tasks, 4, s.always_cut, 256));
+    printf("\n");
+  }
+  return 0;
+}
+"""
+
+
+HEIGHTS_WANT = ["2343344344422443333344444442222",
+                "2342222332244443344444433344444",
+                "2343344344444443344444433344444",
+                "2343344344422443333344444442222",
+                "2343322323344444444333344444444",
+                "2343344324444444444333344444444"]
+
+
+def test_heights_of_the_tiles_of_prompts(tmp_path):
+    """q/k/v, o and down of the two backbones, 2 to 32 blocks of 32 rows on 256 CUs: the heights decide where
+    the sums over k are cut, and with it the last bits of every cache entry and how far they are from 64 bits"""
+    src, exe = tmp_path / "heights.cpp", tmp_path / "heights"
+    src.write_text(HEIGHTS)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", f"-I{CSRC}", "-o", str(exe), str(src)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.stdout.split() == HEIGHTS_WANT
+
+
 def test_partial_sums_of_every_cover_fit_their_buffer(tmp_path):
     src, exe = tmp_path / "covers.cpp", tmp_path / "covers"
     src.write_text(DRIVER)
