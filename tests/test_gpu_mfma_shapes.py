@@ -24,10 +24,10 @@ SHAPE = wl.TINY.shape.replace(name="bf16-edges", dtype=wl.DTYPE_BF16, n_layers=3
                               n_kv_heads=1, head_dim=128, d_ffn=1024 + 40, vocab_text=900, vocab_speech=301)
 
 
-@pytest.mark.parametrize("B", [5, 16, 31, 32, 33, 64, 65, 96, 97, 128, 129])
+@pytest.mark.parametrize("B", [5, 16, 31, 32, 33, 48, 49, 64, 65, 96, 97, 128, 129])
 def test_rows_at_the_edges_of_the_tiles(sb, B):
     """B sequences on the same schedule: B rows in every pass of the lower layers and of the heads
-    (32 is the last count without LDS, 64, 96 and 128 fill a tile of two, three and four blocks of
+    (48 is the last count without LDS, 64, 96 and 128 fill a tile of two, three and four blocks of
     rows, 129 starts a second tile), up to 4 B in the flushes"""
     say(f"case {B} rows")
     weights = wl.make_weights(SHAPE, seed=11, gain_std=0.1)
@@ -62,11 +62,12 @@ LONG_K = SHAPE.replace(name="bf16-long-k", d_model=1032, n_q_heads=8, n_kv_heads
 
 @pytest.mark.parametrize("B,tune", [(6, {}), (6, dict(direct_whole_k=64)), (19, dict(direct_whole_k=64)), (6, dict(direct_max_rows=0)),
                                     (30, dict(direct_max_rows=16)), (36, {}), (36, dict(tiled_row_blocks=2)),
+                                    (52, {}), (70, dict(tiled_row_blocks=2)), (52, dict(fuse_norm=0)), (40, dict(direct_max_rows=32)),
                                     (36, dict(fuse_norm=0)), (6, dict(fuse_norm=0)), (12, dict(mfma_tiled=0)),
                                     (36, dict(mfma_tiled=0)), (36, dict(mfma_tiled=0, fuse_norm=0))])
 def test_projection_kernels_by_their_switches(sb, B, tune):
     """the kernels that the switches lead to, k cut and whole, on the same rows: without LDS and with it
-    for at most 32 rows, row tiles of two blocks, norms as launches, the caller's weights"""
+    for at most 48 rows, row tiles of two blocks, norms as launches, the caller's weights"""
     say(f"case {B} rows, {tune}")
     weights = wl.make_weights(LONG_K, seed=15, gain_std=0.1)
     prompts = [wl.make_prompt(LONG_K, 1 + i % 3, seed=60 + i) for i in range(B)]
@@ -249,9 +250,9 @@ def test_attention_waves_without_tokens(sb, pieces, page):
     sp.close()
 
 
-@pytest.mark.parametrize("B", [6, 40])
+@pytest.mark.parametrize("B", [6, 40, 70])
 def test_magnitudes_far_apart(sb, B):
-    """Gains of 2^-30 and 2^30 with weights that undo them, and MLP activations spread over a factor
+    """(The kernel without LDS with one operand of rows and with three, and the one with it.)  Gains of 2^-30 and 2^30 with weights that undo them, and MLP activations spread over a factor
     of 1024 within a row, undone by the columns of the down projection: powers of two, so that the
     model is the same one.  What the two fp16 parts leave out is 2^-23 of an element or 2^-40 of its
     row's largest, 2^-30 of the smallest elements here, so the tolerance is that of any bf16 model."""
