@@ -110,30 +110,14 @@ inline float wide_tile_cost(int blocks, int n_chunks) { return n_chunks * (0.35f
 
 // Time until n_cu CUs have taken n_high jobs of one length and then n_low of a shorter one, each as it becomes free
 inline float two_lengths_makespan(int n_high, float high, int n_low, float low, int n_cu) {
-  struct Group { float t; int n; } g[64];
-  int groups = 1;
-  g[0] = Group{0.f, n_cu};
-  float end = 0.f;
-  while (n_high + n_low > 0) {
-    int k = 0;
-    for (int i = 1; i < groups; ++i)
-      if (g[i].t < g[k].t) k = i;
-    const bool is_high = n_high > 0;
-    int &left = is_high ? n_high : n_low;
-    const int n = left < g[k].n ? left : g[k].n;
-    const float t = g[k].t + (is_high ? high : low);
-    left -= n;
-    if (t > end) end = t;
-    g[k].n -= n;
-    if (g[k].n == 0) g[k] = g[--groups];
-    int same = -1;
-    for (int i = 0; i < groups; ++i)
-      if (g[i].t == t) same = i;
-    if (same >= 0) g[same].n += n;
-    else if (groups < 64) g[groups++] = Group{t, n};
-    else return 1e30f;
-  }
-  return end;
+  const int late = n_high % n_cu, early = n_cu - late;   // CUs that end with a long job, and the others, which have one less
+  const float start = (float)(n_high / n_cu) * high;     // of the others' first short job
+  if (!late) return start + (float)ceil_div(n_low, n_cu) * low;
+  const float joined = start + high;                     // from here on all CUs take short ones
+  const int ahead = (int)(high / low), rest = n_low - early * ahead;
+  if (rest <= 0) return joined;
+  const int turns = (rest - 1) / n_cu, last = rest - turns * n_cu;   // the early CUs end a turn first
+  return joined + (float)turns * low + (last <= early ? (float)(ahead + 1) * low - high : low);
 }
 
 inline TileCover whole_part(int n_task_tiles, int n_row_tiles) {

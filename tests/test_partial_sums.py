@@ -75,11 +75,25 @@ int main() {
 
 
 MIXED = r"""
+#include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <vector>
 #include "cover.h"
 using namespace spark;
+static float dealt(int n_high, float high, int n_low, float low, int n_cu) {   // one job after the other to whoever is free first
+  std::vector<float> t(n_cu, 0.f);
+  for (int i = 0; i < n_high + n_low; ++i) *std::min_element(t.begin(), t.end()) += i < n_high ? high : low;
+  return *std::max_element(t.begin(), t.end());
+}
 int main() {
+  for (int n_cu : {256, 7})
+    for (float high : {1.01f, 1.39f, 1.5f, 1.99f, 2.5f})
+      for (int n_high = 0; n_high < 3 * n_cu; n_high += n_cu / 7)
+        for (int n_low = 0; n_low < 3 * n_cu; n_low += n_cu / 5) {
+          const float want = dealt(n_high, high, n_low, 1.f, n_cu), got = two_lengths_makespan(n_high, high, n_low, 1.f, n_cu);
+          if (std::fabs(got - want) > 1e-4f * want) { printf("%d of %g and %d: %g, not %g\n", n_high, high, n_low, got, want); return 1; }
+        }
   long covers = 0, two = 0, chosen = 0, stays = 0;
   const int widths[] = {8192, 8264, 13696, 18944, 40000};
   for (int tasks : widths)
