@@ -211,9 +211,8 @@ constexpr int direct_w_tile(int q, int first, int n_blocks) { return q < n_block
 // rows' scales, and the activation rows' exponents, which all threads find together, td_lanes_per_row of them a
 // row: 16, 32 or 64 rows, of which the last operand has 48.
 constexpr int TD_PITCH = 36;   // floats per (tile, activation row): 32 weight rows and a skew of one 16-byte word
-constexpr int td_pieces(int nt, int cols) { return nt * cols <= 240 ? TD_WAVES : TD_WAVES / 2; }   // waves' sums that LDS holds at once
 constexpr int td_lanes_per_row(int cols) { return cols == 16 ? 16 : cols == 32 ? 8 : 4; }
-constexpr size_t td_exp_at(int nt, int cols) { return sizeof(float) * (td_pieces(nt, cols) * nt * cols * TD_PITCH + nt * 32); }
+constexpr size_t td_exp_at(int nt, int cols) { return sizeof(float) * (TD_WAVES * nt * cols * TD_PITCH + nt * 32); }
 constexpr size_t td_lds_bytes(int nt, int cols) { return td_exp_at(nt, cols) + sizeof(int) * (64 * TD_WAVES / td_lanes_per_row(cols)); }
 
 // mfma_direct_k with its k whole: tiles of a workgroup.  One for at most 8 rows, whose activations cost
@@ -231,27 +230,14 @@ inline int direct_tiles(int m, int blocks, int n_cu, bool heads) {
   return nt;
 }
 
-// A long k with few tasks (down) would be streamed by few CUs, each reading all activations of a long row: it is cut
-// over the CUs.  Ranges (1: it is not cut) and chunks in each
-inline int direct_split(int m, int n_in, int n_tasks, int n_cu, int &chunks_per_split) {
-  const int n_chunks = ceil_div(n_in, MG_KC), groups = ceil_div(ceil_div(n_tasks, TG_TASKS), TD_CUT_TILES);
-  const size_t fit = MFMA_PARTIAL_BYTES / range_bytes(groups, TD_CUT_TILES * TG_TASKS, ceil_div(m, 8) * 8);
-  int split = n_cu / groups;
-  if (split > n_chunks / 8) split = n_chunks / 8;
-  if (split > MG_MAX_SPLIT) split = MG_MAX_SPLIT;
-  if ((size_t)split > fit) split = (int)fit;
-  if (split < 1) split = 1;
-  chunks_per_split = ceil_div(n_chunks, split);
-  return ceil_div(n_chunks, chunks_per_split);
-}
-
 // mfma_direct_k with its k cut: tiles of a workgroup, workgroups per range, ranges (1: it is not cut) and chunks in each
 struct DirectCut { int tiles, groups, split, chunks_per_split; };
 // bytes of the ranges' sums: both weight rows of every task, for whole operands of 16 rows
 constexpr size_t direct_partial_bytes(int m, const DirectCut &c) {
   return sizeof(float) * (size_t)c.split * c.groups * c.tiles * 2 * TG_TASKS * (ceil_div(m, 16) * 16);
 }
-// whole_k: the longest k that counts as short.  Of those, what leaves half of the CUs idle (o) is cut in two from 9 rows
+// A long k with few tasks (down) would be streamed by few CUs, each reading all activations of a long row: it is cut
+// over the CUs.  whole_k: the longest k that counts as short.  Of those, what leaves half of the CUs idle (o) is cut in two from 9 rows
 // on: 16 rows 12.60 -> 12.51 ms a step, 32 rows 16.05 -> 15.87, 48 rows 17.09 -> 16.85; 3 and 8 rows are level.  What fills
 // more than half would need a second round of CUs (q/k/v, 288 halves on 256 CUs: a step 1 % slower).
 inline DirectCut direct_cut(int m, int n_in, int n_tasks, int n_cu, int whole_k) {
@@ -260,7 +246,9 @@ inline DirectCut direct_cut(int m, int n_in, int n_tasks, int n_cu, int whole_k)
   if (n_in > whole_k && blocks < 4 * n_cu) {
     c.tiles = TD_CUT_TILES;
     c.groups = ceil_div(blocks, TD_CUT_TILES);
-    c.split = direct_split(m, n_in, n_tasks, n_cu, c.chunks_per_split);
+    c.split = n_cu / c.groups;
+    if (c.split > n_chunks / 8) c.split = n_chunks / 8;
+    if (c.split > MG_MAX_SPLIT) c.split = MG_MAX_SPLIT;
   } else if (n_in <= whole_k && m > 8 && 2 * blocks <= n_cu && n_chunks >= 16) {
     c.split = 2;
   }

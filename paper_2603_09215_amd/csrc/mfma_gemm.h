@@ -1252,10 +1252,10 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
               const RowDesc *__restrict__ rows, int m_rows, ProjIn in, int n_in, int n_tasks, int n_groups,
               int chunks_per_split, float *__restrict__ part, int *__restrict__ arrivals) {
   static_assert(COLS % 16 == 0 && COLS <= OP_ROWS, "operands of 16 activation rows");
-  constexpr int CG = COLS / 16, KS = 32, STEPS = MG_KC / KS, RING = td_ring(NT), THREADS = 64 * TD_WAVES, PIECES = td_pieces(NT, COLS);
+  constexpr int CG = COLS / 16, KS = 32, STEPS = MG_KC / KS, RING = td_ring(NT), THREADS = 64 * TD_WAVES;
   extern __shared__ uint4 td_smem[];
   float *s_t = (float *)td_smem;                             // [waves][NT][COLS][TD_PITCH]
-  float *s_wdown = s_t + PIECES * NT * COLS * TD_PITCH;      // [NT][32 operand rows]
+  float *s_wdown = s_t + TD_WAVES * NT * COLS * TD_PITCH;    // [NT][32 operand rows]
   int *s_exp = (int *)((char *)td_smem + td_exp_at(NT, COLS));   // [THREADS / LPR], the first COLS are needed
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, kq = lane >> 4;   // operand row / column, and which eight of the step's 32 k
@@ -1389,36 +1389,20 @@ mfma_direct_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict_
 
   // the waves' sums, [activation row][weight row]: a lane has four neighbouring weight rows of one activation row
   if (threadIdx.x < NT * 32) s_wdown[threadIdx.x] = wd;
-  auto piece = [&](int w, int q, int g, int h) { return (f32x4_t *)(s_t + ((w * NT + q) * COLS + 16 * g + col) * TD_PITCH + 16 * h + 4 * kq); };
-  if constexpr (PIECES < TD_WAVES) {   // the upper waves hand theirs to the lower ones
-    if (wave >= PIECES) {
 #pragma unroll
-      for (int q = 0; q < NT; ++q)
+  for (int q = 0; q < NT; ++q)
 #pragma unroll
-        for (int g = 0; g < CG; ++g)
+    for (int g = 0; g < CG; ++g)
 #pragma unroll
-          for (int h = 0; h < 2; ++h) *piece(wave - PIECES, q, g, h) = folded[q][g][h];
-    }
-    __syncthreads();
-  }
-  if (wave < PIECES) {
-#pragma unroll
-    for (int q = 0; q < NT; ++q)
-#pragma unroll
-      for (int g = 0; g < CG; ++g)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          f32x4_t *p = piece(wave, q, g, h);
-          *p = PIECES < TD_WAVES ? folded[q][g][h] + *p : folded[q][g][h];
-        }
-  }
+      for (int h = 0; h < 2; ++h)
+        *(f32x4_t *)(s_t + ((wave * NT + q) * COLS + 16 * g + col) * TD_PITCH + 16 * h + 4 * kq) = folded[q][g][h];
   __syncthreads();
   // the sum of an operand row, always in the order of the waves, without its scales
   // (one factor after the other: their product may lie outside the range of an fp32 where the result does not)
   auto sum = [&](int q, int row, int m, float x_down) {
     float y = s_t[(q * COLS + m) * TD_PITCH + row];
 #pragma unroll
-    for (int w = 1; w < PIECES; ++w) y += s_t[((w * NT + q) * COLS + m) * TD_PITCH + row];
+    for (int w = 1; w < TD_WAVES; ++w) y += s_t[((w * NT + q) * COLS + m) * TD_PITCH + row];
     return y * x_down * s_wdown[q * 32 + row];
   };
   // 16 lanes finish a row's tasks of one tile after the other

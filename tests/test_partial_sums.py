@@ -36,11 +36,10 @@ static void projection(int m, int n_in, int n_tasks, bool always, bool never, in
       mixed += tc.n_cut > 0 && tc.n_whole > 0;
     }
   if (m <= OP_ROWS) {
-    int cps;
-    const int split = direct_split(m, n_in, n_tasks, n_cu, cps), groups = ceil_div(ceil_div(n_tasks, TG_TASKS), TD_CUT_TILES);
-    const size_t bytes = split * range_bytes(groups, TD_CUT_TILES * TG_TASKS, ceil_div(m, 8) * 8);
-    if (split > 1 && bytes > MFMA_PARTIAL_BYTES) bad("direct", m, n_in, n_tasks, 1, 1, bytes);
-    if (split < 1 || split > MG_MAX_SPLIT || split * cps < ceil_div(n_in, MG_KC)) bad("direct ranges", m, n_in, n_tasks, 1, 1, bytes);
+    const DirectCut c = direct_cut(m, n_in, n_tasks, n_cu, 0);
+    const size_t bytes = direct_partial_bytes(m, c);
+    if (c.split > 1 && bytes > MFMA_PARTIAL_BYTES) bad("direct", m, n_in, n_tasks, 1, 1, bytes);
+    if (c.split < 1 || c.split > MG_MAX_SPLIT || c.split * c.chunks_per_split < ceil_div(n_in, MG_KC)) bad("direct ranges", m, n_in, n_tasks, 1, 1, bytes);
   }
   // the kernel on the caller's weights: one tile, all rows; its residual projections are always cut
   const size_t rows_bytes = range_bytes(1, n_tasks, ceil_div(m, 8) * 8);
