@@ -306,7 +306,8 @@ int spark_measure_read(spark_ctx *ctx, const void *buf, size_t bytes, int32_t re
  *   caller's weight rows through LDS instead of reading the context's copy in operand order),
  *   "mfma_small_tiles" and "mfma_small_max_k" (which of those launches run four waves a workgroup),
  *   "direct_max_rows" (rows up to which those on the copy do without LDS, at most 48),
- *   "direct_whole_k" (the longest input width that those cut in two ranges at most),
+ *   "direct_whole_k" (the longest input width that those never cut; negative: as a new context chooses, 8192, of
+ *   which launches of few tasks are cut in two),
  *   "tiled_row_blocks" (blocks of 32 rows in a row tile of the others, 2..4, at most), "fuse_norm" (0:
  *   every RMSNorm of the batched path is its own launch), "prefill_rows" (prompt rows per pass, a
  *   multiple of 32, at most 1024, or 256 where the scratch area has no room for more; 0: by the

@@ -237,10 +237,12 @@ constexpr size_t direct_partial_bytes(int m, const DirectCut &c) {
   return sizeof(float) * (size_t)c.split * c.groups * c.tiles * 2 * TG_TASKS * (ceil_div(m, 16) * 16);
 }
 // A long k with few tasks (down) would be streamed by few CUs, each reading all activations of a long row: it is cut
-// over the CUs.  whole_k: the longest k that counts as short.  Of those, what leaves half of the CUs idle (o) is cut in two from 9 rows
+// over the CUs.  whole_k: the longest k that is never cut; negative: by the rule, for which 8192 and less are short.  Of those, what leaves half of the CUs idle (o) is cut in two from 9 rows
 // on: 16 rows 12.60 -> 12.51 ms a step, 32 rows 16.05 -> 15.87, 48 rows 17.09 -> 16.85; 3 and 8 rows are level.  What fills
 // more than half would need a second round of CUs (q/k/v, 288 halves on 256 CUs: a step 1 % slower).
 inline DirectCut direct_cut(int m, int n_in, int n_tasks, int n_cu, int whole_k) {
+  const bool by_rule = whole_k < 0;
+  if (by_rule) whole_k = 8192;
   const int n_chunks = ceil_div(n_in, MG_KC), blocks = ceil_div(n_tasks, TG_TASKS);
   DirectCut c{1, blocks, 1, n_chunks};
   if (n_in > whole_k && blocks < 4 * n_cu) {
@@ -249,7 +251,7 @@ inline DirectCut direct_cut(int m, int n_in, int n_tasks, int n_cu, int whole_k)
     c.split = n_cu / c.groups;
     if (c.split > n_chunks / 8) c.split = n_chunks / 8;
     if (c.split > MG_MAX_SPLIT) c.split = MG_MAX_SPLIT;
-  } else if (n_in <= whole_k && m > 8 && 2 * blocks <= n_cu && n_chunks >= 16) {
+  } else if (by_rule && n_in <= whole_k && m > 8 && 2 * blocks <= n_cu && n_chunks >= 16) {
     c.split = 2;
   }
   while (c.split > 1 && direct_partial_bytes(m, c) > MFMA_PARTIAL_BYTES) --c.split;

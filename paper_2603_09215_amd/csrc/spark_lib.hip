@@ -107,7 +107,7 @@ struct spark_ctx {
   bool use_mfma = true;        // "mfma" = 0 keeps every row count on the vector kernels
   int tiled_row_blocks = 4;     // blocks of 32 rows in a tile of mfma_tiled_k, at most
   int direct_max_rows = OP_ROWS;   // rows up to which mfma_direct_k runs
-  int direct_whole_k = 8192;    // ... and the longest k that it cuts in two at most
+  int direct_whole_k = -1;      // ... and the longest k that it never cuts (negative: see direct_cut)
   int mfma_xcd_max_split = 4;  // row tiles share an XCD when k has at most this many ranges
   int mfma_small_tiles = 32;   // launches of mfma_rows_k with fewer 8-wave tiles use 4-wave workgroups
   int mfma_min_rows = MFMA_MIN_ROWS;

@@ -60,7 +60,8 @@ def test_prompt_lengths(sb, n, page, group, shared):
 LONG_K = SHAPE.replace(name="bf16-long-k", d_model=1032, n_q_heads=8, n_kv_heads=2, d_ffn=1304)
 
 
-@pytest.mark.parametrize("B,tune", [(6, {}), (6, dict(direct_whole_k=64)), (19, dict(direct_whole_k=64)), (6, dict(direct_max_rows=0)),
+@pytest.mark.parametrize("B,tune", [(6, {}), (6, dict(direct_whole_k=64)), (19, dict(direct_whole_k=64)), (19, dict(direct_whole_k=8192)),
+                                    (40, dict(direct_whole_k=-1)), (6, dict(direct_max_rows=0)),
                                     (30, dict(direct_max_rows=16)), (36, {}), (36, dict(tiled_row_blocks=2)),
                                     (52, {}), (70, dict(tiled_row_blocks=2)), (52, dict(fuse_norm=0)), (40, dict(direct_max_rows=32)),
                                     (36, dict(fuse_norm=0)), (6, dict(fuse_norm=0)), (12, dict(mfma_tiled=0)),

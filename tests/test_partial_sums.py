@@ -162,10 +162,11 @@ int main() {
     for (int n_in : {64, 128, 896, 1024, 3584, 4096, 8192, 8256, 13696, 18944})
       for (int tasks = 8; tasks <= 20000; tasks += tasks < 5000 ? 8 : 168)
         for (int m = 1; m <= 48; m += m < 9 ? 1 : 13)
-          for (int whole_k : {0, 8192}) {
+          for (int whole_k : {0, 8192, -1}) {
             const DirectCut c = direct_cut(m, n_in, tasks, n_cu, whole_k);
             const int chunks = ceil_div(n_in, MG_KC);
-            const bool bad = c.split < 1 || c.split > MG_MAX_SPLIT || c.split * c.chunks_per_split < chunks ||      // all of k,
+            const bool bad = (whole_k > 0 && n_in <= whole_k && c.split > 1) ||                                     // as told,
+                             c.split < 1 || c.split > MG_MAX_SPLIT || c.split * c.chunks_per_split < chunks ||      // all of k,
                              (c.split - 1) * c.chunks_per_split >= chunks ||                                        // no empty range,
                              c.groups * c.tiles * TG_TASKS < tasks || (c.groups - 1) * c.tiles * TG_TASKS >= tasks ||   // all tasks,
                              (c.split > 1 && (direct_partial_bytes(m, c) > MFMA_PARTIAL_BYTES || c.groups > 2 * n_cu));
