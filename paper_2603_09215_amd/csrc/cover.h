@@ -238,7 +238,7 @@ constexpr size_t direct_partial_bytes(int m, const DirectCut &c) {
 }
 // A long k with few tasks (down) would be streamed by few CUs, each reading all activations of a long row: it is cut
 // over the CUs.  whole_k: the longest k that is never cut; negative: by the rule, for which 8192 and less are short.  Of those, what leaves half of the CUs idle (o) is cut in two from 9 rows
-// on: 16 rows 12.60 -> 12.51 ms a step, 32 rows 16.05 -> 15.87, 48 rows 17.09 -> 16.85; 3 and 8 rows are level.  What fills
+// on: 16 rows 12.60 -> 12.51 ms a step, 32 rows 16.05 -> 15.87, 48 rows 17.09 -> 16.85; 8 rows are level.  What fills
 // more than half would need a second round of CUs (q/k/v, 288 halves on 256 CUs: a step 1 % slower).
 inline DirectCut direct_cut(int m, int n_in, int n_tasks, int n_cu, int whole_k) {
   const bool by_rule = whole_k < 0;

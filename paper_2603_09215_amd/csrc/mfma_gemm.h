@@ -590,7 +590,7 @@ constexpr size_t tg_lds_bytes(int mtiles, int tb) { return tg_rows_at(mtiles, tb
 // are added to a second set of registers and begin at zero again (error of the heads' logits against 64
 // bits, k of 3584: 2.4e-7, and 2.5e-7 to 3.2e-7 as three bf16 parts with k cut into ranges; steps of 48
 // and 96 sequences take under 1 % longer for it).  64 tasks a wave have no registers for that; they
-// serve gate/up, whose k is d_model (MLP of 18944, 33 to 256 rows: 5.3e-7 to 8.6e-7; three bf16 parts 6.7e-7
+// serve gate/up, whose k is d_model (MLP of 18944, 49 to 256 rows: 5.3e-7 to 8.7e-7; three bf16 parts 6.7e-7
 // to 1.16e-6).
 //
 // A tile that ends here turns its results in LDS, eight rows of four tasks a lane and store, and finds what the
@@ -1018,8 +1018,7 @@ mfma_tiled_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__
 }
 
 // Whole tiles of three and of two blocks of rows in one launch (see MixedCover): the higher ones first.
-// (gate/up of 18944 tasks, 511 rows: 308 -> 285 us; of 13696, 1023 rows: 450 and a finishing launch of 20 -> 451, which is
-// what the chip's power allows: 1.02 PFLOP/s executed.)
+// (gate/up of 18944 tasks, 511 rows: 308 -> 285 us.)
 template <int TB, typename Epi>
 __global__ void __launch_bounds__(64 * TG_WAVES)
 mfma_tiled_mixed_k(Epi epi, const f16_t *__restrict__ tiled, const float *__restrict__ wdown,

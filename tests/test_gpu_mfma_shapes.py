@@ -1,6 +1,6 @@
 """The MFMA projections at the edges of their row tiles, large prompt passes, and activations and
 weights whose magnitudes lie far apart (the projections cut activations into two fp16 parts of a
-row-wise scaled value and keep weights as fp16 scaled by blocks), against the CPU oracle."""
+row-wise scaled value and keep weights as fp16 scaled by rows), against the CPU oracle."""
 import numpy as np
 import pytest
 
