@@ -167,7 +167,17 @@ inline MixedCover choose_mixed(int m, int n_in, int n_tasks, int most_blocks, in
   const TileCover tc = cover_tiled(m, n_in, n_tasks, mt, 2, false, false, n_cu, 0);
   if (tc.n_cut) return none;
   const MixedCover mc = cover_mixed(m, n_in, n_tasks, n_cu);
-  return mc.cost < ceil_div(tc.n_whole, n_cu) * wide_tile_cost(mt, ceil_div(n_in, MG_KC)) ? mc : none;
+  const int n_chunks = ceil_div(n_in, MG_KC);
+  const float tile = wide_tile_cost(mt, n_chunks);
+  if (mc.cost >= ceil_div(tc.n_whole, n_cu) * tile) return none;
+  // More than one round of CUs: the chip's power holds the rate then, so that what counts is the work, not what the last
+  // round leaves idle, and equal work in lower tiles takes longer.  (Prompts of a quarter of the layers with it and without: 3584 wide, 16
+  // blocks of rows 5140 and 5219 us, 17 5318 and 5390, 25 7240 and 7320, but 26 7439 and 7356, 27 7477 and 7385; 4096 wide, 22 blocks 8295
+  // and 8452, 23 8487 and 8467.  The work saved there is 7, 2, 4, 1 and -2 %; 4 and 1 %.)  In less than one, it is the idle CUs: 5 and 6
+  // blocks 2932 and 3010, 4096 wide, 7 and 8 4267 and 4447.
+  const float work = (mc.part[0].n_whole + mc.part[1].n_whole) * wide_tile_cost(3, n_chunks) + (mc.part[2].n_whole + mc.part[3].n_whole) * wide_tile_cost(2, n_chunks);
+  if (tc.n_whole > n_cu && work > 0.98f * (float)tc.n_whole * tile) return none;
+  return mc;
 }
 
 // Blocks of 32 rows in a row tile of a projection with 32 tasks a wave and more rows than one tile

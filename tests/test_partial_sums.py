@@ -117,8 +117,12 @@ int main() {
         two += mc.part[1].n_task_tiles > 0;
         // taken only where no result has a longer chain of running sums for it: no tile of equal height is cut
         const TileCover tc = cover_tiled(m, 3584, tasks, tiled_row_blocks_for(m, 3), 2, false, false, n_cu, 4);
-        if (choose_mixed(m, 3584, tasks, 3, n_cu).cost > 0.f) {
+        const MixedCover ch = choose_mixed(m, 3584, tasks, 3, n_cu);
+        if (ch.cost > 0.f) {
           if (tc.n_cut) { printf("in place of cut tiles: %d tasks, %d rows\n", tasks, m); return 1; }
+          // and where there is more than one round, only for less work: fewer blocks of rows
+          const int mt = tiled_row_blocks_for(m, 3), high = ch.part[0].n_whole + ch.part[1].n_whole, low = ch.part[2].n_whole + ch.part[3].n_whole;
+          if (tc.n_whole > n_cu && 3 * high + 2 * low >= mt * tc.n_whole) { printf("no less work: %d tasks, %d rows\n", tasks, m); return 1; }
           ++chosen;
         }
         stays += tc.n_cut > 0;
@@ -148,7 +152,7 @@ def test_covers_by_tiles_of_two_heights_take_every_block_once(tmp_path):
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0, out.stdout
     n, n_two, n_taken, n_cut = (int(w) for w in out.stdout.split() if w.isdigit())
-    assert n > 3000 and n_two > 300 and n_taken > 500 and n_cut > 500, out.stdout
+    assert n > 3000 and n_two > 300 and n_taken > 150 and n_cut > 500, out.stdout
 
 
 CUTS = r"""
