@@ -16,6 +16,10 @@ HIPCC_FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
                # packed fp32 instructions stay off for every HIP source of this library
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
+# One kernel that holds all the operations of a step in a loop: constants and addresses kept over the loop
+# (the machine-level hoisting) spill.
+EXTRA_FLAGS = {"small_steps": ["-mllvm", "-disable-machine-licm"]}
+
 
 def sources() -> list[pathlib.Path]:
     return sorted(CSRC.glob("*.hip"))
@@ -51,7 +55,7 @@ def _compile(src: pathlib.Path) -> pathlib.Path:
     is a memory round trip, and in these kernels it has only ever meant an array that the compiler
     could not keep in registers (an index computed at run time)."""
     obj = OBJ_DIR / (src.stem + ".o")
-    cmd = ["hipcc", *HIPCC_FLAGS, "-Rpass-analysis=kernel-resource-usage", "-c", "-o", str(obj), str(src)]
+    cmd = ["hipcc", *HIPCC_FLAGS, *EXTRA_FLAGS.get(src.stem, []), "-Rpass-analysis=kernel-resource-usage", "-c", "-o", str(obj), str(src)]
     proc = subprocess.run(cmd, capture_output=True, text=True)
     if proc.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src.name}:\n" + proc.stderr[-4000:])

@@ -162,7 +162,7 @@ __device__ __forceinline__ bool row_max(u64 head_key, float &mx) {
 // grid (workgroups per row, rows); logits [row][V]; qbuf [row][V]; class_mass [row][SAMPLE_BINS],
 // zero on entry; best [row]: the head's arg-max key (its upper half is the largest logit).  A NaN
 // logit (the key says so) leaves everything as it is: the emit step reports it.
-__global__ void __launch_bounds__(SAMPLE_THREADS)
+static __global__ void __launch_bounds__(SAMPLE_THREADS)
 sample_mass_k(const float *__restrict__ logits, int V, double temperature, unsigned *__restrict__ qbuf,
               u64 *__restrict__ class_mass, const u64 *__restrict__ best) {
   __shared__ u64 s_first[SAMPLE_BINS];
@@ -269,24 +269,32 @@ __device__ __forceinline__ u64 wave_walk(u64 key, u64 run, unsigned cls, u64 t, 
 // ALONE: one workgroup has the whole row (a vocabulary of at most SAMPLE_CHUNK) and forms its masses itself; qbuf,
 // class_mass and the others are not touched.  (1536 logits: 3.1 and 15.1 us as two launches with some 60 barriers in
 // the second, 8.0 as one with the classes' running sums found once and up to 64 candidates sorted by one wave.)
-template <bool ALONE>
-__global__ void __launch_bounds__(SAMPLE_THREADS)
-sample_pick_k(const float *__restrict__ logits, int V, double temperature, double top_p, const u64 *__restrict__ omega,
-              const unsigned *__restrict__ qbuf, u64 *__restrict__ class_mass, u64 *__restrict__ cand,
-              unsigned *__restrict__ cand_count, unsigned *__restrict__ arrive, u64 *__restrict__ best) {
+// COHERENT (with ALONE): the logits were written by other workgroups of the same launch.
+template <bool ALONE, bool COHERENT = false>
+__device__ __forceinline__ void sample_pick(int row, int block, int n_blocks, const float *__restrict__ logits, int V, double temperature,
+                                            double top_p, u64 word, u64 head_key, const unsigned *__restrict__ qbuf,
+                                            u64 *__restrict__ class_mass, u64 *__restrict__ cand, unsigned *__restrict__ cand_count,
+                                            unsigned *__restrict__ arrive, u64 *__restrict__ best) {
   __shared__ u64 s_first[SAMPLE_BINS], s_keys[SAMPLE_CAP], s_run[SAMPLE_CAP], s_wave[SAMPLE_WAVES], s_pick[3], s_found[3][3];
   __shared__ int s_cnt[SAMPLE_WAVES], s_n, s_slot, s_last;
   constexpr int PER = SAMPLE_CHUNK / SAMPLE_THREADS;
   static_assert(sizeof(unsigned) * SAMPLE_CHUNK <= sizeof(s_run), "a row of masses takes the place of the running sums");
-  const int row = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int tid = threadIdx.x;
+  if constexpr (COHERENT) asm volatile("" : "+v"(tid));   // (in a loop over steps: nothing of it is kept from one to the next)
+  const int lane = tid & 63, wave = tid >> 6;
   const float *lg = logits + (size_t)row * V;
+  auto logit = [&](int i) { return COHERENT ? load_device_scope(lg + i) : lg[i]; };
+  auto draw = [&](int tok) {
+    const u64 key = argmax_key(logit(tok), tok);
+    if constexpr (COHERENT) __hip_atomic_store(best + row, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else best[row] = key;
+  };
   const unsigned *q = ALONE ? (const unsigned *)s_run : qbuf + (size_t)row * V;
   u64 *row_mass = class_mass + (size_t)row * SAMPLE_BINS;
   u64 *row_cand = cand + (size_t)row * SAMPLE_CAP;
-  const int c0 = blockIdx.x * SAMPLE_CHUNK;
-  const u64 word = omega[row];
+  const int c0 = block * SAMPLE_CHUNK;
   float mx;
-  if (!row_max(best[row], mx)) return;
+  if (!row_max(head_key, mx)) return;
 
   // ---- every workgroup: total, target, the classes that can matter
   unsigned mass[PER];
@@ -294,14 +302,14 @@ sample_pick_k(const float *__restrict__ logits, int V, double temperature, doubl
     float l[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-      const int i = j * SAMPLE_THREADS + threadIdx.x;
-      l[j] = lg[i < V ? i : 0];
+      const int i = j * SAMPLE_THREADS + tid;
+      l[j] = logit(i < V ? i : 0);
     }
-    for (int b = threadIdx.x; b < SAMPLE_BINS; b += SAMPLE_THREADS) s_first[b] = 0;
+    for (int b = tid; b < SAMPLE_BINS; b += SAMPLE_THREADS) s_first[b] = 0;
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-      const int i = j * SAMPLE_THREADS + threadIdx.x;
+      const int i = j * SAMPLE_THREADS + tid;
       mass[j] = 0u;
       if (j * SAMPLE_THREADS < V) {   // (whole waves vote)
         if (i < V) mass[j] = mass_of(l[j], mx, temperature);
@@ -312,12 +320,12 @@ sample_pick_k(const float *__restrict__ logits, int V, double temperature, doubl
   } else {
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-      const int i = c0 + j * SAMPLE_THREADS + threadIdx.x;
+      const int i = c0 + j * SAMPLE_THREADS + tid;
       mass[j] = i < V ? q[i] : 0u;
     }
-    for (int b = threadIdx.x; b < SAMPLE_BINS; b += SAMPLE_THREADS) s_first[b] = row_mass[b];
+    for (int b = tid; b < SAMPLE_BINS; b += SAMPLE_THREADS) s_first[b] = row_mass[b];
   }
-  if (threadIdx.x == 0) s_n = 0;
+  if (tid == 0) s_n = 0;
   __syncthreads();
   ClassRun classes;
   const u64 total = classes.init(s_first, s_wave);
@@ -338,7 +346,7 @@ sample_pick_k(const float *__restrict__ logits, int V, double temperature, doubl
   // ---- this workgroup's candidates, then into the row's list
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
-    const int i = c0 + j * SAMPLE_THREADS + threadIdx.x;
+    const int i = c0 + j * SAMPLE_THREADS + tid;
     const unsigned v = mass[j];
     if (v != 0) {
       const unsigned cls = mass_class(v);
@@ -351,21 +359,21 @@ sample_pick_k(const float *__restrict__ logits, int V, double temperature, doubl
   __syncthreads();
   if constexpr (!ALONE) {
     const int n_local = s_n;
-    if (threadIdx.x == 0 && n_local > 0)
+    if (tid == 0 && n_local > 0)
       s_slot = (int)__hip_atomic_fetch_add(cand_count + row, (unsigned)n_local, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (n_local > 0) {
       const int slot = s_slot;
-      for (int j = threadIdx.x; j < n_local && j < SAMPLE_CAP; j += SAMPLE_THREADS)
+      for (int j = tid; j < n_local && j < SAMPLE_CAP; j += SAMPLE_THREADS)
         if (slot + j < SAMPLE_CAP)
           __hip_atomic_store(row_cand + slot + j, s_keys[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     wait_memory_ops();                     // candidates written before the count
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
       const unsigned prev = __hip_atomic_fetch_add(arrive + row, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      s_last = prev == gridDim.x - 1;
+      s_last = prev == (unsigned)n_blocks - 1;
       if (s_last) {
         __hip_atomic_store(arrive + row, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s_n = (int)__hip_atomic_load(cand_count + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -376,7 +384,7 @@ sample_pick_k(const float *__restrict__ logits, int V, double temperature, doubl
     __syncthreads();
     if (!s_last) return;
     // the last workgroup of the row (every workgroup has read the class masses by now)
-    for (int b = threadIdx.x; b < SAMPLE_BINS; b += SAMPLE_THREADS) row_mass[b] = 0;
+    for (int b = tid; b < SAMPLE_BINS; b += SAMPLE_THREADS) row_mass[b] = 0;
   }
   const int n = s_n;
   if (n <= 64) {
@@ -412,7 +420,7 @@ sample_pick_k(const float *__restrict__ logits, int V, double temperature, doubl
       const u64 k = wave_walk(key, run, (unsigned)s_found[0][0], x + 1 - s_found[0][1], through);
       if (lane == 0) {
         const int tok = (int)(0xffffffffu - (unsigned)(k & 0xffffffffull));
-        best[row] = argmax_key(lg[tok], tok);
+        draw(tok);
       }
     }
     return;
@@ -421,14 +429,14 @@ sample_pick_k(const float *__restrict__ logits, int V, double temperature, doubl
     // candidates into LDS, padded with zero keys (they sort last) to a power of two
     int np = 64;
     while (np < n) np <<= 1;
-    for (int i = threadIdx.x; i < np; i += SAMPLE_THREADS)
+    for (int i = tid; i < np; i += SAMPLE_THREADS)
       if (i >= n) s_keys[i] = 0ull;
       else if (!ALONE) s_keys[i] = __hip_atomic_load(row_cand + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // bitonic sort, largest key first
     for (int k = 2; k <= np; k <<= 1)
       for (int j = k >> 1; j > 0; j >>= 1) {
         __syncthreads();
-        const int t = threadIdx.x;
+        const int t = tid;
         if (t < np / 2) {
           const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1)), p = i | j;
           const u64 a = s_keys[i], b = s_keys[p];
@@ -439,7 +447,7 @@ sample_pick_k(const float *__restrict__ logits, int V, double temperature, doubl
     __syncthreads();
     // running sums of the sorted masses: thread t holds candidates 2t and 2t + 1
     {
-      const int i0 = 2 * threadIdx.x;
+      const int i0 = 2 * tid;
       const u64 q0 = i0 < np ? s_keys[i0] >> 32 : 0, q1 = i0 + 1 < np ? s_keys[i0 + 1] >> 32 : 0;
       u64 incl = q0 + q1;
 #pragma unroll
@@ -460,9 +468,9 @@ sample_pick_k(const float *__restrict__ logits, int V, double temperature, doubl
     classes.find(x + 1, s_found[0]);
     __syncthreads();
     class_walk(s_keys, s_run, np, (unsigned)s_found[0][0], x + 1 - s_found[0][1], s_pick);
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
       const int tok = (int)(0xffffffffu - (unsigned)(s_pick[0] & 0xffffffffull));
-      best[row] = argmax_key(lg[tok], tok);
+      draw(tok);
     }
     return;
   }
@@ -494,12 +502,22 @@ sample_pick_k(const float *__restrict__ logits, int V, double temperature, doubl
       const u64 hits = __ballot(hit);
       const int c = __popcll(hits);
       if (need <= c) {
-        if (hit && __popcll(hits & ((1ull << lane) - 1ull)) == need - 1) best[row] = argmax_key(lg[i], i);
+        if (hit && __popcll(hits & ((1ull << lane) - 1ull)) == need - 1) draw(i);
         break;
       }
       need -= c;
     }
   }
+}
+
+template <bool ALONE>
+__global__ void __launch_bounds__(SAMPLE_THREADS)
+sample_pick_k(const float *__restrict__ logits, int V, double temperature, double top_p, const u64 *__restrict__ omega,
+              const unsigned *__restrict__ qbuf, u64 *__restrict__ class_mass, u64 *__restrict__ cand,
+              unsigned *__restrict__ cand_count, unsigned *__restrict__ arrive, u64 *__restrict__ best) {
+  const int row = blockIdx.y;
+  sample_pick<ALONE>(row, blockIdx.x, gridDim.x, logits, V, temperature, top_p, omega[row], best[row], qbuf, class_mass, cand, cand_count,
+                     arrive, best);
 }
 
 }  // namespace spark

@@ -13,7 +13,7 @@ namespace spark {
 enum { ST_LEN = 0, ST_G, ST_JSTREAM, ST_NPENDING, ST_OFFSET, ST_NEXT, ST_ACTIVE, ST_LASTFULL, ST_TEXTBUDGET, ST_PHASE, ST_WORDS };
 // plan words
 enum { PL_NLOWER = 0, PL_NUPPER, PL_NEE, PL_NFULL, PL_ERR, PL_WORDS = 8 };
-enum { ERR_NAN = 1, ERR_INACTIVE = 2 };
+enum { ERR_NAN = 1, ERR_INACTIVE = 2, ERR_STALLED = 4 };
 
 struct SchedParams {
   int n_layers, exit_layer, period_k, phase, scope, n_text, n_speech;
@@ -91,7 +91,7 @@ __device__ __forceinline__ void emit_one(const StepIO &io, int i, const int *__r
   st[ST_LASTFULL] = full;
 }
 
-__global__ void __launch_bounds__(SCHED_THREADS)
+static __global__ void __launch_bounds__(SCHED_THREADS)
 emit_k(StepIO io, const int *__restrict__ forced, int *__restrict__ out_tokens) {
   if ((int)threadIdx.x < io.n) emit_one(io, threadIdx.x, forced, out_tokens);
 }
@@ -199,7 +199,7 @@ embed_rows_k(const RowDesc *__restrict__ rows, const int *__restrict__ state,
 }
 
 // rope[pos][i] = (cos, sin)(pos * inv_freq[i]), angle formed in fp32, evaluated in fp64
-__global__ void rope_table_k(const float *__restrict__ inv_freq, int half, int max_pos, float2 *rope) {
+static __global__ void rope_table_k(const float *__restrict__ inv_freq, int half, int max_pos, float2 *rope) {
   int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= half * max_pos) return;
   int pos = idx / half, i = idx - pos * half;

@@ -23,6 +23,7 @@
 #include "mfma_gemm.h"
 #include "sampling.h"
 #include "sched.h"
+#include "small_steps.h"
 
 using namespace spark;
 
@@ -38,6 +39,11 @@ constexpr int MAX_STEPS_PER_CALL = 256;
 constexpr int MFMA_MIN_ROWS = 5;
 constexpr int TILED_WIDE_TASKS = 8192;   // gate/up from here on has tiles enough for 64 tasks a wave at any row count (32 tiles)
 constexpr int MAX_SEQ_LEN = 16384;
+// Models whose steps can run in one launch (small_steps.h): fp32, a layer and a head of at most so many bytes
+// (for the calls it pays for: small_steps_pay).
+constexpr size_t SMALL_LAYER_BYTES = (size_t)8 << 20;
+constexpr int SMALL_FLAGS_AT = 32;   // words from the plan to the words of the hand-overs: a cache line of their own
+static_assert(SMALL_FLAGS_AT >= PL_WORDS, "the plan comes first");
 
 struct Layout {  // byte offsets into the scratch buffer
   size_t state, page_table, plan, lower, upper, ee, full, prefill_rows, prefill_tokens, seq_ids,
@@ -118,6 +124,10 @@ struct spark_ctx {
   bool has_tiled = false;      // the context owns the MFMA-ordered copy of the projection weights
   bool use_tiled = true;       // "mfma_tiled" = 0 keeps the MFMA projections on the kernel that stages weights through LDS
   bool fuse_norm = true;       // the residual projections' finishing launches prepare the next norm's input (no separate launch)
+  bool small_ok = false;       // the model's steps can run in one launch
+  size_t small_layer_bytes = 0;   // of one layer's weights
+  bool use_small = true;       // "small_steps" = 0 keeps them on a launch per operation
+  unsigned small_epoch = 0;    // such launches so far
   bool static_scratch = false; // the scratch area is the library's static device array (spark_init_static)
   int device = 0;
   float temperature = 0.f, top_p = 0.f;   // nucleus sampling, off while temperature <= 0
@@ -271,7 +281,7 @@ void layout(const spark_config &c, const Derived &d, Layout &l) {
   const size_t qw = (size_t)c.n_q_heads * c.head_dim;
   l.state = take(sizeof(int) * ST_WORDS * c.max_batch);
   l.page_table = take(sizeof(int) * (size_t)d.max_pages * c.max_batch);
-  l.plan = take(sizeof(int) * PL_WORDS);
+  l.plan = take(sizeof(int) * (SMALL_FLAGS_AT + SMALL_WGS));
   l.lower = take(sizeof(RowDesc) * c.max_batch);
   l.upper = take(sizeof(RowDesc) * (size_t)c.max_batch * d.rmax);
   l.ee = take(sizeof(RowDesc) * c.max_batch);
@@ -1176,6 +1186,92 @@ int enqueue_step(spark_ctx *c, int n, int n_upper, int n_ee, int n_full, const i
   return SPARK_OK;
 }
 
+// Where the words that the phases of such a launch hand over lie: in the MLP activations of the other path, and in
+// what it keeps from the queries to the attention partials
+struct SmallWords { size_t act, x, end_a, qkv, attn, u, end_b; };
+SmallWords small_words(const spark_config &g, int n, int rows) {
+  const size_t qw = (size_t)g.n_q_heads * g.head_dim, kvw = (size_t)g.n_kv_heads * g.head_dim, dm = g.d_model;
+  SmallWords w;
+  w.act = 0;
+  w.x = w.act + (size_t)rows * g.d_ffn;
+  w.end_a = w.x + (size_t)(n + rows) * dm;
+  w.qkv = 0;
+  w.attn = w.qkv + (size_t)rows * (qw + 2 * kvw);
+  w.u = w.attn + (size_t)rows * qw;
+  w.end_b = w.u + (size_t)n * dm;
+  return w;
+}
+
+size_t layer_bytes_fp32(const spark_config &g) {
+  const size_t qw = (size_t)g.n_q_heads * g.head_dim, kvw = (size_t)g.n_kv_heads * g.head_dim, dm = g.d_model;
+  return sizeof(float) * ((qw + 2 * kvw) * dm + dm * qw + 3 * (size_t)g.d_ffn * dm);
+}
+
+// Whether the steps of a model can run in one launch, whatever the call.  Every workgroup has a task of every
+// projection of a layer: that it has written its part of a row then says that it no longer reads what the row was made of.
+bool shape_allows_small(const spark_config &g, const Derived &d, const Layout &lo) {
+  const size_t qw = (size_t)g.n_q_heads * g.head_dim, kvw = (size_t)g.n_kv_heads * g.head_dim, dm = g.d_model;
+  const int half_d = g.d_model / 2, wide = SMALL_CHUNK * SMALL_MAX_CHUNKS;
+  const SmallWords w = small_words(g, SMALL_SEQS, SMALL_ROWS);
+  return g.dtype == SPARK_DTYPE_FP32 && g.d_model <= SMALL_NORM_CHUNKS * SMALL_CHUNK && (int)qw <= wide && g.d_ffn <= wide && d.V <= 65536 &&
+         half_d >= SMALL_WGS && g.d_ffn >= SMALL_WGS &&
+         layer_bytes_fp32(g) <= SMALL_LAYER_BYTES &&
+         sizeof(float) * (size_t)d.V * dm <= SMALL_LAYER_BYTES &&
+         small_phase(g.d_model, (int)(qw + 2 * kvw) / 2).tile > 0 && small_phase((int)qw, half_d).tile > 0 &&
+         small_phase(g.d_model, g.d_ffn).tile > 0 && small_phase(g.d_ffn, half_d).tile > 0 && small_phase(g.d_model, (d.V + 1) / 2).tile > 0 &&
+         sizeof(u64) * w.end_a <= lo.mfma_part - lo.act && sizeof(u64) * w.end_b <= lo.lens_u - lo.qbuf;
+}
+
+// Whether a call's steps are better in one launch: rows of the largest pass, positions of the longest context.
+// The launch has an eighth of the chip, so it loses what it gains where there is much to do: the sums (rows times the
+// layer's weights) and the attention tasks of a workgroup (rows times query heads over SMALL_WGS) times the context.
+// Measured, us a step, one launch / a launch per operation, layers of 3.9 and of 8.1 MB, with the sum below:
+//   3.9 MB  1 sequence 42.9 / 83.1 (0.1), 8: 72.5 / 123.4 (0.6), 16: 115 / 159 (1.1), 1 of 900 tokens 81 / 95 (0.3), 8 of 900 123 / 147 (1.4)
+//   8.1 MB  1 sequence 49.5 / 84.9 (0.1), 8: 106 / 132 (1.1), 4 of 900 121 / 138 (1.4), 8 of 400 153 / 146 (1.9), 16: 184 / 168 (2.2), 8 of 900 209 / 155 (2.8)
+bool small_steps_pay(const spark_ctx *c, int n, int rows, int positions) {
+  if (!c->small_ok || !c->use_small || c->prof_class >= 0 || n > SMALL_SEQS || rows > SMALL_ROWS || positions > SMALL_CTX) return false;
+  const int rounds = (rows * c->cfg.n_q_heads + SMALL_WGS - 1) / SMALL_WGS;
+  return rows * (double)c->small_layer_bytes / (double)(256u << 20) + rounds * (double)positions / 4096.0 <= 1.5;
+}
+
+// all steps of a call in one launch; rows: of the largest pass
+bool enqueue_small_steps(spark_ctx *c, int steps, int n, int rows, bool forced, bool sampled) {
+  const spark_config &g = c->cfg;
+  SmallSteps a;
+  a.sp = c->sp;
+  a.d = g.d_model; a.nq = g.n_q_heads; a.nkv = g.n_kv_heads; a.F = g.d_ffn; a.V = c->dv.V; a.eps = g.rms_eps;
+  const int qw = g.n_q_heads * g.head_dim, half_d = g.d_model / 2;
+  a.qkv = small_phase(g.d_model, (g.n_q_heads + 2 * g.n_kv_heads) * (g.head_dim / 2));
+  a.o = small_phase(qw, half_d); a.gateup = small_phase(g.d_model, g.d_ffn); a.down = small_phase(g.d_ffn, half_d);
+  a.lens = small_phase(g.d_model, half_d); a.vocab = small_phase(g.d_model, (c->dv.V + 1) / 2);
+  auto f = [](const void *p) { return (const float *)p; };
+  a.embed = f(c->w.embed); a.attn_norm = c->w.attn_norm; a.wq = f(c->w.wq); a.wk = f(c->w.wk); a.wv = f(c->w.wv); a.wo = f(c->w.wo);
+  a.mlp_norm = c->w.mlp_norm; a.wg = f(c->w.wg); a.wu = f(c->w.wu); a.wd = f(c->w.wd); a.final_norm = c->w.final_norm;
+  a.lm_head = f(c->w.lm_head); a.lens_a = f(c->w.lens_a); a.lens_b = c->w.lens_b; a.lens_norm = c->w.lens_norm; a.lens_head = f(c->w.lens_head);
+  a.rope = at<float2>(c, c->lo.rope);
+  a.kv = kv_view(c);
+  a.hidden = c->pb.hidden; a.logits = at<float>(c, c->lo.logits);
+  const SmallWords w = small_words(g, n, rows);
+  a.words_a = at<u64>(c, c->lo.act); a.words_b = at<u64>(c, c->lo.qbuf);
+  a.count_a = (int)w.end_a; a.count_b = (int)w.end_b;
+  a.act_words = a.words_a + w.act; a.x_words = a.words_a + w.x;
+  a.qkv_words = a.words_b + w.qkv; a.attn_words = a.words_b + w.attn; a.u_words = a.words_b + w.u;
+  a.wg_best = at<u64>(c, c->lo.sample_cand);   // (the sampler of a vocabulary this small keeps no list there)
+  a.plan = at<int>(c, c->lo.plan);
+  a.flags = (unsigned *)(a.plan + SMALL_FLAGS_AT);
+  a.state = at<int>(c, c->lo.state); a.seq_ids = at<int>(c, c->lo.seq_ids);
+  a.forced = forced ? at<int>(c, c->lo.forced) : nullptr;
+  a.words = sampled ? at<u64>(c, c->lo.rand_words) : nullptr;
+  a.best = at<u64>(c, c->lo.best);
+  a.out_tokens = at<int>(c, c->lo.out_tokens); a.out_depth = at<int>(c, c->lo.out_depth);
+  a.n = n; a.steps = steps;
+  a.temperature = c->temperature; a.top_p = c->top_p;
+  a.epoch = ++c->small_epoch;
+  if (launch_small_steps(a, g.head_dim, c->stream) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
 int decode_chunk(spark_ctx *c, int steps, int n, const int32_t *seq_ids, const int32_t *forced,
                  const uint64_t *rand_words, int32_t *out_tokens, int32_t *out_depth) {
   const spark_config &g = c->cfg;
@@ -1237,10 +1333,13 @@ int decode_chunk(spark_ctx *c, int steps, int n, const int32_t *seq_ids, const i
   }
   std::vector<int> want_depth((size_t)steps * n), want_text((size_t)steps * n),
       want_rows((size_t)steps * n);
+  struct Shape { int n_upper, n_ee, n_full, max_pos; };
+  std::vector<Shape> shapes(steps);
+  int most_rows = 0;
   for (int st = 0; st < steps; ++st) {
-    int n_upper = 0, n_ee = 0, n_full = 0, max_pos = 0;
-    for (int i = 0; i < n; ++i) max_pos = std::max(max_pos, mir[i].len);   // position of the new row
-    c->attn_splits_now = max_pos / ATTN_SLICE + 1;
+    Shape &sh = shapes[st];
+    sh = Shape{0, 0, 0, 0};
+    for (int i = 0; i < n; ++i) sh.max_pos = std::max(sh.max_pos, mir[i].len);   // position of the new row
     for (int i = 0; i < n; ++i) {
       int is_text, full;
       const Seq &sq = c->seqs[seq_ids[i]];
@@ -1248,24 +1347,34 @@ int decode_chunk(spark_ctx *c, int steps, int n, const int32_t *seq_ids, const i
       want_depth[st * n + i] = full ? g.n_layers : g.exit_layer;
       want_text[st * n + i] = is_text;
       want_rows[st * n + i] = full ? mir[i].npend + 1 : 0;
-      if (full) { n_upper += mir[i].npend + 1; ++n_full; mir[i].npend = 0; }
-      else { ++n_ee; mir[i].npend += 1; }
+      if (full) { sh.n_upper += mir[i].npend + 1; ++sh.n_full; mir[i].npend = 0; }
+      else { ++sh.n_ee; mir[i].npend += 1; }
       mir[i].g += 1;
       if (!is_text) mir[i].j += 1;
       mir[i].len += 1;
     }
-    const int *pf = forced && st ? at<int>(c, c->lo.forced) + (size_t)(st - 1) * n : nullptr;
-    int *pt = st ? at<int>(c, c->lo.out_tokens) + (size_t)(st - 1) * n : nullptr;
-    int *od = at<int>(c, c->lo.out_depth) + (size_t)st * n;
-    const unsigned long long *rw =
-        rand_words ? at<unsigned long long>(c, c->lo.rand_words) + (size_t)st * n : nullptr;
-    rc = g.dtype == SPARK_DTYPE_BF16 ? enqueue_step<bf16_t>(c, n, n_upper, n_ee, n_full, pf, pt, rw, od)
-                                     : enqueue_step<float>(c, n, n_upper, n_ee, n_full, pf, pt, rw, od);
-    if (rc) return rc;
+    most_rows = std::max(most_rows, sh.n_upper);
   }
-  emit_k<<<1, SCHED_THREADS, 0, c->stream>>>(step_io(c, n), forced ? at<int>(c, c->lo.forced) + (size_t)(steps - 1) * n : nullptr,
-                                            at<int>(c, c->lo.out_tokens) + (size_t)(steps - 1) * n);
-  HIP_TRY(c, hipGetLastError());
+  const bool sampled = rand_words && c->temperature > 0.f;
+  // (a device that has no room for all workgroups of such a launch at once refuses it)
+  if (!(small_steps_pay(c, n, std::max(n, most_rows), shapes[steps - 1].max_pos + 1) && (!sampled || c->dv.V <= SAMPLE_CHUNK) &&
+        enqueue_small_steps(c, steps, n, std::max(n, most_rows), forced != nullptr, sampled))) {
+    for (int st = 0; st < steps; ++st) {
+      const Shape &sh = shapes[st];
+      c->attn_splits_now = sh.max_pos / ATTN_SLICE + 1;
+      const int *pf = forced && st ? at<int>(c, c->lo.forced) + (size_t)(st - 1) * n : nullptr;
+      int *pt = st ? at<int>(c, c->lo.out_tokens) + (size_t)(st - 1) * n : nullptr;
+      int *od = at<int>(c, c->lo.out_depth) + (size_t)st * n;
+      const unsigned long long *rw =
+          rand_words ? at<unsigned long long>(c, c->lo.rand_words) + (size_t)st * n : nullptr;
+      rc = g.dtype == SPARK_DTYPE_BF16 ? enqueue_step<bf16_t>(c, n, sh.n_upper, sh.n_ee, sh.n_full, pf, pt, rw, od)
+                                       : enqueue_step<float>(c, n, sh.n_upper, sh.n_ee, sh.n_full, pf, pt, rw, od);
+      if (rc) return rc;
+    }
+    emit_k<<<1, SCHED_THREADS, 0, c->stream>>>(step_io(c, n), forced ? at<int>(c, c->lo.forced) + (size_t)(steps - 1) * n : nullptr,
+                                              at<int>(c, c->lo.out_tokens) + (size_t)(steps - 1) * n);
+    HIP_TRY(c, hipGetLastError());
+  }
 
   // results
   const size_t cnt = (size_t)steps * n;
@@ -1278,6 +1387,11 @@ int decode_chunk(spark_ctx *c, int steps, int n, const int32_t *seq_ids, const i
   HIP_TRY(c, hipMemcpyAsync(h_plan, at<int>(c, c->lo.plan), sizeof(int) * PL_WORDS,
                             hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
+  if (h_plan[PL_ERR] & ERR_STALLED) {
+    int zero = 0;
+    (void)hipMemcpy(at<int>(c, c->lo.plan) + PL_ERR, &zero, sizeof(int), hipMemcpyHostToDevice);
+    return fail(c, SPARK_EHIP, "the workgroups of a launch waited for each other in vain");
+  }
   memcpy(out_tokens, h_tok, sizeof(int) * cnt);
   memcpy(out_depth, h_dep, sizeof(int) * cnt);
 
@@ -1421,6 +1535,11 @@ int init_context(const spark_config *cfg, const spark_weights *weights, void *kv
   // the MFMA kernels load 16-byte vectors of 8 weights; other widths stay on the vector kernel
   c->mfma_ok = cfg->d_model % 8 == 0 && (cfg->n_q_heads * cfg->head_dim) % 8 == 0 && cfg->d_ffn % 8 == 0;
   c->use_mfma = c->mfma_ok;
+  int cooperative = 0;
+  c->small_ok = shape_allows_small(*cfg, c->dv, c->lo) &&
+                hipDeviceGetAttribute(&cooperative, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && cooperative &&
+                prop.multiProcessorCount >= SMALL_WGS && small_steps_fit(cfg->head_dim);
+  c->small_layer_bytes = layer_bytes_fp32(*cfg);
   // a scratch area of the full size holds the MFMA-ordered copy of the projection weights (the
   // static area never does)
   tiled_map(*cfg, c->dv, c->tm);
@@ -1555,6 +1674,7 @@ int spark_tune(spark_ctx *c, const char *name, int32_t value) {
   else if (k == "attn_prompt_min_rows") c->attn_prompt_min_rows = std::max(0, (int)value);
   else if (k == "direct_max_rows") c->direct_max_rows = value;
   else if (k == "direct_whole_k") c->direct_whole_k = value;
+  else if (k == "small_steps") c->use_small = value != 0;
   else if (k == "fuse_norm") c->fuse_norm = value != 0;
   else return fail(c, SPARK_EINVAL, "unknown tuning name '%s'", name);
   return SPARK_OK;

@@ -1,0 +1,109 @@
+"""Steps of small fp32 models in one launch (small_steps.h): the shapes and row counts at which its phases can go wrong,
+against the oracle, and against the same steps as a launch per operation."""
+from contextlib import closing
+
+import numpy as np
+import pytest
+
+import workloads as wl
+from parity_util import compare_run, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sb():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_09215_amd import binding
+    binding.load_library()
+    return binding
+
+
+# the narrowest model (a task of every projection for each of the 32 workgroups); widths that are no multiple of a
+# wave's 256 elements, an odd vocabulary; the longest normalised rows (four pieces); heads of 128 with one query head
+# per key head, pages that hold less than a trip of attention
+SHAPES = [
+    ("narrow", dict(d_model=64, n_q_heads=1, n_kv_heads=1, d_ffn=32, vocab_text=20, vocab_speech=13), 1, 16),
+    ("ragged", dict(d_model=264, n_q_heads=6, n_kv_heads=3, d_ffn=1032, vocab_text=900, vocab_speech=401), 3, 16),
+    ("long rows", dict(d_model=1024, n_q_heads=2, n_kv_heads=1, d_ffn=256, vocab_text=900, vocab_speech=100), 5, 64),
+    ("wide heads", dict(d_model=256, n_q_heads=3, n_kv_heads=3, head_dim=128, d_ffn=520, vocab_text=600, vocab_speech=7), 2, 48),
+]
+
+
+@pytest.mark.parametrize("name,over,batch,page", SHAPES, ids=[s[0] for s in SHAPES])
+def test_shapes(sb, name, over, batch, page):
+    w = wl.TINY
+    shape = w.shape.replace(name=name, **over)
+    weights = wl.make_weights(shape, seed=4, gain_std=0.1)
+    say(f"small steps, {name}")
+    # a first prompt of one token: attention over nothing but the pass' own rows
+    prompts = [wl.make_prompt(shape, 1 + 17 * b, seed=60 + b) for b in range(batch)]
+    with closing(sb.Spark(shape, w.schedule, weights, max_batch=batch, max_seq_len=160, kv_page_tokens=page)) as sp:
+        compare_run(sp, shape, w.schedule, weights, prompts, [b % 6 for b in range(batch)], 20, chunk=9, check_kv_every=9,
+                    label=f"small {name}")
+
+
+def _run(sb, shape, sched, weights, lens, offsets, calls, small, sample=False, stream=None):
+    """tokens, depths, the logits after each call and the cache of the last position, free running"""
+    n = len(lens)
+    with closing(sb.Spark(shape, sched, weights, max_batch=n, max_seq_len=1100, kv_page_tokens=64, stream=stream)) as sp:
+        sp.tune("small_steps", small)
+        if sample:
+            sp.set_sampling(0.7, 0.9)
+        ids = [sp.seq_open(o) for o in offsets]
+        for b, (s, m) in enumerate(zip(ids, lens)):
+            sp.prefill(s, wl.make_prompt(shape, m, seed=80 + b))
+        words = np.random.Generator(np.random.Philox(9)).integers(0, 2 ** 64, size=(sum(calls), n), dtype=np.uint64)
+        tok, dep, logits, at = [], [], [], 0
+        for steps in calls:
+            t, d = sp.decode_sampled(steps, ids, words[at:at + steps]) if sample else sp.decode(steps, ids)
+            tok.append(t), dep.append(d), logits.append(np.stack([sp.get_logits(s)[0] for s in ids]))
+            at += steps
+        kv = [np.concatenate(sp.get_kv(s, 0, m + at - 2)) for s, m in zip(ids, lens)]
+    return np.concatenate(tok), np.concatenate(dep), np.stack(logits), np.stack(kv)
+
+
+# 16 sequences are the most, 64 rows of a pass too (16 flushes of four rows); contexts that outgrow the launch's 1024
+# positions during the run go on as launches per operation
+@pytest.mark.parametrize("lens,aligned,calls,sample", [
+    ([5 + 3 * b for b in range(16)], True, [7, 1, 12], False),
+    ([9 + 2 * b for b in range(17)], True, [6], False),
+    ([1012, 700, 63], False, [5, 5, 8], False),
+    ([30, 2, 200, 64], False, [11, 4], True),
+], ids=["most rows", "one sequence more", "longest contexts", "sampled"])
+def test_same_as_a_launch_per_operation(sb, lens, aligned, calls, sample):
+    w = wl.TINY
+    weights = wl.make_weights(w.shape, seed=0, gain_std=0.1)
+    say(f"small steps against launches, {len(lens)} sequences")
+    offsets = [0 if aligned else b % 6 for b in range(len(lens))]
+    a = _run(sb, w.shape, w.schedule, weights, lens, offsets, calls, 1, sample)
+    b = _run(sb, w.shape, w.schedule, weights, lens, offsets, calls, 0, sample)
+    assert np.array_equal(a[1], b[1]) and np.array_equal(a[0], b[0])
+    # sums of at most 1024 terms in 32 bits in another order, through four layers: 5e-7 seen, logits of about 0.3
+    assert np.abs(a[2] - b[2]).max() < 1e-5 and np.abs(a[3] - b[3]).max() < 1e-5
+
+
+def test_two_contexts_on_two_threads(sb):
+    """launches that wait inside share the chip: each thread's results are those it gets alone"""
+    import threading
+
+    import torch
+    w = wl.TINY
+    weights = wl.make_weights(w.shape, seed=0, gain_std=0.1)
+    say("small steps on two threads")
+    lens = [20, 33]
+    alone = _run(sb, w.shape, w.schedule, weights, lens, [0, 2], [10] * 4, 1)
+    out = [None, None]
+
+    def go(i):
+        out[i] = _run(sb, w.shape, w.schedule, weights, lens, [0, 2], [10] * 4, 1, stream=torch.cuda.Stream())
+
+    threads = [threading.Thread(target=go, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    for o in out:
+        assert o is not None and all(np.array_equal(x, y) for x, y in zip(o, alone))
