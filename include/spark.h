@@ -312,7 +312,9 @@ int spark_measure_read(spark_ctx *ctx, const void *buf, size_t bytes, int32_t re
  *   every RMSNorm of the batched path is its own launch), "prefill_rows" (prompt rows per pass, a
  *   multiple of 32, at most 1024, or 256 where the scratch area has no room for more; 0: by the
  *   length of the prompt, as in a new context), "small_steps" (0: the steps of small fp32 models are
- *   launches per operation; otherwise all steps of a call are one cooperative launch where that is faster).
+ *   launches per operation; otherwise all steps of a call are one cooperative launch where that is faster),
+ *   "one_row" (0: the layers of a pass of one row are launches per operation; 1: they are one cooperative
+ *   launch where that is faster, as in a new context; 2: wherever the shape allows it).
  * SPARK_EINVAL for an unknown name. */
 int spark_tune(spark_ctx *ctx, const char *name, int32_t value);
 

@@ -18,7 +18,7 @@ HIPCC_FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
 
 # One kernel that holds all the operations of a step in a loop: constants and addresses kept over the loop
 # (the machine-level hoisting) spill.
-EXTRA_FLAGS = {"small_steps": ["-mllvm", "-disable-machine-licm"]}
+EXTRA_FLAGS = {"small_steps": ["-mllvm", "-disable-machine-licm"], "one_row": ["-mllvm", "-disable-machine-licm"]}
 
 
 def sources() -> list[pathlib.Path]:

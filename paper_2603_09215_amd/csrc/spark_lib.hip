@@ -21,6 +21,7 @@
 #include "gemv.h"
 #include "measure.h"
 #include "mfma_gemm.h"
+#include "one_row.h"
 #include "sampling.h"
 #include "sched.h"
 #include "small_steps.h"
@@ -128,6 +129,11 @@ struct spark_ctx {
   size_t small_layer_bytes = 0;   // of one layer's weights
   bool use_small = true;       // "small_steps" = 0 keeps them on a launch per operation
   unsigned small_epoch = 0;    // such launches so far
+  bool row_ok = false;         // the layers of a pass of one row can run in one launch
+  int use_row = 1;             // "one_row": 0 keeps them on a launch per operation, 2 takes the one launch also where it does not pay
+  size_t layer_bytes = 0;      // of one layer's weights, bf16
+  bool row_words_clean = false;   // no word of its hand-overs holds a number that is still to come
+  unsigned row_tag = 0;        // the last number used
   bool static_scratch = false; // the scratch area is the library's static device array (spark_init_static)
   int device = 0;
   float temperature = 0.f, top_p = 0.f;   // nucleus sampling, off while temperature <= 0
@@ -625,6 +631,11 @@ int mfma_occupancy(spark_ctx *c) {
   return found->second;
 }
 
+// (what lies there then are no words of a hand-over any more)
+float *partial_sums(spark_ctx *c) {
+  c->row_words_clean = false;
+  return at<float>(c, c->lo.mfma_part);
+}
 // (a cover is chosen so that its partial sums fit; one that did not would write into what lies behind them)
 int partials_fit(spark_ctx *c, size_t bytes) {
   if (bytes <= MFMA_PARTIAL_BYTES) return SPARK_OK;
@@ -657,7 +668,7 @@ int launch_tiled(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, int n
   if (max_words) *max_words = tc.n_cut ? (n_tasks + 31) / 32 : (n_tasks + 32 * TB - 1) / (32 * TB);
   const f16_t *tiled = at<f16_t>(c, c->lo.tiled) + w.elems;
   const float *wdown = at<float>(c, c->lo.wdown) + w.blocks * 32;
-  float *part = at<float>(c, c->lo.mfma_part);
+  float *part = partial_sums(c);
   const int grid = tc.n_whole + tc.n_cut * tc.n_split;
   const size_t lds = tg_lds_bytes(MTILES, TB);
   auto launch = [&](auto kern) {
@@ -747,7 +758,7 @@ int launch_direct_cols(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m,
     }
   }
   kern<<<groups * split, 64 * TD_WAVES, lds, c->stream>>>(epi, at<f16_t>(c, c->lo.tiled) + w.elems, at<float>(c, c->lo.wdown) + w.blocks * 32,
-                                                          rows, m, in, n_in, n_tasks, groups, cps, at<float>(c, c->lo.mfma_part),
+                                                          rows, m, in, n_in, n_tasks, groups, cps, partial_sums(c),
                                                           at<int>(c, c->lo.arrivals));   // (zero between launches, attention's too)
   HIP_TRY(c, hipGetLastError());
   return SPARK_OK;
@@ -802,7 +813,7 @@ int launch_mfma_shape(spark_ctx *c, const Epi &epi, const RowDesc *rows, int m, 
   int split = choose_split(tiles, occ * c->n_cu, n_chunks, tiles < 32 ? 4 : 8, range_bytes(1, n_tasks, m_pad));
   const int cps = (n_chunks + split - 1) / split;
   split = (n_chunks + cps - 1) / cps;
-  float *part = at<float>(c, c->lo.mfma_part);
+  float *part = partial_sums(c);
   // one-dimensional grid: the kernel deals its ids so that the row tiles of a weight tile share an XCD
   const int xcd_groups = z > 1 && split <= c->mfma_xcd_max_split;
   const int tiles_padded = xcd_groups ? (bx * split + 7) / 8 * 8 : bx * split;
@@ -1010,6 +1021,88 @@ int run_layers_mfma(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
 }
 
 // layers [l0, l1) on m rows described by `rows` (device)
+// ------------------------------------------------------------------ a pass of one row in one launch
+
+// Where the words of the hand-overs lie in the area of the partial sums (which the other projections leave floats in)
+struct RowWords { size_t h0, h1, qkv, attn, act, part, end; };
+RowWords row_words(const spark_config &g) {
+  const size_t qw = (size_t)g.n_q_heads * g.head_dim, kvw = (size_t)g.n_kv_heads * g.head_dim, dm = g.d_model;
+  RowWords w;
+  w.h0 = 0;
+  w.h1 = w.h0 + dm;
+  w.qkv = w.h1 + dm;
+  w.attn = w.qkv + qw + 2 * kvw;
+  w.act = w.attn + qw;
+  w.part = w.act + (size_t)ROW_PARTS * ROW_WGS * row_slots(g.d_ffn);
+  w.end = w.part + (size_t)(g.n_q_heads / g.n_kv_heads) * ROW_WGS * (ROW_HD + 2);   // (a workgroup has one slice of a KV head)
+  return w;
+}
+
+OneRow one_row_shape(const spark_config &g) {
+  OneRow a{};
+  a.d = g.d_model; a.nq = g.n_q_heads; a.nkv = g.n_kv_heads; a.F = g.d_ffn; a.eps = g.rms_eps;
+  return a;
+}
+
+// Every workgroup has a pair of every projection, of gate/up one in each piece: that it has written its part of a row
+// then says that it no longer reads what the row was made of.
+bool shape_allows_one_row(const spark_config &g) {
+  const int qw = g.n_q_heads * g.head_dim;
+  OneRow a = one_row_shape(g);
+  return g.dtype == SPARK_DTYPE_BF16 && g.head_dim == ROW_HD && g.n_q_heads / g.n_kv_heads <= ROW_MAX_GROUP && g.n_q_heads <= ROW_WGS &&
+         g.d_model % 8 == 0 && g.d_ffn % 8 == 0 && g.d_model <= ROW_MAX_D && qw <= ROW_MAX_D && g.d_model >= 2 * ROW_WGS &&
+         (g.n_q_heads + 2 * g.n_kv_heads) * (ROW_HD / 2) >= ROW_WGS && g.d_ffn >= ROW_PARTS * ROW_WGS &&
+         one_row_lds(a) > 0 && sizeof(row_word) * row_words(g).end <= MFMA_PARTIAL_BYTES;
+}
+
+// Whether a pass of one row takes the one launch.  Its hand-overs cost a layer some 20 us whatever the layer's size, a
+// cooperative launch some 20 us more than a plain one, and attention has at most one slice of 64 tokens per workgroup.
+// Measured, us a step of eight layers with small heads, a launch per operation / one launch:
+//   4 MB a layer 194 / 325, 23 MB 222 / 328, 90 MB 319 / 355 (1500 tokens: 339 / 381), 198 MB 437 / 423 (1200 tokens: 452 / 446),
+//   293 MB 541 / 505, 354 MB 636 / 579, 408 MB 661 / 624 (8000 tokens: 744 / 711), 466 MB 730 / 684 (3900 tokens: 784 / 724)
+// So a layer wins 2 to 9 us from ROW_LAYER_BYTES on, and runs of ROW_LAYERS and more make up for the launch.
+constexpr size_t ROW_LAYER_BYTES = (size_t)180 << 20;
+constexpr int ROW_LAYERS = 4;
+bool one_row_runs(const spark_ctx *c, int layers) {
+  if (!c->row_ok || !c->use_row || c->prof_class >= 0 || c->attn_splits_now <= 0 || c->cfg.n_kv_heads * c->attn_splits_now > ROW_WGS) return false;
+  return c->use_row == 2 || (c->layer_bytes >= ROW_LAYER_BYTES && layers >= ROW_LAYERS);
+}
+
+__global__ void __launch_bounds__(256) clear_words_k(row_word *words, size_t n) {
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) words[i] = 0ull;
+}
+
+// false: the device has no room for all workgroups of such a launch at once
+bool enqueue_one_row(spark_ctx *c, int l0, int l1, const RowDesc *row) {
+  const spark_config &g = c->cfg;
+  OneRow a = one_row_shape(g);
+  const size_t lds = one_row_lds(a);
+  const RowWords w = row_words(g);
+  row_word *words = at<row_word>(c, c->lo.mfma_part);
+  const unsigned layers = (unsigned)(l1 - l0);
+  if (!c->row_words_clean || c->row_tag + layers < c->row_tag) {   // (or the numbers start again)
+    clear_words_k<<<256, 256, 0, c->stream>>>(words, w.end);
+    c->row_words_clean = true;
+    c->row_tag = 0;
+  }
+  a.l0 = l0; a.l1 = l1;
+  a.scale = 1.0f / sqrtf((float)ROW_HD);
+  a.wq = (const bf16_t *)c->w.wq; a.wk = (const bf16_t *)c->w.wk; a.wv = (const bf16_t *)c->w.wv; a.wo = (const bf16_t *)c->w.wo;
+  a.wg = (const bf16_t *)c->w.wg; a.wu = (const bf16_t *)c->w.wu; a.wd = (const bf16_t *)c->w.wd;
+  a.attn_norm = c->w.attn_norm; a.mlp_norm = c->w.mlp_norm;
+  a.rope = at<float2>(c, c->lo.rope);
+  a.kv = kv_view(c);
+  a.row = row;
+  a.hidden = c->pb.hidden;
+  a.h0 = words + w.h0; a.h1 = words + w.h1; a.qkv = words + w.qkv; a.attn = words + w.attn; a.act = words + w.act; a.part = words + w.part;
+  a.tag = c->row_tag + 1;
+  c->row_tag += layers;
+  a.error = at<int>(c, c->lo.plan) + PL_ERR;
+  if (launch_one_row(a, lds, c->stream) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
 template <typename WT>
 int run_layers(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
   const spark_config &g = c->cfg;
@@ -1027,6 +1120,7 @@ int run_layers(spark_ctx *c, int l0, int l1, const RowDesc *rows, int m) {
   }
   const int d = g.d_model, hd = g.head_dim, nq = g.n_q_heads, nkv = g.n_kv_heads, F = g.d_ffn;
   const size_t qw = (size_t)nq * hd, kvw = (size_t)nkv * hd;
+  if (std::is_same<WT, bf16_t>::value && m == 1 && one_row_runs(c, l1 - l0) && enqueue_one_row(c, l0, l1, rows)) return SPARK_OK;
   float *hidden = c->pb.hidden;
   int rc;
   for (int l = l0; l < l1; ++l) {
@@ -1159,10 +1253,12 @@ int enqueue_step(spark_ctx *c, int n, int n_upper, int n_ee, int n_full, const i
     embed_rows_k<WT><<<n, 256, 0, c->stream>>>(lower, io.state, nullptr, (const WT *)c->w.embed, g.d_model, c->pb.hidden);
   }
   HIP_TRY(c, hipGetLastError());
-  if ((rc = run_layers<WT>(c, 0, g.exit_layer, lower, n))) return rc;
+  // a single row that runs full depth and completes no other is the same row above the exit layer: one run of layers
+  const int first_run = n == 1 && n_upper == 1 ? g.n_layers : g.exit_layer;
+  if ((rc = run_layers<WT>(c, 0, first_run, lower, n))) return rc;
   if (n_ee && (rc = run_lens_head<WT>(c, ee, n_ee))) return rc;
   if (n_full) {
-    if ((rc = run_layers<WT>(c, g.exit_layer, g.n_layers, upper, n_upper))) return rc;
+    if ((rc = run_layers<WT>(c, first_run, g.n_layers, upper, n_upper))) return rc;
     if ((rc = run_final_head<WT>(c, full, n_full))) return rc;
   }
   if (rand_dev && c->temperature > 0.f) {   // the drawn token takes the arg-max's place
@@ -1536,10 +1632,12 @@ int init_context(const spark_config *cfg, const spark_weights *weights, void *kv
   c->mfma_ok = cfg->d_model % 8 == 0 && (cfg->n_q_heads * cfg->head_dim) % 8 == 0 && cfg->d_ffn % 8 == 0;
   c->use_mfma = c->mfma_ok;
   int cooperative = 0;
-  c->small_ok = shape_allows_small(*cfg, c->dv, c->lo) &&
-                hipDeviceGetAttribute(&cooperative, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && cooperative &&
+  if (hipDeviceGetAttribute(&cooperative, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess) cooperative = 0;
+  c->small_ok = shape_allows_small(*cfg, c->dv, c->lo) && cooperative &&
                 prop.multiProcessorCount >= SMALL_WGS && small_steps_fit(cfg->head_dim);
   c->small_layer_bytes = layer_bytes_fp32(*cfg);
+  c->layer_bytes = layer_bytes_fp32(*cfg) / 2;
+  c->row_ok = shape_allows_one_row(*cfg) && cooperative && prop.multiProcessorCount >= ROW_WGS && one_row_fit();
   // a scratch area of the full size holds the MFMA-ordered copy of the projection weights (the
   // static area never does)
   tiled_map(*cfg, c->dv, c->tm);
@@ -1675,6 +1773,7 @@ int spark_tune(spark_ctx *c, const char *name, int32_t value) {
   else if (k == "direct_max_rows") c->direct_max_rows = value;
   else if (k == "direct_whole_k") c->direct_whole_k = value;
   else if (k == "small_steps") c->use_small = value != 0;
+  else if (k == "one_row") c->use_row = std::max(0, std::min(2, (int)value));
   else if (k == "fuse_norm") c->fuse_norm = value != 0;
   else return fail(c, SPARK_EINVAL, "unknown tuning name '%s'", name);
   return SPARK_OK;

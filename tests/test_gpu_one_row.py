@@ -1,0 +1,87 @@
+"""The layers of a pass of one row in one launch (one_row.h): the shapes and contexts at which its phases can go wrong,
+against the oracle, and against the same steps as a launch per operation."""
+from contextlib import closing
+
+import numpy as np
+import pytest
+
+import workloads as wl
+from parity_util import compare_run, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sb():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_09215_amd import binding
+    binding.load_library()
+    return binding
+
+
+def _shape(name, **over):
+    return wl.TINY.shape.replace(name=name, dtype=wl.DTYPE_BF16, n_layers=4, head_dim=128, **over)
+
+
+# the narrowest model (a pair of every projection for each of the 256 workgroups) and one query head per key head; widths
+# that are no multiple of a unit's 512 elements nor of the workgroups, seven query heads; 16 query heads; rows of two widths
+SHAPES = [
+    ("narrow", dict(d_model=512, n_q_heads=2, n_kv_heads=2, d_ffn=768), 16),
+    ("ragged", dict(d_model=776, n_q_heads=7, n_kv_heads=1, d_ffn=1400), 16),
+    ("sixteen", dict(d_model=1024, n_q_heads=16, n_kv_heads=1, d_ffn=776), 64),
+    ("wide", dict(d_model=520, n_q_heads=16, n_kv_heads=4, d_ffn=2056), 48),
+]
+
+
+# prompts of 1, 31 .. 33 and 62 tokens: a context of the step's own token alone, slices that fill up during the run
+@pytest.mark.parametrize("name,over,page", SHAPES, ids=[s[0] for s in SHAPES])
+def test_shapes(sb, name, over, page):
+    w = wl.TINY
+    shape = _shape(name, **over)
+    weights = wl.make_weights(shape, seed=4)
+    for n in (1, 31, 62):
+        say(f"one row, {name}, {n}")
+        with closing(sb.Spark(shape, w.schedule, weights, max_batch=1, max_seq_len=192, kv_page_tokens=page)) as sp:
+            sp.tune("one_row", 2)
+            compare_run(sp, shape, w.schedule, weights, [wl.make_prompt(shape, n, seed=60)], [n % 6], 14, chunk=5, check_kv_every=7,
+                        label=f"one row {name} {n}")
+
+
+def _decode(sb, shape, sched, weights, prompt, steps, on, between):
+    """forced steps of one sequence; after a few of them `between` other sequences take steps (wide passes, which leave
+    other things in the area of the hand-overs)"""
+    with closing(sb.Spark(shape, sched, weights, max_batch=12, max_seq_len=2176, kv_page_tokens=64)) as sp:
+        sp.tune("one_row", on)
+        sid = sp.seq_open(0)
+        sp.prefill(sid, prompt)
+        forced = np.arange(steps, dtype=np.int32)[:, None] % shape.vocab
+        logits = []
+        for at in range(0, steps, 5):
+            sp.decode(min(5, steps - at), [sid], forced[at:at + 5])
+            logits.append(sp.get_logits(sid)[0])
+            if between:
+                ids = [sp.seq_open(b) for b in range(between)]
+                for b, s in enumerate(ids):
+                    sp.prefill(s, wl.make_prompt(shape, 20 + b, seed=b))
+                sp.decode(3, ids)
+                for s in ids:
+                    sp.seq_close(s)
+        kv = np.concatenate(sp.get_kv(sid, 0, len(prompt) + steps - 2))
+    return np.stack(logits).astype(np.float64), kv
+
+
+# eight key heads: up to 1024 positions the slices have 32 tokens, up to 2048 64, and beyond that the steps are launches per
+# operation; the second row of each pair crosses the line during the run
+@pytest.mark.parametrize("n,between", [(1000, 0), (1020, 0), (2030, 0), (2045, 0), (90, 11)])
+def test_contexts_and_other_passes(sb, n, between):
+    shape = _shape("contexts", d_model=1024, n_q_heads=16, n_kv_heads=8, d_ffn=1536)
+    weights = wl.make_weights(shape, seed=4)
+    prompt = wl.make_prompt(shape, n, seed=61)
+    a, ka = _decode(sb, shape, wl.TINY.schedule, weights, prompt, 15, 0, between)
+    b, kb = _decode(sb, shape, wl.TINY.schedule, weights, prompt, 15, 2, between)
+    # another order of the 32-bit sums; a cache entry may round to the neighbouring 16-bit value (2^-8 of it), which
+    # moves the outputs of the layers above by far less than that
+    assert np.linalg.norm(a - b) <= 2.0 ** -8 * np.linalg.norm(a)
+    assert np.all(np.abs(ka - kb) <= 2.0 ** -7 * np.abs(ka) + 1e-3 * np.abs(ka).max())
