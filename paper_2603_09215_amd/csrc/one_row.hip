@@ -156,16 +156,24 @@ struct Walk {
   }
 };
 
-// The slice of the context that a workgroup attends to
-struct Slice { int head, index, count, size, first; bool mine; };
+// The slice of the context that a workgroup attends to, for `heads` query heads from `head` on, all of KV head `kv`.
+// While there are workgroups enough slices are short, and the query heads of a KV head are dealt to several.
+struct Slice { int kv, head, heads, index, count, size, first; bool mine; };
 __device__ __forceinline__ Slice slice_of(const OneRow &a, int pos, int wg) {
   Slice s;
-  s.size = ROW_SLICE / 2;   // short ones while there are workgroups enough
+  s.size = ROW_SLICE / 2;
   if (a.nkv * (pos / s.size + 1) > ROW_WGS) s.size = ROW_SLICE;
   s.count = pos / s.size + 1;
-  s.mine = wg < a.nkv * s.count;
-  s.head = s.mine ? wg / s.count : 0;
-  s.index = s.mine ? wg - s.head * s.count : 0;
+  const int group = a.nq / a.nkv;
+  int deal = 0;   // workgroups per KV head and slice, as a power of two
+  while (deal < 2 && (2 << deal) <= group && a.nkv * s.count * (2 << deal) <= ROW_WGS) ++deal;
+  const int most = (group + (1 << deal) - 1) >> deal, id = wg / s.count;
+  s.mine = id < a.nkv << deal;
+  s.kv = s.mine ? id >> deal : 0;
+  const int g0 = s.mine ? (id & ((1 << deal) - 1)) * most : 0;
+  s.head = s.kv * group + g0;
+  s.heads = min(most, group - g0);
+  s.index = s.mine ? wg - id * s.count : 0;
   s.first = s.index * s.size;
   return s;
 }
@@ -444,8 +452,8 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
       for (int e = 0; e < 2; ++e) {
         const int at_tok = sl.first + e * (ROW_SLICE / 2) + (t >> 4);
         const int p = sl.mine && at_tok < rd.pos ? at_tok : 0;   // (the others' are not used)
-        kr[e] = *(const uint4 *)((const bf16_t *)a.kv.pool + kv_elem_offset(a.kv, rd.seq, p, layer, 0, sl.head) + (t & 15) * 8);
-        vr[e] = *(const uint4 *)((const bf16_t *)a.kv.pool + kv_elem_offset(a.kv, rd.seq, p, layer, 1, sl.head) + (t & 15) * 8);
+        kr[e] = *(const uint4 *)((const bf16_t *)a.kv.pool + kv_elem_offset(a.kv, rd.seq, p, layer, 0, sl.kv) + (t & 15) * 8);
+        vr[e] = *(const uint4 *)((const bf16_t *)a.kv.pool + kv_elem_offset(a.kv, rd.seq, p, layer, 1, sl.kv) + (t & 15) * 8);
       }
     }
     {
@@ -489,18 +497,18 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
       const OneRow &a = fresh_args();
       const int t = fresh_aux();
       const unsigned tag = a.tag + (unsigned)(layer - l0);
-      const int group = a.nq / a.nkv, pos = a.row->pos;
+      const int pos = a.row->pos;
       const Slice sl = slice_of(a, pos, wg);
       const int ch = t & 15;
       const bool mine = sl.mine;
       float *qs = (float *)(lds + a.lds_act), *sc = qs + ROW_MAX_GROUP * ROW_HD, *vs = sc + ROW_MAX_GROUP * ROW_SLICE;
       float *kn = vs + ROW_SLICE * ROW_HD;   // the new token's key
       if (mine) {
-        const int n = group * ROW_HD;
+        const int n = sl.heads * ROW_HD;
         const bool last = pos < sl.first + sl.size;   // the slice has the new token: its key and value are words as well
         float q[5];
-        const unsigned new_at = last ? (unsigned)((a.nq + (t & ROW_HD ? a.nkv : 0) + sl.head) * ROW_HD + (t & (ROW_HD - 1))) : (unsigned)(sl.head * n);
-        take_words<5>(broken, a.qkv, tag, [&](int i) { return i < 4 ? (unsigned)(sl.head * n + min(i * ROW_AUX + t, n - 1)) : new_at; }, q);
+        const unsigned new_at = last ? (unsigned)((a.nq + (t & ROW_HD ? a.nkv : 0) + sl.kv) * ROW_HD + (t & (ROW_HD - 1))) : (unsigned)(sl.head * ROW_HD);
+        take_words<5>(broken, a.qkv, tag, [&](int i) { return i < 4 ? (unsigned)(sl.head * ROW_HD + min(i * ROW_AUX + t, n - 1)) : new_at; }, q);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           if (i * ROW_AUX + t < n) qs[i * ROW_AUX + t] = q[i] * a.scale;
@@ -529,11 +537,11 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
               kf[e][i] = v.x; kf[e][i + 1] = v.y; kf[e][i + 2] = v.z; kf[e][i + 3] = v.w;
             }
         }
-        for (int g0 = 0; g0 < group; g0 += 4) {
+        for (int g0 = 0; g0 < sl.heads; g0 += 4) {
           float s[4][2];
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            const float *q = qs + min(g0 + j, group - 1) * ROW_HD + ch * 8;
+            const float *q = qs + min(g0 + j, sl.heads - 1) * ROW_HD + ch * 8;
             s[j][0] = s[j][1] = 0.f;
 #pragma unroll
             for (int i = 0; i < 8; i += 4) {
@@ -549,7 +557,7 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
           if (ch == 0)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              if (g0 + j < group)
+              if (g0 + j < sl.heads)
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
                   const int tok = e * (ROW_SLICE / 2) + (t >> 4);
@@ -563,17 +571,16 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
       const OneRow &a = fresh_args();
       const int t = fresh_aux();
       const unsigned tag = a.tag + (unsigned)(layer - l0);
-      const int group = a.nq / a.nkv;
       const Slice sl = slice_of(a, a.row->pos, wg);
       const int dim = t & (ROW_HD - 1), quarter = __builtin_amdgcn_readfirstlane(t >> 7);
       float *sc = (float *)(lds + a.lds_act) + ROW_MAX_GROUP * ROW_HD, *vs = sc + ROW_MAX_GROUP * ROW_SLICE, *red = vs + ROW_SLICE * ROW_HD;
       if (sl.mine) {   // a quarter of the threads (two waves) takes every fourth head; thread: one dimension
-        row_word *to = a.part + ((size_t)sl.head * group * sl.count + sl.index) * (ROW_HD + 2);
+        row_word *to = a.part + ((size_t)sl.head * sl.count + sl.index) * (ROW_HD + 2);
         auto weigh = [&](auto heads) {
           constexpr int HEADS = decltype(heads)::value;
           float p[HEADS], o[HEADS], m[HEADS], l[HEADS];
 #pragma unroll
-          for (int j = 0; j < HEADS; ++j) p[j] = sc[min(quarter + 4 * j, group - 1) * ROW_SLICE + lane];
+          for (int j = 0; j < HEADS; ++j) p[j] = sc[min(quarter + 4 * j, sl.heads - 1) * ROW_SLICE + lane];
 #pragma unroll
           for (int j = 0; j < HEADS; ++j) m[j] = wave_largest(p[j]);
 #pragma unroll
@@ -595,30 +602,34 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
 #pragma unroll
           for (int j = 0; j < HEADS; ++j) {
             const int g = quarter + 4 * j;
-            if (g < group) {
+            if (g < sl.heads) {
               row_word *w = to + g * sl.count * (ROW_HD + 2);
               put_word(w + dim, o[j], tag);
               if (dim < 2) put_word(w + ROW_HD + dim, dim ? l[j] : m[j], tag);
             }
           }
         };
-        if (group <= 8) weigh(std::integral_constant<int, 2>());
+        if (sl.heads <= 4) weigh(std::integral_constant<int, 1>());
+        else if (sl.heads <= 8) weigh(std::integral_constant<int, 2>());
         else weigh(std::integral_constant<int, ROW_MAX_GROUP / 4>());
       }
-      // the slices of a head meet at one of the last workgroups
-      const int head = ROW_WGS - 1 - wg;
+      // the slices of a head meet at some of the last workgroups, a part of its dimensions at each
+      const int deal = a.nq * 2 <= ROW_WGS, id = ROW_WGS - 1 - wg, head = id >> deal, width = ROW_HD >> deal, groups = ROW_AUX / width;
+      const int d0 = (id & ((1 << deal) - 1)) * width + (t & (width - 1));
       if (head < a.nq) {
         float M = -INFINITY, L = 0.f, O = 0.f;
         const row_word *p = a.part + (size_t)head * sl.count * (ROW_HD + 2);
-        for (int s0 = quarter; s0 < sl.count; s0 += 32) {
-          float v[24];
-          take_words<24>(broken, p, tag, [&](int i) {
-            const int s = min(s0 + 4 * (i / 3), sl.count - 1), e = i % 3;
-            return (unsigned)(s * (ROW_HD + 2) + (e == 0 ? dim : ROW_HD - 1 + e));
+        constexpr int N = 6;   // slices that a thread asks for at a time
+        for (int b = 0; b < sl.count; b += N * groups) {
+          const int s0 = b + t / width;
+          float v[3 * N];
+          take_words<3 * N>(broken, p, tag, [&](int i) {
+            const int s = min(s0 + groups * (i / 3), sl.count - 1), e = i % 3;
+            return (unsigned)(s * (ROW_HD + 2) + (e == 0 ? d0 : ROW_HD - 1 + e));
           }, v);
 #pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            if (s0 + 4 * i < sl.count) {
+          for (int i = 0; i < N; ++i) {
+            if (s0 + groups * i < sl.count) {
               const float Mn = fmaxf(M, v[3 * i + 1]);
               const float f0 = expf(M - Mn), f1 = expf(v[3 * i + 1] - Mn);
               O = O * f0 + v[3 * i] * f1;
@@ -627,22 +638,22 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
             }
           }
         }
-        red[quarter * ROW_HD + dim] = O;
-        red[(4 + quarter) * ROW_HD + dim] = M;
-        red[(8 + quarter) * ROW_HD + dim] = L;
+        red[t] = O;
+        red[ROW_AUX + t] = M;
+        red[2 * ROW_AUX + t] = L;
       }
       aux_barrier_();
-      if (head < a.nq && quarter == 0) {
+      if (head < a.nq && t < width) {
         float M = -INFINITY, L = 0.f, O = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) M = fmaxf(M, red[(4 + i) * ROW_HD + dim]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float f = expf(red[(4 + i) * ROW_HD + dim] - M);
-          O += red[i * ROW_HD + dim] * f;
-          L += red[(8 + i) * ROW_HD + dim] * f;
+#pragma unroll 4
+        for (int i = 0; i < groups; ++i) M = fmaxf(M, red[ROW_AUX + i * width + t]);
+#pragma unroll 4
+        for (int i = 0; i < groups; ++i) {
+          const float f = expf(red[ROW_AUX + i * width + t] - M);
+          O += red[i * width + t] * f;
+          L += red[2 * ROW_AUX + i * width + t] * f;
         }
-        put_word(a.attn + head * ROW_HD + dim, O * (1.0f / L), tag);
+        put_word(a.attn + head * ROW_HD + d0, O * (1.0f / L), tag);
       }
     }
     // ---- o
