@@ -33,7 +33,8 @@ constexpr int ROW_HD = 128;             // head_dim
 constexpr int ROW_MAX_GROUP = 16;       // query heads per KV head
 constexpr int ROW_SLICE = 64;           // tokens of an attention slice, at most
 constexpr int ROW_MAX_D = 8 * ROW_AUX;  // width of a row that is gathered at once
-constexpr int ROW_MAX_POLLS = 1 << 18;
+// Some seconds; then the launch gives up.  Other streams' kernels may hold compute units that its last workgroups wait for.
+constexpr int ROW_MAX_POLLS = 1 << 22;
 
 typedef unsigned long long row_word;
 

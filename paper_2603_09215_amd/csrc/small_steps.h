@@ -30,7 +30,7 @@ constexpr int SMALL_MAX_CHUNKS = 16;             // ... and pieces of a row: inp
 constexpr int SMALL_X_FLOATS = 16384, SMALL_PART_FLOATS = 4096;   // LDS: staged rows, sums of the pieces
 constexpr int SMALL_NORM_CHUNKS = 4;             // pieces of a normalised row, at most
 constexpr size_t SMALL_LDS = sizeof(float) * (SMALL_X_FLOATS + SMALL_PART_FLOATS + SMALL_ROWS * SMALL_NORM_CHUNKS);
-constexpr int SMALL_MAX_POLLS = 1 << 18;         // some tenths of a second; then the launch gives up
+constexpr int SMALL_MAX_POLLS = 1 << 22;         // some seconds; then the launch gives up (other streams' kernels may hold its last workgroups up)
 static_assert(SMALL_SEQS <= SMALL_WGS && SMALL_SEQS <= SMALL_WAVES, "a workgroup draws for one sequence, a wave reads one's arg-max");
 
 // A projection phase: `n_tasks` pairs of weight rows of n_in

@@ -85,3 +85,33 @@ def test_contexts_and_other_passes(sb, n, between):
     # moves the outputs of the layers above by far less than that
     assert np.linalg.norm(a - b) <= 2.0 ** -8 * np.linalg.norm(a)
     assert np.all(np.abs(ka - kb) <= 2.0 ** -7 * np.abs(ka) + 1e-3 * np.abs(ka).max())
+
+
+def test_two_contexts_on_two_threads(sb):
+    """launches of which each has the whole chip, on two streams at once: each thread's results are those it gets alone"""
+    import threading
+
+    import torch
+    shape = _shape("threads", d_model=1024, n_q_heads=16, n_kv_heads=8, d_ffn=1536)
+    weights = wl.make_weights(shape, seed=4)
+    say("one row on two threads")
+
+    def go(stream):
+        with closing(sb.Spark(shape, wl.TINY.schedule, weights, max_batch=1, max_seq_len=192, kv_page_tokens=64, stream=stream)) as sp:
+            sp.tune("one_row", 2)
+            sid = sp.seq_open(0)
+            sp.prefill(sid, wl.make_prompt(shape, 50, seed=62))
+            return np.concatenate([sp.decode(10, [sid])[0] for _ in range(4)]), sp.get_logits(sid)[0]
+
+    alone, out = go(None), [None, None]
+
+    def thread(i):
+        out[i] = go(torch.cuda.Stream())
+
+    threads = [threading.Thread(target=thread, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    for o in out:
+        assert o is not None and all(np.array_equal(x, y) for x, y in zip(o, alone))
