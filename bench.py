@@ -251,6 +251,8 @@ def main() -> int:
                         "GBps": round(by / med / 1e6, 1), "frac_of_hbm_peak": round(by / med / 1e6 / HBM_PEAK_GBS, 4)}
 
     # ---- roofline of the dominant kernel: gate/up projection, HIP events on the library's stream
+    # (steps whose launches are bracketed run a launch per operation; the timed steps above run one row's layers in one launch,
+    # whose bandwidth is that of whole_step and step_classes)
     esz = 2 if shape.dtype == wl.DTYPE_BF16 else 4
     gateup_bytes = 2 * shape.d_ffn * shape.d_model * esz
     sp.profile_select("gateup")

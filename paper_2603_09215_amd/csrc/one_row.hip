@@ -1,8 +1,8 @@
 // The kernel of one_row.h, a translation unit of its own.
 //
-// What bounds it: the hand-overs.  A layer of the Step shape takes 84 us (a launch per operation: 101), 68 of them the
-// bytes at the rate of a plain read.  Of the rest a hand-over costs 2 to 4 us from the last workgroup's sums to the next
-// phase's first product, attention's three together 11, of which the units fetched meanwhile (up to ten a wave,
+// What bounds it: the hand-overs.  A layer of the Step shape takes 86 us (20 layers 1 715, 28 layers 2 418, by
+// rocprofv3; a launch per operation: 101), 68 of them the bytes at the rate of a plain read.  Of the rest a hand-over costs 2 to 4 us from the last workgroup's sums to the next
+// phase's first product, attention's three together 8, of which the units fetched meanwhile (up to ten a wave,
 // 40 MB in all) win back the larger part; and the workgroups reach the end of a phase up to 5 us apart.
 #include "one_row.h"
 
