@@ -215,7 +215,11 @@ int spark_step(spark_ctx *ctx, int32_t n, const int32_t *seq_ids, const int32_t 
 
 /* n_steps consecutive steps of the same n sequences without returning to the host in between:
  * the emitted id (or forced_next[s*n + i] when given and >= 0) feeds the next step on the device.
- * out_tokens / out_depth [host] are [n_steps][n].  Same results as n_steps calls of spark_step. */
+ * out_tokens / out_depth [host] are [n_steps][n].  Same results as n_steps calls of spark_step.
+ * Some steps are one launch whose workgroups wait for each other (spark_tune, "small_steps" and "one_row") and need
+ * room on the device together.  Should they not get it for some seconds, because another process or stream keeps
+ * compute units, such a launch gives up: the call then runs again from its start as launches per operation, returns
+ * what those give, spark_last_error says so, and the context keeps to them until spark_tune asks for the others. */
 int spark_decode(spark_ctx *ctx, int32_t n_steps, int32_t n, const int32_t *seq_ids,
                  const int32_t *forced_next, int32_t *out_tokens, int32_t *out_depth);
 
@@ -314,7 +318,9 @@ int spark_measure_read(spark_ctx *ctx, const void *buf, size_t bytes, int32_t re
  *   length of the prompt, as in a new context), "small_steps" (0: the steps of small fp32 models are
  *   launches per operation; otherwise all steps of a call are one cooperative launch where that is faster),
  *   "one_row" (0: the layers of a pass of one row are launches per operation; 1: they are one cooperative
- *   launch where that is faster, as in a new context; 2: wherever the shape allows it).
+ *   launch where that is faster, as in a new context; 2: wherever the shape allows it), "wait_polls" (how often
+ *   a workgroup of such a launch asks for what another one hands over before it gives up; negative: and as often whether
+ *   the others have started; 0: for some seconds, as in a new context).
  * SPARK_EINVAL for an unknown name. */
 int spark_tune(spark_ctx *ctx, const char *name, int32_t value);
 

@@ -33,7 +33,8 @@ constexpr int ROW_HD = 128;             // head_dim
 constexpr int ROW_MAX_GROUP = 16;       // query heads per KV head
 constexpr int ROW_SLICE = 64;           // tokens of an attention slice, at most
 constexpr int ROW_MAX_D = 8 * ROW_AUX;  // width of a row that is gathered at once
-// Some seconds; then the launch gives up.  Other streams' kernels may hold compute units that its last workgroups wait for.
+// Some seconds; then the launch gives up and the call goes on as launches per operation.  Other streams' and processes'
+// kernels may hold compute units that its last workgroups wait for.
 constexpr int ROW_MAX_POLLS = 1 << 22;
 
 typedef unsigned long long row_word;
@@ -50,6 +51,7 @@ struct OneRow {
   row_word *h0, *h1, *qkv, *attn, *act, *part;   // [d], [d], [(nq + 2 nkv) * 128], [nq * 128], [ROW_PARTS][ROW_WGS][pairs of a piece], [nq][slices][ROW_HD + 2]
   unsigned tag;      // of layer l0; the next layers' follow
   int *error;        // ERR_STALLED is set here when a wait runs out
+  int max_polls;     // questions of a wait before it runs out
   int pairs;         // of a phase and workgroup, at most
   // LDS, in bytes
   int lds_x, lds_act, lds_part, lds_misc;

@@ -69,10 +69,15 @@ __device__ __forceinline__ void put_word(row_word *p, float v, unsigned tag) {
 }
 __device__ __forceinline__ row_word peek_word(const row_word *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// N words, the i-th at at(i); all lanes of the wave together.  `broken`: some wait of this wave has run out of polls: then
-// it asks for nothing any more, and what it hands on it hands on, so that the others need not run out as well.
+// Whether some wait of this wave has run out of polls: then it asks for nothing any more, and what it hands on it hands
+// on, so that the others need not run out as well.  Nothing is read or written where it would not be otherwise.
+struct Patience {
+  bool broken;
+  int max_polls;
+};
+// N words, the i-th at at(i); all lanes of the wave together
 template <int N, typename At>
-__device__ __forceinline__ void take_words(bool &broken, const row_word *p, unsigned tag, const At &at, float (&v)[N]) {
+__device__ __forceinline__ void take_words(Patience &wait, const row_word *p, unsigned tag, const At &at, float (&v)[N]) {
   row_word w[N];
   unsigned todo = (1u << N) - 1u;   // what has come for the whole wave is not asked for again
 #pragma unroll
@@ -84,8 +89,8 @@ __device__ __forceinline__ void take_words(bool &broken, const row_word *p, unsi
 #pragma unroll
     for (int i = 0; i < N; ++i)
       if (__all((int)((unsigned)(w[i] >> 32) == tag))) todo &= ~(1u << i);
-    if (todo == 0u || broken) break;
-    if (polls == ROW_MAX_POLLS) broken = true;
+    if (todo == 0u || wait.broken) break;
+    if (polls == wait.max_polls) wait.broken = true;
     __builtin_amdgcn_s_sleep(1);
   }
 #pragma unroll
@@ -226,17 +231,17 @@ __device__ __forceinline__ void put_row(const OneRow &a, char *lds, int t, const
     if ((t & 63) == 63) ((float *)(lds + a.lds_misc))[t >> 6] = ss;
   }
 }
-__device__ __forceinline__ void gather_row(const OneRow &a, char *lds, int t, bool &broken, const row_word *words, int n, const float *gamma, unsigned tag, bool wait_words = false) {
+__device__ __forceinline__ void gather_row(const OneRow &a, char *lds, int t, Patience &wait, const row_word *words, int n, const float *gamma, unsigned tag, bool wait_words = false) {
   float g[8], v[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) g[i] = gamma ? gamma[min(i * ROW_AUX + t, n - 1)] : 1.f;
   if (wait_words) {   // for a while yet nothing will have come: one word of eight is asked for
     float first[1];
-    take_words<1>(broken, words, tag, [&](int) { return (unsigned)min((t >> 6) * ROW_AUX + t, n - 1); }, first);
+    take_words<1>(wait, words, tag, [&](int) { return (unsigned)min((t >> 6) * ROW_AUX + t, n - 1); }, first);
   } else {
     __builtin_amdgcn_s_sleep(ROW_NAP);
   }
-  take_words<8>(broken, words, tag, [&](int i) { return (unsigned)min(i * ROW_AUX + t, n - 1); }, v);
+  take_words<8>(wait, words, tag, [&](int i) { return (unsigned)min(i * ROW_AUX + t, n - 1); }, v);
   put_row(a, lds, t, v, g, n, gamma != nullptr);
 }
 
@@ -408,7 +413,7 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
   }
 
   // -------------------------------------------------------------- the other waves
-  bool broken = false;
+  Patience wait{false, fresh_args().max_polls};
   int set = 0;
   float2 h = make_float2(0.f, 0.f);   // the thread's pair of the hidden state
   unsigned arrived = 0;
@@ -437,7 +442,7 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
       put_row(a, lds, t, v, g, a.d, true);
     } else {
       const OneRow &a = fresh_args();
-      gather_row(a, lds, fresh_aux(), broken, a.h1, a.d, a.attn_norm + (size_t)layer * a.d, a.tag + (unsigned)(layer - l0) - 1u);
+      gather_row(a, lds, fresh_aux(), wait, a.h1, a.d, a.attn_norm + (size_t)layer * a.d, a.tag + (unsigned)(layer - l0) - 1u);
     }
     barrier();
     // the slice of attention that this workgroup has: its old keys and values, and what the epilogue needs, are fetched
@@ -508,7 +513,7 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
         const bool last = pos < sl.first + sl.size;   // the slice has the new token: its key and value are words as well
         float q[5];
         const unsigned new_at = last ? (unsigned)((a.nq + (t & ROW_HD ? a.nkv : 0) + sl.kv) * ROW_HD + (t & (ROW_HD - 1))) : (unsigned)(sl.head * ROW_HD);
-        take_words<5>(broken, a.qkv, tag, [&](int i) { return i < 4 ? (unsigned)(sl.head * ROW_HD + min(i * ROW_AUX + t, n - 1)) : new_at; }, q);
+        take_words<5>(wait, a.qkv, tag, [&](int i) { return i < 4 ? (unsigned)(sl.head * ROW_HD + min(i * ROW_AUX + t, n - 1)) : new_at; }, q);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           if (i * ROW_AUX + t < n) qs[i * ROW_AUX + t] = q[i] * a.scale;
@@ -623,7 +628,7 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
         for (int b = 0; b < sl.count; b += N * groups) {
           const int s0 = b + t / width;
           float v[3 * N];
-          take_words<3 * N>(broken, p, tag, [&](int i) {
+          take_words<3 * N>(wait, p, tag, [&](int i) {
             const int s = min(s0 + groups * (i / 3), sl.count - 1), e = i % 3;
             return (unsigned)(s * (ROW_HD + 2) + (e == 0 ? d0 : ROW_HD - 1 + e));
           }, v);
@@ -659,7 +664,7 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
     // ---- o
     {
       const OneRow &a = fresh_args();
-      gather_row(a, lds, fresh_aux(), broken, a.attn, a.nq * ROW_HD, nullptr, a.tag + (unsigned)(layer - l0), true);
+      gather_row(a, lds, fresh_aux(), wait, a.attn, a.nq * ROW_HD, nullptr, a.tag + (unsigned)(layer - l0), true);
     }
     barrier();
     {
@@ -681,7 +686,7 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
     {
       const OneRow &a = fresh_args();
       const int t = fresh_aux();
-      gather_row(a, lds, t, broken, a.h0, a.d, a.mlp_norm + (size_t)layer * a.d, a.tag + (unsigned)(layer - l0));
+      gather_row(a, lds, t, wait, a.h0, a.d, a.mlp_norm + (size_t)layer * a.d, a.tag + (unsigned)(layer - l0));
       float *act = (float *)(lds + a.lds_act);
       for (int k = a.F + t; k < ((a.F + 511) & ~511); k += ROW_AUX) act[x_pos(k)] = 0.f;   // (meets weights)
     }
@@ -715,7 +720,7 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
           from[i] = (b * ROW_WGS + w) * slots + j;
           at[i] = x_pos(o.first + j);
         }
-        take_words<N>(broken, a.act, tag, [&](int i) { return (unsigned)from[i]; }, v);
+        take_words<N>(wait, a.act, tag, [&](int i) { return (unsigned)from[i]; }, v);
 #pragma unroll
         for (int i = 0; i < N; ++i) act[at[i]] = v[i];
       }
@@ -742,7 +747,7 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
       set ^= 1;
     }
   }
-  if (broken && lane == 0) atomicOr(fresh_args().error, ERR_STALLED);
+  if (wait.broken && lane == 0) atomicOr(fresh_args().error, ERR_STALLED);
 }
 
 size_t one_row_lds(OneRow &a) {

@@ -30,7 +30,8 @@ constexpr int SMALL_MAX_CHUNKS = 16;             // ... and pieces of a row: inp
 constexpr int SMALL_X_FLOATS = 16384, SMALL_PART_FLOATS = 4096;   // LDS: staged rows, sums of the pieces
 constexpr int SMALL_NORM_CHUNKS = 4;             // pieces of a normalised row, at most
 constexpr size_t SMALL_LDS = sizeof(float) * (SMALL_X_FLOATS + SMALL_PART_FLOATS + SMALL_ROWS * SMALL_NORM_CHUNKS);
-constexpr int SMALL_MAX_POLLS = 1 << 22;         // some seconds; then the launch gives up (other streams' kernels may hold its last workgroups up)
+constexpr int SMALL_MAX_POLLS = 1 << 22;         // some seconds; then the launch gives up (other streams' and processes' kernels may
+                                                 // hold its last workgroups up) and the call runs again as launches per operation
 static_assert(SMALL_SEQS <= SMALL_WGS && SMALL_SEQS <= SMALL_WAVES, "a workgroup draws for one sequence, a wave reads one's arg-max");
 
 // A projection phase: `n_tasks` pairs of weight rows of n_in
@@ -79,6 +80,9 @@ struct SmallSteps {
   int n, steps;
   double temperature, top_p;
   unsigned epoch;            // number of the launch
+  int max_polls, first_polls;   // questions of a wait before it runs out; of the first one, that all workgroups have started
+  float *kept;               // copies of the sequences' pending rows as the call finds them, `kept_rows` places for each
+  int kept_rows;
 };
 
 // whether a workgroup of the launch has room on the current device; asked once, before the first launch

@@ -29,7 +29,7 @@ struct SmallShared {
   int lower_first[SMALL_SEQS], upper_first[SMALL_ROWS];   // position of the first row that the pass has of the row's sequence
   int lower_row0[SMALL_SEQS], upper_row0[SMALL_ROWS];     // and that row
   int page[SMALL_SEQS][SMALL_CTX / 16];
-  int n_upper, n_ee, n_full, go;
+  int n_upper, n_ee, n_full, broken;
   u64 best[SMALL_SEQS], key[SMALL_SEQS];
   float score[SMALL_CTX + 64], red[SMALL_WAVES * 128];
 };
@@ -42,11 +42,12 @@ __device__ __forceinline__ void put_word(u64 *p, float v, unsigned tag) {
 }
 __device__ __forceinline__ u64 peek_word(const u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// The last tag that was waited for, and whether some wait of this workgroup has run out of polls: then it asks for
-// nothing any more, and what it hands on it hands on, so that the others need not run out as well
+// The last tag that was waited for, and whether some wait of this wave has run out of polls: then it asks for nothing any
+// more, and what it hands on it hands on, so that the others need not run out as well
 struct SmallLine {
   unsigned tag;
   bool broken;
+  int max_polls;
 };
 // N neighbouring words with tag `tag`, all lanes of the wave together (on: whether this lane asks)
 template <int N>
@@ -59,7 +60,7 @@ __device__ __forceinline__ void take_words(SmallLine &line, const u64 *p, unsign
 #pragma unroll
     for (int i = 0; i < N; ++i) ok = ok && (unsigned)(w[i] >> 32) == tag;
     if (__all((int)ok) || line.broken) break;
-    if (polls == SMALL_MAX_POLLS) line.broken = true;
+    if (polls == line.max_polls) line.broken = true;
   }
 #pragma unroll
   for (int i = 0; i < N; ++i) v[i] = on ? __uint_as_float((unsigned)w[i]) : 0.f;
@@ -71,14 +72,17 @@ __device__ __forceinline__ u64 small_key(u64 key, int step) {
   const unsigned index = 0xffffffffu - (unsigned)key;
   return (key & 0xffffffff00000000ull) | (u64)((unsigned)(step + 1) << 16) | (u64)(key ? (0xffffu - index) & 0xffffu : 0u);
 }
+// (a wait that has run out: 0 for all lanes, as keys of some workgroups alone would not belong to the logits)
 __device__ __forceinline__ u64 take_key(SmallLine &line, const u64 *p, int step) {
   u64 k;
+  bool ok;
   for (int polls = 0;; ++polls) {
     k = peek_word(p);
-    if (__all((int)(((unsigned)k >> 16) == (unsigned)(step + 1))) || line.broken) break;
-    if (polls == SMALL_MAX_POLLS) line.broken = true;
+    ok = __all((int)(((unsigned)k >> 16) == (unsigned)(step + 1)));
+    if (ok || line.broken) break;
+    if (polls == line.max_polls) line.broken = true;
   }
-  return k >> 32 ? (k & 0xffffffff00000000ull) | (u64)(0xffffffffu - (0xffffu - ((unsigned)k & 0xffffu))) : 0ull;
+  return ok && k >> 32 ? (k & 0xffffffff00000000ull) | (u64)(0xffffffffu - (0xffffu - ((unsigned)k & 0xffffu))) : 0ull;
 }
 
 // sum over the wave, in its last lane
@@ -341,7 +345,7 @@ __device__ __forceinline__ void small_attention(SmallLine &line, SmallShared &sh
 #pragma unroll
         for (int i = 0; i < 4; ++i) ok = ok && (unsigned)(wq[i] >> 32) == tag && (unsigned)(wk[i] >> 32) == tag && (unsigned)(wv[i] >> 32) == tag;
         if (__all((int)ok) || line.broken) break;
-        if (polls == SMALL_MAX_POLLS) line.broken = true;
+        if (polls == line.max_polls) line.broken = true;
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) { qf[i] = __uint_as_float((unsigned)wq[i]); kf[i] = __uint_as_float((unsigned)wk[i]); vf[i] = __uint_as_float((unsigned)wv[i]); }
@@ -409,7 +413,7 @@ small_steps_k(SmallSteps) {
   float *lds = (float *)smem4;
   __shared__ SmallShared sh;
   const int n = fresh_args().n, steps = fresh_args().steps;
-  SmallLine line{0u, false};
+  SmallLine line{0u, false, fresh_args().max_polls};
   {
     const SmallSteps &a = fresh_args();
     const int tid = threadIdx.x;
@@ -422,6 +426,12 @@ small_steps_k(SmallSteps) {
     for (int i = tid; i < n * (SMALL_CTX / 16); i += SMALL_THREADS) {
       const int b = i / (SMALL_CTX / 16), p = i % (SMALL_CTX / 16);
       sh.page[b][p] = p < a.kv.max_pages ? a.kv.page_table[sh.seq[b] * a.kv.max_pages + p] : 0;
+    }
+    // a call that has to run again needs the pending rows, which its full-depth steps complete in place
+    for (int i = blockIdx.x; i < n * a.kept_rows; i += SMALL_WGS) {
+      const int b = i / a.kept_rows, r = i % a.kept_rows;
+      if (r < sh.st[b][ST_NPENDING])
+        for (int k = tid; k < a.d; k += SMALL_THREADS) a.kept[(size_t)i * a.d + k] = load_device_scope(a.hidden + (size_t)(sh.seq[b] * a.sp.rmax + r) * a.d + k);
     }
     // what an earlier launch has left in the words is not to be taken for a tag
     const int me = blockIdx.x * SMALL_THREADS + tid;
@@ -437,10 +447,14 @@ small_steps_k(SmallSteps) {
     if (tid == 0) __hip_atomic_store(a.flags + blockIdx.x, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (tid < 64) {
       int polls = 0;
-      while (!__all((int)(__hip_atomic_load(a.flags + (tid & (SMALL_WGS - 1)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.epoch)) && ++polls < SMALL_MAX_POLLS) {}
-      if (polls >= SMALL_MAX_POLLS) line.broken = true;
+      while (!__all((int)(__hip_atomic_load(a.flags + (tid & (SMALL_WGS - 1)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.epoch)) && ++polls < a.first_polls) {}
+      if (tid == 0) sh.broken = polls >= a.first_polls;
     }
     __syncthreads();
+    if (sh.broken) {   // (a workgroup that has yet to start would copy pending rows that this one has completed)
+      if (tid == 0) atomicOr(a.plan + PL_ERR, ERR_STALLED);
+      return;
+    }
   }
 
   for (int step = 0; step < steps; ++step) {

@@ -81,7 +81,7 @@ struct PassBuffers {
 
 struct Seq {
   bool open = false, prefilled = false;
-  int cycle_offset = 0, len = 0, g = 0, j_stream = 0, n_pending = 0, last_full = 0;
+  int cycle_offset = 0, len = 0, g = 0, j_stream = 0, n_pending = 0, last_full = 0, next = 0;   // next: input of the next step
   int text_budget = 0;   // > 0: speech only after this many text tokens
   int phase = 0;         // the sequence's phase on speech positions (the configuration's, unless moved)
   std::vector<int> pages;
@@ -134,6 +134,8 @@ struct spark_ctx {
   size_t layer_bytes = 0;      // of one layer's weights, bf16
   bool row_words_clean = false;   // no word of its hand-overs holds a number that is still to come
   unsigned row_tag = 0;        // the last number used
+  int wait_polls = 0;          // "wait_polls": questions of a wait inside those launches before it runs out (0: as many as the kernels' headers say)
+  bool may_wait = true;        // the call being enqueued may take such launches: it can run again should a wait run out
   bool static_scratch = false; // the scratch area is the library's static device array (spark_init_static)
   int device = 0;
   float temperature = 0.f, top_p = 0.f;   // nucleus sampling, off while temperature <= 0
@@ -1064,7 +1066,7 @@ bool shape_allows_one_row(const spark_config &g) {
 constexpr size_t ROW_LAYER_BYTES = (size_t)180 << 20;
 constexpr int ROW_LAYERS = 4;
 bool one_row_runs(const spark_ctx *c, int layers) {
-  if (!c->row_ok || !c->use_row || c->prof_class >= 0 || c->attn_splits_now <= 0 || c->cfg.n_kv_heads * c->attn_splits_now > ROW_WGS) return false;
+  if (!c->row_ok || !c->use_row || !c->may_wait || c->prof_class >= 0 || c->attn_splits_now <= 0 || c->cfg.n_kv_heads * c->attn_splits_now > ROW_WGS) return false;
   return c->use_row == 2 || (c->layer_bytes >= ROW_LAYER_BYTES && layers >= ROW_LAYERS);
 }
 
@@ -1098,6 +1100,7 @@ bool enqueue_one_row(spark_ctx *c, int l0, int l1, const RowDesc *row) {
   a.tag = c->row_tag + 1;
   c->row_tag += layers;
   a.error = at<int>(c, c->lo.plan) + PL_ERR;
+  a.max_polls = c->wait_polls ? std::abs(c->wait_polls) : ROW_MAX_POLLS;
   if (launch_one_row(a, lds, c->stream) == hipSuccess) return true;
   (void)hipGetLastError();
   return false;
@@ -1282,6 +1285,18 @@ int enqueue_step(spark_ctx *c, int n, int n_upper, int n_ee, int n_full, const i
   return SPARK_OK;
 }
 
+// Copies of the pending rows of a call's sequences lie in the slots of prompt rows, which no step uses, `pending` places
+// (the most that one has) for each
+float *kept_rows(spark_ctx *c) { return c->base.hidden + (size_t)c->cfg.max_batch * c->dv.rmax * c->cfg.d_model; }
+
+// grid (pending, sequences); back: from the copies to the sequences' slots
+__global__ void __launch_bounds__(256) copy_pending_k(const int *seq_ids, const int *state, int rmax, int d, float *hidden, float *kept, bool back) {
+  const int seq = seq_ids[blockIdx.y], r = blockIdx.x;
+  if (r >= state[seq * ST_WORDS + ST_NPENDING]) return;
+  float *slot = hidden + (size_t)(seq * rmax + r) * d, *copy = kept + (size_t)(blockIdx.y * gridDim.x + r) * d;
+  for (int k = threadIdx.x * 4; k < d; k += 256 * 4) *(float4 *)((back ? slot : copy) + k) = *(const float4 *)((back ? copy : slot) + k);
+}
+
 // Where the words that the phases of such a launch hand over lie: in the MLP activations of the other path, and in
 // what it keeps from the queries to the attention partials
 struct SmallWords { size_t act, x, end_a, qkv, attn, u, end_b; };
@@ -1325,13 +1340,13 @@ bool shape_allows_small(const spark_config &g, const Derived &d, const Layout &l
 //   3.9 MB  1 sequence 42.9 / 83.1 (0.1), 8: 72.5 / 123.4 (0.6), 16: 115 / 159 (1.1), 1 of 900 tokens 81 / 95 (0.3), 8 of 900 123 / 147 (1.4)
 //   8.1 MB  1 sequence 49.5 / 84.9 (0.1), 8: 106 / 132 (1.1), 4 of 900 121 / 138 (1.4), 8 of 400 153 / 146 (1.9), 16: 184 / 168 (2.2), 8 of 900 209 / 155 (2.8)
 bool small_steps_pay(const spark_ctx *c, int n, int rows, int positions) {
-  if (!c->small_ok || !c->use_small || c->prof_class >= 0 || n > SMALL_SEQS || rows > SMALL_ROWS || positions > SMALL_CTX) return false;
+  if (!c->small_ok || !c->use_small || !c->may_wait || c->prof_class >= 0 || n > SMALL_SEQS || rows > SMALL_ROWS || positions > SMALL_CTX) return false;
   const int rounds = (rows * c->cfg.n_q_heads + SMALL_WGS - 1) / SMALL_WGS;
   return rows * (double)c->small_layer_bytes / (double)(256u << 20) + rounds * (double)positions / 4096.0 <= 1.5;
 }
 
-// all steps of a call in one launch; rows: of the largest pass
-bool enqueue_small_steps(spark_ctx *c, int steps, int n, int rows, bool forced, bool sampled) {
+// all steps of a call in one launch; rows: of the largest pass; pending: of a sequence as the call begins, at most
+bool enqueue_small_steps(spark_ctx *c, int steps, int n, int rows, int pending, bool forced, bool sampled) {
   const spark_config &g = c->cfg;
   SmallSteps a;
   a.sp = c->sp;
@@ -1363,9 +1378,37 @@ bool enqueue_small_steps(spark_ctx *c, int steps, int n, int rows, bool forced, 
   a.n = n; a.steps = steps;
   a.temperature = c->temperature; a.top_p = c->top_p;
   a.epoch = ++c->small_epoch;
+  a.max_polls = c->wait_polls ? std::abs(c->wait_polls) : SMALL_MAX_POLLS;
+  a.first_polls = c->wait_polls < 0 ? a.max_polls : SMALL_MAX_POLLS;
+  a.kept = kept_rows(c); a.kept_rows = pending;
   if (launch_small_steps(a, g.head_dim, c->stream) == hipSuccess) return true;
   (void)hipGetLastError();
   return false;
+}
+
+// The call's sequences as they were before it, on the device (their counters from the host's mirror, their pending rows from
+// the copies), for another run of it: a launch whose workgroups wait for each other has given up.  This context keeps to
+// launches per operation from then on.
+int begin_again(spark_ctx *c, int n, const int32_t *seq_ids, int pending) {
+  c->use_small = false;
+  c->use_row = 0;
+  c->row_words_clean = false;
+  HIP_TRY(c, hipMemsetAsync(at<int>(c, c->lo.plan) + PL_ERR, 0, sizeof(int), c->stream));
+  for (int i = 0; i < n; ++i) {
+    const Seq &s = c->seqs[seq_ids[i]];
+    int st[ST_WORDS];
+    st[ST_LEN] = s.len; st[ST_G] = s.g; st[ST_JSTREAM] = s.j_stream; st[ST_NPENDING] = s.n_pending; st[ST_OFFSET] = s.cycle_offset;
+    st[ST_NEXT] = s.next; st[ST_ACTIVE] = 1; st[ST_LASTFULL] = s.last_full; st[ST_TEXTBUDGET] = s.text_budget; st[ST_PHASE] = s.phase;
+    HIP_TRY(c, hipMemcpyAsync(at<int>(c, c->lo.state) + (size_t)seq_ids[i] * ST_WORDS, st, sizeof(st), hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));   // (`st` has been read)
+  }
+  if (pending) {
+    copy_pending_k<<<dim3(pending, n), 256, 0, c->stream>>>(at<int>(c, c->lo.seq_ids), at<int>(c, c->lo.state), c->dv.rmax, c->cfg.d_model,
+                                                            c->base.hidden, kept_rows(c), true);
+    HIP_TRY(c, hipGetLastError());
+  }
+  snprintf(c->err, sizeof(c->err), "a launch whose workgroups wait for each other gave up; the call ran again as launches per operation");
+  return SPARK_OK;
 }
 
 int decode_chunk(spark_ctx *c, int steps, int n, const int32_t *seq_ids, const int32_t *forced,
@@ -1452,9 +1495,18 @@ int decode_chunk(spark_ctx *c, int steps, int n, const int32_t *seq_ids, const i
     most_rows = std::max(most_rows, sh.n_upper);
   }
   const bool sampled = rand_words && c->temperature > 0.f;
-  // (a device that has no room for all workgroups of such a launch at once refuses it)
-  if (!(small_steps_pay(c, n, std::max(n, most_rows), shapes[steps - 1].max_pos + 1) && (!sampled || c->dv.V <= SAMPLE_CHUNK) &&
-        enqueue_small_steps(c, steps, n, std::max(n, most_rows), forced != nullptr, sampled))) {
+  int pending = 0;   // rows of a sequence as the call begins, at most
+  for (int i = 0; i < n; ++i) pending = std::max(pending, c->seqs[seq_ids[i]].n_pending);
+  auto enqueue = [&]() -> int {
+    // (a device that has no room for all workgroups of such a launch at once refuses it)
+    if (small_steps_pay(c, n, std::max(n, most_rows), shapes[steps - 1].max_pos + 1) && (!sampled || c->dv.V <= SAMPLE_CHUNK) &&
+        enqueue_small_steps(c, steps, n, std::max(n, most_rows), pending, forced != nullptr, sampled))
+      return SPARK_OK;
+    if (pending && c->row_ok && c->use_row && c->may_wait) {
+      copy_pending_k<<<dim3(pending, n), 256, 0, c->stream>>>(at<int>(c, c->lo.seq_ids), at<int>(c, c->lo.state), c->dv.rmax, g.d_model,
+                                                              c->base.hidden, kept_rows(c), false);
+      HIP_TRY(c, hipGetLastError());
+    }
     for (int st = 0; st < steps; ++st) {
       const Shape &sh = shapes[st];
       c->attn_splits_now = sh.max_pos / ATTN_SLICE + 1;
@@ -1463,30 +1515,36 @@ int decode_chunk(spark_ctx *c, int steps, int n, const int32_t *seq_ids, const i
       int *od = at<int>(c, c->lo.out_depth) + (size_t)st * n;
       const unsigned long long *rw =
           rand_words ? at<unsigned long long>(c, c->lo.rand_words) + (size_t)st * n : nullptr;
-      rc = g.dtype == SPARK_DTYPE_BF16 ? enqueue_step<bf16_t>(c, n, sh.n_upper, sh.n_ee, sh.n_full, pf, pt, rw, od)
-                                       : enqueue_step<float>(c, n, sh.n_upper, sh.n_ee, sh.n_full, pf, pt, rw, od);
-      if (rc) return rc;
+      const int e = g.dtype == SPARK_DTYPE_BF16 ? enqueue_step<bf16_t>(c, n, sh.n_upper, sh.n_ee, sh.n_full, pf, pt, rw, od)
+                                                : enqueue_step<float>(c, n, sh.n_upper, sh.n_ee, sh.n_full, pf, pt, rw, od);
+      if (e) return e;
     }
     emit_k<<<1, SCHED_THREADS, 0, c->stream>>>(step_io(c, n), forced ? at<int>(c, c->lo.forced) + (size_t)(steps - 1) * n : nullptr,
                                               at<int>(c, c->lo.out_tokens) + (size_t)(steps - 1) * n);
     HIP_TRY(c, hipGetLastError());
-  }
+    return SPARK_OK;
+  };
 
-  // results
   const size_t cnt = (size_t)steps * n;
   int *h_tok = c->h_out, *h_dep = c->h_out + (size_t)MAX_STEPS_PER_CALL * g.max_batch;
   int *h_plan = h_dep + (size_t)MAX_STEPS_PER_CALL * g.max_batch;
-  HIP_TRY(c, hipMemcpyAsync(h_tok, at<int>(c, c->lo.out_tokens), sizeof(int) * cnt,
-                            hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(h_dep, at<int>(c, c->lo.out_depth), sizeof(int) * cnt,
-                            hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(h_plan, at<int>(c, c->lo.plan), sizeof(int) * PL_WORDS,
-                            hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  auto run = [&]() -> int {   // and its results
+    if (int e = enqueue()) return e;
+    HIP_TRY(c, hipMemcpyAsync(h_tok, at<int>(c, c->lo.out_tokens), sizeof(int) * cnt,
+                              hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(h_dep, at<int>(c, c->lo.out_depth), sizeof(int) * cnt,
+                              hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(h_plan, at<int>(c, c->lo.plan), sizeof(int) * PL_WORDS,
+                              hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    return SPARK_OK;
+  };
+  c->may_wait = n * pending <= PREFILL_CHUNK;   // (the copies have their places)
+  rc = run();
+  c->may_wait = true;
+  if (rc) return rc;
   if (h_plan[PL_ERR] & ERR_STALLED) {
-    int zero = 0;
-    (void)hipMemcpy(at<int>(c, c->lo.plan) + PL_ERR, &zero, sizeof(int), hipMemcpyHostToDevice);
-    return fail(c, SPARK_EHIP, "the workgroups of a launch waited for each other in vain");
+    if ((rc = begin_again(c, n, seq_ids, pending)) || (rc = run())) return rc;
   }
   memcpy(out_tokens, h_tok, sizeof(int) * cnt);
   memcpy(out_depth, h_dep, sizeof(int) * cnt);
@@ -1512,6 +1570,8 @@ int decode_chunk(spark_ctx *c, int steps, int n, const int32_t *seq_ids, const i
   for (int i = 0; i < n; ++i) {
     Seq &s = c->seqs[seq_ids[i]];
     s.g = mir[i].g; s.j_stream = mir[i].j; s.n_pending = mir[i].npend; s.len = mir[i].len;
+    const size_t k = (size_t)(steps - 1) * n + i;
+    s.next = forced && forced[k] >= 0 ? forced[k] : h_tok[k];
   }
   if (h_plan[PL_ERR]) {
     int e = h_plan[PL_ERR];
@@ -1774,6 +1834,7 @@ int spark_tune(spark_ctx *c, const char *name, int32_t value) {
   else if (k == "direct_whole_k") c->direct_whole_k = value;
   else if (k == "small_steps") c->use_small = value != 0;
   else if (k == "one_row") c->use_row = std::max(0, std::min(2, (int)value));
+  else if (k == "wait_polls") c->wait_polls = std::max(-SMALL_MAX_POLLS, (int)value);
   else if (k == "fuse_norm") c->fuse_norm = value != 0;
   else return fail(c, SPARK_EINVAL, "unknown tuning name '%s'", name);
   return SPARK_OK;
@@ -1821,6 +1882,7 @@ int spark_prefill(spark_ctx *c, int32_t seq_id, const int32_t *prompt, int32_t n
                             hipMemcpyHostToDevice, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   s->len = n - 1;
+  s->next = prompt[n - 1];
   s->prefilled = true;
   return SPARK_OK;
 }

@@ -115,3 +115,49 @@ def test_two_contexts_on_two_threads(sb):
         t.join(60)
     for o in out:
         assert o is not None and all(np.array_equal(x, y) for x, y in zip(o, alone))
+
+
+def _last_error(sp):
+    return sp.lib.spark_last_error(sp.handle).decode()
+
+
+# the call that meets a wait which runs out begins without and with pending rows; one sequence, and three of which single
+# ones run full depth now and then
+@pytest.mark.parametrize("first,n_seq", [(0, 1), (4, 1), (5, 1), (4, 3)])
+def test_waits_that_run_out(sb, first, n_seq):
+    """the call runs again as launches per operation, from its start: bit by bit what a context gives that has been told
+    to take those for this call, and so does what follows, also for a sequence that had no part in the call"""
+    shape = _shape("patience", d_model=1024, n_q_heads=16, n_kv_heads=8, d_ffn=1536)
+    weights = wl.make_weights(shape, seed=4, gain_std=0.1)
+
+    def go(patient):
+        with closing(sb.Spark(shape, wl.TINY.schedule, weights, max_batch=n_seq + 1, max_seq_len=192, kv_page_tokens=16)) as sp:
+            sp.tune("one_row", 2)
+            ids = [sp.seq_open(b) for b in range(n_seq + 1)]
+            for b, s in enumerate(ids):
+                sp.prefill(s, wl.make_prompt(shape, 30 + b, seed=63 + b))
+            ids, other = ids[:n_seq], ids[n_seq:]
+            out = []
+            if first:
+                out += list(sp.decode(first, ids))
+            assert _last_error(sp) == ""
+            if patient:
+                sp.tune("one_row", 0)
+            else:
+                sp.tune("wait_polls", 1)
+            out += list(sp.decode(9, ids))
+            assert ("gave up" in _last_error(sp)) == (not patient)
+            out += list(sp.decode(8, ids))      # launches per operation in both
+            out += list(sp.decode(7, other))
+            sp.tune("wait_polls", 0)
+            sp.tune("one_row", 2)
+            out += list(sp.decode(11, ids + other))
+            out += [sp.get_logits(s)[0] for s in ids + other]
+            for s in ids + other:
+                st = sp.seq_state(s)
+                out += [np.array(sorted(st.values()))] + [x for l in range(shape.n_layers) for p in range(28, st["upper_valid"], 3) for x in sp.get_kv(s, l, p)]
+        return out
+
+    say(f"one row, waits that run out after {first} steps of {n_seq}")
+    for x, y in zip(go(False), go(True), strict=True):
+        assert np.array_equal(x, y)

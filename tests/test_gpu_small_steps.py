@@ -107,3 +107,48 @@ def test_two_contexts_on_two_threads(sb):
         t.join(60)
     for o in out:
         assert o is not None and all(np.array_equal(x, y) for x, y in zip(o, alone))
+
+
+# the call that meets a wait which runs out begins without and with pending rows; greedy and drawn; the wait is one for a
+# value, or the first, for the other workgroups (negative)
+@pytest.mark.parametrize("first,n_seq,sample,polls", [(0, 1, False, 1), (4, 2, False, 1), (5, 16, False, 1), (4, 3, True, 1), (4, 2, False, -1)])
+def test_waits_that_run_out(sb, first, n_seq, sample, polls):
+    """the call runs again as launches per operation, from its start: bit by bit what a context gives that has been told
+    to take those for this call, and so does what follows, also for a sequence that had no part in the call"""
+    w = wl.TINY
+    weights = wl.make_weights(w.shape, seed=0, gain_std=0.1)
+    words = np.random.Generator(np.random.Philox(9)).integers(0, 2 ** 64, size=(40, n_seq + 1), dtype=np.uint64)
+
+    def go(patient):
+        with closing(sb.Spark(w.shape, w.schedule, weights, max_batch=n_seq + 1, max_seq_len=160, kv_page_tokens=16)) as sp:
+            def decode(steps, ids):
+                return list(sp.decode_sampled(steps, ids, words[:steps, :len(ids)]) if sample else sp.decode(steps, ids))
+            if sample:
+                sp.set_sampling(0.7, 0.9)
+            ids = [sp.seq_open(b) for b in range(n_seq + 1)]
+            for b, s in enumerate(ids):
+                sp.prefill(s, wl.make_prompt(w.shape, 30 + b, seed=63 + b))
+            ids, other = ids[:n_seq], ids[n_seq:]
+            out = decode(first, ids) if first else []
+            error = lambda: sp.lib.spark_last_error(sp.handle).decode()   # noqa: E731
+            assert error() == ""
+            if patient:
+                sp.tune("small_steps", 0)
+            else:
+                sp.tune("wait_polls", polls)
+            out += decode(9, ids)
+            assert ("gave up" in error()) == (not patient)
+            out += decode(8, ids)      # launches per operation in both
+            out += decode(7, other)
+            sp.tune("wait_polls", 0)
+            sp.tune("small_steps", 1)
+            out += decode(11, other) + decode(11, ids)
+            out += [sp.get_logits(s)[0] for s in ids]
+            for s in ids + other:
+                st = sp.seq_state(s)
+                out += [np.array(sorted(st.values()))] + [x for l in range(w.shape.n_layers) for p in range(28, st["upper_valid"], 3) for x in sp.get_kv(s, l, p)]
+        return out
+
+    say(f"small steps, waits that run out after {first} steps of {n_seq}")
+    for x, y in zip(go(False), go(True), strict=True):
+        assert np.array_equal(x, y)
