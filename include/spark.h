@@ -199,7 +199,8 @@ int spark_align_phases(spark_ctx *ctx, int32_t n, const int32_t *seq_ids);
  * Sec. IV-B.3); the last id is held as the input of the first spark_step, so that every generated
  * token comes out of spark_step with its executed depth.  One prompt per sequence (SPARK_ESTATE on
  * a second); SPARK_EINVAL: empty prompt or an id outside the vocabulary; SPARK_ENOMEM: longer
- * than max_seq_len or no KV pages left.  Returns when the prompt pass has completed. */
+ * than max_seq_len or no KV pages left.  Returns when the prompt pass has completed.  A pass of one position
+ * may be a launch that gives up and runs again, as described for spark_decode. */
 int spark_prefill(spark_ctx *ctx, int32_t seq_id, const int32_t *prompt, int32_t n);
 
 /* One decoding step for n distinct prefilled sequences seq_ids[0..n) [host] (Algorithm 1).

@@ -136,6 +136,7 @@ struct spark_ctx {
   unsigned row_tag = 0;        // the last number used
   int wait_polls = 0;          // "wait_polls": questions of a wait inside those launches before it runs out (0: as many as the kernels' headers say)
   bool may_wait = true;        // the call being enqueued may take such launches: it can run again should a wait run out
+  bool row_taken = false;      // a pass of one row has since prefill_rows last asked
   bool static_scratch = false; // the scratch area is the library's static device array (spark_init_static)
   int device = 0;
   float temperature = 0.f, top_p = 0.f;   // nucleus sampling, off while temperature <= 0
@@ -1101,7 +1102,10 @@ bool enqueue_one_row(spark_ctx *c, int l0, int l1, const RowDesc *row) {
   c->row_tag += layers;
   a.error = at<int>(c, c->lo.plan) + PL_ERR;
   a.max_polls = c->wait_polls ? std::abs(c->wait_polls) : ROW_MAX_POLLS;
-  if (launch_one_row(a, lds, c->stream) == hipSuccess) return true;
+  if (launch_one_row(a, lds, c->stream) == hipSuccess) {
+    c->row_taken = true;
+    return true;
+  }
   (void)hipGetLastError();
   return false;
 }
@@ -1386,14 +1390,21 @@ bool enqueue_small_steps(spark_ctx *c, int steps, int n, int rows, int pending, 
   return false;
 }
 
-// The call's sequences as they were before it, on the device (their counters from the host's mirror, their pending rows from
-// the copies), for another run of it: a launch whose workgroups wait for each other has given up.  This context keeps to
-// launches per operation from then on.
-int begin_again(spark_ctx *c, int n, const int32_t *seq_ids, int pending) {
+// A launch whose workgroups wait for each other has given up: the call runs again, and this context keeps to launches per
+// operation from then on.
+int stop_waiting(spark_ctx *c) {
   c->use_small = false;
   c->use_row = 0;
   c->row_words_clean = false;
+  snprintf(c->err, sizeof(c->err), "a launch whose workgroups wait for each other gave up; the call ran again as launches per operation");
   HIP_TRY(c, hipMemsetAsync(at<int>(c, c->lo.plan) + PL_ERR, 0, sizeof(int), c->stream));
+  return SPARK_OK;
+}
+
+// The call's sequences as they were before it, on the device (their counters from the host's mirror, their pending rows from
+// the copies), for another run of it
+int begin_again(spark_ctx *c, int n, const int32_t *seq_ids, int pending) {
+  if (int rc = stop_waiting(c)) return rc;
   for (int i = 0; i < n; ++i) {
     const Seq &s = c->seqs[seq_ids[i]];
     int st[ST_WORDS];
@@ -1407,7 +1418,6 @@ int begin_again(spark_ctx *c, int n, const int32_t *seq_ids, int pending) {
                                                             c->base.hidden, kept_rows(c), true);
     HIP_TRY(c, hipGetLastError());
   }
-  snprintf(c->err, sizeof(c->err), "a launch whose workgroups wait for each other gave up; the call ran again as launches per operation");
   return SPARK_OK;
 }
 
@@ -1610,11 +1620,16 @@ template <typename WT> int prefill_rows(spark_ctx *c, int id, const int32_t *pro
       embed_rows_k<WT><<<m, 256, 0, c->stream>>>(rows_dev, nullptr, tok_dev, (const WT *)c->w.embed, g.d_model, c->pb.hidden);
       HIP_TRY(c, hipGetLastError());
       c->attn_splits_now = (p0 + m - 1) / ATTN_SLICE + 1;
+      c->row_taken = false;
       if (int e = run_layers<WT>(c, 0, g.n_layers, rows_dev, m)) return e;
+      if (c->row_taken)
+        HIP_TRY(c, hipMemcpyAsync(c->h_out, at<int>(c, c->lo.plan) + PL_ERR, sizeof(int), hipMemcpyDeviceToHost, c->stream));
       HIP_TRY(c, hipStreamSynchronize(c->stream));
       return SPARK_OK;
     };
     rc = pass();
+    // (a pass begins with the embedding, and writes every hidden value and cache entry that it has: it can simply run again)
+    if (rc == SPARK_OK && c->row_taken && (*c->h_out & ERR_STALLED) && (rc = stop_waiting(c)) == SPARK_OK) rc = pass();
   }
   c->pb = c->base;
   c->prompt_pass = false;

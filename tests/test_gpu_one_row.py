@@ -161,3 +161,26 @@ def test_waits_that_run_out(sb, first, n_seq):
     say(f"one row, waits that run out after {first} steps of {n_seq}")
     for x, y in zip(go(False), go(True), strict=True):
         assert np.array_equal(x, y)
+
+
+# a prompt of two tokens is a pass of one row; prompts of 34 and 514 (32 and 512 rows a pass, the latter in the buffers of
+# large passes) end with one, whose context is the passes before it and whose words lie where those left their partial sums
+@pytest.mark.parametrize("n,rows", [(2, 0), (34, 32), (514, 512)])
+@pytest.mark.parametrize("polls", [0, 1])
+def test_prompt_passes_of_one_row(sb, n, rows, polls):
+    """against the oracle, cache entries too, also where a wait runs out and the pass runs again"""
+    w = wl.TINY
+    shape = _shape("one row of a prompt", d_model=776, n_q_heads=7, n_kv_heads=1, d_ffn=1400)
+    weights = wl.make_weights(shape, seed=4, gain_std=0.1)
+    say(f"one row of a prompt of {n}, {polls} polls")
+    with closing(sb.Spark(shape, w.schedule, weights, max_batch=1, max_seq_len=544, kv_page_tokens=16)) as sp:
+        sp.tune("one_row", 2)
+        sp.tune("wait_polls", polls)
+        sp.tune("prefill_rows", rows)
+        sid = sp.seq_open(0)
+        sp.prefill(sid, wl.make_prompt(shape, n, seed=65))
+        assert ("gave up" in _last_error(sp)) == (polls > 0)
+        sp.seq_close(sid)
+        sp.tune("one_row", 2)
+        compare_run(sp, shape, w.schedule, weights, [wl.make_prompt(shape, n, seed=66)], [0], 8, check_kv_every=1, kv_all_positions=n < 100,
+                    label=f"one row of a prompt of {n}")
