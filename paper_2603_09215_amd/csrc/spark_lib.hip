@@ -22,6 +22,7 @@
 #include "measure.h"
 #include "mfma_gemm.h"
 #include "one_row.h"
+#include "row_rule.h"
 #include "sampling.h"
 #include "sched.h"
 #include "small_steps.h"
@@ -1058,17 +1059,10 @@ bool shape_allows_one_row(const spark_config &g) {
          one_row_lds(a) > 0 && sizeof(row_word) * row_words(g).end <= MFMA_PARTIAL_BYTES;
 }
 
-// Whether a pass of one row takes the one launch.  Its hand-overs cost a layer some 20 us whatever the layer's size, a
-// cooperative launch some 20 us more than a plain one, and attention has at most one slice of 64 tokens per workgroup.
-// Measured, us a step of eight layers with small heads, a launch per operation / one launch:
-//   4 MB a layer 194 / 325, 23 MB 222 / 328, 90 MB 319 / 355 (1500 tokens: 339 / 381), 198 MB 437 / 423 (1200 tokens: 452 / 446),
-//   293 MB 541 / 505, 354 MB 636 / 579, 408 MB 661 / 624 (8000 tokens: 744 / 711), 466 MB 730 / 684 (3900 tokens: 784 / 724)
-// So a layer wins 2 to 9 us from ROW_LAYER_BYTES on, and runs of ROW_LAYERS and more make up for the launch.
-constexpr size_t ROW_LAYER_BYTES = (size_t)180 << 20;
-constexpr int ROW_LAYERS = 4;
+// Whether a pass of one row takes the one launch: where it pays, and attention has at most one slice of 64 tokens per workgroup.
 bool one_row_runs(const spark_ctx *c, int layers) {
   if (!c->row_ok || !c->use_row || !c->may_wait || c->prof_class >= 0 || c->attn_splits_now <= 0 || c->cfg.n_kv_heads * c->attn_splits_now > ROW_WGS) return false;
-  return c->use_row == 2 || (c->layer_bytes >= ROW_LAYER_BYTES && layers >= ROW_LAYERS);
+  return c->use_row == 2 || one_row_pays(c->layer_bytes, layers);
 }
 
 __global__ void __launch_bounds__(256) clear_words_k(row_word *words, size_t n) {
