@@ -220,7 +220,8 @@ int spark_step(spark_ctx *ctx, int32_t n, const int32_t *seq_ids, const int32_t 
  * Some steps are one launch whose workgroups wait for each other (spark_tune, "small_steps" and "one_row") and need
  * room on the device together.  Should they not get it for some seconds, because another process or stream keeps
  * compute units, such a launch gives up: the call then runs again from its start as launches per operation, returns
- * what those give, spark_last_error says so, and the context keeps to them until spark_tune asks for the others. */
+ * what those give, spark_last_error says so, and the context keeps to them until spark_tune asks for the others.  So it
+ * does, without a word, where the runtime refuses such a launch (one process on a card gets them). */
 int spark_decode(spark_ctx *ctx, int32_t n_steps, int32_t n, const int32_t *seq_ids,
                  const int32_t *forced_next, int32_t *out_tokens, int32_t *out_depth);
 

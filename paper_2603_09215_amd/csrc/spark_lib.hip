@@ -1069,7 +1069,8 @@ __global__ void __launch_bounds__(256) clear_words_k(row_word *words, size_t n) 
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) words[i] = 0ull;
 }
 
-// false: the device has no room for all workgroups of such a launch at once
+// false: refused.  The runtime has one cooperative queue for all processes on a card, and to be told that another has it
+// takes 38 ms, so a context asks once (asked on every pass, ten steps of four layers took 380 ms instead of 1.2).
 bool enqueue_one_row(spark_ctx *c, int l0, int l1, const RowDesc *row) {
   const spark_config &g = c->cfg;
   OneRow a = one_row_shape(g);
@@ -1101,6 +1102,7 @@ bool enqueue_one_row(spark_ctx *c, int l0, int l1, const RowDesc *row) {
     return true;
   }
   (void)hipGetLastError();
+  c->use_row = 0;
   return false;
 }
 
@@ -1343,7 +1345,8 @@ bool small_steps_pay(const spark_ctx *c, int n, int rows, int positions) {
   return rows * (double)c->small_layer_bytes / (double)(256u << 20) + rounds * (double)positions / 4096.0 <= 1.5;
 }
 
-// all steps of a call in one launch; rows: of the largest pass; pending: of a sequence as the call begins, at most
+// all steps of a call in one launch; rows: of the largest pass; pending: of a sequence as the call begins, at most.
+// false: refused (as in enqueue_one_row; a call took 39 ms instead of 1)
 bool enqueue_small_steps(spark_ctx *c, int steps, int n, int rows, int pending, bool forced, bool sampled) {
   const spark_config &g = c->cfg;
   SmallSteps a;
@@ -1381,6 +1384,7 @@ bool enqueue_small_steps(spark_ctx *c, int steps, int n, int rows, int pending, 
   a.kept = kept_rows(c); a.kept_rows = pending;
   if (launch_small_steps(a, g.head_dim, c->stream) == hipSuccess) return true;
   (void)hipGetLastError();
+  c->use_small = false;
   return false;
 }
 
@@ -1502,7 +1506,6 @@ int decode_chunk(spark_ctx *c, int steps, int n, const int32_t *seq_ids, const i
   int pending = 0;   // rows of a sequence as the call begins, at most
   for (int i = 0; i < n; ++i) pending = std::max(pending, c->seqs[seq_ids[i]].n_pending);
   auto enqueue = [&]() -> int {
-    // (a device that has no room for all workgroups of such a launch at once refuses it)
     if (small_steps_pay(c, n, std::max(n, most_rows), shapes[steps - 1].max_pos + 1) && (!sampled || c->dv.V <= SAMPLE_CHUNK) &&
         enqueue_small_steps(c, steps, n, std::max(n, most_rows), pending, forced != nullptr, sampled))
       return SPARK_OK;
