@@ -21,6 +21,10 @@ def sb():
     return binding
 
 
+def _last_error(sp):
+    return sp.lib.spark_last_error(sp.handle).decode()
+
+
 def _shape(name, **over):
     return wl.TINY.shape.replace(name=name, dtype=wl.DTYPE_BF16, n_layers=4, head_dim=128, **over)
 
@@ -40,7 +44,7 @@ SHAPES = [
 def test_shapes(sb, name, over, page):
     w = wl.TINY
     shape = _shape(name, **over)
-    weights = wl.make_weights(shape, seed=4)
+    weights = wl.make_weights(shape, seed=4, gain_std=0.1)
     for n in (1, 31, 62):
         say(f"one row, {name}, {n}")
         with closing(sb.Spark(shape, w.schedule, weights, max_batch=1, max_seq_len=192, kv_page_tokens=page)) as sp:
@@ -49,10 +53,10 @@ def test_shapes(sb, name, over, page):
                         label=f"one row {name} {n}")
 
 
-def _decode(sb, shape, sched, weights, prompt, steps, on, between):
+def _decode(sb, shape, sched, weights, prompt, steps, on, between, max_seq_len=2176):
     """forced steps of one sequence; after a few of them `between` other sequences take steps (wide passes, which leave
     other things in the area of the hand-overs)"""
-    with closing(sb.Spark(shape, sched, weights, max_batch=12, max_seq_len=2176, kv_page_tokens=64)) as sp:
+    with closing(sb.Spark(shape, sched, weights, max_batch=12 if between else 1, max_seq_len=max_seq_len, kv_page_tokens=64)) as sp:
         sp.tune("one_row", on)
         sid = sp.seq_open(0)
         sp.prefill(sid, prompt)
@@ -72,19 +76,78 @@ def _decode(sb, shape, sched, weights, prompt, steps, on, between):
     return np.stack(logits).astype(np.float64), kv
 
 
+def _same(a, ka, b, kb):
+    # another order of the 32-bit sums; a cache entry may round to the neighbouring 16-bit value (2^-8 of it), which
+    # moves the outputs of the layers above by far less than that
+    assert np.linalg.norm(a - b) <= 2.0 ** -8 * np.linalg.norm(a)
+    assert np.all(np.abs(ka - kb) <= 2.0 ** -7 * np.abs(ka) + 1e-3 * np.abs(ka).max())
+
+
 # eight key heads: up to 1024 positions the slices have 32 tokens, up to 2048 64, and beyond that the steps are launches per
 # operation; the second row of each pair crosses the line during the run
 @pytest.mark.parametrize("n,between", [(1000, 0), (1020, 0), (2030, 0), (2045, 0), (90, 11)])
 def test_contexts_and_other_passes(sb, n, between):
     shape = _shape("contexts", d_model=1024, n_q_heads=16, n_kv_heads=8, d_ffn=1536)
-    weights = wl.make_weights(shape, seed=4)
+    weights = wl.make_weights(shape, seed=4, gain_std=0.1)
     prompt = wl.make_prompt(shape, n, seed=61)
     a, ka = _decode(sb, shape, wl.TINY.schedule, weights, prompt, 15, 0, between)
     b, kb = _decode(sb, shape, wl.TINY.schedule, weights, prompt, 15, 2, between)
-    # another order of the 32-bit sums; a cache entry may round to the neighbouring 16-bit value (2^-8 of it), which
-    # moves the outputs of the layers above by far less than that
-    assert np.linalg.norm(a - b) <= 2.0 ** -8 * np.linalg.norm(a)
-    assert np.all(np.abs(ka - kb) <= 2.0 ** -7 * np.abs(ka) + 1e-3 * np.abs(ka).max())
+    _same(a, ka, b, kb)
+
+
+# a KV head's query heads are dealt to four workgroups, to two or to one as the slices become more, 16, 8 or 4 (7: 4 and 3, or 2
+# and 1) to a workgroup; each run crosses a line: 32-token slices 33, 65, 129 of one KV head, 33, 65 of two, then 64-token slices
+@pytest.mark.parametrize("heads,kv_heads,n", [(16, 1, 2044), (16, 1, 4092), (16, 1, 8188), (16, 2, 1020), (16, 2, 2044), (16, 2, 4092),
+                                              (7, 1, 2044), (7, 1, 4092), (32, 2, 1020), (32, 2, 2044)])
+def test_query_heads_of_a_workgroup(sb, heads, kv_heads, n):
+    shape = _shape("heads", d_model=512, n_q_heads=heads, n_kv_heads=kv_heads, d_ffn=768)
+    weights = wl.make_weights(shape, seed=4, gain_std=0.1)
+    say(f"one row, {heads} heads of {kv_heads}, {n} tokens")
+    prompt = wl.make_prompt(shape, n, seed=61)
+    a, ka = _decode(sb, shape, wl.TINY.schedule, weights, prompt, 10, 0, 0, n + 64)
+    b, kb = _decode(sb, shape, wl.TINY.schedule, weights, prompt, 10, 2, 0, n + 64)
+    _same(a, ka, b, kb)
+
+
+# cycle offsets, and which of the sequences then sometimes run full depth alone and with nothing pending
+@pytest.mark.parametrize("offsets,which", [((0, 1), {0}), ((1, 0), {1}), ((2, 0), {0, 1}), ((5, 3, 4), {0, 1})])
+def test_layers_above_the_exit_alone(sb, offsets, which):
+    """several rows below the exit layer and one above it: the one launch takes the upper layers of a row that others have left"""
+    w = wl.TINY
+    shape = _shape("upper", d_model=1024, n_q_heads=16, n_kv_heads=8, d_ffn=1536)
+    weights = wl.make_weights(shape, seed=4, gain_std=0.1)
+    steps = 18
+    rows = np.zeros((len(offsets), steps), dtype=int)   # above the exit layer
+    for b, off in enumerate(offsets):
+        pending = 0
+        for g, depth in enumerate(sb.schedule_preview(shape, w.schedule, steps, off)[0]):
+            full = depth == shape.n_layers
+            rows[b, g] = pending + 1 if full else 0
+            pending = 0 if full else pending + 1
+    alone = rows.sum(0) == 1
+    assert alone.sum() >= 3 and set(rows[:, alone].argmax(0)) == which
+    say(f"one row above the exit layer, offsets {offsets}: {int(alone.sum())} steps")
+    with closing(sb.Spark(shape, w.schedule, weights, max_batch=len(offsets), max_seq_len=96, kv_page_tokens=16)) as sp:
+        sp.tune("one_row", 2)
+        compare_run(sp, shape, w.schedule, weights, [wl.make_prompt(shape, 20 + 9 * b, seed=68 + b) for b in range(len(offsets))], list(offsets),
+                    steps, check_kv_every=1, label=f"one row above the exit layer {offsets}")
+
+
+def test_static_scratch(sb):
+    """the words lie in the library's own scratch area too, which holds what another context has left"""
+    shape = _shape("static", d_model=776, n_q_heads=7, n_kv_heads=1, d_ffn=1400)
+    weights = wl.make_weights(shape, seed=4, gain_std=0.1)
+    say("one row on the static scratch area")
+    out = []
+    for static in (True, False, True):
+        with closing(sb.Spark(shape, wl.TINY.schedule, weights, max_batch=1, max_seq_len=96, kv_page_tokens=16, static_scratch=static)) as sp:
+            sp.tune("one_row", 2)
+            sid = sp.seq_open(0)
+            sp.prefill(sid, wl.make_prompt(shape, 2, seed=69))
+            out.append((*sp.decode(14, [sid]), sp.get_logits(sid)[0], *sp.get_kv(sid, 3, 12)))
+            assert _last_error(sp) == ""
+    for o in out[1:]:
+        assert all(np.array_equal(x, y) for x, y in zip(o, out[0], strict=True))
 
 
 def test_two_contexts_on_two_threads(sb):
@@ -93,7 +156,7 @@ def test_two_contexts_on_two_threads(sb):
 
     import torch
     shape = _shape("threads", d_model=1024, n_q_heads=16, n_kv_heads=8, d_ffn=1536)
-    weights = wl.make_weights(shape, seed=4)
+    weights = wl.make_weights(shape, seed=4, gain_std=0.1)
     say("one row on two threads")
 
     def go(stream):
@@ -115,10 +178,6 @@ def test_two_contexts_on_two_threads(sb):
         t.join(60)
     for o in out:
         assert o is not None and all(np.array_equal(x, y) for x, y in zip(o, alone))
-
-
-def _last_error(sp):
-    return sp.lib.spark_last_error(sp.handle).decode()
 
 
 # the call that meets a wait which runs out begins without and with pending rows; one sequence, and three of which single
