@@ -11,6 +11,7 @@
 // The launch is cooperative, so that all workgroups are resident before any waits; every wait is bounded as well.
 #pragma once
 #include "device_common.h"
+#include "handover.h"
 
 namespace spark {
 
@@ -37,7 +38,7 @@ constexpr int ROW_MAX_D = 8 * ROW_AUX;  // width of a row that is gathered at on
 // kernels may hold compute units that its last workgroups wait for.
 constexpr int ROW_MAX_POLLS = 1 << 22;
 
-typedef unsigned long long row_word;
+typedef hand_word row_word;
 
 struct OneRow {
   int l0, l1, d, nq, nkv, F;

@@ -33,42 +33,6 @@ __device__ __forceinline__ void aux_barrier(unsigned *count, unsigned &target) {
   asm volatile("" ::: "memory");
 }
 
-#define ROW_DPP(v, ctrl) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false))
-// sum over the wave, in its last lane
-__device__ __forceinline__ float total_last(float v) {
-  v += ROW_DPP(v, 0x111);
-  v += ROW_DPP(v, 0x112);
-  v += ROW_DPP(v, 0x114);
-  v += ROW_DPP(v, 0x118);
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x142, 0xa, 0xf, false));
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x143, 0xc, 0xf, false));
-  return v;
-}
-__device__ __forceinline__ float wave_total(float v) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(total_last(v)), 63));
-}
-__device__ __forceinline__ float wave_largest(float v) {
-  v = fmaxf(v, ROW_DPP(v, 0x121));   // row_ror 1, 2, 4, 8: over each 16 lanes
-  v = fmaxf(v, ROW_DPP(v, 0x122));
-  v = fmaxf(v, ROW_DPP(v, 0x124));
-  v = fmaxf(v, ROW_DPP(v, 0x128));
-  const int a = __float_as_int(v);
-  return fmaxf(fmaxf(__int_as_float(__builtin_amdgcn_readlane(a, 0)), __int_as_float(__builtin_amdgcn_readlane(a, 16))),
-               fmaxf(__int_as_float(__builtin_amdgcn_readlane(a, 32)), __int_as_float(__builtin_amdgcn_readlane(a, 48))));
-}
-__device__ __forceinline__ float total16(float v) {   // over each 16 lanes, in all of them
-  v += ROW_DPP(v, 0x121);
-  v += ROW_DPP(v, 0x122);
-  v += ROW_DPP(v, 0x124);
-  v += ROW_DPP(v, 0x128);
-  return v;
-}
-
-__device__ __forceinline__ void put_word(row_word *p, float v, unsigned tag) {
-  __hip_atomic_store(p, ((row_word)tag << 32) | __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ row_word peek_word(const row_word *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
 // Whether some wait of this wave has run out of polls: then it asks for nothing any more, and what it hands on it hands
 // on, so that the others need not run out as well.  Nothing is read or written where it would not be otherwise.
 struct Patience {
@@ -227,7 +191,7 @@ __device__ __forceinline__ void put_row(const OneRow &a, char *lds, int t, const
     }
   }
   if (norm) {
-    ss = total_last(ss);
+    ss = wave_total_last(ss);
     if ((t & 63) == 63) ((float *)(lds + a.lds_misc))[t >> 6] = ss;
   }
 }
@@ -247,14 +211,8 @@ __device__ __forceinline__ void gather_row(const OneRow &a, char *lds, int t, Pa
 
 }  // namespace
 
-// The arguments and the thread's number, made anew where they are used: kept over the loop over the layers they and what
-// follows from them do not fit the registers.
-__device__ __forceinline__ const OneRow &fresh_args() {
-  typedef const __attribute__((address_space(4))) OneRow *Args;
-  Args p = (Args)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(p));
-  return *(const OneRow *)p;
-}
+__device__ __forceinline__ const OneRow &fresh_args() { return kernel_args<OneRow>(); }
+// the thread's number, made anew too
 __device__ __forceinline__ int fresh_aux() {
   int t = threadIdx.x - 64 * ROW_STREAM_WAVES;
   asm volatile("" : "+v"(t));
@@ -344,7 +302,7 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
           s1 += fb[4] * x1.x + fb[5] * x1.y + fb[6] * x1.z + fb[7] * x1.w;
           ++w.u;
           if (++w.seg == w.segs || w.u == w.end) {   // the wave's part of a pair is complete
-            const float2 t = make_float2(total_last(s0), total_last(s1));
+            const float2 t = make_float2(wave_total_last(s0), wave_total_last(s1));
             const unsigned to = part_at + (unsigned)(((set * a.pairs + (w.pair - first)) * ROW_STREAM_WAVES + wave) * 8);
             if (lane == 63) asm volatile("ds_write_b64 %0, %1" ::"v"(to), "v"(t) : "memory");
             s0 = s1 = 0.f;
@@ -558,7 +516,7 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
 #pragma unroll
           for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int e = 0; e < 2; ++e) s[j][e] = total16(s[j][e]);
+            for (int e = 0; e < 2; ++e) s[j][e] = row16_total(s[j][e]);
           if (ch == 0)
 #pragma unroll
             for (int j = 0; j < 4; ++j)

@@ -14,6 +14,7 @@
 // The launch is cooperative, so that all workgroups are resident before any waits; every wait is bounded as well.
 #pragma once
 #include "device_common.h"
+#include "handover.h"
 #include "sampling.h"
 #include "sched.h"
 

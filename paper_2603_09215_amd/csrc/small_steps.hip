@@ -5,15 +5,8 @@
 
 namespace spark {
 
-// The arguments, read again where they are used: kept over the whole loop they and what follows from them fill the
-// scalar registers several times over, and the vector registers behind them (190 spilled).
-__device__ __forceinline__ const SmallSteps &fresh_args() {
-  typedef const __attribute__((address_space(4))) SmallSteps *Args;
-  Args p = (Args)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(p));
-  return *(const SmallSteps *)p;
-}
-// ... and so for the thread's number
+__device__ __forceinline__ const SmallSteps &fresh_args() { return kernel_args<SmallSteps>(); }
+// the thread's number, made anew too
 __device__ __forceinline__ int fresh_tid() {
   int t = threadIdx.x;
   asm volatile("" : "+v"(t));
@@ -35,12 +28,6 @@ struct SmallShared {
 };
 
 // ------------------------------------------------------------------ words handed over
-
-// A value and the number of its phase in one 64-bit word.  Who needs it asks until the number is there.
-__device__ __forceinline__ void put_word(u64 *p, float v, unsigned tag) {
-  __hip_atomic_store(p, ((u64)tag << 32) | __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ u64 peek_word(const u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // The last tag that was waited for, and whether some wait of this wave has run out of polls: then it asks for nothing any
 // more, and what it hands on it hands on, so that the others need not run out as well
@@ -85,21 +72,6 @@ __device__ __forceinline__ u64 take_key(SmallLine &line, const u64 *p, int step)
   return ok && k >> 32 ? (k & 0xffffffff00000000ull) | (u64)(0xffffffffu - (0xffffu - ((unsigned)k & 0xffffu))) : 0ull;
 }
 
-// sum over the wave, in its last lane
-__device__ __forceinline__ float wave_total_last(float v) {
-#define SPARK_DPP(ctrl, rows) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, rows, 0xf, false))
-  v += SPARK_DPP(0x111, 0xf);   // row_shr 1, 2, 4, 8: the last lane of a row of 16 has the row's sum
-  v += SPARK_DPP(0x112, 0xf);
-  v += SPARK_DPP(0x114, 0xf);
-  v += SPARK_DPP(0x118, 0xf);
-  v += SPARK_DPP(0x142, 0xa);   // row_bcast 15 into rows 1 and 3, row_bcast 31 into rows 2 and 3
-  v += SPARK_DPP(0x143, 0xc);
-#undef SPARK_DPP
-  return v;
-}
-__device__ __forceinline__ float wave_total(float v) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_total_last(v)), 63));
-}
 // Totals over the wave of a[0..3] and b[0..3]: lane l of the last eight has that of b (l odd) or a of (l >> 1) & 3
 __device__ __forceinline__ float eight_totals(const float (&a)[4], const float (&b)[4], int lane) {
 #define SPARK_DPP(v, ctrl) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false))
@@ -124,28 +96,6 @@ __device__ __forceinline__ float eight_totals(const float (&a)[4], const float (
   v += __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), 0x401f));   // lane ^ 16
   v += __shfl_xor(v, 32, 64);
   return v;
-}
-// sum over each 16 lanes, in all of them
-__device__ __forceinline__ float row16_total(float v) {
-#define SPARK_DPP(ctrl) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false))
-  v += SPARK_DPP(0x121);   // row_ror 1, 2, 4, 8
-  v += SPARK_DPP(0x122);
-  v += SPARK_DPP(0x124);
-  v += SPARK_DPP(0x128);
-#undef SPARK_DPP
-  return v;
-}
-__device__ __forceinline__ float wave_largest(float v) {
-#define SPARK_DPP(ctrl) __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), ctrl, 0xf, 0xf, false))
-  v = fmaxf(v, SPARK_DPP(0x121));
-  v = fmaxf(v, SPARK_DPP(0x122));
-  v = fmaxf(v, SPARK_DPP(0x124));
-  v = fmaxf(v, SPARK_DPP(0x128));
-#undef SPARK_DPP
-  const int a = __float_as_int(v);
-  const float m0 = fmaxf(__int_as_float(__builtin_amdgcn_readlane(a, 0)), __int_as_float(__builtin_amdgcn_readlane(a, 16)));
-  const float m1 = fmaxf(__int_as_float(__builtin_amdgcn_readlane(a, 32)), __int_as_float(__builtin_amdgcn_readlane(a, 48)));
-  return fmaxf(m0, m1);
 }
 __device__ __forceinline__ float4 load_device_scope4(const float *p) {   // p 8-byte aligned
   const float2 a = load_device_scope2(p), b = load_device_scope2(p + 2);
