@@ -181,9 +181,9 @@ def test_two_contexts_on_two_threads(sb):
 
 
 # the call that meets a wait which runs out begins without and with pending rows; one sequence, and three of which single
-# ones run full depth now and then
-@pytest.mark.parametrize("first,n_seq", [(0, 1), (4, 1), (5, 1), (4, 3)])
-def test_waits_that_run_out(sb, first, n_seq):
+# ones run full depth now and then; calls of one step that leave the pending rows alone, or complete them
+@pytest.mark.parametrize("first,n_seq,steps", [(0, 1, 9), (4, 1, 9), (5, 1, 9), (4, 3, 9), *((k, 1, 1) for k in range(1, 7))])
+def test_waits_that_run_out(sb, first, n_seq, steps):
     """the call runs again as launches per operation, from its start: bit by bit what a context gives that has been told
     to take those for this call, and so does what follows, also for a sequence that had no part in the call"""
     shape = _shape("patience", d_model=1024, n_q_heads=16, n_kv_heads=8, d_ffn=1536)
@@ -204,7 +204,7 @@ def test_waits_that_run_out(sb, first, n_seq):
                 sp.tune("one_row", 0)
             else:
                 sp.tune("wait_polls", 1)
-            out += list(sp.decode(9, ids))
+            out += list(sp.decode(steps, ids))
             assert ("gave up" in _last_error(sp)) == (not patient)
             out += list(sp.decode(8, ids))      # launches per operation in both
             out += list(sp.decode(7, other))
@@ -217,7 +217,7 @@ def test_waits_that_run_out(sb, first, n_seq):
                 out += [np.array(sorted(st.values()))] + [x for l in range(shape.n_layers) for p in range(28, st["upper_valid"], 3) for x in sp.get_kv(s, l, p)]
         return out
 
-    say(f"one row, waits that run out after {first} steps of {n_seq}")
+    say(f"one row, waits that run out in {steps} after {first} steps of {n_seq}")
     for x, y in zip(go(False), go(True), strict=True):
         assert np.array_equal(x, y)
 
