@@ -15,18 +15,28 @@ __device__ __forceinline__ void put_word(hand_word *p, float v, unsigned tag) {
 __device__ __forceinline__ hand_word peek_word(const hand_word *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 #define HAND_DPP(v, ctrl, rows) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, rows, 0xf, false))
-// sum over the wave, in its last lane
-__device__ __forceinline__ float wave_total_last(float v) {
+// sums over the halves of the wave, in the last lane of each
+__device__ __forceinline__ float half_totals_last(float v) {
   v += HAND_DPP(v, 0x111, 0xf);   // row_shr 1, 2, 4, 8: the last lane of a row of 16 has the row's sum
   v += HAND_DPP(v, 0x112, 0xf);
   v += HAND_DPP(v, 0x114, 0xf);
   v += HAND_DPP(v, 0x118, 0xf);
-  v += HAND_DPP(v, 0x142, 0xa);   // row_bcast 15 into rows 1 and 3, row_bcast 31 into rows 2 and 3
-  v += HAND_DPP(v, 0x143, 0xc);
+  v += HAND_DPP(v, 0x142, 0xa);   // row_bcast 15 into rows 1 and 3
+  return v;
+}
+// sum over the wave, in its last lane
+__device__ __forceinline__ float wave_total_last(float v) {
+  v = half_totals_last(v);
+  v += HAND_DPP(v, 0x143, 0xc);   // row_bcast 31 into rows 2 and 3
   return v;
 }
 __device__ __forceinline__ float wave_total(float v) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_total_last(v)), 63));
+}
+// ... the last addition in 64 bits
+__device__ __forceinline__ double wave_total64(float v) {
+  const int h = __float_as_int(half_totals_last(v));
+  return (double)__int_as_float(__builtin_amdgcn_readlane(h, 31)) + (double)__int_as_float(__builtin_amdgcn_readlane(h, 63));
 }
 // sum over each 16 lanes, in all of them
 __device__ __forceinline__ float row16_total(float v) {
