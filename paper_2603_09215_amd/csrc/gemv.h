@@ -23,8 +23,8 @@ template <int VEC> __device__ __forceinline__ int lds_pos(int k) {
   return k;
 }
 
-// The last 512-element block of a staged row may be partial; lanes whose weights were masked to
-// zero still multiply what lies there, so it must be finite: fill it with zeros.
+// The last 512-element block of a staged row may be partial; lanes beyond its end multiply what lies there by other
+// weights of the row (issue_stage), so fill it with zeros.
 template <int VEC, int NT> __device__ __forceinline__ void zero_tail(float *xrow, int klen) {
   const int end = (klen + 511) & ~511;
   for (int k = klen + threadIdx.x * 4; k < end; k += NT * 4)
@@ -542,26 +542,6 @@ template <int U> struct WStage {
   uint4 a[U], b[U];
 };
 
-// Issue the loads of elements [kb, kb + U*WSTEP) of a chunk of length klen (lanes beyond klen and
-// waves without a task get zeros).
-template <typename WT, int U>
-__device__ __forceinline__ void issue_stage(WStage<U> &s, const WT *p0, const WT *p1, int kb, int klen,
-                                            int lane, bool valid) {
-  constexpr int VEC = Elem<WT>::VEC;
-  constexpr int WSTEP = 64 * VEC;
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int k = kb + u * WSTEP + lane * VEC;
-    if (valid && k < klen) {
-      s.a[u] = load_weights16(p0 + k);
-      s.b[u] = load_weights16(p1 + k);
-    } else {
-      s.a[u] = make_uint4(0, 0, 0, 0);
-      s.b[u] = make_uint4(0, 0, 0, 0);
-    }
-  }
-}
-
 template <typename WT, int MT>
 __device__ __forceinline__ void fma_block(const uint4 &a, const uint4 &b, const float *xs, int kc,
                                           int kb, int lane, float *acc0, float *acc1) {
@@ -583,14 +563,14 @@ __device__ __forceinline__ void fma_block(const uint4 &a, const uint4 &b, const 
   }
 }
 
-// Same loads without a branch around them: a lane beyond klen, or a wave without a task, reads the
-// first 16 bytes of the row instead (a cache hit) and its products meet zeros in the staged
-// activations (or are discarded).  With every load issued unconditionally the compiler knows how
-// many are outstanding at each point and waits for exactly the stage it is about to use; a
+// Issue the loads of elements [kb, kb + U*WSTEP) of a chunk of length klen, without a branch around them: a lane
+// beyond klen, or a wave without a task, reads the first 16 bytes of the row instead (a cache hit) and its
+// products meet zeros in the staged activations (or are discarded).  With every load issued unconditionally the
+// compiler knows how many are outstanding at each point and waits for exactly the stage it is about to use; a
 // conditional load makes it wait for all of them, which empties the pipeline at every stage.
 template <typename WT, int U>
-__device__ __forceinline__ void issue_stage_nb(WStage<U> &s, const WT *p0, const WT *p1, int kb, int klen,
-                                               int lane, bool valid) {
+__device__ __forceinline__ void issue_stage(WStage<U> &s, const WT *p0, const WT *p1, int kb, int klen,
+                                            int lane, bool valid) {
   constexpr int VEC = Elem<WT>::VEC;
   constexpr int WSTEP = 64 * VEC;
 #pragma unroll
@@ -645,7 +625,7 @@ gemv_rows_k(Pro pro, Epi epi, const RowDesc *__restrict__ rows, int m_rows, int 
   epi.weight_rows(ivalid ? itask : 0, ir0, ir1);
   auto issue = [&](WStage<U> &s) {
     const int k0 = ichunk * kc;
-    issue_stage_nb<WT>(s, ir0 + k0, ir1 + k0, ig * GSTEP, min(kc, n_in - k0), lane, ivalid);
+    issue_stage<WT>(s, ir0 + k0, ir1 + k0, ig * GSTEP, min(kc, n_in - k0), lane, ivalid);
     if (++ig == n_groups) {
       ig = 0;
       if (++ichunk == n_chunks) {

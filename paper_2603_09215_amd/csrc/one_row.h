@@ -34,6 +34,7 @@ constexpr int ROW_HD = 128;             // head_dim
 constexpr int ROW_MAX_GROUP = 16;       // query heads per KV head
 constexpr int ROW_SLICE = 64;           // tokens of an attention slice, at most
 constexpr int ROW_MAX_D = 8 * ROW_AUX;  // width of a row that is gathered at once
+static_assert(2 * (ROW_MAX_D / ROW_HD) <= ROW_WGS, "two workgroups merge a head");
 // Some seconds; then the launch gives up and the call goes on as launches per operation.  Other streams' and processes'
 // kernels may hold compute units that its last workgroups wait for.
 constexpr int ROW_MAX_POLLS = 1 << 22;

@@ -576,9 +576,9 @@ __global__ void __launch_bounds__(ROW_THREADS) one_row_k(OneRow) {
         else if (sl.heads <= 8) weigh(std::integral_constant<int, 2>());
         else weigh(std::integral_constant<int, ROW_MAX_GROUP / 4>());
       }
-      // the slices of a head meet at some of the last workgroups, a part of its dimensions at each
-      const int deal = a.nq * 2 <= ROW_WGS, id = ROW_WGS - 1 - wg, head = id >> deal, width = ROW_HD >> deal, groups = ROW_AUX / width;
-      const int d0 = (id & ((1 << deal) - 1)) * width + (t & (width - 1));
+      // the slices of a head meet at two of the last workgroups, half of its dimensions at each
+      constexpr int width = ROW_HD / 2, groups = ROW_AUX / width;
+      const int id = ROW_WGS - 1 - wg, head = id >> 1, d0 = (id & 1) * width + (t & (width - 1));
       if (head < a.nq) {
         float M = -INFINITY, L = 0.f, O = 0.f;
         const row_word *p = a.part + (size_t)head * sl.count * (ROW_HD + 2);

@@ -1,4 +1,4 @@
-// When the layers of a pass of one row are better in one launch (one_row.h); plain arithmetic, no device code.
+// When the layers of a pass of one row are better in one launch (one_row.h), and their numbers; plain arithmetic, no device code.
 #pragma once
 #include <algorithm>
 #include <cstddef>
@@ -22,5 +22,9 @@ inline bool one_row_pays(size_t layer_bytes, int layers) {
   const double gain = std::min(7.0, ((double)layer_bytes * 1e-6 - 140.0) * 0.1);   // us a layer, low
   return layer_bytes >= ROW_LAYER_BYTES && layers * gain >= 28.0;                  // the launch, high
 }
+
+// Layers are numbered from 1 over all launches of a context; whether the numbers end before those of the next launch, so that
+// they begin again (on cleared words: an old one would be taken for a new one)
+inline bool row_numbers_run_out(unsigned last, unsigned layers) { return last + layers < last; }
 
 }  // namespace spark

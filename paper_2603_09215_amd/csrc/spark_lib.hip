@@ -1053,7 +1053,7 @@ OneRow one_row_shape(const spark_config &g) {
 bool shape_allows_one_row(const spark_config &g) {
   const int qw = g.n_q_heads * g.head_dim;
   OneRow a = one_row_shape(g);
-  return g.dtype == SPARK_DTYPE_BF16 && g.head_dim == ROW_HD && g.n_q_heads / g.n_kv_heads <= ROW_MAX_GROUP && g.n_q_heads <= ROW_WGS &&
+  return g.dtype == SPARK_DTYPE_BF16 && g.head_dim == ROW_HD && g.n_q_heads / g.n_kv_heads <= ROW_MAX_GROUP &&
          g.d_model % 8 == 0 && g.d_ffn % 8 == 0 && g.d_model <= ROW_MAX_D && qw <= ROW_MAX_D && g.d_model >= 2 * ROW_WGS &&
          (g.n_q_heads + 2 * g.n_kv_heads) * (ROW_HD / 2) >= ROW_WGS && g.d_ffn >= ROW_PARTS * ROW_WGS &&
          one_row_lds(a) > 0 && sizeof(row_word) * row_words(g).end <= MFMA_PARTIAL_BYTES;
@@ -1078,7 +1078,7 @@ bool enqueue_one_row(spark_ctx *c, int l0, int l1, const RowDesc *row) {
   const RowWords w = row_words(g);
   row_word *words = at<row_word>(c, c->lo.mfma_part);
   const unsigned layers = (unsigned)(l1 - l0);
-  if (!c->row_words_clean || c->row_tag + layers < c->row_tag) {   // (or the numbers start again)
+  if (!c->row_words_clean || row_numbers_run_out(c->row_tag, layers)) {
     clear_words_k<<<256, 256, 0, c->stream>>>(words, w.end);
     c->row_words_clean = true;
     c->row_tag = 0;

@@ -34,3 +34,21 @@ def test_rule_takes_the_launch_only_where_it_was_measured_to_gain(tmp_path):
         assert not t or gain > 0, (mb, layers, gain)
         # from 189 MB and four layers on, what gains more than 2 % of a step (0.31 us a MB and layer) is not passed over
         assert t or mb < 189 or layers < 4 or gain <= 0.02 * 0.31 * mb * layers, (mb, layers, gain)
+
+
+def test_numbers_begin_again_before_they_run_out(tmp_path):
+    src, exe = tmp_path / "numbers.cpp", tmp_path / "numbers"
+    src.write_text("""
+#include <cstdio>
+#include "row_rule.h"
+int main() {
+  unsigned last, layers;
+  while (scanf("%u %u", &last, &layers) == 2) printf("%d\\n", (int)spark::row_numbers_run_out(last, layers));
+}
+""")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", f"-I{CSRC}", "-o", str(exe), str(src)], check=True)
+    points = [(last, layers) for layers in (1, 4, 28) for last in (0, 1, 2 ** 31 - 1, *(2 ** 32 - 1 - layers + k for k in (-1, 0, 1)), 2 ** 32 - 1)
+              if last < 2 ** 32]
+    out = subprocess.run([str(exe)], input="".join(f"{a} {b}\n" for a, b in points), capture_output=True, text=True, check=True)
+    for (last, layers), took in zip(points, out.stdout.split(), strict=True):
+        assert (took == "1") == (last + layers > 2 ** 32 - 1), (last, layers)
