@@ -275,7 +275,9 @@ def main() -> int:
     wg = sp.dev_weights["wg"]
     same_size = wg.reshape(-1)[:gateup_bytes // wg.element_size()]
     ceiling_same, _ = sp.measure_read(same_size, reps=16, nontemporal=True)
-    roofline = {"bound": "hbm", "kernel": "gemv_rows_k<gate/up + SwiGLU>", "achieved": round(achieved, 1),
+    roofline = {"bound": "hbm", "kernel": "gemv_rows_k<gate/up + SwiGLU>",
+                "timed_steps": "the layers of a pass of one row in one launch, one_row_k, where the library takes it: see whole_step and "
+                               "step_classes; this kernel runs in the other passes and in bracketed steps", "achieved": round(achieved, 1),
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": measured_traffic(shape),
                 "traffic_source": "profiles/ (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs), not this run",

@@ -26,9 +26,11 @@ constexpr int ROW_DEPTH = 4, ROW_SPARE = 2, ROW_PARKED = 8;
 // Pieces that the MLP's activations are handed over in.  With four, a piece's gathering held up the stream of the next
 // (seven layers of the Step shape, 12 steps: 7 695 us against 7 420), with two the last piece's stood alone (8 085).
 constexpr int ROW_PARTS = 3;
-constexpr int ROW_ACT_WORDS = 13;       // activations that a thread gathers at a time
+constexpr int ROW_ACT_WORDS = 13;       // activations that a thread gathers at a time (a piece of 6400 in one trip; a narrower one asks for its last again)
 // Sleeps (units of 64 cycles) before the first question for a row that has just been handed over, and for a piece of the
 // MLP's activations: asked for all the time, the words' own traffic holds up what they wait for (90.2 against 88.9 us a layer).
+// The same at every width, measured at the Step shape: 9 us a layer, which narrow layers, whose phases are shorter, lose (the rule of
+// row_rule.h was measured with them).
 constexpr int ROW_NAP = 40, ROW_PIECE_NAP = 127;
 constexpr int ROW_HD = 128;             // head_dim
 constexpr int ROW_MAX_GROUP = 16;       // query heads per KV head
